@@ -1560,6 +1560,13 @@ int inshr_delta_bound(const inshr_codes *prev, const inshr_codes *cur, uint64_t 
     return INSHR_OK;
 }
 
+static u32 call_chunk_tiles(const inshr_ctx *c, const inshr_codes *prev, uint32_t n_tensors)
+{
+    u64 tiles = 0; // (sizes are checked by the caller)
+    for (uint32_t t = 0; t < n_tensors; t++) tiles += (prev[t].n + DELTA_TILE - 1) / DELTA_TILE;
+    return delta_chunk_tiles(tiles, c->n_cu);
+}
+
 int inshr_delta(inshr_ctx *c, const inshr_codes *prev, const uint32_t *const *prev_perm,
                 const inshr_codes *cur, inshr_delta_out *out, uint32_t n_tensors)
 {
@@ -1567,6 +1574,7 @@ int inshr_delta(inshr_ctx *c, const inshr_codes *prev, const uint32_t *const *pr
     std::vector<DDesc> dd(n_tensors);
     std::vector<u32> chunk_tensor;
     u64 dtile = 0, chunk = 0;
+    const u32 ctiles = call_chunk_tiles(c, prev, n_tensors);
     bool any_scatter = false, any_gather = false, any_perm = false;
     for (uint32_t t = 0; t < n_tensors; t++) {
         uint64_t words = 0;
@@ -1600,7 +1608,8 @@ int inshr_delta(inshr_ctx *c, const inshr_codes *prev, const uint32_t *const *pr
         d.dtile0 = dtile;
         d.chunk0 = chunk;
         const u64 nt = (n + DELTA_TILE - 1) / DELTA_TILE;
-        d.n_chunks = (nt + DELTA_CHUNK - 1) / DELTA_CHUNK;
+        d.n_chunks = (nt + ctiles - 1) / ctiles;
+        d.ctiles = ctiles;
         for (u64 k = 0; k < d.n_chunks; k++) chunk_tensor.push_back(t);
         dtile += nt;
         chunk += d.n_chunks;
@@ -1649,6 +1658,15 @@ int inshr_delta_static(inshr_ctx *c, const inshr_codes *prev, const inshr_codes 
     memset(&a, 0, sizeof(a));
     a.n_tensors = n_tensors;
     u64 dtile = 0, chunk = 0;
+    u32 ctiles = call_chunk_tiles(c, prev, n_tensors);
+    { // (the static scratch holds a fixed number of chunks: longer ones where they would not fit)
+        auto chunks_with = [&](u32 ct) {
+            u64 k = 0;
+            for (uint32_t t = 0; t < n_tensors; t++) k += ((prev[t].n + DELTA_TILE - 1) / DELTA_TILE + ct - 1) / ct;
+            return k;
+        };
+        while (ctiles < (u32)DELTA_CHUNK && chunks_with(ctiles) > (u64)DELTA_STATIC_MAX_CHUNKS) ctiles++;
+    }
     bool any_scatter = false, any_perm = false;
     for (uint32_t t = 0; t < n_tensors; t++) {
         uint64_t words = 0;
@@ -1679,7 +1697,8 @@ int inshr_delta_static(inshr_ctx *c, const inshr_codes *prev, const inshr_codes 
         d.dtile0 = dtile;
         d.chunk0 = chunk;
         const u64 nt = (n + DELTA_TILE - 1) / DELTA_TILE;
-        d.n_chunks = (nt + DELTA_CHUNK - 1) / DELTA_CHUNK;
+        d.n_chunks = (nt + ctiles - 1) / ctiles;
+        d.ctiles = ctiles;
         dtile += nt;
         chunk += d.n_chunks;
         if (d.perm)
@@ -1765,6 +1784,7 @@ int inshr_reconstruct(inshr_ctx *c, const inshr_codes *prev, const inshr_delta_o
     std::vector<XDesc> xd(n_tensors);
     std::vector<u32> chunk_tensor;
     u64 dtile = 0, chunk = 0;
+    const u32 ctiles = call_chunk_tiles(c, prev, n_tensors);
     for (uint32_t t = 0; t < n_tensors; t++) {
         const uint64_t n = prev[t].n;
         inshr_codes cur_codes;
@@ -1793,7 +1813,8 @@ int inshr_reconstruct(inshr_ctx *c, const inshr_codes *prev, const inshr_delta_o
         d.dtile0 = dtile;
         d.chunk0 = chunk;
         const u64 nt = (n + DELTA_TILE - 1) / DELTA_TILE;
-        d.n_chunks = (nt + DELTA_CHUNK - 1) / DELTA_CHUNK;
+        d.n_chunks = (nt + ctiles - 1) / ctiles;
+        d.ctiles = ctiles;
         for (u64 k = 0; k < d.n_chunks; k++) chunk_tensor.push_back(t);
         dtile += nt;
         chunk += d.n_chunks;

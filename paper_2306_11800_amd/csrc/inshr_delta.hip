@@ -2,27 +2,27 @@
 // the stable order of the previous checkpoint's symbol (Algorithm 5) and bit-packed.
 //
 // The regrouping is a stable partition into at most 258 groups:
-//   k_dhist     per chunk (64 tiles of 12288 elements): population of every previous symbol
-//   k_dgroups   per tensor: group offsets and the start of every chunk inside every group
+//   k_dhist     per chunk (1 .. 64 tiles of 12288 elements): population of every previous symbol
+//   k_dgroups   per tensor: group offsets and the start of every chunk inside every group; clears
+//               the stream words that k_dscatter ORs into
 //   k_dscatter  one workgroup of 12 waves per chunk walks its tiles in order.  Per tile each wave
 //               owns 1024 consecutive elements, 64 consecutive elements per step; a returning LDS
 //               add per element (or lane bits OR-ed into the symbol's LDS slot) gives the stable
 //               rank.  The tile's deltas are OR-ed into an LDS image of the output words of every
 //               group's run, and one thread per word stores it (first / last word of a chunk's run
-//               are OR-ed into words that k_dzero cleared).
+//               are OR-ed into words that k_dgroups cleared).
 #include "inshr_launch.h"
 
 namespace inshr {
 
 constexpr int DTILE = DELTA_TILE;   // elements per tile = 1024 per wave of the scatter workgroup
-constexpr int DCHUNK = DELTA_CHUNK; // tiles per chunk
 constexpr int SS = DELTA_SS;        // symbol stride (258 symbols at most)
 constexpr int NWAVE = DTILE / 1024; // waves of a scatter workgroup (two workgroups share a CU)
 constexpr int DBLOCK = NWAVE * 64;
 constexpr int TWORDS = DTILE * 9 / 64;            // most packed u64 words of one tile
-constexpr u64 CHUNK_ELEMS = (u64)DTILE * DCHUNK;  // 786432, a multiple of 16384
-constexpr int HTILE = 16384;                      // step of the counting and gathering kernels
-static_assert(CHUNK_ELEMS % HTILE == 0, "chunks are whole counting steps");
+constexpr int HTILE = 16384;                      // step of the gathering kernel
+constexpr int HBLOCK = 256;                       // threads of a counting workgroup
+static_assert(DTILE % 64 == 0, "a chunk starts at a whole word of any symbol width");
 
 __device__ __forceinline__ u32 lds_extract(const u32 *W, u32 idx, u32 w)
 {
@@ -61,7 +61,7 @@ __device__ __forceinline__ void count_symbols(const DDesc &d, u64 c0, u64 c1, u3
     const GLOBAL_AS unsigned long long *src = gptr(d.prev);
     const u64 total_words = (d.n * W + 63u) >> 6;
     const u32 n_runs = (u32)((c1 - c0 + 63u) >> 6);
-    for (u32 u = tid; u < n_runs; u += BLOCK) {
+    for (u32 u = tid; u < n_runs; u += HBLOCK) {
         const u64 e = c0 + 64ull * u;
         const u32 nvalid = (c1 - e < 64ull) ? (u32)(c1 - e) : 64u;
         const u64 w0 = (e >> 6) * W; // e is a multiple of 64
@@ -80,20 +80,23 @@ __device__ __forceinline__ void count_symbols(const DDesc &d, u64 c0, u64 c1, u3
     }
 }
 
-// population of every previous symbol in one chunk
-__global__ __launch_bounds__(BLOCK) void k_dhist(const DDesc *__restrict__ dd,
-                                                 const u32 *__restrict__ chunk_tensor,
-                                                 u32 *__restrict__ chunk_tot)
+// Population of every previous symbol in one chunk.  Workgroups of 256 threads: the rows of a
+// workgroup take 17 KB of LDS, eight of them fill a CU, and a chunk of one tile (192 runs of 64
+// symbols) still occupies most of its threads.
+__global__ __launch_bounds__(HBLOCK) void k_dhist(const DDesc *__restrict__ dd,
+                                                  const u32 *__restrict__ chunk_tensor,
+                                                  u32 *__restrict__ chunk_tot)
 {
-    __shared__ u32 hw[BLOCK / 64][DH_COPIES * SS];
+    __shared__ u32 hw[HBLOCK / 64][DH_COPIES * SS];
     __shared__ u32 s_nonzero;
     const u64 chunk = blockIdx.x;
     const DDesc d = dd[__builtin_amdgcn_readfirstlane(chunk_tensor[chunk])];
     const u32 tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const u32 S = d.Kp + 2u;
-    const u64 c0 = (chunk - d.chunk0) * CHUNK_ELEMS;
-    const u64 c1 = (c0 + CHUNK_ELEMS < d.n) ? c0 + CHUNK_ELEMS : d.n;
-    for (u32 k = tid; k < (BLOCK / 64) * DH_COPIES * SS; k += BLOCK) (&hw[0][0])[k] = 0u;
+    const u64 c_elems = (u64)d.ctiles * DTILE;
+    const u64 c0 = (chunk - d.chunk0) * c_elems;
+    const u64 c1 = (c0 + c_elems < d.n) ? c0 + c_elems : d.n;
+    for (u32 k = tid; k < (HBLOCK / 64) * DH_COPIES * SS; k += HBLOCK) (&hw[0][0])[k] = 0u;
     if (tid == 0u) s_nonzero = 0u;
     __syncthreads();
     switch (d.wp) {
@@ -107,41 +110,81 @@ __global__ __launch_bounds__(BLOCK) void k_dhist(const DDesc *__restrict__ dd,
     default: count_symbols<9>(d, c0, c1, S, hw[wave]); break;
     }
     __syncthreads();
-    u32 mine = 0u; // population of symbol tid (symbols above S - 1 are in entry S)
-    if (tid >= 1u && tid <= S) {
-        for (int wv = 0; wv < BLOCK / 64; wv++)
-            for (int cp = 0; cp < DH_COPIES; cp++) mine += hw[wv][cp * SS + tid];
-        if (mine) atomicAdd(&s_nonzero, mine);
+    const u32 copies = d.wp <= 7u ? (u32)DH_COPIES : 1u;
+    u32 mine[2] = {0u, 0u}, sum = 0u; // populations of symbols tid, tid + 256 (those above S - 1 are in entry S)
+    for (u32 h = 0; h < 2u; h++) {
+        const u32 sy = tid + h * HBLOCK;
+        if (sy < 1u || sy > S) continue;
+        for (u32 wv = 0; wv < HBLOCK / 64u; wv++)
+            for (u32 cp = 0; cp < copies; cp++) mine[h] += hw[wv][cp * SS + sy];
+        sum += mine[h];
     }
+    sum = wave_sum(sum);
+    if ((tid & 63u) == 0u && sum) atomicAdd(&s_nonzero, sum);
     __syncthreads();
-    if (tid == 0u) mine = (u32)(c1 - c0) - s_nonzero;
-    if (tid < SS) chunk_tot[chunk * SS + tid] = tid < S ? mine : 0u;
+    if (tid == 0u) mine[0] = (u32)(c1 - c0) - s_nonzero;
+    for (u32 h = 0; h < 2u; h++) {
+        const u32 sy = tid + h * HBLOCK;
+        if (sy < (u32)SS) chunk_tot[chunk * SS + sy] = sy < S ? mine[h] : 0u;
+    }
 }
 
-// per tensor: group offsets; chunk_tot becomes the start of each chunk inside its group
-__global__ __launch_bounds__(SS) void k_dgroups(const DDesc *__restrict__ dd,
-                                                u32 *__restrict__ chunk_tot)
+// Per tensor: group offsets; chunk_tot becomes the start of each chunk inside its group.  With CLEAR
+// also the stream words that k_dscatter ORs into are cleared: the first word of every (chunk, group)
+// run, which is also where the run before it ends, and the word where the stream ends.
+// The chunks are taken eight at a time, so that one memory latency covers eight of them.
+template <bool CLEAR>
+__global__ __launch_bounds__(320) void k_dgroups(const DDesc *__restrict__ dd,
+                                                 u32 *__restrict__ chunk_tot)
 {
-    __shared__ u64 tot[SS];
+    __shared__ u64 wtot[5];
     const int t = blockIdx.x;
     const DDesc d = dd[t];
-    const u32 g = threadIdx.x;
+    const u32 g = threadIdx.x, lane = g & 63u, wave = g >> 6;
     const u32 S = d.Kp + 2u;
+    GLOBAL_AS u32 *ct = gptr(chunk_tot) + d.chunk0 * SS + g;
+    const u32 nc = (u32)d.n_chunks;
     u64 run = 0;
-    for (u64 c = d.chunk0; c < d.chunk0 + d.n_chunks; c++) {
-        u32 v = chunk_tot[c * SS + g];
-        chunk_tot[c * SS + g] = (u32)run; // n < 2^32
-        run += v;
-    }
-    tot[g] = (g < S) ? run : 0ull;
-    __syncthreads();
-    if (g == 0) {
-        u64 acc = 0;
-        for (u32 k = 0; k < S; k++) {
-            gptr(d.group_off)[k] = acc;
-            acc += tot[k];
+    if (g < (u32)SS) {
+        for (u32 c = 0; c < nc; c += 8u) {
+            u32 v[8];
+#pragma unroll
+            for (u32 j = 0; j < 8u; j++) v[j] = c + j < nc ? ct[(c + j) * SS] : 0u;
+#pragma unroll
+            for (u32 j = 0; j < 8u; j++) {
+                if (c + j < nc) ct[(c + j) * SS] = (u32)run; // n < 2^32
+                run += v[j];
+            }
         }
-        gptr(d.group_off)[S] = acc;
+    }
+    u64 inc = g < S ? run : 0ull; // inclusive scan over the groups
+    const u64 mine = inc;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const u64 y = __shfl_up(inc, o);
+        if ((int)lane >= o) inc += y;
+    }
+    if (lane == 63u) wtot[wave] = inc;
+    __syncthreads();
+    u64 off = inc - mine; // (u64: the offsets of a tensor below 2^32 elements, as they are stored)
+    for (u32 w = 0; w < wave; w++) off += wtot[w];
+    if (g <= S) gptr(d.group_off)[g] = off; // (entry S: everything)
+    if (!CLEAR || d.prev_perm) return;
+    GLOBAL_AS unsigned long long *out = gptr(d.out);
+    if (g == S) {
+        const u64 word = (d.n * d.wB) >> 6; // where the stream ends
+        if (word < d.out_words) out[word] = 0ull;
+    }
+    if (g >= S) return;
+    for (u32 c = 0; c < nc; c += 8u) {
+        u32 v[8];
+#pragma unroll
+        for (u32 j = 0; j < 8u; j++) v[j] = c + j < nc ? ct[(c + j) * SS] : 0u; // (this thread's own stores)
+#pragma unroll
+        for (u32 j = 0; j < 8u; j++) {
+            const u64 word = ((off + v[j]) * d.wB) >> 6;
+            if (c + j < nc && word < d.out_words) out[word] = 0ull;
+        }
     }
 }
 
@@ -356,7 +399,7 @@ __device__ __forceinline__ void flush_and_commit(ScatterShared &sh, const unsign
 // current 64-byte line in LDS until the line is complete; complete lines are stored whole.  Only the
 // ends of a (chunk, group) run are different: its first partial line is stored word by word, its
 // first word, when shared with the run before, and its last partial word are OR-ed into words that
-// k_dzero cleared.
+// k_dgroups cleared.
 template <bool PERM, bool ORDERED>
 __global__ __launch_bounds__(DBLOCK, 6) void k_dscatter(const DDesc *__restrict__ dd,
                                                      const u32 *__restrict__ chunk_tensor,
@@ -385,8 +428,8 @@ __global__ __launch_bounds__(DBLOCK, 6) void k_dscatter(const DDesc *__restrict_
     const u32 S = d.Kp + 2u, Bm = d.B, wB = d.wB, wp = d.wp, wc = d.wc;
     const u32 srow = S + 1u; // row stride of the (wave, symbol) tables
     const u64 n_tiles = (d.n + DTILE - 1) / DTILE;
-    const u64 lt0 = (chunk - d.chunk0) * DCHUNK;
-    const u64 lt1 = (lt0 + DCHUNK < n_tiles) ? lt0 + DCHUNK : n_tiles;
+    const u64 lt0 = (chunk - d.chunk0) * d.ctiles;
+    const u64 lt1 = (lt0 + d.ctiles < n_tiles) ? lt0 + d.ctiles : n_tiles;
     GLOBAL_AS unsigned long long *out = gptr(d.out);
     if (tid < S) {
         const u32 g0 = (u32)gptr(d.group_off)[tid] + chunk_tot[chunk * SS + tid];
@@ -603,8 +646,9 @@ __global__ __launch_bounds__(BLOCK) void k_dgather(const DDesc *__restrict__ dd,
     const u32 wB = d.wB, Bm = d.B;
     const u32 smax[2] = {d.Kp + 1u, Bm - 1u}; // largest symbol of either stream that is taken as it is
     bool bad_index = false;
-    const u64 c0 = (chunk - d.chunk0) * CHUNK_ELEMS;
-    const u64 c1 = (c0 + CHUNK_ELEMS < d.n) ? c0 + CHUNK_ELEMS : d.n;
+    const u64 c_elems = (u64)d.ctiles * DTILE;
+    const u64 c0 = (chunk - d.chunk0) * c_elems;
+    const u64 c1 = (c0 + c_elems < d.n) ? c0 + c_elems : d.n;
     for (u64 r0 = c0; r0 < c1; r0 += HTILE) {
         const u32 cnt = (c1 - r0 < (u64)HTILE) ? (u32)(c1 - r0) : (u32)HTILE;
         __syncthreads();
@@ -647,27 +691,6 @@ __global__ __launch_bounds__(BLOCK) void k_dgather(const DDesc *__restrict__ dd,
     if (bad_index) atomicOr(flags, DF_PERM);
 }
 
-// clears the stream words that k_dscatter ORs into: the first word of every (chunk, group) run,
-// which is also where the run before it ends, and the word where the stream ends
-__global__ __launch_bounds__(SS) void k_dzero(const DDesc *__restrict__ dd,
-                                              const u32 *__restrict__ chunk_tensor,
-                                              const u32 *__restrict__ chunk_tot)
-{
-    const u64 chunk = blockIdx.x;
-    const DDesc d = dd[__builtin_amdgcn_readfirstlane(chunk_tensor[chunk])];
-    if (d.prev_perm) return;
-    const u32 g = threadIdx.x, S = d.Kp + 2u;
-    u64 pos;
-    if (g < S)
-        pos = gptr(d.group_off)[g] + chunk_tot[chunk * SS + g];
-    else if (g == S && chunk == d.chunk0)
-        pos = d.n;
-    else
-        return;
-    const u64 word = (pos * d.wB) >> 6;
-    if (word < d.out_words) gptr(d.out)[word] = 0ull;
-}
-
 // Restore side (Algorithm 6): s_cur[i] = (s_prev[i] - e[r]) mod B, where r is the position of element
 // i in the stable order of s_prev.  Same chunk and tile walk as k_dscatter, with the data flowing the
 // other way: sweep 1 ranks the elements of a tile; the stream words of every group's run of the tile
@@ -706,8 +729,8 @@ __global__ __launch_bounds__(DBLOCK, 6) void k_drestore(const DDesc *__restrict_
     const u32 S = d.Kp + 2u, Bm = d.B, wB = d.wB, wp = d.wp, wc = d.wc;
     const u32 srow = S + 1u;
     const u64 n_tiles = (d.n + DTILE - 1) / DTILE;
-    const u64 lt0 = (chunk - d.chunk0) * DCHUNK;
-    const u64 lt1 = (lt0 + DCHUNK < n_tiles) ? lt0 + DCHUNK : n_tiles;
+    const u64 lt0 = (chunk - d.chunk0) * d.ctiles;
+    const u64 lt1 = (lt0 + d.ctiles < n_tiles) ? lt0 + d.ctiles : n_tiles;
     if (tid < S) sh.gb[tid] = (u32)gptr(d.group_off)[tid] + chunk_tot[chunk * SS + tid];
     if (tid < SS + 8u) sh.wstart[tid] = 0xFFFFFFFFu;
     if (tid == 0u) sh.hotkey = 0ull;
@@ -857,8 +880,8 @@ hipError_t launch_reconstruct(const DDesc *dd, const XDesc *xd, int nT, u64 n_ch
                               const u32 *chunk_tensor, u32 *chunk_tot, u32 *flags, bool lds_ordered,
                               hipStream_t s)
 {
-    PROF("k_dhist", s, k_dhist<<<(unsigned)n_chunks, BLOCK, 0, s>>>(dd, chunk_tensor, chunk_tot));
-    PROF("k_dgroups", s, k_dgroups<<<nT, SS, 0, s>>>(dd, chunk_tot));
+    PROF("k_dhist", s, k_dhist<<<(unsigned)n_chunks, HBLOCK, 0, s>>>(dd, chunk_tensor, chunk_tot));
+    PROF("k_dgroups", s, k_dgroups<false><<<nT, 320, 0, s>>>(dd, chunk_tot));
     PROF("k_dcheck_groups", s, k_dcheck_groups<<<nT, SS, 0, s>>>(dd, xd, flags));
     if (lds_ordered)
         PROF("k_drestore", s, k_drestore<true><<<(unsigned)n_chunks, DBLOCK, 0, s>>>(dd, xd, chunk_tensor, chunk_tot, flags));
@@ -974,10 +997,8 @@ hipError_t launch_delta(const DDesc *dd, int nT, u64 n_dtiles, u64 n_chunks,
                         const u32 *chunk_tensor, u32 *chunk_tot, u32 *flags, bool any_scatter,
                         bool any_perm, bool any_gather, bool lds_ordered, hipStream_t s)
 {
-    PROF("k_dhist", s, k_dhist<<<(unsigned)n_chunks, BLOCK, 0, s>>>(dd, chunk_tensor, chunk_tot));
-    PROF("k_dgroups", s, k_dgroups<<<nT, SS, 0, s>>>(dd, chunk_tot));
-    if (any_scatter || any_perm)
-        PROF("k_dzero", s, k_dzero<<<(unsigned)n_chunks, SS, 0, s>>>(dd, chunk_tensor, chunk_tot));
+    PROF("k_dhist", s, k_dhist<<<(unsigned)n_chunks, HBLOCK, 0, s>>>(dd, chunk_tensor, chunk_tot));
+    PROF("k_dgroups", s, k_dgroups<true><<<nT, 320, 0, s>>>(dd, chunk_tot));
     if (any_scatter) {
         if (lds_ordered)
             PROF("k_dscatter", s, k_dscatter<false, true><<<(unsigned)n_chunks, DBLOCK, 0, s>>>(dd, chunk_tensor, chunk_tot, flags));

@@ -135,7 +135,8 @@ struct DDesc { // one tensor of a delta call
     const u32 *prev_perm;
     u64 n, out_words;
     u64 dtile0, chunk0, n_chunks;
-    u32 wp, wc, Kp, B, wB, pad;
+    u32 wp, wc, Kp, B, wB;
+    u32 ctiles;          // tiles of a chunk (delta_chunk_tiles)
 };
 struct RDesc { // one tensor of a dequantize call
     const unsigned long long *packed;
@@ -163,7 +164,18 @@ constexpr u32 RF_ORDER = 16u;  // ranks from returning LDS adds disagree with ra
 constexpr u32 DF_PERM = 1u;    // a given permutation holds an index outside its tensor
 constexpr u32 DF_ORDER = 2u;   // ranks from returning LDS adds disagree with ranks from ballots
 constexpr int DELTA_TILE = 12288;
-constexpr int DELTA_CHUNK = 64;
+constexpr int DELTA_CHUNK = 64; // most tiles of a chunk
+// Tiles per chunk of a delta / reconstruct call over n_tiles tiles in all.  A chunk is walked by one
+// workgroup and costs about a tile's time on top of its tiles (its groups' runs are found, opened and
+// closed), so chunks are as long as possible; but two workgroups fit a CU, and with fewer than
+// about six rounds of them the last round leaves much of the chip idle (a 1 Mi tensor in chunks of
+// 64 tiles kept two workgroups busy for 0.44 ms; one-tile chunks: 0.02 ms).
+inline u32 delta_chunk_tiles(u64 n_tiles, int n_cu)
+{
+    const u64 rounds = 6ull * 2ull * (u64)n_cu;
+    const u64 c = (n_tiles + rounds - 1) / rounds;
+    return (u32)(c < 1ull ? 1ull : c > (u64)DELTA_CHUNK ? (u64)DELTA_CHUNK : c);
+}
 constexpr int DELTA_SS = 264;
 // the delta entry point that allocates nothing: its limits, and its descriptors as kernel arguments
 constexpr int DELTA_STATIC_MAX_TENSORS = 16;
