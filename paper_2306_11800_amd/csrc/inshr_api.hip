@@ -42,7 +42,6 @@ struct inshr_ctx {
     // gather pools are sized by it; a search that finds them too small doubles it and runs again
     // (INSHR_POOL_WCAP sets the start)
     uint32_t pool_wcap = 136;
-    std::vector<char> batch_sampled;
     std::string last_err;
 
     u32 *delta_flags = nullptr; // flag word of the delta kernels (DF_*), allocated with the context
@@ -65,7 +64,8 @@ struct inshr_ctx {
     GridDesc grid{};
     std::vector<inshr_config> grid_cfgs;
     std::vector<inshr_tensor> tensors;
-    size_t ts_off = 0, scores_off = 0;
+    std::vector<u32> pos;       // device position of tensors[t]
+    size_t res_off = 0, scores_off = 0;
 };
 
 // ------------------------------------------------------------------------------------------
@@ -255,7 +255,7 @@ int build_grid(const inshr_config *grid, uint32_t n_cfg, double eps, GridDesc &g
 // group: NULL, or one number per tensor; tensors with equal numbers share their thresholds, which
 // are then order statistics of the group's pooled magnitudes (Sec. 4.2, per-layer-type pruning).
 int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const inshr_config *grid,
-               uint32_t n_cfg, double eps, bool light = false, const uint32_t *group = nullptr)
+               uint32_t n_cfg, double eps, bool want_scores, bool light = false, const uint32_t *group = nullptr)
 {
     c->have_search = false;
     if (!tensors || !grid || nT == 0) return INSHR_E_ARG;
@@ -282,43 +282,71 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
     GridDesc g;
     int rc = build_grid(grid, n_cfg, eps, g);
     if (rc) return rc;
-    uint64_t total_tiles = 0;
     for (uint32_t t = 0; t < nT; t++) {
         if (!tensors[t].data || tensors[t].n == 0 || tensors[t].n >= (1ull << 32)) return INSHR_E_ARG;
         if ((uintptr_t)tensors[t].data & 3u) return INSHR_E_ARG;
-        total_tiles += (tensors[t].n + TILE - 1) / TILE;
+    }
+    // Order on the device: the tensors the sweeps search, then the small ones, each of which one
+    // workgroup searches by itself (k_small).  A tensor that shares its thresholds is not searched by
+    // itself, and a light search leaves the sketch what only the sweeps count.
+    std::vector<u32> user_of(nT); // position in the caller's arrays of the tensor at a device position
+    std::vector<u32> &pos = c->pos;
+    pos.resize(nT);
+    uint32_t nB = 0, nS1 = 0, nS0 = 0;
+    {
+        auto cls = [&](uint32_t t) { // 0: sweeps, 1 / 2: small
+            if (light || members[leader[t]] > 1 || tensors[t].n > (u64)SMALL_MAX) return 0;
+            return tensors[t].n > (u64)SMALL_TINY ? 1 : 2;
+        };
+        uint32_t cnt[3] = {0, 0, 0};
+        for (uint32_t t = 0; t < nT; t++) cnt[cls(t)]++;
+        nB = cnt[0];
+        nS1 = cnt[1];
+        nS0 = cnt[2];
+        uint32_t at[3] = {0, nB, nB + nS1};
+        for (uint32_t t = 0; t < nT; t++) {
+            pos[t] = at[cls(t)]++;
+            user_of[pos[t]] = t;
+        }
+    }
+    uint64_t total_tiles = 0, all_tiles = 0; // of the tensors the sweeps search, of all
+    for (uint32_t t = 0; t < nT; t++) {
+        const u64 k = (tensors[t].n + TILE - 1) / TILE;
+        all_tiles += k;
+        if (pos[t] < nB) total_tiles += k;
     }
     HIPCHK(c, hipSetDevice(c->device));
     HIPCHK(c, hipStreamSynchronize(c->stream)); // staging buffers may be in flight (inshr_delta)
 
     // work partition: tiles are dealt out evenly to workgroups in order
     const int n_wg = (int)std::min<uint64_t>(total_tiles, (uint64_t)c->n_cu * c->wg_per_cu);
+    const int n_wg_all = (int)std::min<uint64_t>(all_tiles, (uint64_t)c->n_cu * c->wg_per_cu);
     std::vector<TDesc> td(nT);
     std::vector<u64> wg_tile0(n_wg + 1);
     std::vector<u32> wg_fu0(n_wg);
-    std::vector<std::vector<u32>> t_units(nT);
+    std::vector<u32> unit_tensor; // (the units of a tensor are consecutive)
+    std::vector<u32> t_unit0(nB + 1);
     {
         u64 tile = 0, pool = 0;
         bool any_sampled = false;
         for (uint32_t t = 0; t < nT; t++) {
-            td[t].data = tensors[t].data;
-            td[t].n = tensors[t].n;
+            const uint32_t u = user_of[t];
+            td[t].data = tensors[u].data;
+            td[t].n = tensors[u].n;
             td[t].tile0 = tile;
-            const u64 padded = (tensors[t].n + TILE - 1) / TILE * TILE;
-            td[t].aligned16 = (((uintptr_t)tensors[t].data & 15u) == 0) ? 1u : 0u;
-            td[t].leader = leader[t];
-            td[t].pooled = members[leader[t]] > 1 ? 1u : 0u;
-            td[t].n_pool = n_pool[leader[t]];
+            td[t].pool_grp = td[t].pool_len = 0;
+            td[t].aligned16 = (((uintptr_t)tensors[u].data & 15u) == 0) ? 1u : 0u;
+            td[t].leader = pos[leader[u]];
+            td[t].pooled = members[leader[u]] > 1 ? 1u : 0u;
+            td[t].n_pool = n_pool[leader[u]];
             // (a sampled first sweep predicts where a tensor's own order statistics lie; a group's
             // come from the exact histograms of all its tensors)
-            td[t].sampled = (!td[t].pooled && c->sample_min_n && tensors[t].n >= c->sample_min_n &&
-                             tensors[t].n < (1ull << 31)) ? 1u : 0u;
+            td[t].sampled = (!td[t].pooled && c->sample_min_n && td[t].n >= c->sample_min_n && t < nB &&
+                             td[t].n < (1ull << 31)) ? 1u : 0u;
             any_sampled = any_sampled || td[t].sampled;
-            c->batch_sampled.resize(nT);
-            c->batch_sampled[t] = (char)td[t].sampled;
-            tile += padded / TILE;
+            tile += (td[t].n + TILE - 1) / TILE;
         }
-        for (int w = 0; w <= n_wg; w++) wg_tile0[w] = total_tiles * (u64)w / (u64)n_wg;
+        for (int w = 0; w <= n_wg; w++) wg_tile0[w] = n_wg ? total_tiles * (u64)w / (u64)n_wg : 0;
         // Gather pools: every wave of a (workgroup, tensor) unit owns a share of each pool, sized for
         // pool_wcap keys per tile of the unit plus one full tile (the sweeps stop gathering when the
         // share cannot take a whole tile any more), and never more than the wave's elements.
@@ -330,19 +358,19 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
             wg_fu0[w] = units;
             const u64 lo = wg_tile0[w], hi = wg_tile0[w + 1];
             if (lo >= hi) continue;
-            while (t + 1 < nT && td[t + 1].tile0 <= lo) t++;
+            while (t + 1 < nB && td[t + 1].tile0 <= lo) t++;
             uint32_t tt = t;
             while (true) {
-                t_units[tt].push_back(units++);
-                const u64 t_end = (tt + 1 < nT) ? td[tt + 1].tile0 : total_tiles;
+                const bool first = unit_tensor.empty() || unit_tensor.back() != tt;
+                if (first) t_unit0[tt] = units;
+                unit_tensor.push_back(tt);
+                units++;
+                const u64 t_end = (tt + 1 < nB) ? td[tt + 1].tile0 : total_tiles;
                 const u64 u_lo = std::max(lo, td[tt].tile0), u_hi = std::min(hi, t_end);
                 const u64 tiles_u = u_hi - u_lo;
                 const u64 per_wave = TILE / (BLOCK / 64);
                 const u64 capw = std::min(tiles_u * per_wave, tiles_u * (u64)c->pool_wcap + per_wave);
-                if (t_units[tt].size() == 1) {
-                    td[tt].pool_grp = pool;
-                    td[tt].pool_len = 0;
-                }
+                if (first) td[tt].pool_grp = pool;
                 unit_off.push_back(pool);
                 unit_capw.push_back((u32)capw);
                 td[tt].pool_len += capw * (BLOCK / 64);
@@ -351,60 +379,63 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
                 tt++;
             }
         }
+        t_unit0[nB] = units;
         // device layout
         Carver cv;
         const size_t o_td = cv.take(sizeof(TDesc) * nT);
         const size_t o_gd = cv.take(sizeof(GridDesc));
         const size_t o_wt = cv.take(sizeof(u64) * (n_wg + 1));
+        const size_t o_wa = cv.take(sizeof(u64) * (n_wg_all + 1));
         const size_t o_wf = cv.take(sizeof(u32) * n_wg);
-        const size_t o_tfo = cv.take(sizeof(u32) * (nT + 1));
+        const size_t o_tfo = cv.take(sizeof(u32) * (nB + 1));
         const size_t o_tfi = cv.take(sizeof(u32) * units);
         const size_t o_fut = cv.take(sizeof(u32) * units);
         const size_t o_us = cv.take((size_t)units * 8);
         const size_t o_usb = cv.take((size_t)units * 4);
         const size_t up_bytes = cv.off;
         const size_t o_ts = cv.take(sizeof(TState) * nT);
-        const size_t o_h1 = cv.take((size_t)nT * L1_BINS * 4);
-        const size_t o_h2 = cv.take((size_t)nT * L2_BINS * 4);
+        const size_t o_h1 = cv.take((size_t)nB * L1_BINS * 4);
+        const size_t o_h2 = cv.take((size_t)nB * L2_BINS * 4);
         const size_t o_ngt = cv.take(256);
-        const size_t o_gcn = cv.take((size_t)nT * 2 * MAX_EDGES * 4);
-        const size_t o_gsx = cv.take((size_t)nT * 2 * MAX_EDGES * 8);
-        const size_t o_to = cv.take((size_t)total_tiles * MAX_FRAC * 4);
-        const size_t o_ph1 = cv.take(any_pooled ? (size_t)nT * L1_BINS * 4 : 0);
+        const size_t o_gcn = cv.take((size_t)nB * 2 * MAX_EDGES * 4);
+        const size_t o_gsx = cv.take((size_t)nB * 2 * MAX_EDGES * 8);
+        const size_t o_to = cv.take((size_t)all_tiles * MAX_FRAC * 4);
+        const size_t o_ph1 = cv.take(any_pooled ? (size_t)nB * L1_BINS * 4 : 0);
         const size_t zero_end = cv.off; // [o_ts, zero_end) is cleared before the sweeps
-        const size_t o_psel = cv.take(any_pooled ? (size_t)nT * 2 * SEL_WORDS * 4 : 0);
+        const size_t o_psel = cv.take(any_pooled ? (size_t)nB * 2 * SEL_WORDS * 4 : 0);
+        const size_t o_rs = cv.take(sizeof(SearchResult) * nT);
         const size_t o_tab = cv.take((size_t)nT * COARSE * 4);
         const size_t o_ut = cv.take((size_t)units * 16 * 4);
-        const size_t o_bi = cv.take((size_t)nT * L2_BINS * 4);
-        const size_t o_cur = cv.take((size_t)nT * CURSOR_STRIDE * 4);
-        const size_t o_tb = cv.take((size_t)nT * TGT_STRIDE * 4);
-        const size_t o_tr = cv.take((size_t)nT * TGT_STRIDE * 4);
+        const size_t o_bi = cv.take((size_t)nB * L2_BINS * 4);
+        const size_t o_cur = cv.take((size_t)nB * CURSOR_STRIDE * 4);
+        const size_t o_tb = cv.take((size_t)nB * TGT_STRIDE * 4);
+        const size_t o_tr = cv.take((size_t)nB * TGT_STRIDE * 4);
         const size_t o_tk = cv.take((size_t)nT * TGT_STRIDE * 4);
-        const size_t o_tf = cv.take((size_t)total_tiles * 4);
+        const size_t o_tf = cv.take((size_t)all_tiles * 4);
         const size_t o_sq = cv.take((size_t)units * SQ_STRIDE * 8);
-        const size_t o_ed = cv.take((size_t)nT * MAX_EDGES * 4);
-        const size_t o_sl = cv.take((size_t)nT * (L2_BINS + 64) * 2);
-        const size_t o_pe = cv.take((size_t)nT * MAX_PAIRS * EIDX_STRIDE * 2);
-        const size_t o_eb = cv.take((size_t)nT * MAX_EDGES * 4);
-        const size_t o_ei = cv.take((size_t)nT * MAX_EDGES * 2);
-        const size_t o_gel = cv.take((size_t)nT * MAX_GROUPS * 4);
-        const size_t o_geh = cv.take((size_t)nT * MAX_GROUPS * 4);
-        const size_t o_sgc = cv.take((size_t)nT * MAX_EDGES * 4);
+        const size_t o_ed = cv.take((size_t)nB * MAX_EDGES * 4);
+        const size_t o_sl = cv.take((size_t)nB * (L2_BINS + 64) * 2);
+        const size_t o_pe = cv.take((size_t)nB * MAX_PAIRS * EIDX_STRIDE * 2);
+        const size_t o_eb = cv.take((size_t)nB * MAX_EDGES * 4);
+        const size_t o_ei = cv.take((size_t)nB * MAX_EDGES * 2);
+        const size_t o_gel = cv.take((size_t)nB * MAX_GROUPS * 4);
+        const size_t o_geh = cv.take((size_t)nB * MAX_GROUPS * 4);
+        const size_t o_sgc = cv.take((size_t)nB * MAX_EDGES * 4);
         const size_t o_ms = cv.take((size_t)units * MAX_SUB * 8);
-        const size_t o_sbc = cv.take((size_t)nT * MAX_SUB * 4);
-        const size_t o_sbn = cv.take((size_t)nT * MAX_SUB * 4);
+        const size_t o_sbc = cv.take((size_t)nB * MAX_SUB * 4);
+        const size_t o_sbn = cv.take((size_t)nB * MAX_SUB * 4);
         const size_t o_cb = cv.take((size_t)nT * n_cfg * CB_STRIDE * 4);
         const size_t o_sc = cv.take((size_t)nT * n_cfg * sizeof(Score));
-        const size_t o_bt = cv.take((size_t)nT * n_cfg * CB_STRIDE * 8);
+        const size_t o_bt = cv.take((size_t)nB * n_cfg * CB_STRIDE * 8);
         const size_t o_uc = cv.take((size_t)units * 16 * 4);
-        const size_t o_bg = cv.take((size_t)nT * L2_BINS * 2);
-        const size_t o_go = cv.take((size_t)nT * MAX_GROUPS * 4);
-        const size_t o_ge = cv.take((size_t)nT * MAX_GROUPS * 4);
-        const size_t o_gc = cv.take((size_t)nT * MAX_GROUPS * 4);
-        const size_t o_tgg = cv.take((size_t)nT * TGT_STRIDE * 4);
-        const size_t o_tkl = cv.take((size_t)nT * TGT_STRIDE * 4);
-        const size_t o_tkh = cv.take((size_t)nT * TGT_STRIDE * 4);
-        const size_t o_gl = cv.take((size_t)nT * MAX_GROUPS * 4);
+        const size_t o_bg = cv.take((size_t)nB * L2_BINS * 2);
+        const size_t o_go = cv.take((size_t)nB * MAX_GROUPS * 4);
+        const size_t o_ge = cv.take((size_t)nB * MAX_GROUPS * 4);
+        const size_t o_gc = cv.take((size_t)nB * MAX_GROUPS * 4);
+        const size_t o_tgg = cv.take((size_t)nB * TGT_STRIDE * 4);
+        const size_t o_tkl = cv.take((size_t)nB * TGT_STRIDE * 4);
+        const size_t o_tkh = cv.take((size_t)nB * TGT_STRIDE * 4);
+        const size_t o_gl = cv.take((size_t)nB * MAX_GROUPS * 4);
         const size_t o_pool = cv.take((size_t)pool * 4);
         const size_t o_pool2 = cv.take((size_t)pool * 4);
         rc = ensure_dev(c, c->search_mem, cv.off);
@@ -418,16 +449,12 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         memcpy(hb + o_wt, wg_tile0.data(), sizeof(u64) * (n_wg + 1));
         memcpy(hb + o_wf, wg_fu0.data(), sizeof(u32) * n_wg);
         {
-            u32 *tfo = (u32 *)(hb + o_tfo), *tfi = (u32 *)(hb + o_tfi);
-            u32 k = 0;
-            for (uint32_t tt = 0; tt < nT; tt++) {
-                tfo[tt] = k;
-                for (u32 u : t_units[tt]) tfi[k++] = u;
-            }
-            tfo[nT] = k;
-            u32 *fut = (u32 *)(hb + o_fut);
-            for (uint32_t tt = 0; tt < nT; tt++)
-                for (u32 u : t_units[tt]) fut[u] = tt;
+            u32 *tfi = (u32 *)(hb + o_tfi);
+            for (u32 u = 0; u < units; u++) tfi[u] = u;
+            memcpy(hb + o_tfo, t_unit0.data(), sizeof(u32) * (nB + 1));
+            memcpy(hb + o_fut, unit_tensor.data(), sizeof(u32) * units);
+            u64 *wa = (u64 *)(hb + o_wa);
+            for (int w = 0; w <= n_wg_all; w++) wa[w] = all_tiles * (u64)w / (u64)n_wg_all;
             memcpy(hb + o_us, unit_off.data(), sizeof(u64) * units);
             memcpy(hb + o_usb, unit_capw.data(), sizeof(u32) * units);
         }
@@ -450,13 +477,19 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         bt.any_sampled = any_sampled;
         bt.any_pooled = any_pooled;
         bt.force_miss = c->sample_force_miss;
+        bt.wg_tile0_all = (const u64 *)(db + o_wa);
         bt.nT = (int)nT;
+        bt.nB = (int)nB;
+        bt.nS1 = (int)nS1;
+        bt.nS0 = (int)nS0;
         bt.n_wg = n_wg;
+        bt.n_wg_all = n_wg_all;
         bt.n_pairs = g.n_pairs;
         bt.n_cfg = n_cfg;
-        bt.n_tiles = total_tiles;
+        bt.n_tiles = all_tiles;
         Bufs &B = bt.bufs;
         B.ts = (TState *)(db + o_ts);
+        B.res = (SearchResult *)(db + o_rs);
         B.hist1 = (u32 *)(db + o_h1);
         B.pool_h1 = (u32 *)(db + o_ph1);
         B.pool_sel = (u32 *)(db + o_psel);
@@ -499,34 +532,37 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         B.codebook = (float *)(db + o_cb);
         B.scores = (Score *)(db + o_sc);
         B.bin_term = (double *)(db + o_bt);
-        c->ts_off = o_ts;
+        c->res_off = o_rs;
         c->scores_off = o_sc;
     }
     c->batch.light = light;
+    HIPCHK(c, launch_small(c->batch, c->stream));
     HIPCHK(c, launch_select(c->batch, c->stream));
     if (!light) HIPCHK(c, launch_score(c->batch, c->stream));
 
-    // results: per-tensor state and scores
-    const size_t ts_bytes = sizeof(TState) * nT, sc_bytes = sizeof(Score) * (size_t)nT * n_cfg;
-    rc = ensure_host(c, c->h_down, ts_bytes + sc_bytes);
+    // results, in device order
+    const size_t rs_bytes = sizeof(SearchResult) * nT, sc_bytes = want_scores ? sizeof(Score) * (size_t)nT * n_cfg : 0;
+    rc = ensure_host(c, c->h_down, rs_bytes + sc_bytes);
     if (rc) return rc;
     char *db = (char *)c->search_mem.p;
-    HIPCHK(c, hipMemcpyAsync(c->h_down.p, db + c->ts_off, ts_bytes, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipMemcpyAsync((char *)c->h_down.p + ts_bytes, db + c->scores_off, sc_bytes,
-                             hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipMemcpyAsync(c->h_down.p, db + c->res_off, rs_bytes, hipMemcpyDeviceToHost, c->stream));
+    if (sc_bytes)
+        HIPCHK(c, hipMemcpyAsync((char *)c->h_down.p + rs_bytes, db + c->scores_off, sc_bytes,
+                                 hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    const TState *hts = (const TState *)c->h_down.p;
+    const SearchResult *res = (const SearchResult *)c->h_down.p;
     for (uint32_t t = 0; t < nT; t++) {
-        if (hts[t].nonfinite) return INSHR_E_NONFINITE;
+        if (res[t].nonfinite) return INSHR_E_NONFINITE;
     }
     for (uint32_t t = 0; t < nT; t++) {
-        if (any_pooled && (hts[t].internal_err & 32u)) { // (a tensor alone always keeps the value of rank P)
+        if (any_pooled && (res[pos[t]].internal_err & 32u)) { // (a tensor alone always keeps the value of rank P)
             c->last_err = "the shared thresholds leave tensor " + std::to_string(t) + " without quantized values";
             return INSHR_E_CONFIG;
         }
     }
     for (uint32_t t = 0; t < nT; t++) {
-        if (!hts[t].pool_overflow) continue;
+        const SearchResult &r = res[pos[t]];
+        if (!r.pool_overflow) continue;
         // some wave gathered more keys than its share of a pool holds: larger pools, once more
         const uint32_t full = TILE / (BLOCK / 64);
         if (c->pool_wcap >= full) {
@@ -536,25 +572,26 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         c->pool_wcap = std::min<uint32_t>(full, c->pool_wcap * 2);
         if (getenv("INSHR_SAMPLE_DEBUG"))
             fprintf(stderr, "inshr_search: gather pools too small (tensor %u, code %u): again with %u keys per wave and tile\n",
-                    t, hts[t].pool_overflow, c->pool_wcap);
-        return run_search(c, tensors, nT, grid, n_cfg, eps, light, group);
+                    t, r.pool_overflow, c->pool_wcap);
+        return run_search(c, tensors, nT, grid, n_cfg, eps, want_scores, light, group);
     }
     if (getenv("INSHR_SAMPLE_DEBUG")) { // how many sampled first sweeps had to be repeated exactly
         uint32_t n_sampled = 0, n_redo = 0;
         for (uint32_t t = 0; t < nT; t++) {
-            n_sampled += c->batch_sampled.size() > t && c->batch_sampled[t] ? 1u : 0u;
-            n_redo += hts[t].redo ? 1u : 0u;
-            if (hts[t].redo)
+            n_sampled += td[pos[t]].sampled ? 1u : 0u;
+            const uint32_t redo = res[pos[t]].redo;
+            n_redo += redo ? 1u : 0u;
+            if (redo)
                 fprintf(stderr, "inshr_search: tensor %u (n = %llu) repeated, thresholds missed: 0x%x\n", t,
-                        (unsigned long long)tensors[t].n, hts[t].redo >> 1);
+                        (unsigned long long)tensors[t].n, redo >> 1);
         }
         fprintf(stderr, "inshr_search: %u tensors, %u with a sampled first sweep, %u of them repeated\n",
                 nT, n_sampled, n_redo);
     }
     for (uint32_t t = 0; t < nT; t++) {
-        if (hts[t].internal_err) {
+        if (res[pos[t]].internal_err) {
             c->last_err = "kernel self-check failed on tensor " + std::to_string(t) + ", code " +
-                          std::to_string(hts[t].internal_err);
+                          std::to_string(res[pos[t]].internal_err);
             return INSHR_E_INTERNAL;
         }
     }
@@ -694,23 +731,29 @@ int inshr_profile_read(inshr_ctx *c, inshr_kernel_time *out, uint32_t cap, uint3
     return INSHR_OK;
 }
 
+// what the last search downloaded, in the caller's order
+static void take_results(const inshr_ctx *c, uint32_t nT, uint32_t n_cfg, uint32_t *best, uint8_t *feasible,
+                         inshr_score *scores)
+{
+    static_assert(sizeof(Score) == sizeof(inshr_score), "score layout");
+    const SearchResult *res = (const SearchResult *)c->h_down.p;
+    const Score *hsc = (const Score *)((const char *)c->h_down.p + sizeof(SearchResult) * nT);
+    for (uint32_t t = 0; t < nT; t++) {
+        const u32 p = c->pos[t];
+        best[t] = res[p].best;
+        feasible[t] = (uint8_t)res[p].feasible;
+        if (scores) memcpy(scores + (size_t)t * n_cfg, hsc + (size_t)p * n_cfg, sizeof(Score) * n_cfg);
+    }
+}
+
 int inshr_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t n_tensors,
                  const inshr_config *grid, uint32_t n_cfg, double eps, uint32_t *best,
                  uint8_t *feasible, inshr_score *scores)
 {
     if (!c || !best || !feasible) return INSHR_E_ARG;
-    int rc = run_search(c, tensors, n_tensors, grid, n_cfg, eps);
+    int rc = run_search(c, tensors, n_tensors, grid, n_cfg, eps, scores != nullptr);
     if (rc) return rc;
-    const TState *hts = (const TState *)c->h_down.p;
-    const Score *hsc = (const Score *)((const char *)c->h_down.p + sizeof(TState) * n_tensors);
-    for (uint32_t t = 0; t < n_tensors; t++) {
-        best[t] = hts[t].best;
-        feasible[t] = (uint8_t)hts[t].feasible;
-    }
-    if (scores) {
-        static_assert(sizeof(Score) == sizeof(inshr_score), "score layout");
-        memcpy(scores, hsc, sizeof(Score) * (size_t)n_tensors * n_cfg);
-    }
+    take_results(c, n_tensors, n_cfg, best, feasible, scores);
     return INSHR_OK;
 }
 
@@ -719,15 +762,9 @@ int inshr_search_pooled(inshr_ctx *c, const inshr_tensor *tensors, const uint32_
                         uint32_t *best, uint8_t *feasible, inshr_score *scores)
 {
     if (!c || !best || !feasible || !group) return INSHR_E_ARG;
-    int rc = run_search(c, tensors, n_tensors, grid, n_cfg, eps, false, group);
+    int rc = run_search(c, tensors, n_tensors, grid, n_cfg, eps, scores != nullptr, false, group);
     if (rc) return rc;
-    const TState *hts = (const TState *)c->h_down.p;
-    const Score *hsc = (const Score *)((const char *)c->h_down.p + sizeof(TState) * n_tensors);
-    for (uint32_t t = 0; t < n_tensors; t++) {
-        best[t] = hts[t].best;
-        feasible[t] = (uint8_t)hts[t].feasible;
-    }
-    if (scores) memcpy(scores, hsc, sizeof(Score) * (size_t)n_tensors * n_cfg);
+    take_results(c, n_tensors, n_cfg, best, feasible, scores);
     return INSHR_OK;
 }
 
@@ -753,13 +790,13 @@ static int quantize_with_state(inshr_ctx *c, const inshr_config *cfg, inshr_quan
     std::vector<QDesc> qd(nT);
     for (auto &q : qd) memset(&q, 0, sizeof(q));
     for (uint32_t k = 0; k < n_sel; k++) {
-        const uint32_t t = which[k];
+        const uint32_t u = which[k], t = c->pos[u]; // in the caller's order, on the device
         uint32_t gi = 0;
         for (gi = 0; gi < c->grid.n_cfg; gi++)
             if (same_config(c->grid_cfgs[gi], cfg[k])) break;
         if (gi == c->grid.n_cfg) return INSHR_E_SHAPE;
         uint64_t words = 0, cap = 0;
-        inshr_quantize_bound(c->tensors[t].n, &cfg[k], &words, &cap);
+        inshr_quantize_bound(c->tensors[u].n, &cfg[k], &words, &cap);
         if (!out[k].packed || !out[k].codebook || out[k].packed_words < words) return INSHR_E_CAPACITY;
         if (out[k].outlier_cap && (!out[k].outlier_idx || !out[k].outlier_val)) return INSHR_E_ARG;
         qd[t].packed = (unsigned long long *)out[k].packed;
@@ -792,7 +829,7 @@ static int quantize_with_state(inshr_ctx *c, const inshr_config *cfg, inshr_quan
     const QInfo *qi = (const QInfo *)c->h_down.p;
     int result = INSHR_OK;
     for (uint32_t k = 0; k < n_sel; k++) {
-        const QInfo &r = qi[which[k]];
+        const QInfo &r = qi[c->pos[which[k]]];
         out[k].n_pruned = r.n_pruned;
         out[k].n_outlier = r.n_outlier;
         out[k].n_kept = r.n_kept;
@@ -845,7 +882,7 @@ int inshr_quantize(inshr_ctx *c, const inshr_tensor *tensors, const inshr_config
                 idx.push_back(t);
             }
         }
-        int rc = run_search(c, sub.data(), (uint32_t)sub.size(), &cfg[t0], 1, 0.0);
+        int rc = run_search(c, sub.data(), (uint32_t)sub.size(), &cfg[t0], 1, 0.0, false);
         if (rc) return rc;
         std::vector<inshr_quantized> subout(sub.size());
         std::vector<uint32_t> which(sub.size());
@@ -952,8 +989,8 @@ int sketch_with_state(inshr_ctx *c, const inshr_config *cfg, const uint32_t *whi
                 c->grid_cfgs[gi].outlier_ppm == cfg[k].outlier_ppm)
                 break;
         if (gi == c->grid.n_cfg) return INSHR_E_SHAPE;
-        sd[which[k]].active = 1u;
-        sd[which[k]].cfg = gi;
+        sd[c->pos[which[k]]].active = 1u;
+        sd[c->pos[which[k]]].cfg = gi;
     }
     const size_t n_idx = T.tops.size();
     Carver cv;
@@ -993,7 +1030,7 @@ int sketch_with_state(inshr_ctx *c, const inshr_config *cfg, const uint32_t *whi
     memcpy(hb + o_rep, T.rep.data(), sizeof(double) * n_idx);
     memset(hb + o_uni, 0, sizeof(double) * 256 * nT);
     for (uint32_t k = 0; k < n_sel; k++)
-        memcpy(hb + o_uni + sizeof(double) * 256 * which[k], params->uniforms + (size_t)src[k] * 256,
+        memcpy(hb + o_uni + sizeof(double) * 256 * c->pos[which[k]], params->uniforms + (size_t)src[k] * 256,
                sizeof(double) * 256);
     memcpy(hb + o_sd, sd.data(), sizeof(SketchDesc) * nT);
     HIPCHK(c, hipMemcpyAsync(db, hb, upload, hipMemcpyHostToDevice, c->stream));
@@ -1034,14 +1071,14 @@ int sketch_with_state(inshr_ctx *c, const inshr_config *cfg, const uint32_t *whi
     if (info) {
         const SketchInfo *si = (const SketchInfo *)c->h_down.p;
         for (uint32_t k = 0; k < n_sel; k++) {
-            info[src[k]].n_buckets = si[which[k]].n_buckets;
-            info[src[k]].rounds = si[which[k]].rounds;
+            info[src[k]].n_buckets = si[c->pos[which[k]]].n_buckets;
+            info[src[k]].rounds = si[c->pos[which[k]]].rounds;
         }
     }
     if (multi && choice) {
         const SketchChoice *sc = (const SketchChoice *)((const char *)c->h_down.p + sizeof(SketchInfo) * nT);
         for (uint32_t k = 0; k < n_sel; k++) {
-            const SketchChoice &r = sc[which[k]];
+            const SketchChoice &r = sc[c->pos[which[k]]];
             inshr_sketch_choice &o = choice[src[k]];
             for (int b = 0; b < SK_SETS; b++) {
                 o.sse[b] = r.sse[b];
@@ -1108,7 +1145,7 @@ int inshr_quantize_sketch(inshr_ctx *c, const inshr_tensor *tensors, const inshr
             }
         }
         const uint32_t nS = (uint32_t)sub.size();
-        rc = run_search(c, sub.data(), nS, &cfg[t0], 1, 0.0, true);
+        rc = run_search(c, sub.data(), nS, &cfg[t0], 1, 0.0, false, true);
         if (rc) return rc;
         std::vector<inshr_quantized> subout(nS);
         std::vector<uint32_t> which(nS);
@@ -1192,7 +1229,7 @@ int inshr_search_sketch(inshr_ctx *c, const inshr_tensor *tensors, const inshr_c
             grid7[b] = wide[t0];
             grid7[b].bits = (uint8_t)(2 + b);
         }
-        rc = run_search(c, sub.data(), nS, grid7, SK_SETS, eps, true);
+        rc = run_search(c, sub.data(), nS, grid7, SK_SETS, eps, false, true);
         if (rc) return rc;
         std::vector<inshr_quantized> subout(nS);
         std::vector<uint32_t> which(nS);
@@ -1468,15 +1505,15 @@ int inshr_quantize_sens(inshr_ctx *c, const inshr_tensor *tensors, const float *
             sub[t].data = pass == 0 ? sd[t].S : tensors[t].data;
             sub[t].n = tensors[t].n;
         }
-        rc = run_search(c, sub.data(), nT, frac_grid.data(), (uint32_t)frac_grid.size(), 0.0, true);
+        rc = run_search(c, sub.data(), nT, frac_grid.data(), (uint32_t)frac_grid.size(), 0.0, false, true);
         if (rc) return rc;
-        const TState *hts = (const TState *)c->h_down.p;
+        const SearchResult *res = (const SearchResult *)c->h_down.p;
         for (uint32_t t = 0; t < nT; t++) {
             uint32_t qp = 0, qo = 0;
             while (qp < c->grid.n_p && c->grid.p_ppm[qp] != cfg[t].prune_ppm) qp++;
             while (qo < c->grid.n_o && c->grid.o_ppm[qo] != cfg[t].outlier_ppm) qo++;
             if (qp == c->grid.n_p || qo == c->grid.n_o) return INSHR_E_INTERNAL;
-            const u32 tp = hts[t].thr_mag[qp], to = hts[t].thr_mag[c->grid.n_p + qo];
+            const u32 tp = res[c->pos[t]].thr_mag[qp], to = res[c->pos[t]].thr_mag[c->grid.n_p + qo];
             if (pass == 0) {
                 sd[t].tau_os = to;
                 if (sd[t].by_sens) sd[t].tau_p = tp;
@@ -1503,24 +1540,25 @@ int inshr_quantize_sens(inshr_ctx *c, const inshr_tensor *tensors, const float *
         sub[t].n = si[t].n_kept;
     }
     // the bins: the quantized values as tensors of their own, nothing pruned, nothing protected
-    rc = run_search(c, sub.data(), nT, bin_grid.data(), (uint32_t)bin_grid.size(), 0.0, false);
+    rc = run_search(c, sub.data(), nT, bin_grid.data(), (uint32_t)bin_grid.size(), 0.0, true);
     if (rc) return rc;
     c->have_search = false; // (the state describes the compacted values, not the caller's tensors)
-    const Score *hsc = (const Score *)((const char *)c->h_down.p + sizeof(TState) * nT);
+    const Score *hsc = (const Score *)((const char *)c->h_down.p + sizeof(SearchResult) * nT);
     const uint32_t n_bg = (uint32_t)bin_grid.size();
     std::vector<double> sse_q(nT), sq_q(nT);
     for (uint32_t t = 0; t < nT; t++) {
         const uint32_t gi = bin_of_t[t];
-        sse_q[t] = hsc[(size_t)t * n_bg + gi].sse;
-        sq_q[t] = hsc[(size_t)t * n_bg + gi].sumsq;
+        const u32 p = c->pos[t];
+        sse_q[t] = hsc[(size_t)p * n_bg + gi].sse;
+        sq_q[t] = hsc[(size_t)p * n_bg + gi].sumsq;
         sd[t].packed = (unsigned long long *)out[t].packed;
         sd[t].out_idx = out[t].outlier_idx;
         sd[t].out_val = out[t].outlier_val;
         sd[t].out_cap = out[t].outlier_cap;
         sd[t].codebook = out[t].codebook;
         sd[t].boundaries = out[t].boundaries;
-        sd[t].bkeys = c->batch.bufs.tgt_key + (size_t)t * TGT_STRIDE; // (one pair: nothing pruned or protected)
-        sd[t].cb = c->batch.bufs.codebook + ((size_t)t * n_bg + gi) * CB_STRIDE;
+        sd[t].bkeys = c->batch.bufs.tgt_key + (size_t)p * TGT_STRIDE; // (one pair: nothing pruned or protected)
+        sd[t].cb = c->batch.bufs.codebook + ((size_t)p * n_bg + gi) * CB_STRIDE;
         sd[t].K = bins_of(cfg[t]);
         sd[t].sym_bits = symbol_bits(sd[t].K);
     }

@@ -177,6 +177,9 @@ struct TDesc {           // one tensor of a batch
     u64 n_pool;          // elements of the whole group
 };
 constexpr int SAMPLE_RATE = 8;
+constexpr int SMALL_TINY = 4096;   // tensors up to these sizes are searched by one workgroup each
+constexpr int SMALL_MAX = 16384;   // (k_small); one tile at most
+static_assert(SMALL_MAX <= TILE, "a small tensor is one tile");
 
 struct GridDesc {        // the configuration grid, decomposed
     u32 n_cfg, n_pairs, n_p, n_o;
@@ -243,6 +246,26 @@ struct TState {
     u32 best, feasible;
 };
 
+struct SearchResult {    // what the host reads of a tensor's state
+    u32 nonfinite, internal_err, pool_overflow, redo, best, feasible;
+    u32 thr_mag[MAX_THR];
+};
+// by the last kernel that works on the tensor, after a barrier behind its own changes of the state
+// (which atomics make at the L2 cache: read there)
+__device__ __forceinline__ void store_result(TState *st, SearchResult *res)
+{
+    auto rd = [](u32 *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    SearchResult r;
+    r.nonfinite = rd(&st->nonfinite);
+    r.internal_err = rd(&st->internal_err);
+    r.pool_overflow = rd(&st->pool_overflow);
+    r.redo = rd(&st->redo);
+    r.best = st->best;
+    r.feasible = st->feasible;
+    for (int i = 0; i < MAX_THR; i++) r.thr_mag[i] = st->thr_mag[i];
+    *res = r;
+}
+
 struct Score {           // mirrors inshr_score
     double sse, sumsq;
     u64 n_pruned, n_outlier, n_kept, cost_bits;
@@ -287,6 +310,80 @@ __device__ __forceinline__ double wave_sum_f64(double v)
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
     return v;
+}
+
+// Stable rank of a key's digit among the keys its wave has seen in this pass.  ORDERED: one
+// returning LDS add (same-address LDS atomics are served in ascending lane order, verified when the
+// context is created).  Otherwise lanes with equal digits find each other with eight ballots.
+template <bool ORDERED>
+__device__ __forceinline__ u32 digit_rank(u32 *wcnt, u32 digit, bool valid)
+{
+    if (ORDERED) {
+        u32 r = 0u;
+        if (valid) r = atomicAdd(&wcnt[digit], 1u);
+        return r;
+    }
+    const u32 lane = threadIdx.x & 63u;
+    u64 peers = __ballot(valid);
+#pragma unroll
+    for (int b = 0; b < 8; b++) {
+        const bool bit = (digit >> b) & 1u;
+        const u64 m = __ballot(bit);
+        peers &= bit ? m : ~m;
+    }
+    const u32 rank = __popcll(peers & ((1ull << lane) - 1ull));
+    u32 old = 0u;
+    if (valid) old = wcnt[digit];
+    if (valid && rank == 0u) wcnt[digit] = old + (u32)__popcll(peers);
+    return old + rank;
+}
+
+// payload model (Sec. 5): log2 K bits per quantized value (l16: in units of 2^-16; rounded up), 32 per
+// protected value and per centre
+__device__ __forceinline__ u64 payload_bits(u64 n_kept, u64 n_outlier, u32 K, u32 l16)
+{
+    return ((n_kept * (u64)l16 + 65535ull) >> 16) + 32ull * n_outlier + 32ull * (u64)K;
+}
+
+// Sec. 5: the cheapest configuration within eps, else the most accurate one; ties go to the lowest
+// index.  By one wave; every lane takes every 64th configuration.
+struct Choice {
+    u32 best, feasible;
+};
+__device__ __forceinline__ Choice choose_config(const double *sse, const u64 *cost, u32 n_cfg, double eps, double sumsq)
+{
+    u64 bc = ~0ull;                       // cheapest feasible: cost, then index
+    u64 ba = ~0ull;                       // most accurate: bits of the (non-negative) error, then index
+    u32 gf = 0xFFFFFFFFu, ga = 0xFFFFFFFFu;
+    for (u32 g = threadIdx.x & 63u; g < n_cfg; g += 64u) {
+        const double e = sse[g], rel = (sumsq > 0.0) ? e / sumsq : 0.0;
+        const u64 eb = (u64)__double_as_longlong(e);
+        if (rel <= eps && (gf == 0xFFFFFFFFu || cost[g] < bc)) {
+            bc = cost[g];
+            gf = g;
+        }
+        if (ga == 0xFFFFFFFFu || eb < ba) {
+            ba = eb;
+            ga = g;
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const u64 c2 = __shfl_xor(bc, o), a2 = __shfl_xor(ba, o);
+        const u32 f2 = __shfl_xor(gf, o), g2 = __shfl_xor(ga, o);
+        if (f2 != 0xFFFFFFFFu && (gf == 0xFFFFFFFFu || c2 < bc || (c2 == bc && f2 < gf))) {
+            bc = c2;
+            gf = f2;
+        }
+        if (g2 != 0xFFFFFFFFu && (ga == 0xFFFFFFFFu || a2 < ba || (a2 == ba && g2 < ga))) {
+            ba = a2;
+            ga = g2;
+        }
+    }
+    Choice r;
+    r.feasible = gf != 0xFFFFFFFFu ? 1u : 0u;
+    r.best = r.feasible ? gf : ga;
+    return r;
 }
 
 // Exclusive scan of in(0) .. in(n - 1) (n <= 32 * BLOCK) into out[0..n], out[n] = total; whole

@@ -10,8 +10,10 @@ constexpr int SQ_STRIDE = MAX_FRAC + 1;     // partial sums of squares per (work
 constexpr int SEL_WORDS = MAX_THR * 1024;    // a tensor's selection histograms ([slot][sign][512])
 constexpr int CB_STRIDE = 256;              // codebook entries per configuration
 
-struct Bufs { // device pointers, indexed by the tensor's position in the batch unless noted
+struct Bufs { // device pointers, indexed by the tensor's position on the device unless noted; nB rows
+              // (tensors searched by the sweeps) except ts, table2, tgt_key, codebook, scores (all)
     TState *ts;
+    SearchResult *res; // [nT]
     u32 *hist1;     // [nT][32768]
     u32 *pool_h1;   // [nT][32768] row of a group's leader: the first-level histograms of the group, added up
     u32 *pool_sel;  // [nT][2][SEL_WORDS] row of a group's leader: the group's selection histograms, per pass
@@ -71,8 +73,11 @@ struct Batch {
     const u32 *fu_tensor; // device [units] tensor of each unit
     u32 *grp_list;       // device [nT * MAX_GROUPS] (tensor << 13 | group) of every group
     u32 *n_grp_total;    // device
-    int nT;
-    int n_wg;
+    const u64 *wg_tile0_all; // device [n_wg_all + 1] partition of the tiles of all tensors (quantizing)
+    int nT;              // tensors; on the device in the order: searched by sweeps, small ones
+    int nB;              // tensors searched by the sweeps (the partition wg_tile0 covers their tiles)
+    int nS1, nS0;        // small tensors behind them: up to SMALL_MAX, up to SMALL_TINY values
+    int n_wg, n_wg_all;
     int n_units;
     int n_bucket_blocks;
     bool lds_ordered;    // same-address LDS atomics return in lane order on this device
@@ -198,6 +203,7 @@ void prof_end(hipStream_t s);
 hipError_t launch_select(const Batch &bt, hipStream_t s);
 hipError_t launch_edges(const Batch &bt, hipStream_t s); // edge order, bins without edges (inside launch_select)
 hipError_t launch_score(const Batch &bt, hipStream_t s);
+hipError_t launch_small(const Batch &bt, hipStream_t s); // the whole search of the small tensors
 hipError_t launch_quantize(const Batch &bt, const QDesc *qd, QInfo *qi, hipStream_t s);
 hipError_t launch_delta(const DDesc *dd, int nT, u64 n_dtiles, u64 n_chunks,
                         const u32 *chunk_tensor, u32 *chunk_tot, u32 *flags, bool any_scatter,

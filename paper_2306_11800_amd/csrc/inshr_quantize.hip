@@ -9,56 +9,6 @@
 
 namespace inshr {
 
-// per tensor: prefix of protected counts over its tiles, meta data, codebook / boundary copy
-__global__ __launch_bounds__(BLOCK) void k_qprep(const TDesc *__restrict__ td,
-                                                 const GridDesc *__restrict__ gd,
-                                                 const QDesc *__restrict__ qd,
-                                                 QInfo *__restrict__ qi, Bufs B)
-{
-    extern __shared__ u32 smem[]; // [32768 + 4]
-    __shared__ u32 tmp[BLOCK / 64 + 1];
-    const int i = blockIdx.x;
-    const QDesc q = qd[i];
-    if (q.packed == nullptr) return;
-    const int t = i;
-    const u32 tid = threadIdx.x;
-    const TDesc d = td[t];
-    const TState *st = B.ts + t;
-    const u32 g = q.cfg, pair = gd->cfg_pair[g], K = gd->cfg_K[g];
-    const u32 o = gd->pair_o[pair], n_p = gd->n_p;
-    const u64 n_tiles = (d.n + TILE - 1) / TILE;
-    u32 carry = 0;
-    for (u64 base = 0; base < n_tiles; base += L2_BINS) {
-        const u64 left = n_tiles - base;
-        const int m = left < (u64)L2_BINS ? (int)left : L2_BINS;
-        for (int k = tid; k < m; k += BLOCK) smem[k] = B.tile_out[(d.tile0 + base + k) * MAX_FRAC + o];
-        __syncthreads();
-        u32 tot = block_excl_scan(smem, smem, m, tmp);
-        for (int k = tid; k < m; k += BLOCK) B.tile_off[d.tile0 + base + k] = carry + smem[k];
-        carry += tot;
-        __syncthreads();
-    }
-    // (boundary keys given from outside come as 256 entries, boundary j of K = 2^b at j * 256 / K - 1)
-    const u32 *tk = q.alt_key ? q.alt_key : B.tgt_key + (size_t)t * TGT_STRIDE + pair * NBT;
-    if (q.boundaries)
-        for (u32 j = 1 + tid; j < K; j += BLOCK)
-            gptr(q.boundaries)[j - 1] = __uint_as_float(bits_of_key(tk[bnd_index(K, j)]));
-    const float *cb = q.alt_cb ? q.alt_cb : B.codebook + ((size_t)t * gd->n_cfg + g) * CB_STRIDE;
-    for (u32 k = tid; k < K; k += BLOCK) gptr(q.codebook)[k] = cb[k];
-    if (tid == 0) {
-        QInfo r;
-        r.n_pruned = st->pair_Pn[pair] + st->pair_Pp[pair];
-        r.n_outlier = st->pair_An[pair] + st->pair_Ap[pair];
-        r.n_kept = st->pair_M[pair];
-        r.tau_p = st->thr_mag[gd->pair_p[pair]];
-        r.tau_o = st->thr_mag[n_p + o];
-        r.flags = 0u;
-        if ((u64)carry != r.n_outlier) r.flags |= 1u;  // self-check
-        if (r.n_outlier > q.out_cap) r.flags |= 2u;    // caller buffer too small
-        qi[i] = r;
-    }
-}
-
 // The symbol is a step function of the key: the 255 bin boundaries and the four class edges
 // (first quantized negative key, first pruned key, first quantized positive key, first protected
 // positive key) cut the key axis into at most 260 slots, each with one symbol.  The search's
@@ -82,7 +32,76 @@ struct QuantShared {
     QuantTables qt;
 };
 
-template <bool FULL>
+// cj (0 .. 4) summed over the lower lanes of the wave in `below`; returns the wave's total.
+__device__ __forceinline__ u32 rank_counts(u32 cj, u32 &below)
+{
+    const u64 m0 = __ballot(cj & 1u), m1 = __ballot(cj & 2u), m2 = __ballot(cj & 4u);
+    below = __builtin_amdgcn_mbcnt_hi((u32)(m0 >> 32), __builtin_amdgcn_mbcnt_lo((u32)m0, 0u)) +
+            2u * __builtin_amdgcn_mbcnt_hi((u32)(m1 >> 32), __builtin_amdgcn_mbcnt_lo((u32)m1, 0u)) +
+            4u * __builtin_amdgcn_mbcnt_hi((u32)(m2 >> 32), __builtin_amdgcn_mbcnt_lo((u32)m2, 0u));
+    return (u32)__popcll(m0) + 2u * (u32)__popcll(m1) + 4u * (u32)__popcll(m2);
+}
+
+// Breakpoints in key order and the symbol of every slot, by a workgroup of at least QBP + 8 threads.
+// tk: the pair's boundary keys (they ascend); at equal keys a boundary goes before a class edge.
+__device__ __forceinline__ void make_breakpoints(QuantTables &qt, const u32 *tk, u32 K, u32 tau_p, u32 tau_o)
+{
+    const u32 tid = threadIdx.x, n_bnd = K - 1u, n_bp = n_bnd + 4u;
+    if (tid < n_bnd) qt.raw[tid] = tk[bnd_index(K, tid + 1u)];
+    if (tid < 4u) qt.raw[n_bnd + tid] = class_edge_key(tid, tau_p, tau_o);
+    __syncthreads();
+    auto boundaries_upto = [&](u32 key) -> u32 {
+        u32 lo = 0u, hi = n_bnd;
+        while (lo < hi) {
+            const u32 mid = (lo + hi) >> 1;
+            if (qt.raw[mid] <= key)
+                lo = mid + 1u;
+            else
+                hi = mid;
+        }
+        return lo;
+    };
+    if (tid < n_bp) {
+        const u32 x = qt.raw[tid];
+        u32 r = tid < n_bnd ? tid : boundaries_upto(x);
+#pragma unroll
+        for (u32 e = 0; e < 4u; e++) {
+            const u32 y = qt.raw[n_bnd + e];
+            r += (y < x || (y == x && tid >= n_bnd && n_bnd + e < tid)) ? 1u : 0u;
+        }
+        qt.bp[r] = x;
+    } else if (tid < (u32)QBP + 8u) {
+        qt.bp[tid] = 0xFFFFFFFFu;
+    }
+    __syncthreads();
+    if (tid <= n_bp) { // symbol of each slot, from its smallest key
+        const u32 rep = tid ? qt.bp[tid - 1u] : 0u;
+        const u32 m = mag_of_key(rep);
+        qt.symtab[tid] = (u16)(m < tau_p ? 0u : m > tau_o ? 1u : 2u + boundaries_upto(rep));
+    }
+    __syncthreads();
+}
+
+// Breakpoints at or below the key, by bisection.
+__device__ __forceinline__ u32 slot_of_key(const u32 *bp, u32 n_bp, u32 key)
+{
+    u32 s = 0u;
+#pragma unroll
+    for (u32 step = 256u; step > 0u; step >>= 1)
+        if (s + step <= n_bp && bp[s + step - 1u] <= key) s += step;
+    return s;
+}
+
+// How the symbol of a key is found.  BINS: the search's equal-population bins; building the table
+// of 32768 bins costs a workgroup about 40 us, so it is for long runs of tiles.  CELLS: cells of the
+// key's upper 14 bits, each with its first breakpoint and their number (a dozen of them in the
+// densest cells: a few bisection steps); the table takes 4 us.
+constexpr int Q_BINS = 0, Q_CELLS = 1;
+constexpr int QUANT_CELL_TILES = 16; // most tiles of a run classified by cells (4 .. 40 are alike; 100 costs 20 %)
+constexpr int CELL_SHIFT = 18, CELLS = 1 << (32 - CELL_SHIFT);
+constexpr u32 CELL_MANY = 63u; // number field of a cell: this many or more
+
+template <bool FULL, int MODE>
 __device__ __forceinline__ void classify_tile(const float (&v)[16], u32 mask, const u32 *T,
                                               const u16 *symt, const QuantTables &qt, u32 n_bp, u32 w,
                                               unsigned long long *pk, u32 *wcnt, u32 &omask,
@@ -96,23 +115,34 @@ __device__ __forceinline__ void classify_tile(const float (&v)[16], u32 mask, co
 #pragma unroll
         for (int c = 0; c < 4; c++) {
             key[c] = key_of_float(v[4 * j + c]);
-            e[c] = T[key[c] >> COARSE_SHIFT];
+            e[c] = MODE == Q_BINS ? T[key[c] >> COARSE_SHIFT] : (u32)symt[key[c] >> CELL_SHIFT];
         }
+        if (MODE == Q_BINS) {
 #pragma unroll
-        for (int c = 0; c < 4; c++) e[c] = lookup_u16(symt, key[c], e[c]);
+            for (int c = 0; c < 4; c++) e[c] = lookup_u16(symt, key[c], e[c]);
+        }
         u32 lo32 = 0u, s3 = 0u;
 #pragma unroll
         for (int c = 0; c < 4; c++) {
             u32 sym = e[c];
             if (sym & 0x8000u) { // the bin holds breakpoints: count those at or below the key
-                u32 s = sym & 0x7fffu;
-                if (qt.bp[s] <= key[c]) { // (the bin's first breakpoint exists: s < n_bp)
-                    s++;
-                    if (qt.bp[s] <= key[c]) { // many equal values put many breakpoints into one bin
+                u32 s;
+                if (MODE == Q_BINS) {
+                    s = sym & 0x7fffu;
+                    if (qt.bp[s] <= key[c]) { // (the bin's first breakpoint exists: s < n_bp)
                         s++;
-                        for (u32 step = 256u; step > 0u; step >>= 1)
-                            if (s + step <= n_bp && qt.bp[s + step - 1u] <= key[c]) s += step;
+                        if (qt.bp[s] <= key[c]) { // many equal values put many breakpoints into one bin
+                            s++;
+                            for (u32 step = 256u; step > 0u; step >>= 1)
+                                if (s + step <= n_bp && qt.bp[s + step - 1u] <= key[c]) s += step;
+                        }
                     }
+                } else {
+                    s = sym & 511u;
+                    const u32 m = (sym >> 9) & CELL_MANY; // breakpoints of the cell
+                    const u32 end = m == CELL_MANY ? n_bp : s + m;
+                    for (u32 step = m == CELL_MANY ? 256u : 1u << (31u - (u32)__clz((int)m)); step > 0u; step >>= 1)
+                        if (s + step <= end && qt.bp[s + step - 1u] <= key[c]) s += step;
                 }
                 sym = qt.symtab[s];
             }
@@ -134,15 +164,164 @@ __device__ __forceinline__ void classify_tile(const float (&v)[16], u32 mask, co
         const u32 cj = __popc((omask >> (4 * j)) & 0xFu);
         u32 tot = 0u;
         pre[j] = 0u;
-        if (__ballot(cj != 0u)) {
-            const u64 m0 = __ballot(cj & 1u), m1 = __ballot(cj & 2u), m2 = __ballot(cj & 4u);
-            pre[j] = __builtin_amdgcn_mbcnt_hi((u32)(m0 >> 32), __builtin_amdgcn_mbcnt_lo((u32)m0, 0u)) +
-                     2u * __builtin_amdgcn_mbcnt_hi((u32)(m1 >> 32), __builtin_amdgcn_mbcnt_lo((u32)m1, 0u)) +
-                     4u * __builtin_amdgcn_mbcnt_hi((u32)(m2 >> 32), __builtin_amdgcn_mbcnt_lo((u32)m2, 0u));
-            tot = (u32)__popcll(m0) + 2u * (u32)__popcll(m1) + 4u * (u32)__popcll(m2);
-        }
+        if (__ballot(cj != 0u)) tot = rank_counts(cj, pre[j]);
         if (lane == 0u) wcnt[j * 16 + (tid >> 6)] = tot;
     }
+}
+
+__device__ __forceinline__ void store_protected(const QDesc &q, u64 pos, u32 index, float x)
+{
+    if (pos >= q.out_cap) return;
+    gptr(q.out_idx)[pos] = index;
+    if (q.val_bf16) { // upper 16 bits, rounded to nearest even
+        const u32 b = __float_as_uint(x);
+        ((GLOBAL_AS u16 *)gptr(q.out_val))[pos] = (u16)((b + 0x7FFFu + ((b >> 16) & 1u)) >> 16);
+    } else {
+        gptr(q.out_val)[pos] = x;
+    }
+}
+
+// What a quantized tensor's descriptor, boundaries and codebook are, by the whole workgroup.
+__device__ __forceinline__ void store_head(const QDesc &q, const TState *st, const GridDesc *gd, const u32 *tk,
+                                           const float *cb, u32 found, QInfo *qi)
+{
+    const u32 g = q.cfg, pair = gd->cfg_pair[g], K = gd->cfg_K[g], o = gd->pair_o[pair];
+    const u32 tid = threadIdx.x;
+    if (q.boundaries)
+        for (u32 j = 1 + tid; j < K; j += blockDim.x)
+            gptr(q.boundaries)[j - 1] = __uint_as_float(bits_of_key(tk[bnd_index(K, j)]));
+    for (u32 k = tid; k < K; k += blockDim.x) gptr(q.codebook)[k] = cb[k];
+    if (tid == 0) {
+        QInfo r;
+        r.n_pruned = st->pair_Pn[pair] + st->pair_Pp[pair];
+        r.n_outlier = st->pair_An[pair] + st->pair_Ap[pair];
+        r.n_kept = st->pair_M[pair];
+        r.tau_p = st->thr_mag[gd->pair_p[pair]];
+        r.tau_o = st->thr_mag[gd->n_p + o];
+        r.flags = 0u;
+        if ((u64)found != r.n_outlier) r.flags |= 1u;  // self-check
+        if (r.n_outlier > q.out_cap) r.flags |= 2u;    // caller buffer too small
+        *qi = r;
+    }
+}
+
+// per tensor: prefix of protected counts over its tiles, meta data, codebook / boundary copy
+__global__ __launch_bounds__(BLOCK) void k_qprep(const TDesc *__restrict__ td,
+                                                 const GridDesc *__restrict__ gd,
+                                                 const QDesc *__restrict__ qd,
+                                                 QInfo *__restrict__ qi, Bufs B)
+{
+    extern __shared__ u32 smem[]; // [32768 + 4]
+    __shared__ u32 tmp[BLOCK / 64 + 1];
+    const int i = blockIdx.x;
+    const QDesc q = qd[i];
+    if (q.packed == nullptr) return;
+    const int t = i;
+    const u32 tid = threadIdx.x;
+    const TDesc d = td[t];
+    const TState *st = B.ts + t;
+    const u32 g = q.cfg, pair = gd->cfg_pair[g], o = gd->pair_o[pair];
+    const u64 n_tiles = (d.n + TILE - 1) / TILE;
+    u32 carry = 0;
+    for (u64 base = 0; base < n_tiles; base += L2_BINS) {
+        const u64 left = n_tiles - base;
+        const int m = left < (u64)L2_BINS ? (int)left : L2_BINS;
+        for (int k = tid; k < m; k += BLOCK) smem[k] = B.tile_out[(d.tile0 + base + k) * MAX_FRAC + o];
+        __syncthreads();
+        u32 tot = block_excl_scan(smem, smem, m, tmp);
+        for (int k = tid; k < m; k += BLOCK) B.tile_off[d.tile0 + base + k] = carry + smem[k];
+        carry += tot;
+        __syncthreads();
+    }
+    // (boundary keys given from outside come as 256 entries, boundary j of K = 2^b at j * 256 / K - 1)
+    const u32 *tk = q.alt_key ? q.alt_key : B.tgt_key + (size_t)t * TGT_STRIDE + pair * NBT;
+    const float *cb = q.alt_cb ? q.alt_cb : B.codebook + ((size_t)t * gd->n_cfg + g) * CB_STRIDE;
+    store_head(q, st, gd, tk, cb, carry, qi + i);
+}
+
+// Small tensors (one tile at most): a workgroup each, no table, every symbol by bisection.
+constexpr int QS_NT = 512;                       // threads
+constexpr int QS_J = SMALL_MAX / (4 * QS_NT);    // groups of four values per thread
+__global__ __launch_bounds__(QS_NT) void k_qsmall(const TDesc *__restrict__ td, const GridDesc *__restrict__ gd,
+                                                  const QDesc *__restrict__ qd, QInfo *__restrict__ qi, Bufs B, int t0)
+{
+    __shared__ unsigned long long pk[PKW];
+    __shared__ QuantTables qt;
+    __shared__ u32 wc[64];
+    static_assert(QS_J * (QS_NT / 64) == 64, "one lane per (group, wave)");
+    static_assert(QS_NT >= QBP + 8, "one thread per breakpoint");
+    const int t = t0 + (int)blockIdx.x;
+    const QDesc q = qd[t];
+    if (q.packed == nullptr) return;
+    const TDesc d = td[t];
+    const TState *st = B.ts + t;
+    const u32 tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const u32 n = (u32)d.n;
+    const u32 g = q.cfg, pair = gd->cfg_pair[g], K = gd->cfg_K[g], w = symbol_bits(K);
+    const u32 tau_p = st->thr_mag[gd->pair_p[pair]], tau_o = st->thr_mag[gd->n_p + gd->pair_o[pair]];
+    const u32 *tk = q.alt_key ? q.alt_key : B.tgt_key + (size_t)t * TGT_STRIDE + pair * NBT;
+    const u32 n_words = (n * w + 63u) >> 6;
+    const u32 n_j = (n + 4u * QS_NT - 1u) / (4u * QS_NT);
+    float v[4 * QS_J];
+    const GLOBAL_AS float *src = gptr(d.data);
+#pragma unroll
+    for (int j = 0; j < QS_J; j++)
+#pragma unroll
+        for (int c = 0; c < 4; c++) {
+            const u32 i = 4u * (tid + (u32)QS_NT * j) + c;
+            v[4 * j + c] = i < n ? src[i] : 0.0f;
+        }
+    for (u32 k = tid; k < n_words + 1u && k < (u32)PKW; k += QS_NT) pk[k] = 0ull;
+    if (tid < 64u) wc[tid] = 0u;
+    make_breakpoints(qt, tk, K, tau_p, tau_o);
+    u32 omask = 0u, pre[QS_J];
+#pragma unroll
+    for (int j = 0; j < QS_J; j++) {
+        pre[j] = 0u;
+        if ((u32)j >= n_j) continue;
+        const u32 i0 = 4u * (tid + (u32)QS_NT * j);
+        u32 sym[4], key[4];
+#pragma unroll
+        for (int c = 0; c < 4; c++) key[c] = key_of_float(v[4 * j + c]);
+#pragma unroll
+        for (int c = 0; c < 4; c++) {
+            sym[c] = qt.symtab[slot_of_key(qt.bp, K + 3u, key[c])];
+            if (i0 + c >= n) sym[c] = 0u;
+        }
+        const unsigned long long piece = (unsigned long long)(sym[0] | (sym[1] << w) | (sym[2] << (2u * w))) |
+                                         ((unsigned long long)sym[3] << (3u * w));
+        const u32 bitoff = i0 * w, word = bitoff >> 6, shf = bitoff & 63u;
+        if (piece) {
+            atomicOr(&pk[word], piece << shf);
+            if (shf + 4u * w > 64u) atomicOr(&pk[word + 1u], piece >> (64u - shf));
+        }
+        u32 cj = 0u;
+#pragma unroll
+        for (int c = 0; c < 4; c++) {
+            omask |= (sym[c] == 1u ? 1u : 0u) << (4 * j + c);
+            cj += sym[c] == 1u ? 1u : 0u;
+        }
+        if (__ballot(cj != 0u)) {
+            const u32 tot = rank_counts(cj, pre[j]);
+            if (lane == 0u) wc[j * (QS_NT / 64) + wave] = tot;
+        }
+    }
+    __syncthreads();
+    for (u32 k = tid; k < n_words; k += QS_NT) gptr(q.packed)[k] = pk[k];
+    const u32 x = wc[lane], inc = wave_incl_scan(x), excl = inc - x; // ascending index: group, wave, lane
+    const u32 found = __builtin_amdgcn_readlane(inc, 63);
+    if (found) {
+#pragma unroll
+        for (int j = 0; j < QS_J; j++) {
+            u32 r = __builtin_amdgcn_readlane(excl, j * (QS_NT / 64) + wave) + pre[j];
+#pragma unroll
+            for (int c = 0; c < 4; c++)
+                if ((omask >> (4 * j + c)) & 1u)
+                    store_protected(q, r++, 4u * (tid + (u32)QS_NT * j) + c, v[4 * j + c]);
+        }
+    }
+    const float *cb = q.alt_cb ? q.alt_cb : B.codebook + ((size_t)t * gd->n_cfg + g) * CB_STRIDE;
+    store_head(q, st, gd, tk, cb, found, qi + t);
 }
 
 __global__ __launch_bounds__(BLOCK) void k_quant(const TDesc *__restrict__ td, int nT,
@@ -183,47 +362,25 @@ __global__ __launch_bounds__(BLOCK) void k_quant(const TDesc *__restrict__ td, i
         const u32 tau_p = st->thr_mag[gd->pair_p[pair]], tau_o = st->thr_mag[gd->n_p + o];
         const u32 nb2 = st->nb2;
         const u32 *tk = q.alt_key ? q.alt_key : B.tgt_key + (size_t)t * TGT_STRIDE + pair * NBT;
-        const u32 n_bnd = K - 1u, n_bp = n_bnd + 4u;
+        const u32 n_bp = K + 3u;
         __syncthreads();
-        for (u32 i = tid; i < (u32)COARSE; i += BLOCK) T[i] = entry_for_u16(B.table2[(size_t)t * COARSE + i]);
-        if (tid < n_bnd) qt.raw[tid] = tk[bnd_index(K, tid + 1u)];
-        if (tid < 4u) qt.raw[n_bnd + tid] = class_edge_key(tid, tau_p, tau_o);
-        __syncthreads();
-        if (tid < n_bp) { // sort by counting the smaller ones
-            const u32 x = qt.raw[tid];
-            u32 r = 0u;
-            for (u32 i = 0; i < n_bp; i++) {
-                const u32 y = qt.raw[i];
-                r += (y < x || (y == x && i < tid)) ? 1u : 0u;
+        const bool cells = stop - tile <= (u64)QUANT_CELL_TILES; // (the same for the whole workgroup)
+        if (!cells)
+            for (u32 i = tid; i < (u32)COARSE; i += BLOCK) T[i] = entry_for_u16(B.table2[(size_t)t * COARSE + i]);
+        make_breakpoints(qt, tk, K, tau_p, tau_o);
+        if (cells) { // first breakpoint of every cell and how many it holds, or its symbol
+            constexpr u32 PER = CELLS / BLOCK;
+            u32 s = slot_of_key(qt.bp, n_bp, tid * PER ? (tid * PER << CELL_SHIFT) - 1u : 0u); // (no breakpoint is key 0)
+            for (u32 i = 0; i < PER; i++) {
+                const u32 c = tid * PER + i, last = (c << CELL_SHIFT) | ((1u << CELL_SHIFT) - 1u);
+                u32 e = s;
+                if (s < n_bp && qt.bp[s] <= last) e = slot_of_key(qt.bp, n_bp, last);
+                const u32 m = e - s < CELL_MANY ? e - s : CELL_MANY;
+                symt[c] = m ? (u16)(0x8000u | (m << 9) | s) : qt.symtab[s];
+                s = e;
             }
-            qt.bp[r] = x;
-        } else if (tid < (u32)QBP + 8u) {
-            qt.bp[tid] = 0xFFFFFFFFu;
         }
-        __syncthreads();
-        if (tid <= n_bp) { // symbol of each slot, from its smallest key
-            const u32 rep = tid ? qt.bp[tid - 1u] : 0u;
-            const u32 m = mag_of_key(rep);
-            u32 sym;
-            if (m < tau_p) {
-                sym = 0u;
-            } else if (m > tau_o) {
-                sym = 1u;
-            } else {
-                u32 lo = 0u, hi = n_bnd; // #{boundaries <= rep}
-                while (lo < hi) {
-                    const u32 mid = (lo + hi) >> 1;
-                    if (qt.raw[mid] <= rep)
-                        lo = mid + 1u;
-                    else
-                        hi = mid;
-                }
-                sym = 2u + lo;
-            }
-            qt.symtab[tid] = (u16)sym;
-        }
-        __syncthreads();
-        for (u32 b = tid; b < nb2; b += BLOCK) { // symbol of every bin, or its first breakpoint
+        for (u32 b = cells ? nb2 : tid; b < nb2; b += BLOCK) { // symbol of every bin, or its first breakpoint
             u32 lo = 0u, hi = COARSE - 1u; // key prefix of the bin: last one that starts at or below it
             while (lo < hi) {
                 const u32 mid = (lo + hi + 1u) >> 1;
@@ -297,16 +454,7 @@ __global__ __launch_bounds__(BLOCK) void k_quant(const TDesc *__restrict__ td, i
                     for (int c = 0; c < 4; c++) {
                         const int i = 4 * j + c;
                         if ((omask_p >> i) & 1u) {
-                            const u64 pos = obase + r;
-                            if (pos < q.out_cap) {
-                                gptr(q.out_idx)[pos] = (u32)(e0 + 4u * (tid + 1024u * j) + c);
-                                if (q.val_bf16) { // upper 16 bits, rounded to nearest even
-                                    const u32 b = __float_as_uint(vp[i]);
-                                    ((GLOBAL_AS u16 *)gptr(q.out_val))[pos] = (u16)((b + 0x7FFFu + ((b >> 16) & 1u)) >> 16);
-                                } else {
-                                    gptr(q.out_val)[pos] = vp[i];
-                                }
-                            }
+                            store_protected(q, obase + r, (u32)(e0 + 4u * (tid + 1024u * j) + c), vp[i]);
                             r++;
                         }
                     }
@@ -334,10 +482,19 @@ __global__ __launch_bounds__(BLOCK) void k_quant(const TDesc *__restrict__ td, i
             ahead = tile + 1 < stop && d.aligned16 && tile_cnt(tile + 1) == (u32)TILE;
             if (ahead) load_tile_ahead(d, e0 + TILE, vn);
             u32 omask, pre[4];
-            if (cnt == (u32)TILE) // the same for every lane: the tile code uses ballots
-                classify_tile<true>(v, mask, T, symt, qt, n_bp, w, pk0 + buf * PKW, qt.wcnt[buf], omask, pre);
-            else
-                classify_tile<false>(v, mask, T, symt, qt, n_bp, w, pk0 + buf * PKW, qt.wcnt[buf], omask, pre);
+            unsigned long long *pkb = pk0 + buf * PKW;
+            // (whole tile or not is the same for every lane: the tile code uses ballots)
+            if (cells) {
+                if (cnt == (u32)TILE)
+                    classify_tile<true, Q_CELLS>(v, mask, T, symt, qt, n_bp, w, pkb, qt.wcnt[buf], omask, pre);
+                else
+                    classify_tile<false, Q_CELLS>(v, mask, T, symt, qt, n_bp, w, pkb, qt.wcnt[buf], omask, pre);
+            } else {
+                if (cnt == (u32)TILE)
+                    classify_tile<true, Q_BINS>(v, mask, T, symt, qt, n_bp, w, pkb, qt.wcnt[buf], omask, pre);
+                else
+                    classify_tile<false, Q_BINS>(v, mask, T, symt, qt, n_bp, w, pkb, qt.wcnt[buf], omask, pre);
+            }
             __syncthreads();
 #pragma unroll
             for (int i = 0; i < 16; i++) vp[i] = v[i];
@@ -362,8 +519,12 @@ hipError_t launch_quantize(const Batch &bt, const QDesc *qd, QInfo *qi, hipStrea
         if (e) return e;
         attr = true;
     }
-    PROF("k_qprep", s, k_qprep<<<bt.nT, BLOCK, (L2_BINS + 4) * 4, s>>>(bt.td, bt.gd, qd, qi, bt.bufs));
-    PROF("k_quant", s, k_quant<<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nT, bt.wg_tile0, bt.gd, qd, bt.bufs));
+    if (bt.nB) {
+        PROF("k_qprep", s, k_qprep<<<bt.nB, BLOCK, (L2_BINS + 4) * 4, s>>>(bt.td, bt.gd, qd, qi, bt.bufs));
+        PROF("k_quant", s, k_quant<<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nB, bt.wg_tile0, bt.gd, qd, bt.bufs));
+    }
+    if (bt.nT > bt.nB)
+        PROF("k_qsmall", s, k_qsmall<<<bt.nT - bt.nB, QS_NT, 0, s>>>(bt.td, bt.gd, qd, qi, bt.bufs, bt.nB));
     return hipGetLastError();
 }
 

@@ -435,37 +435,20 @@ __global__ __launch_bounds__(BLOCK) void k_final(const TDesc *__restrict__ td,
         r.n_pruned = st->pair_Pn[q] + st->pair_Pp[q];
         r.n_outlier = st->pair_An[q] + st->pair_Ap[q];
         r.n_kept = st->pair_M[q];
-        // payload model: log2 K bits per quantized value (in units of 2^-16, rounded up), 32 per
-        // protected value and per centre
-        r.cost_bits = ((r.n_kept * (u64)gd->cfg_l16[g] + 65535ull) >> 16) + 32ull * r.n_outlier + 32ull * (u64)K;
+        r.cost_bits = payload_bits(r.n_kept, r.n_outlier, K, gd->cfg_l16[g]);
         sc[g] = r;
         s_sse[g] = sse;
         s_cost[g] = r.cost_bits;
         if (r.n_pruned + r.n_outlier + r.n_kept != n) atomicOr(&st->internal_err, 256u);
     }
     __syncthreads();
-    if (tid == 0) { // Sec. 5: cheapest feasible configuration, else the most accurate one
-        bool have_f = false, have_a = false;
-        u32 best_f = 0, best_a = 0;
-        u64 best_cost = 0;
-        double best_sse = 0.0;
-        const double eps = gd->eps, sumsq = s_sumsq;
-        for (u32 g = 0; g < n_cfg; g++) {
-            const double sse = s_sse[g];
-            const double rel = (sumsq > 0.0) ? sse / sumsq : 0.0;
-            if (rel <= eps && (!have_f || s_cost[g] < best_cost)) {
-                have_f = true;
-                best_f = g;
-                best_cost = s_cost[g];
-            }
-            if (!have_a || sse < best_sse) {
-                have_a = true;
-                best_a = g;
-                best_sse = sse;
-            }
+    if (tid < 64u) {
+        const Choice c = choose_config(s_sse, s_cost, n_cfg, gd->eps, s_sumsq);
+        if (tid == 0u) {
+            st->best = c.best;
+            st->feasible = c.feasible;
+            store_result(st, B.res + t);
         }
-        st->best = have_f ? best_f : best_a;
-        st->feasible = have_f ? 1u : 0u;
     }
 }
 
@@ -487,15 +470,16 @@ hipError_t launch_edges(const Batch &bt, hipStream_t s)
 {
     hipError_t e = set_attrs();
     if (e) return e;
-    PROF("k_edges", s, k_edges<<<bt.nT, BLOCK, SM_EDGES, s>>>(bt.td, bt.gd, bt.bufs));
+    PROF("k_edges", s, k_edges<<<bt.nB, BLOCK, SM_EDGES, s>>>(bt.td, bt.gd, bt.bufs));
     return hipGetLastError();
 }
 
 hipError_t launch_score(const Batch &bt, hipStream_t s)
 {
+    if (bt.nB == 0) return hipSuccess;
     hipError_t e = set_attrs();
     if (e) return e;
-    PROF("k_final", s, k_final<<<bt.nT, BLOCK, SM_FINAL, s>>>(bt.td, bt.gd, bt.t_fu_off, bt.t_fu_ids, bt.bufs));
+    PROF("k_final", s, k_final<<<bt.nB, BLOCK, SM_FINAL, s>>>(bt.td, bt.gd, bt.t_fu_off, bt.t_fu_ids, bt.bufs));
     return hipGetLastError();
 }
 

@@ -852,7 +852,7 @@ __global__ __launch_bounds__(TSEL) void k_thr_pick(const TDesc *__restrict__ td,
 // plan 2: boundary ranks -> active bins -> groups of active bins
 // ------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(BLOCK) void k_plan2(const TDesc *__restrict__ td,
-                                                 const GridDesc *__restrict__ gd, Bufs B)
+                                                 const GridDesc *__restrict__ gd, Bufs B, bool light)
 {
     extern __shared__ u32 smem[];
     u32 *cum = smem; // [nb2 + 1]
@@ -1010,6 +1010,10 @@ __global__ __launch_bounds__(BLOCK) void k_plan2(const TDesc *__restrict__ td,
         st->cand_total = ctot;
         st->n_groups = n_groups;
         st->gshift = gshift;
+    }
+    if (light) { // (nothing follows)
+        __syncthreads();
+        if (tid == 0) store_result(st, B.res + t);
     }
     // (the pairs' boundaries lie NBT apart; those a grid does not use are never read)
 }
@@ -1370,32 +1374,6 @@ __device__ inline u32 block_select_range(Ptr a, u32 n, u32 klo, u32 khi, u32 k, 
         __syncthreads();
     }
     return klo + P;
-}
-
-// Stable rank of a key's digit among the keys its wave has seen in this pass.  ORDERED: one
-// returning LDS add (same-address LDS atomics are served in ascending lane order, verified when the
-// context is created).  Otherwise lanes with equal digits find each other with eight ballots.
-template <bool ORDERED>
-__device__ __forceinline__ u32 digit_rank(u32 *wcnt, u32 digit, bool valid)
-{
-    if (ORDERED) {
-        u32 r = 0u;
-        if (valid) r = atomicAdd(&wcnt[digit], 1u);
-        return r;
-    }
-    const u32 lane = threadIdx.x & 63u;
-    u64 peers = __ballot(valid);
-#pragma unroll
-    for (int b = 0; b < 8; b++) {
-        const bool bit = (digit >> b) & 1u;
-        const u64 m = __ballot(bit);
-        peers &= bit ? m : ~m;
-    }
-    const u32 rank = __popcll(peers & ((1ull << lane) - 1ull));
-    u32 old = 0u;
-    if (valid) old = wcnt[digit];
-    if (valid && rank == 0u) wcnt[digit] = old + (u32)__popcll(peers);
-    return old + rank;
 }
 
 struct GroupHead { // one (tensor, group) of the work list
@@ -1798,33 +1776,34 @@ hipError_t launch_select(const Batch &bt, hipStream_t s)
     hipError_t e = set_attrs();
     if (e) return e;
     const Bufs &B = bt.bufs;
-    PROF("k_hist1", s, (k_hist<1, false><<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nT, bt.wg_tile0, bt.wg_fu0, B)));
-    if (bt.any_pooled) PROF("k_pool_sum", s, k_pool_sum<<<bt.nT, BLOCK, 0, s>>>(bt.td, B));
-    PROF("k_plan1", s, k_plan1<false><<<bt.nT, BLOCK, SM_PLAN1, s>>>(bt.td, bt.gd, B));
-    PROF("k_hist2", s, (k_hist<2, false><<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nT, bt.wg_tile0, bt.wg_fu0, B)));
+    if (bt.nB == 0) return hipSuccess; // (only small tensors)
+    PROF("k_hist1", s, (k_hist<1, false><<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nB, bt.wg_tile0, bt.wg_fu0, B)));
+    if (bt.any_pooled) PROF("k_pool_sum", s, k_pool_sum<<<bt.nB, BLOCK, 0, s>>>(bt.td, B));
+    PROF("k_plan1", s, k_plan1<false><<<bt.nB, BLOCK, SM_PLAN1, s>>>(bt.td, bt.gd, B));
+    PROF("k_hist2", s, (k_hist<2, false><<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nB, bt.wg_tile0, bt.wg_fu0, B)));
     if (bt.any_sampled) {
         // tensors whose sweep 1 was sampled: exact figures from the second histogram; those whose
         // thresholds were mispredicted take the exact sweeps (the kernels skip all other tensors)
-        PROF("k_plan1b", s, k_plan1b<<<bt.nT, BLOCK, SM_PLAN2, s>>>(bt.td, bt.gd, B, bt.force_miss ? 1u : 0u));
-        PROF("k_hist1_redo", s, (k_hist<1, true><<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nT, bt.wg_tile0, bt.wg_fu0, B)));
-        PROF("k_plan1_redo", s, k_plan1<true><<<bt.nT, BLOCK, SM_PLAN1, s>>>(bt.td, bt.gd, B));
-        PROF("k_hist2_redo", s, (k_hist<2, true><<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nT, bt.wg_tile0, bt.wg_fu0, B)));
+        PROF("k_plan1b", s, k_plan1b<<<bt.nB, BLOCK, SM_PLAN2, s>>>(bt.td, bt.gd, B, bt.force_miss ? 1u : 0u));
+        PROF("k_hist1_redo", s, (k_hist<1, true><<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nB, bt.wg_tile0, bt.wg_fu0, B)));
+        PROF("k_plan1_redo", s, k_plan1<true><<<bt.nB, BLOCK, SM_PLAN1, s>>>(bt.td, bt.gd, B));
+        PROF("k_hist2_redo", s, (k_hist<2, true><<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nB, bt.wg_tile0, bt.wg_fu0, B)));
     }
-    PROF("k_thr_setup", s, k_thr_setup<<<bt.nT, TSEL, 0, s>>>(bt.td, B));
+    PROF("k_thr_setup", s, k_thr_setup<<<bt.nB, TSEL, 0, s>>>(bt.td, B));
     PROF("k_thr_count", s, k_thr_count<0><<<bt.n_units, TSEL, 0, s>>>(bt.td, bt.fu_tensor, B));
-    PROF("k_thr_pick", s, k_thr_pick<0><<<bt.nT, TSEL, 0, s>>>(bt.td, B));
+    PROF("k_thr_pick", s, k_thr_pick<0><<<bt.nB, TSEL, 0, s>>>(bt.td, B));
     PROF("k_thr_count", s, k_thr_count<1><<<bt.n_units, TSEL, 0, s>>>(bt.td, bt.fu_tensor, B));
-    PROF("k_thr_pick", s, k_thr_pick<1><<<bt.nT, TSEL, 0, s>>>(bt.td, B));
-    PROF("k_plan2", s, k_plan2<<<bt.nT, BLOCK, SM_PLAN2, s>>>(bt.td, bt.gd, B));
+    PROF("k_thr_pick", s, k_thr_pick<1><<<bt.nB, TSEL, 0, s>>>(bt.td, B));
+    PROF("k_plan2", s, k_plan2<<<bt.nB, BLOCK, SM_PLAN2, s>>>(bt.td, bt.gd, B, bt.light));
     if (bt.light) return hipGetLastError();
     if ((e = launch_edges(bt, s))) return e;
-    PROF("k_gather", s, k_gather<<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nT, bt.wg_tile0, bt.wg_fu0, bt.gd, B));
-    PROF("k_group_list", s, k_group_list<<<bt.nT, 256, 0, s>>>(bt.nT, B, bt.grp_list, bt.n_grp_total));
+    PROF("k_gather", s, k_gather<<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nB, bt.wg_tile0, bt.wg_fu0, bt.gd, B));
+    PROF("k_group_list", s, k_group_list<<<bt.nB, 256, 0, s>>>(bt.nB, B, bt.grp_list, bt.n_grp_total));
     PROF("k_split", s, k_split<<<dim3(bt.n_units, SPLIT_PARTS), BLOCK, SM_SPLIT, s>>>(bt.td, bt.fu_tensor, B));
     if (bt.lds_ordered)
-        PROF("k_bucket", s, k_bucket<true><<<bt.n_bucket_blocks, BB, SM_BUCKET, s>>>(bt.td, bt.nT, bt.grp_list, bt.n_grp_total, B));
+        PROF("k_bucket", s, k_bucket<true><<<bt.n_bucket_blocks, BB, SM_BUCKET, s>>>(bt.td, bt.nB, bt.grp_list, bt.n_grp_total, B));
     else
-        PROF("k_bucket_ballots", s, k_bucket<false><<<bt.n_bucket_blocks, BB, SM_BUCKET, s>>>(bt.td, bt.nT, bt.grp_list, bt.n_grp_total, B));
+        PROF("k_bucket_ballots", s, k_bucket<false><<<bt.n_bucket_blocks, BB, SM_BUCKET, s>>>(bt.td, bt.nB, bt.grp_list, bt.n_grp_total, B));
     return hipGetLastError();
 }
 

@@ -545,7 +545,12 @@ __global__ __launch_bounds__(BLOCK) void k_sketch_score(const TDesc *__restrict_
                 u32 slot = lookup_u16(sh.stab, key, sh.T[key >> COARSE_SHIFT]);
                 if (slot & 0x8000u) {
                     slot &= 0x7fffu;
-                    while (sh.edge[slot] <= key) slot++; // (the list ends with 0xFFFFFFFF, above every finite key)
+                    if (sh.edge[slot] <= key) slot++; // (the list ends with 0xFFFFFFFF, above every finite key)
+                    if (sh.edge[slot] <= key) { // a wide bin (small tensors, many equal values)
+                        slot++;
+                        for (u32 step = 256u; step > 0u; step >>= 1)
+                            if (slot + step <= (u32)SK_EDGES && sh.edge[slot + step - 1u] <= key) slot += step;
+                    }
                 }
                 atomicAdd(&sh.cnt[copy + slot], 1u);
                 atomicAdd(&sh.sx[copy + slot], (double)v[i]);
@@ -788,12 +793,12 @@ hipError_t launch_sketch(const Batch &bt, const SketchDesc *sd, const SketchPara
         PROF("k_sketch_hist", s, k_sketch_hist<true><<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nT, bt.wg_tile0, bt.wg_fu0,
                                                                               bt.gd, sd, P, bt.bufs));
     else
-        PROF("k_sketch_hist", s, k_sketch_hist<false><<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nT, bt.wg_tile0, bt.wg_fu0,
+        PROF("k_sketch_hist", s, k_sketch_hist<false><<<bt.n_wg_all, BLOCK, 0, s>>>(bt.td, bt.nT, bt.wg_tile0_all, nullptr,
                                                                                bt.gd, sd, P, bt.bufs));
     PROF("k_sketch_kmeans", s, k_sketch_kmeans<<<bt.nT, BLOCK, 0, s>>>(bt.gd, sd, P));
     if (P.multi) {
         PROF("k_sketch_score", s,
-             k_sketch_score<<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nT, bt.wg_tile0, bt.gd, sd, P, bt.bufs));
+             k_sketch_score<<<bt.n_wg_all, BLOCK, 0, s>>>(bt.td, bt.nT, bt.wg_tile0_all, bt.gd, sd, P, bt.bufs));
         PROF("k_sketch_choose", s,
              k_sketch_choose<<<bt.nT, 256, 0, s>>>(bt.td, bt.t_fu_off, bt.t_fu_ids, bt.gd, sd, P, bt.bufs));
     }
