@@ -213,7 +213,9 @@ int build_grid(const inshr_config *grid, uint32_t n_cfg, double eps, GridDesc &g
     memset(&g, 0, sizeof(g));
     g.n_cfg = n_cfg;
     g.eps = eps;
-    g.n_bnd = NB8;
+    g.n_all = NB8;
+    g.K_top = 1u;
+    bool used[NBT] = {};
     for (uint32_t i = 0; i < n_cfg; i++) {
         int rc = check_config(grid[i]);
         if (rc) return rc;
@@ -244,8 +246,14 @@ int build_grid(const inshr_config *grid, uint32_t n_cfg, double eps, GridDesc &g
         g.cfg_K[i] = K;
         g.cfg_bits[i] = symbol_bits(K) - 1u;
         g.cfg_l16[i] = (uint32_t)std::floor(std::log2((double)K) * 65536.0 + 0.5);
-        if (K & (K - 1u)) g.n_bnd = NBT; // 3, 6 or 12 bins: the twelfths are boundaries too
+        if (K & (K - 1u))
+            g.n_all = NBT; // 3, 6 or 12 bins: the twelfths are boundaries too
+        else
+            g.K_top = std::max(g.K_top, K);
+        for (uint32_t j = 1; j < K; j++) used[bnd_index(K, j)] = true;
     }
+    for (uint32_t i = 0; i < (uint32_t)NBT; i++)
+        if (used[i]) g.bnd[g.n_bnd++] = (u16)i;
     return INSHR_OK;
 }
 
@@ -401,13 +409,13 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         const size_t o_gsx = cv.take((size_t)nB * 2 * MAX_EDGES * 8);
         const size_t o_to = cv.take((size_t)all_tiles * MAX_FRAC * 4);
         const size_t o_ph1 = cv.take(any_pooled ? (size_t)nB * L1_BINS * 4 : 0);
+        const size_t o_ms = cv.take((size_t)nB * MAX_SUB * 8);
         const size_t zero_end = cv.off; // [o_ts, zero_end) is cleared before the sweeps
         const size_t o_psel = cv.take(any_pooled ? (size_t)nB * 2 * SEL_WORDS * 4 : 0);
         const size_t o_rs = cv.take(sizeof(SearchResult) * nT);
         const size_t o_tab = cv.take((size_t)nT * COARSE * 4);
         const size_t o_ut = cv.take((size_t)units * 16 * 4);
         const size_t o_bi = cv.take((size_t)nB * L2_BINS * 4);
-        const size_t o_cur = cv.take((size_t)nB * CURSOR_STRIDE * 4);
         const size_t o_tb = cv.take((size_t)nB * TGT_STRIDE * 4);
         const size_t o_tr = cv.take((size_t)nB * TGT_STRIDE * 4);
         const size_t o_tk = cv.take((size_t)nT * TGT_STRIDE * 4);
@@ -421,12 +429,10 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         const size_t o_gel = cv.take((size_t)nB * MAX_GROUPS * 4);
         const size_t o_geh = cv.take((size_t)nB * MAX_GROUPS * 4);
         const size_t o_sgc = cv.take((size_t)nB * MAX_EDGES * 4);
-        const size_t o_ms = cv.take((size_t)units * MAX_SUB * 8);
         const size_t o_sbc = cv.take((size_t)nB * MAX_SUB * 4);
         const size_t o_sbn = cv.take((size_t)nB * MAX_SUB * 4);
         const size_t o_cb = cv.take((size_t)nT * n_cfg * CB_STRIDE * 4);
         const size_t o_sc = cv.take((size_t)nT * n_cfg * sizeof(Score));
-        const size_t o_bt = cv.take((size_t)nB * n_cfg * CB_STRIDE * 8);
         const size_t o_uc = cv.take((size_t)units * 16 * 4);
         const size_t o_bg = cv.take((size_t)nB * L2_BINS * 2);
         const size_t o_go = cv.take((size_t)nB * MAX_GROUPS * 4);
@@ -499,7 +505,6 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         B.unit_thr = (u32 *)(db + o_ut);
         B.unit_capw = (const u32 *)(db + o_usb);
         B.binfo = (u32 *)(db + o_bi);
-        B.cursor2 = (u32 *)(db + o_cur);
         B.tgt_bin = (u32 *)(db + o_tb);
         B.tgt_res = (u32 *)(db + o_tr);
         B.tgt_key = (u32 *)(db + o_tk);
@@ -531,7 +536,6 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         B.sub_cnt = (u32 *)(db + o_sbn);
         B.codebook = (float *)(db + o_cb);
         B.scores = (Score *)(db + o_sc);
-        B.bin_term = (double *)(db + o_bt);
         c->res_off = o_rs;
         c->scores_off = o_sc;
     }

@@ -143,6 +143,17 @@ __host__ __device__ __forceinline__ void bnd_fraction(u32 i, u32 &num, u32 &den)
         den = 12u;
     }
 }
+// where a number of bins is kept among those a grid can name: log2 K, or 9, 10, 11 for 3, 6, 12
+constexpr int K_SLOTS = 12;
+__host__ __device__ __forceinline__ u32 k_slot(u32 K)
+{
+    if ((K & (K - 1u)) == 0u) {
+        u32 b = 0u;
+        while ((1u << b) < K) b++;
+        return b;
+    }
+    return K == 3u ? 9u : K == 6u ? 10u : 11u;
+}
 // width of a symbol stream with K bins: pruned, protected and K bins need K + 2 levels (Sec. 6)
 __host__ __device__ __forceinline__ u32 symbol_bits(u32 K)
 {
@@ -189,8 +200,11 @@ struct GridDesc {        // the configuration grid, decomposed
     u32 cfg_bits[MAX_CFG];                    // (meaningful for K = 2^bits only)
     u32 cfg_K[MAX_CFG];                       // number of bins
     u32 cfg_l16[MAX_CFG];                     // log2 K in units of 2^-16, rounded (payload model)
-    u32 n_bnd;                                // boundaries per pair in use: NB8, or NBT when some K is 3, 6 or 12
+    u32 n_bnd;                                // boundaries per pair that some K of the grid uses ...
+    u32 n_all;                                // NB8, or NBT when some K is 3, 6 or 12
+    u32 K_top;                                // largest power of two among the K (1: none)
     u32 pad;
+    u16 bnd[NBT + 1];                         // ... and which: their indices, ascending
     double eps;
 };
 
@@ -293,6 +307,17 @@ __device__ __forceinline__ u32 wave_incl_scan(u32 x)
     x += (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);
     return x;
 }
+__device__ __forceinline__ u32 wave_incl_max(u32 x) // the same for the maximum
+{
+    auto mx = [](u32 a, int b) { return a > (u32)b ? a : (u32)b; };
+    x = mx(x, __builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, true));
+    x = mx(x, __builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, true));
+    x = mx(x, __builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, true));
+    x = mx(x, __builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, true));
+    x = mx(x, __builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false));
+    x = mx(x, __builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false));
+    return x;
+}
 __device__ __forceinline__ u32 wave_or(u32 v)
 {
 #pragma unroll
@@ -386,48 +411,52 @@ __device__ __forceinline__ Choice choose_config(const double *sse, const u64 *co
     return r;
 }
 
+// First grid entry of every (pair, number of bins), 0xFFFF: none.  map: LDS, cleared to 0xFFFF, two
+// entries per word; the lowest index wins.
+__device__ __forceinline__ void enter_config(u16 (*map)[K_SLOTS], u32 g, u32 pair, u32 K)
+{
+    const u32 slot = k_slot(K), sh = (slot & 1u) * 16u;
+    u32 *w = reinterpret_cast<u32 *>(&map[pair][slot & ~1u]);
+    u32 old = *(volatile u32 *)w;
+    while (((old >> sh) & 0xFFFFu) > g) {
+        const u32 seen = atomicCAS(w, old, (old & ~(0xFFFFu << sh)) | (g << sh));
+        if (seen == old) break;
+        old = seen;
+    }
+}
+
 // Exclusive scan of in(0) .. in(n - 1) (n <= 32 * BLOCK) into out[0..n], out[n] = total; whole
 // workgroup of BLOCK threads; tmp is LDS scratch of BLOCK/64 + 1 words.  in may read out[i] only
 // at the index it is asked for.
+// Every wave owns a run of whole rows of 64 elements, so its reads and writes are consecutive (a run
+// of consecutive elements per thread meets one LDS bank in 16 or 32 lanes at once: 50 us for 32768
+// elements instead of 3).
 template <class F> __device__ inline u32 block_excl_scan_fn(F in, u32 *out, int n, u32 *tmp)
 {
-    const int t = threadIdx.x;
-    const int per = (n + BLOCK - 1) / BLOCK;
-    const int lo = t * per;
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = (int)__builtin_amdgcn_readfirstlane((u32)t >> 6);
+    const int rows = (n + BLOCK - 1) / BLOCK;
+    const int base = wave * rows * 64 + lane;
     u32 s = 0;
-    for (int i = 0; i < per; i++) {
-        int idx = lo + i;
-        if (idx < n) s += in(idx);
+#pragma unroll 8
+    for (int r = 0; r < rows; r++) {
+        const int i = base + r * 64;
+        if (i < n) s += in(i);
     }
-    // inclusive scan of s across the wave
-    u32 inc = s;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        u32 v = __shfl_up(inc, o);
-        if ((t & 63) >= o) inc += v;
-    }
-    if ((t & 63) == 63) tmp[t >> 6] = inc;
+    const u32 inc_s = wave_incl_scan(s);
+    if (lane == 63) tmp[wave] = inc_s;
     __syncthreads();
-    if (t == 0) {
-        u32 run = 0;
-        for (int w = 0; w < BLOCK / 64; w++) {
-            u32 v = tmp[w];
-            tmp[w] = run;
-            run += v;
-        }
-        tmp[BLOCK / 64] = run;
+    const u32 wt = wave_incl_scan(lane < BLOCK / 64 ? tmp[lane] : 0u);
+    const u32 total = __builtin_amdgcn_readlane(wt, BLOCK / 64 - 1);
+    u32 carry = wave ? (u32)__builtin_amdgcn_readlane(wt, wave - 1) : 0u;
+#pragma unroll 4
+    for (int r = 0; r < rows; r++) {
+        const int i = base + r * 64;
+        const u32 v = i < n ? in(i) : 0u;
+        const u32 inc = wave_incl_scan(v);
+        if (i < n) out[i] = carry + inc - v;
+        carry += (u32)__builtin_amdgcn_readlane(inc, 63);
     }
-    __syncthreads();
-    u32 base = tmp[t >> 6] + inc - s;
-    for (int i = 0; i < per; i++) {
-        int idx = lo + i;
-        if (idx < n) {
-            u32 v = in(idx);
-            out[idx] = base;
-            base += v;
-        }
-    }
-    u32 total = tmp[BLOCK / 64];
     if (t == 0) out[n] = total;
     __syncthreads();
     return total;

@@ -4,7 +4,6 @@
 
 namespace inshr {
 
-constexpr int CURSOR_STRIDE = L2_BINS + 64; // per-tensor stride of the gather cursors
 constexpr int TGT_STRIDE = 4096;            // per-tensor stride of boundary targets (15 * NBT fits)
 constexpr int SQ_STRIDE = MAX_FRAC + 1;     // partial sums of squares per (workgroup, tensor) unit
 constexpr int SEL_WORDS = MAX_THR * 1024;    // a tensor's selection histograms ([slot][sign][512])
@@ -24,7 +23,6 @@ struct Bufs { // device pointers, indexed by the tensor's position on the device
     u32 *unit_thr;   // [units][16] threshold-bucket keys each wave of the unit gathered
     u32 *hist2;     // [nT][32768]
     u32 *binfo;     // [nT][32768] offset of an active bin's elements in the gather pool, or INACTIVE
-    u32 *cursor2;   // [nT][CURSOR_STRIDE]
     u32 *tgt_bin;   // [nT][TGT_STRIDE] boundary i of pair q at q*NBT + i
     u32 *tgt_res;
     u32 *tgt_key;   // results: boundary keys
@@ -55,11 +53,10 @@ struct Bufs { // device pointers, indexed by the tensor's position on the device
     u32 *seg_cnt;   // [nT][MAX_EDGES] keys per slot that lie in bins without an edge
     u32 *grp_cnt;   // [nT][2][MAX_EDGES] keys per slot from the group of the slot's lower / upper edge
     double *grp_sx; // [nT][2][MAX_EDGES] ... and their sums
-    u64 *mom_sx;    // [units][MAX_SUB] per sub-slot: sum of the 23 mantissa bits over the unit's keys in
-                    // bins without an edge
+    u64 *mom_sx;    // [nT][MAX_SUB] per sub-slot: sum of the 23 mantissa bits over the keys in bins
+                    // without an edge
     float *codebook; // [nT][n_cfg][CB_STRIDE]
     Score *scores;  // [nT][n_cfg]
-    double *bin_term; // [nT][n_cfg][CB_STRIDE] per-bin 2cS - nc^2
     u32 *tile_off;  // [tiles] exclusive prefix of protected values per tensor (quantize)
 };
 

@@ -18,226 +18,296 @@ namespace inshr {
 // ------------------------------------------------------------------------------------------
 // edge order; for every bin without an edge its slot, and the keys per slot in such bins
 // ------------------------------------------------------------------------------------------
+// One workgroup per tensor, bound by the latency of its steps.  The edges are put in order by a
+// radix sort of their ranks (a bitonic sort of 4096 words, lane exchanges and all, took two thirds of
+// the kernel), slots and sub-slots of the bins come from scans over the bins (two bisections per bin
+// took the rest): 1 Mi values, 6 pairs: 200 -> 45 us.
+constexpr int EROWS = MAX_EDGES / BLOCK; // edges per thread
+struct EdgeShared {
+    u32 below[MAX_EDGES];                // sort: keys below the edge; afterwards the bin of each edge, in order
+    u16 item[MAX_EDGES];                 // sort: edge item; afterwards the group of each edge's bin
+    u32 wcount[(BLOCK / 64) * 256];      // sort: digit counters
+    u16 mark[L2_BINS + 64];              // per bin: edges in lower bins + 1 where that changes | 0x8000 where
+                                         // the exponent changes
+    u32 segc[MAX_EDGES];                 // keys per slot in bins without an edge
+    u32 subc[MAX_SUB];                   // ... per sub-slot
+};
+
+template <bool ORDERED>
 __global__ __launch_bounds__(BLOCK) void k_edges(const TDesc *__restrict__ td,
-                                                 const GridDesc *__restrict__ gd, Bufs B)
+                                                 const GridDesc *__restrict__ gd, Bufs B, u32 *__restrict__ grp_list,
+                                                 u32 *__restrict__ n_grp_total)
 {
-    extern __shared__ u32 smem[];
-    u64 *srt = reinterpret_cast<u64 *>(smem); // [4096] sort word, see below
-    u32 *ebin = smem + 2 * MAX_EDGES;         // [4096] bin of each edge, in order
-    u32 *segc = ebin + MAX_EDGES;             // [4096] keys per slot in bins without an edge
+    extern __shared__ double sm_edges[];
+    EdgeShared &sh = *reinterpret_cast<EdgeShared *>(sm_edges);
+    __shared__ u32 ckey[MAX_PAIRS * 4], wsum[4], s_at, s_err;
+    __shared__ u32 w_E[BLOCK / 64], w_X[BLOCK / 64], w_P[BLOCK / 64];
 
     const int t = blockIdx.x;
-    const u32 tid = threadIdx.x;
+    const u32 tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     TState *st = B.ts + t;
     const u64 n = td[t].n, n_neg = st->n_neg;
     const u32 n_pairs = gd->n_pairs, n_p = gd->n_p;
-    // edge items: pair q has the boundaries q * EPP + 0 .. n_bnd - 1 and the class edges
-    // q * EPP + NBT .. NBT + 3; the list holds n_e = n_pairs * (n_bnd + 4) of them
-    const u32 n_bnd = gd->n_bnd, epp = n_bnd + 4u;
-    const u32 n_e = n_pairs * epp;
+    // edge items: pair q has the boundaries q * EPP + (index) and the class edges q * EPP + NBT ..
+    // NBT + 3; the list holds n_e = n_pairs * (n_bnd + 4) of them
+    const u32 n_bnd = gd->n_bnd, n_c = 4u * n_pairs;
+    const u32 n_e = n_pairs * n_bnd + n_c;
     const u32 nb2 = st->nb2, zbin = st->zbin;
+    const u32 G = st->pool_overflow ? 0u : st->n_groups; // (overflow: nothing valid to sort)
     const u32 *tb = B.tgt_bin + (size_t)t * TGT_STRIDE;
     const u32 *trank = B.tgt_rank + (size_t)t * TGT_STRIDE;
     const u32 *tab = B.table2 + (size_t)t * COARSE;
     const u32 *binfo = B.binfo + (size_t)t * L2_BINS;
     const u32 *h2 = B.hist2 + (size_t)t * L2_BINS;
     const u16 *gtab = B.bin_group + (size_t)t * L2_BINS;
+    u32 *elo = B.grp_elo + (size_t)t * MAX_GROUPS;
+    u32 *ehi = B.grp_ehi + (size_t)t * MAX_GROUPS;
+    u32 *sub_code = B.sub_code + (size_t)t * MAX_SUB;
 
-    // Sort word: (keys below the edge << 1 | is boundary) << 18 | order of the key among the class
-    // edges << 12 | item.  Class edges with the same number of keys below them have no key between
-    // them, but they may lie in different bins, so they are put in key order.
-    __shared__ u32 ckey[MAX_PAIRS * 4];
-    if (tid < n_pairs * 4u)
+    if (tid < n_c)
         ckey[tid] = class_edge_key(tid & 3u, st->thr_mag[gd->pair_p[tid >> 2]],
                                    st->thr_mag[n_p + gd->pair_o[tid >> 2]]);
-    __syncthreads();
-    u64 w[MAX_EDGES / BLOCK]; // this thread's words: positions tid + m * BLOCK of the list
-#pragma unroll
-    for (int m = 0; m < MAX_EDGES / BLOCK; m++) {
-        const u32 i = tid + (u32)m * BLOCK;
-        u64 v = ~0ull;
-        if (i < n_e) {
-            const u32 q = i / epp, r = i % epp;
-            const u32 e = r < n_bnd ? r : (u32)NBT + (r - n_bnd);
-            u64 below, is_boundary, corder = 0ull;
-            if (e < (u32)NBT) {
-                below = trank[q * NBT + e];
-                is_boundary = 1ull;
-            } else {
-                const u32 me = q * 4u + (e - NBT), key = ckey[me];
-                for (u32 j = 0; j < n_pairs * 4u; j++)
-                    corder += (ckey[j] < key || (ckey[j] == key && j < me)) ? 1ull : 0ull;
-                switch (e - NBT) {
-                case 0: below = st->pair_An[q]; break;                 // keys < first quantized negative
-                case 1: below = n_neg - st->pair_Pn[q]; break;         // keys < first pruned
-                case 2: below = n_neg + st->pair_Pp[q]; break;         // keys < first quantized positive
-                default: below = n - st->pair_Ap[q]; break;            // keys < first protected positive
-                }
-                is_boundary = 0ull;
-            }
-            v = (((below << 1) | is_boundary) << 18) | (corder << 12) | (u64)(q * EPP + e);
-        }
-        w[m] = v;
+    if (tid == 0u) {
+        s_err = 0u;
+        if (G) s_at = atomicAdd(n_grp_total, G);
     }
-    // Bitonic sort.  Position i = tid + m * BLOCK: a partner i ^ j lies in the same thread for
-    // j >= BLOCK (registers), in the same wave for j < 64 (a lane exchange), and only for the strides
-    // in between in another wave (through LDS, two buffers in turn, one barrier per step): 18 of the
-    // 78 steps.  With a barrier after every step the sort took two thirds of this kernel.
+    for (u32 g = tid; g < st->n_groups; g += BLOCK) {
+        elo[g] = 0xFFFFFFFFu;
+        ehi[g] = 0u;
+    }
+    for (u32 i = tid; i < (L2_BINS + 64u) / 2u; i += BLOCK) reinterpret_cast<u32 *>(sh.mark)[i] = 0u;
+    for (u32 i = tid; i < (u32)MAX_EDGES; i += BLOCK) sh.segc[i] = 0u;
+    for (u32 i = tid; i < (u32)MAX_SUB; i += BLOCK) {
+        sh.subc[i] = 0u;
+        sub_code[i] = 0xFFFFFFFFu; // no bin has this sub-slot
+    }
+    __syncthreads();
+    // work list of the group sort: (tensor, group), in any order
+    for (u32 g = tid; g < G; g += BLOCK) grp_list[s_at + g] = ((u32)t << 13) | g;
+    // The class edges go first, in key order (several may have the same number of keys below them and
+    // still lie in different bins), then the boundaries; a stable sort by the number of keys below
+    // keeps a class edge before a boundary of equal rank.
+    if (tid < n_c) {
+        const u32 q = tid >> 2, key = ckey[tid];
+        u32 order = 0u;
+        for (u32 j = 0; j < n_c; j++) order += (ckey[j] < key || (ckey[j] == key && j < tid)) ? 1u : 0u;
+        u64 below;
+        switch (tid & 3u) {
+        case 0: below = st->pair_An[q]; break;                 // keys < first quantized negative
+        case 1: below = n_neg - st->pair_Pn[q]; break;         // keys < first pruned
+        case 2: below = n_neg + st->pair_Pp[q]; break;         // keys < first quantized positive
+        default: below = n - st->pair_Ap[q]; break;            // keys < first protected positive
+        }
+        sh.below[order] = (u32)below;
+        sh.item[order] = (u16)(q * EPP + (u32)NBT + (tid & 3u));
+    }
+    for (u32 w = tid; w < n_pairs * n_bnd; w += BLOCK) {
+        const u32 q = w / n_bnd, e = gd->bnd[w % n_bnd];
+        sh.below[n_c + w] = trank[q * NBT + e];
+        sh.item[n_c + w] = (u16)(q * EPP + e);
+    }
+    __syncthreads();
     {
-        u64 *buf[2] = {srt, reinterpret_cast<u64 *>(smem + 2 * MAX_EDGES)}; // (ebin and segc are not in use yet)
-        int cur = 0;
-        for (u32 k = 2; k <= (u32)MAX_EDGES; k <<= 1) {
-            for (u32 j = k >> 1; j > 0; j >>= 1) {
-                if (j >= (u32)BLOCK) {
-                    const u32 dm = j / BLOCK;
+        const u32 n_bits = 64u - (u32)__clzll((long long)n); // (keys below an edge: at most n < 2^32)
+        const u32 n_pass = (n_bits + 7u) >> 3;
+        const u32 dwidth = (n_bits + n_pass - 1u) / n_pass, dmask = (1u << dwidth) - 1u;
+        const u32 rows = (n_e + BLOCK - 1u) / BLOCK, chunk = rows * 64u;
+        u32 *wcnt = sh.wcount + wave * 256u;
+        for (u32 pass = 0; pass < n_pass; pass++) {
+            const u32 shift = pass * dwidth;
+            u32 kreg[EROWS], rreg[EROWS];
+            u16 ireg[EROWS];
+            for (u32 i = lane; i < 256u; i += 64u) wcnt[i] = 0u; // (a wave's own row: its operations stay in order)
 #pragma unroll
-                    for (u32 m = 0; m < (u32)(MAX_EDGES / BLOCK); m++) {
-                        const u32 mm = m ^ dm;
-                        if (mm > m) {
-                            const u32 i = tid + m * BLOCK;
-                            const bool up = (i & k) == 0u;
-                            const u64 a = w[m], b = w[mm];
-                            if ((a > b) == up) {
-                                w[m] = b;
-                                w[mm] = a;
-                            }
-                        }
+            for (u32 r = 0; r < (u32)EROWS; r++) {
+                kreg[r] = rreg[r] = 0u;
+                ireg[r] = 0;
+                if (r < rows) {
+                    const u32 i = wave * chunk + r * 64u + lane;
+                    const bool valid = i < n_e;
+                    if (valid) {
+                        kreg[r] = sh.below[i];
+                        ireg[r] = sh.item[i];
                     }
-                } else if (j < 64u) {
-#pragma unroll
-                    for (u32 m = 0; m < (u32)(MAX_EDGES / BLOCK); m++) {
-                        const u32 i = tid + m * BLOCK;
-                        const u64 a = w[m], b = __shfl_xor(a, (int)j);
-                        const bool keep_small = ((i & j) == 0u) == ((i & k) == 0u);
-                        w[m] = keep_small ? (a < b ? a : b) : (a > b ? a : b);
-                    }
-                } else {
-                    u64 *sb = buf[cur];
-#pragma unroll
-                    for (u32 m = 0; m < (u32)(MAX_EDGES / BLOCK); m++) sb[tid + m * BLOCK] = w[m];
-                    __syncthreads();
-#pragma unroll
-                    for (u32 m = 0; m < (u32)(MAX_EDGES / BLOCK); m++) {
-                        const u32 i = tid + m * BLOCK;
-                        const u64 a = w[m], b = sb[i ^ j];
-                        const bool keep_small = ((i & j) == 0u) == ((i & k) == 0u);
-                        w[m] = keep_small ? (a < b ? a : b) : (a > b ? a : b);
-                    }
-                    cur ^= 1; // (the next exchange writes the other buffer: no second barrier)
+                    rreg[r] = digit_rank<ORDERED>(wcnt, (kreg[r] >> shift) & dmask, valid);
                 }
             }
-        }
-        __syncthreads();
+            __syncthreads();
+            u32 tot = 0u, excl = 0u, cw[BLOCK / 64];
+            if (tid < 256u) {
 #pragma unroll
-        for (u32 m = 0; m < (u32)(MAX_EDGES / BLOCK); m++) srt[tid + m * BLOCK] = w[m];
-        __syncthreads();
+                for (u32 w = 0; w < (u32)(BLOCK / 64); w++) cw[w] = sh.wcount[w * 256u + tid];
+#pragma unroll
+                for (u32 w = 0; w < (u32)(BLOCK / 64); w++) tot += cw[w];
+                const u32 inc = wave_incl_scan(tot);
+                excl = inc - tot;
+                if (lane == 63u) wsum[wave] = inc;
+            }
+            __syncthreads();
+            if (tid < 256u) {
+                u32 run = excl;
+#pragma unroll
+                for (u32 w = 0; w < 3u; w++) run += w < wave ? wsum[w] : 0u; // (waves 0..3 scan)
+#pragma unroll
+                for (u32 w = 0; w < (u32)(BLOCK / 64); w++) {
+                    sh.wcount[w * 256u + tid] = run;
+                    run += cw[w];
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (u32 r = 0; r < (u32)EROWS; r++) { // (everything is in registers: the arrays are overwritten)
+                const u32 i = wave * chunk + r * 64u + lane;
+                if (r < rows && i < n_e) {
+                    const u32 at = wcnt[(kreg[r] >> shift) & dmask] + rreg[r];
+                    sh.below[at] = kreg[r];
+                    sh.item[at] = ireg[r];
+                }
+            }
+            __syncthreads();
+        }
     }
     u32 *E = B.edges + (size_t)t * MAX_EDGES;
     u32 *eb = B.edge_bin + (size_t)t * MAX_EDGES;
     u16 *ei = B.edge_item + (size_t)t * MAX_EDGES;
     u16 *pe = B.pair_eidx + (size_t)t * MAX_PAIRS * EIDX_STRIDE;
-    u32 *elo = B.grp_elo + (size_t)t * MAX_GROUPS;
-    u32 *ehi = B.grp_ehi + (size_t)t * MAX_GROUPS;
-    for (u32 pos = tid; pos < (u32)MAX_EDGES; pos += BLOCK) {
-        u32 bin = 0xFFFFFFFFu;
-        if (pos < n_e) {
-            const u32 item = (u32)(srt[pos] & 4095ull);
-            const u32 q = item / EPP, e = item % EPP;
-            u32 key = 0u; // a boundary's key is found later, from the gathered keys
-            if (e < (u32)NBT) {
-                bin = tb[q * NBT + e];
-                if (bin == RESOLVED) {
-                    bin = zbin;
-                    key = ZERO_KEY;
-                }
-            } else {
-                key = class_edge_key(e - NBT, st->thr_mag[gd->pair_p[q]], st->thr_mag[n_p + gd->pair_o[q]]);
-                bin = l2_bin(key, tab[key >> COARSE_SHIFT]);
+    for (u32 pos = tid; pos < n_e; pos += BLOCK) { // (each thread replaces the entries it has read)
+        const u32 item = sh.item[pos];
+        const u32 q = item / EPP, e = item % EPP;
+        u32 key = 0u, bin; // (a boundary's key is found later, from the gathered keys)
+        if (e < (u32)NBT) {
+            bin = tb[q * NBT + e];
+            if (bin == RESOLVED) {
+                bin = zbin;
+                key = ZERO_KEY;
             }
-            E[pos] = key;
-            eb[pos] = bin;
-            ei[pos] = (u16)item;
-            pe[q * EIDX_STRIDE + e] = (u16)pos;
+        } else {
+            key = ckey[q * 4u + (e - NBT)];
+            bin = l2_bin(key, tab[key >> COARSE_SHIFT]);
         }
-        ebin[pos] = bin;
-        segc[pos] = 0u;
+        E[pos] = key;
+        eb[pos] = bin;
+        ei[pos] = (u16)item;
+        pe[q * EIDX_STRIDE + e] = (u16)pos;
+        sh.below[pos] = bin;
+        sh.item[pos] = bin < nb2 ? gtab[bin] : (u16)0xFFFFu;
     }
-    for (u32 g = tid; g < (u32)MAX_GROUPS; g += BLOCK) {
-        elo[g] = 0xFFFFFFFFu;
-        ehi[g] = 0u;
-    }
+    // where the sign and exponent of the bins change (a table prefix is sign, exponent and three
+    // mantissa bits; every prefix has a bin of its own)
+    for (u32 k = 1u + tid; k < 512u; k += BLOCK) sh.mark[(tab[8u * k] >> 5) & 0x7fffu] = 0x8000u;
     __syncthreads();
     for (u32 pos = tid; pos < n_e; pos += BLOCK) {
-        const u32 bin = ebin[pos];
-        if (pos + 1u < n_e && ebin[pos + 1u] < bin) atomicOr(&st->internal_err, 512u);
-        const u32 g = (bin < nb2) ? gtab[bin] : 0xFFFFu;
-        if (g >= (u32)MAX_GROUPS) {
-            atomicOr(&st->internal_err, 512u);
-        } else {
-            atomicMin(&elo[g], pos);
-            atomicMax(&ehi[g], pos + 1u);
+        const u32 bin = sh.below[pos], g = sh.item[pos];
+        const bool last = pos + 1u == n_e;
+        const u32 nbin = last ? 0xFFFFFFFFu : sh.below[pos + 1u];
+        if (nbin < bin || g >= (u32)MAX_GROUPS) s_err = 1u;
+        // the bins behind this one have pos + 1 edges in lower bins
+        if (nbin != bin && bin + 1u < nb2) sh.mark[bin + 1u] = (u16)((sh.mark[bin + 1u] & 0x8000u) | (pos + 1u));
+        // groups are runs of bins, so their edges are runs of the list
+        if (g < (u32)MAX_GROUPS) {
+            if (pos == 0u || sh.item[pos - 1u] != g) elo[g] = pos;
+            if (last || sh.item[pos + 1u] != g) ehi[g] = pos + 1u;
         }
     }
+    __syncthreads();
     // Slot and sub-slot of every bin.  A bin without an edge lies inside one slot; sweep 3 adds the
     // mantissas of its keys as integers, which is exact and linear in the value only among keys of
     // one sign and exponent, so a slot is cut further wherever the exponent changes: sub-slot =
     // (edges in lower bins) + (key >> 23 of the bin).  Both terms grow with the bin, so the sum
     // names the pair; it stays below n_e + 512.
-    u32 *subc = smem;                 // [MAX_SUB] keys per sub-slot (the sort words are done with)
-    __shared__ u32 bfirst[512];       // first bin of every sign and exponent
-    __shared__ u32 s_err;
-    const u32 n_sub = n_e + 512u;
-    u32 *sub_code = B.sub_code + (size_t)t * MAX_SUB;
-    // (a table prefix is sign, exponent and three mantissa bits; every prefix has a bin of its own)
-    for (u32 k = tid; k < 512u; k += BLOCK) bfirst[k] = (tab[8u * k] >> 5) & 0x7fffu;
-    for (u32 i = tid; i < (u32)MAX_SUB; i += BLOCK) {
-        subc[i] = 0u;
-        sub_code[i] = 0xFFFFFFFFu; // no bin has this sub-slot
+    // Every wave walks a run of bins in rows of 64: edges in lower bins = largest mark so far,
+    // exponent = exponent marks so far, P = keys of the bins without an edge so far.  Where a slot
+    // (a sub-slot) begins, P is taken from its count and added to the one before.
+    constexpr u32 ROWS = L2_BINS / BLOCK;
+    const u32 rows = (nb2 + BLOCK - 1u) / BLOCK;
+    u32 pop[ROWS], actm = 0u; // keys of this lane's bins without an edge; its bins with one
+    u32 tE = 0u, tX = 0u, tP = 0u;
+#pragma unroll
+    for (u32 r = 0; r < ROWS; r++) {
+        pop[r] = 0u;
+        const u32 b = (wave * rows + r) * 64u + lane;
+        if (r < rows && b < nb2) {
+            const bool act = binfo[b] != INACTIVE;
+            const u32 c = h2[b];
+            pop[r] = act ? 0u : c;
+            actm |= (act ? 1u : 0u) << r;
+        }
     }
-    if (tid == 0) s_err = 0u;
+    for (u32 r = 0; r < rows; r++) {
+        const u32 b = (wave * rows + r) * 64u + lane;
+        const u32 m = b < nb2 ? (u32)sh.mark[b] : 0u;
+        tE = max(tE, m & 0x7fffu);
+        tX += (u32)__popcll(__ballot(m >> 15));
+    }
+#pragma unroll
+    for (u32 r = 0; r < ROWS; r++) tP += pop[r];
+    tE = wave_incl_max(tE);
+    tP = wave_incl_scan(tP);
+    if (lane == 63u) {
+        w_E[wave] = tE;
+        w_X[wave] = tX;
+        w_P[wave] = tP;
+    }
     __syncthreads();
+    u32 cE = 0u, cX = 0u, cP = 0u; // up to the bin before the row's first
+    for (u32 w = 0; w < wave; w++) {
+        cE = max(cE, w_E[w]);
+        cX += w_X[w];
+        cP += w_P[w];
+    }
     u16 *sl = B.sl + (size_t)t * (L2_BINS + 64);
-    u32 x = 0u;
-    for (u32 b = tid; b < nb2; b += BLOCK) {
-        const u32 bi = binfo[b], hb = h2[b]; // (in flight during the searches)
-        u32 lo = 0u, hi = n_e; // edges in lower bins
-        while (lo < hi) {
-            const u32 mid = (lo + hi) >> 1;
-            if (ebin[mid] < b)
-                lo = mid + 1u;
-            else
-                hi = mid;
+#pragma unroll
+    for (u32 r = 0; r < ROWS; r++) {
+        if (r >= rows) continue;
+        const u32 b = (wave * rows + r) * 64u + lane;
+        const bool in = b < nb2;
+        const u32 m = in ? (u32)sh.mark[b] : 0u;
+        const u64 xm = __ballot(m >> 15);
+        const u32 eM = max(wave_incl_max(m & 0x7fffu), cE);
+        const u32 xM = __builtin_amdgcn_mbcnt_hi((u32)(xm >> 32), __builtin_amdgcn_mbcnt_lo((u32)xm, cX)) + (m >> 15);
+        const u32 pI = wave_incl_scan(pop[r]) + cP, pE = pI - pop[r];
+        u32 ePrev = (u32)__shfl_up((int)eM, 1), xPrev = (u32)__shfl_up((int)xM, 1);
+        if (lane == 0u) {
+            ePrev = cE;
+            xPrev = cX;
         }
-        u32 xh = 511u; // last exponent whose first bin is <= b (not below that of the thread's last bin)
-        while (x < xh) {
-            const u32 mid = (x + xh + 1u) >> 1;
-            if (bfirst[mid] <= b)
-                x = mid;
-            else
-                xh = mid - 1u;
-        }
-        const u32 ss = lo + x;
-        if (bi != INACTIVE) {
-            sl[b] = 0xFFFFu;
-        } else if (ss >= (u32)MAX_SUB) {
-            s_err = 1u;
-            sl[b] = 0xFFFFu;
-        } else {
-            sl[b] = (u16)ss;
-            if (hb) {
-                atomicAdd(&segc[lo], hb);
-                if (atomicAdd(&subc[ss], hb) == 0u) sub_code[ss] = (lo << 9) | x; // first bin to arrive
+        const u32 ss = eM + xM, ssPrev = ePrev + xPrev;
+        if (in) {
+            const bool first = b == 0u;
+            if (ss >= (u32)MAX_SUB) {
+                s_err = 1u;
+                sl[b] = 0xFFFFu;
+            } else {
+                sl[b] = ((actm >> r) & 1u) ? (u16)0xFFFFu : (u16)ss;
+                if (first || ss != ssPrev) {
+                    atomicAdd(&sh.subc[ss], 0u - pE);
+                    if (!first) atomicAdd(&sh.subc[ssPrev], pE);
+                    sub_code[ss] = (eM << 9) | xM;
+                }
+                if (first || eM != ePrev) {
+                    atomicAdd(&sh.segc[eM], 0u - pE);
+                    if (!first) atomicAdd(&sh.segc[ePrev], pE);
+                }
+                if (b + 1u == nb2) {
+                    atomicAdd(&sh.subc[ss], pI);
+                    atomicAdd(&sh.segc[eM], pI);
+                }
             }
         }
+        cE = (u32)__builtin_amdgcn_readlane((int)eM, 63);
+        cX += (u32)__popcll(xm);
+        cP = (u32)__builtin_amdgcn_readlane((int)pI, 63);
     }
     __syncthreads();
     if (tid == 0 && s_err) atomicOr(&st->internal_err, 512u);
     u32 *sc = B.seg_cnt + (size_t)t * MAX_EDGES;
-    for (u32 i = tid; i <= n_e; i += BLOCK) sc[i] = segc[i];
+    for (u32 i = tid; i <= n_e; i += BLOCK) sc[i] = sh.segc[i];
     u32 *sub_cnt = B.sub_cnt + (size_t)t * MAX_SUB;
-    for (u32 i = tid; i < (u32)MAX_SUB; i += BLOCK) sub_cnt[i] = subc[i];
-    if (tid == 0) st->n_sub = min(n_sub, (u32)MAX_SUB);
-    if (tid == 0) st->n_edges = n_e;
+    for (u32 i = tid; i < (u32)MAX_SUB; i += BLOCK) sub_cnt[i] = sh.subc[i];
+    if (tid == 0) {
+        st->n_sub = min(n_e + 512u, (u32)MAX_SUB);
+        st->n_edges = n_e;
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -253,35 +323,39 @@ __global__ __launch_bounds__(BLOCK) void k_final(const TDesc *__restrict__ td,
     extern __shared__ u32 smem[];
     double *V = reinterpret_cast<double *>(smem);              // [4096] sum of each slot
     u64 *C = reinterpret_cast<u64 *>(smem + 2 * MAX_EDGES);    // [4096] keys in slots 0..s
-    double *S8 = reinterpret_cast<double *>(smem + 4 * MAX_EDGES); // [MAX_PAIRS][256] sums of 8-bit bins
+    double *S8 = reinterpret_cast<double *>(smem + 4 * MAX_EDGES); // [MAX_PAIRS][256] sums of a pair's bins
     double *SV = S8 + MAX_PAIRS * 256;                         // [MAX_SUB] sum of each sub-slot
     __shared__ double s_qout[MAX_FRAC];
     __shared__ double s_sumsq;
+    __shared__ __attribute__((aligned(4))) u16 s_cfg[MAX_PAIRS][K_SLOTS]; // first grid entry of (pair, K)
+    __shared__ double s_acc[MAX_PAIRS][K_SLOTS];
 
     const int t = blockIdx.x;
-    const u32 tid = threadIdx.x;
+    const u32 tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     TState *st = B.ts + t;
     const u64 n = td[t].n;
     const u32 m = st->n_edges;
     const u32 u0 = t_fu_off[t], u1 = t_fu_off[t + 1];
-    const u32 n_cfg = gd->n_cfg, n_p = gd->n_p, n_o = gd->n_o;
+    const u32 n_cfg = gd->n_cfg, n_p = gd->n_p, n_o = gd->n_o, n_pairs = gd->n_pairs;
 
     const u32 *segc = B.seg_cnt + (size_t)t * MAX_EDGES;
     const u32 *gc = B.grp_cnt + (size_t)t * 2 * MAX_EDGES;
     const double *gs = B.grp_sx + (size_t)t * 2 * MAX_EDGES;
+    for (u32 i = tid; i < (u32)MAX_PAIRS * (u32)K_SLOTS; i += BLOCK) (&s_cfg[0][0])[i] = 0xFFFFu;
     // Per slot: count and sum.  The counts are kept as inclusive prefixes over the slots (a bin is
     // a run of consecutive slots, so its count is a difference): every thread owns four consecutive
     // slots, the running totals of the threads before it come from a scan.  The sums are kept per
     // slot and added bin by bin: a difference of prefix sums would lose a bin of small values next
     // to large ones (fp64 carries 16 digits, fp32 values span 83).
     __shared__ u64 w_c[BLOCK / 64];
-    // Keys of bins without an edge: sweep 3 left, per unit and sub-slot, the sum of their 23 mantissa
-    // bits.  All keys of a sub-slot share sign and exponent E, so their values add up to
+    // Keys of bins without an edge: sweep 3 left, per sub-slot, the sum of their 23 mantissa bits.
+    // All keys of a sub-slot share sign and exponent E, so their values add up to
     // +-2^(E-150) (2^23 count + sum of mantissas), or +-2^-149 (sum) for E = 0; the integer is
     // below 2^51 and the conversion exact.
     const u32 n_sub = st->n_sub;
     const u32 *sub_code = B.sub_code + (size_t)t * MAX_SUB;
     const u32 *sub_cnt = B.sub_cnt + (size_t)t * MAX_SUB;
+    const u64 *mom = B.mom_sx + (size_t)t * MAX_SUB;
     // (first and last sub-slot of every slot: kept where the slot's sum goes afterwards)
     u32 *ss_lo = reinterpret_cast<u32 *>(V), *ss_hi = ss_lo + 1; // [2 * slot]
     for (u32 i = tid; i <= m; i += BLOCK) {
@@ -289,12 +363,12 @@ __global__ __launch_bounds__(BLOCK) void k_final(const TDesc *__restrict__ td,
         ss_hi[2u * i] = 0u;
     }
     __syncthreads();
+    for (u32 g = tid; g < n_cfg; g += BLOCK) enter_config(s_cfg, g, gd->cfg_pair[g], gd->cfg_K[g]);
     for (u32 ss = tid; ss < n_sub; ss += BLOCK) {
         const u32 code = sub_code[ss];
         double val = 0.0;
         if (code != 0xFFFFFFFFu) {
-            u64 tot = 0ull;
-            for (u32 u = u0; u < u1; u++) tot += B.mom_sx[(size_t)t_fu_ids[u] * MAX_SUB + ss];
+            const u64 tot = mom[ss];
             const u32 bx = code & 511u; // key >> 23: the top bit is set for values >= 0, else all bits are flipped
             const bool neg = (bx & 256u) == 0u;
             const int E = (int)((neg ? ~bx : bx) & 255u);
@@ -347,77 +421,115 @@ __global__ __launch_bounds__(BLOCK) void k_final(const TDesc *__restrict__ td,
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
             const u64 b = __shfl_up(inc_c, o);
-            if ((int)(tid & 63u) >= o) inc_c += b;
+            if ((int)lane >= o) inc_c += b;
         }
-        if ((tid & 63u) == 63u) w_c[tid >> 6] = inc_c;
+        if (lane == 63u) w_c[wave] = inc_c;
         __syncthreads();
         u64 base_c = inc_c - run_c;
-        for (u32 w = 0; w < (tid >> 6); w++) base_c += w_c[w];
+        for (u32 w = 0; w < wave; w++) base_c += w_c[w];
 #pragma unroll
         for (int r = 0; r < 4; r++) C[4u * tid + r] = base_c + pc[r];
     }
-    if (tid <= n_o) {
+    // sums of squares: wave 0 the tensor's, wave 1 + o the protected values' of fraction o; the units'
+    // parts in a fixed order
+    if (wave <= n_o) {
         double s = 0.0;
-        for (u32 u = u0; u < u1; u++) s += B.sq_part[(size_t)t_fu_ids[u] * SQ_STRIDE + tid];
-        if (tid == 0) {
-            s_sumsq = s;
-            st->sumsq = s;
-        } else {
-            s_qout[tid - 1] = s;
-            st->thr_sumsq[n_p + tid - 1] = s;
+        for (u32 u = u0 + lane; u < u1; u += 64u) s += B.sq_part[(size_t)t_fu_ids[u] * SQ_STRIDE + wave];
+        s = wave_sum_f64(s);
+        if (lane == 0u) {
+            if (wave == 0u) {
+                s_sumsq = s;
+                st->sumsq = s;
+            } else {
+                s_qout[wave - 1u] = s;
+                st->thr_sumsq[n_p + wave - 1u] = s;
+            }
         }
     }
     __syncthreads();
 
     const u16 *pe = B.pair_eidx + (size_t)t * MAX_PAIRS * EIDX_STRIDE;
-    // sums of the 8-bit bins of every pair, slot by slot; the bins for fewer bits are unions of them
-    for (u32 w = tid; w < gd->n_pairs * 256u; w += BLOCK) {
-        const u32 q = w >> 8, k = w & 255u;
+    // bin k of K: slots lo + 1 .. hi without those of the pruned gap (g_lo, g_hi]
+    struct Span {
+        u32 lo, hi, g_lo, g_hi;
+    };
+    auto span = [&](u32 q, u32 K, u32 k) -> Span {
         const u16 *e = pe + q * EIDX_STRIDE;
-        // bin k covers slots idx(lo)+1 .. idx(hi) without those of the pruned gap (g_lo, g_hi]
-        const u32 i_lo = (k == 0) ? e[NBT + 0] : e[k - 1u];
-        const u32 i_hi = (k == 255u) ? e[NBT + 3] : e[k];
-        const u32 g_lo = e[NBT + 1], g_hi = e[NBT + 2];
+        Span x;
+        x.lo = (k == 0u) ? e[NBT + 0] : e[bnd_index(K, k)];
+        x.hi = (k == K - 1u) ? e[NBT + 3] : e[bnd_index(K, k + 1u)];
+        x.g_lo = e[NBT + 1];
+        x.g_hi = e[NBT + 2];
+        return x;
+    };
+    auto slot_sum = [&](const Span &x) -> double {
         double sk = 0.0;
-        for (u32 i = i_lo + 1u; i <= min(i_hi, g_lo); i++) sk += V[i];
-        for (u32 i = max(i_lo, g_hi) + 1u; i <= i_hi; i++) sk += V[i];
-        S8[w] = sk;
+        for (u32 i = x.lo + 1u; i <= min(x.hi, x.g_lo); i++) sk += V[i];
+        for (u32 i = max(x.lo, x.g_hi) + 1u; i <= x.hi; i++) sk += V[i];
+        return sk;
+    };
+    // sums of the finest bins of every pair, slot by slot; the bins for fewer bits are unions of them
+    const u32 K_top = gd->K_top;
+    for (u32 w = tid; w < n_pairs * K_top; w += BLOCK) {
+        const u32 q = w / K_top, k = w % K_top;
+        if (K_top > 1u) S8[q * 256u + k] = slot_sum(span(q, K_top, k));
     }
     __syncthreads();
     const u32 *tk = B.tgt_key + (size_t)t * TGT_STRIDE;
     float *cb = B.codebook + (size_t)t * n_cfg * CB_STRIDE;
-    double *bt = B.bin_term + (size_t)t * n_cfg * CB_STRIDE;
-    // one work item per (configuration, bin)
-    for (u32 w = tid; w < n_cfg * (u32)CB_STRIDE; w += BLOCK) {
-        const u32 g = w / CB_STRIDE, k = w % CB_STRIDE;
-        const u32 K = gd->cfg_K[g];
-        if (k >= K) continue;
-        const u32 q = gd->cfg_pair[g];
-        const u16 *e = pe + q * EIDX_STRIDE;
-        // bin k covers keys [lo, hi): slots idx(lo)+1 .. idx(hi); the pruned gap [E2, E3) is left out
-        const u32 i_lo = (k == 0) ? e[NBT + 0] : e[bnd_index(K, k)];
-        const u32 i_hi = (k == K - 1u) ? e[NBT + 3] : e[bnd_index(K, k + 1u)];
-        const u32 g_lo = e[NBT + 1], g_hi = e[NBT + 2];
-        // slots i_lo+1 .. i_hi without those of the pruned gap (g_lo, g_hi]
-        u64 nk = C[i_hi] - C[i_lo];
-        const u32 a = max(i_lo, g_lo), b = min(i_hi, g_hi);
+    auto centre = [&](u32 q, u32 K, u32 k, u32 g, const Span &x, double sk) -> double { // returns 2 c S - n c^2
+        u64 nk = C[x.hi] - C[x.lo];
+        const u32 a = max(x.lo, x.g_lo), b = min(x.hi, x.g_hi);
         if (a < b) nk -= C[b] - C[a];
-        double sk = 0.0;
-        if ((K & (K - 1u)) == 0u) { // a union of 8-bit bins
-            const u32 per = 256u / K;
-            for (u32 j = 0; j < per; j++) sk += S8[q * 256u + k * per + j];
-        } else { // 3, 6 or 12 bins: slot by slot
-            for (u32 i = i_lo + 1u; i <= min(i_hi, g_lo); i++) sk += V[i];
-            for (u32 i = max(i_lo, g_hi) + 1u; i <= i_hi; i++) sk += V[i];
-        }
-        float c;
-        if (nk)
-            c = (float)(sk / (double)nk);
-        else
-            c = float_of_key(tk[q * NBT + bnd_index(K, k == 0 ? 1u : k)]);
+        const float c = nk ? (float)(sk / (double)nk) : float_of_key(tk[q * NBT + bnd_index(K, k == 0u ? 1u : k)]);
         cb[g * CB_STRIDE + k] = c;
         const double cd = (double)c;
-        bt[g * CB_STRIDE + k] = 2.0 * cd * sk - (double)nk * cd * cd;
+        return 2.0 * cd * sk - (double)nk * cd * cd;
+    };
+    // One wave per pair: 3, 6 and 12 bins first (the lanes of a bin share its slots), then K_top bins,
+    // half as many, ... 2: the sums of neighbours are added in place by the wave that reads them.
+    for (u32 q = wave; q < n_pairs; q += BLOCK / 64) {
+        for (u32 s = 9u; s < 12u; s++) {
+            const u32 g = s_cfg[q][s];
+            if (g == 0xFFFFu) continue;
+            const u32 K = 3u << (s - 9u), per = 64u / K; // lanes per bin
+            const u32 k = lane / per, part = lane % per;
+            double sk = 0.0, acc = 0.0;
+            Span x = {0u, 0u, 0u, 0u};
+            if (k < K) {
+                x = span(q, K, k);
+                for (u32 i = x.lo + 1u + part; i <= x.hi; i += per)
+                    if (i <= x.g_lo || i > x.g_hi) sk += V[i];
+            }
+            double tot = 0.0; // (a bin's lanes in a fixed order)
+            for (u32 j = 0; j < per; j++) tot += __shfl(sk, (int)min(k * per + j, 63u));
+            if (k < K && part == 0u) acc = centre(q, K, k, g, x, tot);
+            acc = wave_sum_f64(acc);
+            if (lane == 0u) s_acc[q][s] = acc;
+        }
+        for (u32 K = K_top; K >= 2u; K >>= 1) {
+            const u32 s = k_slot(K), g = s_cfg[q][s];
+            if (g != 0xFFFFu) {
+                double acc = 0.0;
+                for (u32 k = lane; k < K; k += 64u) acc += centre(q, K, k, g, span(q, K, k), S8[q * 256u + k]);
+                acc = wave_sum_f64(acc);
+                if (lane == 0u) s_acc[q][s] = acc;
+            }
+            asm volatile("" ::: "memory");
+            double f[2];
+#pragma unroll
+            for (u32 j = 0; j < 2u; j++) {
+                const u32 k = lane + 64u * j;
+                f[j] = k < K / 2u ? S8[q * 256u + 2u * k] + S8[q * 256u + 2u * k + 1u] : 0.0;
+            }
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (u32 j = 0; j < 2u; j++) {
+                const u32 k = lane + 64u * j;
+                if (k < K / 2u) S8[q * 256u + k] = f[j];
+            }
+            asm volatile("" ::: "memory");
+        }
     }
     __syncthreads();
     Score *sc = B.scores + (size_t)t * n_cfg;
@@ -425,9 +537,7 @@ __global__ __launch_bounds__(BLOCK) void k_final(const TDesc *__restrict__ td,
     __shared__ u64 s_cost[MAX_CFG];
     for (u32 g = tid; g < n_cfg; g += BLOCK) {
         const u32 K = gd->cfg_K[g], q = gd->cfg_pair[g];
-        double acc = 0.0;
-        for (u32 k = 0; k < K; k++) acc += bt[g * CB_STRIDE + k];
-        double sse = s_sumsq - s_qout[gd->pair_o[q]] - acc;
+        double sse = s_sumsq - s_qout[gd->pair_o[q]] - s_acc[q][k_slot(K)];
         if (sse < 0.0) sse = 0.0;
         Score r;
         r.sse = sse;
@@ -442,9 +552,9 @@ __global__ __launch_bounds__(BLOCK) void k_final(const TDesc *__restrict__ td,
         if (r.n_pruned + r.n_outlier + r.n_kept != n) atomicOr(&st->internal_err, 256u);
     }
     __syncthreads();
-    if (tid < 64u) {
+    if (wave == 0u) {
         const Choice c = choose_config(s_sse, s_cost, n_cfg, gd->eps, s_sumsq);
-        if (tid == 0u) {
+        if (lane == 0u) {
             st->best = c.best;
             st->feasible = c.feasible;
             store_result(st, B.res + t);
@@ -452,7 +562,7 @@ __global__ __launch_bounds__(BLOCK) void k_final(const TDesc *__restrict__ td,
     }
 }
 
-constexpr int SM_EDGES = (2 * MAX_EDGES + 2 * MAX_EDGES) * 4;
+constexpr int SM_EDGES = (int)sizeof(EdgeShared);
 constexpr int SM_FINAL = (2 * MAX_EDGES + 2 * MAX_EDGES) * 4 + MAX_PAIRS * 256 * 8 + MAX_SUB * 8;
 
 static bool g_attr_done = false;
@@ -460,7 +570,8 @@ static hipError_t set_attrs()
 {
     if (g_attr_done) return hipSuccess;
     hipError_t e;
-    if ((e = hipFuncSetAttribute((const void *)k_edges, hipFuncAttributeMaxDynamicSharedMemorySize, SM_EDGES))) return e;
+    if ((e = hipFuncSetAttribute((const void *)k_edges<true>, hipFuncAttributeMaxDynamicSharedMemorySize, SM_EDGES))) return e;
+    if ((e = hipFuncSetAttribute((const void *)k_edges<false>, hipFuncAttributeMaxDynamicSharedMemorySize, SM_EDGES))) return e;
     if ((e = hipFuncSetAttribute((const void *)k_final, hipFuncAttributeMaxDynamicSharedMemorySize, SM_FINAL))) return e;
     g_attr_done = true;
     return hipSuccess;
@@ -470,7 +581,10 @@ hipError_t launch_edges(const Batch &bt, hipStream_t s)
 {
     hipError_t e = set_attrs();
     if (e) return e;
-    PROF("k_edges", s, k_edges<<<bt.nB, BLOCK, SM_EDGES, s>>>(bt.td, bt.gd, bt.bufs));
+    if (bt.lds_ordered)
+        PROF("k_edges", s, k_edges<true><<<bt.nB, BLOCK, SM_EDGES, s>>>(bt.td, bt.gd, bt.bufs, bt.grp_list, bt.n_grp_total));
+    else
+        PROF("k_edges", s, k_edges<false><<<bt.nB, BLOCK, SM_EDGES, s>>>(bt.td, bt.gd, bt.bufs, bt.grp_list, bt.n_grp_total));
     return hipGetLastError();
 }
 

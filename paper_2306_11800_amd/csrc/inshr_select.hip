@@ -213,9 +213,11 @@ __global__ __launch_bounds__(BLOCK) void k_hist(const TDesc *__restrict__ td, in
 // ------------------------------------------------------------------------------------------
 __device__ __forceinline__ u32 depth_for(u32 nc, u64 target)
 {
-    u32 d = 0;
-    while (d < 20u && (u64)nc > (target << d)) d++;
-    return d;
+    // smallest d with nc <= target * 2^d: ceil(log2(ceil(nc / target)))
+    if ((u64)nc <= target) return 0u;
+    const u32 q = (nc - 1u) / (u32)target; // (target < nc: below 2^32)
+    const u32 d = 32u - (u32)__clz((int)q);
+    return d < 20u ? d : 20u;
 }
 
 // rank of threshold q: the floor(n * ppm / 1e6) smallest magnitudes are pruned, as many of the
@@ -236,6 +238,7 @@ __device__ __forceinline__ u32 cell_flags(u32 c, const u32 *jlo, const u32 *jhi,
         // magnitude bin j is first-level key bin 16384 + j for positive, 16383 - j for negative
         const u32 p0 = (u32)L1_MAGBINS + jlo[q], p1 = (u32)L1_MAGBINS + jhi[q];
         const u32 n0 = (u32)L1_MAGBINS - 1u - jhi[q], n1 = (u32)L1_MAGBINS - 1u - jlo[q];
+        if ((8u * c + 7u < p0 || 8u * c > p1) && (8u * c + 7u < n0 || 8u * c > n1)) continue;
         for (u32 i = 0; i < 8u; i++) {
             const u32 k = 8u * c + i;
             if ((k >= p0 && k <= p1) || (k >= n0 && k <= n1)) flag |= bucket_flag(k);
@@ -324,6 +327,7 @@ __global__ __launch_bounds__(BLOCK) void k_plan1(const TDesc *__restrict__ td,
     __shared__ u32 tmp[BLOCK / 64 + 1];
     __shared__ u32 s_j[MAX_THR], s_jlo[MAX_THR], s_jhi[MAX_THR], s_cn[MAX_THR], s_cp[MAX_THR];
     __shared__ u64 s_res[MAX_THR], s_bn[MAX_THR], s_bp[MAX_THR];
+    __shared__ u32 s_forced[BLOCK / 64];
 
     const int t = blockIdx.x;
     const u32 tid = threadIdx.x;
@@ -470,7 +474,29 @@ __global__ __launch_bounds__(BLOCK) void k_plan1(const TDesc *__restrict__ td,
         if (sampled && d < 3u && my_force[k]) d = 3u;
         return d;
     };
-    u64 lo = 1, hi = n;
+    // The total of the bins falls with the target.  A prefix of c elements takes at least c / target
+    // bins and fewer than 2 c / target + 1, or 8 more where it is resolved for a window.
+    u32 n_el = 0u, n_forced = 0u;
+#pragma unroll
+    for (int k = 0; k < COARSE / BLOCK; k++) {
+        n_el += nc[tid + BLOCK * k];
+        n_forced += sampled && my_force[k] ? 1u : 0u;
+    }
+    n_el = wave_sum(n_el);
+    n_forced = wave_sum(n_forced);
+    if ((tid & 63u) == 0u) {
+        tmp[tid >> 6] = n_el;
+        s_forced[tid >> 6] = n_forced;
+    }
+    __syncthreads();
+    n_el = n_forced = 0u;
+    for (int w = 0; w < BLOCK / 64; w++) {
+        n_el += tmp[w];
+        n_forced += s_forced[w];
+    }
+    const u32 room = (u32)L2_BINS - (u32)COARSE - 8u * n_forced;
+    u64 lo = n_el / (u32)L2_BINS ? n_el / (u32)L2_BINS : 1u, hi = n;
+    if (n_forced < 1024u) hi = 2ull * n_el / room + 1ull;
     while (lo < hi) {
         u64 mid = lo + ((hi - lo) >> 1);
         u32 s = 0;
@@ -851,16 +877,20 @@ __global__ __launch_bounds__(TSEL) void k_thr_pick(const TDesc *__restrict__ td,
 // ------------------------------------------------------------------------------------------
 // plan 2: boundary ranks -> active bins -> groups of active bins
 // ------------------------------------------------------------------------------------------
+// One workgroup per tensor: bound by the latency of its steps (1 Mi values, 6 pairs: 145 us with a run
+// of bins per thread in the scans and the marks in device memory, 30 us now).
 __global__ __launch_bounds__(BLOCK) void k_plan2(const TDesc *__restrict__ td,
                                                  const GridDesc *__restrict__ gd, Bufs B, bool light)
 {
     extern __shared__ u32 smem[];
-    u32 *cum = smem; // [nb2 + 1]
+    u32 *cum = smem;                  // [nb2 + 1] prefix of the bins' counts; then of the active bins' counts
+    u32 *T = smem + (L2_BINS + 4);    // [COARSE]
+    u32 *act = T + COARSE;            // [L2_BINS / 32] active bins
     __shared__ u32 tmp[BLOCK / 64 + 1];
     __shared__ u64 sAn[MAX_PAIRS], sMn[MAX_PAIRS], sPP[MAX_PAIRS], sM[MAX_PAIRS];
 
     const int t = blockIdx.x;
-    const u32 tid = threadIdx.x;
+    const u32 tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const TDesc d = td[t];
     const u64 n = d.n;
     TState *st = B.ts + t;
@@ -870,11 +900,8 @@ __global__ __launch_bounds__(BLOCK) void k_plan2(const TDesc *__restrict__ td,
     const u32 *h2 = B.hist2 + (size_t)t * L2_BINS;
     const u32 *tab = B.table2 + (size_t)t * COARSE;
     u32 *binfo = B.binfo + (size_t)t * L2_BINS;
-    u32 *cur = B.cursor2 + (size_t)t * CURSOR_STRIDE;
     const u32 n_pairs = gd->n_pairs, n_p = gd->n_p;
 
-    u32 total = block_excl_scan(h2, cum, (int)nb2, tmp);
-    if (tid == 0 && (u64)total != n) atomicOr(&st->internal_err, 16u);
     if (tid < n_pairs) {
         const u32 tp = gd->pair_p[tid], to = n_p + gd->pair_o[tid];
         const u64 n_neg = st->n_neg, n_pos = n - n_neg;
@@ -898,18 +925,28 @@ __global__ __launch_bounds__(BLOCK) void k_plan2(const TDesc *__restrict__ td,
             atomicOr(&st->pool_overflow, 8u);
         }
     }
-    for (u32 i = tid; i < nb2; i += BLOCK) binfo[i] = 0u;
-    __syncthreads();
+    if (light) { // (nothing follows: the sketch quantizer brings its own bins)
+        __syncthreads();
+        if (tid == 0) store_result(st, B.res + t);
+        return;
+    }
+    for (u32 i = tid; i < (u32)COARSE; i += BLOCK) T[i] = tab[i];
+    act[tid] = 0u;
+    static_assert(L2_BINS / 32 == BLOCK, "one word of the active bins per thread");
+    const u32 total = block_excl_scan(h2, cum, (int)nb2, tmp);
+    if (tid == 0 && (u64)total != n) atomicOr(&st->internal_err, 16u);
     const u32 n_bnd = gd->n_bnd;
     const u32 TG = n_pairs * n_bnd;
     u32 *tb = B.tgt_bin + (size_t)t * TGT_STRIDE;
     u32 *tr = B.tgt_res + (size_t)t * TGT_STRIDE;
     u32 *tk = B.tgt_key + (size_t)t * TGT_STRIDE;
     u32 *trank = B.tgt_rank + (size_t)t * TGT_STRIDE;
+    u32 *tlo = B.tgt_klo + (size_t)t * TGT_STRIDE; // key range of the boundary's bin
+    u32 *thi = B.tgt_khi + (size_t)t * TGT_STRIDE;
     for (u32 w = tid; w < TG; w += BLOCK) {
-        const u32 q = w / n_bnd, i = q * (u32)NBT + w % n_bnd; // boundary w % n_bnd of pair q
+        const u32 q = w / n_bnd, j = gd->bnd[w % n_bnd], i = q * (u32)NBT + j; // boundary j of pair q
         u32 num, den;
-        bnd_fraction(w % n_bnd, num, den);
+        bnd_fraction(j, num, den);
         const u64 M = sM[q];
         const u64 k = (u64)num * M / (u64)den;
         const u64 r = (k < sMn[q]) ? sAn[q] + k : sAn[q] + sPP[q] + k;
@@ -929,91 +966,116 @@ __global__ __launch_bounds__(BLOCK) void k_plan2(const TDesc *__restrict__ td,
             tk[i] = 0u;
             continue;
         }
-        u32 bin = lo - 1u;
+        const u32 bin = lo - 1u;
         u64 res = r - (u64)cum[bin];
+        atomicOr(&act[bin >> 5], 1u << (bin & 31u)); // the bin holds an edge: its keys are classified one by one
         if (bin == zbin && res < n_zero) {
             tb[i] = RESOLVED;
             tr[i] = 0u;
             tk[i] = ZERO_KEY;
-            binfo[bin] = 1u; // the bin holds an edge: its other keys are classified one by one
-        } else {
-            if (bin == zbin) res -= n_zero;
-            tb[i] = bin;
-            tr[i] = (u32)res;
-            binfo[bin] = 1u;
+            continue;
         }
+        if (bin == zbin) res -= n_zero;
+        tb[i] = bin;
+        tr[i] = (u32)res;
+        // last 12-bit prefix whose first bin is <= bin
+        lo = 0u;
+        hi = COARSE - 1;
+        while (lo < hi) {
+            const u32 mid = (lo + hi + 1) >> 1;
+            if (((T[mid] >> 5) & 0x7fffu) <= bin)
+                lo = mid;
+            else
+                hi = mid - 1;
+        }
+        const u32 e = T[lo], dd = e & 31u, sub = bin - ((e >> 5) & 0x7fffu);
+        const u32 klo = (lo << COARSE_SHIFT) | (sub << (COARSE_SHIFT - dd));
+        tlo[i] = klo;
+        thi[i] = klo + ((1u << (COARSE_SHIFT - dd)) - 1u);
     }
     // the bins of the class edges (first quantized / pruned / protected key of either sign) are
     // active too, so that every bin without an edge lies inside one slot
     for (u32 i = tid; i < n_pairs * 4u; i += BLOCK) {
         const u32 q = i >> 2;
         const u32 key = class_edge_key(i & 3u, st->thr_mag[gd->pair_p[q]], st->thr_mag[n_p + gd->pair_o[q]]);
-        binfo[l2_bin(key, tab[key >> COARSE_SHIFT])] = 1u;
+        const u32 bin = l2_bin(key, T[key >> COARSE_SHIFT]);
+        atomicOr(&act[bin >> 5], 1u << (bin & 31u));
     }
     __syncthreads();
-    // gathered population of every bin in bin order -> offset of the bin in that order
-    for (u32 i = tid; i < nb2; i += BLOCK)
-        cur[i] = binfo[i] ? (h2[i] - ((i == zbin) ? (u32)n_zero : 0u)) : 0u;
-    __syncthreads();
-    const u32 ctot = block_excl_scan(cur, cur, (int)nb2, tmp);
+    // gathered population of every bin in bin order -> offset of the bin in that order (the counts are
+    // the differences of the prefix they replace; a word's difference is taken before it goes)
+    const u32 ctot = [&] {
+        for (u32 base = 0; base < nb2; base += 8u * BLOCK) { // (a row of eight per thread, then a barrier)
+            u32 c[8];
+#pragma unroll
+            for (u32 j = 0; j < 8u; j++) {
+                const u32 i = base + j * BLOCK + tid;
+                c[j] = 0u;
+                if (i < nb2 && ((act[i >> 5] >> (i & 31u)) & 1u))
+                    c[j] = cum[i + 1u] - cum[i] - ((i == zbin) ? (u32)n_zero : 0u);
+            }
+            __syncthreads();
+#pragma unroll
+            for (u32 j = 0; j < 8u; j++) {
+                const u32 i = base + j * BLOCK + tid;
+                if (i < nb2) cum[i] = c[j];
+            }
+            __syncthreads();
+        }
+        return block_excl_scan(cum, cum, (int)nb2, tmp);
+    }();
     if (tid == 0 && (u64)ctot > d.pool_len) atomicOr(&st->pool_overflow, 2u); // no room for the keys in group order
     // groups: runs of active bins of about 2^gshift gathered keys; at most MAX_GROUPS per tensor
     u32 gshift = GROUP_SHIFT;
     while ((ctot >> gshift) >= (u32)MAX_GROUPS) gshift++;
     const u32 n_groups = ctot ? ((ctot - 1u) >> gshift) + 1u : 1u; // edges exist even without keys
-    u32 *goff = B.grp_off + d.tile0 * 0 + (size_t)t * MAX_GROUPS;
+    u32 *goff = B.grp_off + (size_t)t * MAX_GROUPS;
     u32 *gend = B.grp_end + (size_t)t * MAX_GROUPS;
     u32 *gcur = B.grp_cur + (size_t)t * MAX_GROUPS;
-    for (u32 g = tid; g < (u32)MAX_GROUPS; g += BLOCK) {
+    for (u32 g = tid; g < n_groups; g += BLOCK) {
         goff[g] = 0xFFFFFFFFu;
         gend[g] = 0u;
         gcur[g] = 0u;
     }
     __syncthreads();
+    // Every wave walks a run of bins.  The offsets of the active bins follow each other, so a group
+    // ends where the next one begins; only a wave's first and last active bin may share their group
+    // with another wave.
     u16 *gtab = B.bin_group + (size_t)t * L2_BINS;
-    for (u32 i = tid; i < nb2; i += BLOCK) {
-        if (binfo[i]) {
-            const u32 c = h2[i] - ((i == zbin) ? (u32)n_zero : 0u);
-            const u32 g = min(cur[i] >> gshift, n_groups - 1u); // an empty bin at the very end
-            atomicMin(&goff[g], cur[i]);
-            atomicMax(&gend[g], cur[i] + c);
-            gtab[i] = (u16)g;
-            binfo[i] = cur[i]; // offset of the bin's keys once they are in bin order
-        } else {
-            binfo[i] = INACTIVE;
-            gtab[i] = 0xFFFFu;
+    const u32 rows = (nb2 + BLOCK - 1u) / BLOCK;
+    u32 g_before = 0xFFFFFFFFu, last_end = 0u; // group of the wave's last active bin so far, where that bin ends
+    for (u32 r = 0; r < rows; r++) {
+        const u32 i = (wave * rows + r) * 64u + lane;
+        const bool in = i < nb2;
+        const bool on = in && ((act[(i < nb2 ? i : 0u) >> 5] >> (i & 31u)) & 1u);
+        const u32 off = in ? cum[i] : 0u, end = in ? cum[i + 1u] : 0u;
+        const u32 g = min(off >> gshift, n_groups - 1u); // (an empty bin at the very end)
+        const u64 m = __ballot(on);
+        if (in) {
+            binfo[i] = on ? off : INACTIVE; // offset of the bin's keys once they are in bin order
+            gtab[i] = on ? (u16)g : (u16)0xFFFFu;
         }
-    }
-    __syncthreads();
-    // per target: the key range of its bin
-    u32 *tlo = B.tgt_klo + (size_t)t * TGT_STRIDE;
-    u32 *thi = B.tgt_khi + (size_t)t * TGT_STRIDE;
-    for (u32 w = tid; w < TG; w += BLOCK) {
-        const u32 i = (w / n_bnd) * (u32)NBT + w % n_bnd;
-        const u32 bin = tb[i];
-        if (bin == RESOLVED) continue;
-        // last 12-bit prefix whose first bin is <= bin
-        u32 lo = 0, hi = COARSE - 1;
-        while (lo < hi) {
-            u32 mid = (lo + hi + 1) >> 1;
-            if (((tab[mid] >> 5) & 0x7fffu) <= bin)
-                lo = mid;
-            else
-                hi = mid - 1;
+        if (!m) continue; // (the same for the whole wave)
+        const u64 below = m & ((1ull << lane) - 1ull);
+        u32 gp = (u32)__shfl((int)g, below ? 63 - (int)__clzll((long long)below) : 0);
+        if (!below) gp = g_before;
+        if (on) {
+            if (gp == 0xFFFFFFFFu) {
+                atomicMin(&goff[g], off);
+            } else if (gp != g) {
+                goff[g] = off;
+                atomicMax(&gend[gp], off);
+            }
         }
-        const u32 e = tab[lo], dd = e & 31u, sub = bin - ((e >> 5) & 0x7fffu);
-        const u32 klo = (lo << COARSE_SHIFT) | (sub << (COARSE_SHIFT - dd));
-        tlo[i] = klo;
-        thi[i] = klo + ((1u << (COARSE_SHIFT - dd)) - 1u);
+        const int last = 63 - (int)__clzll((long long)m);
+        g_before = (u32)__builtin_amdgcn_readlane((int)g, last);
+        last_end = (u32)__builtin_amdgcn_readlane((int)end, last);
     }
+    if (lane == 0u && g_before != 0xFFFFFFFFu) atomicMax(&gend[g_before], last_end);
     if (tid == 0) {
         st->cand_total = ctot;
         st->n_groups = n_groups;
         st->gshift = gshift;
-    }
-    if (light) { // (nothing follows)
-        __syncthreads();
-        if (tid == 0) store_result(st, B.res + t);
     }
     // (the pairs' boundaries lie NBT apart; those a grid does not use are never read)
 }
@@ -1159,8 +1221,9 @@ __global__ __launch_bounds__(BLOCK) void k_gather(const TDesc *__restrict__ td, 
             B.unit_cand[(size_t)fu * 16 + wave] = gathered;
             if (overflow) atomicOr(&st->pool_overflow, 4u);
         }
-        u64 *gs = B.mom_sx + (size_t)fu * MAX_SUB;
-        for (u32 i = tid; i < n_slots; i += BLOCK) gs[i] = sx[i];
+        u64 *gs = B.mom_sx + (size_t)t * MAX_SUB; // (integers: the sum does not depend on the order)
+        for (u32 i = tid; i < n_slots; i += BLOCK)
+            if (sx[i]) atomicAdd((unsigned long long *)&gs[i], (unsigned long long)sx[i]);
         double *part = B.sq_part + (size_t)fu * SQ_STRIDE;
 #pragma unroll
         for (int o = 1; o <= MAX_FRAC; o++) {
@@ -1733,25 +1796,12 @@ __global__ __launch_bounds__(BB) void k_bucket(const TDesc *__restrict__ td, int
     }
 }
 
-// list of all (tensor, group) pairs of the batch (one workgroup per tensor; the order of the list
-// is the order in which the group sort takes them and does not matter)
-__global__ __launch_bounds__(256) void k_group_list(int nT, Bufs B, u32 *grp_list, u32 *n_grp_total)
-{
-    __shared__ u32 s_at;
-    const int t = blockIdx.x;
-    const u32 G = B.ts[t].pool_overflow ? 0u : B.ts[t].n_groups; // (overflow: nothing valid to sort)
-    if (G == 0u) return;
-    if (threadIdx.x == 0) s_at = atomicAdd(n_grp_total, G);
-    __syncthreads();
-    const u32 at = s_at;
-    for (u32 g = threadIdx.x; g < G; g += 256u) grp_list[at + g] = ((u32)t << 13) | g;
-}
-
 // ------------------------------------------------------------------------------------------
 // launch wrappers
 // ------------------------------------------------------------------------------------------
 constexpr int SM_PLAN1 = (2 * (L1_MAGBINS + 4) + COARSE + 4) * 4;
-constexpr int SM_PLAN2 = (L2_BINS + 4) * 4;
+constexpr int SM_PLAN1B = (L2_BINS + 4) * 4;
+constexpr int SM_PLAN2 = (L2_BINS + 4 + COARSE + L2_BINS / 32) * 4;
 constexpr int SM_SPLIT = (COARSE + 2 * MAX_GROUPS) * 4 + L2_BINS * 2;
 constexpr int SM_BUCKET = (2 * BUCKET_CAP + (BB / 64) * 256) * 4;
 
@@ -1763,7 +1813,7 @@ static hipError_t set_attrs()
     if ((e = hipFuncSetAttribute((const void *)k_plan1<false>, hipFuncAttributeMaxDynamicSharedMemorySize, SM_PLAN1))) return e;
     if ((e = hipFuncSetAttribute((const void *)k_plan1<true>, hipFuncAttributeMaxDynamicSharedMemorySize, SM_PLAN1))) return e;
     if ((e = hipFuncSetAttribute((const void *)k_plan2, hipFuncAttributeMaxDynamicSharedMemorySize, SM_PLAN2))) return e;
-    if ((e = hipFuncSetAttribute((const void *)k_plan1b, hipFuncAttributeMaxDynamicSharedMemorySize, SM_PLAN2))) return e;
+    if ((e = hipFuncSetAttribute((const void *)k_plan1b, hipFuncAttributeMaxDynamicSharedMemorySize, SM_PLAN1B))) return e;
     if ((e = hipFuncSetAttribute((const void *)k_split, hipFuncAttributeMaxDynamicSharedMemorySize, SM_SPLIT))) return e;
     if ((e = hipFuncSetAttribute((const void *)k_bucket<true>, hipFuncAttributeMaxDynamicSharedMemorySize, SM_BUCKET))) return e;
     if ((e = hipFuncSetAttribute((const void *)k_bucket<false>, hipFuncAttributeMaxDynamicSharedMemorySize, SM_BUCKET))) return e;
@@ -1784,7 +1834,7 @@ hipError_t launch_select(const Batch &bt, hipStream_t s)
     if (bt.any_sampled) {
         // tensors whose sweep 1 was sampled: exact figures from the second histogram; those whose
         // thresholds were mispredicted take the exact sweeps (the kernels skip all other tensors)
-        PROF("k_plan1b", s, k_plan1b<<<bt.nB, BLOCK, SM_PLAN2, s>>>(bt.td, bt.gd, B, bt.force_miss ? 1u : 0u));
+        PROF("k_plan1b", s, k_plan1b<<<bt.nB, BLOCK, SM_PLAN1B, s>>>(bt.td, bt.gd, B, bt.force_miss ? 1u : 0u));
         PROF("k_hist1_redo", s, (k_hist<1, true><<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nB, bt.wg_tile0, bt.wg_fu0, B)));
         PROF("k_plan1_redo", s, k_plan1<true><<<bt.nB, BLOCK, SM_PLAN1, s>>>(bt.td, bt.gd, B));
         PROF("k_hist2_redo", s, (k_hist<2, true><<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nB, bt.wg_tile0, bt.wg_fu0, B)));
@@ -1798,7 +1848,6 @@ hipError_t launch_select(const Batch &bt, hipStream_t s)
     if (bt.light) return hipGetLastError();
     if ((e = launch_edges(bt, s))) return e;
     PROF("k_gather", s, k_gather<<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nB, bt.wg_tile0, bt.wg_fu0, bt.gd, B));
-    PROF("k_group_list", s, k_group_list<<<bt.nB, 256, 0, s>>>(bt.nB, B, bt.grp_list, bt.n_grp_total));
     PROF("k_split", s, k_split<<<dim3(bt.n_units, SPLIT_PARTS), BLOCK, SM_SPLIT, s>>>(bt.td, bt.fu_tensor, B));
     if (bt.lds_ordered)
         PROF("k_bucket", s, k_bucket<true><<<bt.n_bucket_blocks, BB, SM_BUCKET, s>>>(bt.td, bt.nB, bt.grp_list, bt.n_grp_total, B));

@@ -545,12 +545,7 @@ __global__ __launch_bounds__(BLOCK) void k_sketch_score(const TDesc *__restrict_
                 u32 slot = lookup_u16(sh.stab, key, sh.T[key >> COARSE_SHIFT]);
                 if (slot & 0x8000u) {
                     slot &= 0x7fffu;
-                    if (sh.edge[slot] <= key) slot++; // (the list ends with 0xFFFFFFFF, above every finite key)
-                    if (sh.edge[slot] <= key) { // a wide bin (small tensors, many equal values)
-                        slot++;
-                        for (u32 step = 256u; step > 0u; step >>= 1)
-                            if (slot + step <= (u32)SK_EDGES && sh.edge[slot + step - 1u] <= key) slot += step;
-                    }
+                    while (sh.edge[slot] <= key) slot++; // (the list ends with 0xFFFFFFFF, above every finite key)
                 }
                 atomicAdd(&sh.cnt[copy + slot], 1u);
                 atomicAdd(&sh.sx[copy + slot], (double)v[i]);

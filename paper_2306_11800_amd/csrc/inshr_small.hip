@@ -7,7 +7,7 @@
 // 4096-value tensor took 0.45 ms, and in a checkpoint with hundreds of norm weights and biases the
 // per-tensor kernels ran over all of them in several rounds of workgroups.  Sorting 4096 keys takes
 // 15 us.  What it leaves behind for later calls (thresholds, class counts, boundary keys, centres,
-// protected counts, a key -> bin table of one bin per key prefix) has the form of the general path.
+// protected counts, a key -> bin table of eight bins per key prefix) has the form of the general path.
 //
 // Bound by latency: about 70 barriers and LDS round trips of one workgroup.
 #include "inshr_launch.h"
@@ -74,8 +74,8 @@ __global__ __launch_bounds__(NT) void k_small(const TDesc *__restrict__ td, cons
     __shared__ u32 s_thr[MAX_THR], s_cnt[MAX_THR][4];               // magnitude; below (neg, pos), above (neg, pos)
     __shared__ u32 s_A[MAX_PAIRS], s_Ap[MAX_PAIRS], s_gl[MAX_PAIRS], s_gr[MAX_PAIRS], s_Mn[MAX_PAIRS], s_M[MAX_PAIRS];
     __shared__ double s_red[NW][MAX_FRAC + 1], s_sq[MAX_FRAC + 1];  // sums of squares: all, protected per fraction
-    __shared__ __attribute__((aligned(4))) u16 s_cfg[MAX_PAIRS][12]; // first grid entry of (pair, log2 K | 9 + i: 3, 6, 12 bins)
-    __shared__ double s_acc[MAX_PAIRS][12];
+    __shared__ __attribute__((aligned(4))) u16 s_cfg[MAX_PAIRS][K_SLOTS]; // first grid entry of (pair, log2 K | 9 + i: 3, 6, 12 bins)
+    __shared__ double s_acc[MAX_PAIRS][K_SLOTS];
     __shared__ double s_sse[MAX_CFG];
     __shared__ u64 s_cost[MAX_CFG];
 
@@ -89,10 +89,10 @@ __global__ __launch_bounds__(NT) void k_small(const TDesc *__restrict__ td, cons
         s_or = 0u;
         s_and = 0xFFFFFFFFu;
     }
-    for (u32 i = tid; i < (u32)MAX_PAIRS * 12u; i += NT) (&s_cfg[0][0])[i] = 0xFFFFu;
-    // one bin per key prefix (for kernels that want a key -> bin table)
+    for (u32 i = tid; i < (u32)MAX_PAIRS * (u32)K_SLOTS; i += NT) (&s_cfg[0][0])[i] = 0xFFFFu;
+    // eight bins per key prefix (for kernels that want a key -> bin table)
     u32 *tab = B.table2 + (size_t)t * COARSE;
-    for (u32 i = tid; i < (u32)COARSE; i += NT) tab[i] = i << 5;
+    for (u32 i = tid; i < (u32)COARSE; i += NT) tab[i] = (8u * i) << 5 | 3u;
     __syncthreads();
 
     // ---- sort (least significant digit first, equal digits over the bits that differ) ------------
@@ -207,17 +207,7 @@ __global__ __launch_bounds__(NT) void k_small(const TDesc *__restrict__ td, cons
     if (tid == 0u) s_nneg = lower_bound_key(keys, n, ZERO_KEY);
     if (tid == 64u) s_npos0 = upper_bound_key(keys, n, ZERO_KEY);
     if (tid < n_cfg) {
-        const u32 K = gd->cfg_K[tid];
-        const u32 slot = (K & (K - 1u)) == 0u ? 31u - (u32)__clz((int)K) : (K == 3u ? 9u : K == 6u ? 10u : 11u);
-        u32 *w = reinterpret_cast<u32 *>(&s_cfg[gd->cfg_pair[tid]][slot & ~1u]); // (two entries per word)
-        for (u32 old = *(volatile u32 *)w;;) { // the lowest grid index wins
-            const u32 sh = (slot & 1u) * 16u;
-            if (((old >> sh) & 0xFFFFu) <= tid) break;
-            const u32 want = (old & ~(0xFFFFu << sh)) | (tid << sh);
-            const u32 seen = atomicCAS(w, old, want);
-            if (seen == old) break;
-            old = seen;
-        }
+        enter_config(s_cfg, tid, gd->cfg_pair[tid], gd->cfg_K[tid]);
     }
     __syncthreads();
     const u32 n_neg = s_nneg, n_nonpos = s_npos0;
@@ -278,8 +268,8 @@ __global__ __launch_bounds__(NT) void k_small(const TDesc *__restrict__ td, cons
         st->n_neg = n_neg;
         st->n_zero = n_nonpos - n_neg;
         st->n_thr = n_thr;
-        st->nb2 = (u32)COARSE;
-        st->zbin = ZERO_KEY >> COARSE_SHIFT;
+        st->nb2 = 8u * (u32)COARSE;
+        st->zbin = ZERO_KEY >> L1_SHIFT;
         if (mag_of_key(keys[0]) >= 0x7f800000u || mag_of_key(keys[n - 1u]) >= 0x7f800000u) st->nonfinite = 1u;
     }
     // sums of squares of the protected values
@@ -305,7 +295,7 @@ __global__ __launch_bounds__(NT) void k_small(const TDesc *__restrict__ td, cons
     }
 
     // ---- boundaries --------------------------------------------------------------------------------
-    const u32 n_bnd = gd->n_bnd;
+    const u32 n_bnd = gd->n_all; // (all of them: the sums start from 256 bins)
     u32 *tk = B.tgt_key + (size_t)t * TGT_STRIDE;
     for (u32 w = tid; w < n_pairs * n_bnd; w += NT) {
         const u32 q = w / n_bnd, i = w % n_bnd;
@@ -418,8 +408,7 @@ __global__ __launch_bounds__(NT) void k_small(const TDesc *__restrict__ td, cons
     Score *sc = B.scores + (size_t)t * n_cfg;
     for (u32 g = tid; g < n_cfg; g += NT) {
         const u32 K = gd->cfg_K[g], q = gd->cfg_pair[g];
-        const u32 slot = (K & (K - 1u)) == 0u ? 31u - (u32)__clz((int)K) : (K == 3u ? 9u : K == 6u ? 10u : 11u);
-        double sse = s_sq[0] - s_sq[1u + gd->pair_o[q]] - s_acc[q][slot];
+        double sse = s_sq[0] - s_sq[1u + gd->pair_o[q]] - s_acc[q][k_slot(K)];
         if (sse < 0.0) sse = 0.0;
         Score r;
         r.sse = sse;
