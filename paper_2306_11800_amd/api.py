@@ -815,7 +815,9 @@ def entropy_encode(group_off, delta_bits: int, packed=None, values=None):
     if values is not None:
         values = np.ascontiguousarray(values, dtype=np.uint16)
     stats, size = CEntropyStats(), C.c_uint64()
-    out = np.empty(max(64, n // 4), dtype=np.uint8)
+    # room for the headers, tables of every value and a few run lengths, and one byte per value, so that
+    # one call is enough for all but contrived streams (pages that are not written cost nothing)
+    out = np.empty(64 + n_groups * 32 + 8 * min(n, n_groups * ((1 << delta_bits) + 64)) + n, dtype=np.uint8)
     for _ in range(2):
         rc = lib.inshr_entropy_encode(_host_ptr(packed), _host_ptr(values), n, delta_bits,
                                       _host_ptr(group_off), n_groups, _host_ptr(out), out.size,
@@ -825,7 +827,10 @@ def entropy_encode(group_off, delta_bits: int, packed=None, values=None):
         out = np.empty(size.value, dtype=np.uint8)
     if rc:
         raise InshrError(rc, lib.inshr_strerror(rc).decode())
-    return out[:size.value], (stats.n_tokens, stats.table_bytes, stats.payload_bytes)
+    data = out[:size.value]
+    if 2 * data.size < out.size:  # (a result kept for long does not hold the whole buffer)
+        data = data.copy()
+    return data, (stats.n_tokens, stats.table_bytes, stats.payload_bytes)
 
 
 def entropy_decode(data, n: int, delta_bits: int, n_groups: int, as_values: bool = False):

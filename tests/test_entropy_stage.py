@@ -118,3 +118,27 @@ def test_malformed_input_is_refused():
     with pytest.raises(a.InshrError):
         a.entropy_encode(np.array([0, 60, 50, 100], np.uint64), 3, values=v)
 
+
+
+@pytest.mark.parametrize("n,w,n_groups,p_same", [
+    (32_767, 1, 1, 0.5), (32_769, 3, 2, 0.9), (131_071, 9, 1, 0.2), (200_003, 16, 5, 0.97), (262_144, 7, 3, 0.9999)])
+def test_groups_of_several_chunks(n, w, n_groups, p_same):
+    """Groups cut into pieces that several threads encode: runs across the cuts, runs longer than a
+    piece, pieces in which none starts, and groups that share words of the decoded stream."""
+    rng = np.random.default_rng(n)
+    v = rng.integers(0, min(1 << w, 40), n).astype(np.uint16)
+    v[0] = (1 << w) - 1
+    keep = np.where(rng.random(n) < p_same, 0, np.arange(n))
+    v = v[np.maximum.accumulate(keep)]
+    goff = np.concatenate([[0], np.sort(rng.integers(0, n + 1, n_groups - 1)), [n]]).astype(np.uint64)
+    packed = ref.pack(v, w)
+    data, stats = api().entropy_encode(goff, w, packed=packed)
+    data2, stats2 = api().entropy_encode(goff, w, values=v)
+    assert np.array_equal(data, data2) and stats == stats2
+    want = ent.group_costs(v, goff)
+    _, _, groups = parse_groups(data)
+    assert [(t, len(table), b) for _, t, b, table in groups] == [tuple(x) for x in want]
+    back, goff2 = api().entropy_decode(data, n, w, n_groups)
+    assert np.array_equal(back, packed) and np.array_equal(goff2, goff)
+    vals, _ = api().entropy_decode(data, n, w, n_groups, as_values=True)
+    assert np.array_equal(vals, v)
