@@ -200,12 +200,14 @@ class Quantized:
             c_entry = CQuantized()
         self.n = n
         self._bufs = bufs                                   # packed, codebook, boundaries, idx, val
-        self._ptrs = tuple(b.data_ptr() for b in bufs)
+        a, b, c, d, e = bufs
+        self._ptrs = (a.data_ptr(), b.data_ptr(), c.data_ptr(), d.data_ptr(), e.data_ptr())
         self._c = c_entry                                   # element of the CQuantized array
         self._keep = keep                                   # the array itself
         self.bf16 = False                                   # protected values stored as bfloat16
-        c_entry.n_bins = bins if bins else 1 << bits
-        c_entry.sym_bits = symbol_bits(c_entry.n_bins)
+        K = bins if bins else 1 << bits
+        c_entry.n_bins = K
+        c_entry.sym_bits = (K + 1).bit_length()             # symbol_bits(K)
 
     sym_bits = property(lambda self: self._c.sym_bits)
     bits = property(lambda self: self._c.sym_bits - 1)      # of a power-of-two bin count
@@ -249,7 +251,7 @@ class Quantized:
 class TensorBatch(list):
     """A list of tensors with its marshalled C array, for callers that pass the same tensors again
     and again (Context.batch).  The list must not be changed afterwards."""
-    __slots__ = ("_ta",)
+    __slots__ = ("_ta", "_sizes")
 
 
 class QuantizedBatch(list):
@@ -259,7 +261,7 @@ class QuantizedBatch(list):
 
 
 class DeltaBatch(list):
-    __slots__ = ("_pa", "_ca", "_oa", "_prev", "_cur")
+    __slots__ = ("_pa", "_ca", "_oa", "_prev", "_cur", "_rows", "_Kp")
 
 
 @dataclass
@@ -283,11 +285,57 @@ def _tensor_array(tensors: Sequence[torch.Tensor]):
     return arr
 
 
-def _config_array(cfgs):
-    arr = (CConfig * len(cfgs))()
-    for i, cfg in enumerate(cfgs):
-        arr[i] = CConfig(int(cfg[0]), int(cfg[3]) if len(cfg) > 3 else 0, int(cfg[1]), int(cfg[2]))
+def _filled(struct, count, /, **columns):
+    """C array of `count` structs with the given fields, one sequence of values per field (a checkpoint has
+    hundreds of tensors, and an assignment per struct and field costs as much as a small kernel)."""
+    import numpy as np
+    arr = (struct * count)()
+    rows = np.frombuffer(arr, dtype=struct)
+    for name, values in columns.items():
+        rows[name] = values
     return arr
+
+
+_WORDS_PER_BUFFER = 1 << 23  # 64 MB: what a tensor of symbols that outlives the others can hold on to
+
+
+def _word_buffers(words, devices):
+    """int64 tensors of the given sizes, small ones as slices of shared buffers, and their addresses:
+    an allocation per tensor takes longer than its kernel.  Tensors of some size start at a multiple
+    of 512 bytes."""
+    res, at = [], []
+    i, n = 0, len(words)
+    while i < n:
+        dev, sizes, offsets, pads, end, j = devices[i], [], [], [], 0, i
+        while j < n and devices[j] == dev and (j == i or end + words[j] <= _WORDS_PER_BUFFER):
+            if words[j] >= 4096 and end % 64:
+                pads.append(len(sizes))
+                sizes.append(-end % 64)
+                end += sizes[-1]
+            offsets.append(8 * end)
+            sizes.append(words[j])
+            end += words[j]
+            j += 1
+        buf = torch.empty(end, dtype=torch.int64, device=dev)
+        views = list(buf.split_with_sizes(sizes)) if len(sizes) > 1 else [buf]
+        for k in reversed(pads):
+            del views[k]
+        base = buf.data_ptr()
+        res += views
+        at += [base + x for x in offsets]
+        i = j
+    return res, at
+
+
+def _config_array(cfgs):
+    # (a checkpoint's tensors share a few configurations: one struct per different one)
+    cfgs = [c if type(c) is tuple else tuple(c) for c in cfgs]
+    known = {c: bytes(CConfig(int(c[0]), int(c[3]) if len(c) > 3 else 0, int(c[1]), int(c[2]))) for c in set(cfgs)}
+    return (CConfig * len(cfgs)).from_buffer_copy(b"".join([known[c] for c in cfgs]))
+
+
+def _sizes_of(tensors):
+    return tensors._sizes if isinstance(tensors, TensorBatch) else tuple([t.numel() for t in tensors])
 
 
 def cube_of(grid) -> Tuple[List[int], Tuple[int, int, int], tuple]:
@@ -392,6 +440,7 @@ class Context:
         """The same tensors as a list that carries its C array (see TensorBatch)."""
         b = TensorBatch(tensors)
         b._ta = _tensor_array(list(tensors))
+        b._sizes = tuple([t.numel() for t in tensors])
         return b
 
     # -- inshr_search ---------------------------------------------------------------------
@@ -428,7 +477,7 @@ class Context:
         ta = _tensor_array(tensors)
         ca = _config_array(cfgs)
         flags = (INSHR_REUSE_SEARCH if reuse_search else 0) | (INSHR_PROTECT_BF16 if protect_bf16 else 0)
-        if isinstance(out, QuantizedBatch) and out._sizes == tuple(t.numel() for t in tensors):
+        if isinstance(out, QuantizedBatch) and out._sizes == _sizes_of(tensors):
             # the C side checks every buffer against what the configuration needs
             self._check(self.lib.inshr_quantize(self.h, ta, ca, out._qa, nT, flags))
             for q in out:
@@ -525,7 +574,7 @@ class Context:
         u = np.ascontiguousarray(uniforms, dtype=np.float64)
         if u.shape != (nT, 256):
             raise ValueError("uniforms must have shape [len(tensors), 256]")
-        reuse_out = isinstance(out, QuantizedBatch) and out._sizes == tuple(t.numel() for t in tensors)
+        reuse_out = isinstance(out, QuantizedBatch) and out._sizes == _sizes_of(tensors)
         qa = out._qa if reuse_out else (CQuantized * nT)()
         res = out if reuse_out else QuantizedBatch()
         for i, (t, cfg) in enumerate(zip(tensors, cfgs)):
@@ -569,7 +618,7 @@ class Context:
         u = np.ascontiguousarray(uniforms, dtype=np.float64)
         if u.shape != (nT, 256):
             raise ValueError("uniforms must have shape [len(tensors), 256]")
-        reuse_out = isinstance(out, QuantizedBatch) and out._sizes == tuple(t.numel() for t in tensors)
+        reuse_out = isinstance(out, QuantizedBatch) and out._sizes == _sizes_of(tensors)
         qa = out._qa if reuse_out else (CQuantized * nT)()
         res = out if reuse_out else QuantizedBatch()
         for i, (t, cfg) in enumerate(zip(tensors, wide)):
@@ -660,17 +709,21 @@ class Context:
         `out` may carry the list a previous call returned for the same shapes; with the same prev
         and cur lists as in that call only the symbol widths are marshalled again."""
         nT = len(prev)
-        if (isinstance(out, DeltaBatch) and out._prev is prev and out._cur is cur and prev_perm is None
-                and not want_perm):
-            pa, ca, oa = out._pa, out._ca, out._oa
-            for i in range(nT):
-                pa[i].sym_bits, pa[i].bins = prev[i]._c.sym_bits, prev[i]._c.n_bins
-                ca[i].sym_bits, ca[i].bins = cur[i]._c.sym_bits, cur[i]._c.n_bins
-                if out[i].group_off.numel() != pa[i].bins + 3:  # prev was quantized again with other bins
-                    out[i].group_off = out[i].goff_buf[:pa[i].bins + 3]
-            self._check(self.lib.inshr_delta(self.h, pa, None, ca, oa, nT))
-            for i in range(nT):
-                out[i].delta_bits = int(oa[i].delta_bits)
+        if (isinstance(out, DeltaBatch) and out._prev is prev and out._cur is cur and prev_perm is None):
+            p, c, o = out._rows
+            for rows, qs in ((p, prev), (c, cur)):
+                cs = [q._c for q in qs]
+                rows["sym_bits"] = [x.sym_bits for x in cs]
+                rows["bins"] = [x.n_bins for x in cs]
+            Kp = p["bins"].tolist()
+            if Kp != out._Kp:  # prev was quantized again with other bins
+                for d, k, before in zip(out, Kp, out._Kp):
+                    if k != before:
+                        d.group_off = d.goff_buf[:k + 3]
+                out._Kp = Kp
+            self._check(self.lib.inshr_delta(self.h, out._pa, None, out._ca, out._oa, nT))
+            for d, w in zip(out, o["delta_bits"].tolist()):
+                d.delta_bits = w
             return out
         pa = (CCodes * nT)()
         ca = (CCodes * nT)()
@@ -711,6 +764,9 @@ class Context:
         for i in range(nT):
             res[i].delta_bits = int(oa[i].delta_bits)
         res._pa, res._ca, res._oa, res._prev, res._cur = pa, ca, oa, prev, cur
+        import numpy as np
+        res._rows = (np.frombuffer(pa, CCodes), np.frombuffer(ca, CCodes), np.frombuffer(oa, CDeltaOut))
+        res._Kp = res._rows[0]["bins"].tolist()
         return res
 
     def delta_static(self, prev: Sequence[Quantized], cur: Sequence[Quantized], out: List[Delta]) -> List[Delta]:
@@ -739,18 +795,20 @@ class Context:
                    out: Optional[Sequence[torch.Tensor]] = None) -> List[torch.Tensor]:
         """fp32 tensors decoded from the quantized form; returns after the work has completed."""
         nT = len(qs)
-        ia = (CDequantIn * nT)()
-        oa = (C.c_void_p * nT)()
-        res = []
-        for i, q in enumerate(qs):
-            ia[i] = CDequantIn(q._ptrs[0], q._ptrs[1], q._ptrs[3], q._ptrs[4], q.n_outlier, q.n, 0,
-                               1 if q.bf16 else 0, q.K)
-            x = out[i] if out is not None else torch.empty(q.n, dtype=torch.float32,
-                                                           device=q._bufs[0].device)
-            if x.dtype != torch.float32 or x.numel() != q.n or not x.is_contiguous():
-                raise ValueError("output must be a contiguous float32 tensor of n elements")
-            oa[i] = x.data_ptr()
-            res.append(x)
+        if out is None:
+            out = [torch.empty(q.n, dtype=torch.float32, device=q._bufs[0].device) for q in qs]
+        res = list(out[:nT])
+        n = [q.n for q in qs]
+        f32 = torch.float32
+        if [x.numel() for x in res] != n or not all([x.dtype is f32 and x.is_contiguous() for x in res]):
+            raise ValueError("output must be a contiguous float32 tensor of n elements")
+        ptrs = [q._ptrs for q in qs]
+        c = [q._c for q in qs]
+        ia = _filled(CDequantIn, nT, packed=[p[0] for p in ptrs], codebook=[p[1] for p in ptrs],
+                     outlier_idx=[p[3] for p in ptrs], outlier_val=[p[4] for p in ptrs],
+                     n_outlier=[x.n_outlier for x in c], n=n, protected_bf16=[q.bf16 for q in qs],
+                     bins=[x.n_bins for x in c])
+        oa = (C.c_void_p * nT)(*[x.data_ptr() for x in res])
         self._check(self.lib.inshr_dequantize(self.h, ia, oa, nT))
         return res
 
@@ -760,23 +818,25 @@ class Context:
         """Packed symbols (int64 words) of the current checkpoint from the previous codes and the
         delta streams; returns after the work has completed.  bins_cur: the numbers of bins of the
         current checkpoint where they are not 2^bits."""
+        import numpy as np
         nT = len(prev)
-        pa = (CCodes * nT)()
-        da = (CDeltaOut * nT)()
-        ca = (CCodesOut * nT)()
-        res = []
-        for i, (p, d) in enumerate(zip(prev, deltas)):
-            pa[i] = CCodes(p._ptrs[0], p.sym_bits, 0, p.K, p.n)
-            Kc = int(bins_cur[i]) if bins_cur is not None and bins_cur[i] else 1 << int(bits_cur[i])
-            da[i].packed = d.packed.data_ptr()
-            da[i].packed_words = d.packed.numel()
-            da[i].group_off = d.group_off.data_ptr() if d.group_off is not None else None
-            da[i].perm = None
-            da[i].delta_bits = d.delta_bits
-            words = (p.n * symbol_bits(Kc) + 63) // 64
-            w = torch.empty(words, dtype=torch.int64, device=p._bufs[0].device)
-            ca[i] = CCodesOut(w.data_ptr(), words, 0, Kc)
-            res.append(w)
+        deltas = deltas[:nT]
+        n = [p.n for p in prev]
+        c = [p._c for p in prev]
+        Kc = [1 << int(b) for b in bits_cur]
+        if bins_cur is not None:
+            Kc = [int(b) or k for b, k in zip(bins_cur, Kc)]
+        # (nothing but the widths of K differ between tensors: a table, not a call per tensor)
+        width = {k: symbol_bits(k) for k in set(Kc)}
+        words = (np.array(n, np.int64) * np.array([width[k] for k in Kc], np.int64) + 63) // 64
+        res, at = _word_buffers(words.tolist(), [p._bufs[0].device for p in prev])
+        pa = _filled(CCodes, nT, packed=[p._ptrs[0] for p in prev], sym_bits=[x.sym_bits for x in c],
+                     bins=[x.n_bins for x in c], n=n)
+        da = _filled(CDeltaOut, nT, packed=[d.packed.data_ptr() for d in deltas],
+                     packed_words=[d.packed.numel() for d in deltas],
+                     group_off=[0 if d.group_off is None else d.group_off.data_ptr() for d in deltas],
+                     delta_bits=[d.delta_bits for d in deltas])
+        ca = _filled(CCodesOut, nT, packed=at, packed_words=words, bins=Kc)
         self._check(self.lib.inshr_reconstruct(self.h, pa, da, ca, nT))
         return res
 

@@ -793,12 +793,14 @@ static int quantize_with_state(inshr_ctx *c, const inshr_config *cfg, inshr_quan
     const uint32_t nT = (uint32_t)c->batch.nT;
     std::vector<QDesc> qd(nT);
     for (auto &q : qd) memset(&q, 0, sizeof(q));
+    uint32_t gi = 0;
     for (uint32_t k = 0; k < n_sel; k++) {
         const uint32_t u = which[k], t = c->pos[u]; // in the caller's order, on the device
-        uint32_t gi = 0;
-        for (gi = 0; gi < c->grid.n_cfg; gi++)
-            if (same_config(c->grid_cfgs[gi], cfg[k])) break;
-        if (gi == c->grid.n_cfg) return INSHR_E_SHAPE;
+        if (k == 0 || !same_config(c->grid_cfgs[gi], cfg[k])) { // (neighbours often have the same one)
+            for (gi = 0; gi < c->grid.n_cfg; gi++)
+                if (same_config(c->grid_cfgs[gi], cfg[k])) break;
+            if (gi == c->grid.n_cfg) return INSHR_E_SHAPE;
+        }
         uint64_t words = 0, cap = 0;
         inshr_quantize_bound(c->tensors[u].n, &cfg[k], &words, &cap);
         if (!out[k].packed || !out[k].codebook || out[k].packed_words < words) return INSHR_E_CAPACITY;
