@@ -1442,7 +1442,7 @@ int inshr_quantize_sens(inshr_ctx *c, const inshr_tensor *tensors, const float *
     // of bins for the search over the quantized values
     std::vector<inshr_config> frac_grid, bin_grid;
     std::vector<uint32_t> frac_of(nT), bin_of_t(nT);
-    u64 n_total = 0, n_blocks = 0;
+    u64 n_total = 0, n_runs = 0;
     for (uint32_t t = 0; t < nT; t++) {
         int rc = check_config(cfg[t]);
         if (rc) return rc;
@@ -1465,16 +1465,17 @@ int inshr_quantize_sens(inshr_ctx *c, const inshr_tensor *tensors, const float *
         if (i == bin_grid.size()) bin_grid.push_back(b);
         bin_of_t[t] = (uint32_t)i;
         n_total += tensors[t].n;
-        n_blocks += (tensors[t].n + 1023) / 1024;
+        n_runs += (tensors[t].n + SENS_RUN - 1) / SENS_RUN;
     }
+    if (n_runs >= (1ull << 31)) return INSHR_E_ARG; // (32 TB of values)
     HIPCHK(c, hipSetDevice(c->device));
     Carver cv;
     const size_t o_sd = cv.take(sizeof(SDesc) * nT);
     const size_t o_si = cv.take(sizeof(SInfo) * nT);
-    const size_t o_fl = cv.take(256);
-    const size_t o_bk = cv.take(n_blocks * 4);
-    const size_t o_bp = cv.take(n_blocks * 4);
-    const size_t o_bq = cv.take(n_blocks * 16);
+    const size_t o_st = cv.take(n_runs * 8 + 256); // [flags, ticket, pad to 256 bytes; states of the runs]: cleared
+    const size_t o_bp = cv.take(n_runs * 4);
+    const size_t o_bq = cv.take(n_runs * 16);
+    const size_t o_mk = cv.take(n_runs * (SENS_RUN / 4)); // two bits per element
     const size_t o_S = cv.take(n_total * 4 + 64ull * nT);
     const size_t o_W = cv.take(n_total * 4 + 64ull * nT);
     int rc = ensure_dev(c, c->sens_mem, cv.off);
@@ -1482,17 +1483,17 @@ int inshr_quantize_sens(inshr_ctx *c, const inshr_tensor *tensors, const float *
     char *db = (char *)c->sens_mem.p;
     std::vector<SDesc> sd(nT);
     {
-        u64 blk = 0, off = 0;
+        u64 run = 0, off = 0;
         for (uint32_t t = 0; t < nT; t++) {
             memset(&sd[t], 0, sizeof(SDesc));
             sd[t].w = tensors[t].data;
             sd[t].g = grads[t];
             sd[t].n = tensors[t].n;
-            sd[t].blk0 = blk;
+            sd[t].run0 = (u32)run;
             sd[t].S = (float *)(db + o_S) + off;
             sd[t].Wm = (float *)(db + o_W) + off;
             sd[t].by_sens = (prune_by_sensitivity && prune_by_sensitivity[t]) ? 1u : 0u;
-            blk += (tensors[t].n + 1023) / 1024;
+            run += (tensors[t].n + SENS_RUN - 1) / SENS_RUN;
             off += (tensors[t].n + 15) / 16 * 16; // every tensor's scratch starts 64-byte aligned
         }
     }
@@ -1502,37 +1503,47 @@ int inshr_quantize_sens(inshr_ctx *c, const inshr_tensor *tensors, const float *
         return INSHR_OK;
     };
     if ((rc = upload())) return rc;
-    HIPCHK(c, launch_sens_score((const SDesc *)(db + o_sd), (int)nT, n_blocks, c->stream));
+    HIPCHK(c, launch_sens_score((const SDesc *)(db + o_sd), (int)nT, (u32)n_runs, c->stream));
 
-    // thresholds: order statistics of the scores, then of the weights (threshold searches only)
-    std::vector<inshr_tensor> sub(nT);
-    for (int pass = 0; pass < 2; pass++) {
-        for (uint32_t t = 0; t < nT; t++) {
-            sub[t].data = pass == 0 ? sd[t].S : tensors[t].data;
-            sub[t].n = tensors[t].n;
-        }
-        rc = run_search(c, sub.data(), nT, frac_grid.data(), (uint32_t)frac_grid.size(), 0.0, false, true);
-        if (rc) return rc;
+    // thresholds: order statistics of the scores and of the weights (threshold searches only), in one
+    // search where the scratch memory allows it
+    std::vector<inshr_tensor> sub(2 * (size_t)nT);
+    for (uint32_t t = 0; t < nT; t++) {
+        sub[t].data = sd[t].S;
+        sub[nT + t].data = tensors[t].data;
+        sub[t].n = sub[nT + t].n = tensors[t].n;
+    }
+    auto thresholds = [&](uint32_t from, uint32_t to) -> int {
+        const int rs = run_search(c, sub.data() + from, to - from, frac_grid.data(), (uint32_t)frac_grid.size(), 0.0,
+                                  false, true);
+        if (rs) return rs;
         const SearchResult *res = (const SearchResult *)c->h_down.p;
-        for (uint32_t t = 0; t < nT; t++) {
+        for (uint32_t k = from; k < to; k++) {
+            const uint32_t t = k % nT;
             uint32_t qp = 0, qo = 0;
             while (qp < c->grid.n_p && c->grid.p_ppm[qp] != cfg[t].prune_ppm) qp++;
             while (qo < c->grid.n_o && c->grid.o_ppm[qo] != cfg[t].outlier_ppm) qo++;
             if (qp == c->grid.n_p || qo == c->grid.n_o) return INSHR_E_INTERNAL;
-            const u32 tp = res[c->pos[t]].thr_mag[qp], to = res[c->pos[t]].thr_mag[c->grid.n_p + qo];
-            if (pass == 0) {
-                sd[t].tau_os = to;
-                if (sd[t].by_sens) sd[t].tau_p = tp;
-            } else {
-                sd[t].tau_om = to;
-                if (!sd[t].by_sens) sd[t].tau_p = tp;
-            }
+            const u32 *thr = res[c->pos[k - from]].thr_mag;
+            (k < nT ? sd[t].tau_os : sd[t].tau_om) = thr[c->grid.n_p + qo];
+            if ((k < nT) == (sd[t].by_sens != 0u)) sd[t].tau_p = thr[qp];
         }
+        return INSHR_OK;
+    };
+    rc = nT < 32768u ? thresholds(0, 2 * nT) : INSHR_E_CAPACITY;
+    if (rc == INSHR_E_CAPACITY) {
+        rc = thresholds(0, nT);
+        if (!rc) rc = thresholds(nT, 2 * nT);
     }
+    if (rc) return rc;
+    sub.resize(nT);
     c->have_search = false;
     if ((rc = upload())) return rc;
-    HIPCHK(c, launch_sens_partition((const SDesc *)(db + o_sd), (int)nT, n_blocks, (u32 *)(db + o_bk),
-                                    (u32 *)(db + o_bp), (double *)(db + o_bq), (SInfo *)(db + o_si), c->stream));
+    u32 *flags = (u32 *)(db + o_st);
+    HIPCHK(c, hipMemsetAsync(flags, 0, n_runs * 8 + 256, c->stream));
+    HIPCHK(c, launch_sens_partition((const SDesc *)(db + o_sd), (int)nT, (u32)n_runs, flags + 1,
+                                    (u64 *)(db + o_st + 256), (u64 *)(db + o_mk), (u32 *)(db + o_bp),
+                                    (double *)(db + o_bq), (SInfo *)(db + o_si), c->stream));
     std::vector<SInfo> si(nT);
     HIPCHK(c, hipStreamSynchronize(c->stream));
     HIPCHK(c, hipMemcpy(si.data(), db + o_si, sizeof(SInfo) * nT, hipMemcpyDeviceToHost));
@@ -1569,12 +1580,11 @@ int inshr_quantize_sens(inshr_ctx *c, const inshr_tensor *tensors, const float *
         sd[t].sym_bits = symbol_bits(sd[t].K);
     }
     if ((rc = upload())) return rc;
-    HIPCHK(c, hipMemsetAsync(db + o_fl, 0, 4, c->stream));
-    HIPCHK(c, launch_sens_quant((const SDesc *)(db + o_sd), (int)nT, n_blocks, (const u32 *)(db + o_bp),
-                                (u32 *)(db + o_fl), c->stream));
+    HIPCHK(c, launch_sens_quant((const SDesc *)(db + o_sd), (int)nT, (u32)n_runs, (const u64 *)(db + o_mk),
+                                (const u32 *)(db + o_bp), flags, c->stream));
     u32 fl = 0;
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    HIPCHK(c, hipMemcpy(&fl, db + o_fl, 4, hipMemcpyDeviceToHost));
+    HIPCHK(c, hipMemcpy(&fl, flags, 4, hipMemcpyDeviceToHost));
     if (fl & 2u) return INSHR_E_CAPACITY;
     for (uint32_t t = 0; t < nT; t++) {
         out[t].n_pruned = si[t].n_pruned;

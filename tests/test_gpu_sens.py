@@ -150,3 +150,16 @@ def test_large_tensor_against_torch_definitions(ctx):
         sse = float(((x.double() - dec) ** 2).sum())
         assert abs(info[0][1] - sse) <= 1e-6 * sse
         del want, sym, dec, kept, prot, pruned, Y
+
+
+@pytest.mark.parametrize("cfg", [(1, 0, 0), (4, 200000, 1000), (8, 400000, 50000), (0, 100000, 100, 3)])
+def test_run_edges(ctx, cfg):
+    """Tensors that end at, before and behind the end of a run of 16384 elements, one with more runs
+    than a wave looks back over at once, and one of which a run keeps nothing."""
+    rng = np.random.default_rng(94)
+    data = [make(rng, n) for n in (16383, 16384, 16385, 2 * 16384, 130 * 16384 + 65, 5)]
+    data[3][0][16384:] = 3.0 + rng.random(16384).astype(np.float32)
+    by = [True, False, True, False, True, False]
+    qs, info = ctx.quantize_sens([dev(x) for x, _ in data], [dev(g) for _, g in data], [cfg] * 6, by)
+    for q, inf, (x, g), b in zip(qs, info, data, by):
+        check(q, inf, x, g, cfg, b)
