@@ -1,0 +1,58 @@
+"""Delta and its inverse on codes made from symbols: every pair of symbol widths, with and without the
+permutation, tiles that end anywhere, groups of one element, and one group that holds nearly everything
+(its run fills whole tiles, the others are a few bits of a word)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ref
+from test_gpu_parity import dev, u32, u64
+
+pytestmark = pytest.mark.gpu
+
+BINS = [2, 3, 6, 8, 16, 32, 64, 128, 256]  # symbols of 2 (K = 2) to 9 bits
+SIZES = [1, 63, 12287, 12288, 12289, 3 * 12288 + 31, 200_003]
+
+
+def codes(sym, K):
+    from paper_2306_11800_amd import api
+    w = api.symbol_bits(K)
+    f = torch.zeros(256, device="cuda:0")
+    return api.Quantized(sym.size, 8, (dev(ref.pack(sym, w).view(np.int64)), f, f, f.int(), f), bins=K)
+
+
+def symbols(rng, n, K, shape):
+    s = rng.integers(0, K + 2, n)
+    if shape == "skewed":  # one value nearly everywhere, and every value somewhere
+        s = np.where(rng.random(n) < 0.995, K // 2, s)
+        s[:min(n, K + 2)] = rng.permutation(K + 2)[:min(n, K + 2)]
+    return s.astype(np.uint16)
+
+
+@pytest.mark.parametrize("Kp", BINS)
+@pytest.mark.parametrize("ordered", [True, False])
+def test_widths(monkeypatch, Kp, ordered):
+    from paper_2306_11800_amd import api
+    monkeypatch.setenv("INSHR_NO_LDS_ORDER", "0" if ordered else "1")
+    ctx = api.Context(torch.device("cuda:0"))
+    rng = np.random.default_rng(Kp)
+    for Kc in (Kp, 2, 12, 256):
+        for shape in ("even", "skewed"):
+            sizes = SIZES if ordered else SIZES[3:5]
+            sp = [symbols(rng, n, Kp, shape) for n in sizes]
+            sc = [symbols(rng, n, Kc, shape) for n in sizes]
+            qp, qc = [codes(s, Kp) for s in sp], [codes(s, Kc) for s in sc]
+            for perm in (False, True):
+                ds = ctx.delta(qp, qc, want_perm=perm)
+                ctx.sync()
+                for d, a, b in zip(ds, sp, sc):
+                    r = ref.delta(a, 0, b, 0, K_prev=Kp, K_cur=Kc)
+                    assert d.delta_bits == r["delta_bits"]
+                    assert np.array_equal(u64(d.group_off), r["group_off"])
+                    assert np.array_equal(u64(d.packed), ref.pack(r["stream"], r["delta_bits"])), (Kp, Kc, a.size, shape)
+                    if perm:
+                        assert np.array_equal(u32(d.perm), r["perm"])
+            back = ctx.reconstruct(qp, ds, [0] * len(qp), [Kc] * len(qp))
+            for w, q in zip(back, qc):
+                assert torch.equal(w, q.packed), (Kp, Kc, q.n, shape)
+    ctx.close()
