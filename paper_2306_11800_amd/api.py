@@ -285,12 +285,26 @@ def _tensor_array(tensors: Sequence[torch.Tensor]):
     return arr
 
 
+_ROWS = {}  # struct -> numpy type
+_ZEROS = (0,) * 8
+
+
+def _rows(arr, struct):
+    """A C array as numpy rows (the same memory)."""
+    import numpy as np
+    dtype = _ROWS.get(struct)
+    if dtype is None:
+        dtype = _ROWS[struct] = np.dtype(struct)
+    return np.frombuffer(arr, dtype)
+
+
 def _filled(struct, count, /, **columns):
     """C array of `count` structs with the given fields, one sequence of values per field (a checkpoint has
     hundreds of tensors, and an assignment per struct and field costs as much as a small kernel)."""
-    import numpy as np
+    if count <= 8:  # (below what the views cost)
+        return (struct * count)(*zip(*[columns.get(f[0], _ZEROS) for f in struct._fields_]))
     arr = (struct * count)()
-    rows = np.frombuffer(arr, dtype=struct)
+    rows = _rows(arr, struct)
     for name, values in columns.items():
         rows[name] = values
     return arr
@@ -303,6 +317,9 @@ def _word_buffers(words, devices):
     """int64 tensors of the given sizes, small ones as slices of shared buffers, and their addresses:
     an allocation per tensor takes longer than its kernel.  Tensors of some size start at a multiple
     of 512 bytes."""
+    if len(words) <= 4:
+        res = [torch.empty(w, dtype=torch.int64, device=d) for w, d in zip(words, devices)]
+        return res, [x.data_ptr() for x in res]
     res, at = [], []
     i, n = 0, len(words)
     while i < n:
@@ -764,8 +781,7 @@ class Context:
         for i in range(nT):
             res[i].delta_bits = int(oa[i].delta_bits)
         res._pa, res._ca, res._oa, res._prev, res._cur = pa, ca, oa, prev, cur
-        import numpy as np
-        res._rows = (np.frombuffer(pa, CCodes), np.frombuffer(ca, CCodes), np.frombuffer(oa, CDeltaOut))
+        res._rows = (_rows(pa, CCodes), _rows(ca, CCodes), _rows(oa, CDeltaOut))
         res._Kp = res._rows[0]["bins"].tolist()
         return res
 
@@ -818,7 +834,6 @@ class Context:
         """Packed symbols (int64 words) of the current checkpoint from the previous codes and the
         delta streams; returns after the work has completed.  bins_cur: the numbers of bins of the
         current checkpoint where they are not 2^bits."""
-        import numpy as np
         nT = len(prev)
         deltas = deltas[:nT]
         n = [p.n for p in prev]
@@ -826,10 +841,8 @@ class Context:
         Kc = [1 << int(b) for b in bits_cur]
         if bins_cur is not None:
             Kc = [int(b) or k for b, k in zip(bins_cur, Kc)]
-        # (nothing but the widths of K differ between tensors: a table, not a call per tensor)
-        width = {k: symbol_bits(k) for k in set(Kc)}
-        words = (np.array(n, np.int64) * np.array([width[k] for k in Kc], np.int64) + 63) // 64
-        res, at = _word_buffers(words.tolist(), [p._bufs[0].device for p in prev])
+        words = [(x * (k + 1).bit_length() + 63) // 64 for x, k in zip(n, Kc)]  # (symbol_bits(k))
+        res, at = _word_buffers(words, [p._bufs[0].device for p in prev])
         pa = _filled(CCodes, nT, packed=[p._ptrs[0] for p in prev], sym_bits=[x.sym_bits for x in c],
                      bins=[x.n_bins for x in c], n=n)
         da = _filled(CDeltaOut, nT, packed=[d.packed.data_ptr() for d in deltas],
