@@ -8,7 +8,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
-from dataclasses import dataclass
+from dataclasses import dataclass, field
 from typing import List, Optional, Sequence, Tuple
 
 import torch
@@ -261,7 +261,7 @@ class QuantizedBatch(list):
 
 
 class DeltaBatch(list):
-    __slots__ = ("_pa", "_ca", "_oa", "_prev", "_cur", "_rows", "_Kp")
+    __slots__ = ("_pa", "_ca", "_oa", "_prev", "_cur", "_rows")
 
 
 @dataclass
@@ -272,6 +272,11 @@ class Delta:
     group_off: torch.Tensor     # int64 [(1 << bits_prev) + 3]: a view of goff_buf
     perm: Optional[torch.Tensor]  # int32 (bit pattern of u32) [n] or None
     goff_buf: Optional[torch.Tensor] = None  # int64 [GROUP_OFF_ENTRIES]: room for any bits of prev
+    _K: int = field(default=0, init=False, repr=False, compare=False)  # bins of prev group_off was cut for
+
+    def _cut(self, K):
+        self.group_off = self.goff_buf[:K + 3]
+        self._K = K
 
 
 def _tensor_array(tensors: Sequence[torch.Tensor]):
@@ -733,11 +738,14 @@ class Context:
                 rows["sym_bits"] = [x.sym_bits for x in cs]
                 rows["bins"] = [x.n_bins for x in cs]
             Kp = p["bins"].tolist()
-            if Kp != out._Kp:  # prev was quantized again with other bins
-                for d, k, before in zip(out, Kp, out._Kp):
-                    if k != before:
-                        d.group_off = d.goff_buf[:k + 3]
-                out._Kp = Kp
+            if Kp != [d._K for d in out]:  # prev was quantized again with other bins
+                for d, k in zip(out, Kp):
+                    if k != d._K:
+                        d._cut(k)
+            if want_perm:  # (the buffers may have been replaced: a permutation is often asked for later)
+                o["packed"] = [d.packed.data_ptr() for d in out]
+                o["packed_words"] = [d.packed.numel() for d in out]
+                o["perm"] = [0 if d.perm is None else d.perm.data_ptr() for d in out]
             self._check(self.lib.inshr_delta(self.h, out._pa, None, out._ca, out._oa, nT))
             for d, w in zip(out, o["delta_bits"].tolist()):
                 d.delta_bits = w
@@ -768,7 +776,7 @@ class Context:
                 raise ValueError("pre-allocated delta buffer is too small")
             if d.goff_buf is None or d.goff_buf.numel() < GROUP_OFF_ENTRIES:
                 d.goff_buf = torch.empty(GROUP_OFF_ENTRIES, dtype=torch.int64, device=d.packed.device)
-            d.group_off = d.goff_buf[:p.K + 3]
+            d._cut(p.K)
             oa[i].packed = d.packed.data_ptr()
             oa[i].packed_words = d.packed.numel()
             oa[i].group_off = d.goff_buf.data_ptr()
@@ -782,7 +790,6 @@ class Context:
             res[i].delta_bits = int(oa[i].delta_bits)
         res._pa, res._ca, res._oa, res._prev, res._cur = pa, ca, oa, prev, cur
         res._rows = (_rows(pa, CCodes), _rows(ca, CCodes), _rows(oa, CDeltaOut))
-        res._Kp = res._rows[0]["bins"].tolist()
         return res
 
     def delta_static(self, prev: Sequence[Quantized], cur: Sequence[Quantized], out: List[Delta]) -> List[Delta]:
@@ -803,7 +810,7 @@ class Context:
         self._check(self.lib.inshr_delta_static(self.h, pa, ca, oa, nT))
         for i in range(nT):
             out[i].delta_bits = int(oa[i].delta_bits)
-            out[i].group_off = out[i].goff_buf[:prev[i].K + 3]
+            out[i]._cut(prev[i].K)
         return out
 
     # -- inshr_dequantize -----------------------------------------------------------------
@@ -835,12 +842,13 @@ class Context:
         delta streams; returns after the work has completed.  bins_cur: the numbers of bins of the
         current checkpoint where they are not 2^bits."""
         nT = len(prev)
-        deltas = deltas[:nT]
+        deltas = [deltas[i] for i in range(nT)]
         n = [p.n for p in prev]
         c = [p._c for p in prev]
-        Kc = [1 << int(b) for b in bits_cur]
-        if bins_cur is not None:
-            Kc = [int(b) or k for b, k in zip(bins_cur, Kc)]
+        if bins_cur is None:
+            Kc = [1 << int(bits_cur[i]) for i in range(nT)]
+        else:  # (bits_cur is looked at where bins_cur says nothing)
+            Kc = [int(bins_cur[i]) if bins_cur[i] else 1 << int(bits_cur[i]) for i in range(nT)]
         words = [(x * (k + 1).bit_length() + 63) // 64 for x, k in zip(n, Kc)]  # (symbol_bits(k))
         res, at = _word_buffers(words, [p._bufs[0].device for p in prev])
         pa = _filled(CCodes, nT, packed=[p._ptrs[0] for p in prev], sym_bits=[x.sym_bits for x in c],

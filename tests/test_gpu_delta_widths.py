@@ -56,3 +56,36 @@ def test_widths(monkeypatch, Kp, ordered):
             for w, q in zip(back, qc):
                 assert torch.equal(w, q.packed), (Kp, Kc, q.n, shape)
     ctx.close()
+
+
+def test_buffers_and_bins_between_calls():
+    """Output lists used again: a permutation buffer brought later, the group offsets after a static call
+    with other bins in between; bins_cur alone, and per-tensor lists longer than the call."""
+    from paper_2306_11800_amd import api
+    ctx = api.Context(torch.device("cuda:0"))
+    rng = np.random.default_rng(5)
+    for n_t in (3, 12):  # (C arrays are filled in another way above eight tensors)
+        sizes = [5000 + 77 * i for i in range(n_t)]
+        sp = [symbols(rng, n, 16, "even") for n in sizes]
+        sc = [symbols(rng, n, 12, "even") for n in sizes]
+        qp, qc = [codes(s, 16) for s in sp], [codes(s, 12) for s in sc]
+        ds = ctx.delta(qp, qc)
+        want = [ref.delta(a, 0, b, 0, K_prev=16, K_cur=12) for a, b in zip(sp, sc)]
+        for d in ds:
+            d.perm = torch.full((d.n,), -1, dtype=torch.int32, device="cuda:0")
+        assert ctx.delta(qp, qc, want_perm=True, out=ds) is ds
+        ctx.sync()
+        assert all(np.array_equal(u32(d.perm), r["perm"]) for d, r in zip(ds, want))
+        s4 = [symbols(rng, n, 4, "even") for n in sizes]
+        q4 = [codes(s, 4) for s in s4]
+        ctx.delta_static(q4, qc, ds)
+        assert all(d.group_off.numel() == 7 for d in ds)
+        ctx.delta(qp, qc, out=ds)
+        ctx.sync()
+        assert all(np.array_equal(u64(d.group_off), r["group_off"]) for d, r in zip(ds, want))
+        for bits, bins in ((None, [12] * n_t), ([0] * (n_t + 2), [12] * (n_t + 1))):
+            back = ctx.reconstruct(qp, ds, bits, bins)
+            assert all(torch.equal(w, q.packed) for w, q in zip(back, qc))
+        with pytest.raises(IndexError):
+            ctx.reconstruct(qp, ds, [4] * (n_t - 1))
+    ctx.close()
