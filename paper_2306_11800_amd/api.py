@@ -731,7 +731,8 @@ class Context:
         `out` may carry the list a previous call returned for the same shapes; with the same prev
         and cur lists as in that call only the symbol widths are marshalled again."""
         nT = len(prev)
-        if (isinstance(out, DeltaBatch) and out._prev is prev and out._cur is cur and prev_perm is None):
+        if (isinstance(out, DeltaBatch) and out._prev is prev and out._cur is cur and prev_perm is None
+                and not (want_perm and self._other_delta_buffers(out))):
             p, c, o = out._rows
             for rows, qs in ((p, prev), (c, cur)):
                 cs = [q._c for q in qs]
@@ -742,9 +743,7 @@ class Context:
                 for d, k in zip(out, Kp):
                     if k != d._K:
                         d._cut(k)
-            if want_perm:  # (the buffers may have been replaced: a permutation is often asked for later)
-                o["packed"] = [d.packed.data_ptr() for d in out]
-                o["packed_words"] = [d.packed.numel() for d in out]
+            if want_perm:  # (the buffer is often attached after the list's first call)
                 o["perm"] = [0 if d.perm is None else d.perm.data_ptr() for d in out]
             self._check(self.lib.inshr_delta(self.h, out._pa, None, out._ca, out._oa, nT))
             for d, w in zip(out, o["delta_bits"].tolist()):
@@ -791,6 +790,20 @@ class Context:
         res._pa, res._ca, res._oa, res._prev, res._cur = pa, ca, oa, prev, cur
         res._rows = (_rows(pa, CCodes), _rows(ca, CCodes), _rows(oa, CDeltaOut))
         return res
+
+    @staticmethod
+    def _other_delta_buffers(out: "DeltaBatch") -> bool:
+        """Whether a list's buffers are not the ones its C arrays hold, or too small for its symbols now."""
+        p, c, o = out._rows
+        if any([d.goff_buf is None for d in out]):
+            return True
+        widths = [max(a._c.sym_bits, b._c.sym_bits) for a, b in zip(out._prev, out._cur)]
+        need = [(n * w + 63) // 64 for n, w in zip(p["n"].tolist(), widths)]
+        words = [d.packed.numel() for d in out]
+        return (any([w < k for w, k in zip(words, need)]) or words != o["packed_words"].tolist()
+                or [d.packed.data_ptr() for d in out] != o["packed"].tolist()
+                or [d.goff_buf.data_ptr() for d in out] != o["group_off"].tolist()
+                or [d.goff_buf.numel() for d in out] != o["group_off_entries"].tolist())
 
     def delta_static(self, prev: Sequence[Quantized], cur: Sequence[Quantized], out: List[Delta]) -> List[Delta]:
         """inshr_delta_static into the buffers of `out` (a list inshr_delta's binding returned for

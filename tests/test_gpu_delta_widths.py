@@ -76,6 +76,18 @@ def test_buffers_and_bins_between_calls():
         assert ctx.delta(qp, qc, want_perm=True, out=ds) is ds
         ctx.sync()
         assert all(np.array_equal(u32(d.perm), r["perm"]) for d, r in zip(ds, want))
+        for d in ds:  # other buffers in the same list
+            d.goff_buf, d.packed = torch.zeros_like(d.goff_buf), torch.zeros_like(d.packed)
+            d.perm = torch.full((d.n,), -1, dtype=torch.int32, device="cuda:0")
+        ds = ctx.delta(qp, qc, want_perm=True, out=ds)
+        ctx.sync()
+        for d, r in zip(ds, want):
+            assert np.array_equal(u64(d.group_off), r["group_off"]) and np.array_equal(u32(d.perm), r["perm"])
+            assert np.array_equal(u64(d.packed), ref.pack(r["stream"], r["delta_bits"]))
+        kept, ds[0].packed = ds[0].packed, ds[0].packed[:-1]
+        with pytest.raises(ValueError):
+            ctx.delta(qp, qc, want_perm=True, out=ds)
+        ds[0].packed = kept
         s4 = [symbols(rng, n, 4, "even") for n in sizes]
         q4 = [codes(s, 4) for s in s4]
         ctx.delta_static(q4, qc, ds)
