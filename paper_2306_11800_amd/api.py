@@ -728,25 +728,14 @@ class Context:
               prev_perm: Optional[Sequence[Optional[torch.Tensor]]] = None,
               out: Optional[List[Delta]] = None) -> List[Delta]:
         """Enqueues the delta of every (prev[i], cur[i]); call sync() before reading on the host.
-        `out` may carry the list a previous call returned for the same shapes; with the same prev
-        and cur lists as in that call only the symbol widths are marshalled again."""
+        `out` may carry the list a previous call returned; its C arrays are then filled again, by
+        column, with what prev, cur and out hold now."""
         nT = len(prev)
-        if (isinstance(out, DeltaBatch) and out._prev is prev and out._cur is cur and prev_perm is None
-                and not (want_perm and self._other_delta_buffers(out))):
-            p, c, o = out._rows
-            for rows, qs in ((p, prev), (c, cur)):
-                cs = [q._c for q in qs]
-                rows["sym_bits"] = [x.sym_bits for x in cs]
-                rows["bins"] = [x.n_bins for x in cs]
-            Kp = p["bins"].tolist()
-            if Kp != [d._K for d in out]:  # prev was quantized again with other bins
-                for d, k in zip(out, Kp):
-                    if k != d._K:
-                        d._cut(k)
-            if want_perm:  # (the buffer is often attached after the list's first call)
-                o["perm"] = [0 if d.perm is None else d.perm.data_ptr() for d in out]
+        if (isinstance(out, DeltaBatch) and prev_perm is None and len(out) == len(cur) == nT == len(out._oa)
+                and self._refill_delta(prev, cur, out)):
             self._check(self.lib.inshr_delta(self.h, out._pa, None, out._ca, out._oa, nT))
-            for d, w in zip(out, o["delta_bits"].tolist()):
+            out._prev, out._cur = prev, cur
+            for d, w in zip(out, out._rows[2]["delta_bits"].tolist()):
                 d.delta_bits = w
             return out
         pa = (CCodes * nT)()
@@ -773,6 +762,9 @@ class Context:
                           perm=torch.empty(p.n, dtype=torch.int32, device=dev) if want_perm else None)
             if d.packed.numel() < need:
                 raise ValueError("pre-allocated delta buffer is too small")
+            if d.perm is not None and d.perm.numel() < p.n:
+                raise ValueError("pre-allocated permutation buffer is too small")
+            d.n = p.n
             if d.goff_buf is None or d.goff_buf.numel() < GROUP_OFF_ENTRIES:
                 d.goff_buf = torch.empty(GROUP_OFF_ENTRIES, dtype=torch.int64, device=d.packed.device)
             d._cut(p.K)
@@ -792,18 +784,53 @@ class Context:
         return res
 
     @staticmethod
-    def _other_delta_buffers(out: "DeltaBatch") -> bool:
-        """Whether a list's buffers are not the ones its C arrays hold, or too small for its symbols now."""
-        p, c, o = out._rows
-        if any([d.goff_buf is None for d in out]):
-            return True
-        widths = [max(a._c.sym_bits, b._c.sym_bits) for a, b in zip(out._prev, out._cur)]
-        need = [(n * w + 63) // 64 for n, w in zip(p["n"].tolist(), widths)]
-        words = [d.packed.numel() for d in out]
-        return (any([w < k for w, k in zip(words, need)]) or words != o["packed_words"].tolist()
-                or [d.packed.data_ptr() for d in out] != o["packed"].tolist()
-                or [d.goff_buf.data_ptr() for d in out] != o["group_off"].tolist()
-                or [d.goff_buf.numel() for d in out] != o["group_off_entries"].tolist())
+    def _refill_delta(prev, cur, out: "DeltaBatch") -> bool:
+        """Writes what the lists' entries hold now into the C arrays of `out`: entries and buffers may have been
+        replaced since its last call.  False: a buffer is missing or too small (nothing is kept then)."""
+        goff, perm = [d.goff_buf for d in out], [d.perm for d in out]
+        if any([g is None for g in goff]):
+            return False
+        if len(out) <= 8:  # (below what the columns cost)
+            for e, qs in ((out._pa, prev), (out._ca, cur)):
+                for x, q in zip(e, qs):
+                    x.packed, x.sym_bits, x.bins, x.n = q._ptrs[0], q._c.sym_bits, q._c.n_bins, q.n
+            moved = []
+            for x, p, c, d in zip(out._oa, out._pa, out._ca, out):
+                at = d.goff_buf.data_ptr()
+                moved.append(x.group_off != at)
+                x.packed, x.packed_words = d.packed.data_ptr(), d.packed.numel()
+                x.group_off, x.group_off_entries = at, d.goff_buf.numel()
+                x.perm = None if d.perm is None else d.perm.data_ptr()
+                if (x.packed_words < (p.n * max(p.sym_bits, c.sym_bits) + 63) // 64
+                        or x.group_off_entries < GROUP_OFF_ENTRIES):
+                    return False
+            Kp, n = [x.bins for x in out._pa], [x.n for x in out._pa]
+        else:
+            import numpy as np
+            T = torch.Tensor
+            p, c, o = out._rows
+            for rows, qs in ((p, prev), (c, cur)):
+                cs = [q._c for q in qs]
+                rows["packed"] = [q._ptrs[0] for q in qs]
+                rows["n"] = [q.n for q in qs]
+                rows["sym_bits"] = [x.sym_bits for x in cs]
+                rows["bins"] = [x.n_bins for x in cs]
+            packed, at = [d.packed for d in out], list(map(T.data_ptr, goff))
+            moved = (o["group_off"] != np.array(at, np.uint64)).tolist()
+            o["packed"], o["packed_words"] = list(map(T.data_ptr, packed)), list(map(T.numel, packed))
+            o["group_off"], o["group_off_entries"] = at, list(map(T.numel, goff))
+            o["perm"] = [0 if x is None else x.data_ptr() for x in perm]
+            need = (p["n"] * np.maximum(p["sym_bits"], c["sym_bits"]) + 63) // 64
+            if (o["packed_words"] < need).any() or (o["group_off_entries"] < GROUP_OFF_ENTRIES).any():
+                return False
+            Kp, n = p["bins"].tolist(), p["n"].tolist()
+        if any([x is not None and x.numel() < k for x, k in zip(perm, n)]):
+            return False
+        for d, k, m, other in zip(out, Kp, n, moved):
+            d.n = m
+            if other or k != d._K:  # another buffer, or prev was quantized again with other bins
+                d._cut(k)
+        return True
 
     def delta_static(self, prev: Sequence[Quantized], cur: Sequence[Quantized], out: List[Delta]) -> List[Delta]:
         """inshr_delta_static into the buffers of `out` (a list inshr_delta's binding returned for
@@ -819,6 +846,8 @@ class Context:
             oa[i].packed_words = d.packed.numel()
             oa[i].group_off = d.goff_buf.data_ptr()
             oa[i].group_off_entries = d.goff_buf.numel()
+            if d.perm is not None and d.perm.numel() < p.n:
+                raise ValueError("pre-allocated permutation buffer is too small")
             oa[i].perm = d.perm.data_ptr() if d.perm is not None else None
         self._check(self.lib.inshr_delta_static(self.h, pa, ca, oa, nT))
         for i in range(nT):

@@ -68,6 +68,7 @@ def test_buffers_and_bins_between_calls():
         sizes = [5000 + 77 * i for i in range(n_t)]
         sp = [symbols(rng, n, 16, "even") for n in sizes]
         sc = [symbols(rng, n, 12, "even") for n in sizes]
+        sp0, sc0 = list(sp), list(sc)
         qp, qc = [codes(s, 16) for s in sp], [codes(s, 12) for s in sc]
         ds = ctx.delta(qp, qc)
         want = [ref.delta(a, 0, b, 0, K_prev=16, K_cur=12) for a, b in zip(sp, sc)]
@@ -88,6 +89,31 @@ def test_buffers_and_bins_between_calls():
         with pytest.raises(ValueError):
             ctx.delta(qp, qc, want_perm=True, out=ds)
         ds[0].packed = kept
+        # entries of the input lists swapped inside the same lists, one replaced by codes of wider symbols;
+        # without the permutation asked for, buffers replaced and a permutation buffer taken away
+        for d in ds:
+            d.packed = torch.zeros((d.n * 9 + 63) // 64, dtype=torch.int64, device="cuda:0")
+        wide = symbols(rng, sizes[0], 256, "even")
+        for perm in (True, False):
+            qp[:], qc[:] = qc[:], qp[:]
+            sp, sc = sc, sp
+            if perm:
+                qc[0], sc[0] = codes(wide, 256), wide
+            else:
+                ds[0].packed, ds[1].goff_buf = torch.zeros_like(ds[0].packed), torch.zeros_like(ds[1].goff_buf)
+                untouched, ds[2].perm = ds[2].perm.fill_(-1), None
+            K = [(p.K, c.K) for p, c in zip(qp, qc)]
+            ds = ctx.delta(qp, qc, want_perm=perm, out=ds)
+            ctx.sync()
+            for d, a, b, (Kp, Kc) in zip(ds, sp, sc, K):
+                r = ref.delta(a, 0, b, 0, K_prev=Kp, K_cur=Kc)
+                assert np.array_equal(u64(d.group_off), r["group_off"])
+                assert np.array_equal(u64(d.packed)[:(d.n * d.delta_bits + 63) // 64], ref.pack(r["stream"], r["delta_bits"]))
+                if d.perm is not None:
+                    assert np.array_equal(u32(d.perm), r["perm"])
+        assert bool((untouched == -1).all())
+        qp, sp = [codes(s, 16) for s in sp0], sp0
+        qc, sc = [codes(s, 12) for s in sc0], sc0
         s4 = [symbols(rng, n, 4, "even") for n in sizes]
         q4 = [codes(s, 4) for s in s4]
         ctx.delta_static(q4, qc, ds)
