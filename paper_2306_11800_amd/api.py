@@ -315,40 +315,6 @@ def _filled(struct, count, /, **columns):
     return arr
 
 
-_WORDS_PER_BUFFER = 1 << 23  # 64 MB: what a tensor of symbols that outlives the others can hold on to
-
-
-def _word_buffers(words, devices):
-    """int64 tensors of the given sizes, small ones as slices of shared buffers, and their addresses:
-    an allocation per tensor takes longer than its kernel.  Tensors of some size start at a multiple
-    of 512 bytes."""
-    if len(words) <= 4:
-        res = [torch.empty(w, dtype=torch.int64, device=d) for w, d in zip(words, devices)]
-        return res, [x.data_ptr() for x in res]
-    res, at = [], []
-    i, n = 0, len(words)
-    while i < n:
-        dev, sizes, offsets, pads, end, j = devices[i], [], [], [], 0, i
-        while j < n and devices[j] == dev and (j == i or end + words[j] <= _WORDS_PER_BUFFER):
-            if words[j] >= 4096 and end % 64:
-                pads.append(len(sizes))
-                sizes.append(-end % 64)
-                end += sizes[-1]
-            offsets.append(8 * end)
-            sizes.append(words[j])
-            end += words[j]
-            j += 1
-        buf = torch.empty(end, dtype=torch.int64, device=dev)
-        views = list(buf.split_with_sizes(sizes)) if len(sizes) > 1 else [buf]
-        for k in reversed(pads):
-            del views[k]
-        base = buf.data_ptr()
-        res += views
-        at += [base + x for x in offsets]
-        i = j
-    return res, at
-
-
 def _config_array(cfgs):
     # (a checkpoint's tensors share a few configurations: one struct per different one)
     cfgs = [c if type(c) is tuple else tuple(c) for c in cfgs]
@@ -892,14 +858,16 @@ class Context:
         else:  # (bits_cur is looked at where bins_cur says nothing)
             Kc = [int(bins_cur[i]) if bins_cur[i] else 1 << int(bits_cur[i]) for i in range(nT)]
         words = [(x * (k + 1).bit_length() + 63) // 64 for x, k in zip(n, Kc)]  # (symbol_bits(k))
-        res, at = _word_buffers(words, [p._bufs[0].device for p in prev])
+        # (a tensor of its own for each: a slice of a shared buffer would keep all of it alive, and be saved with it)
+        i64 = torch.int64
+        res = [torch.empty(w, dtype=i64, device=p._bufs[0].device) for w, p in zip(words, prev)]
         pa = _filled(CCodes, nT, packed=[p._ptrs[0] for p in prev], sym_bits=[x.sym_bits for x in c],
                      bins=[x.n_bins for x in c], n=n)
         da = _filled(CDeltaOut, nT, packed=[d.packed.data_ptr() for d in deltas],
                      packed_words=[d.packed.numel() for d in deltas],
                      group_off=[0 if d.group_off is None else d.group_off.data_ptr() for d in deltas],
                      delta_bits=[d.delta_bits for d in deltas])
-        ca = _filled(CCodesOut, nT, packed=at, packed_words=words, bins=Kc)
+        ca = _filled(CCodesOut, nT, packed=[x.data_ptr() for x in res], packed_words=words, bins=Kc)
         self._check(self.lib.inshr_reconstruct(self.h, pa, da, ca, nT))
         return res
 

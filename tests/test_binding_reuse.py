@@ -1,5 +1,6 @@
 """Output lists given to the binding again after their entries, or those of the input lists, were replaced:
-what reaches the C entry point is what the lists hold at the call.  The library is a stand-in that records
+what reaches the C entry point is what the lists hold at the call.  Output tensors that the binding makes have
+memory of their own.  The library is a stand-in that records
 its arguments (host memory only, no device)."""
 import ctypes as C
 
@@ -15,6 +16,10 @@ class Recorder:
     def inshr_delta_bound(self, p, c, words):
         p, c = p._obj, c._obj
         words._obj.value = (p.n * max(p.sym_bits, c.sym_bits) + 63) // 64
+        return 0
+
+    def inshr_reconstruct(self, h, pa, da, ca, n):
+        self.words = [(x.packed, x.packed_words, x.bins) for x in ca]
         return 0
 
     def inshr_delta(self, h, pa, pp, ca, oa, n):
@@ -88,3 +93,15 @@ def test_delta_follows_the_lists(n_t, want_perm):
             ctx.delta(prev, cur, want_perm=want_perm, out=out)
         setattr(out[0], name, kept)
     again()
+
+
+@pytest.mark.parametrize("n_t", [1, 4, 12])
+def test_reconstructed_tensors_are_their_own(n_t):
+    ctx = context()
+    prev = [codes(1000 + 4096 * i, 16) for i in range(n_t)]
+    out = ctx.delta(prev, prev)
+    res = ctx.reconstruct(prev, out, [4] * n_t)
+    assert ctx.lib.words == [(x.data_ptr(), x.numel(), 16) for x in res]
+    for x, p in zip(res, prev):  # nothing else stays allocated with one of them, or is saved with it
+        assert x.numel() == (p.n * 5 + 63) // 64 and x.storage_offset() == 0
+        assert x.untyped_storage().nbytes() == 8 * x.numel()
