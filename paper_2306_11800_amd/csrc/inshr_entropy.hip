@@ -38,6 +38,9 @@ namespace {
 
 // Values per chunk of work: a thread's start costs about as much as 32 Ki values take to encode.
 constexpr uint64_t CHUNK = 1u << 15;
+// Values whose tokens are kept at a time (at most 32 MB of them); a larger group is kept whole, since its
+// code is known when all of it has been read.
+constexpr uint64_t WINDOW = 1u << 23;
 constexpr uint32_t MAX_THREADS = 16;
 
 uint32_t threads_for(uint64_t n)
@@ -178,7 +181,9 @@ struct Count {
 // stay in its arrays.
 struct Worker {
     uint32_t values; // that there can be
+    static constexpr uint64_t SLAB = 8 * CHUNK;
     std::vector<std::unique_ptr<uint32_t[]>> slabs; // of tokens
+    size_t slabs_used = 0;
     uint32_t *slab_at = nullptr;
     uint64_t slab_left = 0;
     std::vector<Count> counts;
@@ -202,6 +207,15 @@ struct Worker {
         count.assign(values + RUNS, 0ull);
     }
 
+    // Gives up the tokens, counts and symbols of the window before (the memory is used again)
+    void next_window()
+    {
+        slabs_used = 0;
+        slab_left = 0;
+        counts.clear();
+        syms.clear();
+    }
+
     // the distinct ones of `longer` with their counts
     template <class F> void drain_longer(F &&f)
     {
@@ -213,13 +227,13 @@ struct Worker {
         longer.clear();
     }
 
-    // Room for k more tokens; what is in a slab stays where it is
+    // Room for k more tokens (a chunk's at most); what is in a slab stays where it is
     uint32_t *room(uint64_t k)
     {
         if (slab_left < k) {
-            slab_left = std::max<uint64_t>(k, 8 * CHUNK);
-            slabs.emplace_back(new uint32_t[slab_left]);
-            slab_at = slabs.back().get();
+            if (slabs_used == slabs.size()) slabs.emplace_back(new uint32_t[SLAB]);
+            slab_at = slabs[slabs_used++].get();
+            slab_left = SLAB;
         }
         return slab_at;
     }
@@ -493,11 +507,16 @@ int encode(const ValueReader &rd, uint64_t n, uint32_t delta_bits, const uint64_
         }
         gr.chunk1 = (uint32_t)chunks.size();
     }
+    std::vector<uint32_t> windows(1, 0u); // first group of each, and their end
+    for (uint32_t g = 0; g < n_groups; g++)
+        if (g > windows.back() && group_off[g + 1] - group_off[windows.back()] > WINDOW) windows.push_back(g);
+    windows.push_back(n_groups);
     inshr_entropy_stats st;
     memset(&st, 0, sizeof(st));
     uint64_t used = 24;
-    auto place = [&] { // where every group goes
-        for (Group &gr : groups) {
+    auto place = [&](uint32_t g0, uint32_t g1) { // where every group goes
+        for (uint32_t g = g0; g < g1; g++) {
+            Group &gr = groups[g];
             gr.at = used;
             used += 32 + 8ull * gr.n_sym + (gr.payload_bits + 7) / 8;
             st.n_tokens += gr.n_tokens;
@@ -538,8 +557,9 @@ int encode(const ValueReader &rd, uint64_t n, uint32_t delta_bits, const uint64_
         }
     };
     auto payload_of = [&](const Group &gr) { return out + gr.at + 32 + 8ull * gr.n_sym; };
-    auto join_bytes = [&] { // bytes shared by chunks
-        for (const Group &gr : groups) {
+    auto join_bytes = [&](uint32_t g0, uint32_t g1) { // bytes shared by chunks
+        for (uint32_t g = g0; g < g1; g++) {
+            const Group &gr = groups[g];
             if (!gr.payload_bits) continue;
             uint8_t *p = payload_of(gr);
             for (int pass = 0; pass < 2; pass++)
@@ -564,26 +584,33 @@ int encode(const ValueReader &rd, uint64_t n, uint32_t delta_bits, const uint64_
     team.start([&](uint32_t thread) {
         Worker &me = workers[thread];
         me.init(rd.w);
-        team.run(chunks.size(), [&](uint64_t k) {
-            chunks[k].thread = thread;
-            me.read_chunk(rd, groups[chunks[k].group].lo, chunks[k]);
-        }, none);
-        team.run(n_groups, [&](uint64_t g) {
-            groups[g].thread = thread;
-            me.code_group(groups[g], chunks.data(), all);
-        }, [&] {
-            place();
-            fits = out && used <= out_cap;
-        });
-        if (!fits) return;
-        team.run(n_groups, [&](uint64_t g) { head_group((uint32_t)g, me); }, none);
-        team.run(chunks.size(), [&](uint64_t k) {
-            Chunk &c = chunks[k];
-            const Group &gr = groups[c.group];
-            if (!gr.payload_bits) return;
-            me.load(c.group, gr, all);
-            me.write_chunk(c, payload_of(gr));
-        }, join_bytes);
+        for (size_t w = 0; w + 1 < windows.size(); w++) {
+            const uint32_t g0 = windows[w], g1 = windows[w + 1];
+            const uint32_t c0 = groups[g0].chunk0, n_chunks = groups[g1 - 1].chunk1 - c0;
+            me.next_window();
+            team.run(n_chunks, [&](uint64_t k) {
+                Chunk &c = chunks[c0 + k];
+                c.thread = thread;
+                me.read_chunk(rd, groups[c.group].lo, c);
+            }, none);
+            team.run(g1 - g0, [&](uint64_t k) {
+                Group &gr = groups[g0 + k];
+                gr.thread = thread;
+                me.code_group(gr, chunks.data(), all);
+            }, [&] {
+                place(g0, g1);
+                fits = out && used <= out_cap;
+            });
+            if (!fits) continue; // (the sizes of the rest are wanted all the same)
+            team.run(g1 - g0, [&](uint64_t k) { head_group((uint32_t)(g0 + k), me); }, none);
+            team.run(n_chunks, [&](uint64_t k) {
+                Chunk &c = chunks[c0 + k];
+                const Group &gr = groups[c.group];
+                if (!gr.payload_bits) return;
+                me.load(c.group, gr, all);
+                me.write_chunk(c, payload_of(gr));
+            }, [&] { join_bytes(g0, g1); });
+        }
     });
     if (fits) {
         uint8_t *p = out;

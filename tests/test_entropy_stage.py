@@ -2,7 +2,10 @@
 against the oracle: run-length tokens and the payload size of every group are unique and must match
 exactly (the total cost of a Huffman code does not depend on tie-breaking); the codes themselves are
 checked for validity: the container decodes back to the same stream, bit for bit."""
+import ctypes as C
 import struct
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -142,3 +145,50 @@ def test_groups_of_several_chunks(n, w, n_groups, p_same):
     assert np.array_equal(back, packed) and np.array_equal(goff2, goff)
     vals, _ = api().entropy_decode(data, n, w, n_groups, as_values=True)
     assert np.array_equal(vals, v)
+
+
+PEAK = """
+import resource, sys
+import numpy as np
+from paper_2306_11800_amd import api
+n, n_groups = 48 << 20, 64
+goff = np.arange(n_groups + 1, dtype=np.uint64) * (n // n_groups)
+packed = np.full(n // 64, 0x5555555555555555, np.uint64)   # no two neighbours are equal: a token per value
+api.entropy_encode(goff[:2] // 1024, 1, packed=packed)
+before = resource.getrusage(resource.RUSAGE_SELF).ru_maxrss
+data, stats = api.entropy_encode(goff, 1, packed=packed)
+print(stats[0], resource.getrusage(resource.RUSAGE_SELF).ru_maxrss - before)
+back, _ = api.entropy_decode(data, n, 1, n_groups)
+assert np.array_equal(back, packed)
+"""
+
+
+def test_memory_of_a_long_stream():
+    """The encoder holds the tokens (4 bytes each) of 8 Mi values, or of one group where that is larger: 32 MB
+    here, beside the 6 MB of the container; all 48 Mi of them would be 192 MB."""
+    r = subprocess.run([sys.executable, "-c", PEAK], capture_output=True, text=True, timeout=300, check=True)
+    tokens, kb = [int(x) for x in r.stdout.split()]
+    assert tokens == 48 << 20
+    assert kb < 96 * 1024
+
+
+def test_groups_across_windows():
+    """More values than the encoder holds tokens of: windows of several groups, a group larger than a window,
+    empty groups at a window's end, and a buffer that only the first windows fit."""
+    rng = np.random.default_rng(5)
+    sizes = [3 << 20, 5 << 20, 1, 0, 9 << 20, 0, (1 << 20) + 3, 0]
+    goff = np.concatenate([[0], np.cumsum(sizes)]).astype(np.uint64)
+    v = np.repeat(rng.integers(0, 18, int(goff[-1]) // 7 + 1), 7)[:int(goff[-1])].astype(np.uint16)
+    data, stats = api().entropy_encode(goff, 5, values=v)
+    _, _, groups = parse_groups(data)
+    for (n_values, n_tokens, bits, table), lo, hi in zip(groups, goff[:-1], goff[1:]):
+        alone, st = api().entropy_encode(np.array([0, hi - lo], np.uint64), 5, values=v[int(lo):int(hi)])
+        assert parse_groups(alone)[2] == [(n_values, n_tokens, bits, table)] and n_values == hi - lo
+    vals, goff2 = api().entropy_decode(data, v.size, 5, len(sizes), as_values=True)
+    assert np.array_equal(vals, v) and np.array_equal(goff2, goff)
+    size, st = C.c_uint64(), api().CEntropyStats()
+    small = np.empty(data.size // 2, np.uint8)
+    rc = api().load_library().inshr_entropy_encode(None, v.ctypes.data, v.size, 5, goff.ctypes.data, len(sizes),
+                                                  small.ctypes.data, small.size, C.byref(size), C.byref(st))
+    assert rc == -4 and size.value == data.size
+    assert (st.n_tokens, st.table_bytes, st.payload_bytes) == stats
