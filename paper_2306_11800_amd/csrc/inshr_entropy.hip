@@ -686,7 +686,8 @@ struct Decoder { // one thread's tables
     uint64_t first_code[65], count[65];
     uint32_t first_sym[65], look_bits;
 
-    // the canonical code of a group; false: the table is none
+    // The canonical code of a group; false: the table is none.  Lengths may name more codes than there
+    // are (or be 0): those past the last code of their length stand for nothing.
     bool load(const Coded &c, uint32_t w)
     {
         token.resize(c.n_sym);
@@ -697,7 +698,7 @@ struct Decoder { // one thread's tables
             uint32_t len = 0;
             get(p, end, token[i]);
             get(p, end, len);
-            if (len > 63u || (i && len < before) || (c.n_sym > 1 && len == 0)) return false;
+            if (len > 63u || (i && len < before)) return false;
             count[len]++;
             before = len;
         }
@@ -706,7 +707,6 @@ struct Decoder { // one thread's tables
         uint64_t code = 0;
         uint32_t s = 0;
         for (uint32_t l = 0; l <= 63; l++) {
-            if (l && code + count[l] > (1ull << l)) return false; // more codes than there are
             first_code[l] = code;
             first_sym[l] = s;
             code = (code + count[l]) << 1;
@@ -717,9 +717,9 @@ struct Decoder { // one thread's tables
         const uint64_t size = 1ull << look_bits;
         look.assign(size, Entry{0, 0, 0, 0, 0});
         for (uint32_t l = 1; l <= look_bits; l++)
-            for (uint64_t k = 0; k < count[l]; k++) {
+            for (uint64_t k = 0; k < count[l] && first_code[l] + k < (1ull << l); k++) {
                 const int32_t t = token[first_sym[l] + k];
-                Entry e{1u, (uint16_t)-t, (uint8_t)l, 1, 0};
+                Entry e{1u, (uint16_t)(0u - (uint32_t)t), (uint8_t)l, 1, 0}; // (INT32_MIN has no negative)
                 if (t > 0) {
                     e.run = (uint32_t)t - 1u;
                     e.again = 1;

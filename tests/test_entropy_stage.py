@@ -192,3 +192,30 @@ def test_groups_across_windows():
                                                   small.ctypes.data, small.size, C.byref(size), C.byref(st))
     assert rc == -4 and size.value == data.size
     assert (st.n_tokens, st.table_bytes, st.payload_bytes) == stats
+
+
+def container(n, w, groups):
+    """A container from group tuples (n_values, n_tokens, payload_bits, [(token, length)], payload bytes)."""
+    b = struct.pack("<IIQII", 0x31454449, len(groups), n, w, 0)
+    for n_values, n_tokens, bits, table, payload in groups:
+        b += struct.pack("<QQQII", n_values, n_tokens, bits, len(table), 0)
+        b += b"".join(struct.pack("<iI", t, l) for t, l in table) + payload
+    return np.frombuffer(b, np.uint8)
+
+
+@pytest.mark.parametrize("n_values", [3, 600])  # (few tokens are decoded bit by bit)
+def test_tables_that_name_codes_that_are_not_there(n_values):
+    """Tables that no encoder writes, but whose tokens decode: three codes of one bit, of which the third can
+    not occur; lengths of zero in a group without tokens."""
+    bits = np.arange(n_values) % 3 == 1
+    payload = np.packbits(bits, bitorder="little").tobytes()
+    data = container(n_values, 3, [(n_values, n_values, n_values, [(0, 1), (-1, 1), (-2, 1), (-3, 2)], payload),
+                                   (0, 0, 0, [(-1, 0), (-2, 0), (-4, 3)], b"")])
+    vals, goff = api().entropy_decode(data, n_values, 3, 2, as_values=True)
+    assert np.array_equal(vals, bits.astype(np.uint16)) and goff.tolist() == [0, n_values, n_values]
+    # tokens that are no value (the smallest 32-bit number has no negative), where they are used
+    for bad in (-(1 << 31), -8):
+        data = container(n_values, 3, [(n_values, n_values, n_values, [(0, 1), (bad, 1)], payload)])
+        with pytest.raises(api().InshrError) as e:
+            api().entropy_decode(data, n_values, 3, 1)
+        assert e.value.code == -5
