@@ -381,8 +381,8 @@ typedef struct {
  * n_groups + 1 entries (group g = values [group_off[g], group_off[g+1]); group_off[0] = 0,
  * group_off[n_groups] = n).  One group spanning everything encodes a stream without regrouping.
  * out (host, out_cap bytes) receives the container; *out_bytes its size.  With out == NULL or
- * out_cap too small the call returns INSHR_E_CAPACITY and *out_bytes is the size needed.
- * stats may be NULL. */
+ * out_cap too small the call returns INSHR_E_CAPACITY and *out_bytes is the size needed (0: the host
+ * has no memory for the call's work).  stats may be NULL. */
 int inshr_entropy_encode(const uint64_t *packed, const uint16_t *values, uint64_t n,
                          uint32_t delta_bits, const uint64_t *group_off, uint32_t n_groups,
                          uint8_t *out, uint64_t out_cap, uint64_t *out_bytes,
@@ -390,7 +390,8 @@ int inshr_entropy_encode(const uint64_t *packed, const uint16_t *values, uint64_
 
 /* Inverse: the container back into `packed` (ceil(n * delta_bits / 64) words) or `values` (n
  * entries), the other NULL, and group_off (n_groups + 1 entries, may be NULL).  n, delta_bits and
- * n_groups must be those of the encoder.  INSHR_E_SHAPE: the container is malformed. */
+ * n_groups must be those of the encoder.  INSHR_E_SHAPE: the container is malformed;
+ * INSHR_E_CAPACITY: the host has no memory for the call's work. */
 int inshr_entropy_decode(const uint8_t *in, uint64_t in_bytes, uint64_t n, uint32_t delta_bits,
                          uint32_t n_groups, uint64_t *packed, uint16_t *values, uint64_t *group_off);
 

@@ -913,7 +913,7 @@ def entropy_encode(group_off, delta_bits: int, packed=None, values=None):
         rc = lib.inshr_entropy_encode(_host_ptr(packed), _host_ptr(values), n, delta_bits,
                                       _host_ptr(group_off), n_groups, _host_ptr(out), out.size,
                                       C.byref(size), C.byref(stats))
-        if rc != -4:
+        if rc != -4 or not size.value:
             break
         out = np.empty(size.value, dtype=np.uint8)
     if rc:

@@ -25,8 +25,9 @@
 #include <atomic>
 #include <cstdint>
 #include <cstring>
+#include <exception>
 #include <memory>
-#include <system_error>
+#include <new>
 #include <thread>
 #include <vector>
 
@@ -52,7 +53,8 @@ uint32_t threads_for(uint64_t n)
 }
 
 // The threads of one call: run(items, f) hands item 0, 1, .. to whichever thread is free and
-// returns on every thread when all items are done, the last one's once(), too.
+// returns on every thread when all items are done, the last one's once(), too.  When memory runs out
+// on one of them, failed() says so and whatever is run afterwards does nothing.
 class Team {
 public:
     explicit Team(uint32_t n) : size_(n) {}
@@ -69,7 +71,7 @@ public:
                     while (!go_.load(std::memory_order_acquire)) std::this_thread::yield();
                     body(t);
                 });
-            } catch (const std::system_error &) { // fewer threads than asked for: the rest do it
+            } catch (const std::exception &) { // fewer threads than asked for: the rest do it
                 break;
             }
         }
@@ -84,11 +86,11 @@ public:
         for (;;) {
             const uint64_t i = next_.fetch_add(1, std::memory_order_relaxed);
             if (i >= items) break;
-            f(i);
+            guard([&] { f(i); });
         }
         const uint32_t turn = turn_.load(std::memory_order_relaxed);
         if (arrived_.fetch_add(1, std::memory_order_acq_rel) + 1 == size_) {
-            once();
+            guard(once);
             arrived_.store(0, std::memory_order_relaxed);
             next_.store(0, std::memory_order_relaxed);
             turn_.store(turn + 1, std::memory_order_release);
@@ -97,9 +99,20 @@ public:
         }
     }
 
+    template <class G> void guard(G &&g)
+    {
+        if (failed()) return;
+        try {
+            g();
+        } catch (const std::exception &) { // (std::bad_alloc)
+            failed_.store(true, std::memory_order_relaxed);
+        }
+    }
+    bool failed() const { return failed_.load(std::memory_order_relaxed); }
+
 private:
     uint32_t size_;
-    std::atomic<bool> go_{false};
+    std::atomic<bool> go_{false}, failed_{false};
     std::atomic<uint64_t> next_{0};
     std::atomic<uint32_t> arrived_{0}, turn_{0};
 };
@@ -583,7 +596,7 @@ int encode(const ValueReader &rd, uint64_t n, uint32_t delta_bits, const uint64_
     auto none = [] {};
     team.start([&](uint32_t thread) {
         Worker &me = workers[thread];
-        me.init(rd.w);
+        team.guard([&] { me.init(rd.w); });
         for (size_t w = 0; w + 1 < windows.size(); w++) {
             const uint32_t g0 = windows[w], g1 = windows[w + 1];
             const uint32_t c0 = groups[g0].chunk0, n_chunks = groups[g1 - 1].chunk1 - c0;
@@ -612,6 +625,7 @@ int encode(const ValueReader &rd, uint64_t n, uint32_t delta_bits, const uint64_
             }, [&] { join_bytes(g0, g1); });
         }
     });
+    if (team.failed()) throw std::bad_alloc();
     if (fits) {
         uint8_t *p = out;
         put<uint32_t>(p, MAGIC);
@@ -863,6 +877,7 @@ int decode(const uint8_t *in, uint64_t in_bytes, uint64_t n, uint32_t delta_bits
             c.tail = fw.acc;
         }, [] {});
     });
+    if (team.failed()) throw std::bad_alloc();
     for (const Coded &c : groups)
         if (!c.ok) return INSHR_E_SHAPE;
     if (packed)
@@ -893,14 +908,23 @@ int inshr_entropy_encode(const uint64_t *packed, const uint16_t *values, uint64_
     if ((packed == nullptr) == (values == nullptr)) return INSHR_E_ARG; // exactly one of the two
     const ValueReader rd = packed ? ValueReader{(const uint8_t *)packed, ((n * delta_bits + 63) / 64) * 8, delta_bits}
                                   : ValueReader{(const uint8_t *)values, 2 * n, 16u};
-    return encode(rd, n, delta_bits, group_off, n_groups, out, out_cap, out_bytes, stats);
+    try {
+        return encode(rd, n, delta_bits, group_off, n_groups, out, out_cap, out_bytes, stats);
+    } catch (const std::exception &) { // (std::bad_alloc)
+        *out_bytes = 0; // (not NULL: checked before anything is allocated)
+        return INSHR_E_CAPACITY;
+    }
 }
 
 int inshr_entropy_decode(const uint8_t *in, uint64_t in_bytes, uint64_t n, uint32_t delta_bits,
                          uint32_t n_groups, uint64_t *packed, uint16_t *values, uint64_t *group_off)
 {
     if (!in || (packed == nullptr) == (values == nullptr)) return INSHR_E_ARG;
-    return decode(in, in_bytes, n, delta_bits, n_groups, packed, values, group_off);
+    try {
+        return decode(in, in_bytes, n, delta_bits, n_groups, packed, values, group_off);
+    } catch (const std::exception &) { // (std::bad_alloc)
+        return INSHR_E_CAPACITY;
+    }
 }
 
 } // extern "C"

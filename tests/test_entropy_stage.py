@@ -219,3 +219,42 @@ def test_tables_that_name_codes_that_are_not_there(n_values):
         with pytest.raises(api().InshrError) as e:
             api().entropy_decode(data, n_values, 3, 1)
         assert e.value.code == -5
+
+
+NO_MEMORY = """
+import ctypes as C, resource
+import numpy as np
+from paper_2306_11800_amd import api
+lib = api.load_library()
+
+def limited(call):  # with room for 8 MB more
+    vm = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+    old = resource.getrlimit(resource.RLIMIT_AS)
+    resource.setrlimit(resource.RLIMIT_AS, (vm + (8 << 20), old[1]))
+    rc = call()
+    resource.setrlimit(resource.RLIMIT_AS, old)
+    return rc
+
+n = 24 << 20                                                       # 96 MB of tokens
+goff = np.array([0, n], np.uint64)
+packed = np.full(n // 64, 0x5555555555555555, np.uint64)
+out = np.empty(n, np.uint8)
+size = C.c_uint64(7)
+enc = lambda: lib.inshr_entropy_encode(packed.ctypes.data, None, n, 1, goff.ctypes.data, 1, out.ctypes.data,
+                                       out.size, C.byref(size), None)
+print(limited(enc), size.value, enc())
+table = np.zeros((16 << 20, 2), np.int32)                          # 64 MB of tokens of a code
+table[:, 1] = 40
+head = np.concatenate([np.array([0x31454449, 1, 0, 0, 1, 0], np.uint32),
+                       np.array([0, 0, 0, 0, 0, 0, len(table), 0], np.uint32)])
+data = np.concatenate([head.view(np.uint8), table.view(np.uint8).ravel()])
+dec = lambda: lib.inshr_entropy_decode(data.ctypes.data, data.size, 0, 1, 1, packed.ctypes.data, None, None)
+print(limited(dec), dec())
+"""
+
+
+def test_host_memory_that_runs_out_is_an_error():
+    """... and never ends the program, on whichever of the call's threads it runs out."""
+    r = subprocess.run([sys.executable, "-c", NO_MEMORY], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr
+    assert r.stdout.split() == ["-4", "0", "0", "-4", "0"]
