@@ -828,7 +828,7 @@ class Context:
         nT = len(qs)
         if out is None:
             out = [torch.empty(q.n, dtype=torch.float32, device=q._bufs[0].device) for q in qs]
-        res = list(out[:nT])
+        res = [out[i] for i in range(nT)]
         n = [q.n for q in qs]
         f32 = torch.float32
         if [x.numel() for x in res] != n or not all([x.dtype is f32 and x.is_contiguous() for x in res]):

@@ -3,6 +3,7 @@ what reaches the C entry point is what the lists hold at the call.  Output tenso
 memory of their own.  The library is a stand-in that records
 its arguments (host memory only, no device)."""
 import ctypes as C
+from collections import deque
 
 import pytest
 import torch
@@ -20,6 +21,10 @@ class Recorder:
 
     def inshr_reconstruct(self, h, pa, da, ca, n):
         self.words = [(x.packed, x.packed_words, x.bins) for x in ca]
+        return 0
+
+    def inshr_dequantize(self, h, ia, oa, n):
+        self.out = list(oa)
         return 0
 
     def inshr_delta(self, h, pa, pp, ca, oa, n):
@@ -105,3 +110,12 @@ def test_reconstructed_tensors_are_their_own(n_t):
     for x, p in zip(res, prev):  # nothing else stays allocated with one of them, or is saved with it
         assert x.numel() == (p.n * 5 + 63) // 64 and x.storage_offset() == 0
         assert x.untyped_storage().nbytes() == 8 * x.numel()
+
+
+@pytest.mark.parametrize("kind", [list, tuple, deque, lambda x: dict(enumerate(x))])
+def test_dequantize_takes_any_outputs_by_index(kind):
+    ctx = context()
+    q = [codes(1000 + i, 16) for i in range(3)]
+    out = [torch.zeros(1000 + i) for i in range(4)]  # (more than needed)
+    res = ctx.dequantize(q, kind(out))
+    assert all(a is b for a, b in zip(res, out)) and ctx.lib.out == [x.data_ptr() for x in out[:3]]
