@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+from array import array
 from dataclasses import dataclass, field
 from typing import List, Optional, Sequence, Tuple
 
@@ -311,7 +312,7 @@ def _filled(struct, count, /, **columns):
     arr = (struct * count)()
     rows = _rows(arr, struct)
     for name, values in columns.items():
-        rows[name] = values
+        rows[name] = array("Q", values)  # (a third faster than from the list)
     return arr
 
 
@@ -773,19 +774,23 @@ class Context:
             Kp, n = [x.bins for x in out._pa], [x.n for x in out._pa]
         else:
             import numpy as np
-            T = torch.Tensor
+            at_of, size_of = torch.Tensor.data_ptr, torch.Tensor.numel
             p, c, o = out._rows
+
+            def u64(values):  # (half of what a list costs numpy)
+                return array("Q", values)
+
             for rows, qs in ((p, prev), (c, cur)):
                 cs = [q._c for q in qs]
-                rows["packed"] = [q._ptrs[0] for q in qs]
-                rows["n"] = [q.n for q in qs]
-                rows["sym_bits"] = [x.sym_bits for x in cs]
-                rows["bins"] = [x.n_bins for x in cs]
-            packed, at = [d.packed for d in out], list(map(T.data_ptr, goff))
-            moved = (o["group_off"] != np.array(at, np.uint64)).tolist()
-            o["packed"], o["packed_words"] = list(map(T.data_ptr, packed)), list(map(T.numel, packed))
-            o["group_off"], o["group_off_entries"] = at, list(map(T.numel, goff))
-            o["perm"] = [0 if x is None else x.data_ptr() for x in perm]
+                rows["packed"] = u64([q._ptrs[0] for q in qs])
+                rows["n"] = u64([q.n for q in qs])
+                rows["sym_bits"] = u64([x.sym_bits for x in cs])
+                rows["bins"] = u64([x.n_bins for x in cs])
+            packed, at = [d.packed for d in out], u64(map(at_of, goff))
+            moved = (o["group_off"] != at).tolist()
+            o["packed"], o["packed_words"] = u64(map(at_of, packed)), u64(map(size_of, packed))
+            o["group_off"], o["group_off_entries"] = at, u64(map(size_of, goff))
+            o["perm"] = u64([0 if x is None else x.data_ptr() for x in perm])
             need = (p["n"] * np.maximum(p["sym_bits"], c["sym_bits"]) + 63) // 64
             if (o["packed_words"] < need).any() or (o["group_off_entries"] < GROUP_OFF_ENTRIES).any():
                 return False
