@@ -1614,11 +1614,21 @@ int inshr_delta_bound(const inshr_codes *prev, const inshr_codes *cur, uint64_t 
     return INSHR_OK;
 }
 
+// Tiles per chunk of a call; longer chunks where the counts of so many would not fit the scratch limit.
 static u32 call_chunk_tiles(const inshr_ctx *c, const inshr_codes *prev, uint32_t n_tensors)
 {
     u64 tiles = 0; // (sizes are checked by the caller)
     for (uint32_t t = 0; t < n_tensors; t++) tiles += (prev[t].n + DELTA_TILE - 1) / DELTA_TILE;
-    return delta_chunk_tiles(tiles, c->n_cu);
+    u32 ct = delta_chunk_tiles(tiles, c->n_cu);
+    if (!c->scratch_limit) return ct;
+    auto scratch = [&] { // of a reconstruct call, which takes the most
+        u64 chunks = 0;
+        for (uint32_t t = 0; t < n_tensors; t++) chunks += ((prev[t].n + DELTA_TILE - 1) / DELTA_TILE + ct - 1) / ct;
+        return (sizeof(DDesc) + sizeof(XDesc) + sizeof(u64) * (DELTA_SS + 8)) * n_tensors +
+               chunks * 4 * (1 + DELTA_SS) + 6 * 256;
+    };
+    while (ct < (u32)DELTA_CHUNK && scratch() > c->scratch_limit) ct = std::min(2 * ct, (u32)DELTA_CHUNK);
+    return ct;
 }
 
 int inshr_delta(inshr_ctx *c, const inshr_codes *prev, const uint32_t *const *prev_perm,

@@ -127,3 +127,28 @@ def test_buffers_and_bins_between_calls():
         with pytest.raises(IndexError):
             ctx.reconstruct(qp, ds, [4] * (n_t - 1))
     ctx.close()
+
+
+def test_small_scratch():
+    """A limit on the scratch that only long chunks fit: the same streams and symbols."""
+    from paper_2306_11800_amd import api
+    rng = np.random.default_rng(9)
+    sizes = [10_000_001, 12_289, 5]  # (the first alone is 814 tiles, 13 of the longest chunks)
+    sp, sc = [symbols(rng, n, 16, "even") for n in sizes], [symbols(rng, n, 12, "skewed") for n in sizes]
+    qp, qc = [codes(s, 16) for s in sp], [codes(s, 12) for s in sc]
+    ctx, small = api.Context(torch.device("cuda:0")), api.Context(torch.device("cuda:0"), scratch_bytes=32 << 10)
+    for perm in (False, True):
+        want = ctx.delta(qp, qc, want_perm=perm)
+        got = small.delta(qp, qc, want_perm=perm)
+        ctx.sync()
+        small.sync()
+        for a, b in zip(got, want):
+            assert torch.equal(a.packed, b.packed) and torch.equal(a.group_off, b.group_off)
+            assert not perm or torch.equal(a.perm, b.perm)
+    for w, q in zip(small.reconstruct(qp, got, [0] * 3, [12] * 3), qc):
+        assert torch.equal(w, q.packed)
+    with pytest.raises(api.InshrError) as e:
+        api.Context(torch.device("cuda:0"), scratch_bytes=8 << 10).delta(qp, qc)
+    assert e.value.code == -4
+    ctx.close()
+    small.close()
