@@ -388,8 +388,9 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
             }
         }
         t_unit0[nB] = units;
-        // device layout
+        // device layout; what only boundaries and scores need is left out of a light search (k_plan2 ends it)
         Carver cv;
+        auto full = [&](size_t bytes) { return light ? (size_t)0 : bytes; };
         const size_t o_td = cv.take(sizeof(TDesc) * nT);
         const size_t o_gd = cv.take(sizeof(GridDesc));
         const size_t o_wt = cv.take(sizeof(u64) * (n_wg + 1));
@@ -405,45 +406,45 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         const size_t o_h1 = cv.take((size_t)nB * L1_BINS * 4);
         const size_t o_h2 = cv.take((size_t)nB * L2_BINS * 4);
         const size_t o_ngt = cv.take(256);
-        const size_t o_gcn = cv.take((size_t)nB * 2 * MAX_EDGES * 4);
-        const size_t o_gsx = cv.take((size_t)nB * 2 * MAX_EDGES * 8);
+        const size_t o_gcn = cv.take(full((size_t)nB * 2 * MAX_EDGES * 4));
+        const size_t o_gsx = cv.take(full((size_t)nB * 2 * MAX_EDGES * 8));
         const size_t o_to = cv.take((size_t)all_tiles * MAX_FRAC * 4);
         const size_t o_ph1 = cv.take(any_pooled ? (size_t)nB * L1_BINS * 4 : 0);
-        const size_t o_ms = cv.take((size_t)nB * MAX_SUB * 8);
+        const size_t o_ms = cv.take(full((size_t)nB * MAX_SUB * 8));
         const size_t zero_end = cv.off; // [o_ts, zero_end) is cleared before the sweeps
         const size_t o_psel = cv.take(any_pooled ? (size_t)nB * 2 * SEL_WORDS * 4 : 0);
         const size_t o_rs = cv.take(sizeof(SearchResult) * nT);
         const size_t o_tab = cv.take((size_t)nT * COARSE * 4);
         const size_t o_ut = cv.take((size_t)units * 16 * 4);
-        const size_t o_bi = cv.take((size_t)nB * L2_BINS * 4);
-        const size_t o_tb = cv.take((size_t)nB * TGT_STRIDE * 4);
-        const size_t o_tr = cv.take((size_t)nB * TGT_STRIDE * 4);
-        const size_t o_tk = cv.take((size_t)nT * TGT_STRIDE * 4);
+        const size_t o_bi = cv.take(full((size_t)nB * L2_BINS * 4));
+        const size_t o_tb = cv.take(full((size_t)nB * TGT_STRIDE * 4));
+        const size_t o_tr = cv.take(full((size_t)nB * TGT_STRIDE * 4));
+        const size_t o_tk = cv.take(full((size_t)nT * TGT_STRIDE * 4));
         const size_t o_tf = cv.take((size_t)all_tiles * 4);
         const size_t o_sq = cv.take((size_t)units * SQ_STRIDE * 8);
-        const size_t o_ed = cv.take((size_t)nB * MAX_EDGES * 4);
-        const size_t o_sl = cv.take((size_t)nB * (L2_BINS + 64) * 2);
-        const size_t o_pe = cv.take((size_t)nB * MAX_PAIRS * EIDX_STRIDE * 2);
-        const size_t o_eb = cv.take((size_t)nB * MAX_EDGES * 4);
-        const size_t o_ei = cv.take((size_t)nB * MAX_EDGES * 2);
-        const size_t o_gel = cv.take((size_t)nB * MAX_GROUPS * 4);
-        const size_t o_geh = cv.take((size_t)nB * MAX_GROUPS * 4);
-        const size_t o_sgc = cv.take((size_t)nB * MAX_EDGES * 4);
-        const size_t o_sbc = cv.take((size_t)nB * MAX_SUB * 4);
-        const size_t o_sbn = cv.take((size_t)nB * MAX_SUB * 4);
-        const size_t o_cb = cv.take((size_t)nT * n_cfg * CB_STRIDE * 4);
-        const size_t o_sc = cv.take((size_t)nT * n_cfg * sizeof(Score));
-        const size_t o_uc = cv.take((size_t)units * 16 * 4);
-        const size_t o_bg = cv.take((size_t)nB * L2_BINS * 2);
-        const size_t o_go = cv.take((size_t)nB * MAX_GROUPS * 4);
-        const size_t o_ge = cv.take((size_t)nB * MAX_GROUPS * 4);
-        const size_t o_gc = cv.take((size_t)nB * MAX_GROUPS * 4);
-        const size_t o_tgg = cv.take((size_t)nB * TGT_STRIDE * 4);
-        const size_t o_tkl = cv.take((size_t)nB * TGT_STRIDE * 4);
-        const size_t o_tkh = cv.take((size_t)nB * TGT_STRIDE * 4);
-        const size_t o_gl = cv.take((size_t)nB * MAX_GROUPS * 4);
+        const size_t o_ed = cv.take(full((size_t)nB * MAX_EDGES * 4));
+        const size_t o_sl = cv.take(full((size_t)nB * (L2_BINS + 64) * 2));
+        const size_t o_pe = cv.take(full((size_t)nB * MAX_PAIRS * EIDX_STRIDE * 2));
+        const size_t o_eb = cv.take(full((size_t)nB * MAX_EDGES * 4));
+        const size_t o_ei = cv.take(full((size_t)nB * MAX_EDGES * 2));
+        const size_t o_gel = cv.take(full((size_t)nB * MAX_GROUPS * 4));
+        const size_t o_geh = cv.take(full((size_t)nB * MAX_GROUPS * 4));
+        const size_t o_sgc = cv.take(full((size_t)nB * MAX_EDGES * 4));
+        const size_t o_sbc = cv.take(full((size_t)nB * MAX_SUB * 4));
+        const size_t o_sbn = cv.take(full((size_t)nB * MAX_SUB * 4));
+        const size_t o_cb = cv.take(full((size_t)nT * n_cfg * CB_STRIDE * 4));
+        const size_t o_sc = cv.take(full((size_t)nT * n_cfg * sizeof(Score)));
+        const size_t o_uc = cv.take(full((size_t)units * 16 * 4));
+        const size_t o_bg = cv.take(full((size_t)nB * L2_BINS * 2));
+        const size_t o_go = cv.take(full((size_t)nB * MAX_GROUPS * 4));
+        const size_t o_ge = cv.take(full((size_t)nB * MAX_GROUPS * 4));
+        const size_t o_gc = cv.take(full((size_t)nB * MAX_GROUPS * 4));
+        const size_t o_tgg = cv.take(full((size_t)nB * TGT_STRIDE * 4));
+        const size_t o_tkl = cv.take(full((size_t)nB * TGT_STRIDE * 4));
+        const size_t o_tkh = cv.take(full((size_t)nB * TGT_STRIDE * 4));
+        const size_t o_gl = cv.take(full((size_t)nB * MAX_GROUPS * 4));
         const size_t o_pool = cv.take((size_t)pool * 4);
-        const size_t o_pool2 = cv.take((size_t)pool * 4);
+        const size_t o_pool2 = cv.take(full((size_t)pool * 4));
         rc = ensure_dev(c, c->search_mem, cv.off);
         if (rc) return rc;
         rc = ensure_host(c, c->h_up, up_bytes);
@@ -1467,7 +1468,7 @@ int inshr_quantize_sens(inshr_ctx *c, const inshr_tensor *tensors, const float *
         n_total += tensors[t].n;
         n_runs += (tensors[t].n + SENS_RUN - 1) / SENS_RUN;
     }
-    if (n_runs >= (1ull << 31)) return INSHR_E_ARG; // (32 TB of values)
+    if (n_runs >= (1ull << 31)) return INSHR_E_ARG; // (2^45 values)
     HIPCHK(c, hipSetDevice(c->device));
     Carver cv;
     const size_t o_sd = cv.take(sizeof(SDesc) * nT);
@@ -1475,7 +1476,6 @@ int inshr_quantize_sens(inshr_ctx *c, const inshr_tensor *tensors, const float *
     const size_t o_st = cv.take(n_runs * 8 + 256); // [flags, ticket, pad to 256 bytes; states of the runs]: cleared
     const size_t o_bp = cv.take(n_runs * 4);
     const size_t o_bq = cv.take(n_runs * 16);
-    const size_t o_mk = cv.take(n_runs * (SENS_RUN / 4)); // two bits per element
     const size_t o_S = cv.take(n_total * 4 + 64ull * nT);
     const size_t o_W = cv.take(n_total * 4 + 64ull * nT);
     int rc = ensure_dev(c, c->sens_mem, cv.off);
@@ -1542,8 +1542,8 @@ int inshr_quantize_sens(inshr_ctx *c, const inshr_tensor *tensors, const float *
     u32 *flags = (u32 *)(db + o_st);
     HIPCHK(c, hipMemsetAsync(flags, 0, n_runs * 8 + 256, c->stream));
     HIPCHK(c, launch_sens_partition((const SDesc *)(db + o_sd), (int)nT, (u32)n_runs, flags + 1,
-                                    (u64 *)(db + o_st + 256), (u64 *)(db + o_mk), (u32 *)(db + o_bp),
-                                    (double *)(db + o_bq), (SInfo *)(db + o_si), c->stream));
+                                    (u64 *)(db + o_st + 256), (u32 *)(db + o_bp), (double *)(db + o_bq),
+                                    (SInfo *)(db + o_si), c->stream));
     std::vector<SInfo> si(nT);
     HIPCHK(c, hipStreamSynchronize(c->stream));
     HIPCHK(c, hipMemcpy(si.data(), db + o_si, sizeof(SInfo) * nT, hipMemcpyDeviceToHost));
@@ -1580,8 +1580,8 @@ int inshr_quantize_sens(inshr_ctx *c, const inshr_tensor *tensors, const float *
         sd[t].sym_bits = symbol_bits(sd[t].K);
     }
     if ((rc = upload())) return rc;
-    HIPCHK(c, launch_sens_quant((const SDesc *)(db + o_sd), (int)nT, (u32)n_runs, (const u64 *)(db + o_mk),
-                                (const u32 *)(db + o_bp), flags, c->stream));
+    HIPCHK(c, launch_sens_quant((const SDesc *)(db + o_sd), (int)nT, (u32)n_runs, (const u32 *)(db + o_bp), flags,
+                                c->stream));
     u32 fl = 0;
     HIPCHK(c, hipStreamSynchronize(c->stream));
     HIPCHK(c, hipMemcpy(&fl, flags, 4, hipMemcpyDeviceToHost));

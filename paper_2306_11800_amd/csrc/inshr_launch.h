@@ -109,7 +109,7 @@ struct QInfo {
 constexpr int SENS_RUN = 16384;
 struct SDesc { // one tensor of a call that partitions by magnitude and sensitivity
     const float *w, *g;
-    float *S;           // scratch: the sensitivity scores |g * w|
+    float *S;           // scratch: the sensitivity scores |g * w|; then the classes (sens_masks)
     float *Wm;          // scratch: the quantized values in index order
     u64 n;
     u32 run0, pad;      // first run of SENS_RUN elements of this tensor in the call-wide numbering
@@ -211,9 +211,9 @@ u32 *delta_static_flags(int device);      // the flag word of launch_delta_stati
 hipError_t launch_delta_static(int device, const DeltaStaticArgs &a, u64 n_dtiles, u64 n_chunks,
                                bool any_scatter, bool any_perm, bool lds_ordered, hipStream_t s);
 hipError_t launch_sens_score(const SDesc *sd, int nT, u32 n_runs, hipStream_t s);
-hipError_t launch_sens_partition(const SDesc *sd, int nT, u32 n_runs, u32 *ticket, u64 *state, u64 *masks,
+hipError_t launch_sens_partition(const SDesc *sd, int nT, u32 n_runs, u32 *ticket, u64 *state,
                                  u32 *run_prot, double *run_sq, SInfo *info, hipStream_t s);
-hipError_t launch_sens_quant(const SDesc *sd, int nT, u32 n_runs, const u64 *masks, const u32 *run_prot, u32 *flags,
+hipError_t launch_sens_quant(const SDesc *sd, int nT, u32 n_runs, const u32 *run_prot, u32 *flags,
                              hipStream_t s);
 hipError_t launch_lds_order_check(u32 *violations, hipStream_t s);
 hipError_t launch_dequantize(const RDesc *rd, int nT, u64 n_tiles, u64 max_outlier, u32 *flags,

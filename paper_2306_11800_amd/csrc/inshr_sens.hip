@@ -110,8 +110,22 @@ __device__ __forceinline__ u64 sens_before(u64 *state, u32 run, u32 first, u32 c
     return sum;
 }
 
+// Classes of a block of SBLK elements: two masks (quantized, protected) per row of 64.  They take the
+// place of the block's scores once its wave has read these (16 bytes per row; a row has at least one score, and
+// a tensor's scores end at a multiple of 64 bytes).  Lane r holds the first mask of row r, lane
+// SROWS + r the second.
+__device__ __forceinline__ GLOBAL_AS u64 *sens_masks(const SDesc &d, u64 block)
+{
+    return (GLOBAL_AS u64 *)(gptr(d.S) + block);
+}
+__device__ __forceinline__ bool has_mask(u32 lane, u64 left) // left: elements from the block's first on
+{
+    return lane < 2u * SROWS && (lane % SROWS) * 64u < left;
+}
+__device__ __forceinline__ u32 mask_at(u32 lane) { return 2u * (lane % SROWS) + lane / SROWS; }
+
 __global__ __launch_bounds__(SWG) void k_sens_partition(const SDesc *__restrict__ sd, int nT, u32 *__restrict__ ticket,
-                                                        u64 *__restrict__ state, u64 *__restrict__ masks,
+                                                        u64 *__restrict__ state,
                                                         u32 *__restrict__ run_prot, double *__restrict__ run_sq)
 {
     __shared__ u32 s_run, s_kept[SWG / 64], s_prot[SWG / 64];
@@ -148,7 +162,8 @@ __global__ __launch_bounds__(SWG) void k_sens_partition(const SDesc *__restrict_
         if (c == 0u) q_pruned = fma(xd, xd, q_pruned);
         if (c == 1u) q_prot = fma(xd, xd, q_prot);
     }
-    if (lane < 2u * SROWS) masks[((u64)run * (SWG / 64) + wave) * (2u * SROWS) + lane] = mine;
+    const u64 block = e0 - lane;
+    if (has_mask(lane, d.n > block ? d.n - block : 0ull)) sens_masks(d, block)[mask_at(lane)] = mine; // (all scores are in registers)
     q_pruned = wave_sum_f64(q_pruned);
     q_prot = wave_sum_f64(q_prot);
     if (lane == 0u) {
@@ -242,7 +257,7 @@ __global__ __launch_bounds__(SWG) void k_sens_scan(const SDesc *__restrict__ sd,
     }
 }
 
-__global__ __launch_bounds__(SWG) void k_sens_quant(const SDesc *__restrict__ sd, int nT, const u64 *__restrict__ masks,
+__global__ __launch_bounds__(SWG) void k_sens_quant(const SDesc *__restrict__ sd, int nT,
                                                     const u32 *__restrict__ run_prot, u32 *__restrict__ flags)
 {
     __shared__ u32 bk[256];               // boundary keys, ascending, and no key above them
@@ -259,7 +274,7 @@ __global__ __launch_bounds__(SWG) void k_sens_quant(const SDesc *__restrict__ sd
 #pragma unroll
     for (u32 r = 0; r < SROWS; r++) w[r] = r * 64u + lane < left ? gw[r * 64u] : 0.0f;
     u64 mine = 0ull;
-    if (lane < 2u * SROWS) mine = masks[((u64)run * (SWG / 64) + wave) * (2u * SROWS) + lane];
+    if (has_mask(lane, left)) mine = sens_masks(d, e0)[mask_at(lane)];
     const u32 n_mine = (u32)__popcll(mine);
     if (tid < 256u) {
         const u32 key = tid + 1u < K ? d.bkeys[bnd_index(K, tid + 1u)] : 0xFFFFFFFFu;
@@ -339,18 +354,18 @@ hipError_t launch_sens_score(const SDesc *sd, int nT, u32 n_runs, hipStream_t s)
 }
 
 // ticket and state are clear before
-hipError_t launch_sens_partition(const SDesc *sd, int nT, u32 n_runs, u32 *ticket, u64 *state, u64 *masks,
+hipError_t launch_sens_partition(const SDesc *sd, int nT, u32 n_runs, u32 *ticket, u64 *state,
                                  u32 *run_prot, double *run_sq, SInfo *info, hipStream_t s)
 {
-    PROF("k_sens_partition", s, k_sens_partition<<<n_runs, SWG, 0, s>>>(sd, nT, ticket, state, masks, run_prot, run_sq));
+    PROF("k_sens_partition", s, k_sens_partition<<<n_runs, SWG, 0, s>>>(sd, nT, ticket, state, run_prot, run_sq));
     PROF("k_sens_scan", s, k_sens_scan<<<nT, SWG, 0, s>>>(sd, state, run_prot, run_sq, info));
     return hipGetLastError();
 }
 
-hipError_t launch_sens_quant(const SDesc *sd, int nT, u32 n_runs, const u64 *masks, const u32 *run_prot, u32 *flags,
+hipError_t launch_sens_quant(const SDesc *sd, int nT, u32 n_runs, const u32 *run_prot, u32 *flags,
                              hipStream_t s)
 {
-    PROF("k_sens_quant", s, k_sens_quant<<<n_runs, SWG, 0, s>>>(sd, nT, masks, run_prot, flags));
+    PROF("k_sens_quant", s, k_sens_quant<<<n_runs, SWG, 0, s>>>(sd, nT, run_prot, flags));
     return hipGetLastError();
 }
 

@@ -163,3 +163,46 @@ def test_run_edges(ctx, cfg):
     qs, info = ctx.quantize_sens([dev(x) for x, _ in data], [dev(g) for _, g in data], [cfg] * 6, by)
     for q, inf, (x, g), b in zip(qs, info, data, by):
         check(q, inf, x, g, cfg, b)
+
+
+def scratch_of(call):
+    """Device memory that a new context's first call takes (its outputs come from torch's cache)."""
+    from paper_2306_11800_amd import api
+    for _ in range(2):
+        c = api.Context(torch.device("cuda:0"))
+        before = torch.cuda.mem_get_info()[0]
+        keep = call(c)
+        taken = before - torch.cuda.mem_get_info()[0]
+        c.close()
+        del keep
+    return taken
+
+
+def test_scratch_memory(ctx):
+    """The call takes the scores and the compacted values, and beside them no more than a search of the same
+    tensors takes, although it looks for the thresholds of both metrics at once."""
+    rng = np.random.default_rng(7)
+    sizes = [20_000 + 3 * i for i in range(200)] + [9_000_001]
+    data = [make(rng, n) for n in sizes]
+    ts, gs = [dev(a) for a, _ in data], [dev(b) for _, b in data]
+    search = scratch_of(lambda c: c.search(ts, [(4, 0, 0)], 0.1, want_scores=False))
+    sens = scratch_of(lambda c: c.quantize_sens(ts, gs, [(4, 200000, 10000)] * len(ts), [False, True, True] * 67))
+    own = sum(8 * n + 128 + 28 * (n // 16384 + 1) for n in sizes)
+    assert sens <= search + own + (16 << 20), (sens, search, own)
+
+
+def test_scratch_limit(ctx):
+    """A limit that the scores and the compacted values just fit."""
+    from paper_2306_11800_amd import api
+    rng = np.random.default_rng(8)
+    big = dev((0.02 * rng.standard_normal(30_000_003)).astype(np.float32))
+    data = [make(rng, n) for n in (70_001, 33)]
+    ts, gs = [big] + [dev(a) for a, _ in data], [big.flip(0)] + [dev(b) for _, b in data]
+    c = api.Context(torch.device("cuda:0"), scratch_bytes=8 * sum(t.numel() for t in ts) + (1 << 20))
+    cfgs, by = [(4, 200000, 10000)] * 3, [True, True, False]
+    qs, infos = c.quantize_sens(ts, gs, cfgs, by)
+    want, _ = ctx.quantize_sens(ts[:1], gs[:1], cfgs[:1], by[:1])
+    assert torch.equal(qs[0].packed, want[0].packed) and torch.equal(qs[0].outlier_idx, want[0].outlier_idx)
+    for q, inf, (x, g), b in zip(qs[1:], infos[1:], data, by[1:]):
+        check(q, inf, x, g, cfgs[0], b)
+    c.close()
