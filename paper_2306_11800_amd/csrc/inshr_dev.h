@@ -188,8 +188,12 @@ struct TDesc {           // one tensor of a batch
     u64 n_pool;          // elements of the whole group
 };
 constexpr int SAMPLE_RATE = 8;
-constexpr int SMALL_TINY = 4096;   // tensors up to these sizes are searched by one workgroup each
-constexpr int SMALL_MAX = 16384;   // (k_small); one tile at most
+// Tensors up to these sizes are searched by one workgroup each (k_small): as many keys as LDS takes beside
+// the pairs' sums, and by 512 threads, two workgroups to a CU, up to a quarter of that.  105 configurations,
+// one tensor / 300 at once, us of kernel time by sweeps, by 1024 threads, by 512: 256 values
+// 241 / 475, 35 / 69, 39 / 49; 4096: 275 / 530, 47 / 92, 53 / 71; 16384: 318 / 658, 79 / 149, -.
+constexpr int SMALL_TINY = 4096;
+constexpr int SMALL_MAX = 16384;   // one tile at most
 static_assert(SMALL_MAX <= TILE, "a small tensor is one tile");
 
 struct GridDesc {        // the configuration grid, decomposed

@@ -9,7 +9,10 @@
 // 15 us.  What it leaves behind for later calls (thresholds, class counts, boundary keys, centres,
 // protected counts, a key -> bin table of eight bins per key prefix) has the form of the general path.
 //
-// Bound by latency: about 70 barriers and LDS round trips of one workgroup.
+// Bound by latency: about 70 barriers and LDS round trips of one workgroup, and walks of at most 129 values
+// per lane and bin (sum_range).  15 pairs, 90 configurations, one tensor / 300 tensors at once, us: 4096
+// Gaussian values 84 / 95, 16384 100 / 199; 16384 values of one 69 / 132 and 90 % of zero 138 / 269
+// (with every bin walked value by value 6600 / 12400 and 4300 / 7400).
 #include "inshr_launch.h"
 
 namespace inshr {
@@ -41,14 +44,24 @@ __device__ __forceinline__ u32 upper_bound_key(const u32 *keys, u32 n, u32 key) 
 
 __device__ __forceinline__ double value_of_key(u32 k) { return (double)__uint_as_float(bits_of_key(k)); }
 
-// Sum of the values of sorted positions [a, b); the walk starts at a lane's own offset, so that the
-// lanes of a wave, whose ranges are equally long, do not read the same LDS bank step after step.
+// Sum of the values of sorted positions [a, b), which lie in one 8-bit bin (or in a bin of fewer than 256
+// values); the walk starts at a lane's own offset, so that the lanes of a wave, whose ranges are equally
+// long, do not read the same LDS bank step after step.  A bin holds at most n_kept / 256 + 1 values, 65
+// here, unless one value is repeated: all boundaries that fall among equal keys lie at the first of
+// them, so that one bin starts with the whole run (of a constant or mostly zero tensor, nearly
+// everything).  The run is taken at once: count times value, which is exact (14 + 24 bits).
 __device__ __forceinline__ double sum_range(const u32 *keys, u32 a, u32 b)
 {
     if (a >= b) return 0.0;
+    double s = 0.0;
+    if (b - a > 2u * SMALL_MAX / 256u) {
+        const u32 first = keys[a], run = upper_bound_key(keys + a, b - a, first);
+        s = (double)run * value_of_key(first);
+        a += run;
+        if (a >= b) return s;
+    }
     const u32 len = b - a;
     u32 i = a + (threadIdx.x & 63u) % len;
-    double s = 0.0;
     for (u32 j = 0; j < len; j++) {
         s += value_of_key(keys[i]);
         i = i + 1u < b ? i + 1u : a;
