@@ -408,7 +408,7 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         const size_t o_ngt = cv.take(256);
         const size_t o_gcn = cv.take(full((size_t)nB * 2 * MAX_EDGES * 4));
         const size_t o_gsx = cv.take(full((size_t)nB * 2 * MAX_EDGES * 8));
-        const size_t o_to = cv.take((size_t)all_tiles * MAX_FRAC * 4);
+        const size_t o_to = cv.take((size_t)total_tiles * MAX_FRAC * 4);
         const size_t o_ph1 = cv.take(any_pooled ? (size_t)nB * L1_BINS * 4 : 0);
         const size_t o_ms = cv.take(full((size_t)nB * MAX_SUB * 8));
         const size_t zero_end = cv.off; // [o_ts, zero_end) is cleared before the sweeps
@@ -420,7 +420,7 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         const size_t o_tb = cv.take(full((size_t)nB * TGT_STRIDE * 4));
         const size_t o_tr = cv.take(full((size_t)nB * TGT_STRIDE * 4));
         const size_t o_tk = cv.take(full((size_t)nT * TGT_STRIDE * 4));
-        const size_t o_tf = cv.take((size_t)all_tiles * 4);
+        const size_t o_tf = cv.take((size_t)total_tiles * 4);
         const size_t o_sq = cv.take((size_t)units * SQ_STRIDE * 8);
         const size_t o_ed = cv.take(full((size_t)nB * MAX_EDGES * 4));
         const size_t o_sl = cv.take(full((size_t)nB * (L2_BINS + 64) * 2));

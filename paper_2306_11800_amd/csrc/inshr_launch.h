@@ -57,7 +57,7 @@ struct Bufs { // device pointers, indexed by the tensor's position on the device
                     // without an edge
     float *codebook; // [nT][n_cfg][CB_STRIDE]
     Score *scores;  // [nT][n_cfg]
-    u32 *tile_off;  // [tiles] exclusive prefix of protected values per tensor (quantize)
+    u32 *tile_off;  // [tiles of the nB] exclusive prefix of protected values per tensor (quantize)
 };
 
 struct Batch {

@@ -7,7 +7,7 @@
 // 4096-value tensor took 0.45 ms, and in a checkpoint with hundreds of norm weights and biases the
 // per-tensor kernels ran over all of them in several rounds of workgroups.  Sorting 4096 keys takes
 // 15 us.  What it leaves behind for later calls (thresholds, class counts, boundary keys, centres,
-// protected counts, a key -> bin table of eight bins per key prefix) has the form of the general path.
+// a key -> bin table of eight bins per key prefix) has the form of the general path.
 //
 // Bound by latency: about 70 barriers and LDS round trips of one workgroup, and walks of at most 129 values
 // per lane and bin (sum_range).  15 pairs, 90 configurations, one tensor / 300 tensors at once, us: 4096
@@ -276,7 +276,6 @@ __global__ __launch_bounds__(NT) void k_small(const TDesc *__restrict__ td, cons
         if (Mn + Mp == 0u || Mn > n || Mp > n) atomicOr(&st->internal_err, 32u);
     }
     if (tid < n_thr) st->thr_mag[tid] = s_thr[tid];
-    if (tid < n_o) B.tile_out[d.tile0 * MAX_FRAC + tid] = s_cnt[n_p + tid][2] + s_cnt[n_p + tid][3];
     if (tid == 0u) {
         st->n_neg = n_neg;
         st->n_zero = n_nonpos - n_neg;
