@@ -350,8 +350,10 @@ __global__ __launch_bounds__(BLOCK) void k_final(const TDesc *__restrict__ td,
     __shared__ u64 w_c[BLOCK / 64];
     // Keys of bins without an edge: sweep 3 left, per sub-slot, the sum of their 23 mantissa bits.
     // All keys of a sub-slot share sign and exponent E, so their values add up to
-    // +-2^(E-150) (2^23 count + sum of mantissas), or +-2^-149 (sum) for E = 0; the integer is
-    // below 2^51 and the conversion exact.
+    // +-2^(E-150) (2^23 count + sum of mantissas), or +-2^-149 (sum) for E = 0.  The integer is below
+    // 2^24 count: converted exactly for a sub-slot of up to 2^29 keys (a bin holds n_kept / K keys, K the
+    // grid's largest), and rounded once, like any sum in 64 bits, where a larger tensor and a grid of
+    // few bins put more into one.
     const u32 n_sub = st->n_sub;
     const u32 *sub_code = B.sub_code + (size_t)t * MAX_SUB;
     const u32 *sub_cnt = B.sub_cnt + (size_t)t * MAX_SUB;
