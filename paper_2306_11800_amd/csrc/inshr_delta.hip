@@ -425,8 +425,7 @@ __device__ __forceinline__ void rank_rows(const u32 *P, const u32 *C, u32 *wst, 
             }
             reg[r] = at | (within << 16);
             if (CUR) {
-                const u32 x = sp - sc, y = x + Bm; // the one that did not wrap below zero is the smaller
-                u32 m = x < y ? x : y;
+                u32 m = delta_of(sp, sc, Bm);
                 asm volatile("" : "+v"(m)); // (computed here: its operands take twice the registers)
                 dv[r >> 1] = (r & 1u) ? dv[r >> 1] | (m << 16) : m;
             }
@@ -705,7 +704,7 @@ __global__ __launch_bounds__(DBLOCK, 6) void k_dscatter(const DDesc *__restrict_
 
 // regrouping given: e[r] = d[perm[r]] by gathering
 // A given permutation is checked as it is used: an index outside the tensor is skipped and raises
-// DF_PERM; symbols are clamped like those of the scatter, so a delta always fits its field.
+// DF_PERM; symbols are clamped, so that a delta always fits its field.
 __global__ __launch_bounds__(BLOCK) void k_dgather(const DDesc *__restrict__ dd,
                                                    const u32 *__restrict__ chunk_tensor,
                                                    u32 *__restrict__ flags)

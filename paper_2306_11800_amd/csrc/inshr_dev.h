@@ -161,6 +161,14 @@ __host__ __device__ __forceinline__ u32 symbol_bits(u32 K)
     while ((1u << w) < K + 2u) w++;
     return w;
 }
+// difference of two symbols modulo B (Sec. 6); below B also where a malformed stream holds a current symbol
+// that is not, so that no delta reaches into another one's field
+__host__ __device__ __forceinline__ u32 delta_of(u32 prev, u32 cur, u32 B)
+{
+    const u32 x = prev - cur, y = x + B; // the one that did not wrap below zero is the smaller
+    const u32 m = x < y ? x : y;
+    return m < B - 1u ? m : B - 1u;
+}
 
 __host__ __device__ __forceinline__ u32 bucket_flag(u32 l1_bin) { return 0x80000000u >> (l1_bin & 7u); }
 __host__ __device__ __forceinline__ bool in_threshold_bucket(u32 key, u32 entry)
