@@ -475,16 +475,16 @@ __device__ __forceinline__ void regroup_rows(const u32 *wst, u16 *to, const u32 
 //
 // Output: a group's run of one tile is a few dozen bytes, and 258 groups interleave, so storing it
 // as it comes would reach memory as partial lines.  Each group therefore keeps the words of its
-// current 64-byte line in LDS until the line is complete; complete lines are stored whole.  Only the
+// current 32-byte line in LDS until the line is complete; complete lines are stored whole.  Only the
 // ends of a (chunk, group) run are different: its first partial line is stored word by word, its
 // first word, when shared with the run before, and its last partial word are OR-ed into words that
 // k_dgroups cleared.
 //
-// Bound by instruction issue and the LDS pipe together (9-bit symbols: per 64 elements 35 vector and
-// 7.5 LDS instructions, VALU 0.61 and LDS 0.63 of a CU's 58 cycles).  Packing words from regrouped fields
-// costs fewer vector instructions than OR-ing every delta into an image of the words (35 against 40) and
-// leaves room for the permutation in the same array: 6.7 G elements 11.8 -> 11.7 ms, 100 M elements of
-// 4 bits with the permutation 0.37 -> 0.27 ms.
+// Bound by instruction issue and the LDS pipe together (6.7 G elements of 9-bit symbols, 11.5 ms: per 64
+// elements 43 vector and 9.5 LDS instructions, vector issue 0.68 and LDS 0.65 of the time; 1.06 G elements
+// of narrower ones, 1.72 ms: 35 and 7.5, 0.61 and 0.63).  Packing words from regrouped fields costs fewer
+// vector instructions than OR-ing every delta into an image of the words (49, and 10.2 of LDS; 11.6 ms) and
+// leaves room for the permutation in the same array: 100 M elements of 4 bits with it 0.37 -> 0.26 ms.
 template <bool PERM, bool ORDERED>
 __global__ __launch_bounds__(DBLOCK, 6) void k_dscatter(const DDesc *__restrict__ dd,
                                                      const u32 *__restrict__ chunk_tensor,

@@ -21,7 +21,7 @@ namespace inshr {
 // One workgroup per tensor, bound by the latency of its steps.  The edges are put in order by a
 // radix sort of their ranks (a bitonic sort of 4096 words, lane exchanges and all, took two thirds of
 // the kernel), slots and sub-slots of the bins come from scans over the bins (two bisections per bin
-// took the rest): 1 Mi values, 6 pairs: 200 -> 45 us.
+// took the rest): 1 Mi values, 6 pairs: 200 -> 40 us.
 constexpr int EROWS = MAX_EDGES / BLOCK; // edges per thread
 struct EdgeShared {
     u32 below[MAX_EDGES];                // sort: keys below the edge; afterwards the bin of each edge, in order

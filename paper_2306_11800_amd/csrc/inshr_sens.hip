@@ -17,8 +17,9 @@
 //   k_sens_quant      symbols (packed), protected list in index order, boundaries and centres
 //
 // All but the scan stream; the masks (2 bits per element) save the last pass the scores.  202 M values
-// in 9 tensors, 4 bits: score 455 us (5.3 TB/s), partition 569 us (4.1 TB/s; a counting, a serial
-// scan and a compacting pass took 430 + 980 + 630), quant 380 us (from masks; from the scores 711).
+// in 9 tensors, 4 bits: score 460 us (5.3 TB/s), partition 580 us (4.0 TB/s; a counting, a serial
+// scan and a compacting pass took 430 + 980 + 630), quant 380 us (from masks; from the scores 711; bound
+// by vector issue: 75 instructions per 64 elements).
 #include "inshr_launch.h"
 
 namespace inshr {

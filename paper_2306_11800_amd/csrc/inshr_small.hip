@@ -4,9 +4,9 @@
 //
 // The sweeps of the general path (two histograms, threshold select, gather, group sort) are about
 // twenty launches with tables of 32768 bins per tensor behind them, whatever the tensor's size: a
-// 4096-value tensor took 0.45 ms, and in a checkpoint with hundreds of norm weights and biases the
-// per-tensor kernels ran over all of them in several rounds of workgroups.  Sorting 4096 keys takes
-// 15 us.  What it leaves behind for later calls (thresholds, class counts, boundary keys, centres,
+// step of a 4096-value tensor took 0.52 ms (0.14 so), and in a checkpoint with hundreds of norm weights
+// and biases the per-tensor kernels ran over all of them in several rounds of workgroups.  Sorting 4096
+// keys takes 15 us.  What it leaves behind for later calls (thresholds, class counts, boundary keys, centres,
 // a key -> bin table of eight bins per key prefix) has the form of the general path.
 //
 // Bound by latency: about 70 barriers and LDS round trips of one workgroup, and walks of at most 129 values
