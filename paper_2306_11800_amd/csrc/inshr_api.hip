@@ -49,6 +49,7 @@ struct inshr_ctx {
     bool static_pending = false; // the same for inshr_delta_static (its flag word is in its own scratch)
     DevBuf search_mem; // everything a search leaves behind for inshr_quantize
     DevBuf aux_mem;    // quantize descriptors, delta scratch
+    DevBuf totals_mem; // symbol populations of a delta or reconstruct call, per tensor
     DevBuf sketch_mem; // sketch tables, histograms, bucket lists and the centres they give
     DevBuf sens_mem;   // scores, compacted values and block counts of inshr_quantize_sens
     double sketch_alpha = 0.0;                 // the bucket tables last built, and for which alpha
@@ -672,6 +673,7 @@ void inshr_destroy(inshr_ctx *c)
     if (c->aux_mem.p) (void)hipFree(c->aux_mem.p);
     if (c->sketch_mem.p) (void)hipFree(c->sketch_mem.p);
     if (c->sens_mem.p) (void)hipFree(c->sens_mem.p);
+    if (c->totals_mem.p) (void)hipFree(c->totals_mem.p);
     if (c->delta_flags) (void)hipFree(c->delta_flags);
     if (c->h_up.p) (void)hipHostFree(c->h_up.p);
     if (c->h_down.p) (void)hipHostFree(c->h_down.p);
@@ -1631,6 +1633,27 @@ static u32 call_chunk_tiles(const inshr_ctx *c, const inshr_codes *prev, uint32_
     return ct;
 }
 
+// Symbol populations of the tensors of a call, where some tensor has enough chunks for them to be added up.
+static bool wants_totals(const std::vector<DDesc> &dd)
+{
+    for (const DDesc &d : dd)
+        if (d.n_chunks > DELTA_FEW) return true;
+    return false;
+}
+static u32 *call_totals(const inshr_ctx *c, const std::vector<DDesc> &dd)
+{
+    return wants_totals(dd) ? (u32 *)c->totals_mem.p : nullptr;
+}
+static int ensure_totals(inshr_ctx *c, const std::vector<DDesc> &dd)
+{
+    return wants_totals(dd) ? ensure_dev(c, c->totals_mem, sizeof(u32) * DELTA_SS * dd.size()) : INSHR_OK;
+}
+static int clear_totals(inshr_ctx *c, const std::vector<DDesc> &dd)
+{
+    if (wants_totals(dd)) HIPCHK(c, hipMemsetAsync(c->totals_mem.p, 0, sizeof(u32) * DELTA_SS * dd.size(), c->stream));
+    return INSHR_OK;
+}
+
 int inshr_delta(inshr_ctx *c, const inshr_codes *prev, const uint32_t *const *prev_perm,
                 const inshr_codes *cur, inshr_delta_out *out, uint32_t n_tensors)
 {
@@ -1694,6 +1717,7 @@ int inshr_delta(inshr_ctx *c, const inshr_codes *prev, const uint32_t *const *pr
     if (rc) return rc;
     rc = ensure_host(c, c->h_up, up_bytes);
     if (rc) return rc;
+    if ((rc = ensure_totals(c, dd))) return rc;
     // the staging buffer may still be in flight from an earlier asynchronous delta call
     HIPCHK(c, hipStreamSynchronize(c->stream));
     rc = take_delta_flags(c); // (of a call whose flags nobody has asked for yet)
@@ -1703,9 +1727,10 @@ int inshr_delta(inshr_ctx *c, const inshr_codes *prev, const uint32_t *const *pr
     memcpy(hb + o_ct, chunk_tensor.data(), sizeof(u32) * chunk_tensor.size());
     HIPCHK(c, hipMemcpyAsync(db, hb, up_bytes, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemsetAsync(c->delta_flags, 0, sizeof(u32), c->stream));
+    if ((rc = clear_totals(c, dd))) return rc;
     c->delta_pending = true;
     HIPCHK(c, launch_delta((const DDesc *)(db + o_dd), (int)n_tensors, dtile, chunk,
-                           (const u32 *)(db + o_ct), (u32 *)(db + o_ck), c->delta_flags, any_scatter,
+                           (const u32 *)(db + o_ct), (u32 *)(db + o_ck), call_totals(c, dd), c->delta_flags, any_scatter,
                            any_perm, any_gather, c->lds_ordered, c->stream));
     return INSHR_OK;
 }
@@ -1903,8 +1928,10 @@ int inshr_reconstruct(inshr_ctx *c, const inshr_codes *prev, const inshr_delta_o
     if (rc) return rc;
     rc = ensure_host(c, c->h_down, sizeof(u32));
     if (rc) return rc;
+    if ((rc = ensure_totals(c, dd))) return rc;
     HIPCHK(c, hipStreamSynchronize(c->stream));
     char *hb = (char *)c->h_up.p, *db = (char *)c->aux_mem.p;
+    if ((rc = clear_totals(c, dd))) return rc;
     for (uint32_t t = 0; t < n_tensors; t++) dd[t].group_off = (u64 *)(db + o_go) + (size_t)t * (DELTA_SS + 8);
     memset(hb, 0, up_bytes);
     memcpy(hb + o_dd, dd.data(), sizeof(DDesc) * n_tensors);
@@ -1914,7 +1941,7 @@ int inshr_reconstruct(inshr_ctx *c, const inshr_codes *prev, const inshr_delta_o
     u32 *flags = (u32 *)(db + o_fl);
     HIPCHK(c, launch_reconstruct((const DDesc *)(db + o_dd), (const XDesc *)(db + o_xd),
                                  (int)n_tensors, chunk, (const u32 *)(db + o_ct),
-                                 (u32 *)(db + o_ck), flags, c->lds_ordered, c->stream));
+                                 (u32 *)(db + o_ck), call_totals(c, dd), flags, c->lds_ordered, c->stream));
     HIPCHK(c, hipMemcpyAsync(c->h_down.p, flags, sizeof(u32), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     const u32 f = *(const u32 *)c->h_down.p;

@@ -85,12 +85,13 @@ __device__ __forceinline__ void count_symbols(const DDesc &d, u64 c0, u64 c1, u3
 // symbols) still occupies most of its threads.
 __global__ __launch_bounds__(HBLOCK) void k_dhist(const DDesc *__restrict__ dd,
                                                   const u32 *__restrict__ chunk_tensor,
-                                                  u32 *__restrict__ chunk_tot)
+                                                  u32 *__restrict__ chunk_tot, u32 *__restrict__ totals)
 {
     __shared__ u32 hw[HBLOCK / 64][DH_COPIES * SS];
     __shared__ u32 s_nonzero;
     const u64 chunk = blockIdx.x;
-    const DDesc d = dd[__builtin_amdgcn_readfirstlane(chunk_tensor[chunk])];
+    const u32 t = __builtin_amdgcn_readfirstlane(chunk_tensor[chunk]);
+    const DDesc d = dd[t];
     const u32 tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const u32 S = d.Kp + 2u;
     const u64 c_elems = (u64)d.ctiles * DTILE;
@@ -126,64 +127,75 @@ __global__ __launch_bounds__(HBLOCK) void k_dhist(const DDesc *__restrict__ dd,
     for (u32 h = 0; h < 2u; h++) {
         const u32 sy = tid + h * HBLOCK;
         if (sy < (u32)SS) chunk_tot[chunk * SS + sy] = sy < S ? mine[h] : 0u;
+        if (d.n_chunks > DELTA_FEW && sy < S && mine[h]) atomicAdd(&totals[t * (u32)SS + sy], mine[h]); // (cleared beforehand)
     }
 }
 
 // Per tensor: group offsets; chunk_tot becomes the start of each chunk inside its group.  With CLEAR
 // also the stream words that k_dscatter ORs into are cleared: the first word of every (chunk, group)
 // run, which is also where the run before it ends, and the word where the stream ends.
-// The chunks are taken eight at a time, so that one memory latency covers eight of them.
+// A workgroup takes 64 symbols, a lane each, its waves equal shares of the chunks: their sums first, then
+// the starts from the sums of the shares before.  Bound by memory latency, sixteen chunks at a time (one
+// workgroup per tensor whose threads walked all chunks of a symbol, eight at a time: 28 us for the 86 chunks
+// of 1 Mi elements, 9 us so; up to 3072 chunks belong to one tensor).
+// With at most DELTA_FEW chunks one workgroup does it all, a wave per 64 symbols, and adds the populations up itself.
+constexpr u32 DG_WAVES = 8, DG_AHEAD = 16, DG_BLOCKS = (SS + 63) / 64;
+static_assert(DELTA_FEW <= DG_AHEAD && DG_BLOCKS <= DG_WAVES, "one round of loads, a wave per 64 symbols");
 template <bool CLEAR>
-__global__ __launch_bounds__(320) void k_dgroups(const DDesc *__restrict__ dd,
-                                                 u32 *__restrict__ chunk_tot)
+__global__ __launch_bounds__(64 * DG_WAVES) void k_dgroups(const DDesc *__restrict__ dd, u32 *__restrict__ chunk_tot,
+                                                           const u32 *__restrict__ totals)
 {
-    __shared__ u64 wtot[5];
-    const int t = blockIdx.x;
+    __shared__ u32 share[DG_WAVES][64];
+    const u32 t = blockIdx.y, lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const DDesc d = dd[t];
-    const u32 g = threadIdx.x, lane = g & 63u, wave = g >> 6;
-    const u32 S = d.Kp + 2u;
-    GLOBAL_AS u32 *ct = gptr(chunk_tot) + d.chunk0 * SS + g;
-    const u32 nc = (u32)d.n_chunks;
-    u64 run = 0;
-    if (g < (u32)SS) {
-        for (u32 c = 0; c < nc; c += 8u) {
-            u32 v[8];
-#pragma unroll
-            for (u32 j = 0; j < 8u; j++) v[j] = c + j < nc ? ct[(c + j) * SS] : 0u;
-#pragma unroll
-            for (u32 j = 0; j < 8u; j++) {
-                if (c + j < nc) ct[(c + j) * SS] = (u32)run; // n < 2^32
-                run += v[j];
-            }
-        }
-    }
-    u64 inc = g < S ? run : 0ull; // inclusive scan over the groups
-    const u64 mine = inc;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const u64 y = __shfl_up(inc, o);
-        if ((int)lane >= o) inc += y;
-    }
-    if (lane == 63u) wtot[wave] = inc;
-    __syncthreads();
-    u64 off = inc - mine; // (u64: the offsets of a tensor below 2^32 elements, as they are stored)
-    for (u32 w = 0; w < wave; w++) off += wtot[w];
-    if (g <= S) gptr(d.group_off)[g] = off; // (entry S: everything)
-    if (!CLEAR || d.prev_perm) return;
+    const u32 S = d.Kp + 2u, nc = (u32)d.n_chunks;
+    const bool few = nc <= DELTA_FEW, clear = CLEAR && !d.prev_perm;
+    if (few ? blockIdx.x != 0u : blockIdx.x * 64u > S) return;
+    const u32 part = few ? wave : blockIdx.x, g = part * 64u + lane; // this lane's symbol
+    const bool is = part < DG_BLOCKS && g < S;
+    GLOBAL_AS u32 *ct = gptr(chunk_tot) + d.chunk0 * SS + (is ? g : 0u);
     GLOBAL_AS unsigned long long *out = gptr(d.out);
-    if (g == S) {
+    const u32 per = few ? nc : (nc + DG_WAVES - 1u) / DG_WAVES; // chunks of a share
+    const u32 c0 = few ? 0u : wave * per < nc ? wave * per : nc, c1 = c0 + per < nc ? c0 + per : nc;
+    u32 v[DG_AHEAD];
+    auto load = [&](u32 c) {
+#pragma unroll
+        for (u32 j = 0; j < DG_AHEAD; j++) v[j] = is && c + j < c1 ? ct[(u64)(c + j) * SS] : 0u;
+    };
+    u32 sum = 0u; // of the share
+    for (u32 c = c0; c < c1; c += DG_AHEAD) {
+        load(c);
+#pragma unroll
+        for (u32 j = 0; j < DG_AHEAD; j++) sum += v[j];
+    }
+    share[wave][lane] = sum;
+    __syncthreads();
+    u32 off = 0u, run = 0u; // symbols of lower groups (below 2^32, as n is); of this one before the share
+    if (few) {
+        for (u32 w = 0; w < wave; w++) off += wave_sum(share[w][lane]);
+        off += wave_incl_scan(sum) - sum;
+    } else {
+        for (u32 r = 0; r <= part; r++) {
+            const u32 h = r * 64u + lane, x = h < S ? totals[t * (u32)SS + h] : 0u;
+            off += r < part ? wave_sum(x) : wave_incl_scan(x) - x;
+        }
+        for (u32 w = 0; w < wave; w++) run += share[w][lane];
+    }
+    if ((few || wave == 0u) && g <= S) gptr(d.group_off)[g] = off; // (entry S: everything)
+    if (clear && (few || wave == 0u) && g == S) {
         const u64 word = (d.n * d.wB) >> 6; // where the stream ends
         if (word < d.out_words) out[word] = 0ull;
     }
-    if (g >= S) return;
-    for (u32 c = 0; c < nc; c += 8u) {
-        u32 v[8];
+    if (!is) return;
+    for (u32 c = c0; c < c1; c += DG_AHEAD) {
+        if (!few) load(c); // (a single round's are still there)
 #pragma unroll
-        for (u32 j = 0; j < 8u; j++) v[j] = c + j < nc ? ct[(c + j) * SS] : 0u; // (this thread's own stores)
-#pragma unroll
-        for (u32 j = 0; j < 8u; j++) {
-            const u64 word = ((off + v[j]) * d.wB) >> 6;
-            if (c + j < nc && word < d.out_words) out[word] = 0ull;
+        for (u32 j = 0; j < DG_AHEAD; j++) {
+            if (c + j >= c1) break;
+            ct[(u64)(c + j) * SS] = run; // (n < 2^32)
+            const u64 word = ((u64)(off + run) * d.wB) >> 6;
+            if (clear && word < d.out_words) out[word] = 0ull;
+            run += v[j];
         }
     }
 }
@@ -968,12 +980,23 @@ __global__ __launch_bounds__(SS) void k_dcheck_groups(const DDesc *__restrict__ 
         atomicOr(flags, RF_GROUPS);
 }
 
+// totals: NULL when no tensor has more than DELTA_FEW chunks
+template <bool CLEAR>
+static void launch_dgroups(const DDesc *dd, int nT, u32 *chunk_tot, const u32 *totals, hipStream_t s)
+{
+    for (int t0 = 0; t0 < nT; t0 += 65535) { // (the grid's second dimension ends there)
+        const int k = nT - t0 < 65535 ? nT - t0 : 65535;
+        PROF("k_dgroups", s, k_dgroups<CLEAR><<<dim3(totals ? DG_BLOCKS : 1u, k), 64 * DG_WAVES, 0, s>>>(
+                              dd + t0, chunk_tot, totals ? totals + (size_t)t0 * SS : nullptr));
+    }
+}
+
 hipError_t launch_reconstruct(const DDesc *dd, const XDesc *xd, int nT, u64 n_chunks,
-                              const u32 *chunk_tensor, u32 *chunk_tot, u32 *flags, bool lds_ordered,
+                              const u32 *chunk_tensor, u32 *chunk_tot, u32 *totals, u32 *flags, bool lds_ordered,
                               hipStream_t s)
 {
-    PROF("k_dhist", s, k_dhist<<<(unsigned)n_chunks, HBLOCK, 0, s>>>(dd, chunk_tensor, chunk_tot));
-    PROF("k_dgroups", s, k_dgroups<false><<<nT, 320, 0, s>>>(dd, chunk_tot));
+    PROF("k_dhist", s, k_dhist<<<(unsigned)n_chunks, HBLOCK, 0, s>>>(dd, chunk_tensor, chunk_tot, totals));
+    launch_dgroups<false>(dd, nT, chunk_tot, totals, s);
     PROF("k_dcheck_groups", s, k_dcheck_groups<<<nT, SS, 0, s>>>(dd, xd, flags));
     if (lds_ordered)
         PROF("k_drestore", s, k_drestore<true><<<(unsigned)n_chunks, DBLOCK, 0, s>>>(dd, xd, chunk_tensor, chunk_tot, flags));
@@ -1032,7 +1055,8 @@ constexpr size_t DST_DD = 0;                                                   /
 constexpr size_t DST_FLAGS = DST_DD + sizeof(DDesc) * DELTA_STATIC_MAX_TENSORS; // u32 flag word
 constexpr size_t DST_CT = (DST_FLAGS + 256) & ~(size_t)255;                    // u32[MAX_CHUNKS]
 constexpr size_t DST_CK = DST_CT + sizeof(u32) * DELTA_STATIC_MAX_CHUNKS;      // u32[MAX_CHUNKS][SS]
-constexpr size_t DST_BYTES = DST_CK + sizeof(u32) * (size_t)DELTA_STATIC_MAX_CHUNKS * DELTA_SS;
+constexpr size_t DST_TOT = DST_CK + sizeof(u32) * (size_t)DELTA_STATIC_MAX_CHUNKS * DELTA_SS; // u32[MAX_TENSORS][SS]
+constexpr size_t DST_BYTES = DST_TOT + sizeof(u32) * DELTA_STATIC_MAX_TENSORS * DELTA_SS;
 static __device__ __align__(256) unsigned char scratch[DST_BYTES];
 
 constexpr int MAX_DEVICES = 64;
@@ -1057,12 +1081,13 @@ u32 *delta_static_flags(int device)
 
 // descriptors from the kernel arguments into the scratch array; tensor of every chunk; flags cleared
 __global__ __launch_bounds__(256) void k_dstatic_setup(DeltaStaticArgs a, DDesc *__restrict__ dd,
-                                                       u32 *__restrict__ chunk_tensor,
+                                                       u32 *__restrict__ chunk_tensor, u32 *__restrict__ totals,
                                                        u32 *__restrict__ flags)
 {
     const u32 tid = threadIdx.x;
     if (tid < a.n_tensors) dd[tid] = a.dd[tid];
     if (tid == 0u) *flags = 0u;
+    for (u32 i = tid; i < a.n_tensors * (u32)SS; i += 256u) totals[i] = 0u;
     for (u32 t = 0; t < a.n_tensors; t++) {
         const u64 c0 = a.dd[t].chunk0, c1 = c0 + a.dd[t].n_chunks;
         for (u64 c = c0 + tid; c < c1; c += 256u) chunk_tensor[c] = t;
@@ -1079,18 +1104,19 @@ hipError_t launch_delta_static(int device, const DeltaStaticArgs &a, u64 n_dtile
     DDesc *dd = (DDesc *)(base + DST_DD);
     u32 *flags = (u32 *)(base + DST_FLAGS);
     u32 *chunk_tensor = (u32 *)(base + DST_CT);
+    u32 *totals = (u32 *)(base + DST_TOT);
     u32 *chunk_tot = (u32 *)(base + DST_CK); // every entry of the chunks in use is written by k_dhist
-    PROF("k_dstatic_setup", s, k_dstatic_setup<<<1, 256, 0, s>>>(a, dd, chunk_tensor, flags));
-    return launch_delta(dd, (int)a.n_tensors, n_dtiles, n_chunks, chunk_tensor, chunk_tot, flags,
+    PROF("k_dstatic_setup", s, k_dstatic_setup<<<1, 256, 0, s>>>(a, dd, chunk_tensor, totals, flags));
+    return launch_delta(dd, (int)a.n_tensors, n_dtiles, n_chunks, chunk_tensor, chunk_tot, totals, flags,
                         any_scatter, any_perm, false, lds_ordered, s);
 }
 
 hipError_t launch_delta(const DDesc *dd, int nT, u64 n_dtiles, u64 n_chunks,
-                        const u32 *chunk_tensor, u32 *chunk_tot, u32 *flags, bool any_scatter,
+                        const u32 *chunk_tensor, u32 *chunk_tot, u32 *totals, u32 *flags, bool any_scatter,
                         bool any_perm, bool any_gather, bool lds_ordered, hipStream_t s)
 {
-    PROF("k_dhist", s, k_dhist<<<(unsigned)n_chunks, HBLOCK, 0, s>>>(dd, chunk_tensor, chunk_tot));
-    PROF("k_dgroups", s, k_dgroups<true><<<nT, 320, 0, s>>>(dd, chunk_tot));
+    PROF("k_dhist", s, k_dhist<<<(unsigned)n_chunks, HBLOCK, 0, s>>>(dd, chunk_tensor, chunk_tot, totals));
+    launch_dgroups<true>(dd, nT, chunk_tot, totals, s);
     if (any_scatter) {
         if (lds_ordered)
             PROF("k_dscatter", s, k_dscatter<false, true><<<(unsigned)n_chunks, DBLOCK, 0, s>>>(dd, chunk_tensor, chunk_tot, flags));

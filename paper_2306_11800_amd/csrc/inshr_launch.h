@@ -168,6 +168,7 @@ constexpr u32 DF_PERM = 1u;    // a given permutation holds an index outside its
 constexpr u32 DF_ORDER = 2u;   // ranks from returning LDS adds disagree with ranks from ballots
 constexpr int DELTA_TILE = 12288;
 constexpr int DELTA_CHUNK = 64; // most tiles of a chunk
+constexpr u32 DELTA_FEW = 16;   // chunks of a tensor up to which nobody adds its symbols' populations up in `totals`
 // Tiles per chunk of a delta / reconstruct call over n_tiles tiles in all.  A chunk is walked by one
 // workgroup and costs about a tile's time on top of its tiles (its groups' runs are found, opened and
 // closed), so chunks are as long as possible; but two workgroups fit a CU, and with fewer than
@@ -204,7 +205,7 @@ hipError_t launch_score(const Batch &bt, hipStream_t s);
 hipError_t launch_small(const Batch &bt, hipStream_t s); // the whole search of the small tensors
 hipError_t launch_quantize(const Batch &bt, const QDesc *qd, QInfo *qi, hipStream_t s);
 hipError_t launch_delta(const DDesc *dd, int nT, u64 n_dtiles, u64 n_chunks,
-                        const u32 *chunk_tensor, u32 *chunk_tot, u32 *flags, bool any_scatter,
+                        const u32 *chunk_tensor, u32 *chunk_tot, u32 *totals, u32 *flags, bool any_scatter,
                         bool any_perm, bool any_gather, bool lds_ordered, hipStream_t s);
 hipError_t delta_static_init(int device); // once per device, with that device current
 u32 *delta_static_flags(int device);      // the flag word of launch_delta_static on that device
@@ -219,7 +220,7 @@ hipError_t launch_lds_order_check(u32 *violations, hipStream_t s);
 hipError_t launch_dequantize(const RDesc *rd, int nT, u64 n_tiles, u64 max_outlier, u32 *flags,
                              u32 *ones, int n_cu, hipStream_t s);
 hipError_t launch_reconstruct(const DDesc *dd, const XDesc *xd, int nT, u64 n_chunks,
-                              const u32 *chunk_tensor, u32 *chunk_tot, u32 *flags, bool lds_ordered,
+                              const u32 *chunk_tensor, u32 *chunk_tot, u32 *totals, u32 *flags, bool lds_ordered,
                               hipStream_t s);
 
 // ------------------------------------------------------------------------------------------

@@ -152,3 +152,23 @@ def test_small_scratch():
     assert e.value.code == -4
     ctx.close()
     small.close()
+
+
+@pytest.mark.parametrize("n", [16 * 12288, 17 * 12288 + 5, 257 * 12288 + 1])
+def test_numbers_of_chunks(n):
+    """Chunks of one tile: as many as one workgroup takes for a tensor's groups, one more, shares of many."""
+    from paper_2306_11800_amd import api
+    ctx = api.Context(torch.device("cuda:0"))
+    rng = np.random.default_rng(n)
+    K = 32
+    a, b = (symbols(rng, n, K, "skewed" if n % 2 else "even") for _ in range(2))
+    prev, cur = codes(a, K), codes(b, K)
+    d = ctx.delta([prev], [cur], want_perm=True)[0]
+    ctx.sync()
+    order = np.argsort(a, kind="stable")
+    assert np.array_equal(u32(d.perm), order)
+    assert np.array_equal(u64(d.group_off), np.searchsorted(a[order], np.arange(K + 3)))
+    e = (a.astype(np.int64) - b.astype(np.int64)) % (K + 2)
+    assert np.array_equal(u64(d.packed), ref.pack(e[order].astype(np.uint16), api.symbol_bits(K)))
+    assert torch.equal(ctx.reconstruct([prev], [d], [5], [K])[0], cur.packed)
+    ctx.close()
