@@ -151,9 +151,10 @@ typedef struct {
 int inshr_quantize_bound(uint64_t n, const inshr_config *cfg, uint64_t *packed_words,
                          uint64_t *outlier_cap);
 
-#define INSHR_REUSE_SEARCH 1u /* thresholds / boundaries / centres come from the last inshr_search
-                                 on this context, which must have covered exactly these tensors
-                                 (same pointers, sizes, order) and contained each cfg[i] in its
+#define INSHR_REUSE_SEARCH 1u /* thresholds / boundaries / centres are those of the last inshr_search
+                                 on this context (a search that was not asked for scores leaves
+                                 boundaries and centres to this call), which must have covered
+                                 exactly these tensors (same pointers, sizes, order) and contained each cfg[i] in its
                                  grid; the data must not have changed since */
 
 #define INSHR_PROTECT_BF16 2u  /* protected values are stored in bfloat16 (Sec. 4.2): out[i].outlier_val

@@ -49,7 +49,7 @@ struct inshr_ctx {
     bool static_pending = false; // the same for inshr_delta_static (its flag word is in its own scratch)
     DevBuf search_mem; // everything a search leaves behind for inshr_quantize
     DevBuf aux_mem;    // quantize descriptors, delta scratch
-    DevBuf totals_mem; // symbol populations of a delta or reconstruct call, per tensor
+    DevBuf totals_mem; // symbol populations of a delta or reconstruct call, when aux_mem has a limit
     DevBuf sketch_mem; // sketch tables, histograms, bucket lists and the centres they give
     DevBuf sens_mem;   // scores, compacted values and block counts of inshr_quantize_sens
     double sketch_alpha = 0.0;                 // the bucket tables last built, and for which alpha
@@ -67,6 +67,16 @@ struct inshr_ctx {
     std::vector<inshr_tensor> tensors;
     std::vector<u32> pos;       // device position of tensors[t]
     size_t res_off = 0, scores_off = 0;
+    // (what the state holds of boundaries and centres, and what it takes to work out more of them)
+    std::vector<u32> resolved;  // per device position: VIEW_NONE, VIEW_ALL or the one configuration
+    std::vector<TDesc> td;
+    std::vector<u32> groups;    // of the search, empty: none
+    double eps = 0.0;
+    int mode = 0;
+    bool any_pooled = false;
+    uint32_t wcap = 0;          // pool_wcap of the pools' layout
+    uint64_t pool_len = 0;      // u32 entries of the second pool
+    size_t view_off = 0, gw_off = 0, tgo_off = 0, gun_off = 0, view_end = 0;
 };
 
 // ------------------------------------------------------------------------------------------
@@ -191,6 +201,20 @@ struct Carver { // lays sub-buffers out in one allocation, 256-byte aligned
     }
 };
 
+struct QuantScratch { // of inshr_quantize; the first up_bytes are uploaded
+    size_t qd, wg, un, up_bytes, qi, bytes;
+    QuantScratch(uint32_t nT, uint32_t nB, int n_wg)
+    {
+        Carver cv;
+        qd = cv.take(sizeof(QDesc) * nT);
+        wg = cv.take(sizeof(u32) * (n_wg + 1));
+        un = cv.take(sizeof(Unit) * ((size_t)n_wg + nB));
+        up_bytes = cv.off;
+        qi = cv.take(sizeof(QInfo) * nT);
+        bytes = cv.off;
+    }
+};
+
 uint32_t bins_of(const inshr_config &c) { return c.bins ? c.bins : (1u << c.bits); }
 bool same_config(const inshr_config &a, const inshr_config &b)
 {
@@ -258,14 +282,159 @@ int build_grid(const inshr_config *grid, uint32_t n_cfg, double eps, GridDesc &g
     return INSHR_OK;
 }
 
-// light: thresholds, class counts and the second-level table only (for the sketch quantizer, which
-// brings its own bins and takes the protected counts per tile in its own sweep); the state is then
+// The tiles of the tensors ts (device positions, ascending) dealt out evenly to at most n_wg workgroups, in
+// order, and the waves' shares of a gather pool: every wave of a unit owns room for wcap keys per tile of the
+// unit plus one full tile (the sweeps stop gathering when the share cannot take a whole tile any more), and
+// never more than the wave's elements.
+struct Partition {
+    std::vector<Unit> units;
+    std::vector<u32> wg0;   // [workgroups + 1]
+    std::vector<u32> t_off; // [tensors of the search by sweeps + 1] units of every tensor
+    u64 pool = 0;
+};
+void deal_tiles(const std::vector<TDesc> &td, uint32_t nB, const std::vector<u32> &ts, int n_wg, uint32_t wcap,
+                Partition &p)
+{
+    auto tiles_of = [&](u32 t) { return (td[t].n + TILE - 1) / TILE; };
+    if (ts.empty()) {
+        p.wg0.assign(1, 0u);
+        p.t_off.assign(nB + 1, 0u);
+        return;
+    }
+    u64 total = 0;
+    for (u32 t : ts) total += tiles_of(t);
+    n_wg = (int)std::min<u64>(total, (u64)n_wg);
+    p.units.clear();
+    p.wg0.assign(1, 0u);
+    p.t_off.assign(nB + 1, 0u);
+    p.pool = 0;
+    const u64 per_wave = TILE / (BLOCK / 64);
+    size_t k = 0;
+    u64 done = 0; // tiles of the tensors before ts[k]
+    for (int w = 0; w < n_wg; w++) {
+        const u64 lo = total * (u64)w / (u64)n_wg, hi = total * (u64)(w + 1) / (u64)n_wg;
+        for (u64 at = lo; at < hi;) {
+            while (at >= done + tiles_of(ts[k])) done += tiles_of(ts[k++]);
+            const u64 end = std::min(hi, done + tiles_of(ts[k]));
+            Unit u;
+            u.tile0 = (u32)(td[ts[k]].tile0 + (at - done));
+            u.tile1 = (u32)(td[ts[k]].tile0 + (end - done));
+            u.off = p.pool;
+            u.capw = (u32)std::min((end - at) * per_wave, (end - at) * (u64)wcap + per_wave);
+            u.tensor = ts[k];
+            p.t_off[u.tensor + 1]++;
+            p.units.push_back(u);
+            p.pool += (u64)u.capw * (BLOCK / 64);
+            at = end;
+        }
+        p.wg0.push_back((u32)p.units.size());
+    }
+    for (uint32_t t = 0; t < nB; t++) p.t_off[t + 1] += p.t_off[t];
+}
+
+// Gather units for the tensors ts (device positions, ascending), on the device and in p.  The copy is staged
+// at offset at of h_up: nothing in flight reads that part of it, and where it is too small to
+// hold it, nothing in flight reads any of it.
+int upload_units(inshr_ctx *c, const std::vector<u32> &view, const std::vector<u32> &ts, Partition &p, size_t at)
+{
+    Batch &bt = c->batch;
+    const uint32_t nB = (uint32_t)bt.nB;
+    for (int n_wg = bt.n_wg;; n_wg = (n_wg + 1) / 2) { // (fewer workgroups need less of the pool)
+        deal_tiles(c->td, nB, ts, n_wg, c->wcap, p);
+        if (p.pool <= c->pool_len || n_wg == 1) break;
+    }
+    if (p.pool > c->pool_len || p.units.size() > (size_t)bt.n_wg + nB) {
+        c->last_err = "gather units do not fit the search's scratch";
+        return INSHR_E_INTERNAL;
+    }
+    int rc = ensure_host(c, c->h_up, at + (c->view_end - c->view_off));
+    if (rc) return rc;
+    char *hb = (char *)c->h_up.p + at, *db = (char *)c->search_mem.p;
+    memcpy(hb, view.data(), sizeof(u32) * nB);
+    memcpy(hb + (c->gw_off - c->view_off), p.wg0.data(), sizeof(u32) * p.wg0.size());
+    memcpy(hb + (c->tgo_off - c->view_off), p.t_off.data(), sizeof(u32) * (nB + 1));
+    memcpy(hb + (c->gun_off - c->view_off), p.units.data(), sizeof(Unit) * p.units.size());
+    HIPCHK(c, hipMemcpyAsync(db + c->view_off, hb, c->gun_off - c->view_off + sizeof(Unit) * p.units.size(),
+                             hipMemcpyHostToDevice, c->stream));
+    bt.n_gwg = (int)p.wg0.size() - 1;
+    bt.n_gunits = (int)p.units.size();
+    return INSHR_OK;
+}
+
+// Enqueues the work that gives boundaries, centres and errors of the configurations in view (per device
+// position; VIEW_NONE: nothing; at: see upload_units).  The state is complete once the work is done and
+// its results (TState::pool_overflow among them) have been looked at.
+int resolve(inshr_ctx *c, const std::vector<u32> &view, size_t at)
+{
+    std::vector<u32> ts;
+    for (uint32_t t = 0; t < (uint32_t)c->batch.nB; t++)
+        if (view[t] != VIEW_NONE) ts.push_back(t);
+    if (ts.empty()) return INSHR_OK;
+    Partition p;
+    const int rc = upload_units(c, view, ts, p, at);
+    if (rc) return rc;
+    HIPCHK(c, launch_resolve(c->batch, c->stream));
+    return INSHR_OK;
+}
+
+// Tensors that launch_fused takes: its lists of protected values (one entry per protected value, in 1 / 16 of
+// a unit's share of a pool for each wave) are made for small fractions.
+constexpr uint32_t FUSE_MAX_PPM = 10000, FUSE_MIN_WCAP = 32;
+
+// What a search is for.  CHOOSE: best and feasible alone; where bounds of the errors settle the choice of a
+// tensor, nothing else is worked out for it (resolve() does so for the configurations that
+// inshr_quantize asks for).  SCORES: every configuration's score.  GIVEN: thresholds and class counts for
+// a quantizer whose configuration is given.  LIGHT: the same for the sketch quantizer, which
+// brings its own bins and takes the protected counts per tile in its own sweep; the state is then
 // not offered to INSHR_REUSE_SEARCH.
+enum { CHOOSE, SCORES, GIVEN, LIGHT };
+
+// The results of a search or of resolve(), which are in h_down: 1 when a wave's share of a gather pool was
+// too small and the search has to be repeated (with the larger pools that pool_wcap stands for now).
+int check_results(inshr_ctx *c, uint32_t nT, bool any_pooled)
+{
+    const std::vector<u32> &pos = c->pos;
+    const SearchResult *res = (const SearchResult *)c->h_down.p;
+    for (uint32_t t = 0; t < nT; t++) {
+        if (res[t].nonfinite) return INSHR_E_NONFINITE;
+    }
+    for (uint32_t t = 0; t < nT; t++) {
+        if (any_pooled && (res[pos[t]].internal_err & 32u)) { // (a tensor alone always keeps the value of rank P)
+            c->last_err = "the shared thresholds leave tensor " + std::to_string(t) + " without quantized values";
+            return INSHR_E_CONFIG;
+        }
+    }
+    for (uint32_t t = 0; t < nT; t++) {
+        const SearchResult &r = res[pos[t]];
+        if (!r.pool_overflow) continue;
+        // some wave gathered more keys than its share of a pool holds: larger pools, once more
+        const uint32_t full = TILE / (BLOCK / 64);
+        if (c->wcap >= full) {
+            c->last_err = "gather pool overflow with full-size pools on tensor " + std::to_string(t);
+            return INSHR_E_INTERNAL;
+        }
+        c->pool_wcap = std::min<uint32_t>(full, c->wcap * 2);
+        if (getenv("INSHR_SAMPLE_DEBUG"))
+            fprintf(stderr, "inshr_search: gather pools too small (tensor %u, code %u): again with %u keys per wave and tile\n",
+                    t, r.pool_overflow, c->pool_wcap);
+        return 1;
+    }
+    for (uint32_t t = 0; t < nT; t++) {
+        if (res[pos[t]].internal_err) {
+            c->last_err = "kernel self-check failed on tensor " + std::to_string(t) + ", code " +
+                          std::to_string(res[pos[t]].internal_err);
+            return INSHR_E_INTERNAL;
+        }
+    }
+    return INSHR_OK;
+}
+
 // group: NULL, or one number per tensor; tensors with equal numbers share their thresholds, which
 // are then order statistics of the group's pooled magnitudes (Sec. 4.2, per-layer-type pruning).
 int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const inshr_config *grid,
-               uint32_t n_cfg, double eps, bool want_scores, bool light = false, const uint32_t *group = nullptr)
+               uint32_t n_cfg, double eps, int mode, const uint32_t *group = nullptr)
 {
+    const bool light = mode == LIGHT, want_scores = mode == SCORES;
     c->have_search = false;
     if (!tensors || !grid || nT == 0) return INSHR_E_ARG;
     // leader of every tensor's group and the group's size
@@ -330,13 +499,13 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
     // work partition: tiles are dealt out evenly to workgroups in order
     const int n_wg = (int)std::min<uint64_t>(total_tiles, (uint64_t)c->n_cu * c->wg_per_cu);
     const int n_wg_all = (int)std::min<uint64_t>(all_tiles, (uint64_t)c->n_cu * c->wg_per_cu);
-    std::vector<TDesc> td(nT);
+    std::vector<TDesc> &td = c->td;
+    td.assign(nT, TDesc());
     std::vector<u64> wg_tile0(n_wg + 1);
-    std::vector<u32> wg_fu0(n_wg);
-    std::vector<u32> unit_tensor; // (the units of a tensor are consecutive)
-    std::vector<u32> t_unit0(nB + 1);
+    size_t view_at = 0; // in h_up, behind what this call and a quantizer upload
+    c->wcap = c->pool_wcap;
     {
-        u64 tile = 0, pool = 0;
+        u64 tile = 0;
         bool any_sampled = false;
         for (uint32_t t = 0; t < nT; t++) {
             const uint32_t u = user_of[t];
@@ -344,7 +513,6 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
             td[t].n = tensors[u].n;
             td[t].tile0 = tile;
             td[t].pool_grp = td[t].pool_len = 0;
-            td[t].aligned16 = (((uintptr_t)tensors[u].data & 15u) == 0) ? 1u : 0u;
             td[t].leader = pos[leader[u]];
             td[t].pooled = members[leader[u]] > 1 ? 1u : 0u;
             td[t].n_pool = n_pool[leader[u]];
@@ -356,39 +524,20 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
             tile += (td[t].n + TILE - 1) / TILE;
         }
         for (int w = 0; w <= n_wg; w++) wg_tile0[w] = n_wg ? total_tiles * (u64)w / (u64)n_wg : 0;
-        // Gather pools: every wave of a (workgroup, tensor) unit owns a share of each pool, sized for
-        // pool_wcap keys per tile of the unit plus one full tile (the sweeps stop gathering when the
-        // share cannot take a whole tile any more), and never more than the wave's elements.
-        std::vector<u64> unit_off;
-        std::vector<u32> unit_capw;
-        u32 units = 0;
-        uint32_t t = 0;
-        for (int w = 0; w < n_wg; w++) {
-            wg_fu0[w] = units;
-            const u64 lo = wg_tile0[w], hi = wg_tile0[w + 1];
-            if (lo >= hi) continue;
-            while (t + 1 < nB && td[t + 1].tile0 <= lo) t++;
-            uint32_t tt = t;
-            while (true) {
-                const bool first = unit_tensor.empty() || unit_tensor.back() != tt;
-                if (first) t_unit0[tt] = units;
-                unit_tensor.push_back(tt);
-                units++;
-                const u64 t_end = (tt + 1 < nB) ? td[tt + 1].tile0 : total_tiles;
-                const u64 u_lo = std::max(lo, td[tt].tile0), u_hi = std::min(hi, t_end);
-                const u64 tiles_u = u_hi - u_lo;
-                const u64 per_wave = TILE / (BLOCK / 64);
-                const u64 capw = std::min(tiles_u * per_wave, tiles_u * (u64)c->pool_wcap + per_wave);
-                if (first) td[tt].pool_grp = pool;
-                unit_off.push_back(pool);
-                unit_capw.push_back((u32)capw);
-                td[tt].pool_len += capw * (BLOCK / 64);
-                pool += capw * (BLOCK / 64);
-                if (t_end >= hi) break;
-                tt++;
-            }
+        Partition part;
+        {
+            std::vector<u32> all(nB);
+            for (uint32_t t = 0; t < nB; t++) all[t] = t;
+            deal_tiles(td, nB, all, n_wg, c->wcap, part);
         }
-        t_unit0[nB] = units;
+        const u32 units = (u32)part.units.size();
+        const u64 pool = part.pool;
+        for (u32 u = units; u-- > 0;) { // a tensor's span of the pool: its units'
+            TDesc &d = td[part.units[u].tensor];
+            d.pool_grp = part.units[u].off;
+            d.pool_len += (u64)part.units[u].capw * (BLOCK / 64);
+        }
+        c->pool_len = pool;
         // device layout; what only boundaries and scores need is left out of a light search (k_plan2 ends it)
         Carver cv;
         auto full = [&](size_t bytes) { return light ? (size_t)0 : bytes; };
@@ -398,21 +547,26 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         const size_t o_wa = cv.take(sizeof(u64) * (n_wg_all + 1));
         const size_t o_wf = cv.take(sizeof(u32) * n_wg);
         const size_t o_tfo = cv.take(sizeof(u32) * (nB + 1));
-        const size_t o_tfi = cv.take(sizeof(u32) * units);
-        const size_t o_fut = cv.take(sizeof(u32) * units);
-        const size_t o_us = cv.take((size_t)units * 8);
-        const size_t o_usb = cv.take((size_t)units * 4);
+        const size_t o_un = cv.take(sizeof(Unit) * units);
         const size_t up_bytes = cv.off;
         const size_t o_ts = cv.take(sizeof(TState) * nT);
-        const size_t o_h1 = cv.take((size_t)nB * L1_BINS * 4);
+        const size_t o_h1 = cv.off; // once the thresholds stand, the first histogram makes room for ...
+        cv.take(((size_t)n_wg + nB) * 16 * 4); // ... counts and sums of the gather units and ...
+        c->view_off = cv.take(sizeof(u32) * nB); // ... what upload_units writes
+        c->gw_off = cv.take(nB ? sizeof(u32) * (n_wg + 1) : 0);
+        c->tgo_off = cv.take(nB ? sizeof(u32) * (nB + 1) : 0);
+        c->gun_off = cv.take(sizeof(Unit) * ((size_t)n_wg + nB));
+        c->view_end = cv.off;
+        cv.off = std::max(cv.off, o_h1 + (size_t)nB * L1_BINS * 4);
         const size_t o_h2 = cv.take((size_t)nB * L2_BINS * 4);
+        const size_t o_ph1 = cv.take(any_pooled ? (size_t)nB * L1_BINS * 4 : 0);
+        const size_t zero_full = cv.off; // [o_ts, here) is cleared before the sweeps, and for a light search
+        const size_t o_to = cv.take((size_t)total_tiles * MAX_FRAC * 4);
+        const size_t zero_end = light ? cv.off : zero_full; // ... up to here (launch_resolve clears what it adds to)
         const size_t o_ngt = cv.take(256);
         const size_t o_gcn = cv.take(full((size_t)nB * 2 * MAX_EDGES * 4));
         const size_t o_gsx = cv.take(full((size_t)nB * 2 * MAX_EDGES * 8));
-        const size_t o_to = cv.take((size_t)total_tiles * MAX_FRAC * 4);
-        const size_t o_ph1 = cv.take(any_pooled ? (size_t)nB * L1_BINS * 4 : 0);
         const size_t o_ms = cv.take(full((size_t)nB * MAX_SUB * 8));
-        const size_t zero_end = cv.off; // [o_ts, zero_end) is cleared before the sweeps
         const size_t o_psel = cv.take(any_pooled ? (size_t)nB * 2 * SEL_WORDS * 4 : 0);
         const size_t o_rs = cv.take(sizeof(SearchResult) * nT);
         const size_t o_tab = cv.take((size_t)nT * COARSE * 4);
@@ -435,7 +589,7 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         const size_t o_sbn = cv.take(full((size_t)nB * MAX_SUB * 4));
         const size_t o_cb = cv.take(full((size_t)nT * n_cfg * CB_STRIDE * 4));
         const size_t o_sc = cv.take(full((size_t)nT * n_cfg * sizeof(Score)));
-        const size_t o_uc = cv.take(full((size_t)units * 16 * 4));
+        const size_t o_uc = cv.take(full(((size_t)n_wg + nB) * 16 * 4));
         const size_t o_bg = cv.take(full((size_t)nB * L2_BINS * 2));
         const size_t o_go = cv.take(full((size_t)nB * MAX_GROUPS * 4));
         const size_t o_ge = cv.take(full((size_t)nB * MAX_GROUPS * 4));
@@ -448,23 +602,21 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         const size_t o_pool2 = cv.take(full((size_t)pool * 4));
         rc = ensure_dev(c, c->search_mem, cv.off);
         if (rc) return rc;
-        rc = ensure_host(c, c->h_up, up_bytes);
+        // (as large as quantizing from this state will want it)
+        view_at = std::max(up_bytes, QuantScratch(nT, nB, n_wg).up_bytes);
+        rc = ensure_host(c, c->h_up, view_at + (c->view_end - c->view_off));
         if (rc) return rc;
         char *hb = (char *)c->h_up.p;
         char *db = (char *)c->search_mem.p;
         memcpy(hb + o_td, td.data(), sizeof(TDesc) * nT);
         memcpy(hb + o_gd, &g, sizeof(GridDesc));
         memcpy(hb + o_wt, wg_tile0.data(), sizeof(u64) * (n_wg + 1));
-        memcpy(hb + o_wf, wg_fu0.data(), sizeof(u32) * n_wg);
+        memcpy(hb + o_wf, part.wg0.data(), sizeof(u32) * n_wg);
+        memcpy(hb + o_tfo, part.t_off.data(), sizeof(u32) * (nB + 1));
+        memcpy(hb + o_un, part.units.data(), sizeof(Unit) * units);
         {
-            u32 *tfi = (u32 *)(hb + o_tfi);
-            for (u32 u = 0; u < units; u++) tfi[u] = u;
-            memcpy(hb + o_tfo, t_unit0.data(), sizeof(u32) * (nB + 1));
-            memcpy(hb + o_fut, unit_tensor.data(), sizeof(u32) * units);
             u64 *wa = (u64 *)(hb + o_wa);
             for (int w = 0; w <= n_wg_all; w++) wa[w] = all_tiles * (u64)w / (u64)n_wg_all;
-            memcpy(hb + o_us, unit_off.data(), sizeof(u64) * units);
-            memcpy(hb + o_usb, unit_capw.data(), sizeof(u32) * units);
         }
         HIPCHK(c, hipMemcpyAsync(db, hb, up_bytes, hipMemcpyHostToDevice, c->stream));
         HIPCHK(c, hipMemsetAsync(db + o_ts, 0, zero_end - o_ts, c->stream));
@@ -475,8 +627,8 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         bt.wg_tile0 = (const u64 *)(db + o_wt);
         bt.wg_fu0 = (const u32 *)(db + o_wf);
         bt.t_fu_off = (const u32 *)(db + o_tfo);
-        bt.t_fu_ids = (const u32 *)(db + o_tfi);
-        bt.fu_tensor = (const u32 *)(db + o_fut);
+        bt.wg_gu0 = (const u32 *)(db + c->gw_off);
+        bt.t_gu_off = (const u32 *)(db + c->tgo_off);
         bt.grp_list = (u32 *)(db + o_gl);
         bt.n_grp_total = (u32 *)(db + o_ngt);
         bt.n_units = (int)units;
@@ -503,9 +655,10 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         B.pool_sel = (u32 *)(db + o_psel);
         B.hist2 = (u32 *)(db + o_h2);
         B.table2 = (u32 *)(db + o_tab);
-        B.unit_off = (const u64 *)(db + o_us);
+        B.units = (const Unit *)(db + o_un);
+        B.gunits = (const Unit *)(db + c->gun_off);
+        B.view = (const u32 *)(db + c->view_off);
         B.unit_thr = (u32 *)(db + o_ut);
-        B.unit_capw = (const u32 *)(db + o_usb);
         B.binfo = (u32 *)(db + o_bi);
         B.tgt_bin = (u32 *)(db + o_tb);
         B.tgt_res = (u32 *)(db + o_tr);
@@ -513,6 +666,7 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         B.pool = (u32 *)(db + o_pool);
         B.pool2 = (u32 *)(db + o_pool2);
         B.unit_cand = (u32 *)(db + o_uc);
+        B.unit_prot = (u32 *)(db + o_h1);
         B.bin_group = (u16 *)(db + o_bg);
         B.grp_off = (u32 *)(db + o_go);
         B.grp_end = (u32 *)(db + o_ge);
@@ -523,6 +677,8 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         B.tile_out = (u32 *)(db + o_to);
         B.tile_off = (u32 *)(db + o_tf);
         B.sq_part = (double *)(db + o_sq);
+        B.sq_prot = (double *)(db + o_h1);
+        static_assert(MAX_FRAC * sizeof(double) == 16 * sizeof(u32), "sq_prot and unit_prot take the same room");
         B.edges = (u32 *)(db + o_ed);
         B.sl = (u16 *)(db + o_sl);
         B.pair_eidx = (u16 *)(db + o_pe);
@@ -544,42 +700,42 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
     c->batch.light = light;
     HIPCHK(c, launch_small(c->batch, c->stream));
     HIPCHK(c, launch_select(c->batch, c->stream));
-    if (!light) HIPCHK(c, launch_score(c->batch, c->stream));
+    c->resolved.assign(nT, VIEW_ALL); // (the small tensors are searched completely)
+    std::fill(c->resolved.begin(), c->resolved.begin() + nB, VIEW_NONE);
+    if (mode == CHOOSE) {
+        HIPCHK(c, launch_decide(c->batch, c->stream));
+    } else if (mode == SCORES) {
+        std::fill(c->resolved.begin(), c->resolved.begin() + nB, VIEW_ALL);
+        if ((rc = resolve(c, c->resolved, view_at))) return rc;
+    } else {
+        HIPCHK(c, launch_counts(c->batch, c->stream));
+    }
 
     // results, in device order
     const size_t rs_bytes = sizeof(SearchResult) * nT, sc_bytes = want_scores ? sizeof(Score) * (size_t)nT * n_cfg : 0;
-    rc = ensure_host(c, c->h_down, rs_bytes + sc_bytes);
+    rc = ensure_host(c, c->h_down, rs_bytes + std::max(sc_bytes, sizeof(QInfo) * nT));
     if (rc) return rc;
     char *db = (char *)c->search_mem.p;
-    HIPCHK(c, hipMemcpyAsync(c->h_down.p, db + c->res_off, rs_bytes, hipMemcpyDeviceToHost, c->stream));
-    if (sc_bytes)
-        HIPCHK(c, hipMemcpyAsync((char *)c->h_down.p + rs_bytes, db + c->scores_off, sc_bytes,
-                                 hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
     const SearchResult *res = (const SearchResult *)c->h_down.p;
-    for (uint32_t t = 0; t < nT; t++) {
-        if (res[t].nonfinite) return INSHR_E_NONFINITE;
-    }
-    for (uint32_t t = 0; t < nT; t++) {
-        if (any_pooled && (res[pos[t]].internal_err & 32u)) { // (a tensor alone always keeps the value of rank P)
-            c->last_err = "the shared thresholds leave tensor " + std::to_string(t) + " without quantized values";
-            return INSHR_E_CONFIG;
-        }
-    }
-    for (uint32_t t = 0; t < nT; t++) {
-        const SearchResult &r = res[pos[t]];
-        if (!r.pool_overflow) continue;
-        // some wave gathered more keys than its share of a pool holds: larger pools, once more
-        const uint32_t full = TILE / (BLOCK / 64);
-        if (c->pool_wcap >= full) {
-            c->last_err = "gather pool overflow with full-size pools on tensor " + std::to_string(t);
-            return INSHR_E_INTERNAL;
-        }
-        c->pool_wcap = std::min<uint32_t>(full, c->pool_wcap * 2);
-        if (getenv("INSHR_SAMPLE_DEBUG"))
-            fprintf(stderr, "inshr_search: gather pools too small (tensor %u, code %u): again with %u keys per wave and tile\n",
-                    t, r.pool_overflow, c->pool_wcap);
-        return run_search(c, tensors, nT, grid, n_cfg, eps, want_scores, light, group);
+    for (;;) {
+        HIPCHK(c, hipMemcpyAsync(c->h_down.p, db + c->res_off, rs_bytes, hipMemcpyDeviceToHost, c->stream));
+        if (sc_bytes)
+            HIPCHK(c, hipMemcpyAsync((char *)c->h_down.p + rs_bytes, db + c->scores_off, sc_bytes,
+                                     hipMemcpyDeviceToHost, c->stream));
+        HIPCHK(c, hipStreamSynchronize(c->stream));
+        rc = check_results(c, nT, any_pooled);
+        if (rc == 1) return run_search(c, tensors, nT, grid, n_cfg, eps, mode, group);
+        if (rc) return rc;
+        // tensors whose choice the bounds leave open are scored
+        std::vector<u32> open(nB, VIEW_NONE);
+        bool any_open = false;
+        for (uint32_t t = 0; t < nB; t++)
+            if (res[t].best == VIEW_NONE) {
+                open[t] = c->resolved[t] = VIEW_ALL;
+                any_open = true;
+            }
+        if (!any_open) break;
+        if ((rc = resolve(c, open, view_at))) return rc;
     }
     if (getenv("INSHR_SAMPLE_DEBUG")) { // how many sampled first sweeps had to be repeated exactly
         uint32_t n_sampled = 0, n_redo = 0;
@@ -594,18 +750,57 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         fprintf(stderr, "inshr_search: %u tensors, %u with a sampled first sweep, %u of them repeated\n",
                 nT, n_sampled, n_redo);
     }
-    for (uint32_t t = 0; t < nT; t++) {
-        if (res[pos[t]].internal_err) {
-            c->last_err = "kernel self-check failed on tensor " + std::to_string(t) + ", code " +
-                          std::to_string(res[pos[t]].internal_err);
-            return INSHR_E_INTERNAL;
-        }
-    }
     c->grid = g;
     c->grid_cfgs.assign(grid, grid + n_cfg);
     c->tensors.assign(tensors, tensors + nT);
+    c->groups.clear();
+    if (group) c->groups.assign(group, group + nT);
+    c->eps = eps;
+    c->mode = mode;
+    c->any_pooled = any_pooled;
     c->have_search = !light;
     return INSHR_OK;
+}
+
+// The last search once more, for larger pools (check_results).
+int repeat_search(inshr_ctx *c)
+{
+    const std::vector<inshr_tensor> tensors = c->tensors;
+    const std::vector<inshr_config> grid = c->grid_cfgs;
+    const std::vector<u32> groups = c->groups;
+    return run_search(c, tensors.data(), (uint32_t)tensors.size(), grid.data(), (uint32_t)grid.size(), c->eps, c->mode,
+                      groups.empty() ? nullptr : groups.data());
+}
+
+// Everything a search with scores leaves behind, for all tensors.
+int resolve_all(inshr_ctx *c)
+{
+    const uint32_t nT = (uint32_t)c->batch.nT;
+    for (;;) {
+        std::vector<u32> view(nT, VIEW_NONE);
+        bool any = false;
+        for (uint32_t t = 0; t < (uint32_t)c->batch.nB; t++)
+            if (c->resolved[t] != VIEW_ALL) {
+                view[t] = VIEW_ALL;
+                any = true;
+            }
+        if (!any) return INSHR_OK;
+        HIPCHK(c, hipStreamSynchronize(c->stream));
+        int rc = resolve(c, view, 0);
+        if (rc) return rc;
+        rc = ensure_host(c, c->h_down, sizeof(SearchResult) * nT);
+        if (rc) return rc;
+        HIPCHK(c, hipMemcpyAsync(c->h_down.p, (char *)c->search_mem.p + c->res_off, sizeof(SearchResult) * nT,
+                                 hipMemcpyDeviceToHost, c->stream));
+        HIPCHK(c, hipStreamSynchronize(c->stream));
+        rc = check_results(c, nT, c->any_pooled);
+        if (rc == 1) {
+            if ((rc = repeat_search(c))) return rc;
+            continue;
+        }
+        if (rc) return rc;
+        std::fill(c->resolved.begin(), c->resolved.end(), VIEW_ALL);
+    }
 }
 
 } // namespace
@@ -671,9 +866,9 @@ void inshr_destroy(inshr_ctx *c)
     (void)hipStreamSynchronize(c->stream);
     if (c->search_mem.p) (void)hipFree(c->search_mem.p);
     if (c->aux_mem.p) (void)hipFree(c->aux_mem.p);
+    if (c->totals_mem.p) (void)hipFree(c->totals_mem.p);
     if (c->sketch_mem.p) (void)hipFree(c->sketch_mem.p);
     if (c->sens_mem.p) (void)hipFree(c->sens_mem.p);
-    if (c->totals_mem.p) (void)hipFree(c->totals_mem.p);
     if (c->delta_flags) (void)hipFree(c->delta_flags);
     if (c->h_up.p) (void)hipHostFree(c->h_up.p);
     if (c->h_down.p) (void)hipHostFree(c->h_down.p);
@@ -758,7 +953,7 @@ int inshr_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t n_tensors,
                  uint8_t *feasible, inshr_score *scores)
 {
     if (!c || !best || !feasible) return INSHR_E_ARG;
-    int rc = run_search(c, tensors, n_tensors, grid, n_cfg, eps, scores != nullptr);
+    int rc = run_search(c, tensors, n_tensors, grid, n_cfg, eps, scores ? SCORES : CHOOSE);
     if (rc) return rc;
     take_results(c, n_tensors, n_cfg, best, feasible, scores);
     return INSHR_OK;
@@ -769,7 +964,7 @@ int inshr_search_pooled(inshr_ctx *c, const inshr_tensor *tensors, const uint32_
                         uint32_t *best, uint8_t *feasible, inshr_score *scores)
 {
     if (!c || !best || !feasible || !group) return INSHR_E_ARG;
-    int rc = run_search(c, tensors, n_tensors, grid, n_cfg, eps, scores != nullptr, false, group);
+    int rc = run_search(c, tensors, n_tensors, grid, n_cfg, eps, scores ? SCORES : CHOOSE, group);
     if (rc) return rc;
     take_results(c, n_tensors, n_cfg, best, feasible, scores);
     return INSHR_OK;
@@ -819,23 +1014,96 @@ static int quantize_with_state(inshr_ctx *c, const inshr_config *cfg, inshr_quan
         qd[t].alt_key = alt_key ? alt_key + (size_t)t * 256 : nullptr;
         qd[t].alt_cb = alt_cb ? alt_cb + (size_t)t * 256 : nullptr;
     }
-    Carver cv;
-    const size_t o_qd = cv.take(sizeof(QDesc) * nT);
-    const size_t o_qi = cv.take(sizeof(QInfo) * nT);
-    int rc = ensure_dev(c, c->aux_mem, cv.off);
+    const uint32_t nB = (uint32_t)c->batch.nB;
+    const QuantScratch lay(nT, nB, c->batch.n_wg);
+    const size_t o_qd = lay.qd, o_wg = lay.wg, o_un = lay.un, o_qi = lay.qi, up_bytes = lay.up_bytes;
+    int rc = ensure_dev(c, c->aux_mem, lay.bytes);
     if (rc) return rc;
-    rc = ensure_host(c, c->h_up, sizeof(QDesc) * nT);
+    rc = ensure_host(c, c->h_up, up_bytes);
     if (rc) return rc;
-    rc = ensure_host(c, c->h_down, sizeof(QInfo) * nT);
+    rc = ensure_host(c, c->h_down, (sizeof(QInfo) + sizeof(SearchResult)) * nT);
     if (rc) return rc;
     char *db = (char *)c->aux_mem.p;
     HIPCHK(c, hipStreamSynchronize(c->stream)); // staging buffers may be in flight (inshr_delta)
-    memcpy(c->h_up.p, qd.data(), sizeof(QDesc) * nT);
-    HIPCHK(c, hipMemcpyAsync(db + o_qd, c->h_up.p, sizeof(QDesc) * nT, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, launch_quantize(c->batch, (const QDesc *)(db + o_qd), (QInfo *)(db + o_qi), c->stream));
-    HIPCHK(c, hipMemcpyAsync(c->h_down.p, db + o_qi, sizeof(QInfo) * nT, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    const QInfo *qi = (const QInfo *)c->h_down.p;
+    // Tensors whose boundaries and centres the state does not hold are quantized in one sweep that works them
+    // out (launch_fused).  Where that does not do (a protect fraction whose lists are long, or what the
+    // kernels find too much for them), and for those the state holds, the ordinary way.
+    std::vector<char> done(nT, 0), apart(nT, 0);
+    const std::vector<QDesc> asked = nB ? qd : std::vector<QDesc>();
+    for (;;) {
+        std::vector<u32> fuse, ready, view(nT, VIEW_NONE);
+        bool open = false;
+        for (uint32_t t = 0; t < nB; t++) {
+            if (!asked[t].packed || done[t]) continue;
+            if (alt_key || c->resolved[t] == VIEW_ALL || c->resolved[t] == asked[t].cfg)
+                ready.push_back(t);
+            else if (!apart[t] && c->wcap >= FUSE_MIN_WCAP && c->grid_cfgs[asked[t].cfg].outlier_ppm <= FUSE_MAX_PPM)
+                fuse.push_back(t);
+            else
+                open = true;
+        }
+        Partition p;
+        if (!fuse.empty()) {
+            if ((rc = upload_units(c, view, fuse, p, up_bytes))) return rc;
+            for (u32 t : fuse) c->resolved[t] = VIEW_NONE;
+        } else if (open) {
+            ready.clear();
+            for (uint32_t t = 0; t < nB; t++) {
+                if (!asked[t].packed || done[t]) continue;
+                if (c->resolved[t] != VIEW_ALL && c->resolved[t] != asked[t].cfg) view[t] = asked[t].cfg;
+                ready.push_back(t);
+            }
+            if ((rc = resolve(c, view, up_bytes))) return rc;
+        }
+        for (uint32_t t = 0; nB && t < nT; t++) {
+            qd[t] = asked[t];
+            if (done[t]) qd[t].packed = nullptr;
+        }
+        for (u32 t : fuse) {
+            const u32 u0 = p.t_off[t], u1 = p.t_off[t + 1];
+            qd[t].fused = 1u;
+            qd[t].span = p.units[u0].off;
+            qd[t].span_len = p.units[u1 - 1].off + (u64)p.units[u1 - 1].capw * (BLOCK / 64) - qd[t].span;
+        }
+        Partition pq;
+        deal_tiles(c->td, nB, ready, c->batch.n_wg, c->wcap, pq);
+        char *hb = (char *)c->h_up.p;
+        memcpy(hb + o_qd, qd.data(), sizeof(QDesc) * nT);
+        memcpy(hb + o_wg, pq.wg0.data(), sizeof(u32) * pq.wg0.size());
+        memcpy(hb + o_un, pq.units.data(), sizeof(Unit) * pq.units.size());
+        HIPCHK(c, hipMemcpyAsync(db, hb, o_un + sizeof(Unit) * pq.units.size(), hipMemcpyHostToDevice, c->stream));
+        const QDesc *dq = (const QDesc *)(db + o_qd);
+        QInfo *dqi = (QInfo *)(db + o_qi);
+        if (!fuse.empty()) HIPCHK(c, launch_fused(c->batch, dq, dqi, c->stream));
+        HIPCHK(c, launch_quantize(c->batch, dq, (const Unit *)(db + o_un), (const u32 *)(db + o_wg),
+                                  (int)pq.wg0.size() - 1, dqi, c->stream));
+        const bool any = !fuse.empty() || open;
+        // (search results first: check_results looks for them there)
+        if (any)
+            HIPCHK(c, hipMemcpyAsync(c->h_down.p, (char *)c->search_mem.p + c->res_off, sizeof(SearchResult) * nT,
+                                     hipMemcpyDeviceToHost, c->stream));
+        HIPCHK(c, hipMemcpyAsync((char *)c->h_down.p + sizeof(SearchResult) * nT, db + o_qi, sizeof(QInfo) * nT,
+                                 hipMemcpyDeviceToHost, c->stream));
+        HIPCHK(c, hipStreamSynchronize(c->stream));
+        if (!any) break;
+        rc = check_results(c, nT, c->any_pooled);
+        if (rc < 0) return rc;
+        if (rc == 1) { // larger pools: from the start
+            if ((rc = repeat_search(c))) return rc;
+            std::fill(done.begin(), done.end(), 0);
+            continue;
+        }
+        const SearchResult *res = (const SearchResult *)c->h_down.p;
+        for (uint32_t t = 0; t < nT; t++) done[t] = asked[t].packed && (t >= nB || done[t]);
+        for (u32 t : ready) done[t] = 1;
+        for (u32 t : fuse) (res[t].fuse_bad ? apart : done)[t] = 1;
+        for (uint32_t t = 0; t < nB; t++)
+            if (view[t] != VIEW_NONE) c->resolved[t] = view[t];
+        bool all = true;
+        for (uint32_t t = 0; t < nT; t++) all = all && (done[t] || !asked[t].packed);
+        if (all) break;
+    }
+    const QInfo *qi = (const QInfo *)((const char *)c->h_down.p + sizeof(SearchResult) * nT);
     int result = INSHR_OK;
     for (uint32_t k = 0; k < n_sel; k++) {
         const QInfo &r = qi[c->pos[which[k]]];
@@ -891,7 +1159,7 @@ int inshr_quantize(inshr_ctx *c, const inshr_tensor *tensors, const inshr_config
                 idx.push_back(t);
             }
         }
-        int rc = run_search(c, sub.data(), (uint32_t)sub.size(), &cfg[t0], 1, 0.0, false);
+        int rc = run_search(c, sub.data(), (uint32_t)sub.size(), &cfg[t0], 1, 0.0, GIVEN);
         if (rc) return rc;
         std::vector<inshr_quantized> subout(sub.size());
         std::vector<uint32_t> which(sub.size());
@@ -988,6 +1256,10 @@ int sketch_with_state(inshr_ctx *c, const inshr_config *cfg, const uint32_t *whi
 {
     // multi: centres for 2 .. 8 bits, their exact errors and the choice (cfg[k].bits must be 8 then:
     // it names the grid entry that carries the tensor's prune / protect fractions)
+    if (!c->batch.light) { // (protected counts per tile and sums of squares, as a search with scores leaves them)
+        int rr = resolve_all(c);
+        if (rr) return rr;
+    }
     const uint32_t nT = (uint32_t)c->batch.nT;
     std::vector<SketchDesc> sd(nT);
     for (auto &d : sd) d.active = d.cfg = 0u;
@@ -1154,7 +1426,7 @@ int inshr_quantize_sketch(inshr_ctx *c, const inshr_tensor *tensors, const inshr
             }
         }
         const uint32_t nS = (uint32_t)sub.size();
-        rc = run_search(c, sub.data(), nS, &cfg[t0], 1, 0.0, false, true);
+        rc = run_search(c, sub.data(), nS, &cfg[t0], 1, 0.0, LIGHT);
         if (rc) return rc;
         std::vector<inshr_quantized> subout(nS);
         std::vector<uint32_t> which(nS);
@@ -1238,7 +1510,7 @@ int inshr_search_sketch(inshr_ctx *c, const inshr_tensor *tensors, const inshr_c
             grid7[b] = wide[t0];
             grid7[b].bits = (uint8_t)(2 + b);
         }
-        rc = run_search(c, sub.data(), nS, grid7, SK_SETS, eps, false, true);
+        rc = run_search(c, sub.data(), nS, grid7, SK_SETS, eps, LIGHT);
         if (rc) return rc;
         std::vector<inshr_quantized> subout(nS);
         std::vector<uint32_t> which(nS);
@@ -1371,8 +1643,6 @@ int inshr_sketch_quantiles(inshr_ctx *c, const inshr_tensor *tensors, uint32_t n
         md[t].x = tensors[t].data;
         md[t].n = tensors[t].n;
         md[t].chunk0 = chunks;
-        md[t].aligned16 = (((uintptr_t)tensors[t].data & 15u) == 0) ? 1u : 0u;
-        md[t].pad = 0u;
         chunks += (tensors[t].n + SK_MAG_CHUNK - 1) / SK_MAG_CHUNK;
         for (uint32_t k = 0; k < n_q; k++) {
             if (!(q[k] >= 0.0 && q[k] <= 1.0)) return INSHR_E_ARG;
@@ -1517,7 +1787,7 @@ int inshr_quantize_sens(inshr_ctx *c, const inshr_tensor *tensors, const float *
     }
     auto thresholds = [&](uint32_t from, uint32_t to) -> int {
         const int rs = run_search(c, sub.data() + from, to - from, frac_grid.data(), (uint32_t)frac_grid.size(), 0.0,
-                                  false, true);
+                                  LIGHT);
         if (rs) return rs;
         const SearchResult *res = (const SearchResult *)c->h_down.p;
         for (uint32_t k = from; k < to; k++) {
@@ -1559,7 +1829,7 @@ int inshr_quantize_sens(inshr_ctx *c, const inshr_tensor *tensors, const float *
         sub[t].n = si[t].n_kept;
     }
     // the bins: the quantized values as tensors of their own, nothing pruned, nothing protected
-    rc = run_search(c, sub.data(), nT, bin_grid.data(), (uint32_t)bin_grid.size(), 0.0, true);
+    rc = run_search(c, sub.data(), nT, bin_grid.data(), (uint32_t)bin_grid.size(), 0.0, SCORES);
     if (rc) return rc;
     c->have_search = false; // (the state describes the compacted values, not the caller's tensors)
     const Score *hsc = (const Score *)((const char *)c->h_down.p + sizeof(SearchResult) * nT);
@@ -1633,24 +1903,26 @@ static u32 call_chunk_tiles(const inshr_ctx *c, const inshr_codes *prev, uint32_
     return ct;
 }
 
-// Symbol populations of the tensors of a call, where some tensor has enough chunks for them to be added up.
-static bool wants_totals(const std::vector<DDesc> &dd)
+// Room for the symbol populations of the tensors of a call: none where no tensor has enough chunks for them to
+// be added up.
+static size_t totals_bytes(const std::vector<DDesc> &dd)
 {
     for (const DDesc &d : dd)
-        if (d.n_chunks > DELTA_FEW) return true;
-    return false;
+        if (d.n_chunks > DELTA_FEW) return sizeof(u32) * DELTA_SS * dd.size();
+    return 0;
 }
-static u32 *call_totals(const inshr_ctx *c, const std::vector<DDesc> &dd)
+// That room, cleared: at offset o of aux_mem, or an allocation of its own where the caller limits the size of
+// one (a call that fitted the limit without them still does).
+static int clear_totals(inshr_ctx *c, size_t bytes, size_t o, u32 **totals)
 {
-    return wants_totals(dd) ? (u32 *)c->totals_mem.p : nullptr;
-}
-static int ensure_totals(inshr_ctx *c, const std::vector<DDesc> &dd)
-{
-    return wants_totals(dd) ? ensure_dev(c, c->totals_mem, sizeof(u32) * DELTA_SS * dd.size()) : INSHR_OK;
-}
-static int clear_totals(inshr_ctx *c, const std::vector<DDesc> &dd)
-{
-    if (wants_totals(dd)) HIPCHK(c, hipMemsetAsync(c->totals_mem.p, 0, sizeof(u32) * DELTA_SS * dd.size(), c->stream));
+    *totals = nullptr;
+    if (!bytes) return INSHR_OK;
+    if (c->scratch_limit) {
+        const int rc = ensure_dev(c, c->totals_mem, bytes);
+        if (rc) return rc;
+    }
+    *totals = (u32 *)(c->scratch_limit ? c->totals_mem.p : (char *)c->aux_mem.p + o);
+    HIPCHK(c, hipMemsetAsync(*totals, 0, bytes, c->stream));
     return INSHR_OK;
 }
 
@@ -1712,12 +1984,12 @@ int inshr_delta(inshr_ctx *c, const inshr_codes *prev, const uint32_t *const *pr
     const size_t o_dd = cv.take(sizeof(DDesc) * n_tensors);
     const size_t o_ct = cv.take(sizeof(u32) * chunk_tensor.size());
     const size_t up_bytes = cv.off;
+    const size_t tt_bytes = totals_bytes(dd), o_tt = cv.take(c->scratch_limit ? 0 : tt_bytes);
     const size_t o_ck = cv.take((size_t)chunk * DELTA_SS * 4);
     int rc = ensure_dev(c, c->aux_mem, cv.off);
     if (rc) return rc;
     rc = ensure_host(c, c->h_up, up_bytes);
     if (rc) return rc;
-    if ((rc = ensure_totals(c, dd))) return rc;
     // the staging buffer may still be in flight from an earlier asynchronous delta call
     HIPCHK(c, hipStreamSynchronize(c->stream));
     rc = take_delta_flags(c); // (of a call whose flags nobody has asked for yet)
@@ -1727,10 +1999,11 @@ int inshr_delta(inshr_ctx *c, const inshr_codes *prev, const uint32_t *const *pr
     memcpy(hb + o_ct, chunk_tensor.data(), sizeof(u32) * chunk_tensor.size());
     HIPCHK(c, hipMemcpyAsync(db, hb, up_bytes, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemsetAsync(c->delta_flags, 0, sizeof(u32), c->stream));
-    if ((rc = clear_totals(c, dd))) return rc;
+    u32 *totals;
+    if ((rc = clear_totals(c, tt_bytes, o_tt, &totals))) return rc;
     c->delta_pending = true;
     HIPCHK(c, launch_delta((const DDesc *)(db + o_dd), (int)n_tensors, dtile, chunk,
-                           (const u32 *)(db + o_ct), (u32 *)(db + o_ck), call_totals(c, dd), c->delta_flags, any_scatter,
+                           (const u32 *)(db + o_ct), (u32 *)(db + o_ck), totals, c->delta_flags, any_scatter,
                            any_perm, any_gather, c->lds_ordered, c->stream));
     return INSHR_OK;
 }
@@ -1921,6 +2194,7 @@ int inshr_reconstruct(inshr_ctx *c, const inshr_codes *prev, const inshr_delta_o
     const size_t o_fl = cv.take(sizeof(u32));
     const size_t up_bytes = cv.off;
     const size_t o_go = cv.take(sizeof(u64) * (DELTA_SS + 8) * n_tensors); // group offsets from prev
+    const size_t tt_bytes = totals_bytes(dd), o_tt = cv.take(c->scratch_limit ? 0 : tt_bytes);
     const size_t o_ck = cv.take((size_t)chunk * DELTA_SS * 4);
     int rc = ensure_dev(c, c->aux_mem, cv.off);
     if (rc) return rc;
@@ -1928,10 +2202,10 @@ int inshr_reconstruct(inshr_ctx *c, const inshr_codes *prev, const inshr_delta_o
     if (rc) return rc;
     rc = ensure_host(c, c->h_down, sizeof(u32));
     if (rc) return rc;
-    if ((rc = ensure_totals(c, dd))) return rc;
     HIPCHK(c, hipStreamSynchronize(c->stream));
     char *hb = (char *)c->h_up.p, *db = (char *)c->aux_mem.p;
-    if ((rc = clear_totals(c, dd))) return rc;
+    u32 *totals;
+    if ((rc = clear_totals(c, tt_bytes, o_tt, &totals))) return rc;
     for (uint32_t t = 0; t < n_tensors; t++) dd[t].group_off = (u64 *)(db + o_go) + (size_t)t * (DELTA_SS + 8);
     memset(hb, 0, up_bytes);
     memcpy(hb + o_dd, dd.data(), sizeof(DDesc) * n_tensors);
@@ -1941,7 +2215,7 @@ int inshr_reconstruct(inshr_ctx *c, const inshr_codes *prev, const inshr_delta_o
     u32 *flags = (u32 *)(db + o_fl);
     HIPCHK(c, launch_reconstruct((const DDesc *)(db + o_dd), (const XDesc *)(db + o_xd),
                                  (int)n_tensors, chunk, (const u32 *)(db + o_ct),
-                                 (u32 *)(db + o_ck), call_totals(c, dd), flags, c->lds_ordered, c->stream));
+                                 (u32 *)(db + o_ck), totals, flags, c->lds_ordered, c->stream));
     HIPCHK(c, hipMemcpyAsync(c->h_down.p, flags, sizeof(u32), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     const u32 f = *(const u32 *)c->h_down.p;

@@ -547,7 +547,7 @@ __global__ __launch_bounds__(DBLOCK, 6) void k_dscatter(const DDesc *__restrict_
 
     auto tile_cnt = [&](u64 lt) -> u32 {
         const u64 rem = d.n - lt * (u64)DTILE;
-        return rem < (u64)DTILE ? (u32)rem : (u32)DTILE;
+        return tile_len(rem, (u32)DTILE);
     };
     lds_fetch<NWAVE>(gptr(d.prev), lt0 * (u64)DTILE, tile_cnt(lt0), wp, Pw, wave);
     lds_fetch<NWAVE>(gptr(d.cur), lt0 * (u64)DTILE, tile_cnt(lt0), wc, Cw, wave);
@@ -733,7 +733,7 @@ __global__ __launch_bounds__(BLOCK) void k_dgather(const DDesc *__restrict__ dd,
     const u64 c0 = (chunk - d.chunk0) * c_elems;
     const u64 c1 = (c0 + c_elems < d.n) ? c0 + c_elems : d.n;
     for (u64 r0 = c0; r0 < c1; r0 += HTILE) {
-        const u32 cnt = (c1 - r0 < (u64)HTILE) ? (u32)(c1 - r0) : (u32)HTILE;
+        const u32 cnt = tile_len(c1 - r0, (u32)HTILE);
         __syncthreads();
         for (u32 k = tid; k < 256u * wB; k += BLOCK) pk[k] = 0ull;
         __syncthreads();
@@ -828,7 +828,7 @@ __global__ __launch_bounds__(DBLOCK, 6) void k_drestore(const DDesc *__restrict_
     u32 e_max = 0u, s_max = 0u, order_bad = 0u; // largest delta, largest symbol
     auto tile_cnt = [&](u64 lt) -> u32 {
         const u64 rem = d.n - lt * (u64)DTILE;
-        return rem < (u64)DTILE ? (u32)rem : (u32)DTILE;
+        return tile_len(rem, (u32)DTILE);
     };
     lds_fetch<NWAVE>(gptr(d.prev), lt0 * (u64)DTILE, tile_cnt(lt0), wp, Pw, wave);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");

@@ -186,7 +186,6 @@ struct TDesc {           // one tensor of a batch
     u64 pool_grp;        // where this tensor's keys in bin-group order go in the first pool (u32 units):
                          // the span of the tensor's (workgroup, tensor) units there, ...
     u64 pool_len;        // ... and its length
-    u32 aligned16;       // data pointer is 16-byte aligned (float4 loads allowed)
     u32 sampled;         // sweep 1 reads one tile in SAMPLE_RATE (large tensors): its histogram only
                          // shapes the second-level table and predicts where the thresholds lie
     // thresholds per layer type (Sec. 4.2): the tensors of a group share the thresholds, which are
@@ -270,10 +269,11 @@ struct TState {
     double sumsq;                      // sum of x^2
     double thr_sumsq[MAX_THR];         // prune: sum x^2 over mag < tau; protect: over mag > tau
     u32 best, feasible;
+    u32 fuse_bad;                      // the fused quantizer's means do not hold this tensor and configuration
 };
 
 struct SearchResult {    // what the host reads of a tensor's state
-    u32 nonfinite, internal_err, pool_overflow, redo, best, feasible;
+    u32 nonfinite, internal_err, pool_overflow, redo, best, feasible, fuse_bad;
     u32 thr_mag[MAX_THR];
 };
 // by the last kernel that works on the tensor, after a barrier behind its own changes of the state
@@ -288,6 +288,7 @@ __device__ __forceinline__ void store_result(TState *st, SearchResult *res)
     r.redo = rd(&st->redo);
     r.best = st->best;
     r.feasible = st->feasible;
+    r.fuse_bad = rd(&st->fuse_bad);
     for (int i = 0; i < MAX_THR; i++) r.thr_mag[i] = st->thr_mag[i];
     *res = r;
 }

@@ -9,6 +9,17 @@ constexpr int SQ_STRIDE = MAX_FRAC + 1;     // partial sums of squares per (work
 constexpr int SEL_WORDS = MAX_THR * 1024;    // a tensor's selection histograms ([slot][sign][512])
 constexpr int CB_STRIDE = 256;              // codebook entries per configuration
 
+struct Unit {       // the tiles of one tensor that one workgroup of a sweep walks
+    u64 off;          // the unit's share of the sweep's gather pool (u32 units): wave w owns
+    u32 capw;         // [off + w * capw, off + (w + 1) * capw)
+    u32 tile0, tile1; // batch-wide tile numbers
+    u32 tensor;
+};
+
+// Which configurations of the grid the boundaries, centres and errors of a tensor are worked out for
+// (`View` below): none, all, or one of them (its index).
+constexpr u32 VIEW_NONE = 0xFFFFFFFFu, VIEW_ALL = 0xFFFFFFFEu;
+
 struct Bufs { // device pointers, indexed by the tensor's position on the device unless noted; nB rows
               // (tensors searched by the sweeps) except ts, table2, tgt_key, codebook, scores (all)
     TState *ts;
@@ -17,9 +28,9 @@ struct Bufs { // device pointers, indexed by the tensor's position on the device
     u32 *pool_h1;   // [nT][32768] row of a group's leader: the first-level histograms of the group, added up
     u32 *pool_sel;  // [nT][2][SEL_WORDS] row of a group's leader: the group's selection histograms, per pass
     u32 *table2;    // [nT][4096]
-    const u64 *unit_off; // [units] start of each (workgroup, tensor) unit's share of a gather pool (u32 units)
-    const u32 *unit_capw; // [units] one wave's share of it: wave w of the unit owns
-                         // [unit_off + w * capw, unit_off + (w + 1) * capw)
+    const Unit *units;   // [units] of sweeps 1 and 2 (and of the pool they gather into)
+    const Unit *gunits;  // [gather units] of sweep 3
+    const u32 *view;     // [nB] VIEW_NONE, VIEW_ALL or a configuration
     u32 *unit_thr;   // [units][16] threshold-bucket keys each wave of the unit gathered
     u32 *hist2;     // [nT][32768]
     u32 *binfo;     // [nT][32768] offset of an active bin's elements in the gather pool, or INACTIVE
@@ -29,7 +40,8 @@ struct Bufs { // device pointers, indexed by the tensor's position on the device
     u32 *pool;      // first gather pool: the keys of the threshold windows (sweep 2), wave-private shares;
                     // afterwards every tensor's keys of active bins in bin-group order (TDesc::pool_grp)
     u32 *pool2;     // second gather pool, same layout: the keys of active bins as sweep 3 gathers them
-    u32 *unit_cand; // [units][16] active-bin keys each wave of the unit gathered
+    u32 *unit_cand; // [gather units][16] active-bin keys each wave of the unit gathered
+    u32 *unit_prot; // [gather units][16] protected values each wave listed (fused; in hist1, read no more)
     u16 *bin_group; // [nT][32768] group of each active bin
     u32 *grp_off;   // [nT][MAX_GROUPS] first / one-past-last position of each group in bin order
     u32 *grp_end;
@@ -39,6 +51,7 @@ struct Bufs { // device pointers, indexed by the tensor's position on the device
     u32 *tgt_khi;
     u32 *tile_out;  // [tiles][MAX_FRAC] protected values per tile and protect fraction
     double *sq_part; // [units][SQ_STRIDE]
+    double *sq_prot; // [gather units][MAX_FRAC] squares of the protected values (in hist1, read no more)
     // scoring: all boundaries and class edges of all pairs in one list ordered by key ("edges");
     // slot s holds the keys with exactly s edges at or below them
     u32 *edges;     // [nT][MAX_EDGES] edge keys in that order
@@ -65,9 +78,9 @@ struct Batch {
     const GridDesc *gd;  // device
     const u64 *wg_tile0; // device [n_wg + 1]
     const u32 *wg_fu0;   // device [n_wg] first (workgroup, tensor) unit of each workgroup
-    const u32 *t_fu_off; // device [nT + 1] CSR of the units that touch each tensor ...
-    const u32 *t_fu_ids; // device         ... in ascending workgroup order
-    const u32 *fu_tensor; // device [units] tensor of each unit
+    const u32 *t_fu_off; // device [nT + 1] first unit of each tensor (in ascending workgroup order)
+    const u32 *wg_gu0;   // device [n_gwg + 1] gather units of each workgroup of sweep 3
+    const u32 *t_gu_off; // device [nB + 1] gather units of each tensor
     u32 *grp_list;       // device [nT * MAX_GROUPS] (tensor << 13 | group) of every group
     u32 *n_grp_total;    // device
     const u64 *wg_tile0_all; // device [n_wg_all + 1] partition of the tiles of all tensors (quantizing)
@@ -76,6 +89,7 @@ struct Batch {
     int nS1, nS0;        // small tensors behind them: up to SMALL_MAX, up to SMALL_TINY values
     int n_wg, n_wg_all;
     int n_units;
+    int n_gwg, n_gunits; // workgroups and units of sweep 3
     int n_bucket_blocks;
     bool lds_ordered;    // same-address LDS atomics return in lane order on this device
     bool light;          // thresholds and class counts only: no boundaries, no scores (the sketch
@@ -100,6 +114,8 @@ struct QDesc { // one tensor of a quantize call (indexed like the batch)
     const u32 *alt_key; // NULL, or 256 boundary keys that replace the search's (boundary j of K at
                         // (j << (8 - bits)) - 1) ...
     const float *alt_cb; // ... and the K centres that go with them
+    u64 span, span_len;  // fused: the tensor's span of either gather pool (u32 units)
+    u32 fused, pad;      // boundaries and centres are worked out while quantizing (launch_fused)
 };
 struct QInfo {
     u64 n_pruned, n_outlier, n_kept;
@@ -199,11 +215,19 @@ void prof_end(hipStream_t s);
         prof_end(s);                                                                              \
     } while (0)
 
-hipError_t launch_select(const Batch &bt, hipStream_t s);
-hipError_t launch_edges(const Batch &bt, hipStream_t s); // edge order, bins without edges (inside launch_select)
-hipError_t launch_score(const Batch &bt, hipStream_t s);
+hipError_t launch_select(const Batch &bt, hipStream_t s); // thresholds: sweeps 1 and 2 and what follows from them
+hipError_t launch_counts(const Batch &bt, hipStream_t s); // class counts of every pair: ends a search without a choice
+hipError_t launch_decide(const Batch &bt, hipStream_t s); // the choice, where bounds of the errors settle it
+// boundaries, centres and errors of the configurations in view (sweep 3 and what follows from it)
+hipError_t launch_resolve(const Batch &bt, hipStream_t s);
+hipError_t launch_edges(const Batch &bt, hipStream_t s); // edge order, bins without edges (inside launch_resolve)
+hipError_t launch_score(const Batch &bt, hipStream_t s); // centres, errors, choice (inside launch_resolve)
 hipError_t launch_small(const Batch &bt, hipStream_t s); // the whole search of the small tensors
-hipError_t launch_quantize(const Batch &bt, const QDesc *qd, QInfo *qi, hipStream_t s);
+// the tensors of the units (and the small ones), whose boundaries and centres the state holds
+hipError_t launch_quantize(const Batch &bt, const QDesc *qd, const Unit *units, const u32 *wg_u0, int n_wg, QInfo *qi,
+                           hipStream_t s);
+// the tensors marked in their descriptors, which the batch's gather units cover
+hipError_t launch_fused(const Batch &bt, const QDesc *qd, QInfo *qi, hipStream_t s);
 hipError_t launch_delta(const DDesc *dd, int nT, u64 n_dtiles, u64 n_chunks,
                         const u32 *chunk_tensor, u32 *chunk_tot, u32 *totals, u32 *flags, bool any_scatter,
                         bool any_perm, bool any_gather, bool lds_ordered, hipStream_t s);
@@ -224,6 +248,63 @@ hipError_t launch_reconstruct(const DDesc *dd, const XDesc *xd, int nT, u64 n_ch
                               hipStream_t s);
 
 // ------------------------------------------------------------------------------------------
+// the pairs and boundaries in view
+// ------------------------------------------------------------------------------------------
+struct View {
+    u32 q0, n_pairs; // pairs q0 .. q0 + n_pairs - 1
+    u32 n_bnd;       // boundaries per pair
+    u32 K;           // bins of the one configuration, or 0: all of the grid's
+    u32 cfg;         // the one configuration
+};
+__device__ __forceinline__ View view_of(const GridDesc *gd, u32 view)
+{
+    View v;
+    if (view == VIEW_ALL) {
+        v.q0 = 0u;
+        v.n_pairs = gd->n_pairs;
+        v.n_bnd = gd->n_bnd;
+        v.K = 0u;
+        v.cfg = 0u;
+    } else {
+        v.q0 = gd->cfg_pair[view];
+        v.n_pairs = 1u;
+        v.K = gd->cfg_K[view];
+        v.n_bnd = v.K - 1u;
+        v.cfg = view;
+    }
+    return v;
+}
+// the i-th boundary of a pair in view
+__device__ __forceinline__ u32 view_bnd(const GridDesc *gd, const View &v, u32 i)
+{
+    return v.K ? bnd_index(v.K, i + 1u) : (u32)gd->bnd[i];
+}
+
+// Class counts of every (prune, protect) pair from the exact thresholds, by the first n_pairs threads.
+__device__ __forceinline__ void store_pairs(TState *st, const GridDesc *gd, u64 n)
+{
+    const u32 tid = threadIdx.x;
+    if (tid >= gd->n_pairs) return;
+    const u32 tp = gd->pair_p[tid], to = gd->n_p + gd->pair_o[tid];
+    const u64 n_neg = st->n_neg, n_pos = n - n_neg;
+    const u64 Pn = st->thr_lt_neg[tp], Pp = st->thr_lt_pos[tp];
+    const u64 An = st->thr_gt_neg[to], Ap = st->thr_gt_pos[to];
+    const u64 Mn = n_neg - An - Pn, Mp = n_pos - Ap - Pp;
+    st->pair_An[tid] = An;
+    st->pair_Ap[tid] = Ap;
+    st->pair_Pn[tid] = Pn;
+    st->pair_Pp[tid] = Pp;
+    st->pair_Mn[tid] = Mn;
+    st->pair_M[tid] = Mn + Mp;
+    if (Mn + Mp == 0ull || Mn > n || Mp > n) {
+        // (shared thresholds can leave a tensor without quantized values: reported, and the
+        // tensor's gathered keys are not processed)
+        atomicOr(&st->internal_err, 32u);
+        atomicOr(&st->pool_overflow, 8u);
+    }
+}
+
+// ------------------------------------------------------------------------------------------
 // tile iteration shared by the streaming kernels
 // ------------------------------------------------------------------------------------------
 __device__ __forceinline__ int find_tensor(const TDesc *td, int nT, u64 tile)
@@ -239,24 +320,42 @@ __device__ __forceinline__ int find_tensor(const TDesc *td, int nT, u64 tile)
     return lo;
 }
 
+// Elements of a tile of `full` when rem (below 2^32, as every tensor is) are left from its first on.  In 32
+// bits: where the compiler knew a tile to be whole from the 64-bit comparison that also chose its length, it
+// has taken the length from a condition code that address arithmetic had overwritten since.
+__device__ __forceinline__ u32 tile_len(u64 rem, u32 full)
+{
+    const u32 r = (u32)rem;
+    return r < full ? r : full;
+}
+
+// four values at a 4-byte aligned address, which is what a 16-byte global load asks for
+typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
+
+// A whole tile, asked for without any branch: the values may stay in flight until their first use (a tile
+// fetched ahead).
+__device__ __forceinline__ void load_tile_ahead(const TDesc &d, u64 e0, float (&v)[16])
+{
+    const GLOBAL_AS f4_any *p4 = (const GLOBAL_AS f4_any *)(gptr(d.data) + e0);
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        const f4_any q = p4[threadIdx.x + 1024u * j];
+        v[4 * j + 0] = q.x;
+        v[4 * j + 1] = q.y;
+        v[4 * j + 2] = q.z;
+        v[4 * j + 3] = q.w;
+    }
+}
+
 // v[4*j + c] = element 4*(tid + 1024*j) + c of the tile; returns the mask of valid entries
 __device__ __forceinline__ u32 load_tile(const TDesc &d, u64 e0, u32 cnt, float (&v)[16])
 {
-    const GLOBAL_AS float *p = gptr(d.data) + e0;
-    const u32 tid = threadIdx.x;
-    if (cnt == (u32)TILE && d.aligned16) {
-        typedef float f4 __attribute__((ext_vector_type(4)));
-        const GLOBAL_AS f4 *p4 = (const GLOBAL_AS f4 *)p;
-#pragma unroll
-        for (int j = 0; j < 4; j++) {
-            const f4 q = p4[tid + 1024u * j];
-            v[4 * j + 0] = q.x;
-            v[4 * j + 1] = q.y;
-            v[4 * j + 2] = q.z;
-            v[4 * j + 3] = q.w;
-        }
+    if (cnt == (u32)TILE) {
+        load_tile_ahead(d, e0, v);
         return 0xFFFFu;
     }
+    const GLOBAL_AS float *p = gptr(d.data) + e0;
+    const u32 tid = threadIdx.x;
     u32 mask = 0u;
 #pragma unroll
     for (int j = 0; j < 4; j++) {
@@ -272,22 +371,6 @@ __device__ __forceinline__ u32 load_tile(const TDesc &d, u64 e0, u32 cnt, float 
         }
     }
     return mask;
-}
-
-// A whole tile at a 16-byte aligned address, asked for without any branch: the values may stay in
-// flight until their first use (a tile fetched ahead).
-__device__ __forceinline__ void load_tile_ahead(const TDesc &d, u64 e0, float (&v)[16])
-{
-    typedef float f4 __attribute__((ext_vector_type(4)));
-    const GLOBAL_AS f4 *p4 = (const GLOBAL_AS f4 *)(gptr(d.data) + e0);
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-        const f4 q = p4[threadIdx.x + 1024u * j];
-        v[4 * j + 0] = q.x;
-        v[4 * j + 1] = q.y;
-        v[4 * j + 2] = q.z;
-        v[4 * j + 3] = q.w;
-    }
 }
 
 } // namespace inshr

@@ -5,25 +5,12 @@
 // classifies, searches the boundary list, packs and gathers the protected values.  The position
 // of a tile's protected values in the output list is the prefix sum of the per-tile counts that
 // the gathering sweep of the search recorded.
-#include "inshr_launch.h"
+//
+// (This sweep is for tensors whose boundaries and centres the state holds; where it holds thresholds only, the
+// sweep of launch_fused works them out and quantizes in one.)
+#include "inshr_quant.h"
 
 namespace inshr {
-
-// The symbol is a step function of the key: the 255 bin boundaries and the four class edges
-// (first quantized negative key, first pruned key, first quantized positive key, first protected
-// positive key) cut the key axis into at most 260 slots, each with one symbol.  The search's
-// equal-population bins (32768 of them) are far finer than the slots, so a table gives the symbol
-// of every bin that holds no breakpoint; in the few bins that do, the key is compared with the
-// breakpoints from the bin's first one on.
-constexpr int QBP = 264;          // breakpoints, padded
-constexpr int PKW = 256 * 9;      // most packed words of a tile
-
-struct QuantTables {
-    u32 bp[QBP + 8];   // sorted breakpoints, then 0xFFFFFFFF
-    u32 raw[QBP];      // boundaries of the configuration, then the class edges
-    u16 symtab[QBP];   // symbol of slot s = #{breakpoints <= key}
-    u32 wcnt[2][64];   // protected values per (quarter j, wave) of the tile, per buffer
-};
 
 struct QuantShared {
     u32 T[COARSE];                     // key prefix -> bins
@@ -31,66 +18,6 @@ struct QuantShared {
     unsigned long long pk[2 * PKW];    // two bit buffers of packed symbols
     QuantTables qt;
 };
-
-// cj (0 .. 4) summed over the lower lanes of the wave in `below`; returns the wave's total.
-__device__ __forceinline__ u32 rank_counts(u32 cj, u32 &below)
-{
-    const u64 m0 = __ballot(cj & 1u), m1 = __ballot(cj & 2u), m2 = __ballot(cj & 4u);
-    below = __builtin_amdgcn_mbcnt_hi((u32)(m0 >> 32), __builtin_amdgcn_mbcnt_lo((u32)m0, 0u)) +
-            2u * __builtin_amdgcn_mbcnt_hi((u32)(m1 >> 32), __builtin_amdgcn_mbcnt_lo((u32)m1, 0u)) +
-            4u * __builtin_amdgcn_mbcnt_hi((u32)(m2 >> 32), __builtin_amdgcn_mbcnt_lo((u32)m2, 0u));
-    return (u32)__popcll(m0) + 2u * (u32)__popcll(m1) + 4u * (u32)__popcll(m2);
-}
-
-// Breakpoints in key order and the symbol of every slot, by a workgroup of at least QBP + 8 threads.
-// tk: the pair's boundary keys (they ascend); at equal keys a boundary goes before a class edge.
-__device__ __forceinline__ void make_breakpoints(QuantTables &qt, const u32 *tk, u32 K, u32 tau_p, u32 tau_o)
-{
-    const u32 tid = threadIdx.x, n_bnd = K - 1u, n_bp = n_bnd + 4u;
-    if (tid < n_bnd) qt.raw[tid] = tk[bnd_index(K, tid + 1u)];
-    if (tid < 4u) qt.raw[n_bnd + tid] = class_edge_key(tid, tau_p, tau_o);
-    __syncthreads();
-    auto boundaries_upto = [&](u32 key) -> u32 {
-        u32 lo = 0u, hi = n_bnd;
-        while (lo < hi) {
-            const u32 mid = (lo + hi) >> 1;
-            if (qt.raw[mid] <= key)
-                lo = mid + 1u;
-            else
-                hi = mid;
-        }
-        return lo;
-    };
-    if (tid < n_bp) {
-        const u32 x = qt.raw[tid];
-        u32 r = tid < n_bnd ? tid : boundaries_upto(x);
-#pragma unroll
-        for (u32 e = 0; e < 4u; e++) {
-            const u32 y = qt.raw[n_bnd + e];
-            r += (y < x || (y == x && tid >= n_bnd && n_bnd + e < tid)) ? 1u : 0u;
-        }
-        qt.bp[r] = x;
-    } else if (tid < (u32)QBP + 8u) {
-        qt.bp[tid] = 0xFFFFFFFFu;
-    }
-    __syncthreads();
-    if (tid <= n_bp) { // symbol of each slot, from its smallest key
-        const u32 rep = tid ? qt.bp[tid - 1u] : 0u;
-        const u32 m = mag_of_key(rep);
-        qt.symtab[tid] = (u16)(m < tau_p ? 0u : m > tau_o ? 1u : 2u + boundaries_upto(rep));
-    }
-    __syncthreads();
-}
-
-// Breakpoints at or below the key, by bisection.
-__device__ __forceinline__ u32 slot_of_key(const u32 *bp, u32 n_bp, u32 key)
-{
-    u32 s = 0u;
-#pragma unroll
-    for (u32 step = 256u; step > 0u; step >>= 1)
-        if (s + step <= n_bp && bp[s + step - 1u] <= key) s += step;
-    return s;
-}
 
 // How the symbol of a key is found.  BINS: the search's equal-population bins; building the table
 // of 32768 bins costs a workgroup about 40 us, so it is for long runs of tiles.  CELLS: cells of the
@@ -169,42 +96,6 @@ __device__ __forceinline__ void classify_tile(const float (&v)[16], u32 mask, co
     }
 }
 
-__device__ __forceinline__ void store_protected(const QDesc &q, u64 pos, u32 index, float x)
-{
-    if (pos >= q.out_cap) return;
-    gptr(q.out_idx)[pos] = index;
-    if (q.val_bf16) { // upper 16 bits, rounded to nearest even
-        const u32 b = __float_as_uint(x);
-        ((GLOBAL_AS u16 *)gptr(q.out_val))[pos] = (u16)((b + 0x7FFFu + ((b >> 16) & 1u)) >> 16);
-    } else {
-        gptr(q.out_val)[pos] = x;
-    }
-}
-
-// What a quantized tensor's descriptor, boundaries and codebook are, by the whole workgroup.
-__device__ __forceinline__ void store_head(const QDesc &q, const TState *st, const GridDesc *gd, const u32 *tk,
-                                           const float *cb, u32 found, QInfo *qi)
-{
-    const u32 g = q.cfg, pair = gd->cfg_pair[g], K = gd->cfg_K[g], o = gd->pair_o[pair];
-    const u32 tid = threadIdx.x;
-    if (q.boundaries)
-        for (u32 j = 1 + tid; j < K; j += blockDim.x)
-            gptr(q.boundaries)[j - 1] = __uint_as_float(bits_of_key(tk[bnd_index(K, j)]));
-    for (u32 k = tid; k < K; k += blockDim.x) gptr(q.codebook)[k] = cb[k];
-    if (tid == 0) {
-        QInfo r;
-        r.n_pruned = st->pair_Pn[pair] + st->pair_Pp[pair];
-        r.n_outlier = st->pair_An[pair] + st->pair_Ap[pair];
-        r.n_kept = st->pair_M[pair];
-        r.tau_p = st->thr_mag[gd->pair_p[pair]];
-        r.tau_o = st->thr_mag[gd->n_p + o];
-        r.flags = 0u;
-        if ((u64)found != r.n_outlier) r.flags |= 1u;  // self-check
-        if (r.n_outlier > q.out_cap) r.flags |= 2u;    // caller buffer too small
-        *qi = r;
-    }
-}
-
 // per tensor: prefix of protected counts over its tiles, meta data, codebook / boundary copy
 __global__ __launch_bounds__(BLOCK) void k_qprep(const TDesc *__restrict__ td,
                                                  const GridDesc *__restrict__ gd,
@@ -215,7 +106,7 @@ __global__ __launch_bounds__(BLOCK) void k_qprep(const TDesc *__restrict__ td,
     __shared__ u32 tmp[BLOCK / 64 + 1];
     const int i = blockIdx.x;
     const QDesc q = qd[i];
-    if (q.packed == nullptr) return;
+    if (q.packed == nullptr || q.fused) return;
     const int t = i;
     const u32 tid = threadIdx.x;
     const TDesc d = td[t];
@@ -324,8 +215,8 @@ __global__ __launch_bounds__(QS_NT) void k_qsmall(const TDesc *__restrict__ td, 
     store_head(q, st, gd, tk, cb, found, qi + t);
 }
 
-__global__ __launch_bounds__(BLOCK) void k_quant(const TDesc *__restrict__ td, int nT,
-                                                 const u64 *__restrict__ wg_tile0,
+__global__ __launch_bounds__(BLOCK) void k_quant(const TDesc *__restrict__ td, const Unit *__restrict__ units,
+                                                 const u32 *__restrict__ wg_u0,
                                                  const GridDesc *__restrict__ gd,
                                                  const QDesc *__restrict__ qd_by_tensor, Bufs B)
 {
@@ -338,23 +229,15 @@ __global__ __launch_bounds__(BLOCK) void k_quant(const TDesc *__restrict__ td, i
     QuantTables &qt = qs.qt;
 
     const u32 tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const u64 tile_lo = wg_tile0[blockIdx.x], tile_hi = wg_tile0[blockIdx.x + 1];
-    if (tile_lo >= tile_hi) return;
     for (u32 k = tid; k < 2u * PKW; k += BLOCK) pk0[k] = 0ull;
-    int t = find_tensor(td, nT, tile_lo);
-    u64 tile = tile_lo;
     u32 buf = 0u;
-    while (tile < tile_hi) {
+    for (u32 u = wg_u0[blockIdx.x]; u < wg_u0[blockIdx.x + 1]; u++) {
+        const Unit un = units[u];
+        const int t = (int)un.tensor;
+        u64 tile = un.tile0;
+        const u64 stop = un.tile1;
         const TDesc d = td[t];
-        const u64 n_tiles_t = (d.n + TILE - 1) / TILE;
-        const u64 t_end = d.tile0 + n_tiles_t;
-        const u64 stop = t_end < tile_hi ? t_end : tile_hi;
         const QDesc q = qd_by_tensor[t];
-        if (q.packed == nullptr) { // tensor not part of this call
-            tile = stop;
-            t++;
-            continue;
-        }
         const TState *st = B.ts + t;
         const u32 g = q.cfg, pair = gd->cfg_pair[g], K = gd->cfg_K[g];
         const u32 w = symbol_bits(K);
@@ -403,7 +286,7 @@ __global__ __launch_bounds__(BLOCK) void k_quant(const TDesc *__restrict__ td, i
         GLOBAL_AS unsigned long long *packed = gptr(q.packed);
         auto tile_cnt = [&](u64 tl) -> u32 {
             const u64 rem = d.n - (tl - d.tile0) * (u64)TILE;
-            return rem < (u64)TILE ? (u32)rem : (u32)TILE;
+            return tile_len(rem, (u32)TILE);
         };
         // Software pipeline of one tile: (1) the tile's values, asked for during the tile before,
         // arrive; (2) the words and protected values of the tile before leave (their stores drain
@@ -478,8 +361,8 @@ __global__ __launch_bounds__(BLOCK) void k_quant(const TDesc *__restrict__ td, i
             // offset of this tile's protected values in the list (needed one tile later)
             const u32 obase = __builtin_amdgcn_readfirstlane(B.tile_off[tile]);
             if (have_prev) write_out(tile - 1, buf ^ 1u);
-            // a whole, aligned next tile is asked for now and used one iteration later
-            ahead = tile + 1 < stop && d.aligned16 && tile_cnt(tile + 1) == (u32)TILE;
+            // a whole next tile is asked for now and used one iteration later
+            ahead = tile + 1 < stop && tile_cnt(tile + 1) == (u32)TILE;
             if (ahead) load_tile_ahead(d, e0 + TILE, vn);
             u32 omask, pre[4];
             unsigned long long *pkb = pk0 + buf * PKW;
@@ -506,11 +389,11 @@ __global__ __launch_bounds__(BLOCK) void k_quant(const TDesc *__restrict__ td, i
             buf ^= 1u;
         }
         if (have_prev) write_out(stop - 1, buf ^ 1u);
-        t++;
     }
 }
 
-hipError_t launch_quantize(const Batch &bt, const QDesc *qd, QInfo *qi, hipStream_t s)
+hipError_t launch_quantize(const Batch &bt, const QDesc *qd, const Unit *units, const u32 *wg_u0, int n_wg, QInfo *qi,
+                           hipStream_t s)
 {
     static bool attr = false;
     if (!attr) {
@@ -519,9 +402,9 @@ hipError_t launch_quantize(const Batch &bt, const QDesc *qd, QInfo *qi, hipStrea
         if (e) return e;
         attr = true;
     }
-    if (bt.nB) {
+    if (n_wg) {
         PROF("k_qprep", s, k_qprep<<<bt.nB, BLOCK, (L2_BINS + 4) * 4, s>>>(bt.td, bt.gd, qd, qi, bt.bufs));
-        PROF("k_quant", s, k_quant<<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nB, bt.wg_tile0, bt.gd, qd, bt.bufs));
+        PROF("k_quant", s, k_quant<<<n_wg, BLOCK, 0, s>>>(bt.td, units, wg_u0, bt.gd, qd, bt.bufs));
     }
     if (bt.nT > bt.nB)
         PROF("k_qsmall", s, k_qsmall<<<bt.nT - bt.nB, QS_NT, 0, s>>>(bt.td, bt.gd, qd, qi, bt.bufs, bt.nB));

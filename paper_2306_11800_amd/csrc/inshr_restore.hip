@@ -52,7 +52,7 @@ __global__ __launch_bounds__(DQ_BLOCK) void k_dequant(const RDesc *__restrict__ 
     auto fetch = [&](int tt, u64 tile) {
         const RDesc d = rd[tt];
         const u64 e0 = (tile - d.tile0) * DQ_TILE;
-        const u32 cnt = (d.n - e0 < (u64)DQ_TILE) ? (u32)(d.n - e0) : (u32)DQ_TILE;
+        const u32 cnt = tile_len(d.n - e0, (u32)DQ_TILE);
         const u32 nd = 2u * ((cnt * d.w + 63u) >> 6); // dwords of the tile, all inside the packed array
         const GLOBAL_AS u32 *src = (const GLOBAL_AS u32 *)(gptr(d.packed) + e0 * d.w / 64u);
 #pragma unroll
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(DQ_BLOCK) void k_dequant(const RDesc *__restrict__ 
     for (u64 tile = tile_lo; tile < tile_hi; tile++) {
         const RDesc d = rd[t];
         const u64 e0 = (tile - d.tile0) * DQ_TILE;
-        const u32 cnt = (d.n - e0 < (u64)DQ_TILE) ? (u32)(d.n - e0) : (u32)DQ_TILE;
+        const u32 cnt = tile_len(d.n - e0, (u32)DQ_TILE);
         const u32 w = d.w, K = d.K;
         __syncthreads(); // the previous tile has been decoded
 #pragma unroll

@@ -46,12 +46,14 @@ __global__ __launch_bounds__(BLOCK) void k_edges(const TDesc *__restrict__ td,
     const int t = blockIdx.x;
     const u32 tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     TState *st = B.ts + t;
+    if (B.view[t] == VIEW_NONE) return;
+    const View vw = view_of(gd, B.view[t]);
     const u64 n = td[t].n, n_neg = st->n_neg;
-    const u32 n_pairs = gd->n_pairs, n_p = gd->n_p;
+    const u32 n_p = gd->n_p;
     // edge items: pair q has the boundaries q * EPP + (index) and the class edges q * EPP + NBT ..
-    // NBT + 3; the list holds n_e = n_pairs * (n_bnd + 4) of them
-    const u32 n_bnd = gd->n_bnd, n_c = 4u * n_pairs;
-    const u32 n_e = n_pairs * n_bnd + n_c;
+    // NBT + 3; the list holds n_e = (pairs in view) * (n_bnd + 4) of them
+    const u32 n_bnd = vw.n_bnd, n_c = 4u * vw.n_pairs;
+    const u32 n_e = vw.n_pairs * n_bnd + n_c;
     const u32 nb2 = st->nb2, zbin = st->zbin;
     const u32 G = st->pool_overflow ? 0u : st->n_groups; // (overflow: nothing valid to sort)
     const u32 *tb = B.tgt_bin + (size_t)t * TGT_STRIDE;
@@ -65,8 +67,8 @@ __global__ __launch_bounds__(BLOCK) void k_edges(const TDesc *__restrict__ td,
     u32 *sub_code = B.sub_code + (size_t)t * MAX_SUB;
 
     if (tid < n_c)
-        ckey[tid] = class_edge_key(tid & 3u, st->thr_mag[gd->pair_p[tid >> 2]],
-                                   st->thr_mag[n_p + gd->pair_o[tid >> 2]]);
+        ckey[tid] = class_edge_key(tid & 3u, st->thr_mag[gd->pair_p[vw.q0 + (tid >> 2)]],
+                                   st->thr_mag[n_p + gd->pair_o[vw.q0 + (tid >> 2)]]);
     if (tid == 0u) {
         s_err = 0u;
         if (G) s_at = atomicAdd(n_grp_total, G);
@@ -88,7 +90,7 @@ __global__ __launch_bounds__(BLOCK) void k_edges(const TDesc *__restrict__ td,
     // still lie in different bins), then the boundaries; a stable sort by the number of keys below
     // keeps a class edge before a boundary of equal rank.
     if (tid < n_c) {
-        const u32 q = tid >> 2, key = ckey[tid];
+        const u32 q = vw.q0 + (tid >> 2), key = ckey[tid];
         u32 order = 0u;
         for (u32 j = 0; j < n_c; j++) order += (ckey[j] < key || (ckey[j] == key && j < tid)) ? 1u : 0u;
         u64 below;
@@ -101,8 +103,8 @@ __global__ __launch_bounds__(BLOCK) void k_edges(const TDesc *__restrict__ td,
         sh.below[order] = (u32)below;
         sh.item[order] = (u16)(q * EPP + (u32)NBT + (tid & 3u));
     }
-    for (u32 w = tid; w < n_pairs * n_bnd; w += BLOCK) {
-        const u32 q = w / n_bnd, e = gd->bnd[w % n_bnd];
+    for (u32 w = tid; w < vw.n_pairs * n_bnd; w += BLOCK) {
+        const u32 q = vw.q0 + w / n_bnd, e = view_bnd(gd, vw, w % n_bnd);
         sh.below[n_c + w] = trank[q * NBT + e];
         sh.item[n_c + w] = (u16)(q * EPP + e);
     }
@@ -182,7 +184,7 @@ __global__ __launch_bounds__(BLOCK) void k_edges(const TDesc *__restrict__ td,
                 key = ZERO_KEY;
             }
         } else {
-            key = ckey[q * 4u + (e - NBT)];
+            key = ckey[(q - vw.q0) * 4u + (e - NBT)];
             bin = l2_bin(key, tab[key >> COARSE_SHIFT]);
         }
         E[pos] = key;
@@ -318,7 +320,7 @@ __device__ __forceinline__ float float_of_key(u32 k) { return __uint_as_float(bi
 __global__ __launch_bounds__(BLOCK) void k_final(const TDesc *__restrict__ td,
                                                  const GridDesc *__restrict__ gd,
                                                  const u32 *__restrict__ t_fu_off,
-                                                 const u32 *__restrict__ t_fu_ids, Bufs B)
+                                                 const u32 *__restrict__ t_gu_off, Bufs B)
 {
     extern __shared__ u32 smem[];
     double *V = reinterpret_cast<double *>(smem);              // [4096] sum of each slot
@@ -333,10 +335,11 @@ __global__ __launch_bounds__(BLOCK) void k_final(const TDesc *__restrict__ td,
     const int t = blockIdx.x;
     const u32 tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     TState *st = B.ts + t;
+    if (B.view[t] == VIEW_NONE) return;
+    const View vw = view_of(gd, B.view[t]);
     const u64 n = td[t].n;
     const u32 m = st->n_edges;
-    const u32 u0 = t_fu_off[t], u1 = t_fu_off[t + 1];
-    const u32 n_cfg = gd->n_cfg, n_p = gd->n_p, n_o = gd->n_o, n_pairs = gd->n_pairs;
+    const u32 n_cfg = gd->n_cfg, n_p = gd->n_p, n_o = gd->n_o;
 
     const u32 *segc = B.seg_cnt + (size_t)t * MAX_EDGES;
     const u32 *gc = B.grp_cnt + (size_t)t * 2 * MAX_EDGES;
@@ -365,7 +368,11 @@ __global__ __launch_bounds__(BLOCK) void k_final(const TDesc *__restrict__ td,
         ss_hi[2u * i] = 0u;
     }
     __syncthreads();
-    for (u32 g = tid; g < n_cfg; g += BLOCK) enter_config(s_cfg, g, gd->cfg_pair[g], gd->cfg_K[g]);
+    if (vw.K) {
+        if (tid == 0u) enter_config(s_cfg, vw.cfg, vw.q0, vw.K);
+    } else {
+        for (u32 g = tid; g < n_cfg; g += BLOCK) enter_config(s_cfg, g, gd->cfg_pair[g], gd->cfg_K[g]);
+    }
     for (u32 ss = tid; ss < n_sub; ss += BLOCK) {
         const u32 code = sub_code[ss];
         double val = 0.0;
@@ -436,7 +443,10 @@ __global__ __launch_bounds__(BLOCK) void k_final(const TDesc *__restrict__ td,
     // parts in a fixed order
     if (wave <= n_o) {
         double s = 0.0;
-        for (u32 u = u0 + lane; u < u1; u += 64u) s += B.sq_part[(size_t)t_fu_ids[u] * SQ_STRIDE + wave];
+        if (wave == 0u)
+            for (u32 u = t_fu_off[t] + lane; u < t_fu_off[t + 1]; u += 64u) s += B.sq_part[(size_t)u * SQ_STRIDE];
+        else
+            for (u32 u = t_gu_off[t] + lane; u < t_gu_off[t + 1]; u += 64u) s += B.sq_prot[(size_t)u * MAX_FRAC + wave - 1u];
         s = wave_sum_f64(s);
         if (lane == 0u) {
             if (wave == 0u) {
@@ -471,9 +481,9 @@ __global__ __launch_bounds__(BLOCK) void k_final(const TDesc *__restrict__ td,
         return sk;
     };
     // sums of the finest bins of every pair, slot by slot; the bins for fewer bits are unions of them
-    const u32 K_top = gd->K_top;
-    for (u32 w = tid; w < n_pairs * K_top; w += BLOCK) {
-        const u32 q = w / K_top, k = w % K_top;
+    const u32 K_top = !vw.K ? gd->K_top : (vw.K & (vw.K - 1u)) ? 1u : vw.K;
+    for (u32 w = tid; w < vw.n_pairs * K_top; w += BLOCK) {
+        const u32 q = vw.q0 + w / K_top, k = w % K_top;
         if (K_top > 1u) S8[q * 256u + k] = slot_sum(span(q, K_top, k));
     }
     __syncthreads();
@@ -490,7 +500,7 @@ __global__ __launch_bounds__(BLOCK) void k_final(const TDesc *__restrict__ td,
     };
     // One wave per pair: 3, 6 and 12 bins first (the lanes of a bin share its slots), then K_top bins,
     // half as many, ... 2: the sums of neighbours are added in place by the wave that reads them.
-    for (u32 q = wave; q < n_pairs; q += BLOCK / 64) {
+    for (u32 q = vw.q0 + wave; q < vw.q0 + vw.n_pairs; q += BLOCK / 64) {
         for (u32 s = 9u; s < 12u; s++) {
             const u32 g = s_cfg[q][s];
             if (g == 0xFFFFu) continue;
@@ -517,6 +527,7 @@ __global__ __launch_bounds__(BLOCK) void k_final(const TDesc *__restrict__ td,
                 acc = wave_sum_f64(acc);
                 if (lane == 0u) s_acc[q][s] = acc;
             }
+            if (vw.K) break;
             asm volatile("" ::: "memory");
             double f[2];
 #pragma unroll
@@ -538,6 +549,7 @@ __global__ __launch_bounds__(BLOCK) void k_final(const TDesc *__restrict__ td,
     __shared__ double s_sse[MAX_CFG];
     __shared__ u64 s_cost[MAX_CFG];
     for (u32 g = tid; g < n_cfg; g += BLOCK) {
+        if (vw.K && g != vw.cfg) continue;
         const u32 K = gd->cfg_K[g], q = gd->cfg_pair[g];
         double sse = s_sumsq - s_qout[gd->pair_o[q]] - s_acc[q][k_slot(K)];
         if (sse < 0.0) sse = 0.0;
@@ -555,12 +567,14 @@ __global__ __launch_bounds__(BLOCK) void k_final(const TDesc *__restrict__ td,
     }
     __syncthreads();
     if (wave == 0u) {
-        const Choice c = choose_config(s_sse, s_cost, n_cfg, gd->eps, s_sumsq);
-        if (lane == 0u) {
-            st->best = c.best;
-            st->feasible = c.feasible;
-            store_result(st, B.res + t);
+        if (!vw.K) {
+            const Choice c = choose_config(s_sse, s_cost, n_cfg, gd->eps, s_sumsq);
+            if (lane == 0u) {
+                st->best = c.best;
+                st->feasible = c.feasible;
+            }
         }
+        if (lane == 0u) store_result(st, B.res + t);
     }
 }
 
@@ -595,7 +609,7 @@ hipError_t launch_score(const Batch &bt, hipStream_t s)
     if (bt.nB == 0) return hipSuccess;
     hipError_t e = set_attrs();
     if (e) return e;
-    PROF("k_final", s, k_final<<<bt.nB, BLOCK, SM_FINAL, s>>>(bt.td, bt.gd, bt.t_fu_off, bt.t_fu_ids, bt.bufs));
+    PROF("k_final", s, k_final<<<bt.nB, BLOCK, SM_FINAL, s>>>(bt.td, bt.gd, bt.t_fu_off, bt.t_gu_off, bt.bufs));
     return hipGetLastError();
 }
 

@@ -23,6 +23,8 @@
 //                          marked tensors alone, unsampled (the results never depend on sampling).
 //   k_thr_setup/count/pick exact thresholds and class counts from the gathered buckets: all
 //                          thresholds of a tensor in two counting passes over its gathered keys
+//   What follows is for searches with scores and for tensors whose choice the bounds of the errors leave open
+//   (other searches end with k_decide; their boundaries come with the quantizer's sweep, k_fuse):
 //   k_plan2                exact rank of every boundary of every (prune, protect) pair -> its bin;
 //                          only those bins (and the bins of the class edges) are "active";
 //                          groups of consecutive active bins
@@ -127,8 +129,8 @@ __global__ __launch_bounds__(BLOCK) void k_hist(const TDesc *__restrict__ td, in
         // pool that belongs to this wave alone: the workgroup's region starts at its first element
         // of the tensor, and a wave's share of it is as large as the wave's share of the elements
         // (1024 per tile), so no counter is shared.
-        const u32 capw = B.unit_capw[fu];
-        GLOBAL_AS u32 *gdst = gptr(B.pool) + B.unit_off[fu] + (u64)wave * capw;
+        const u32 capw = B.units[fu].capw;
+        GLOBAL_AS u32 *gdst = gptr(B.pool) + B.units[fu].off + (u64)wave * capw;
         u32 gathered = 0u; // wave-uniform
         bool overflow = false;
         if (LEVEL == 2) {
@@ -142,7 +144,7 @@ __global__ __launch_bounds__(BLOCK) void k_hist(const TDesc *__restrict__ td, in
             if (LEVEL == 1 && sampled && (tile - d.tile0) % (u64)SAMPLE_RATE != 0u) continue;
             const u64 e0 = (tile - d.tile0) * (u64)TILE;
             const u64 rem = d.n - e0;
-            const u32 cnt = rem < (u64)TILE ? (u32)rem : (u32)TILE;
+            const u32 cnt = tile_len(rem, (u32)TILE);
             float v[16];
             const u32 mask = load_tile(d, e0, cnt, v);
             if (LEVEL == 1) {
@@ -301,33 +303,102 @@ __global__ __launch_bounds__(BLOCK) void k_pool_sum(const TDesc *__restrict__ td
         atomicAdd((unsigned long long *)&B.ts[d.leader].pool_zero, (unsigned long long)B.ts[t].n_zero);
 }
 
-// magnitude bin of a rank: last j in [0, 16384) with A[j] <= rank (A: exclusive prefix of the counts)
-__device__ __forceinline__ u32 magbin_of_rank(const u32 *A, u64 rank)
+// First-level magnitude bins in blocks of 16: keys in the blocks before each, of both signs and negative ones.
+constexpr u32 MAG_BLOCKS = L1_MAGBINS / 16;
+static_assert(MAG_BLOCKS == BLOCK, "one block of magnitude bins per thread");
+struct MagPrefix {
+    u32 all[MAG_BLOCKS], neg[MAG_BLOCKS], w_all[BLOCK / 64], w_neg[BLOCK / 64];
+    u32 total, total_neg;
+};
+typedef u32 u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void load_mag_block(const u32 *h, u32 m, u32 (&cn)[16], u32 (&cp)[16])
 {
-    int lo = 0, hi = L1_MAGBINS;
-    while (lo < hi) {
-        int mid = (lo + hi) >> 1;
-        if ((u64)A[mid] > rank)
-            hi = mid;
-        else
-            lo = mid + 1;
+    const GLOBAL_AS u32x4 *p = (const GLOBAL_AS u32x4 *)gptr(h);
+#pragma unroll
+    for (u32 i = 0; i < 4u; i++) { // magnitude bin j is key bin 16384 + j for positive, 16383 - j for negative
+        const u32x4 x = p[(u32)L1_MAGBINS / 4u + 4u * m + i], y = p[(u32)L1_MAGBINS / 4u - 1u - 4u * m - i];
+#pragma unroll
+        for (u32 j = 0; j < 4u; j++) {
+            cp[4u * i + j] = x[j];
+            cn[4u * i + j] = y[3u - j];
+        }
     }
-    return (u32)(lo > 0 ? lo - 1 : 0);
+}
+__device__ __forceinline__ void mag_prefix(MagPrefix &mp, const u32 *h, u32 scale) // by the whole workgroup
+{
+    const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    u32 cn[16], cp[16], n = 0u, p = 0u;
+    load_mag_block(h, tid, cn, cp);
+#pragma unroll
+    for (u32 i = 0; i < 16u; i++) {
+        n += cn[i];
+        p += cp[i];
+    }
+    n *= scale;
+    p = p * scale + n;
+    const u32 ip = wave_incl_scan(p), in = wave_incl_scan(n);
+    __syncthreads(); // (what was here before is not read any more)
+    if (lane == 63u) {
+        mp.w_all[wave] = ip;
+        mp.w_neg[wave] = in;
+    }
+    __syncthreads();
+    u32 bp = 0u, bn = 0u;
+    for (u32 w = 0; w < wave; w++) {
+        bp += mp.w_all[w];
+        bn += mp.w_neg[w];
+    }
+    mp.all[tid] = bp + ip - p;
+    mp.neg[tid] = bn + in - n;
+    if (tid == BLOCK - 1u) {
+        mp.total = bp + ip;
+        mp.total_neg = bn + in;
+    }
+    __syncthreads();
+}
+struct MagBin {
+    u32 j, below, below_neg, cn, cp; // keys below the bin, and its own, by sign
+};
+// the last bin with at most `rank` keys below it
+__device__ __forceinline__ MagBin magbin_of_rank(const MagPrefix &mp, const u32 *h, u32 scale, u64 rank)
+{
+    u32 m = 0u;
+#pragma unroll
+    for (u32 step = MAG_BLOCKS / 2u; step > 0u; step >>= 1)
+        if ((u64)mp.all[m + step] <= rank) m += step;
+    u32 cn[16], cp[16], run = mp.all[m], neg = mp.neg[m];
+    load_mag_block(h, m, cn, cp);
+    MagBin r = {16u * m, run, neg, cn[0] * scale, cp[0] * scale};
+#pragma unroll
+    for (u32 i = 0; i < 16u; i++) {
+        if ((u64)run <= rank) {
+            r.j = 16u * m + i;
+            r.below = run;
+            r.below_neg = neg;
+            r.cn = cn[i] * scale;
+            r.cp = cp[i] * scale;
+        }
+        run += (cn[i] + cp[i]) * scale;
+        neg += cn[i] * scale;
+    }
+    return r;
 }
 
+constexpr u32 SPREAD_BINS = 12288; // bins that go where they narrow the bounds of the errors
+static_assert(COARSE + L2_BINS / 4 + SPREAD_BINS <= L2_BINS, "fits beside a bin per prefix and the windows");
 // REDO: only the tensors whose sampled sweep 1 mispredicted (their histogram is exact now).
 template <bool REDO>
 __global__ __launch_bounds__(BLOCK) void k_plan1(const TDesc *__restrict__ td,
                                                  const GridDesc *__restrict__ gd, Bufs B)
 {
-    extern __shared__ u32 smem[];
-    u32 *A = smem;                    // [16385] magnitude-bin counts -> exclusive prefix
-    u32 *Bn = smem + (L1_MAGBINS + 4); // [16385] negative counts -> exclusive prefix
-    u32 *nc = Bn + (L1_MAGBINS + 4);  // [4097] per coarse prefix
-    __shared__ u32 tmp[BLOCK / 64 + 1];
+    __shared__ MagPrefix mp;
+    __shared__ u32 tmp[BLOCK / 64];
     __shared__ u32 s_j[MAX_THR], s_jlo[MAX_THR], s_jhi[MAX_THR], s_cn[MAX_THR], s_cp[MAX_THR];
     __shared__ u64 s_res[MAX_THR], s_bn[MAX_THR], s_bp[MAX_THR];
     __shared__ u32 s_forced[BLOCK / 64];
+    __shared__ double s_q[BLOCK / 64];
+    __shared__ float s_w[BLOCK / 64];
+    constexpr u32 PER = COARSE / BLOCK; // key prefixes per thread: PER * tid ..
 
     const int t = blockIdx.x;
     const u32 tid = threadIdx.x;
@@ -338,66 +409,70 @@ __global__ __launch_bounds__(BLOCK) void k_plan1(const TDesc *__restrict__ td,
     const u32 scale = sampled ? (u32)SAMPLE_RATE : 1u; // a sampled histogram stands for the whole
     const u32 *h1 = B.hist1 + (size_t)t * L1_BINS;
     const bool pooled = td[t].pooled != 0u; // (never sampled)
+    u32 nc[PER]; // keys under every prefix
+    {
+        const GLOBAL_AS u32x4 *p = (const GLOBAL_AS u32x4 *)gptr(h1) + tid * (PER * 2u);
+        u32x4 x[PER * 2u];
+#pragma unroll
+        for (u32 i = 0; i < PER * 2u; i++) x[i] = p[i];
+#pragma unroll
+        for (u32 k = 0; k < PER; k++) {
+            const u32x4 y = x[2u * k] + x[2u * k + 1u];
+            nc[k] = (y.x + y.y + y.z + y.w) * scale;
+        }
+    }
     if (pooled) {
         // the thresholds are order statistics of the group: their bins and the ranks inside them
         // come from the group's histogram; everything else below is the tensor's own
         const u32 *ph = B.pool_h1 + (size_t)td[t].leader * L1_BINS;
-        for (int j = tid; j < L1_MAGBINS; j += BLOCK) A[j] = ph[L1_MAGBINS - 1 - j] + ph[L1_MAGBINS + j];
-        __syncthreads();
-        const u32 gtotal = block_excl_scan(A, A, L1_MAGBINS, tmp);
-        if (tid == 0 && (u64)gtotal != td[t].n_pool) atomicOr(&st->internal_err, 1u);
+        mag_prefix(mp, ph, 1u);
+        if (tid == 0 && (u64)mp.total != td[t].n_pool) atomicOr(&st->internal_err, 1u);
         if (tid < gd->n_p + gd->n_o) {
             const u64 R = threshold_rank(gd, tid, td[t].n_pool);
-            const u32 j = magbin_of_rank(A, R);
-            s_j[tid] = j;
-            s_res[tid] = R - (u64)A[j];
-            st->pool_expect[tid] = A[j + 1] - A[j];
+            const MagBin g = magbin_of_rank(mp, ph, 1u, R);
+            s_j[tid] = g.j;
+            s_res[tid] = R - (u64)g.below;
+            st->pool_expect[tid] = g.cn + g.cp;
         }
-        __syncthreads();
     }
-    for (int j = tid; j < L1_MAGBINS; j += BLOCK) {
-        u32 cn = h1[L1_MAGBINS - 1 - j] * scale, cp = h1[L1_MAGBINS + j] * scale;
-        A[j] = cn + cp;
-        Bn[j] = cn;
-    }
-    for (int c = tid; c < COARSE; c += BLOCK) {
-        u32 s = 0;
-        for (int i = 0; i < 8; i++) s += h1[8 * c + i];
-        nc[c] = s * scale;
-    }
-    __syncthreads();
-    u32 total = block_excl_scan(A, A, L1_MAGBINS, tmp);
-    const u32 total_neg = block_excl_scan(Bn, Bn, L1_MAGBINS, tmp);
+    mag_prefix(mp, h1, scale);
+    const u32 total = mp.total;
     if (tid == 0 && !sampled) { // (a sampled tensor gets these from the exact second histogram)
         if ((u64)total != n) atomicOr(&st->internal_err, 1u);
-        st->n_neg = total_neg;
+        st->n_neg = mp.total_neg;
         // magnitude bins from 0x7f800000 >> 17 on hold Inf and NaN only
-        if (total - A[0x7f800000u >> L1_SHIFT] != 0u) st->nonfinite = 1u;
+        static_assert((0x7f800000u >> L1_SHIFT) % 16u == 0u, "a whole block");
+        if (total - mp.all[(0x7f800000u >> L1_SHIFT) / 16u] != 0u) st->nonfinite = 1u;
     }
 
     const u32 n_p = gd->n_p, n_o = gd->n_o, n_thr = n_p + n_o;
     if (tid < n_thr) {
         const u64 R = threshold_rank(gd, tid, n);
-        // bin of a rank: last j in [0, 16384) with A[j] <= rank
-        auto bin_of = [&](u64 rank) -> u32 {
-            int lo = 0, hi = L1_MAGBINS;
-            while (lo < hi) {
-                int mid = (lo + hi) >> 1;
-                if ((u64)A[mid] > rank)
-                    hi = mid;
-                else
-                    lo = mid + 1;
+        auto bin_of = [&](u64 rank) -> u32 { return magbin_of_rank(mp, h1, scale, rank).j; };
+        if (!sampled && pooled) {
+            const u32 j = s_jlo[tid] = s_jhi[tid] = s_j[tid];
+            u32 cn[16], cp[16], below = mp.all[j / 16u], below_neg = mp.neg[j / 16u];
+            load_mag_block(h1, j / 16u, cn, cp);
+            u32 own_n = 0u, own_p = 0u;
+#pragma unroll
+            for (u32 i = 0; i < 16u; i++) {
+                below += i < j % 16u ? cn[i] + cp[i] : 0u;
+                below_neg += i < j % 16u ? cn[i] : 0u;
+                own_n = i == j % 16u ? cn[i] : own_n;
+                own_p = i == j % 16u ? cp[i] : own_p;
             }
-            return (u32)(lo > 0 ? lo - 1 : 0);
-        };
-        if (!sampled) {
-            const u32 j = pooled ? s_j[tid] : bin_of(R);
-            s_j[tid] = s_jlo[tid] = s_jhi[tid] = j;
-            if (!pooled) s_res[tid] = R - (u64)A[j];
-            s_bn[tid] = Bn[j];
-            s_bp[tid] = A[j] - Bn[j];
-            s_cn[tid] = h1[L1_MAGBINS - 1 - j];
-            s_cp[tid] = h1[L1_MAGBINS + j];
+            s_bn[tid] = below_neg;
+            s_bp[tid] = below - below_neg;
+            s_cn[tid] = own_n;
+            s_cp[tid] = own_p;
+        } else if (!sampled) {
+            const MagBin g = magbin_of_rank(mp, h1, 1u, R);
+            s_j[tid] = s_jlo[tid] = s_jhi[tid] = g.j;
+            s_res[tid] = R - (u64)g.below;
+            s_bn[tid] = g.below_neg;
+            s_bp[tid] = g.below - g.below_neg;
+            s_cn[tid] = g.cn;
+            s_cp[tid] = g.cp;
         } else {
             // The rank's bin is only predicted: all bins that may hold it are gathered.  The
             // estimate of a cumulative count c from one tile in SAMPLE_RATE has a standard
@@ -443,18 +518,19 @@ __global__ __launch_bounds__(BLOCK) void k_plan1(const TDesc *__restrict__ td,
     // second-level table: smallest target population whose bin total fits
     // (exact zeros are counted, never gathered or sorted: they do not ask for bins; a prefix with
     // gathered first-level bins gets at least 8 bins, so that the second histogram resolves them)
-    if (tid == 0) {
-        const u32 zc = ZERO_KEY >> COARSE_SHIFT;
+    constexpr u32 ZC = ZERO_KEY >> COARSE_SHIFT;
+    static_assert(ZC % PER == 0u, "the first prefix of its thread");
+    if (tid == ZC / PER) {
         const u64 nz = st->n_zero;
-        nc[zc] = (u64)nc[zc] > nz ? (u32)(nc[zc] - nz) : 1u;
-        if (sampled) {
-            st->n_zero = 0ull; // (an estimate: the second sweep counts the zeros exactly)
-            st->mag_min = 0xFFFFFFFFu;
-            st->mag_max = 0u;
-        }
+        nc[0] = (u64)nc[0] > nz ? (u32)(nc[0] - nz) : 1u;
     }
     __syncthreads();
-    // gathered first-level bins of this thread's key prefixes (prefix c = tid + BLOCK * k)
+    if (tid == 0 && sampled) {
+        st->n_zero = 0ull; // (an estimate: the second sweep counts the zeros exactly)
+        st->mag_min = 0xFFFFFFFFu;
+        st->mag_max = 0u;
+    }
+    // gathered first-level bins of this thread's key prefixes
     // (the windows of the ranks 0 and n - 1 of a sampled tensor are gathered, but nothing has to be
     // resolved inside them: they ask for no bins)
     u32 extreme = 0u;
@@ -463,45 +539,79 @@ __global__ __launch_bounds__(BLOCK) void k_plan1(const TDesc *__restrict__ td,
             const u64 R = threshold_rank(gd, q, n);
             if (R == 0ull || R == n - 1ull) extreme |= 1u << q;
         }
-    u32 my_flags[COARSE / BLOCK], my_force[COARSE / BLOCK];
-#pragma unroll
-    for (int k = 0; k < COARSE / BLOCK; k++) {
-        my_flags[k] = cell_flags(tid + (u32)BLOCK * k, s_jlo, s_jhi, n_thr);
-        my_force[k] = extreme ? cell_flags(tid + (u32)BLOCK * k, s_jlo, s_jhi, n_thr, extreme) : my_flags[k];
-    }
-    auto depth_of = [&](int c, u64 target, int k) -> u32 {
-        u32 d = nc[c] ? depth_for(nc[c], target) : 0u;
-        if (sampled && d < 3u && my_force[k]) d = 3u;
-        return d;
-    };
-    // The total of the bins falls with the target.  A prefix of c elements takes at least c / target
-    // bins and fewer than 2 c / target + 1, or 8 more where it is resolved for a window.
+    // A prefix of c elements that lie around m adds c (m / 16)^2 / 4^depth to the uncertainty of the errors that
+    // k_decide bounds from the bins (half a prefix is a sixteenth of its values' exponent); a given number of
+    // bins leaves least of it when they are dealt out by the cube root of c m^2.  SPREAD_BINS are,
+    // on top of the equal populations (whichever asks for more): the bounds at 7 and 8 bits are 0.4 .. 0.9 %
+    // wide then instead of 3 .. 6 % (Gaussian to Student-t(3) values, 1 Mi; with 8192 bins 0.5 .. 1.2 %), and
+    // the bins that boundaries fall into hold 15 % more.
+    u32 my_flags[PER], my_least[PER]; // least depth
+    float my_w[PER];
+    double q = 0.0, my_q[PER];
     u32 n_el = 0u, n_forced = 0u;
 #pragma unroll
-    for (int k = 0; k < COARSE / BLOCK; k++) {
-        n_el += nc[tid + BLOCK * k];
-        n_forced += sampled && my_force[k] ? 1u : 0u;
+    for (u32 k = 0; k < PER; k++) {
+        const u32 c = PER * tid + k;
+        my_flags[k] = cell_flags(c, s_jlo, s_jhi, n_thr);
+        const u32 force = !sampled ? 0u : extreme ? cell_flags(c, s_jlo, s_jhi, n_thr, extreme) : my_flags[k];
+        my_least[k] = force ? 3u : 0u;
+        n_forced += force ? 8u : 0u;
+        n_el += nc[k];
+        const u32 key = (c << COARSE_SHIFT) | (1u << (COARSE_SHIFT - 1)); // (infinities: the tensor is refused)
+        const double m = mag_of_key(key) < 0x7f800000u ? (double)__uint_as_float(bits_of_key(key)) : 0.0;
+        my_q[k] = (double)nc[k] * m * m;
+        q += my_q[k];
     }
     n_el = wave_sum(n_el);
     n_forced = wave_sum(n_forced);
+    q = wave_sum_f64(q);
     if ((tid & 63u) == 0u) {
         tmp[tid >> 6] = n_el;
         s_forced[tid >> 6] = n_forced;
+        s_q[tid >> 6] = q;
     }
     __syncthreads();
     n_el = n_forced = 0u;
+    q = 0.0;
     for (int w = 0; w < BLOCK / 64; w++) {
         n_el += tmp[w];
         n_forced += s_forced[w];
+        q += s_q[w];
     }
-    const u32 room = (u32)L2_BINS - (u32)COARSE - 8u * n_forced;
+    float w_sum = 0.0f;
+#pragma unroll
+    for (u32 k = 0; k < PER; k++) {
+        my_w[k] = q > 0.0 ? cbrtf((float)(my_q[k] / q)) : 0.0f;
+        w_sum += my_w[k];
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) w_sum += __shfl_xor(w_sum, o);
+    if ((tid & 63u) == 0u) s_w[tid >> 6] = w_sum;
+    __syncthreads();
+    w_sum = 0.0f;
+    for (int w = 0; w < BLOCK / 64; w++) w_sum += s_w[w];
+    // (windows that span most prefixes, of values all over the range of fp32, leave no room for this)
+    const bool spread = n_forced <= (u32)L2_BINS / 4u && w_sum > 0.0f; // (there is always room for 4096 + n_forced + SPREAD_BINS)
+#pragma unroll
+    for (u32 k = 0; k < PER; k++) {
+        const float bins = spread ? my_w[k] * ((float)SPREAD_BINS / w_sum) : 0.0f;
+        const u32 d = bins >= 2.0f ? (u32)ilogbf(bins) : 0u;
+        if (d > my_least[k]) my_least[k] = d < 9u ? d : 9u;
+    }
+    // The total of the bins falls with the target.  A prefix of c elements takes at least c / target
+    // bins and fewer than 2 c / target + 1, or its least number where that is more.
+    const u32 room = (u32)L2_BINS - (u32)COARSE - n_forced - (spread ? SPREAD_BINS : 0u);
+    auto depth_of = [&](u64 target, u32 k) -> u32 {
+        const u32 d = nc[k] ? depth_for(nc[k], target) : 0u;
+        return d < my_least[k] ? my_least[k] : d;
+    };
     u64 lo = n_el / (u32)L2_BINS ? n_el / (u32)L2_BINS : 1u, hi = n;
-    if (n_forced < 1024u) hi = 2ull * n_el / room + 1ull;
+    if (n_forced < 8192u) hi = 2ull * n_el / room + 1ull;
     while (lo < hi) {
         u64 mid = lo + ((hi - lo) >> 1);
         u32 s = 0;
 #pragma unroll
-        for (int k = 0; k < COARSE / BLOCK; k++) s += 1u << depth_of(tid + BLOCK * k, mid, k);
+        for (u32 k = 0; k < PER; k++) s += 1u << depth_of(mid, k);
         s = wave_sum(s);
         __syncthreads();
         if ((tid & 63u) == 0u) tmp[tid >> 6] = s;
@@ -513,23 +623,33 @@ __global__ __launch_bounds__(BLOCK) void k_plan1(const TDesc *__restrict__ td,
         else
             lo = mid + 1;
     }
-    __syncthreads();
-    u32 *cnt = A; // reuse: bins per coarse prefix
+    u32 d[PER], bins = 0u;
 #pragma unroll
-    for (int k = 0; k < COARSE / BLOCK; k++) cnt[tid + BLOCK * k] = 1u << depth_of(tid + BLOCK * k, lo, k);
-    __syncthreads();
-    u32 nb2 = block_excl_scan(cnt, Bn, COARSE, tmp); // Bn[c] = base
-    u32 *tab = B.table2 + (size_t)t * COARSE;
-#pragma unroll
-    for (int k = 0; k < COARSE / BLOCK; k++) {
-        const int c = tid + BLOCK * k;
-        const u32 d = depth_of(c, lo, k);
-        // top byte: which of the 8 first-level bins under this key prefix are gathered
-        tab[c] = my_flags[k] | (Bn[c] << 5) | d;
+    for (u32 k = 0; k < PER; k++) {
+        d[k] = depth_of(lo, k);
+        bins += 1u << d[k];
     }
+    const u32 inc = wave_incl_scan(bins);
+    __syncthreads();
+    if ((tid & 63u) == 63u) tmp[tid >> 6] = inc;
+    __syncthreads();
+    u32 base = inc - bins, nb2 = 0u;
+    for (u32 w = 0; w < BLOCK / 64; w++) {
+        base += w < tid >> 6 ? tmp[w] : 0u;
+        nb2 += tmp[w];
+    }
+    u32x4 entry;
+#pragma unroll
+    for (u32 k = 0; k < PER; k++) {
+        // top byte: which of the 8 first-level bins under this key prefix are gathered
+        entry[k] = my_flags[k] | (base << 5) | d[k];
+        if (PER * tid + k == ZC) st->zbin = base;
+        base += 1u << d[k];
+    }
+    static_assert(PER == 4u, "an entry per element of a vector");
+    ((GLOBAL_AS u32x4 *)gptr(B.table2 + (size_t)t * COARSE))[tid] = entry;
     if (tid == 0) {
         st->nb2 = nb2;
-        st->zbin = Bn[ZERO_KEY >> COARSE_SHIFT];
         if (nb2 > (u32)L2_BINS) atomicOr(&st->internal_err, 2u);
     }
 }
@@ -701,8 +821,7 @@ __global__ __launch_bounds__(TSEL) void k_thr_setup(const TDesc *__restrict__ td
 }
 
 template <int ROUND>
-__global__ __launch_bounds__(TSEL) void k_thr_count(const TDesc *__restrict__ td,
-                                                    const u32 *__restrict__ fu_tensor, Bufs B)
+__global__ __launch_bounds__(TSEL) void k_thr_count(const TDesc *__restrict__ td, Bufs B)
 {
     __shared__ u32 hist[SEL_HIST];
     __shared__ unsigned char which[L1_MAGBINS]; // bucket of a magnitude bin + 1, or 0
@@ -712,7 +831,8 @@ __global__ __launch_bounds__(TSEL) void k_thr_count(const TDesc *__restrict__ td
     const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const u32 c = B.unit_thr[(size_t)fu * 16 + wave]; // keys in this wave's fragment
     if (__syncthreads_or(c != 0u) == 0) return;
-    const int t = (int)fu_tensor[fu];
+    const Unit un = B.units[fu];
+    const int t = (int)un.tensor;
     const TState *st = B.ts + t;
     const u32 n_thr = st->n_thr, nb = st->n_buckets;
     const u32 n_slots = (ROUND == 0 ? nb : n_thr) * 1024u;
@@ -726,7 +846,7 @@ __global__ __launch_bounds__(TSEL) void k_thr_count(const TDesc *__restrict__ td
     __syncthreads();
     if (tid < nb) which[st->bucket_magbin[tid]] = (unsigned char)(tid + 1u);
     __syncthreads();
-    const u32 *list = B.pool + B.unit_off[fu] + (u64)wave * B.unit_capw[fu];
+    const u32 *list = B.pool + un.off + (u64)wave * un.capw;
     // smallest / largest magnitude among the gathered keys (first pass): for a tensor whose first
     // sweep was sampled the windows of the ranks 0 and n - 1 were gathered, so these are the
     // tensor's own extremes (exact zeros are never gathered: TState::n_zero tells of them)
@@ -877,97 +997,142 @@ __global__ __launch_bounds__(TSEL) void k_thr_pick(const TDesc *__restrict__ td,
 // ------------------------------------------------------------------------------------------
 // plan 2: boundary ranks -> active bins -> groups of active bins
 // ------------------------------------------------------------------------------------------
-// One workgroup per tensor: bound by the latency of its steps (1 Mi values, 6 pairs: 145 us with a run
-// of bins per thread in the scans and the marks in device memory, 30 us now).
-__global__ __launch_bounds__(BLOCK) void k_plan2(const TDesc *__restrict__ td,
-                                                 const GridDesc *__restrict__ gd, Bufs B, bool light)
+// a search that chooses nothing (thresholds for the sketch quantizer, which brings its own bins, or for
+// a quantizer whose configuration is given) ends here
+__global__ __launch_bounds__(64) void k_counts(const TDesc *__restrict__ td, const GridDesc *__restrict__ gd, Bufs B)
 {
-    extern __shared__ u32 smem[];
-    u32 *cum = smem;                  // [nb2 + 1] prefix of the bins' counts; then of the active bins' counts
-    u32 *T = smem + (L2_BINS + 4);    // [COARSE]
-    u32 *act = T + COARSE;            // [L2_BINS / 32] active bins
-    __shared__ u32 tmp[BLOCK / 64 + 1];
+    const int t = blockIdx.x;
+    TState *st = B.ts + t;
+    store_pairs(st, gd, td[t].n);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        st->best = 0u;
+        st->feasible = 0u;
+        store_result(st, B.res + t);
+    }
+}
+
+// One workgroup per tensor, bound by the latency of its steps.  A thread holds the counts of 32 consecutive
+// bins in registers; prefixes over groups of eight bins are all that LDS keeps, so two workgroups fit a CU
+// (1 Mi values, 6 pairs: 46 us with all 32768 prefixes in LDS and a scan over rows of 64 bins, 28 us so).
+__global__ __launch_bounds__(BLOCK) void k_plan2(const TDesc *__restrict__ td, const GridDesc *__restrict__ gd, Bufs B,
+                                                 u32 *__restrict__ n_grp_total)
+{
+    __shared__ u32 pre8[L2_BINS / 8]; // keys in the bins before every eighth
+    __shared__ u32 T[COARSE];
+    __shared__ u32 act[L2_BINS / 32]; // active bins
+    __shared__ u32 tmp[BLOCK / 64], tmp2[BLOCK / 64];
     __shared__ u64 sAn[MAX_PAIRS], sMn[MAX_PAIRS], sPP[MAX_PAIRS], sM[MAX_PAIRS];
 
     const int t = blockIdx.x;
     const u32 tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (t == 0 && tid == 0u) *n_grp_total = 0u; // (k_edges adds to it)
+    if (B.view[t] == VIEW_NONE) return;
+    const View vw = view_of(gd, B.view[t]);
     const TDesc d = td[t];
     const u64 n = d.n;
     TState *st = B.ts + t;
-    const u32 nb2 = st->nb2;
     const u32 zbin = st->zbin;
-    const u64 n_zero = st->n_zero;
+    const u32 n_zero = (u32)st->n_zero;
     const u32 *h2 = B.hist2 + (size_t)t * L2_BINS;
     const u32 *tab = B.table2 + (size_t)t * COARSE;
-    u32 *binfo = B.binfo + (size_t)t * L2_BINS;
-    const u32 n_pairs = gd->n_pairs, n_p = gd->n_p;
+    const u32 n_p = gd->n_p;
 
-    if (tid < n_pairs) {
-        const u32 tp = gd->pair_p[tid], to = n_p + gd->pair_o[tid];
-        const u64 n_neg = st->n_neg, n_pos = n - n_neg;
-        const u64 Pn = st->thr_lt_neg[tp], Pp = st->thr_lt_pos[tp];
-        const u64 An = st->thr_gt_neg[to], Ap = st->thr_gt_pos[to];
-        const u64 Mn = n_neg - An - Pn, Mp = n_pos - Ap - Pp;
-        st->pair_An[tid] = An;
-        st->pair_Ap[tid] = Ap;
-        st->pair_Pn[tid] = Pn;
-        st->pair_Pp[tid] = Pp;
-        st->pair_Mn[tid] = Mn;
-        st->pair_M[tid] = Mn + Mp;
-        sAn[tid] = An;
-        sMn[tid] = Mn;
-        sPP[tid] = Pn + Pp;
-        sM[tid] = Mn + Mp;
-        if (Mn + Mp == 0ull || Mn > n || Mp > n) {
-            // (shared thresholds can leave a tensor without quantized values: reported, and the
-            // tensor's gathered keys are not processed)
-            atomicOr(&st->internal_err, 32u);
-            atomicOr(&st->pool_overflow, 8u);
-        }
-    }
-    if (light) { // (nothing follows: the sketch quantizer brings its own bins)
-        __syncthreads();
-        if (tid == 0) store_result(st, B.res + t);
-        return;
-    }
+    u32x4 c[8]; // the thread's bins (those past the last one are empty)
+#pragma unroll
+    for (u32 i = 0; i < 8u; i++) c[i] = ((const GLOBAL_AS u32x4 *)gptr(h2))[tid * 8u + i];
     for (u32 i = tid; i < (u32)COARSE; i += BLOCK) T[i] = tab[i];
     act[tid] = 0u;
     static_assert(L2_BINS / 32 == BLOCK, "one word of the active bins per thread");
-    const u32 total = block_excl_scan(h2, cum, (int)nb2, tmp);
+    store_pairs(st, gd, n);
+    if (tid < gd->n_pairs) { // (its own stores)
+        sAn[tid] = st->pair_An[tid];
+        sMn[tid] = st->pair_Mn[tid];
+        sPP[tid] = st->pair_Pn[tid] + st->pair_Pp[tid];
+        sM[tid] = st->pair_M[tid];
+    }
+    { // what sweep 3 and the group sort add to starts at zero
+        const u32x4 z = {0u, 0u, 0u, 0u};
+        auto clear = [&](void *p, size_t bytes) { // (rows start at multiples of 16 bytes and are as long)
+            GLOBAL_AS u32x4 *x = (GLOBAL_AS u32x4 *)gptr((u32 *)p);
+            for (size_t i = tid; i < bytes / 16u; i += BLOCK) x[i] = z;
+        };
+        clear(B.grp_cnt + (size_t)t * 2 * MAX_EDGES, 2 * MAX_EDGES * 4);
+        clear(B.grp_sx + (size_t)t * 2 * MAX_EDGES, 2 * MAX_EDGES * 8);
+        clear(B.mom_sx + (size_t)t * MAX_SUB, MAX_SUB * 8);
+        clear(B.tile_out + d.tile0 * MAX_FRAC, (size_t)((n + TILE - 1) / TILE) * MAX_FRAC * 4);
+    }
+    u32 part[4], mine = 0u;
+#pragma unroll
+    for (u32 i = 0; i < 8u; i++) {
+        if ((i & 1u) == 0u) part[i >> 1] = mine;
+        mine += c[i].x + c[i].y + c[i].z + c[i].w;
+    }
+    const u32 inc_n = wave_incl_scan(mine);
+    if (lane == 63u) tmp[wave] = inc_n;
+    __syncthreads();
+    u32 before = inc_n - mine, total = 0u;
+    for (u32 w = 0; w < BLOCK / 64; w++) {
+        const u32 x = tmp[w];
+        before += w < wave ? x : 0u;
+        total += x;
+    }
+#pragma unroll
+    for (u32 i = 0; i < 4u; i++) pre8[4u * tid + i] = before + part[i];
     if (tid == 0 && (u64)total != n) atomicOr(&st->internal_err, 16u);
-    const u32 n_bnd = gd->n_bnd;
-    const u32 TG = n_pairs * n_bnd;
+    __syncthreads();
+    const u32 n_bnd = vw.n_bnd;
+    const u32 TG = vw.n_pairs * n_bnd;
     u32 *tb = B.tgt_bin + (size_t)t * TGT_STRIDE;
     u32 *tr = B.tgt_res + (size_t)t * TGT_STRIDE;
     u32 *tk = B.tgt_key + (size_t)t * TGT_STRIDE;
     u32 *trank = B.tgt_rank + (size_t)t * TGT_STRIDE;
     u32 *tlo = B.tgt_klo + (size_t)t * TGT_STRIDE; // key range of the boundary's bin
     u32 *thi = B.tgt_khi + (size_t)t * TGT_STRIDE;
-    for (u32 w = tid; w < TG; w += BLOCK) {
-        const u32 q = w / n_bnd, j = gd->bnd[w % n_bnd], i = q * (u32)NBT + j; // boundary j of pair q
+    constexpr u32 NW = (MAX_PAIRS * NBT + BLOCK - 1) / BLOCK; // boundaries per thread: worked on side by side
+    u32 e_at[NW], e_r[NW], e_g[NW];
+    bool e_ok[NW];
+#pragma unroll
+    for (u32 k = 0; k < NW; k++) {
+        const u32 w = tid + k * BLOCK;
+        e_at[k] = e_r[k] = e_g[k] = 0u;
+        e_ok[k] = false;
+        if (w >= TG) continue;
+        const u32 q = vw.q0 + w / n_bnd, j = view_bnd(gd, vw, w % n_bnd); // boundary j of pair q
         u32 num, den;
         bnd_fraction(j, num, den);
-        const u64 M = sM[q];
-        const u64 k = (u64)num * M / (u64)den;
-        const u64 r = (k < sMn[q]) ? sAn[q] + k : sAn[q] + sPP[q] + k;
-        trank[i] = (u32)r;
-        // first index in [0, nb2] with cum[idx] > r
-        u32 lo = 0, hi = nb2;
-        while (lo < hi) {
-            u32 mid = (lo + hi) >> 1;
-            if ((u64)cum[mid] > r)
-                hi = mid;
-            else
-                lo = mid + 1;
-        }
-        if (r >= n || lo == 0u) {
+        const u64 x = (u64)num * sM[q], kk = den == 256u ? x >> 8 : x / 12ull;
+        const u64 r = (kk < sMn[q]) ? sAn[q] + kk : sAn[q] + sPP[q] + kk;
+        e_at[k] = q * (u32)NBT + j;
+        e_ok[k] = r < n;
+        e_r[k] = (u32)(r < n ? r : 0ull);
+        trank[e_at[k]] = (u32)r;
+        if (r >= n) {
             atomicOr(&st->internal_err, 64u);
-            tb[i] = RESOLVED;
-            tk[i] = 0u;
-            continue;
+            tb[e_at[k]] = RESOLVED;
+            tk[e_at[k]] = 0u;
         }
-        const u32 bin = lo - 1u;
-        u64 res = r - (u64)cum[bin];
+    }
+#pragma unroll
+    for (u32 step = L2_BINS / 16; step > 0u; step >>= 1) { // last group of eight bins that starts at or before the rank
+#pragma unroll
+        for (u32 k = 0; k < NW; k++) e_g[k] += pre8[e_g[k] + step] <= e_r[k] ? step : 0u;
+    }
+#pragma unroll
+    for (u32 k = 0; k < NW; k++) {
+        if (!e_ok[k]) continue;
+        const u32 i = e_at[k], g = e_g[k], r = e_r[k];
+        const u32x4 x = ((const GLOBAL_AS u32x4 *)gptr(h2))[2u * g], y = ((const GLOBAL_AS u32x4 *)gptr(h2))[2u * g + 1u];
+        const u32 f[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+        u32 run = pre8[g], bin = 8u * g, res = r - run;
+#pragma unroll
+        for (u32 e = 1; e < 8u; e++) {
+            run += f[e - 1u];
+            if (run <= r) {
+                bin = 8u * g + e;
+                res = r - run;
+            }
+        }
         atomicOr(&act[bin >> 5], 1u << (bin & 31u)); // the bin holds an edge: its keys are classified one by one
         if (bin == zbin && res < n_zero) {
             tb[i] = RESOLVED;
@@ -977,53 +1142,42 @@ __global__ __launch_bounds__(BLOCK) void k_plan2(const TDesc *__restrict__ td,
         }
         if (bin == zbin) res -= n_zero;
         tb[i] = bin;
-        tr[i] = (u32)res;
-        // last 12-bit prefix whose first bin is <= bin
-        lo = 0u;
-        hi = COARSE - 1;
-        while (lo < hi) {
-            const u32 mid = (lo + hi + 1) >> 1;
-            if (((T[mid] >> 5) & 0x7fffu) <= bin)
-                lo = mid;
-            else
-                hi = mid - 1;
-        }
-        const u32 e = T[lo], dd = e & 31u, sub = bin - ((e >> 5) & 0x7fffu);
-        const u32 klo = (lo << COARSE_SHIFT) | (sub << (COARSE_SHIFT - dd));
+        tr[i] = res;
+        u32 p = 0u; // key prefix of the bin: the last one that starts at or below it
+#pragma unroll
+        for (u32 step = COARSE / 2; step > 0u; step >>= 1)
+            if (((T[p + step] >> 5) & 0x7fffu) <= bin) p += step;
+        const u32 e = T[p], dd = e & 31u, sub = bin - ((e >> 5) & 0x7fffu);
+        const u32 klo = (p << COARSE_SHIFT) | (sub << (COARSE_SHIFT - dd));
         tlo[i] = klo;
         thi[i] = klo + ((1u << (COARSE_SHIFT - dd)) - 1u);
     }
     // the bins of the class edges (first quantized / pruned / protected key of either sign) are
     // active too, so that every bin without an edge lies inside one slot
-    for (u32 i = tid; i < n_pairs * 4u; i += BLOCK) {
-        const u32 q = i >> 2;
+    for (u32 i = tid; i < vw.n_pairs * 4u; i += BLOCK) {
+        const u32 q = vw.q0 + (i >> 2);
         const u32 key = class_edge_key(i & 3u, st->thr_mag[gd->pair_p[q]], st->thr_mag[n_p + gd->pair_o[q]]);
         const u32 bin = l2_bin(key, T[key >> COARSE_SHIFT]);
         atomicOr(&act[bin >> 5], 1u << (bin & 31u));
     }
     __syncthreads();
-    // gathered population of every bin in bin order -> offset of the bin in that order (the counts are
-    // the differences of the prefix they replace; a word's difference is taken before it goes)
-    const u32 ctot = [&] {
-        for (u32 base = 0; base < nb2; base += 8u * BLOCK) { // (a row of eight per thread, then a barrier)
-            u32 c[8];
+    // gathered population of every active bin in bin order -> offset of the bin in that order
+    const u32 word = act[tid];
+    mine = 0u;
 #pragma unroll
-            for (u32 j = 0; j < 8u; j++) {
-                const u32 i = base + j * BLOCK + tid;
-                c[j] = 0u;
-                if (i < nb2 && ((act[i >> 5] >> (i & 31u)) & 1u))
-                    c[j] = cum[i + 1u] - cum[i] - ((i == zbin) ? (u32)n_zero : 0u);
-            }
-            __syncthreads();
-#pragma unroll
-            for (u32 j = 0; j < 8u; j++) {
-                const u32 i = base + j * BLOCK + tid;
-                if (i < nb2) cum[i] = c[j];
-            }
-            __syncthreads();
-        }
-        return block_excl_scan(cum, cum, (int)nb2, tmp);
-    }();
+    for (u32 i = 0; i < 32u; i++) {
+        const u32 pop = c[i >> 2][i & 3u] - (32u * tid + i == zbin ? n_zero : 0u);
+        mine += (word >> i) & 1u ? pop : 0u;
+    }
+    const u32 inc_p = wave_incl_scan(mine);
+    if (lane == 63u) tmp2[wave] = inc_p;
+    __syncthreads();
+    u32 off = inc_p - mine, ctot = 0u;
+    for (u32 w = 0; w < BLOCK / 64; w++) {
+        const u32 x = tmp2[w];
+        off += w < wave ? x : 0u;
+        ctot += x;
+    }
     if (tid == 0 && (u64)ctot > d.pool_len) atomicOr(&st->pool_overflow, 2u); // no room for the keys in group order
     // groups: runs of active bins of about 2^gshift gathered keys; at most MAX_GROUPS per tensor
     u32 gshift = GROUP_SHIFT;
@@ -1038,40 +1192,37 @@ __global__ __launch_bounds__(BLOCK) void k_plan2(const TDesc *__restrict__ td,
         gcur[g] = 0u;
     }
     __syncthreads();
-    // Every wave walks a run of bins.  The offsets of the active bins follow each other, so a group
-    // ends where the next one begins; only a wave's first and last active bin may share their group
-    // with another wave.
-    u16 *gtab = B.bin_group + (size_t)t * L2_BINS;
-    const u32 rows = (nb2 + BLOCK - 1u) / BLOCK;
-    u32 g_before = 0xFFFFFFFFu, last_end = 0u; // group of the wave's last active bin so far, where that bin ends
-    for (u32 r = 0; r < rows; r++) {
-        const u32 i = (wave * rows + r) * 64u + lane;
-        const bool in = i < nb2;
-        const bool on = in && ((act[(i < nb2 ? i : 0u) >> 5] >> (i & 31u)) & 1u);
-        const u32 off = in ? cum[i] : 0u, end = in ? cum[i + 1u] : 0u;
-        const u32 g = min(off >> gshift, n_groups - 1u); // (an empty bin at the very end)
-        const u64 m = __ballot(on);
-        if (in) {
-            binfo[i] = on ? off : INACTIVE; // offset of the bin's keys once they are in bin order
-            gtab[i] = on ? (u16)g : (u16)0xFFFFu;
-        }
-        if (!m) continue; // (the same for the whole wave)
-        const u64 below = m & ((1ull << lane) - 1ull);
-        u32 gp = (u32)__shfl((int)g, below ? 63 - (int)__clzll((long long)below) : 0);
-        if (!below) gp = g_before;
-        if (on) {
-            if (gp == 0xFFFFFFFFu) {
-                atomicMin(&goff[g], off);
-            } else if (gp != g) {
-                goff[g] = off;
-                atomicMax(&gend[gp], off);
+    // Offset and group of the thread's bins.  The offsets of the active bins follow each other, so a group
+    // ends where the next one begins; only a thread's first and last active bin may share their group
+    // with another thread.
+    GLOBAL_AS u32x4 *binfo = (GLOBAL_AS u32x4 *)gptr(B.binfo + (size_t)t * L2_BINS);
+    GLOBAL_AS u32x4 *gtab = (GLOBAL_AS u32x4 *)gptr((u32 *)(B.bin_group + (size_t)t * L2_BINS));
+    u32 gp = 0xFFFFFFFFu;
+#pragma unroll
+    for (u32 i8 = 0; i8 < 4u; i8++) { // eight bins at a time
+        u32x4 o[2], gr = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (u32 j = 0; j < 8u; j++) {
+            const u32 i = 8u * i8 + j;
+            u32 at = INACTIVE, g = 0xFFFFu;
+            if ((word >> i) & 1u) {
+                at = off;
+                g = min(off >> gshift, n_groups - 1u); // (an empty bin at the very end)
+                if (g != gp) {
+                    atomicMin(&goff[g], off);
+                    if (gp != 0xFFFFFFFFu) atomicMax(&gend[gp], off);
+                    gp = g;
+                }
+                off += c[i >> 2][i & 3u] - (32u * tid + i == zbin ? n_zero : 0u);
             }
+            o[j >> 2][j & 3u] = at;
+            gr[j >> 1] |= g << (16u * (j & 1u));
         }
-        const int last = 63 - (int)__clzll((long long)m);
-        g_before = (u32)__builtin_amdgcn_readlane((int)g, last);
-        last_end = (u32)__builtin_amdgcn_readlane((int)end, last);
+        binfo[8u * tid + 2u * i8] = o[0];
+        binfo[8u * tid + 2u * i8 + 1u] = o[1];
+        gtab[4u * tid + i8] = gr;
     }
-    if (lane == 0u && g_before != 0xFFFFFFFFu) atomicMax(&gend[g_before], last_end);
+    if (gp != 0xFFFFFFFFu) atomicMax(&gend[gp], off);
     if (tid == 0) {
         st->cand_total = ctot;
         st->n_groups = n_groups;
@@ -1140,9 +1291,7 @@ __device__ __forceinline__ void gather_tile(const float (&v)[16], u32 mask, cons
 
 constexpr int SM_GATHER = MAX_SUB * 8 + COARSE * 4 + L2_BINS * 2 + (BLOCK / 64) * 8 + MAX_FRAC * 4;
 
-__global__ __launch_bounds__(BLOCK) void k_gather(const TDesc *__restrict__ td, int nT,
-                                                  const u64 *__restrict__ wg_tile0,
-                                                  const u32 *__restrict__ wg_fu0,
+__global__ __launch_bounds__(BLOCK) void k_gather(const TDesc *__restrict__ td, const u32 *__restrict__ wg_gu0,
                                                   const GridDesc *__restrict__ gd, Bufs B)
 {
     // one static array (the only one, so it starts at LDS address 0): table offsets then fold into
@@ -1157,17 +1306,17 @@ __global__ __launch_bounds__(BLOCK) void k_gather(const TDesc *__restrict__ td, 
     u32 *s_tau_o = reinterpret_cast<u32 *>(s_red + BLOCK / 64); // [MAX_FRAC]
 
     const u32 tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const u64 tile_lo = wg_tile0[blockIdx.x], tile_hi = wg_tile0[blockIdx.x + 1];
-    if (tile_lo >= tile_hi) return;
     const u32 n_p = gd->n_p, n_o = gd->n_o;
-    int t = find_tensor(td, nT, tile_lo);
-    const int t_first = t;
-    u64 tile = tile_lo;
-    while (tile < tile_hi) {
+    for (u32 gu = wg_gu0[blockIdx.x]; gu < wg_gu0[blockIdx.x + 1]; gu++) {
+        const Unit un = B.gunits[gu];
+        const int t = (int)un.tensor;
+        const u32 view = B.view[t];
+        if (view == VIEW_NONE) { // (nothing behind this unit waits for it)
+            if (tid < BLOCK / 64) B.unit_cand[(size_t)gu * 16 + tid] = 0u;
+            continue;
+        }
+        const u32 only_o = view == VIEW_ALL ? (u32)MAX_FRAC : gd->pair_o[gd->cfg_pair[view]];
         const TDesc d = td[t];
-        const u64 n_tiles_t = (d.n + TILE - 1) / TILE;
-        const u64 t_end = d.tile0 + n_tiles_t;
-        const u64 stop = t_end < tile_hi ? t_end : tile_hi;
         TState *st = B.ts + t;
         const u32 n_slots = st->n_sub;
         {
@@ -1177,25 +1326,25 @@ __global__ __launch_bounds__(BLOCK) void k_gather(const TDesc *__restrict__ td, 
         }
         for (int i = tid; i < COARSE; i += BLOCK) T[i] = entry_for_u16(B.table2[(size_t)t * COARSE + i]);
         for (u32 i = tid; i < n_slots; i += BLOCK) sx[i] = 0ull;
-        if (tid < MAX_FRAC) s_tau_o[tid] = (tid < n_o) ? st->thr_mag[n_p + tid] : 0x7fffffffu;
+        if (tid < MAX_FRAC) // (one configuration: its protect fraction alone)
+            s_tau_o[tid] = (tid < n_o && (only_o == (u32)MAX_FRAC || tid == only_o)) ? st->thr_mag[n_p + tid] : 0x7fffffffu;
         __syncthreads();
         u32 tau_o_min = 0x7fffffffu;
         for (u32 o = 0; o < n_o; o++) tau_o_min = min(tau_o_min, s_tau_o[o]);
         // keys of active bins go, in arrival order, to a region of the pool that belongs to this
         // wave alone (the workgroup's region starts at its first element of the tensor; a wave's
         // share of it is as large as its share of the elements)
-        const u32 fu = wg_fu0[blockIdx.x] + (u32)(t - t_first);
-        const u32 capw = B.unit_capw[fu];
-        GLOBAL_AS u32 *gdst = gptr(B.pool2) + B.unit_off[fu] + (u64)wave * capw;
+        const u32 capw = un.capw;
+        GLOBAL_AS u32 *gdst = gptr(B.pool2) + un.off + (u64)wave * capw;
         u32 gathered = 0u; // wave-uniform
         bool overflow = false;
         double q_out[MAX_FRAC];
 #pragma unroll
         for (int o = 0; o < MAX_FRAC; o++) q_out[o] = 0.0;
-        for (; tile < stop; tile++) { // no barrier inside: the waves drift apart freely
+        for (u64 tile = un.tile0; tile < un.tile1; tile++) { // no barrier inside: the waves drift apart freely
             const u64 e0 = (tile - d.tile0) * (u64)TILE;
             const u64 rem = d.n - e0;
-            const u32 cnt = rem < (u64)TILE ? (u32)rem : (u32)TILE;
+            const u32 cnt = tile_len(rem, (u32)TILE);
             float v[16];
             const u32 mask = load_tile(d, e0, cnt, v);
             u32 oc[MAX_FRAC]; // protected values of this wave in this tile (wave-uniform)
@@ -1218,17 +1367,17 @@ __global__ __launch_bounds__(BLOCK) void k_gather(const TDesc *__restrict__ td, 
         __syncthreads();
         // flush partial sums of this (workgroup, tensor) unit in a fixed order
         if (lane == 0u) {
-            B.unit_cand[(size_t)fu * 16 + wave] = gathered;
+            B.unit_cand[(size_t)gu * 16 + wave] = gathered;
             if (overflow) atomicOr(&st->pool_overflow, 4u);
         }
         u64 *gs = B.mom_sx + (size_t)t * MAX_SUB; // (integers: the sum does not depend on the order)
         for (u32 i = tid; i < n_slots; i += BLOCK)
             if (sx[i]) atomicAdd((unsigned long long *)&gs[i], (unsigned long long)sx[i]);
-        double *part = B.sq_part + (size_t)fu * SQ_STRIDE;
+        double *part = B.sq_prot + (size_t)gu * MAX_FRAC;
 #pragma unroll
-        for (int o = 1; o <= MAX_FRAC; o++) {
-            if (o > (int)n_o) break;
-            double x = wave_sum_f64(q_out[o - 1]);
+        for (int o = 0; o < MAX_FRAC; o++) {
+            if (o >= (int)n_o) break;
+            double x = wave_sum_f64(q_out[o]);
             if (lane == 0u) s_red[wave] = x;
             __syncthreads();
             if (tid == 0) {
@@ -1238,7 +1387,6 @@ __global__ __launch_bounds__(BLOCK) void k_gather(const TDesc *__restrict__ td, 
             }
             __syncthreads();
         }
-        t++;
     }
 }
 
@@ -1249,8 +1397,7 @@ constexpr int SPLIT_PER = 8; // keys per thread per step
 constexpr int SPLIT_PARTS = 4; // workgroups that share one unit (they take its steps in turn)
 constexpr int STAGE_G = 1536;   // most groups of a tensor for the staged stores of the split
 
-__global__ __launch_bounds__(BLOCK) void k_split(const TDesc *__restrict__ td,
-                                                 const u32 *__restrict__ fu_tensor, Bufs B)
+__global__ __launch_bounds__(BLOCK) void k_split(const TDesc *__restrict__ td, Bufs B)
 {
     extern __shared__ u32 smem[];
     u32 *T = smem;                                   // [4096]
@@ -1258,18 +1405,19 @@ __global__ __launch_bounds__(BLOCK) void k_split(const TDesc *__restrict__ td,
     u32 *gbase = gcount + MAX_GROUPS;                // [MAX_GROUPS]
     u16 *gtab = reinterpret_cast<u16 *>(gbase + MAX_GROUPS); // [32768]
 
-    const u32 fu = blockIdx.x;
-    const int t = (int)fu_tensor[fu];
+    const u32 gu = blockIdx.x;
+    const Unit un = B.gunits[gu];
+    const int t = (int)un.tensor;
     const u32 tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const TDesc d = td[t];
     const TState *st = B.ts + t;
     // every wave splits the fragment that the same wave of the gathering sweep wrote
-    const u32 c = B.unit_cand[(size_t)fu * 16 + wave];
+    const u32 c = B.unit_cand[(size_t)gu * 16 + wave];
     u32 cmax = 0u;
-    for (int w = 0; w < BLOCK / 64; w++) cmax = max(cmax, B.unit_cand[(size_t)fu * 16 + w]);
+    for (int w = 0; w < BLOCK / 64; w++) cmax = max(cmax, B.unit_cand[(size_t)gu * 16 + w]);
     if (cmax == 0u || st->pool_overflow) return; // (an overflow: the search is repeated with larger pools)
     const u32 nb2 = st->nb2, G = st->n_groups;
-    const u32 *src = B.pool2 + B.unit_off[fu] + (u64)wave * B.unit_capw[fu];
+    const u32 *src = B.pool2 + un.off + (u64)wave * un.capw;
     u32 *dst = B.pool + d.pool_grp; // the tensor's span of the first pool, one key per slot in bin-group order
     const u32 *goff = B.grp_off + (size_t)t * MAX_GROUPS;
     u32 *gcur = B.grp_cur + (size_t)t * MAX_GROUPS;
@@ -1799,9 +1947,7 @@ __global__ __launch_bounds__(BB) void k_bucket(const TDesc *__restrict__ td, int
 // ------------------------------------------------------------------------------------------
 // launch wrappers
 // ------------------------------------------------------------------------------------------
-constexpr int SM_PLAN1 = (2 * (L1_MAGBINS + 4) + COARSE + 4) * 4;
 constexpr int SM_PLAN1B = (L2_BINS + 4) * 4;
-constexpr int SM_PLAN2 = (L2_BINS + 4 + COARSE + L2_BINS / 32) * 4;
 constexpr int SM_SPLIT = (COARSE + 2 * MAX_GROUPS) * 4 + L2_BINS * 2;
 constexpr int SM_BUCKET = (2 * BUCKET_CAP + (BB / 64) * 256) * 4;
 
@@ -1810,9 +1956,6 @@ static hipError_t set_attrs()
 {
     if (g_attr_done) return hipSuccess;
     hipError_t e;
-    if ((e = hipFuncSetAttribute((const void *)k_plan1<false>, hipFuncAttributeMaxDynamicSharedMemorySize, SM_PLAN1))) return e;
-    if ((e = hipFuncSetAttribute((const void *)k_plan1<true>, hipFuncAttributeMaxDynamicSharedMemorySize, SM_PLAN1))) return e;
-    if ((e = hipFuncSetAttribute((const void *)k_plan2, hipFuncAttributeMaxDynamicSharedMemorySize, SM_PLAN2))) return e;
     if ((e = hipFuncSetAttribute((const void *)k_plan1b, hipFuncAttributeMaxDynamicSharedMemorySize, SM_PLAN1B))) return e;
     if ((e = hipFuncSetAttribute((const void *)k_split, hipFuncAttributeMaxDynamicSharedMemorySize, SM_SPLIT))) return e;
     if ((e = hipFuncSetAttribute((const void *)k_bucket<true>, hipFuncAttributeMaxDynamicSharedMemorySize, SM_BUCKET))) return e;
@@ -1829,31 +1972,45 @@ hipError_t launch_select(const Batch &bt, hipStream_t s)
     if (bt.nB == 0) return hipSuccess; // (only small tensors)
     PROF("k_hist1", s, (k_hist<1, false><<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nB, bt.wg_tile0, bt.wg_fu0, B)));
     if (bt.any_pooled) PROF("k_pool_sum", s, k_pool_sum<<<bt.nB, BLOCK, 0, s>>>(bt.td, B));
-    PROF("k_plan1", s, k_plan1<false><<<bt.nB, BLOCK, SM_PLAN1, s>>>(bt.td, bt.gd, B));
+    PROF("k_plan1", s, k_plan1<false><<<bt.nB, BLOCK, 0, s>>>(bt.td, bt.gd, B));
     PROF("k_hist2", s, (k_hist<2, false><<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nB, bt.wg_tile0, bt.wg_fu0, B)));
     if (bt.any_sampled) {
         // tensors whose sweep 1 was sampled: exact figures from the second histogram; those whose
         // thresholds were mispredicted take the exact sweeps (the kernels skip all other tensors)
         PROF("k_plan1b", s, k_plan1b<<<bt.nB, BLOCK, SM_PLAN1B, s>>>(bt.td, bt.gd, B, bt.force_miss ? 1u : 0u));
         PROF("k_hist1_redo", s, (k_hist<1, true><<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nB, bt.wg_tile0, bt.wg_fu0, B)));
-        PROF("k_plan1_redo", s, k_plan1<true><<<bt.nB, BLOCK, SM_PLAN1, s>>>(bt.td, bt.gd, B));
+        PROF("k_plan1_redo", s, k_plan1<true><<<bt.nB, BLOCK, 0, s>>>(bt.td, bt.gd, B));
         PROF("k_hist2_redo", s, (k_hist<2, true><<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nB, bt.wg_tile0, bt.wg_fu0, B)));
     }
     PROF("k_thr_setup", s, k_thr_setup<<<bt.nB, TSEL, 0, s>>>(bt.td, B));
-    PROF("k_thr_count", s, k_thr_count<0><<<bt.n_units, TSEL, 0, s>>>(bt.td, bt.fu_tensor, B));
+    PROF("k_thr_count", s, k_thr_count<0><<<bt.n_units, TSEL, 0, s>>>(bt.td, B));
     PROF("k_thr_pick", s, k_thr_pick<0><<<bt.nB, TSEL, 0, s>>>(bt.td, B));
-    PROF("k_thr_count", s, k_thr_count<1><<<bt.n_units, TSEL, 0, s>>>(bt.td, bt.fu_tensor, B));
+    PROF("k_thr_count", s, k_thr_count<1><<<bt.n_units, TSEL, 0, s>>>(bt.td, B));
     PROF("k_thr_pick", s, k_thr_pick<1><<<bt.nB, TSEL, 0, s>>>(bt.td, B));
-    PROF("k_plan2", s, k_plan2<<<bt.nB, BLOCK, SM_PLAN2, s>>>(bt.td, bt.gd, B, bt.light));
-    if (bt.light) return hipGetLastError();
+    return hipGetLastError();
+}
+
+hipError_t launch_counts(const Batch &bt, hipStream_t s)
+{
+    if (bt.nB) PROF("k_counts", s, k_counts<<<bt.nB, 64, 0, s>>>(bt.td, bt.gd, bt.bufs));
+    return hipGetLastError();
+}
+
+hipError_t launch_resolve(const Batch &bt, hipStream_t s)
+{
+    hipError_t e = set_attrs();
+    if (e) return e;
+    const Bufs &B = bt.bufs;
+    if (bt.nB == 0) return hipSuccess;
+    PROF("k_plan2", s, k_plan2<<<bt.nB, BLOCK, 0, s>>>(bt.td, bt.gd, B, bt.n_grp_total));
     if ((e = launch_edges(bt, s))) return e;
-    PROF("k_gather", s, k_gather<<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nB, bt.wg_tile0, bt.wg_fu0, bt.gd, B));
-    PROF("k_split", s, k_split<<<dim3(bt.n_units, SPLIT_PARTS), BLOCK, SM_SPLIT, s>>>(bt.td, bt.fu_tensor, B));
+    PROF("k_gather", s, k_gather<<<bt.n_gwg, BLOCK, 0, s>>>(bt.td, bt.wg_gu0, bt.gd, B));
+    PROF("k_split", s, k_split<<<dim3(bt.n_gunits, SPLIT_PARTS), BLOCK, SM_SPLIT, s>>>(bt.td, B));
     if (bt.lds_ordered)
         PROF("k_bucket", s, k_bucket<true><<<bt.n_bucket_blocks, BB, SM_BUCKET, s>>>(bt.td, bt.nB, bt.grp_list, bt.n_grp_total, B));
     else
         PROF("k_bucket_ballots", s, k_bucket<false><<<bt.n_bucket_blocks, BB, SM_BUCKET, s>>>(bt.td, bt.nB, bt.grp_list, bt.n_grp_total, B));
-    return hipGetLastError();
+    return launch_score(bt, s);
 }
 
 } // namespace inshr

@@ -64,7 +64,6 @@ struct MagDesc {
     const float *x;
     u64 n;
     u64 chunk0; // first chunk of this tensor in the call-wide numbering
-    u32 aligned16, pad;
 };
 hipError_t launch_sketch_quantiles(const MagDesc *md, int nT, u64 n_chunks, int n_wg, const u32 *cell, const u32 *tops,
                                    const double *rep, u32 n_idx, u32 *hist, u32 *nonfinite,

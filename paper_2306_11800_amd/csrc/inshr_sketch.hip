@@ -137,7 +137,7 @@ __global__ __launch_bounds__(BLOCK) void k_sketch_hist(const TDesc *__restrict__
         for (; tile < stop; tile++) {
             const u64 e0 = (tile - d.tile0) * (u64)TILE;
             const u64 rem = d.n - e0;
-            const u32 cnt = rem < (u64)TILE ? (u32)rem : (u32)TILE;
+            const u32 cnt = tile_len(rem, (u32)TILE);
             float v[16];
             const u32 mask = load_tile(d, e0, cnt, v);
             u32 n_prot = 0u; // protected values of this wave in the tile (wave-uniform)
@@ -534,7 +534,7 @@ __global__ __launch_bounds__(BLOCK) void k_sketch_score(const TDesc *__restrict_
         for (; tile < stop; tile++) {
             const u64 e0 = (tile - d.tile0) * (u64)TILE;
             const u64 rem = d.n - e0;
-            const u32 c = rem < (u64)TILE ? (u32)rem : (u32)TILE;
+            const u32 c = tile_len(rem, (u32)TILE);
             float v[16];
             const u32 mask = load_tile(d, e0, c, v);
 #pragma unroll 4
@@ -576,7 +576,6 @@ __global__ __launch_bounds__(BLOCK) void k_sketch_score(const TDesc *__restrict_
 // where the quantizer looks for them
 __global__ __launch_bounds__(256) void k_sketch_choose(const TDesc *__restrict__ td,
                                                        const u32 *__restrict__ t_fu_off,
-                                                       const u32 *__restrict__ t_fu_ids,
                                                        const GridDesc *__restrict__ gd,
                                                        const SketchDesc *__restrict__ sd,
                                                        SketchParams P, Bufs B)
@@ -595,8 +594,8 @@ __global__ __launch_bounds__(256) void k_sketch_choose(const TDesc *__restrict__
         sumsq = 0.0;
         protsq = 0.0;
         for (u32 u = t_fu_off[t]; u < t_fu_off[t + 1]; u++) {
-            sumsq += B.sq_part[(size_t)t_fu_ids[u] * SQ_STRIDE];
-            protsq += B.sq_part[(size_t)t_fu_ids[u] * SQ_STRIDE + 1u + gd->pair_o[pair]];
+            sumsq += B.sq_part[(size_t)u * SQ_STRIDE];
+            protsq += B.sq_part[(size_t)u * SQ_STRIDE + 1u + gd->pair_o[pair]];
         }
     }
     const double not_protected = sumsq - protsq;
@@ -685,16 +684,15 @@ __global__ __launch_bounds__(BLOCK) void k_sketch_maghist(const MagDesc *__restr
         const u64 t_end = d.chunk0 + (d.n + SK_MAG_CHUNK - 1) / SK_MAG_CHUNK;
         const u64 stop = t_end < c_hi ? t_end : c_hi;
         for (; c < stop; c++) {
-            TDesc td1; // (the tile loader of the sweeps: 16-byte loads where the address allows)
+            TDesc td1; // (for the tile loader of the sweeps)
             td1.data = d.x;
             td1.n = d.n;
-            td1.aligned16 = d.aligned16;
 #pragma unroll 1
             for (u32 tl = 0; tl < (u32)SK_MAG_CHUNK / TILE; tl++) {
                 const u64 e0 = (c - d.chunk0) * (u64)SK_MAG_CHUNK + (u64)tl * TILE;
                 if (e0 >= d.n) break;
                 const u64 rem = d.n - e0;
-                const u32 cnt = rem < (u64)TILE ? (u32)rem : (u32)TILE;
+                const u32 cnt = tile_len(rem, (u32)TILE);
                 float v[16];
                 const u32 mask = load_tile(td1, e0, cnt, v);
 #pragma unroll
@@ -795,7 +793,7 @@ hipError_t launch_sketch(const Batch &bt, const SketchDesc *sd, const SketchPara
         PROF("k_sketch_score", s,
              k_sketch_score<<<bt.n_wg_all, BLOCK, 0, s>>>(bt.td, bt.nT, bt.wg_tile0_all, bt.gd, sd, P, bt.bufs));
         PROF("k_sketch_choose", s,
-             k_sketch_choose<<<bt.nT, 256, 0, s>>>(bt.td, bt.t_fu_off, bt.t_fu_ids, bt.gd, sd, P, bt.bufs));
+             k_sketch_choose<<<bt.nT, 256, 0, s>>>(bt.td, bt.t_fu_off, bt.gd, sd, P, bt.bufs));
     }
     return hipGetLastError();
 }

@@ -1,0 +1,123 @@
+"""A search that is asked for its choice alone (want_scores=False) against one that scores every
+configuration: the choice, and what the quantizer gives afterwards for the chosen configuration and for
+others of the grid, on value families at sizes that the sweeps search, at bounds that leave the choice
+open, that all and that no configuration meets."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2306_11800_amd import api, synth
+from test_gpu_fuzz import family
+from test_gpu_small import KINDS, repeated
+
+pytestmark = pytest.mark.gpu
+
+GRIDS = {
+    "full": synth.grid_full(),
+    "bins": synth.grid_paper(prune=(0.0, 0.2, 0.5), protect=(0.0, 0.005, 0.02), bins=(2, 3, 4, 6, 12, 16, 256)),
+}
+
+
+def dev(x):
+    return torch.from_numpy(x).to("cuda:0")
+
+
+def same(a, b):
+    """Integers equal, centres to 1e-6 (their sums are grouped by other edge lists)."""
+    assert len(a) == len(b)
+    for x, y in zip(a, b):
+        assert (x.n_pruned, x.n_outlier, x.n_kept, x.K) == (y.n_pruned, y.n_outlier, y.n_kept, y.K)
+        assert torch.equal(x.packed, y.packed)
+        assert torch.equal(x.boundaries[:x.K - 1].view(torch.int32), y.boundaries[:y.K - 1].view(torch.int32))
+        assert torch.equal(x.outlier_idx[:x.n_outlier], y.outlier_idx[:y.n_outlier])
+        assert torch.equal(x.outlier_val[:x.n_outlier], y.outlier_val[:y.n_outlier])
+        np.testing.assert_allclose(x.codebook[:x.K].cpu().numpy(), y.codebook[:y.K].cpu().numpy(), rtol=1e-6)
+
+
+@pytest.mark.parametrize("ordered", [True, False])
+@pytest.mark.parametrize("grid", sorted(GRIDS))
+def test_choice_alone(monkeypatch, grid, ordered):
+    monkeypatch.setenv("INSHR_NO_LDS_ORDER", "0" if ordered else "1")
+    scored, bare = api.Context(torch.device("cuda:0")), api.Context(torch.device("cuda:0"))
+    g = GRIDS[grid]
+    rng = np.random.default_rng(41)
+    sizes = [16385, 40_000, 131_073, 700_001] if ordered else [16385, 70_000]
+    xs = [family(rng, k, n) for k in range(10) for n in sizes] + [repeated(rng, k, n) for k in KINDS for n in sizes[:2]]
+    ts = [dev(x) for x in xs] + [dev(family(rng, 0, 300))]  # (and one that a workgroup searches by itself)
+    _, _, sc = scored.search(ts, g, synth.EPS_DEFAULT)
+    rel = np.array([s.sse / s.sumsq if s.sumsq else 0.0 for s in sc]).reshape(len(ts), len(g))
+    # 2e-9: below what the sums resolve; the middle configuration's own error: open for its tensor
+    for eps in [synth.EPS_DEFAULT, 1.0, 2e-9, float(np.sort(rel[0])[len(g) // 2]), float(np.sort(rel[7])[len(g) // 4])]:
+        want = scored.search(ts, g, eps)
+        got = bare.search(ts, g, eps, want_scores=False)
+        near = np.abs(rel - eps) <= 4e-6 * eps + 1e-12  # (an error that rounds to the bound may fall on either side)
+        for t in range(len(ts)):
+            if not near[t].any() and eps > 1e-8:
+                assert (got[0][t], got[1][t]) == (want[0][t], want[1][t]), (t, eps)
+        for cfgs in ([g[b] for b in want[0]], [g[(7 * t + 3) % len(g)] for t in range(len(ts))]):
+            same(bare.quantize(ts, cfgs, reuse_search=True), scored.quantize(ts, cfgs, reuse_search=True))
+    scored.close()
+    bare.close()
+
+
+def test_shares_of_the_pool_grow_in_the_quantizer(monkeypatch):
+    """One value makes up most of the tensor and holds boundaries: all its keys are gathered."""
+    rng = np.random.default_rng(42)
+    x = repeated(rng, "run", 400_000)
+    y = np.where(rng.random(400_000) < 0.8, np.float32(0.25), x).astype(np.float32)
+    ts = [dev(y), dev(family(rng, 0, 50_000))]
+    want = api.Context(torch.device("cuda:0"))
+    b, _, _ = want.search(ts, GRIDS["full"], 0.01)
+    monkeypatch.setenv("INSHR_POOL_WCAP", "1")
+    small = api.Context(torch.device("cuda:0"))
+    b2, _, _ = small.search(ts, GRIDS["full"], 0.01, want_scores=False)
+    assert list(b) == list(b2)
+    cfgs = [GRIDS["full"][k] for k in b]
+    same(small.quantize(ts, cfgs, reuse_search=True), want.quantize(ts, cfgs, reuse_search=True))
+    same(small.quantize(ts, cfgs), want.quantize(ts, cfgs, reuse_search=True))
+    want.close()
+    small.close()
+
+
+def test_pooled_choice_and_sketch_on_top(monkeypatch):
+    """Thresholds per group without scores; the sketch quantizer reuses a search that only chose."""
+    rng = np.random.default_rng(43)
+    ts = [dev(family(rng, k, n)) for k, n in [(0, 90_000), (0, 30_001), (9, 50_000), (9, 900)]]
+    ctx, bare = api.Context(torch.device("cuda:0")), api.Context(torch.device("cuda:0"))
+    groups = [0, 0, 1, 1]
+    want = ctx.search(ts, GRIDS["full"], 0.01, groups=groups)
+    got = bare.search(ts, GRIDS["full"], 0.01, want_scores=False, groups=groups)
+    assert list(want[0]) == list(got[0]) and list(want[1]) == list(got[1])
+    # (a member's share of the protected values is not bounded by the fraction: a configuration without any)
+    cfg = [(4, 200_000, 0)] * len(ts)
+    same(bare.quantize(ts, cfg, reuse_search=True), ctx.quantize(ts, cfg, reuse_search=True))
+    u = rng.uniform(size=(len(ts), 256))
+    cfgs = [(8, 200_000, 1000)] * len(ts)
+    a = ctx.search(ts, GRIDS["full"], 0.01) and ctx.search_sketch(ts, cfgs, u, 0.01, reuse_search=True)
+    b = bare.search(ts, GRIDS["full"], 0.01, want_scores=False) and bare.search_sketch(ts, cfgs, u, 0.01, reuse_search=True)
+    same(a[0], b[0])
+    np.testing.assert_allclose([c["sse"] for c in a[1]], [c["sse"] for c in b[1]], rtol=1e-6, atol=1e-12)
+    ctx.close()
+    bare.close()
+
+
+@pytest.mark.parametrize("off", [1, 2, 3])
+def test_slices_that_start_anywhere(off):
+    """16-byte loads from tensors that are aligned to 4 bytes only: the same as from aligned copies."""
+    rng = np.random.default_rng(44)
+    sizes = [16_384 + off, 24_576, 90_000 + off]  # (a tile of the sweeps is a multiple of 4096)
+    flat = dev(family(rng, 1, 262_144))
+    cuts = [flat[k * 65_536 + off:][:n] for k, n in enumerate(sizes)]
+    assert all(t.data_ptr() % 16 == 4 * off for t in cuts)
+    copies = [t.clone() for t in cuts]
+    a, b = api.Context(torch.device("cuda:0")), api.Context(torch.device("cuda:0"))
+    for want_scores in (True, False):
+        ra, rb = (c.search(ts, GRIDS["full"], 0.01, want_scores=want_scores) for c, ts in ((a, cuts), (b, copies)))
+        assert list(ra[0]) == list(rb[0]) and list(ra[1]) == list(rb[1])
+        cfgs = [GRIDS["full"][k] for k in ra[0]]
+        same(a.quantize(cuts, cfgs, reuse_search=True), b.quantize(copies, cfgs, reuse_search=True))
+    u = rng.uniform(size=(len(cuts), 256))
+    cfgs = [(8, 200_000, 1000)] * len(cuts)
+    same(a.search_sketch(cuts, cfgs, u, 0.01)[0], b.search_sketch(copies, cfgs, u, 0.01)[0])
+    a.close()
+    b.close()
