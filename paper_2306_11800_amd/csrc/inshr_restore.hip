@@ -2,7 +2,7 @@
 // 2 + b gives the centre of bin b, and the elements with symbol 1 take their original values from
 // the protected list.
 //
-//   k_dequant            workgroups of 256 threads (eight per CU) walk runs of tiles of 16384 elements:
+//   k_dequant            workgroups of 256 threads (seven per CU) walk runs of tiles of 16384 elements:
 //                        the tile's packed words (asked for one tile ahead) and the codebook are
 //                        staged in LDS, every thread decodes 4 consecutive elements at a time and
 //                        stores them as one 16-byte piece, 16 pieces per tile.  Waiting for the next
@@ -31,12 +31,43 @@ __device__ __forceinline__ int find_rdesc(const RDesc *rd, int nT, u64 tile)
 constexpr int DQ_BLOCK = 256;
 constexpr int DQ_TILE = DEQUANT_TILE; // 64 elements per thread
 constexpr int DQ_ROUNDS = DQ_TILE / (4 * DQ_BLOCK);
+constexpr int DQ_PRE = (DQ_TILE * 9 / 128 + DQ_BLOCK - 1) / DQ_BLOCK; // 16-byte pieces of packed words per thread and tile
+typedef u32 dq_u4 __attribute__((ext_vector_type(4)));
+// device memory: 16 bytes at any 4-byte (words: 8-byte) address
+typedef u32 dq_u4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef float dq_f4_any __attribute__((ext_vector_type(4), aligned(4)));
 
-__global__ __launch_bounds__(DQ_BLOCK) void k_dequant(const RDesc *__restrict__ rd, int nT, u64 n_tiles,
-                                                      u32 *__restrict__ flags, u32 *__restrict__ ones)
+// 4 symbols of w bits from bit off of the words on, as values; their largest enters s_max, the number of those
+// that are 1 comes back (the same for the whole wave).  Symbols at index `left` and above are no elements.
+template <bool FULL>
+__device__ __forceinline__ u32 decode4(const u32 *W, const float *value, u32 off, u32 w, u32 left, u32 &s_max, float (&x)[4])
 {
-    __shared__ u32 W[((DQ_TILE * 9 / 32 + DQ_BLOCK - 1) / DQ_BLOCK) * DQ_BLOCK + 4];
-    __shared__ float cb[256];
+    const u32 wd = off >> 5, mask = (1u << w) - 1u;
+    const u32 a = W[wd], b = W[wd + 1u], c = W[wd + 2u];
+    const u32 lo = __builtin_amdgcn_alignbit(b, a, off & 31u), hi = __builtin_amdgcn_alignbit(c, b, off & 31u);
+    // (three symbols are at most 27 bits)
+    const u32 sym[4] = {lo & mask, (lo >> w) & mask, (lo >> (2u * w)) & mask, __builtin_amdgcn_alignbit(hi, lo, 3u * w) & mask};
+    u32 ones = 0u;
+#pragma unroll
+    for (u32 k = 0; k < 4u; k++) {
+        const bool valid = FULL || k < left;
+        ones += (u32)__popcll(__ballot(valid && sym[k] == 1u));
+        s_max = valid && sym[k] > s_max ? sym[k] : s_max;
+        x[k] = value[sym[k]];
+    }
+    return ones;
+}
+
+// Bound by memory, as far as the seven workgroups of a CU keep requests in flight: the rounds of a tile are unrolled four at a time, so that
+// a thread gets by with 72 registers (all sixteen at once took 197, two workgroups per CU: 1.06 G elements
+// 1.52 ms, 1.05 ms so, 5.2 GB: 4.9 TB/s).  The value table holds zeros for the symbols that have no centre,
+// so a symbol is one read of it and no comparison.
+__global__ __launch_bounds__(DQ_BLOCK, 7) void k_dequant(const RDesc *__restrict__ rd, int nT, u64 n_tiles,
+                                                         u32 *__restrict__ flags, u32 *__restrict__ ones)
+{
+    __shared__ __attribute__((aligned(16))) u32 W[DQ_PRE * DQ_BLOCK * 4];
+    static_assert(DQ_TILE * 9 / 32 + 2 < DQ_PRE * DQ_BLOCK * 4, "two words past the last symbol's first");
+    __shared__ float value[512]; // of every symbol that 9 bits can hold
     const u32 tid = threadIdx.x;
     // every workgroup takes a run of consecutive tiles: the tensor of the first is searched for, the
     // others follow from it
@@ -45,75 +76,69 @@ __global__ __launch_bounds__(DQ_BLOCK) void k_dequant(const RDesc *__restrict__ 
     const u64 tile_hi = tile_lo + per < n_tiles ? tile_lo + per : n_tiles;
     if (tile_lo >= tile_hi) return;
     int t = __builtin_amdgcn_readfirstlane(find_rdesc(rd, nT, tile_lo));
-    int t_cb = -1; // tensor whose codebook is in LDS
-    u32 bad = 0u;
-    constexpr int PRE = (DQ_TILE * 9 / 32 + DQ_BLOCK - 1) / DQ_BLOCK; // dwords per thread and tile
-    u32 pre[PRE]; // the next tile's packed words, asked for one tile ahead
+    int t_value = -1; // tensor whose values are in LDS
+    bool bad = false;
+    dq_u4 pre[DQ_PRE]; // the next tile's packed words, asked for one tile ahead
     auto fetch = [&](int tt, u64 tile) {
-        const RDesc d = rd[tt];
+        const RDesc &d = rd[tt];
         const u64 e0 = (tile - d.tile0) * DQ_TILE;
         const u32 cnt = tile_len(d.n - e0, (u32)DQ_TILE);
         const u32 nd = 2u * ((cnt * d.w + 63u) >> 6); // dwords of the tile, all inside the packed array
         const GLOBAL_AS u32 *src = (const GLOBAL_AS u32 *)(gptr(d.packed) + e0 * d.w / 64u);
 #pragma unroll
-        for (int j = 0; j < PRE; j++) {
-            const u32 k = tid + (u32)DQ_BLOCK * j;
-            pre[j] = k < nd ? src[k] : 0u;
+        for (int j = 0; j < DQ_PRE; j++) {
+            const u32 k = 4u * (tid + (u32)DQ_BLOCK * j);
+            pre[j] = {0u, 0u, 0u, 0u};
+            if (k + 4u <= nd) {
+                pre[j] = *(const GLOBAL_AS dq_u4_any *)(src + k);
+            } else if (k < nd) { // (an even number of dwords)
+                pre[j].x = src[k];
+                pre[j].y = src[k + 1u];
+            }
         }
     };
     fetch(t, tile_lo);
     for (u64 tile = tile_lo; tile < tile_hi; tile++) {
-        const RDesc d = rd[t];
-        const u64 e0 = (tile - d.tile0) * DQ_TILE;
-        const u32 cnt = tile_len(d.n - e0, (u32)DQ_TILE);
-        const u32 w = d.w, K = d.K;
+        const int t_now = t;
+        const u64 e0 = (tile - rd[t].tile0) * DQ_TILE;
+        const u32 cnt = tile_len(rd[t].n - e0, (u32)DQ_TILE);
+        const u32 w = rd[t].w, K = rd[t].K;
+        GLOBAL_AS float *dst = gptr(rd[t].dst) + e0;
         __syncthreads(); // the previous tile has been decoded
 #pragma unroll
-        for (int j = 0; j < PRE; j++) W[tid + (u32)DQ_BLOCK * j] = pre[j]; // zero past the tile's words
-        if (t != t_cb) {
-            if (tid < 256u) cb[tid] = tid < K ? gptr(d.codebook)[tid] : 0.0f;
-            t_cb = t;
+        for (int j = 0; j < DQ_PRE; j++) ((dq_u4 *)W)[tid + (u32)DQ_BLOCK * j] = pre[j]; // zero past the tile's words
+        if (t != t_value) {
+            for (u32 s = tid; s < 512u; s += DQ_BLOCK) value[s] = s >= 2u && s < K + 2u ? gptr(rd[t].codebook)[s - 2u] : 0.0f;
+            t_value = t;
         }
         __syncthreads();
-        const int t_now = t;
         if (tile + 1 < tile_hi) {
             while (t + 1 < nT && rd[t + 1].tile0 <= tile + 1) t++;
             fetch(t, tile + 1);
         }
-        GLOBAL_AS float *dst = gptr(d.dst) + e0;
-        const bool vec = cnt == (u32)DQ_TILE && ((((u64)dst) & 15u) == 0u);
-        const u32 mask = (1u << w) - 1u;
-        u32 n_one = 0u;
-#pragma unroll
-        for (u32 j = 0; j < (u32)DQ_ROUNDS; j++) {
-            const u32 i0 = 4u * (tid + (u32)DQ_BLOCK * j);
-            // four symbols are 4 w <= 36 bits from bit i0 * w on
-            const u32 off = i0 * w, wd = off >> 5, sh = off & 31u;
-            const u64 lo = ((u64)W[wd + 1] << 32) | (u64)W[wd];
-            const u64 bits = (lo >> sh) | (sh ? ((u64)W[wd + 2] << (64u - sh)) : 0ull);
-            float x[4];
-#pragma unroll
-            for (u32 c = 0; c < 4u; c++) {
-                const u32 sym = (u32)(bits >> (c * w)) & mask;
-                const bool valid = i0 + c < cnt;
-                n_one += (u32)__popcll(__ballot(valid && sym == 1u));
-                if (valid && sym >= K + 2u) bad = 1u;
-                const u32 b = sym - 2u;
-                x[c] = (sym >= 2u && b < K) ? cb[b] : 0.0f;
+        u32 n_one = 0u, s_max = 0u;
+        if (cnt == (u32)DQ_TILE) {
+#pragma unroll 4
+            for (u32 j = 0; j < (u32)DQ_ROUNDS; j++) {
+                const u32 i0 = 4u * (tid + (u32)DQ_BLOCK * j);
+                float x[4];
+                n_one += decode4<true>(W, value, i0 * w, w, 4u, s_max, x);
+                *(GLOBAL_AS dq_f4_any *)(dst + i0) = {x[0], x[1], x[2], x[3]};
             }
-            if (vec) {
-                typedef float f4 __attribute__((ext_vector_type(4)));
-                f4 q = {x[0], x[1], x[2], x[3]};
-                ((GLOBAL_AS f4 *)dst)[tid + (u32)DQ_BLOCK * j] = q;
-            } else {
+        } else {
+            for (u32 r0 = 0; r0 < cnt; r0 += 4u * DQ_BLOCK) {
+                const u32 i0 = r0 + 4u * tid;
+                float x[4];
+                n_one += decode4<false>(W, value, i0 * w, w, i0 < cnt ? cnt - i0 : 0u, s_max, x);
 #pragma unroll
                 for (u32 c = 0; c < 4u; c++)
                     if (i0 + c < cnt) dst[i0 + c] = x[c];
             }
         }
+        bad |= s_max >= K + 2u;
         if ((tid & 63u) == 0u && n_one) atomicAdd(&ones[t_now], n_one);
     }
-    if (__ballot(bad != 0u) && (tid & 63u) == 0u) atomicOr(flags, RF_SYMBOL);
+    if (__ballot(bad) && (tid & 63u) == 0u) atomicOr(flags, RF_SYMBOL);
 }
 
 __global__ __launch_bounds__(256) void k_dequant_protected(const RDesc *__restrict__ rd,
@@ -146,7 +171,9 @@ __global__ __launch_bounds__(256) void k_dequant_protected(const RDesc *__restri
 hipError_t launch_dequantize(const RDesc *rd, int nT, u64 n_tiles, u64 max_outlier, u32 *flags,
                              u32 *ones, int n_cu, hipStream_t s)
 {
-    u64 grid = (u64)n_cu * 64u; // 8 resident workgroups per CU, 8 rounds
+    // the workgroups that are resident together, each with one run of tiles (more and shorter runs end with a
+    // round that is partly empty, and each starts without words asked for ahead: 8 rounds 1.26, 2 rounds 1.21 ms)
+    u64 grid = (u64)n_cu * 7u;
     if (grid > n_tiles) grid = n_tiles;
     PROF("k_dequant", s, k_dequant<<<(unsigned)grid, DQ_BLOCK, 0, s>>>(rd, nT, n_tiles, flags, ones));
     u64 blocks = (max_outlier + 255u) / 256u;

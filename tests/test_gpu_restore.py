@@ -57,6 +57,23 @@ def test_dequantize_matches_the_oracle(ctx):
             assert np.array_equal(got.cpu().numpy().view(np.uint32), want.view(np.uint32)), (cfg, x.size)
 
 
+@pytest.mark.parametrize("bits", [1, 2, 5, 7, 8])  # symbols of 2 to 9 bits
+def test_dequantize_into_slices(ctx, bits):
+    """Outputs that start anywhere (whole tiles are stored 16 bytes at a time); what lies around a slice stays."""
+    rng = np.random.default_rng(bits)
+    for n in (3, 16383, 16384, 16385, 3 * 16384 + 5):
+        x = (0.02 * rng.standard_t(4, n)).astype(np.float32)
+        t = [dev(x)] * 4
+        qs = ctx.quantize(t, [(bits, 100000, 1000)] * 4)
+        buf = [torch.full((n + 8,), 7.0, device="cuda:0") for _ in t]
+        ctx.dequantize(qs, out=[b[k:k + n] for k, b in enumerate(buf)])
+        r = ref.quantize(x, (bits, 100000, 1000))
+        for k, (q, b) in enumerate(zip(qs, buf)):
+            want = np.full(n + 8, 7.0, np.float32)
+            want[k:k + n] = ref.dequantize(r["sym"], bits, q.codebook.cpu().numpy(), r["outlier_idx"], r["outlier_val"])
+            assert np.array_equal(b.cpu().numpy().view(np.uint32), want.view(np.uint32)), (n, k)
+
+
 def test_dequantized_error_is_the_searched_score(ctx):
     prev, _ = synth.config0(seed=33, n=1_500_001)
     grid = synth.grid_small()
