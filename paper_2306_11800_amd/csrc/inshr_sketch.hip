@@ -190,13 +190,13 @@ __global__ __launch_bounds__(BLOCK) void k_sketch_kmeans(const GridDesc *__restr
 {
     __shared__ u32 s_u32[BLOCK / 64 + 2];
     __shared__ double s_red[2 * (BLOCK / 64)];
-    __shared__ double cen[256], craw[256];
-    __shared__ u32 seg[257], seg_prev[257];
-    __shared__ u32 s_pick[2], s_last[2], s_changed, s_chosen;
+    __shared__ double cen[512], craw[256]; // the sorted centres of every set, those of 2 << (set + 1) from 4 * (2 ^ set - 1)
+    __shared__ u32 seg[512 + SK_SETS];     // first buckets of the clusters, [clusters] = m
+    __shared__ u32 s_max[BLOCK / 64], s_pick[2], s_last[2], s_changed[SK_SETS], s_live, s_chosen;
     const int t = blockIdx.x;
     const SketchDesc s = sd[t];
     if (!s.active) return;
-    const u32 tid = threadIdx.x, lane = tid & 63u;
+    const u32 tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // one set of centres for the configuration's bits, or (P.multi) one for each of 2 .. 8 bits: the
     // draws of a narrower set are the first draws of the widest
     const u32 K = P.multi ? 256u : 1u << gd->cfg_bits[s.cfg];
@@ -222,168 +222,192 @@ __global__ __launch_bounds__(BLOCK) void k_sketch_kmeans(const GridDesc *__restr
         cmax = y > cmax ? y : cmax;
     }
     if (lane == 63u) s_u32[tid >> 6] = inc;
-    if (lane == 0u) seg_prev[tid >> 6] = cmax; // (scratch until the Lloyd rounds)
+    if (lane == 0u) s_max[tid >> 6] = cmax;
     __syncthreads();
     u32 base = 0u, m = 0u, maxc = 0u;
     for (u32 wv = 0; wv < BLOCK / 64; wv++) {
         const u32 y = s_u32[wv];
         if (wv < (tid >> 6)) base += y;
         m += y;
-        maxc = seg_prev[wv] > maxc ? seg_prev[wv] : maxc;
+        maxc = s_max[wv] > maxc ? s_max[wv] : maxc;
     }
-    const bool fits = m <= (u32)SK_LDS;
-    double *xq = fits ? l_x : P.xq + (size_t)t * SK_HIST;
-    double *w = fits ? l_w : P.w + (size_t)t * SK_HIST;
-    double *dist = fits ? l_d : P.d + (size_t)t * SK_HIST;
-    u32 pos = base + inc - mine;
-    for (u32 i = 0; i < PER; i++) {
-        const u32 v = tid * PER + i;
-        const u32 slot = slot_in_value_order(v < (u32)SK_HIST ? v : 0u);
-        const u32 c = v < (u32)SK_HIST ? h[slot] : 0u;
-        if (c) {
-            xq[pos] = slot_value(slot, P);
-            w[pos] = (double)c; // the count, replaced by the weight below
-            pos++;
-        }
-    }
-    __syncthreads();
-    if (m == 0u) { // (cannot happen: at least one value lies between the thresholds)
-        if (tid == 0) {
-            P.info[t].n_buckets = 0u;
-            P.info[t].rounds = 0u;
-        }
-        return;
-    }
-    // ---- sample weights (Algorithm 2): sigma * C / max C + (1 - sigma) * |X| / max |X| ----
-    const double x_first = fabs(xq[0]), x_last = fabs(xq[m - 1u]);
-    const double mx = x_first > x_last ? x_first : x_last;
-    const double one_minus = sub_rn(1.0, P.sigma);
-    __syncthreads();
-    for (u32 i = tid; i < m; i += BLOCK) {
-        const double c_hat = div_rn(w[i], (double)maxc);
-        const double x_hat = mx > 0.0 ? div_rn(fabs(xq[i]), mx) : 0.0;
-        w[i] = add_rn(mul_rn(P.sigma, c_hat), mul_rn(one_minus, x_hat));
-    }
-    __syncthreads();
-
-    // ---- weighted K-Means++ draws (Algorithm 3) ----
-    const u32 per = (m + BLOCK - 1u) / BLOCK;
-    const u32 lo = tid * per < m ? tid * per : m, hi = lo + per < m ? lo + per : m;
-    double *uni = cen; // the draws' random numbers (the sorted centres take this array afterwards)
-    if (tid < 256u) uni[tid] = P.uniforms[(size_t)t * 256 + tid];
-    if (tid < 2u) {
-        s_pick[tid] = 0xFFFFFFFFu;
-        s_last[tid] = 0u;
-    }
-    __syncthreads();
-    // Per draw: (1) every thread sums the probabilities of its share, a wave scan gives the running
-    // sums inside the wave, the wave totals go to LDS; (2) every thread adds the totals of the
-    // waves before its own (in wave order) and the first thread whose running sum exceeds the
-    // target announces itself; (3) that thread walks its share.  With at most one bucket per
-    // thread (the rule) step 3 is empty.  The LDS cells alternate between two copies from draw to
-    // draw, so that a draw never waits for the cells of the one before to be read.
-    for (u32 r = 0; r < K; r++) {
-        const u32 cp = r & 1u;
-        double sum = 0.0;
-        u32 last_pos = 0u; // last bucket of the share that could be drawn, + 1
-        for (u32 i = lo; i < hi; i++) {
-            const double p = r ? mul_rn(dist[i], w[i]) : w[i];
-            sum = add_rn(sum, p);
-            if (p > 0.0) last_pos = i + 1u;
-        }
-        double inc = sum;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const double y = __shfl_up(inc, o);
-            if ((int)lane >= o) inc = add_rn(inc, y);
-        }
-        const double before = __shfl_up(inc, 1); // inclusive value of the lane below
-        if (lane == 63u) s_red[cp * (BLOCK / 64) + (tid >> 6)] = inc;
-        __syncthreads();
-        double wbase = 0.0, total = 0.0;
-        for (u32 wv = 0; wv < BLOCK / 64; wv++) {
-            if (wv == (tid >> 6)) wbase = total;
-            total = add_rn(total, s_red[cp * (BLOCK / 64) + wv]);
-        }
-        if (r > 0u && !(total > 0.0)) { // every bucket is a centre already: repeat the last one
-            if (tid == 0) craw[r] = craw[r - 1u];
-            continue; // (nothing of this draw's cells is used again before two more barriers)
-        }
-        const double target = mul_rn(uni[r], total);
-        const double excl = lane ? add_rn(wbase, before) : wbase;
-        const double incl = add_rn(wbase, inc);
-        // one atomic per wave: its first lane above the target, its last lane with a drawable bucket
-        const u64 above = __ballot(incl > target), drawable = __ballot(last_pos != 0u);
-        if (above && lane == (u32)__builtin_ctzll(above)) atomicMin(&s_pick[cp], tid);
-        if (drawable && lane == 63u - (u32)__builtin_clzll(drawable)) atomicMax(&s_last[cp], last_pos);
-        __syncthreads();
-        const u32 pick = s_pick[cp];
-        u32 j;
-        if (per == 1u) {
-            // no running sum exceeds the target (rounding): the last bucket that could be drawn
-            j = pick != 0xFFFFFFFFu ? pick : (s_last[cp] ? s_last[cp] - 1u : 0u);
-            if (tid == 0) {
-                craw[r] = xq[j];
-                s_pick[cp ^ 1u] = 0xFFFFFFFFu;
-                s_last[cp ^ 1u] = 0u;
+    // the rest, for bucket lists in LDS or in device memory
+    auto cluster = [&](auto *xq, auto *w, auto *dist) {
+        u32 pos = base + inc - mine;
+        for (u32 i = 0; i < PER; i++) {
+            const u32 v = tid * PER + i;
+            const u32 slot = slot_in_value_order(v < (u32)SK_HIST ? v : 0u);
+            const u32 c = v < (u32)SK_HIST ? h[slot] : 0u;
+            if (c) {
+                xq[pos] = slot_value(slot, P);
+                w[pos] = (double)c; // the count, replaced by the weight below
+                pos++;
             }
-        } else {
-            if (tid == (pick == 0xFFFFFFFFu ? 0u : pick)) {
-                u32 jj = s_last[cp] ? s_last[cp] - 1u : 0u;
-                if (pick != 0xFFFFFFFFu) {
-                    double run = excl; // the running sum at the start of this thread's share
-                    jj = last_pos ? last_pos - 1u : lo;
+        }
+        __syncthreads();
+        if (m == 0u) { // (cannot happen: at least one value lies between the thresholds)
+            if (tid == 0) {
+                P.info[t].n_buckets = 0u;
+                P.info[t].rounds = 0u;
+            }
+            return;
+        }
+        // ---- sample weights (Algorithm 2): sigma * C / max C + (1 - sigma) * |X| / max |X| ----
+        const double x_first = fabs(xq[0]), x_last = fabs(xq[m - 1u]);
+        const double mx = x_first > x_last ? x_first : x_last;
+        const double one_minus = sub_rn(1.0, P.sigma);
+        __syncthreads();
+        for (u32 i = tid; i < m; i += BLOCK) {
+            const double c_hat = div_rn(w[i], (double)maxc);
+            const double x_hat = mx > 0.0 ? div_rn(fabs(xq[i]), mx) : 0.0;
+            w[i] = add_rn(mul_rn(P.sigma, c_hat), mul_rn(one_minus, x_hat));
+        }
+        __syncthreads();
+
+        // ---- weighted K-Means++ draws (Algorithm 3) ----
+        const u32 per = (m + BLOCK - 1u) / BLOCK;
+        const u32 lo = tid * per < m ? tid * per : m, hi = lo + per < m ? lo + per : m;
+        double *uni = cen; // the draws' random numbers (the sorted centres take this array afterwards)
+        if (tid < 256u) uni[tid] = P.uniforms[(size_t)t * 256 + tid];
+        if (tid < 2u) {
+            s_pick[tid] = 0xFFFFFFFFu;
+            s_last[tid] = 0u;
+        }
+        __syncthreads();
+        // Per draw: (1) every thread sums the probabilities of its share, a wave scan gives the running
+        // sums inside the wave, the wave totals go to LDS; (2) every thread adds the totals of the
+        // waves before its own (in wave order) and the first thread whose running sum exceeds the
+        // target announces itself; (3) that thread walks its share.  With at most one bucket per
+        // thread (the rule) step 3 is empty.  The LDS cells alternate between two copies from draw to
+        // draw, so that a draw never waits for the cells of the one before to be read.
+        // Waves without buckets only take part in the barriers (their sums are zero, and whatever they would find,
+        // the last bucket's thread finds too).  With one bucket per thread its value, weight and distance
+        // are registers.
+        const bool one = per == 1u;
+        const u32 n_act = (m + per * 64u - 1u) / (per * 64u);
+        double x1 = 0.0, w1 = 0.0, d1 = 0.0;
+        if (one && tid < m) {
+            x1 = xq[tid];
+            w1 = w[tid];
+        }
+        for (u32 r = 0; r < K; r++) {
+            const u32 cp = r & 1u;
+            double inc = 0.0, before = 0.0;
+            u32 last_pos = 0u; // last bucket of the share that could be drawn, + 1
+            if (wave < n_act) {
+                if (one) {
+                    inc = r ? mul_rn(d1, w1) : w1;
+                    last_pos = inc > 0.0 ? tid + 1u : 0u;
+                } else {
                     for (u32 i = lo; i < hi; i++) {
-                        run = add_rn(run, r ? mul_rn(dist[i], w[i]) : w[i]);
-                        if (run > target) {
-                            jj = i;
-                            break;
-                        }
+                        const double p = r ? mul_rn(dist[i], w[i]) : w[i];
+                        inc = add_rn(inc, p);
+                        if (p > 0.0) last_pos = i + 1u;
                     }
                 }
-                s_chosen = jj;
-                craw[r] = xq[jj];
-                s_pick[cp ^ 1u] = 0xFFFFFFFFu;
-                s_last[cp ^ 1u] = 0u;
+#pragma unroll
+                for (int o = 1; o < 64; o <<= 1) {
+                    const double y = __shfl_up(inc, o);
+                    if ((int)lane >= o) inc = add_rn(inc, y);
+                }
+                before = __shfl_up(inc, 1); // inclusive value of the lane below
+                if (lane == 63u) s_red[cp * (BLOCK / 64) + wave] = inc;
             }
             __syncthreads();
-            j = s_chosen;
+            double wbase = 0.0, total = 0.0;
+            for (u32 wv = 0; wv < n_act; wv++) {
+                if (wv == wave) wbase = total;
+                total = add_rn(total, s_red[cp * (BLOCK / 64) + wv]);
+            }
+            if (r > 0u && !(total > 0.0)) { // every bucket is a centre already: repeat the last one
+                if (tid == 0) craw[r] = craw[r - 1u];
+                continue; // (nothing of this draw's cells is used again before two more barriers)
+            }
+            const double target = mul_rn(uni[r], total);
+            const double excl = lane ? add_rn(wbase, before) : wbase;
+            if (wave < n_act) { // one atomic per wave: its first lane above the target, its last lane with a drawable bucket
+                const double incl = add_rn(wbase, inc);
+                const u64 above = __ballot(incl > target && lo < hi), drawable = __ballot(last_pos != 0u);
+                if (above && lane == (u32)__builtin_ctzll(above)) atomicMin(&s_pick[cp], tid);
+                if (drawable && lane == 63u - (u32)__builtin_clzll(drawable)) atomicMax(&s_last[cp], last_pos);
+            }
+            __syncthreads();
+            const u32 pick = s_pick[cp];
+            u32 j;
+            if (one) {
+                // no running sum exceeds the target (rounding): the last bucket that could be drawn
+                j = pick != 0xFFFFFFFFu ? pick : (s_last[cp] ? s_last[cp] - 1u : 0u);
+                if (tid == 0) {
+                    craw[r] = xq[j];
+                    s_pick[cp ^ 1u] = 0xFFFFFFFFu;
+                    s_last[cp ^ 1u] = 0u;
+                }
+                const double df = sub_rn(x1, xq[j]);
+                const double d2 = mul_rn(df, df);
+                d1 = (r == 0u || d2 < d1) ? d2 : d1;
+            } else {
+                if (tid == (pick == 0xFFFFFFFFu ? 0u : pick)) {
+                    u32 jj = s_last[cp] ? s_last[cp] - 1u : 0u;
+                    if (pick != 0xFFFFFFFFu) {
+                        double run = excl; // the running sum at the start of this thread's share
+                        jj = last_pos ? last_pos - 1u : lo;
+                        for (u32 i = lo; i < hi; i++) {
+                            run = add_rn(run, r ? mul_rn(dist[i], w[i]) : w[i]);
+                            if (run > target) {
+                                jj = i;
+                                break;
+                            }
+                        }
+                    }
+                    s_chosen = jj;
+                    craw[r] = xq[jj];
+                    s_pick[cp ^ 1u] = 0xFFFFFFFFu;
+                    s_last[cp ^ 1u] = 0u;
+                }
+                __syncthreads();
+                j = s_chosen;
+                const double cj = xq[j];
+                for (u32 i = lo; i < hi; i++) {
+                    const double df = sub_rn(xq[i], cj);
+                    const double d2 = mul_rn(df, df);
+                    dist[i] = (r == 0u || d2 < dist[i]) ? d2 : dist[i];
+                }
+            }
         }
-        const double cj = xq[j];
-        for (u32 i = lo; i < hi; i++) {
-            const double df = sub_rn(xq[i], cj);
-            const double d2 = mul_rn(df, df);
-            dist[i] = (r == 0u || d2 < dist[i]) ? d2 : dist[i];
-        }
-    }
-    __syncthreads();
-    u32 rounds = 0u;
-    for (u32 set = 0; set < n_sets; set++) {
-        const u32 bits = P.multi ? 2u + set : gd->cfg_bits[s.cfg];
-        const u32 Kb = 1u << bits;
-        // ---- sort the centres ----
         __syncthreads();
-        if (tid < Kb) {
-            const double x = craw[tid];
-            u32 rank = 0u;
+        // ---- the sets of centres, all at once: the widest takes the first waves, a cluster per thread --------------
+        // (one after the other, each with a few rounds of bisection and of sums by few threads, they took half of the
+        // kernel's 1.17 ms for 74 tensors; 0.59 ms so)
+        u32 set = n_sets - 1u, j0 = 0u; // this wave's set; its first thread
+        while (set > 0u && wave * 64u >= j0 + (4u << set)) j0 += ((4u << set) + 63u) & ~63u, set--;
+        const u32 bits = P.multi ? 2u + set : gd->cfg_bits[s.cfg], Kb = 1u << bits, k = tid - j0;
+        const bool mine_k = k < Kb; // (threads past the last set's: none)
+        double *c_set = cen + (P.multi ? (4u << set) - 4u : 0u);
+        u32 *seg_set = seg + (P.multi ? (4u << set) - 4u + set : 0u);
+        double c_raw = 0.0;
+        u32 rank = 0u;
+        if (mine_k) {
+            c_raw = craw[k];
             for (u32 i = 0; i < Kb; i++) {
                 const double y = craw[i];
-                rank += (y < x || (y == x && i < tid)) ? 1u : 0u;
+                rank += (y < c_raw || (y == c_raw && i < k)) ? 1u : 0u;
             }
-            cen[rank] = x;
+        }
+        if (tid < (u32)SK_SETS) s_changed[tid] = 0u;
+        if (tid == 0u) s_live = n_sets;
+        if (mine_k) { // (the draws' random numbers, which this array held, have been used)
+            c_set[rank] = c_raw;
+            if (k == 0u) seg_set[Kb] = m;
         }
         __syncthreads();
-        // ---- weighted Lloyd rounds: cluster j = buckets (mid[j-1], mid[j]] ----
-        rounds = 0u;
+        // weighted Lloyd rounds: cluster k = buckets (mid[k-1], mid[k]]; a set whose clusters stay as they are is done
+        u32 rounds = 0u, first_prev = 0u;
+        bool busy = mine_k;
         for (u32 it = 0; it < P.max_iter; it++) {
-            if (tid == 0) s_changed = (it == 0u) ? 1u : 0u;
-            __syncthreads();
-            if (tid <= Kb) {
-                u32 first = 0u;
-                if (tid == Kb) {
-                    first = m;
-                } else if (tid > 0u) {
-                    const double mid = mul_rn(add_rn(cen[tid - 1u], cen[tid]), 0.5);
+            u32 first = 0u;
+            if (busy) {
+                if (k > 0u) {
+                    const double mid = mul_rn(add_rn(c_set[k - 1u], c_set[k]), 0.5);
                     u32 a = 0u, b = m; // first bucket above the midpoint
                     while (a < b) {
                         const u32 c = (a + b) >> 1;
@@ -394,48 +418,73 @@ __global__ __launch_bounds__(BLOCK) void k_sketch_kmeans(const GridDesc *__restr
                     }
                     first = a;
                 }
-                seg[tid] = first;
-                if (it > 0u && seg_prev[tid] != first) s_changed = 1u;
+                seg_set[k] = first;
+                if (it == 0u || first_prev != first) s_changed[set] = it + 1u;
+                first_prev = first;
             }
             __syncthreads();
-            if (!s_changed) break;
-            if (tid < Kb) {
+            if (busy && s_changed[set] != it + 1u) {
+                busy = false;
+                if (k == 0u) atomicSub(&s_live, 1u);
+            }
+            if (busy) {
                 double sw = 0.0, swx = 0.0;
-                for (u32 i = seg[tid]; i < seg[tid + 1u]; i++) {
+                const u32 end = seg_set[k + 1u];
+                u32 i = first;
+                for (; i + 8u <= end; i += 8u) { // (eight reads in flight, added in order)
+                    double wi[8], xi[8];
+#pragma unroll
+                    for (u32 q = 0; q < 8u; q++) {
+                        wi[q] = w[i + q];
+                        xi[q] = xq[i + q];
+                    }
+#pragma unroll
+                    for (u32 q = 0; q < 8u; q++) {
+                        sw = add_rn(sw, wi[q]);
+                        swx = add_rn(swx, mul_rn(wi[q], xi[q]));
+                    }
+                }
+                for (; i < end; i++) {
                     sw = add_rn(sw, w[i]);
                     swx = add_rn(swx, mul_rn(w[i], xq[i]));
                 }
-                if (sw > 0.0) cen[tid] = div_rn(swx, sw);
+                if (sw > 0.0) c_set[k] = div_rn(swx, sw);
+                rounds++;
             }
-            if (tid <= Kb) seg_prev[tid] = seg[tid];
-            rounds++;
             __syncthreads();
+            if (!s_live) break; // (changes between the next two barriers only)
+        }
+        // ---- codebooks and boundaries ----
+        const u32 sh = 8u - bits;
+        u32 *ak = P.alt_key + (size_t)t * n_sets * 256;
+        float *acb = P.alt_cb + (size_t)t * n_sets * 256;
+        for (u32 i = tid; i < n_sets * 256u; i += BLOCK) {
+            ak[i] = 0u;
+            acb[i] = 0.0f;
         }
         __syncthreads();
-        // ---- codebook and boundaries ----
-        const u32 sh = 8u - bits;
-        u32 *ak = P.alt_key + ((size_t)t * n_sets + set) * 256;
-        float *acb = P.alt_cb + ((size_t)t * n_sets + set) * 256;
-        if (tid < 256u) ak[tid] = 0u;
-        __syncthreads();
-        if (tid < Kb) {
-            acb[tid] = __double2float_rn(cen[tid]);
-            if (tid + 1u < Kb) {
-                const double a = (double)__double2float_rn(cen[tid]), b = (double)__double2float_rn(cen[tid + 1u]);
+        if (mine_k) {
+            ak += set * 256u;
+            acb += set * 256u;
+            acb[k] = __double2float_rn(c_set[k]);
+            if (k + 1u < Kb) {
+                const double a = (double)__double2float_rn(c_set[k]), b = (double)__double2float_rn(c_set[k + 1u]);
                 const double mid = mul_rn(add_rn(a, b), 0.5);
                 // a value goes to the upper centre when it lies strictly above the midpoint: the
                 // boundary is the smallest fp32 number above it
-                ak[((tid + 1u) << sh) - 1u] = key_of_float(__double2float_rd(mid)) + 1u;
+                ak[((k + 1u) << sh) - 1u] = key_of_float(__double2float_rd(mid)) + 1u;
             }
-        } else if (tid < 256u) {
-            acb[tid] = 0.0f;
+            if (k == 0u && P.multi) P.set_rounds[(size_t)t * SK_SETS + set] = rounds;
         }
-        if (tid == 0 && P.multi) P.set_rounds[(size_t)t * SK_SETS + set] = rounds;
-    }
-    if (tid == 0) {
-        P.info[t].n_buckets = m;
-        P.info[t].rounds = rounds;
-    }
+        if (tid == 0) { // (the widest set's thread)
+            P.info[t].n_buckets = m;
+            P.info[t].rounds = rounds;
+        }
+    };
+    if (m <= (u32)SK_LDS)
+        cluster(l_x, l_w, l_d);
+    else
+        cluster(gptr(P.xq) + (size_t)t * SK_HIST, gptr(P.w) + (size_t)t * SK_HIST, gptr(P.d) + (size_t)t * SK_HIST);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -572,6 +621,8 @@ __global__ __launch_bounds__(BLOCK) void k_sketch_score(const TDesc *__restrict_
     }
 }
 
+// (bound by latency: the slots' shares by all threads, then added in slot order by a thread per set from LDS; a
+// thread per set that walked the slots in device memory took 0.25 ms, 0.02 ms so)
 // per tensor: error of every set, the fewest bits within eps, and that set's keys and centres
 // where the quantizer looks for them
 __global__ __launch_bounds__(256) void k_sketch_choose(const TDesc *__restrict__ td,
@@ -580,7 +631,10 @@ __global__ __launch_bounds__(256) void k_sketch_choose(const TDesc *__restrict__
                                                        const SketchDesc *__restrict__ sd,
                                                        SketchParams P, Bufs B)
 {
-    __shared__ double s_sse[SK_SETS];
+    constexpr int N = SK_EDGES + 1;
+    __shared__ double s_sse[SK_SETS], s_sq[256], s_prot[256];
+    __shared__ double term[SK_SETS][N]; // what a slot takes off a set's error
+    __shared__ u32 top[SK_SETS][256];   // largest of a set's boundaries up to each
     __shared__ u32 s_best;
     const int t = blockIdx.x;
     const SketchDesc s = sd[t];
@@ -593,34 +647,59 @@ __global__ __launch_bounds__(256) void k_sketch_choose(const TDesc *__restrict__
     if (P.light) { // no scoring kernel has added the units' parts up
         sumsq = 0.0;
         protsq = 0.0;
-        for (u32 u = t_fu_off[t]; u < t_fu_off[t + 1]; u++) {
-            sumsq += B.sq_part[(size_t)u * SQ_STRIDE];
-            protsq += B.sq_part[(size_t)u * SQ_STRIDE + 1u + gd->pair_o[pair]];
+        for (u32 u0 = t_fu_off[t], u1 = t_fu_off[t + 1]; u0 < u1; u0 += 256u) { // 256 read together, added in order
+            const u32 k = u1 - u0 < 256u ? u1 - u0 : 256u;
+            if (tid < k) {
+                s_sq[tid] = B.sq_part[(size_t)(u0 + tid) * SQ_STRIDE];
+                s_prot[tid] = B.sq_part[(size_t)(u0 + tid) * SQ_STRIDE + 1u + gd->pair_o[pair]];
+            }
+            __syncthreads();
+            for (u32 i = 0; i < k; i++) {
+                sumsq += s_sq[i];
+                protsq += s_prot[i];
+            }
+            __syncthreads();
         }
     }
     const double not_protected = sumsq - protsq;
     const u32 *gc = P.slot_cnt + (size_t)t * SK_SLOTS;
     const double *gx = P.slot_sx + (size_t)t * SK_SLOTS;
     const u32 *edge = P.slot_edge + (size_t)t * SK_SLOTS;
-    if (tid < (u32)SK_SETS) {
-        const u32 set = tid, bits = 2u + set, Kb = 1u << bits, sh = 8u - bits;
+    const u32 lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    for (u32 set = wave; set < (u32)SK_SETS; set += 4u) { // a wave per set
+        const u32 Kb = 4u << set, sh = 6u - set;
         const u32 *ak = P.alt_key + ((size_t)t * SK_SETS + set) * 256;
-        const float *acb = P.alt_cb + ((size_t)t * SK_SETS + set) * 256;
-        double gain = 0.0;
-        u32 cluster = 0u; // of the current slot: boundaries of this set at or below the slot's keys
-        for (u32 slot = 0; slot <= (u32)SK_EDGES; slot++) {
-            if (slot > 0u) { // the slot starts at edge[slot - 1]
-                const u32 first = edge[slot - 1u];
-                while (cluster + 1u < Kb && ak[((cluster + 1u) << sh) - 1u] <= first) cluster++;
-            }
-            const u32 n = gc[slot];
-            if (n) {
-                const double c = (double)acb[cluster];
-                gain += 2.0 * c * gx[slot] - (double)n * c * c;
-            }
+        u32 before = 0u;
+        for (u32 k = lane; k - lane < Kb; k += 64u) {
+            const u32 y = wave_incl_max(k > 0u && k < Kb ? ak[(k << sh) - 1u] : 0u);
+            const u32 m = y > before ? y : before;
+            if (k < Kb) top[set][k] = m;
+            before = (u32)__builtin_amdgcn_readlane((int)m, 63);
         }
+    }
+    __syncthreads();
+    for (u32 slot = tid; slot < (u32)N; slot += 256u) {
+        const u32 n = gc[slot], first = slot ? edge[slot - 1u] : 0u; // the slot starts at edge[slot - 1]
+        const double x = gx[slot];
+#pragma unroll
+        for (u32 set = 0; set < (u32)SK_SETS; set++) {
+            const float *acb = P.alt_cb + ((size_t)t * SK_SETS + set) * 256;
+            u32 cluster = 0u; // of the slot: boundaries of this set at or below the slot's keys
+            if (slot)
+#pragma unroll
+                for (u32 step = 2u << set; step > 0u; step >>= 1)
+                    if (top[set][cluster + step] <= first) cluster += step;
+            const double c = (double)acb[cluster];
+            term[set][slot] = n ? 2.0 * c * x - (double)n * c * c : 0.0;
+        }
+    }
+    __syncthreads();
+    if (tid < (u32)SK_SETS) {
+        double gain = 0.0;
+#pragma unroll 8
+        for (int slot = 0; slot < N; slot++) gain += term[tid][slot];
         const double sse = not_protected - gain;
-        s_sse[set] = sse > 0.0 ? sse : 0.0;
+        s_sse[tid] = sse > 0.0 ? sse : 0.0;
     }
     __syncthreads();
     if (tid == 0) {

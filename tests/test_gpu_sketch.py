@@ -164,6 +164,20 @@ def test_search_over_bits(ctx):
                  reuse_grid=grid)
 
 
+@pytest.mark.parametrize("m", [1, 63, 64, 65, 257, 1023, 1024, 1025, 4096, 4097])
+def test_search_over_bits_with_so_many_buckets(ctx, m):
+    """Bucket lists at the edges of a wave, of one bucket per thread and of LDS."""
+    rng = np.random.default_rng(m)
+    gamma = 1.01 / 0.99
+    mag = 1e-12 * gamma ** (np.arange(m) // 2 + 0.5)
+    x = np.where(np.arange(m) % 2 == 0, mag, -mag)
+    x = rng.permutation(np.repeat(x, rng.integers(1, 4, m))).astype(np.float32)
+    check_search(ctx, [x, x[:1]], [(0, 0, 0), (0, 0, 0)], 1e-3, 0.01, 0.2, 100, 30 + m)
+    base = ref.quantize(x, (8, 0, 0))
+    got = sk.quantize_values(x, base["sym"], 256, 0.01, 0.2, rng.uniform(size=256), 1)["n_buckets"]
+    assert got == m
+
+
 def test_stand_alone_state_is_not_offered_for_reuse(ctx):
     """Stand-alone sketch calls search for thresholds and counts only; an equal-frequency quantize
     that asks for the state of the last search must then be refused."""
