@@ -20,7 +20,8 @@ struct QuantShared {
 };
 
 // How the symbol of a key is found.  BINS: the search's equal-population bins; building the table
-// of 32768 bins costs a workgroup about 40 us, so it is for long runs of tiles.  CELLS: cells of the
+// of 32768 bins takes a walk over 32 bins per thread (with a search per bin a workgroup needed about 40 us; 355 M values in
+// 292 tensors 0.73 -> 0.65 ms), so it is for long runs of tiles.  CELLS: cells of the
 // key's upper 14 bits, each with its first breakpoint and their number (a dozen of them in the
 // densest cells: a few bisection steps); the table takes 4 us.
 constexpr int Q_BINS = 0, Q_CELLS = 1;
@@ -30,7 +31,7 @@ constexpr u32 CELL_MANY = 63u; // number field of a cell: this many or more
 
 template <bool FULL, int MODE>
 __device__ __forceinline__ void classify_tile(const float (&v)[16], u32 mask, const u32 *T,
-                                              const u16 *symt, const QuantTables &qt, u32 n_bp, u32 w,
+                                              const u16 *symt, const QuantTables &qt, u32 n_bp, u32 zero_slot, u32 w,
                                               unsigned long long *pk, u32 *wcnt, u32 &omask,
                                               u32 (&pre)[4])
 {
@@ -54,7 +55,9 @@ __device__ __forceinline__ void classify_tile(const float (&v)[16], u32 mask, co
             u32 sym = e[c];
             if (sym & 0x8000u) { // the bin holds breakpoints: count those at or below the key
                 u32 s;
-                if (MODE == Q_BINS) {
+                if (key[c] == ZERO_KEY) { // (checkpoints of sparse updates are mostly zeros, with many a boundary there)
+                    s = zero_slot;
+                } else if (MODE == Q_BINS) {
                     s = sym & 0x7fffu;
                     if (qt.bp[s] <= key[c]) { // (the bin's first breakpoint exists: s < n_bp)
                         s++;
@@ -263,25 +266,43 @@ __global__ __launch_bounds__(BLOCK) void k_quant(const TDesc *__restrict__ td, c
                 s = e;
             }
         }
-        for (u32 b = cells ? nb2 : tid; b < nb2; b += BLOCK) { // symbol of every bin, or its first breakpoint
-            u32 lo = 0u, hi = COARSE - 1u; // key prefix of the bin: last one that starts at or below it
+        constexpr u32 PER_BINS = L2_BINS / BLOCK;
+        if (!cells && tid * PER_BINS < nb2) { // symbol of every bin, or its first breakpoint: 32 bins in a row
+            u32 lo = 0u, hi = COARSE - 1u; // key prefix of the first one: last one that starts at or below it
             while (lo < hi) {
                 const u32 mid = (lo + hi + 1u) >> 1;
-                if ((T[mid] >> 6) <= b)
+                if ((T[mid] >> 6) <= tid * PER_BINS)
                     lo = mid;
                 else
                     hi = mid - 1u;
             }
-            const u32 e = T[lo], dd = e & 31u, sub = b - (e >> 6);
-            const u32 first = (lo << COARSE_SHIFT) | (sub << (COARSE_SHIFT - dd));
-            const u32 last = first + ((1u << (COARSE_SHIFT - dd)) - 1u);
-            u32 below = 0u, upto = 0u; // breakpoints < first, breakpoints <= last
-            for (u32 step = 256u; step > 0u; step >>= 1) {
-                if (below + step <= n_bp && qt.bp[below + step - 1u] < first) below += step;
-                if (upto + step <= n_bp && qt.bp[upto + step - 1u] <= last) upto += step;
+            u32 e = T[lo], sub = tid * PER_BINS - (e >> 6);
+            const u32 start = (lo << COARSE_SHIFT) | (sub << (COARSE_SHIFT - (e & 31u)));
+            u32 s = start ? slot_of_key(qt.bp, n_bp, start - 1u) : 0u; // breakpoints in lower bins
+            u32 next = qt.bp[s], sym = qt.symtab[s], row[PER_BINS / 2];
+#pragma unroll
+            for (u32 i = 0; i < PER_BINS; i++) { // (entries past the last bin are not looked at)
+                const u32 dd = e & 31u;
+                const u32 last = (lo << COARSE_SHIFT) | (sub << (COARSE_SHIFT - dd)) | ((1u << (COARSE_SHIFT - dd)) - 1u);
+                u32 x = sym;
+                if (s < n_bp && next <= last) {
+                    x = 0x8000u | s;
+                    if (qt.bp[++s] <= last) s = slot_of_key(qt.bp, n_bp, last); // (many equal values in one bin)
+                    next = qt.bp[s];
+                    sym = qt.symtab[s];
+                }
+                row[i >> 1] = (i & 1u) ? row[i >> 1] | (x << 16) : x;
+                if (++sub >> dd) {
+                    sub = 0u;
+                    lo = lo + 1u < (u32)COARSE ? lo + 1u : lo;
+                    e = T[lo];
+                }
             }
-            symt[b] = (below == upto) ? qt.symtab[below] : (u16)(0x8000u | below);
+            typedef u32 u4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+            for (u32 i = 0; i < PER_BINS / 8; i++) ((u4 *)symt)[tid * (PER_BINS / 8) + i] = {row[4 * i], row[4 * i + 1], row[4 * i + 2], row[4 * i + 3]};
         }
+        const u32 zero_slot = __builtin_amdgcn_readfirstlane(slot_of_key(qt.bp, n_bp, ZERO_KEY));
         __syncthreads();
         GLOBAL_AS unsigned long long *packed = gptr(q.packed);
         auto tile_cnt = [&](u64 tl) -> u32 {
@@ -369,14 +390,14 @@ __global__ __launch_bounds__(BLOCK) void k_quant(const TDesc *__restrict__ td, c
             // (whole tile or not is the same for every lane: the tile code uses ballots)
             if (cells) {
                 if (cnt == (u32)TILE)
-                    classify_tile<true, Q_CELLS>(v, mask, T, symt, qt, n_bp, w, pkb, qt.wcnt[buf], omask, pre);
+                    classify_tile<true, Q_CELLS>(v, mask, T, symt, qt, n_bp, zero_slot, w, pkb, qt.wcnt[buf], omask, pre);
                 else
-                    classify_tile<false, Q_CELLS>(v, mask, T, symt, qt, n_bp, w, pkb, qt.wcnt[buf], omask, pre);
+                    classify_tile<false, Q_CELLS>(v, mask, T, symt, qt, n_bp, zero_slot, w, pkb, qt.wcnt[buf], omask, pre);
             } else {
                 if (cnt == (u32)TILE)
-                    classify_tile<true, Q_BINS>(v, mask, T, symt, qt, n_bp, w, pkb, qt.wcnt[buf], omask, pre);
+                    classify_tile<true, Q_BINS>(v, mask, T, symt, qt, n_bp, zero_slot, w, pkb, qt.wcnt[buf], omask, pre);
                 else
-                    classify_tile<false, Q_BINS>(v, mask, T, symt, qt, n_bp, w, pkb, qt.wcnt[buf], omask, pre);
+                    classify_tile<false, Q_BINS>(v, mask, T, symt, qt, n_bp, zero_slot, w, pkb, qt.wcnt[buf], omask, pre);
             }
             __syncthreads();
 #pragma unroll
