@@ -17,8 +17,8 @@
 //   k_fprot    protected values: the sweep's lists, one per wave -> the tensor's list in index order
 //   k_fhead    per tensor: centres, boundaries, class counts
 //
-// 6.7 G values in 3 bits, 0.5 % protected: k_fuse 10.9 ms (27 GB read, 2.5 GB written: 2.7 TB/s; bound by its LDS
-// accesses, three per value with the sum's add, and the wave's instructions between them), k_fsplit 0.35,
+// 6.7 G values, symbols of 9 bits: k_fuse 10.9 ms (27 GB read, 7.6 GB written: 3.2 TB/s; bound by its dependent
+// LDS accesses, two per value and the sum's add, and the wave's instructions between them), k_fsplit 0.34,
 // k_fsel 0.25, k_fpatch 0.42, k_fprot 0.37; boundaries, centres and k_quant for one configuration took
 // 8.7 (k_gather) + 0.6 + 8.9 (k_quant).  100 M values in 48 tensors: 0.28 ms where k_plan2 .. k_quant took 0.70.
 //
