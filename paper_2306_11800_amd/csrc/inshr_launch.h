@@ -92,6 +92,7 @@ struct Batch {
     int n_gwg, n_gunits; // workgroups and units of sweep 3
     int n_bucket_blocks;
     bool lds_ordered;    // same-address LDS atomics return in lane order on this device
+    bool choose;         // the search ends with k_decide
     bool light;          // thresholds and class counts only: no boundaries, no scores (the sketch
                          // quantizer brings its own bins)
     bool any_sampled;    // some tensor's sweep 1 is sampled
