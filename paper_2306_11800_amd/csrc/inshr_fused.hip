@@ -685,13 +685,13 @@ constexpr u32 SEL_ROWS = 16;
 __global__ __launch_bounds__(64 * SEL_WAVES) void k_fsel(const GridDesc *__restrict__ gd, const QDesc *__restrict__ qd, Bufs B)
 {
     __shared__ u32 hist[SEL_WAVES][256];
-    const int t = blockIdx.y;
+    const int t = blockIdx.x; // (a grid's second dimension ends at 65535)
     const QDesc q = qd[t];
     if (!q.fused) return;
     TState *st = B.ts + t;
     if (st->fuse_bad) return;
     const u32 lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const u32 j = blockIdx.x * SEL_WAVES + wave, K = gd->cfg_K[q.cfg];
+    const u32 j = blockIdx.y * SEL_WAVES + wave, K = gd->cfg_K[q.cfg];
     if (j >= K - 1u) return; // (no barrier below)
     const u32 u = B.tgt_bin[(size_t)t * TGT_STRIDE + j];
     if (u == RESOLVED) return;
@@ -980,7 +980,7 @@ hipError_t launch_fused(const Batch &bt, const QDesc *qd, QInfo *qi, hipStream_t
     PROF("k_fplan", s, k_fplan<<<bt.nB, BLOCK, 0, s>>>(bt.td, bt.gd, qd, B));
     PROF("k_fuse", s, k_fuse<<<bt.n_gwg, BLOCK, 0, s>>>(bt.td, bt.wg_gu0, bt.gd, qd, B));
     PROF("k_fsplit", s, k_fsplit<<<dim3(bt.n_gunits, FS_PARTS), BLOCK, 0, s>>>(qd, B));
-    PROF("k_fsel", s, k_fsel<<<dim3(256 / SEL_WAVES, bt.nB), 64 * SEL_WAVES, 0, s>>>(bt.gd, qd, B));
+    PROF("k_fsel", s, k_fsel<<<dim3(bt.nB, 256 / SEL_WAVES), 64 * SEL_WAVES, 0, s>>>(bt.gd, qd, B));
     PROF("k_fpatch", s, k_fpatch<<<dim3(bt.n_gunits, FP_PARTS), BLOCK, 0, s>>>(bt.gd, qd, B));
     PROF("k_fprot", s, k_fprot<<<bt.n_gunits, BLOCK, 0, s>>>(bt.td, bt.t_gu_off, qd, B));
     PROF("k_fhead", s, k_fhead<<<bt.nB, BLOCK, 0, s>>>(bt.gd, bt.t_gu_off, qd, qi, B));

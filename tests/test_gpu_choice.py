@@ -121,3 +121,30 @@ def test_slices_that_start_anywhere(off):
     same(a.search_sketch(cuts, cfgs, u, 0.01)[0], b.search_sketch(copies, cfgs, u, 0.01)[0])
     a.close()
     b.close()
+
+
+def test_more_tensors_than_a_grid_dimension():
+    """More tensors for the sweeps than the second and third dimension of a grid hold (65535), one call with one
+    configuration: every tensor is quantized as by itself."""
+    n, n_t, kinds, cfg = 16_385, 65_540, 64, (4, 200_000, 1000)
+    flat = dev(family(np.random.default_rng(45), 1, n + kinds))
+    ctx = api.Context(torch.device("cuda:0"))
+    want = [ctx.quantize([flat[k:k + n]], [cfg])[0] for k in range(kinds)]
+    rows = dict(packed=(-(-n * api.symbol_bits(16) // 64), torch.int64), codebook=(256, torch.float32),
+                boundaries=(255, torch.float32), outlier_idx=(n // 1000 + 1, torch.int32),
+                outlier_val=(n // 1000 + 1, torch.float32))
+    bufs = {k: torch.zeros(n_t, w, dtype=t, device="cuda:0") for k, (w, t) in rows.items()}
+    out = [api.Quantized(n, 4, b) for b in zip(*(b.unbind(0) for b in bufs.values()))]
+    cuts = [flat[k:k + n] for k in range(kinds)]
+    got = ctx.quantize([cuts[t % kinds] for t in range(n_t)], [cfg] * n_t, out=out)
+    assert len({(q.n_pruned, q.n_outlier, q.n_kept) for q in got[::kinds]}) == 1
+    for k, w in enumerate(want):
+        assert (got[k].n_pruned, got[k].n_outlier, got[k].n_kept) == (w.n_pruned, w.n_outlier, w.n_kept)
+        for name in rows:
+            x = getattr(w, name)
+            part = bufs[name][k::kinds, :x.numel()]
+            if name == "codebook":  # (its sums are exact integers: equal too)
+                assert torch.equal(part, x.expand_as(part)), k
+            else:
+                assert torch.equal(part.view(torch.int32), x.view(torch.int32).expand(part.shape[0], -1)), (name, k)
+    ctx.close()
