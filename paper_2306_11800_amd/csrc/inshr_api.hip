@@ -319,7 +319,7 @@ void deal_tiles(const std::vector<TDesc> &td, uint32_t nB, const std::vector<u32
             Unit u;
             u.tile0 = (u32)(td[ts[k]].tile0 + (at - done));
             u.tile1 = (u32)(td[ts[k]].tile0 + (end - done));
-            u.off = p.pool;
+            u.off16 = (u32)(p.pool / (BLOCK / 64));
             u.capw = (u32)std::min((end - at) * per_wave, (end - at) * (u64)wcap + per_wave);
             u.tensor = ts[k];
             p.t_off[u.tensor + 1]++;
@@ -534,7 +534,7 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         const u64 pool = part.pool;
         for (u32 u = units; u-- > 0;) { // a tensor's span of the pool: its units'
             TDesc &d = td[part.units[u].tensor];
-            d.pool_grp = part.units[u].off;
+            d.pool_grp = part.units[u].off();
             d.pool_len += (u64)part.units[u].capw * (BLOCK / 64);
         }
         c->pool_len = pool;
@@ -551,7 +551,8 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         const size_t up_bytes = cv.off;
         const size_t o_ts = cv.take(sizeof(TState) * nT);
         const size_t o_h1 = cv.off; // once the thresholds stand, the first histogram makes room for ...
-        cv.take(((size_t)n_wg + nB) * 16 * 4); // ... counts and sums of the gather units and ...
+        cv.take(((size_t)n_wg + nB) * 16 * 4); // ... counts and sums of the gather units (unit_prot, sq_prot), ...
+        const size_t o_uc = cv.take(((size_t)n_wg + nB) * 16 * 4); // ... the keys they gathered (unit_cand) and ...
         c->view_off = cv.take(sizeof(u32) * nB); // ... what upload_units writes
         c->gw_off = cv.take(nB ? sizeof(u32) * (n_wg + 1) : 0);
         c->tgo_off = cv.take(nB ? sizeof(u32) * (nB + 1) : 0);
@@ -589,7 +590,6 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         const size_t o_sbn = cv.take(full((size_t)nB * MAX_SUB * 4));
         const size_t o_cb = cv.take(full((size_t)nT * n_cfg * CB_STRIDE * 4));
         const size_t o_sc = cv.take(full((size_t)nT * n_cfg * sizeof(Score)));
-        const size_t o_uc = cv.take(full(((size_t)n_wg + nB) * 16 * 4));
         const size_t o_bg = cv.take(full((size_t)nB * L2_BINS * 2));
         const size_t o_go = cv.take(full((size_t)nB * MAX_GROUPS * 4));
         const size_t o_ge = cv.take(full((size_t)nB * MAX_GROUPS * 4));
@@ -1063,8 +1063,8 @@ static int quantize_with_state(inshr_ctx *c, const inshr_config *cfg, inshr_quan
         for (u32 t : fuse) {
             const u32 u0 = p.t_off[t], u1 = p.t_off[t + 1];
             qd[t].fused = 1u;
-            qd[t].span = p.units[u0].off;
-            qd[t].span_len = p.units[u1 - 1].off + (u64)p.units[u1 - 1].capw * (BLOCK / 64) - qd[t].span;
+            qd[t].span = p.units[u0].off();
+            qd[t].span_len = p.units[u1 - 1].off() + (u64)p.units[u1 - 1].capw * (BLOCK / 64) - qd[t].span;
         }
         Partition pq;
         deal_tiles(c->td, nB, ready, c->batch.n_wg, c->wcap, pq);

@@ -224,6 +224,7 @@ struct TState {
     u32 internal_err;
     u32 pool_overflow;                 // a wave's share of a gather pool, or the tensor's span for the keys
                                        // in group order, was too small: the search is repeated with larger pools
+    u32 fuse_bad;                      // the fused quantizer's means do not hold this tensor and configuration
     u64 n_neg, n_zero;                 // strictly negative values; exact zeros (after -0 -> +0)
     // thresholds: index t < n_p is the prune threshold of p_ppm[t], t >= n_p the protect
     // threshold of o_ppm[t - n_p]
@@ -269,11 +270,11 @@ struct TState {
     double sumsq;                      // sum of x^2
     double thr_sumsq[MAX_THR];         // prune: sum x^2 over mag < tau; protect: over mag > tau
     u32 best, feasible;
-    u32 fuse_bad;                      // the fused quantizer's means do not hold this tensor and configuration
 };
 
 struct SearchResult {    // what the host reads of a tensor's state
-    u32 nonfinite, internal_err, pool_overflow, redo, best, feasible, fuse_bad;
+    u32 nonfinite, internal_err, pool_overflow, redo, best;
+    u16 feasible, fuse_bad;
     u32 thr_mag[MAX_THR];
 };
 // by the last kernel that works on the tensor, after a barrier behind its own changes of the state
@@ -287,8 +288,8 @@ __device__ __forceinline__ void store_result(TState *st, SearchResult *res)
     r.pool_overflow = rd(&st->pool_overflow);
     r.redo = rd(&st->redo);
     r.best = st->best;
-    r.feasible = st->feasible;
-    r.fuse_bad = rd(&st->fuse_bad);
+    r.feasible = (u16)st->feasible;
+    r.fuse_bad = (u16)rd(&st->fuse_bad);
     for (int i = 0; i < MAX_THR; i++) r.thr_mag[i] = st->thr_mag[i];
     *res = r;
 }

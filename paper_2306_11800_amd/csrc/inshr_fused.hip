@@ -54,13 +54,13 @@ __device__ __forceinline__ ProtLists prot_lists(const Unit &un, u64 span)
 {
     ProtLists p;
     const u64 tiles = un.tile1 - un.tile0;
-    p.counts = span + (un.off - span) / 2u;
+    p.counts = span + (un.off() - span) / 2u;
     p.list = p.counts + tiles * F_TILEW;
     p.cap = (u32)((8ull * un.capw - tiles * F_TILEW) / 16u); // (a share has room for at least 136 keys per tile)
     return p;
 }
 // Values listed by wave w of a unit: keys and indices, each in one half of its share of the second pool.
-__device__ __forceinline__ u32 *open_keys(const Bufs &B, const Unit &un, u32 w) { return B.pool2 + un.off + (u64)w * un.capw; }
+__device__ __forceinline__ u32 *open_keys(const Bufs &B, const Unit &un, u32 w) { return B.pool2 + un.off() + (u64)w * un.capw; }
 __device__ __forceinline__ u32 open_cap(const Unit &un) { return un.capw / 2u; }
 
 // ------------------------------------------------------------------------------------------

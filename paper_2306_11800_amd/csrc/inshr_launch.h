@@ -10,10 +10,11 @@ constexpr int SEL_WORDS = MAX_THR * 1024;    // a tensor's selection histograms 
 constexpr int CB_STRIDE = 256;              // codebook entries per configuration
 
 struct Unit {       // the tiles of one tensor that one workgroup of a sweep walks
-    u64 off;          // the unit's share of the sweep's gather pool (u32 units): wave w owns
+    u32 off16;        // the unit's share of the sweep's gather pool (u32 units, off() = 16 * off16): wave w owns
     u32 capw;         // [off + w * capw, off + (w + 1) * capw)
     u32 tile0, tile1; // batch-wide tile numbers
     u32 tensor;
+    __host__ __device__ u64 off() const { return 16ull * off16; } // (a share is BLOCK / 64 = 16 times capw long)
 };
 
 // Which configurations of the grid the boundaries, centres and errors of a tensor are worked out for
@@ -40,7 +41,7 @@ struct Bufs { // device pointers, indexed by the tensor's position on the device
     u32 *pool;      // first gather pool: the keys of the threshold windows (sweep 2), wave-private shares;
                     // afterwards every tensor's keys of active bins in bin-group order (TDesc::pool_grp)
     u32 *pool2;     // second gather pool, same layout: the keys of active bins as sweep 3 gathers them
-    u32 *unit_cand; // [gather units][16] active-bin keys each wave of the unit gathered
+    u32 *unit_cand; // [gather units][16] active-bin keys each wave of the unit gathered (in hist1, read no more)
     u32 *unit_prot; // [gather units][16] protected values each wave listed (fused; in hist1, read no more)
     u16 *bin_group; // [nT][32768] group of each active bin
     u32 *grp_off;   // [nT][MAX_GROUPS] first / one-past-last position of each group in bin order

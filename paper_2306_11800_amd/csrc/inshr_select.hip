@@ -130,7 +130,7 @@ __global__ __launch_bounds__(BLOCK) void k_hist(const TDesc *__restrict__ td, in
         // of the tensor, and a wave's share of it is as large as the wave's share of the elements
         // (1024 per tile), so no counter is shared.
         const u32 capw = B.units[fu].capw;
-        GLOBAL_AS u32 *gdst = gptr(B.pool) + B.units[fu].off + (u64)wave * capw;
+        GLOBAL_AS u32 *gdst = gptr(B.pool) + B.units[fu].off() + (u64)wave * capw;
         u32 gathered = 0u; // wave-uniform
         bool overflow = false;
         if (LEVEL == 2) {
@@ -848,7 +848,7 @@ __global__ __launch_bounds__(TSEL) void k_thr_count(const TDesc *__restrict__ td
     __syncthreads();
     if (tid < nb) which[st->bucket_magbin[tid]] = (unsigned char)(tid + 1u);
     __syncthreads();
-    const u32 *list = B.pool + un.off + (u64)wave * un.capw;
+    const u32 *list = B.pool + un.off() + (u64)wave * un.capw;
     // smallest / largest magnitude among the gathered keys (first pass): for a tensor whose first
     // sweep was sampled the windows of the ranks 0 and n - 1 were gathered, so these are the
     // tensor's own extremes (exact zeros are never gathered: TState::n_zero tells of them)
@@ -1337,7 +1337,7 @@ __global__ __launch_bounds__(BLOCK) void k_gather(const TDesc *__restrict__ td, 
         // wave alone (the workgroup's region starts at its first element of the tensor; a wave's
         // share of it is as large as its share of the elements)
         const u32 capw = un.capw;
-        GLOBAL_AS u32 *gdst = gptr(B.pool2) + un.off + (u64)wave * capw;
+        GLOBAL_AS u32 *gdst = gptr(B.pool2) + un.off() + (u64)wave * capw;
         u32 gathered = 0u; // wave-uniform
         bool overflow = false;
         double q_out[MAX_FRAC];
@@ -1419,7 +1419,7 @@ __global__ __launch_bounds__(BLOCK) void k_split(const TDesc *__restrict__ td, B
     for (int w = 0; w < BLOCK / 64; w++) cmax = max(cmax, B.unit_cand[(size_t)gu * 16 + w]);
     if (cmax == 0u || st->pool_overflow) return; // (an overflow: the search is repeated with larger pools)
     const u32 nb2 = st->nb2, G = st->n_groups;
-    const u32 *src = B.pool2 + un.off + (u64)wave * un.capw;
+    const u32 *src = B.pool2 + un.off() + (u64)wave * un.capw;
     u32 *dst = B.pool + d.pool_grp; // the tensor's span of the first pool, one key per slot in bin-group order
     const u32 *goff = B.grp_off + (size_t)t * MAX_GROUPS;
     u32 *gcur = B.grp_cur + (size_t)t * MAX_GROUPS;
