@@ -1097,7 +1097,10 @@ static int quantize_with_state(inshr_ctx *c, const inshr_config *cfg, inshr_quan
         const SearchResult *res = (const SearchResult *)c->h_down.p;
         for (uint32_t t = 0; t < nT; t++) done[t] = asked[t].packed && (t >= nB || done[t]);
         for (u32 t : ready) done[t] = 1;
-        for (u32 t : fuse) (res[t].fuse_bad ? apart : done)[t] = 1;
+        for (u32 t : fuse) {
+            (res[t].fuse_bad ? apart : done)[t] = 1;
+            if (!res[t].fuse_bad) c->resolved[t] = asked[t].cfg; // (what the sweep worked out is in the state)
+        }
         for (uint32_t t = 0; t < nB; t++)
             if (view[t] != VIEW_NONE) c->resolved[t] = view[t];
         bool all = true;

@@ -848,8 +848,10 @@ __global__ __launch_bounds__(BLOCK) void k_fpatch(const GridDesc *__restrict__ g
 // protected values
 // ------------------------------------------------------------------------------------------
 // A unit's lists, one per wave, hold for every tile and quarter those of the wave's 256 consecutive values, in
-// index order.  The tensor's order is tile, quarter, wave.
-__global__ __launch_bounds__(BLOCK) void k_fprot(const TDesc *__restrict__ td, const u32 *__restrict__ t_gu_off,
+// index order.  The tensor's order is tile, quarter, wave.  The tiles' counts stay behind for k_quant, which takes a
+// further call for the same configuration (6.7 G values: 8.5 ms, this sweep again 12.4).
+__global__ __launch_bounds__(BLOCK) void k_fprot(const TDesc *__restrict__ td, const GridDesc *__restrict__ gd,
+                                                 const u32 *__restrict__ t_gu_off,
                                                  const QDesc *__restrict__ qd, Bufs B)
 {
     constexpr u32 NW = BLOCK / 64;
@@ -862,9 +864,14 @@ __global__ __launch_bounds__(BLOCK) void k_fprot(const TDesc *__restrict__ td, c
     const TState *st = B.ts + t;
     if (st->fuse_bad) return;
     u32 own = lane < 16u ? B.unit_prot[(size_t)gu * 16 + lane] : 0u;
-    if (__ballot(own != 0u) == 0ull) return;
     const QDesc q = qd[t];
     const TDesc d = td[t];
+    const u32 tiles = un.tile1 - un.tile0, per = (tiles + NW - 1u) / NW;
+    GLOBAL_AS u32 *tile_out = gptr(B.tile_out) + (size_t)un.tile0 * MAX_FRAC + gd->pair_o[gd->cfg_pair[q.cfg]];
+    if (__ballot(own != 0u) == 0ull) {
+        for (u32 k = tid; k < tiles; k += BLOCK) tile_out[(size_t)k * MAX_FRAC] = 0u;
+        return;
+    }
     // protected values of the tensor's units before this one
     u32 before = 0u;
     for (u32 k = t_gu_off[t] * 16u + tid; k < gu * 16u; k += BLOCK) before += B.unit_prot[k];
@@ -872,7 +879,6 @@ __global__ __launch_bounds__(BLOCK) void k_fprot(const TDesc *__restrict__ td, c
     if (lane == 0u) s_before[wave] = before;
     const ProtLists pl = prot_lists(un, q.span);
     const GLOBAL_AS u32 *counts = gptr(B.pool) + pl.counts, *list = gptr(B.pool) + pl.list;
-    const u32 tiles = un.tile1 - un.tile0, per = (tiles + NW - 1u) / NW;
     const u32 lo = wave * per < tiles ? wave * per : tiles, hi = lo + per < tiles ? lo + per : tiles;
     // lane = quarter * 16 + list: its count of a tile is u16 number `quarter` of the list's four
     const u32 l = lane & 15u, j = lane >> 4;
@@ -891,8 +897,9 @@ __global__ __launch_bounds__(BLOCK) void k_fprot(const TDesc *__restrict__ td, c
     dst += wave_sum(j == 0u ? src : 0u);
     for (u32 k = lo; k < hi; k++) {
         const u32 c = count_of(k);
-        if (__ballot(c != 0u) == 0ull) continue;
         const u32 inc = wave_incl_scan(c); // in the order of the lanes: quarter, list
+        if (lane == 63u) tile_out[(size_t)k * MAX_FRAC] = inc;
+        if (__ballot(c != 0u) == 0ull) continue;
         const u32 c0 = (u32)__shfl((int)c, (int)l), c1 = (u32)__shfl((int)c, (int)(l + 16u)), c2 = (u32)__shfl((int)c, (int)(l + 32u));
         const u32 c3 = (u32)__shfl((int)c, (int)(l + 48u));
         const u32 from = src + (j > 0u ? c0 : 0u) + (j > 1u ? c1 : 0u) + (j > 2u ? c2 : 0u);
@@ -946,6 +953,7 @@ __global__ __launch_bounds__(BLOCK) void k_fhead(const GridDesc *__restrict__ gd
     __syncthreads();
     const u32 *tk = B.tgt_key + (size_t)t * TGT_STRIDE + pair * NBT;
     const u32 tau_p = st->thr_mag[gd->pair_p[pair]], tau_o = st->thr_mag[gd->n_p + gd->pair_o[pair]];
+    float *codebook = B.codebook + ((size_t)t * gd->n_cfg + q.cfg) * CB_STRIDE; // (for a further call)
     // a wave per bin: its cells by sign and exponent, lowest key to highest, then the lanes in a fixed order
     for (u32 k = wave; k < K; k += BLOCK / 64) {
         const u32 lo = k ? tk[bnd_index(K, k)] : class_edge_key(0u, tau_p, tau_o);
@@ -966,7 +974,7 @@ __global__ __launch_bounds__(BLOCK) void k_fhead(const GridDesc *__restrict__ gd
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o);
         if (lane == 0u)
-            cb[k] = n ? (float)(s / (double)n) : __uint_as_float(bits_of_key(tk[bnd_index(K, k == 0u ? 1u : k)]));
+            codebook[k] = cb[k] = n ? (float)(s / (double)n) : __uint_as_float(bits_of_key(tk[bnd_index(K, k == 0u ? 1u : k)]));
     }
     if (tid == 0u && s_n != st->pair_M[pair]) atomicOr(&st->internal_err, 2048u); // every quantized value is in a cell
     __syncthreads();
@@ -982,7 +990,7 @@ hipError_t launch_fused(const Batch &bt, const QDesc *qd, QInfo *qi, hipStream_t
     PROF("k_fsplit", s, k_fsplit<<<dim3(bt.n_gunits, FS_PARTS), BLOCK, 0, s>>>(qd, B));
     PROF("k_fsel", s, k_fsel<<<dim3(bt.nB, 256 / SEL_WAVES), 64 * SEL_WAVES, 0, s>>>(bt.gd, qd, B));
     PROF("k_fpatch", s, k_fpatch<<<dim3(bt.n_gunits, FP_PARTS), BLOCK, 0, s>>>(bt.gd, qd, B));
-    PROF("k_fprot", s, k_fprot<<<bt.n_gunits, BLOCK, 0, s>>>(bt.td, bt.t_gu_off, qd, B));
+    PROF("k_fprot", s, k_fprot<<<bt.n_gunits, BLOCK, 0, s>>>(bt.td, bt.gd, bt.t_gu_off, qd, B));
     PROF("k_fhead", s, k_fhead<<<bt.nB, BLOCK, 0, s>>>(bt.gd, bt.t_gu_off, qd, qi, B));
     return hipGetLastError();
 }

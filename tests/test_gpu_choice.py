@@ -148,3 +148,33 @@ def test_more_tensors_than_a_grid_dimension():
             else:
                 assert torch.equal(part.view(torch.int32), x.view(torch.int32).expand(part.shape[0], -1)), (name, k)
     ctx.close()
+
+
+def test_quantizing_again_from_a_choice():
+    """What the sweep worked out stays in the state: a further call for the same configuration gives the same bytes
+    without it (k_quant), also after calls for others; protected values nowhere, everywhere, and in some tiles only."""
+    rng = np.random.default_rng(46)
+    n = 150_001
+    some = family(rng, 0, n)
+    some[40_000:41_000] *= np.float32(50)
+    xs = [some, family(rng, 0, 16_385), family(rng, 1, n), np.zeros(n, np.float32)]
+    ts = [dev(x) for x in xs]
+    ctx, want = api.Context(torch.device("cuda:0")), api.Context(torch.device("cuda:0"))
+    g = GRIDS["full"]
+    best = ctx.search(ts, g, 0.01, want_scores=False)[0]
+    want.search(ts, g, 0.01)
+    first, other, bare = [g[b] for b in best], [(3, 50_000, 1000)] * len(ts), [(8, 0, 0)] * len(ts)
+    for cfgs in (first, other, bare):
+        a = ctx.quantize(ts, cfgs, reuse_search=True)
+        ctx.profile(True)
+        b = ctx.quantize(ts, cfgs, reuse_search=True)
+        kernels = ctx.profile_read()
+        ctx.profile(False)
+        assert "k_fuse" not in kernels and "k_quant" in kernels, kernels
+        same(a, b)
+        for x, y in zip(a, b):
+            assert torch.equal(x.codebook, y.codebook)
+        same(b, want.quantize(ts, cfgs, reuse_search=True))
+    same(ctx.quantize(ts, first, reuse_search=True), want.quantize(ts, first, reuse_search=True))
+    ctx.close()
+    want.close()
