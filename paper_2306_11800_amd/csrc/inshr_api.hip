@@ -1056,12 +1056,14 @@ static int quantize_with_state(inshr_ctx *c, const inshr_config *cfg, inshr_quan
             }
             if ((rc = resolve(c, view, up_bytes))) return rc;
         }
-        for (uint32_t t = 0; nB && t < nT; t++) {
+        for (uint32_t t = 0; nB && t < nT; t++) { // (the state holds nothing yet for those that wait for a later pass)
             qd[t] = asked[t];
-            if (done[t]) qd[t].packed = nullptr;
+            if (done[t] || t < nB) qd[t].packed = nullptr;
         }
+        for (u32 t : ready) qd[t].packed = asked[t].packed;
         for (u32 t : fuse) {
             const u32 u0 = p.t_off[t], u1 = p.t_off[t + 1];
+            qd[t].packed = asked[t].packed;
             qd[t].fused = 1u;
             qd[t].span = p.units[u0].off();
             qd[t].span_len = p.units[u1 - 1].off() + (u64)p.units[u1 - 1].capw * (BLOCK / 64) - qd[t].span;

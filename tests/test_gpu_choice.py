@@ -178,3 +178,31 @@ def test_quantizing_again_from_a_choice():
     same(ctx.quantize(ts, first, reuse_search=True), want.quantize(ts, first, reuse_search=True))
     ctx.close()
     want.close()
+
+
+def test_tensors_of_every_kind_in_one_call():
+    """One call with tensors that the state holds, that the sweep takes, that it gives up (one bin holds more values
+    than a wave should read), that protect too much for its lists, and a small one: several passes, each on its own
+    tensors only."""
+    rng = np.random.default_rng(47)
+    n = 200_001
+    crowd = family(rng, 0, n)
+    crowd[:140_000] = np.float32(0.25)
+    ts = [dev(x) for x in (family(rng, 0, n), family(rng, 1, n), crowd, family(rng, 2, n), family(rng, 0, 900))]
+    ctx, want = api.Context(torch.device("cuda:0")), api.Context(torch.device("cuda:0"))
+    g = GRIDS["bins"]
+    few, many = (0, 200_000, 5000, 16), (0, 200_000, 20_000, 16)
+    want.search(ts, g, 0.01)
+    ctx.search(ts, g, 0.01, want_scores=False)
+    ctx.quantize(ts, [few, many, many, many, few], reuse_search=True)  # (the first stays in the state)
+    cfgs = [few, few, few, (0, 0, 20_000, 16), few]
+    for again in (False, True):
+        ctx.profile(True)
+        got = ctx.quantize(ts, cfgs, reuse_search=True)
+        kernels = ctx.profile_read()
+        ctx.profile(False)
+        same(got, want.quantize(ts, cfgs, reuse_search=True))
+        assert ("k_fuse" in kernels, "k_gather" in kernels) == (not again, not again), kernels
+        assert kernels["k_quant"][1] == (1 if again else 2), kernels
+    ctx.close()
+    want.close()
