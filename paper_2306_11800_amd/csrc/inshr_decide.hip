@@ -19,9 +19,15 @@
 //     same x^ = m_j.  With the means c of P: F_P'(x^) <= F_P(x^) + sum r_j max(0, (m_j - c_j)^2 - (m_j -
 //     c_(j-1))^2); with the means c' of P', which lie between c and the mean that every possible move
 //     together would give, F_P'(x^) >= F_P(x^) - sum r_j max(0, (m_j - c'_(j-1))^2 - (m_j - c'_j)^2).
-// The sums are taken in units of a power of two near the tensor's root mean square, in fp32 over the 32 bins of
-// a thread and in fp64 beyond; middles, means and their distances are fp32.  Each of these roundings is below
-// 1e-6 of the sum of squares; 1e-5 of it is added on either side.
+// The sums over ranks are taken in fp64, in units of a power of two near the tensor's root mean square, and so
+// are means and the lowest means c'.  What is rounded to fp32 (u = 2^-24):
+//   - the middles, by u of their size each; any number may stand for a bin's middle as long as its distance to
+//     the values is counted, so |x - x^| grows by at most u |x|: 2 u of the sum of squares in F
+//   - V's terms and their sums over 32 bins, 34 u of V up to the rank; 1e-5 of it (168 u) is added
+//   - the distances in U and L, differences of squares that may cancel: at most 13 u (m^2 + mean^2) per square,
+//     26 u (1.6e-6) of the three squares together; 4e-6 of them is added to each difference
+//   - F and the pruned squares when they are added up, the roots and their squares: a few u of the sum of squares
+//     where a bound is near eps or a lower one.  1e-5 (168 u) of the sum of squares is added on either side.
 //
 // One workgroup per tensor, bound by the latency of its steps: 43 us for one tensor, 140 us for 146 tensors and 105
 // configurations (k_plan2, which it takes the place of, 49 and 125 us).
@@ -177,31 +183,40 @@ __global__ __launch_bounds__(BLOCK) void k_decide(const TDesc *__restrict__ td, 
         if (((sh.T[p0 + step] >> 5) & 0x7fffu) <= 32u * tid) p0 += step;
     auto walk = [&](auto &&f) { // f(i, keys, middle, half the width) of the thread's bins in order
         u32 p = p0, e = sh.T[p0], sub = 32u * tid - ((e >> 5) & 0x7fffu);
+        u4 next = ((const GLOBAL_AS u4 *)gptr(h2))[tid * 8u];
+#pragma unroll 1
+        for (u32 i4 = 0; i4 < 8u; i4++) { // (four at a time, read again: 32 in registers, in fp64 too, would spill)
+            const u4 now = next;
+            if (i4 < 7u) next = ((const GLOBAL_AS u4 *)gptr(h2))[tid * 8u + i4 + 1u];
 #pragma unroll
-        for (u32 i = 0; i < 32u; i++) {
-            const u32 k = c[i >> 2][i & 3u], d = e & 31u;
-            float m = 0.0f, r = 0.0f;
-            if (k) { // (finite values only: no bin of infinities)
-                const u32 first = (p << COARSE_SHIFT) | (sub << (COARSE_SHIFT - d));
-                const float a = __uint_as_float(bits_of_key(first)) * unit;
-                const float b = __uint_as_float(bits_of_key(first + ((1u << (COARSE_SHIFT - d)) - 1u))) * unit;
-                m = 0.5f * (a + b);
-                r = 0.5f * (b - a);
-            }
-            f(i, (float)k, m, r);
-            if (++sub >> d) {
-                sub = 0u;
-                p = p + 1u < (u32)COARSE ? p + 1u : p;
-                e = sh.T[p];
+            for (u32 j = 0; j < 4u; j++) {
+                const u32 k = now[j], d = e & 31u;
+                float m = 0.0f, r = 0.0f;
+                if (k) { // (finite values only: no bin of infinities)
+                    const u32 first = (p << COARSE_SHIFT) | (sub << (COARSE_SHIFT - d));
+                    const float a = __uint_as_float(bits_of_key(first)) * unit;
+                    const float b = __uint_as_float(bits_of_key(first + ((1u << (COARSE_SHIFT - d)) - 1u))) * unit;
+                    m = 0.5f * (a + b);
+                    r = 0.5f * (b - a);
+                }
+                f(4u * i4 + j, k, m, r);
+                if (++sub >> d) {
+                    sub = 0u;
+                    p = p + 1u < (u32)COARSE ? p + 1u : p;
+                    e = sh.T[p];
+                }
             }
         }
     };
-    float s1 = 0.0f, s2 = 0.0f, v = 0.0f;
-    walk([&](u32, float k, float m, float r) {
-        s1 += k * m;
-        s2 += k * m * m;
-        v += k * r * r;
-    });
+    double s1 = 0.0, s2 = 0.0;
+    float v = 0.0f;
+    auto add = [&](u32 k, float m, float r) {
+        const double km = (double)k * (double)m;
+        s1 += km;
+        s2 += km * (double)m;
+        v += (float)k * r * r;
+    };
+    walk([&](u32, u32 k, float m, float r) { add(k, m, r); });
     auto scan = [&](double x, int which) { // exclusive over the lanes; the waves' totals to LDS
         double y = x;
 #pragma unroll
@@ -212,7 +227,7 @@ __global__ __launch_bounds__(BLOCK) void k_decide(const TDesc *__restrict__ td, 
         if (lane == 63u) sh.w_s[which][wave] = y;
         return y - x;
     };
-    double b1 = scan((double)s1, 0), b2 = scan((double)s2, 1), bv = scan((double)v, 2);
+    double b1 = scan(s1, 0), b2 = scan(s2, 1), bv = scan((double)v, 2);
     __syncthreads(); // (all edges are marked)
     const u32 word = sh.act[tid], n_marks = (u32)__popc(word);
     const u32 inc = wave_incl_scan(n_marks);
@@ -227,19 +242,18 @@ __global__ __launch_bounds__(BLOCK) void k_decide(const TDesc *__restrict__ td, 
     }
     sh.before[tid] = at;
     if (word) {
-        s1 = s2 = v = 0.0f;
-        walk([&](u32 i, float k, float m, float r) {
+        s1 = s2 = 0.0;
+        v = 0.0f;
+        walk([&](u32 i, u32 k, float m, float r) {
             if ((word >> i) & 1u) {
-                sh.m.s1[at] = b1 + (double)s1;
-                sh.m.s2[at] = b2 + (double)s2;
+                sh.m.s1[at] = b1 + s1;
+                sh.m.s2[at] = b2 + s2;
                 sh.m.v[at] = (float)(bv + (double)v);
                 sh.m.mid[at] = m;
                 sh.m.rad[at] = r;
                 at++;
             }
-            s1 += k * m;
-            s2 += k * m * m;
-            v += k * r * r;
+            add(k, m, r);
         });
     }
     __syncthreads();
@@ -256,8 +270,8 @@ __global__ __launch_bounds__(BLOCK) void k_decide(const TDesc *__restrict__ td, 
         const u32 x = sh.before[w] + (u32)__popc(sh.act[w] & ((1u << (e_bin[k] & 31u)) - 1u));
         const float r = (float)e_res[k], h = sh.m.rad[x];
         em[k] = sh.m.mid[x];
-        e1[k] = sh.m.s1[x] + (double)r * (double)em[k];
-        e2[k] = sh.m.s2[x] + (double)r * ((double)em[k] * (double)em[k]);
+        e1[k] = sh.m.s1[x] + (double)e_res[k] * (double)em[k];
+        e2[k] = sh.m.s2[x] + (double)e_res[k] * ((double)em[k] * (double)em[k]);
         const u32 q = i / per_pair, j = i % per_pair;
         if (j == n_bnd || j == n_bnd + 3u) sh.v[q][j == n_bnd ? 0 : 1] = sh.m.v[x] + r * h * h;
     }
@@ -304,18 +318,20 @@ __global__ __launch_bounds__(BLOCK) void k_decide(const TDesc *__restrict__ td, 
                     Q -= gQ;
                 }
                 if (nk == 0u || nk > 0x7fffffffu || (float)n > 1e4f * (float)nk) empty = true; // (no bound)
-                const float kn = (float)(nk ? nk : 1u), inv = 1.0f / kn, Sf = (float)S, mean = Sf * inv;
-                const float xu = b + 1u < K ? (float)sh.e.res[up] : 0.0f, xl = b ? (float)sh.e.res[lo] : 0.0f;
+                nk = nk ? nk : 1u;
+                const double mean_d = S / (double)nk;
+                const float mean = (float)mean_d;
+                const u32 xu = b + 1u < K ? sh.e.res[up] : 0u, xl = b ? sh.e.res[lo] : 0u;
                 float low = ml; // the lowest mean that the moves can give
-                if (kn > xu) {
-                    low = (Sf - xu * mu + xl * ml) / (kn - xu + xl);
+                if (nk > xu) { // (the counts are exact)
+                    low = (float)((S - (double)xu * (double)mu + (double)xl * (double)ml) / ((double)(nk - xu) + (double)xl));
                     low = fminf(fmaxf(low, ml), mean);
                 }
-                if (j) F += fmax(Q - S * S * (double)inv, 0.0);
+                if (j) F += fmax(Q - S * mean_d, 0.0);
                 if (b && j) { // boundary b, between bins b - 1 and b
                     const float x = ml - mean, y = ml - c_prev, z = ml - l_prev, w = fmaxf(low - ml, 0.0f);
-                    U += xl * fmaxf(x * x - y * y, 0.0f);
-                    L += xl * fmaxf(z * z - w * w, 0.0f);
+                    U += (float)xl * fmaxf(x * x - y * y + 4e-6f * (ml * ml + mean * mean + c_prev * c_prev), 0.0f);
+                    L += (float)xl * fmaxf(z * z - w * w + 4e-6f * (ml * ml + low * low + l_prev * l_prev), 0.0f);
                 }
                 c_prev = mean;
                 l_prev = low;

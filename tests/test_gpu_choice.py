@@ -206,3 +206,31 @@ def test_tensors_of_every_kind_in_one_call():
         assert kernels["k_quant"][1] == (1 if again else 2), kernels
     ctx.close()
     want.close()
+
+
+@pytest.mark.parametrize("values", ["heavy", "few", "run", "family 0", "family 1"])
+def test_bounds_that_sit_on_an_error(values):
+    """eps just beside the exact error of a configuration: the choice is the scored search's, also where one value
+    makes up nearly all of a tensor and the boundaries lie among few others."""
+    rng = np.random.default_rng(50)
+    n = 300_001 if values.startswith("family") else 17_001  # (the scored search is slow where a bin holds most values)
+    if values == "heavy":
+        x = np.full(n, np.float32(0.95))
+        x[:n // 100] = np.exp(rng.normal(3, 0.5, n // 100)).astype(np.float32)
+        x = rng.permutation(x)
+    elif values == "few":
+        x = rng.choice(np.array([-1.5, -0.1, 0.0, 0.3, 0.30001, 0.31, 2.0, 7.0], np.float32), n)
+    else:
+        x = repeated(rng, "run", n) if values == "run" else family(rng, int(values[-1]), n)
+    ts, g = [dev(x)], GRIDS["full"]
+    scored, bare = api.Context(torch.device("cuda:0")), api.Context(torch.device("cuda:0"))
+    rel = np.array([s.sse / s.sumsq for s in scored.search(ts, g, 0.01)[2]])
+    for k in range(4, len(g), 9):
+        for f in (1 - 1e-4, 1 - 2e-5, 1 + 2e-5, 1 + 1e-4):
+            eps = float(rel[k] * f)
+            if (np.abs(rel - eps) <= 4e-6 * eps + 1e-12).any():
+                continue  # (an error that rounds to the bound may fall on either side)
+            want, got = scored.search(ts, g, eps), bare.search(ts, g, eps, want_scores=False)
+            assert (got[0][0], got[1][0]) == (want[0][0], want[1][0]), (k, f)
+    scored.close()
+    bare.close()
