@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import ref
 from paper_2306_11800_amd import api, synth
 from test_gpu_fuzz import family
 from test_gpu_small import KINDS, repeated
@@ -206,6 +207,65 @@ def test_tensors_of_every_kind_in_one_call():
         assert kernels["k_quant"][1] == (1 if again else 2), kernels
     ctx.close()
     want.close()
+
+
+def test_sums_of_long_units(monkeypatch):
+    """Units of more than 64 tiles (the sweep empties its cells after as many): one tensor of 131 M values three
+    times in one call on 256 workgroups gives what it gives alone in units of 16 tiles, and its centres are
+    the means of the values of their bins."""
+    n, cfg = 131_072_000 + 5, (5, 200_000, 1000)
+    x = torch.empty(n, device="cuda:0")
+    x.normal_(generator=torch.Generator(device="cuda:0").manual_seed(48))
+    alone = api.Context(torch.device("cuda:0"))
+    want = alone.quantize([x], [cfg])[0]
+    monkeypatch.setenv("INSHR_WG_PER_CU", "1")
+    ctx = api.Context(torch.device("cuda:0"))
+    ctx.profile(True)
+    got = ctx.quantize([x] * 3, [cfg] * 3)
+    kernels = ctx.profile_read()
+    assert "k_fuse" in kernels and "k_quant" not in kernels, kernels
+    for q in got:
+        same([q], [want])
+        assert torch.equal(q.codebook, want.codebook)  # (the sums are exact integers)
+    ctx.close()
+    alone.close()
+    kept = x[(x.abs() >= want.tau_prune) & (x.abs() <= want.tau_outlier)]
+    assert kept.numel() == want.n_kept
+    b = torch.bucketize(kept, want.boundaries[:31], right=True)
+    s = torch.zeros(32, dtype=torch.float64, device="cuda:0").index_add_(0, b, kept.double())
+    mean = s / torch.bincount(b, minlength=32)
+    # (2^-24 of rounding to fp32; the fp64 sums of 3 M values of one sign are exact to 1e-9)
+    np.testing.assert_allclose(want.codebook[:32].cpu().numpy(), mean.cpu().numpy(), rtol=1e-7)
+
+
+@pytest.mark.parametrize("values", ["protected", "open"])
+def test_lists_that_overflow(values):
+    """Values of one wave's list that lie side by side, more than its share takes: protected ones (the largest
+    percent of the tensor in one run), and values of one bin that holds boundaries.  The tensor is given up by
+    the sweep and goes through k_gather and k_quant; the one beside it does not."""
+    rng = np.random.default_rng(49)
+    n = 1 << 20
+    x, beside = family(rng, 0, n), family(rng, 0, n)
+    if values == "protected":
+        x[100_000:110_485] = np.float32(50) * (1 + rng.random(10_485).astype(np.float32))
+    else:
+        x[100_000:130_000] = np.float32(np.median(np.abs(x)))
+    cfg, g = (8, 0, 10_000), [(8, 0, 10_000)]
+    ts = [dev(x), dev(beside)]
+    ctx = api.Context(torch.device("cuda:0"))
+    ctx.search(ts, g, 0.01, want_scores=False)
+    ctx.profile(True)
+    got = ctx.quantize(ts, [cfg] * 2, reuse_search=True)
+    kernels = ctx.profile_read()
+    ctx.profile(False)
+    assert "k_fuse" in kernels and kernels["k_gather"][1] == kernels["k_quant"][1] == 1, kernels
+    same(got, ctx.quantize(ts, [cfg] * 2))
+    for q, v in zip(got, (x, beside)):
+        r = ref.quantize(v, cfg)
+        assert np.array_equal(q.packed.cpu().numpy().view(np.uint64), ref.pack(r["sym"], 9))
+        np.testing.assert_allclose(q.codebook.cpu().numpy(), r["codebook"], rtol=1e-6)
+        assert np.array_equal(q.outlier_idx.cpu().numpy()[:q.n_outlier], np.flatnonzero(r["sym"] == 1))
+    ctx.close()
 
 
 @pytest.mark.parametrize("values", ["heavy", "few", "run", "family 0", "family 1"])
