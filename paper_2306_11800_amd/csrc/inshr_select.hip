@@ -1312,11 +1312,7 @@ __global__ __launch_bounds__(BLOCK) void k_gather(const TDesc *__restrict__ td, 
     for (u32 gu = wg_gu0[blockIdx.x]; gu < wg_gu0[blockIdx.x + 1]; gu++) {
         const Unit un = B.gunits[gu];
         const int t = (int)un.tensor;
-        const u32 view = B.view[t];
-        if (view == VIEW_NONE) { // (nothing behind this unit waits for it)
-            if (tid < BLOCK / 64) B.unit_cand[(size_t)gu * 16 + tid] = 0u;
-            continue;
-        }
+        const u32 view = B.view[t]; // (units are dealt to tensors in view only)
         const u32 only_o = view == VIEW_ALL ? (u32)MAX_FRAC : gd->pair_o[gd->cfg_pair[view]];
         const TDesc d = td[t];
         TState *st = B.ts + t;
