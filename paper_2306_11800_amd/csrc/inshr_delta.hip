@@ -63,7 +63,7 @@ __device__ __forceinline__ void count_symbols(const DDesc &d, u64 c0, u64 c1, u3
     const u32 n_runs = (u32)((c1 - c0 + 63u) >> 6);
     for (u32 u = tid; u < n_runs; u += HBLOCK) {
         const u64 e = c0 + 64ull * u;
-        const u32 nvalid = (c1 - e < 64ull) ? (u32)(c1 - e) : 64u;
+        const u32 nvalid = tile_len(c1 - e, 64u);
         const u64 w0 = (e >> 6) * W; // e is a multiple of 64
         u32 x[2 * W + 1];
 #pragma unroll

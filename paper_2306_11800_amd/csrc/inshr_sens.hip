@@ -331,7 +331,7 @@ __global__ __launch_bounds__(SWG) void k_sens_quant(const SDesc *__restrict__ sd
     __syncthreads();
     if (!left) return;
     // 1024 symbols of wb bits are 16 * wb whole words; the tensor's last block may end earlier
-    const u32 n_here = left < (u64)SBLK ? (u32)left : (u32)SBLK;
+    const u32 n_here = tile_len(left, (u32)SBLK);
     const u32 n_words = (n_here * wb + 63u) >> 6;
     const u32 inv = (1u << 20) / wb + 1u; // bit0 / wb for bit0 < 1024 wb
     GLOBAL_AS unsigned long long *dst = gptr(d.packed) + (e0 * wb >> 6); // e0 * wb is a multiple of 64
