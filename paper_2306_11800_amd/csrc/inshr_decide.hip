@@ -4,7 +4,7 @@
 // within eps.  What a configuration costs follows from the exact class counts; its error is known within a
 // few percent from the equal-population bins of sweep 2, and that is nearly always enough.  Boundaries and
 // centres are then worked out for the chosen configuration alone, by the quantizer, instead of for every
-// pair of the grid: of 32768 bins 259 hold an edge instead of 4005, the gathered keys of which took sweep 3,
+// pair of the grid: of 32768 bins 259 hold an edge instead of up to 3885, the gathered keys of which took sweep 3,
 // the split and the group sort two thirds of a search (6.7 G values, 105 configurations: 17.1 of 24.2 ms;
 // k_decide in their place: 0.08 ms.  Search and quantizing together 33.2 -> 19.5 ms).
 // A tensor whose bounds leave the choice open is scored exactly (launch_resolve), as before.

@@ -56,7 +56,7 @@ __device__ __forceinline__ ProtLists prot_lists(const Unit &un, u64 span)
     const u64 tiles = un.tile1 - un.tile0;
     p.counts = span + (un.off() - span) / 2u;
     p.list = p.counts + tiles * F_TILEW;
-    p.cap = (u32)((8ull * un.capw - tiles * F_TILEW) / 16u); // (a share has room for at least 136 keys per tile)
+    p.cap = (u32)((8ull * un.capw - tiles * F_TILEW) / 16u); // (a share has room for 32 keys per tile and 1024 more, or for all: at least 510, and 14 per tile)
     return p;
 }
 // Values listed by wave w of a unit: keys and indices, each in one half of its share of the second pool.

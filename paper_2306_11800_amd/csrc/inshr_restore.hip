@@ -59,7 +59,7 @@ __device__ __forceinline__ u32 decode4(const u32 *W, const float *value, u32 off
 }
 
 // Bound by memory, as far as the seven workgroups of a CU keep requests in flight: the rounds of a tile are unrolled four at a time, so that
-// a thread gets by with 72 registers (all sixteen at once took 197, two workgroups per CU: 1.06 G elements
+// a thread gets by with 54 registers (all sixteen at once took 197, two workgroups per CU: 1.06 G elements
 // 1.52 ms, 1.05 ms so, 5.2 GB: 4.9 TB/s).  The value table holds zeros for the symbols that have no centre,
 // so a symbol is one read of it and no comparison.
 __global__ __launch_bounds__(DQ_BLOCK, 7) void k_dequant(const RDesc *__restrict__ rd, int nT, u64 n_tiles,
