@@ -698,7 +698,7 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         c->scores_off = o_sc;
     }
     c->batch.light = light;
-    c->batch.choose = mode == CHOOSE;
+    c->batch.spread = mode == CHOOSE || mode == LIGHT;
     HIPCHK(c, launch_small(c->batch, c->stream));
     HIPCHK(c, launch_select(c->batch, c->stream));
     c->resolved.assign(nT, VIEW_ALL); // (the small tensors are searched completely)

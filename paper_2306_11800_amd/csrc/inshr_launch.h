@@ -93,7 +93,7 @@ struct Batch {
     int n_gwg, n_gunits; // workgroups and units of sweep 3
     int n_bucket_blocks;
     bool lds_ordered;    // same-address LDS atomics return in lane order on this device
-    bool choose;         // the search ends with k_decide
+    bool spread;         // k_decide or the sketch kernels work with the second histogram's bins
     bool light;          // thresholds and class counts only: no boundaries, no scores (the sketch
                          // quantizer brings its own bins)
     bool any_sampled;    // some tensor's sweep 1 is sampled

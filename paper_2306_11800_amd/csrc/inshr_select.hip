@@ -389,7 +389,7 @@ static_assert(COARSE + L2_BINS / 4 + SPREAD_BINS <= L2_BINS, "fits beside a bin 
 // REDO: only the tensors whose sampled sweep 1 mispredicted (their histogram is exact now).
 template <bool REDO>
 __global__ __launch_bounds__(BLOCK) void k_plan1(const TDesc *__restrict__ td,
-                                                 const GridDesc *__restrict__ gd, Bufs B, bool choose)
+                                                 const GridDesc *__restrict__ gd, Bufs B, bool wanted)
 {
     __shared__ MagPrefix mp;
     __shared__ u32 tmp[BLOCK / 64];
@@ -544,9 +544,10 @@ __global__ __launch_bounds__(BLOCK) void k_plan1(const TDesc *__restrict__ td,
     // bins leaves least of it when they are dealt out by the cube root of c m^2.  SPREAD_BINS are,
     // on top of the equal populations (whichever asks for more): the bounds at 7 and 8 bits are 0.4 .. 0.9 %
     // wide then instead of 3 .. 6 % (Gaussian to Student-t(3) values, 1 Mi; with 8192 bins 0.5 .. 1.2 %), and
-    // the bins that boundaries fall into hold 15 % more.  Only k_decide gains from it, so only its searches
-    // do it (6.7 G values, 105 configurations with scores: k_split 3.74 and k_bucket 5.70 ms with it, 3.14 and
-    // 5.13 without).
+    // the bins that boundaries fall into hold 15 % more.  So searches that end with k_decide do it, and those before
+    // sketch bins, whose boundaries lie in the tails (1.6 G values: k_sketch_score 2.73 ms with it, 2.76 without,
+    // k_quant 2.11, 2.13), but none with scores (6.7 G values, 105 configurations: k_split 3.74 and k_bucket 5.70 ms
+    // with it, 3.14 and 5.13 without).
     u32 my_flags[PER], my_least[PER]; // least depth
     float my_w[PER];
     double q = 0.0, my_q[PER];
@@ -593,7 +594,7 @@ __global__ __launch_bounds__(BLOCK) void k_plan1(const TDesc *__restrict__ td,
     w_sum = 0.0f;
     for (int w = 0; w < BLOCK / 64; w++) w_sum += s_w[w];
     // (windows that span most prefixes, of values all over the range of fp32, leave no room for this)
-    const bool spread = choose && n_forced <= (u32)L2_BINS / 4u && w_sum > 0.0f; // (there is always room for 4096 + n_forced + SPREAD_BINS)
+    const bool spread = wanted && n_forced <= (u32)L2_BINS / 4u && w_sum > 0.0f; // (there is always room for 4096 + n_forced + SPREAD_BINS)
 #pragma unroll
     for (u32 k = 0; k < PER; k++) {
         const float bins = spread ? my_w[k] * ((float)SPREAD_BINS / w_sum) : 0.0f;
@@ -1970,14 +1971,14 @@ hipError_t launch_select(const Batch &bt, hipStream_t s)
     if (bt.nB == 0) return hipSuccess; // (only small tensors)
     PROF("k_hist1", s, (k_hist<1, false><<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nB, bt.wg_tile0, bt.wg_fu0, B)));
     if (bt.any_pooled) PROF("k_pool_sum", s, k_pool_sum<<<bt.nB, BLOCK, 0, s>>>(bt.td, B));
-    PROF("k_plan1", s, k_plan1<false><<<bt.nB, BLOCK, 0, s>>>(bt.td, bt.gd, B, bt.choose));
+    PROF("k_plan1", s, k_plan1<false><<<bt.nB, BLOCK, 0, s>>>(bt.td, bt.gd, B, bt.spread));
     PROF("k_hist2", s, (k_hist<2, false><<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nB, bt.wg_tile0, bt.wg_fu0, B)));
     if (bt.any_sampled) {
         // tensors whose sweep 1 was sampled: exact figures from the second histogram; those whose
         // thresholds were mispredicted take the exact sweeps (the kernels skip all other tensors)
         PROF("k_plan1b", s, k_plan1b<<<bt.nB, BLOCK, SM_PLAN1B, s>>>(bt.td, bt.gd, B, bt.force_miss ? 1u : 0u));
         PROF("k_hist1_redo", s, (k_hist<1, true><<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nB, bt.wg_tile0, bt.wg_fu0, B)));
-        PROF("k_plan1_redo", s, k_plan1<true><<<bt.nB, BLOCK, 0, s>>>(bt.td, bt.gd, B, bt.choose));
+        PROF("k_plan1_redo", s, k_plan1<true><<<bt.nB, BLOCK, 0, s>>>(bt.td, bt.gd, B, bt.spread));
         PROF("k_hist2_redo", s, (k_hist<2, true><<<bt.n_wg, BLOCK, 0, s>>>(bt.td, bt.nB, bt.wg_tile0, bt.wg_fu0, B)));
     }
     PROF("k_thr_setup", s, k_thr_setup<<<bt.nB, TSEL, 0, s>>>(bt.td, B));
