@@ -18,13 +18,20 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0  # MI355X published HBM3E bandwidth
 
 
-def algorithmic_bytes_per_element(bits_cur: int, bits_prev: int) -> float:
-    """Floor traffic of the path per element: two reads to find the order statistics, one to score,
-    one to quantize (+ packed write), delta reads both symbol streams and writes one."""
+SAMPLED_MIN_N = 16 << 20  # values from which the first sweep reads one tile in eight (INSHR_SAMPLE_MIN_N)
+SWEPT_MIN_N = 16385       # smaller tensors are searched by one workgroup each, in one read
+
+
+def algorithmic_bytes_per_element(n: int, bits_cur: int, bits_prev: int) -> float:
+    """Bytes the path reads and writes per element of a tensor whose choice the bounds settle: the first
+    sweep (one tile in eight of a large tensor), the second one and the quantizing sweep read the values,
+    the last writes the symbols; the delta reads the previous symbols twice (counting, scatter) and the current
+    ones once and writes its stream.  Gathered and listed keys (a few percent) are not counted."""
     w = bits_cur + 1
     wp = bits_prev + 1
     wb = max(bits_cur, bits_prev) + 1
-    return 16.0 + (2 * w + wp + wb) / 8.0
+    sweep1 = 0.5 if n >= SAMPLED_MIN_N else 4.0 if n >= SWEPT_MIN_N else 0.0
+    return sweep1 + 8.0 + (2 * w + 2 * wp + wb) / 8.0
 
 
 def cpu_baseline(sample, grid, eps, threads):
@@ -267,10 +274,10 @@ def main():
     ms_per_step = dt / args.steps * 1e3
     value = n_total * 4 / (dt / args.steps) / 1e9
 
-    # floor-traffic model of the whole path with the configurations actually chosen
+    # bytes the whole path reads and writes with the configurations actually chosen
     a_bytes = 0.0
     for t, c, bp in zip(cur, cfgs, best_p):
-        a_bytes += t.numel() * algorithmic_bytes_per_element(c[0], grid[bp][0])
+        a_bytes += t.numel() * algorithmic_bytes_per_element(t.numel(), c[0], grid[bp][0])
     path_gbs = a_bytes / (dt / args.steps) / 1e9
 
     # dominant kernel: algorithmic bytes per launch / average launch duration (HIP events)
@@ -279,7 +286,7 @@ def main():
     mean_w = sum(t.numel() * (c[0] + 1) for t, c in zip(cur, cfgs)) / n_total
     kernel_bytes = {
         "k_hist1": 4.0, "k_hist2": 4.0, "k_gather": 4.0, "k_score": 4.0,
-        "k_quant": 4.0 + mean_w / 8.0,
+        "k_quant": 4.0 + mean_w / 8.0, "k_fuse": 4.0 + mean_w / 8.0,
         "k_dhist": mean_w / 8.0, "k_dscatter": 3.0 * mean_w / 8.0,
     }
     dom_bytes = kernel_bytes.get(dom, 4.0) * n_total
