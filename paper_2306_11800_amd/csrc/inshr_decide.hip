@@ -5,8 +5,8 @@
 // few percent from the equal-population bins of sweep 2, and that is nearly always enough.  Boundaries and
 // centres are then worked out for the chosen configuration alone, by the quantizer, instead of for every
 // pair of the grid: of 32768 bins 259 hold an edge instead of up to 3885, the gathered keys of which took sweep 3,
-// the split and the group sort two thirds of a search (6.7 G values, 105 configurations: 17.1 of 24.2 ms;
-// k_decide in their place: 0.08 ms.  Search and quantizing together 33.2 -> 19.5 ms).
+// the split and the group sort two thirds of a search (6.7 G values, 105 configurations: 16.8 of 25.0 ms;
+// k_decide in their place: 0.07 ms.  Search and quantizing together 33.4 -> 20.0 ms).
 // A tensor whose bounds leave the choice open is scored exactly (launch_resolve), as before.
 //
 // The bounds.  Let x^ be the sorted values with every value replaced by the middle of its bin's key range
@@ -29,8 +29,8 @@
 //   - F and the pruned squares when they are added up, the roots and their squares: a few u of the sum of squares
 //     where a bound is near eps or a lower one.  1e-5 (168 u) of the sum of squares is added on either side.
 //
-// One workgroup per tensor, bound by the latency of its steps: 43 us for one tensor, 140 us for 146 tensors and 105
-// configurations (k_plan2, which it takes the place of, 49 and 125 us).
+// One workgroup per tensor (its LDS leaves room for one on a CU), bound by the latency of its steps: 39 us for one tensor
+// (k_plan2, the first of those it takes the place of, 36 us), 128 us for 294 tensors and 105 configurations.
 #include "inshr_launch.h"
 
 namespace inshr {

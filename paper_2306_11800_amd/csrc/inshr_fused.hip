@@ -17,10 +17,11 @@
 //   k_fprot    protected values: the sweep's lists, one per wave -> the tensor's list in index order
 //   k_fhead    per tensor: centres, boundaries, class counts
 //
-// 6.7 G values, symbols of 9 bits: k_fuse 10.9 ms (27 GB read, 7.6 GB written: 3.2 TB/s; bound by its dependent
-// LDS accesses, two per value and the sum's add, and the wave's instructions between them), k_fsplit 0.34,
-// k_fsel 0.25, k_fpatch 0.42, k_fprot 0.37; boundaries, centres and k_quant for one configuration took
-// 8.7 (k_gather) + 0.6 + 8.9 (k_quant).  100 M values in 48 tensors: 0.28 ms where k_plan2 .. k_quant took 0.70.
+// 6.7 G values, symbols of 9 bits: k_fuse 11.0 ms (27.0 GB read, 8.7 GB written: 3.2 TB/s; vector issue takes 0.71 of
+// the CU-cycles, the LDS pipe 0.46, half of it bank conflicts of the table reads; one workgroup of 16 waves fits a CU, and
+// its waves wait half of the time), k_fsplit 0.34, k_fsel 0.22, k_fpatch 0.41, k_fprot 0.37; boundaries, centres and
+// k_quant for one configuration took 8.7 (k_gather) + 0.6 + 8.9 (k_quant).  100 M values in 48 tensors: 0.25 ms where
+// k_plan2 .. k_quant took 0.70.
 //
 // A tensor that these means do not hold (a bin with more values than one wave should read, lists that
 // overflow) is marked (TState::fuse_bad); the host sends it through launch_resolve and launch_quantize.

@@ -545,9 +545,9 @@ __global__ __launch_bounds__(BLOCK) void k_plan1(const TDesc *__restrict__ td,
     // on top of the equal populations (whichever asks for more): the bounds at 7 and 8 bits are 0.4 .. 0.9 %
     // wide then instead of 3 .. 6 % (Gaussian to Student-t(3) values, 1 Mi; with 8192 bins 0.5 .. 1.2 %), and
     // the bins that boundaries fall into hold 15 % more.  So searches that end with k_decide do it, and those before
-    // sketch bins, whose boundaries lie in the tails (1.6 G values: k_sketch_score 2.73 ms with it, 2.76 without,
+    // sketch bins, whose boundaries lie in the tails (1.9 G values: k_sketch_score 2.73 ms with it, 2.76 without,
     // k_quant 2.11, 2.13), but none with scores (6.7 G values, 105 configurations: k_split 3.74 and k_bucket 5.70 ms
-    // with it, 3.14 and 5.13 without).
+    // with it, 3.13 and 5.11 without).
     u32 my_flags[PER], my_least[PER]; // least depth
     float my_w[PER];
     double q = 0.0, my_q[PER];
