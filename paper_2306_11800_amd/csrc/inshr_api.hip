@@ -1290,8 +1290,7 @@ int sketch_with_state(inshr_ctx *c, const inshr_config *cfg, const uint32_t *whi
     const size_t o_info = cv.take(sizeof(SketchInfo) * nT);
     const size_t o_hist = cv.take(sizeof(u32) * SK_HIST * nT);
     const size_t o_xq = cv.take(sizeof(double) * SK_HIST * nT);
-    const size_t o_w = cv.take(sizeof(double) * SK_HIST * nT);
-    const size_t o_d = cv.take(sizeof(double) * SK_HIST * nT);
+    const size_t o_wd = cv.take(2 * sizeof(double) * SK_HIST * nT);
     const size_t n_sets = multi ? SK_SETS : 1;
     const size_t o_key = cv.take(sizeof(u32) * 256 * n_sets * nT);
     const size_t o_cb = cv.take(sizeof(float) * 256 * n_sets * nT);
@@ -1332,8 +1331,7 @@ int sketch_with_state(inshr_ctx *c, const inshr_config *cfg, const uint32_t *whi
     P.uniforms = (const double *)(db + o_uni);
     P.hist = (u32 *)(db + o_hist);
     P.xq = (double *)(db + o_xq);
-    P.w = (double *)(db + o_w);
-    P.d = (double *)(db + o_d);
+    P.wd = (double *)(db + o_wd);
     P.alt_key = (u32 *)(db + o_key);
     P.alt_cb = (float *)(db + o_cb);
     P.info = (SketchInfo *)(db + o_info);

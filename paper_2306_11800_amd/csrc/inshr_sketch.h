@@ -37,7 +37,7 @@ struct SketchParams {
     const double *rep;     // [n_idx] 2 gamma^(i_lo + b) / (gamma + 1)
     const double *uniforms; // [nT][256] the random numbers of the draws
     u32 *hist;             // [nT][SK_HIST], zero on entry
-    double *xq, *w, *d;    // [nT][SK_HIST] bucket values, weights, squared distances
+    double *xq, *wd;       // [nT][SK_HIST] bucket values; pairs of weight and squared distance or product
     u32 *alt_key;          // [nT][256] boundary keys where the quantizer looks for them
     float *alt_cb;         // [nT][256] codebook
     SketchInfo *info;      // [nT]

@@ -13,10 +13,10 @@
 //                    histogram (positive buckets, negative buckets, zeros).  Zeros and denormals,
 //                    whose ranges are wider, are set aside and search the bucket list.
 //   k_sketch_kmeans  one workgroup per tensor: compacts the non-empty buckets, draws the K
-//                    starting centres (running sums by a block scan, the draw itself by the one
-//                    thread whose share holds it), then Lloyd rounds on the sorted list — a
+//                    starting centres (one wave with the buckets in its registers: running sums by a
+//                    scan), then Lloyd rounds on the sorted list by a wave per set of centres — a
 //                    cluster is a contiguous run of buckets, found by bisection on the midpoints
-//                    and summed in index order by one thread — until the runs repeat.
+//                    and summed in index order by one lane — until the runs repeat.
 //                    All arithmetic is fp64 without contraction (products and sums rounded
 //                    separately).  For the search over the bit width (Sec. 5 restricted to the
 //                    number of bins) the draws are made once for 256 clusters and the rounds run
@@ -30,6 +30,8 @@
 //   k_sketch_choose  per tensor: the error of every set from the slot moments, the fewest bits
 //                    within the bound, and that set's keys and centres for the quantizer.
 #include "inshr_sketch.h"
+
+#include <type_traits>
 
 // The clustering follows its definition operation by operation: no product may be fused into the
 // sum that takes it.  The __dmul_rn / __dadd_rn of the HIP headers are plain operators compiled with
@@ -184,15 +186,305 @@ __device__ __forceinline__ double slot_value(u32 slot, const SketchParams &P)
     return -P.rep[slot - (u32)SK_MAX_IDX];
 }
 
-__global__ __launch_bounds__(BLOCK) void k_sketch_kmeans(const GridDesc *__restrict__ gd,
-                                                         const SketchDesc *__restrict__ sd,
-                                                         SketchParams P)
+// Inclusive prefix sum of non-negative numbers over the 64 lanes, with data-parallel-primitive moves as in
+// wave_incl_scan, and the value of the lane below (0 in lane 0).
+template <int CTRL, int ROWS> __device__ __forceinline__ double moved(double x)
 {
-    __shared__ u32 s_u32[BLOCK / 64 + 2];
-    __shared__ double s_red[2 * (BLOCK / 64)];
+    const u64 b = (u64)__double_as_longlong(x);
+    const u32 lo = (u32)__builtin_amdgcn_update_dpp(0, (int)(u32)b, CTRL, ROWS, 0xf, ROWS == 0xf);
+    const u32 hi = (u32)__builtin_amdgcn_update_dpp(0, (int)(u32)(b >> 32), CTRL, ROWS, 0xf, ROWS == 0xf);
+    return __longlong_as_double((long long)(((u64)hi << 32) | lo));
+}
+__device__ __forceinline__ double wave_incl_sum(double x)
+{
+    x = add_rn(x, moved<0x111, 0xf>(x));
+    x = add_rn(x, moved<0x112, 0xf>(x));
+    x = add_rn(x, moved<0x114, 0xf>(x));
+    x = add_rn(x, moved<0x118, 0xf>(x));
+    x = add_rn(x, moved<0x142, 0xa>(x));
+    return add_rn(x, moved<0x143, 0xc>(x));
+}
+__device__ __forceinline__ double lane_below(double x) { return moved<0x138, 0xf>(x); }
+__device__ __forceinline__ double lane_value(double x, u32 lane)
+{
+    const u64 b = (u64)__double_as_longlong(x);
+    const u32 lo = (u32)__builtin_amdgcn_readlane((int)(u32)b, (int)lane);
+    const u32 hi = (u32)__builtin_amdgcn_readlane((int)(u32)(b >> 32), (int)lane);
+    return __longlong_as_double((long long)(((u64)hi << 32) | lo));
+}
+
+constexpr int KM_BLOCK = 512; // threads of a clustering workgroup (256 registers each: see draw_centres)
+typedef double d2 __attribute__((ext_vector_type(2)));
+
+// Weighted K-Means++ draws (Algorithm 3) by one wave, from a list of at most 64 * PER buckets of which a lane keeps PER,
+// value, weight and distance, in registers: a draw waits for nobody.  Per draw a lane adds the probabilities of its
+// buckets up, a scan gives the running sums of the lanes, and the first lane whose running sum exceeds the target
+// finds its bucket (every lane looks, one is asked).  Bound by the chain of dependent fp64 operations: 256 draws
+// from up to 256 / 384 / 1024 / 1536 buckets 65 / 89 / 152 / 200 us (by all waves, two barriers a draw and three from more than
+// 1024 buckets: 200 us and more).  xw: weights in x.
+template <u32 PER, class T, class D>
+__device__ __forceinline__ void draw_centres(const T *xq, const D *xw, u32 m, u32 K, const double *uni, double *craw)
+{
+    const u32 lane = threadIdx.x & 63u, lo = lane * PER;
+    double x[PER], v[PER], d[PER];
+#pragma unroll
+    for (u32 q = 0; q < PER; q++) {
+        const u32 i = lo + q < m ? lo + q : m - 1u;
+        x[q] = xq[i];
+        v[q] = lo + q < m ? xw[i].x : 0.0;
+        d[q] = 1.0; // (the first draw's probabilities are the weights)
+    }
+    double xj = 0.0;
+    for (u32 r = 0; r < K; r++) {
+        double upto[PER];
+        upto[0] = mul_rn(d[0], v[0]);
+#pragma unroll
+        for (u32 q = 1; q < PER; q++) upto[q] = add_rn(upto[q - 1u], mul_rn(d[q], v[q]));
+        const double inc = wave_incl_sum(upto[PER - 1u]), before = lane_below(inc), total = lane_value(inc, 63u);
+        if (r == 0u || total > 0.0) { // (else every bucket is a centre already: the last one again)
+            const double target = mul_rn(uni[r], total);
+            const u64 above = __ballot(lo < m && inc > target);
+            if (above) {
+                // (where rounding leaves no sum of the lane above: its last bucket that can be drawn)
+                double rest = sub_rn(target, before);
+                const double whole = upto[PER - 1u];
+                rest = whole > rest ? rest : __longlong_as_double(__double_as_longlong(whole) - 1ll);
+                double pick = x[PER - 1u];
+#pragma unroll
+                for (u32 q = PER - 1u; q-- > 0u;) pick = upto[q] > rest ? x[q] : pick;
+                xj = lane_value(pick, (u32)__builtin_ctzll(above));
+            } else { // no running sum exceeds the target (rounding): the last bucket that can be drawn
+                double pick = x[0];
+                bool some = false;
+#pragma unroll
+                for (u32 q = 0; q < PER; q++) {
+                    const bool is = mul_rn(d[q], v[q]) > 0.0;
+                    pick = is ? x[q] : pick;
+                    some |= is;
+                }
+                const u64 can = __ballot(some);
+                xj = lane_value(pick, can ? 63u - (u32)__builtin_clzll(can) : 0u);
+            }
+        }
+        if (lane == 0u) craw[r] = xj;
+#pragma unroll
+        for (u32 q = 0; q < PER; q++) {
+            const double df = sub_rn(x[q], xj), d2 = mul_rn(df, df);
+            d[q] = (r == 0u || d2 < d[q]) ? d2 : d[q];
+        }
+    }
+}
+// The same from longer lists, by all threads; the distances in y of xw.
+template <class T, class D>
+__device__ __forceinline__ void draw_centres_long(const T *xq, D *xw, u32 m, u32 K, const double *uni, double *craw,
+                                                  double *s_red, u32 *s_pick, u32 *s_last, u32 &s_chosen)
+{
+    const u32 tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const u32 per = (m + KM_BLOCK - 1u) / KM_BLOCK;
+    const u32 lo = tid * per < m ? tid * per : m, hi = lo + per < m ? lo + per : m;
+    if (tid < 2u) {
+        s_pick[tid] = 0xFFFFFFFFu;
+        s_last[tid] = 0u;
+    }
+    __syncthreads();
+    // Per draw: (1) every thread sums the probabilities of its share, a scan gives the running
+    // sums inside the wave, the wave totals go to LDS; (2) every thread adds the totals of the
+    // waves before its own (in wave order) and the first thread whose running sum exceeds the
+    // target announces itself; (3) that thread walks its share.  The LDS cells alternate between two copies
+    // from draw to draw, so that a draw never waits for the cells of the one before to be read.
+    for (u32 r = 0; r < K; r++) {
+        const u32 cp = r & 1u;
+        double inc = 0.0;
+        u32 last_pos = 0u; // last bucket of the share that could be drawn, + 1
+        for (u32 i = lo; i < hi; i++) {
+            const d2 b = xw[i];
+            const double p = r ? mul_rn(b.y, b.x) : b.x;
+            inc = add_rn(inc, p);
+            if (p > 0.0) last_pos = i + 1u;
+        }
+        inc = wave_incl_sum(inc);
+        const double before = lane_below(inc);
+        if (lane == 63u) s_red[cp * (KM_BLOCK / 64) + wave] = inc;
+        __syncthreads();
+        double wbase = 0.0, total = 0.0;
+        for (u32 wv = 0; wv < KM_BLOCK / 64; wv++) {
+            if (wv == wave) wbase = total;
+            total = add_rn(total, s_red[cp * (KM_BLOCK / 64) + wv]);
+        }
+        if (r > 0u && !(total > 0.0)) { // every bucket is a centre already: repeat the last one
+            if (tid == 0) craw[r] = craw[r - 1u];
+            continue; // (nothing of this draw's cells is used again before two more barriers)
+        }
+        const double target = mul_rn(uni[r], total);
+        const double excl = add_rn(wbase, before), incl = add_rn(wbase, inc);
+        // one atomic per wave: its first lane above the target, its last lane with a drawable bucket
+        const u64 above = __ballot(incl > target && lo < hi), drawable = __ballot(last_pos != 0u);
+        if (above && lane == (u32)__builtin_ctzll(above)) atomicMin(&s_pick[cp], tid);
+        if (drawable && lane == 63u - (u32)__builtin_clzll(drawable)) atomicMax(&s_last[cp], last_pos);
+        __syncthreads();
+        const u32 pick = s_pick[cp];
+        if (tid == (pick == 0xFFFFFFFFu ? 0u : pick)) {
+            // no running sum exceeds the target (rounding): the last bucket that could be drawn
+            u32 jj = s_last[cp] ? s_last[cp] - 1u : 0u;
+            if (pick != 0xFFFFFFFFu) {
+                double run = excl; // the running sum at the start of this thread's share
+                jj = last_pos ? last_pos - 1u : lo;
+                for (u32 i = lo; i < hi; i++) {
+                    const d2 b = xw[i];
+                    run = add_rn(run, r ? mul_rn(b.y, b.x) : b.x);
+                    if (run > target) {
+                        jj = i;
+                        break;
+                    }
+                }
+            }
+            s_chosen = jj;
+            craw[r] = xq[jj];
+            s_pick[cp ^ 1u] = 0xFFFFFFFFu;
+            s_last[cp ^ 1u] = 0u;
+        }
+        __syncthreads();
+        const double cj = xq[s_chosen];
+        for (u32 i = lo; i < hi; i++) {
+            const double df = sub_rn(xq[i], cj), dd = mul_rn(df, df), old = xw[i].y;
+            xw[i].y = (r == 0u || dd < old) ? dd : old;
+        }
+    }
+}
+
+// Weights and products of the run [i, e) of a list, each added up in index order.  PADDED: 15 entries may be read past
+// the list's end; eight entries are then asked for before the eight before them are added: about 14 ns a bucket,
+// 25 with eight reads and the sums of what they bring in turn.
+template <bool PADDED, class D> __device__ __forceinline__ d2 run_sum(const D *xw, u32 i, u32 e)
+{
+    double sw = 0.0, sx = 0.0;
+    if (!PADDED) {
+        for (; i < e; i++) {
+            const d2 b = xw[i];
+            sw = add_rn(sw, b.x);
+            sx = add_rn(sx, b.y);
+        }
+        return d2{sw, sx};
+    }
+    constexpr u32 N = 8;
+    d2 a[N], b[N];
+    auto ask = [&](d2 (&to)[N]) {
+#pragma unroll
+        for (u32 j = 0; j < N; j++) to[j] = xw[i + j];
+    };
+    auto add = [&](const d2 (&from)[N]) {
+#pragma unroll
+        for (u32 j = 0; j < N; j++) {
+            sw = add_rn(sw, from[j].x);
+            sx = add_rn(sx, from[j].y);
+        }
+    };
+    auto add_rest = [&](const d2 (&from)[N]) { // (a sum that starts at +0.0 does not change by another +0.0)
+#pragma unroll
+        for (u32 j = 0; j < N; j++) {
+            sw = add_rn(sw, i + j < e ? from[j].x : 0.0);
+            sx = add_rn(sx, i + j < e ? from[j].y : 0.0);
+        }
+    };
+    if (i >= e) return d2{0.0, 0.0};
+    ask(a);
+    while (e - i > 2u * N) {
+        i += N;
+        ask(b);
+        add(a);
+        i += N;
+        ask(a);
+        add(b);
+    }
+    if (e - i > N) {
+        i += N;
+        ask(b);
+        add(a);
+        add_rest(b);
+    } else {
+        add_rest(a);
+    }
+    return d2{sw, sx};
+}
+
+// Weighted Lloyd rounds of one set of Kb centres by one wave, from the sorted centres c_set, which it leaves the last
+// ones in; the number of rounds is returned.  Cluster k = the buckets in (midpoint k-1, midpoint k], a run of the
+// sorted list, belongs to lane k % 64.  No wave waits for another set's rounds, and a cluster whose run is the one of
+// the round before keeps its centre.  Bound by the longest run that changed: a cluster around zero can hold
+// half of the buckets.
+template <u32 Q, bool PADDED, class T, class D>
+__device__ __forceinline__ u32 lloyd_rounds(const T *xq, const D *xw, u32 m, u32 Kb, double *c_set, u32 max_iter)
+{
+    const u32 lane = threadIdx.x & 63u;
+    double c[Q];
+    u32 first[Q], end[Q], steps = 1u; // steps: a power of two above m
+    while (steps <= m) steps <<= 1;
+#pragma unroll
+    for (u32 q = 0; q < Q; q++) {
+        c[q] = q * 64u + lane < Kb ? c_set[q * 64u + lane] : 0.0;
+        first[q] = end[q] = 0xFFFFFFFFu;
+    }
+    u32 rounds = 0u;
+    for (u32 it = 0; it < max_iter; it++) {
+        double mid[Q];
+        u32 a[Q];
+#pragma unroll
+        for (u32 q = 0; q < Q; q++) {
+            double below = lane_below(c[q]);
+            const double across = lane_value(c[q > 0u ? q - 1u : 0u], 63u);
+            if (q > 0u) below = lane == 0u ? across : below;
+            mid[q] = mul_rn(add_rn(below, c[q]), 0.5);
+            a[q] = 0u;
+        }
+        for (u32 step = steps >> 1; step > 0u; step >>= 1) { // buckets up to the midpoint
+#pragma unroll
+            for (u32 q = 0; q < Q; q++) {
+                const u32 to = a[q] + step;
+                const double x = xq[(to < m ? to : m) - 1u];
+                a[q] = to <= m && !(x > mid[q]) ? to : a[q];
+            }
+        }
+        bool again[Q], other = false;
+#pragma unroll
+        for (u32 q = 0; q < Q; q++) {
+            const u32 k = q * 64u + lane;
+            a[q] = k == 0u ? 0u : k < Kb ? a[q] : m;
+        }
+#pragma unroll
+        for (u32 q = 0; q < Q; q++) {
+            const u32 next = q + 1u < Q ? (u32)__builtin_amdgcn_readlane((int)a[q + 1u < Q ? q + 1u : q], 0) : m;
+            const u32 up = __shfl_down(a[q], 1), e = lane == 63u ? next : up;
+            other |= a[q] != first[q];
+            again[q] = a[q] != first[q] || e != end[q];
+            first[q] = a[q];
+            end[q] = e;
+        }
+        if (__ballot(other) == 0ull) break;
+#pragma unroll
+        for (u32 q = 0; q < Q; q++) {
+            if (!again[q]) continue;
+            const d2 s = run_sum<PADDED>(xw, first[q], end[q]);
+            if (s.x > 0.0) c[q] = div_rn(s.y, s.x);
+        }
+        rounds++;
+    }
+#pragma unroll
+    for (u32 q = 0; q < Q; q++)
+        if (q * 64u + lane < Kb) c_set[q * 64u + lane] = c[q];
+    return rounds;
+}
+
+// One workgroup per tensor, bound by the latency of one wave's draws and Lloyd rounds.  74 tensors of 390 buckets:
+// 0.62 ms -> 0.31; 17 of up to 300 buckets: 0.36 -> 0.15; 33 of about 1000: 2.1 -> 0.8 ms (before: a bucket per thread, all
+// sets' rounds in step, every cluster added up in every round).
+__global__ __launch_bounds__(KM_BLOCK) void k_sketch_kmeans(const GridDesc *__restrict__ gd,
+                                                            const SketchDesc *__restrict__ sd,
+                                                            SketchParams P)
+{
+    constexpr u32 WAVES = KM_BLOCK / 64;
+    __shared__ u32 s_n[WAVES], s_max[WAVES], s_pick[2], s_last[2], s_rounds[SK_SETS], s_chosen;
+    __shared__ double s_red[2 * WAVES];
     __shared__ double cen[512], craw[256]; // the sorted centres of every set, those of 2 << (set + 1) from 4 * (2 ^ set - 1)
-    __shared__ u32 seg[512 + SK_SETS];     // first buckets of the clusters, [clusters] = m
-    __shared__ u32 s_max[BLOCK / 64], s_pick[2], s_last[2], s_changed[SK_SETS], s_live, s_chosen;
     const int t = blockIdx.x;
     const SketchDesc s = sd[t];
     if (!s.active) return;
@@ -202,49 +494,51 @@ __global__ __launch_bounds__(BLOCK) void k_sketch_kmeans(const GridDesc *__restr
     const u32 K = P.multi ? 256u : 1u << gd->cfg_bits[s.cfg];
     const u32 n_sets = P.multi ? (u32)SK_SETS : 1u;
     const u32 *h = P.hist + (size_t)t * SK_HIST;
-    // bucket values, weights and squared distances: in LDS when the list is short enough (a few
+    // bucket values; weights and, in turn, squared distances or products: in LDS when the list is short enough (a few
     // hundred to a few thousand buckets is the rule), else in the tensor's scratch rows
-    __shared__ double l_x[SK_LDS], l_w[SK_LDS], l_d[SK_LDS];
+    __shared__ double l_x[SK_LDS];
+    __shared__ d2 l_w[SK_LDS + 16];
 
-    // ---- the non-empty buckets in value order (Algorithm 1: unique with counts) ----
-    constexpr u32 PER = (SK_HIST + BLOCK - 1) / BLOCK;
-    u32 mine = 0u, cmax = 0u;
-    for (u32 i = 0; i < PER; i++) {
-        const u32 v = tid * PER + i;
-        const u32 c = v < (u32)SK_HIST ? h[slot_in_value_order(v)] : 0u;
-        mine += c ? 1u : 0u;
-        cmax = c > cmax ? c : cmax;
-    }
-    u32 inc = wave_incl_scan(mine);
+    // ---- the non-empty buckets in value order (Algorithm 1: unique with counts); a wave has whole rows of 64 ----
+    constexpr u32 ROWS = (SK_HIST + KM_BLOCK - 1) / KM_BLOCK;
+    u32 cnt[ROWS], mine = 0u, cmax = 0u;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const u32 y = __shfl_xor(cmax, o);
-        cmax = y > cmax ? y : cmax;
+    for (u32 i = 0; i < ROWS; i++) {
+        const u32 v = (wave * ROWS + i) * 64u + lane;
+        cnt[i] = v < (u32)SK_HIST ? h[slot_in_value_order(v)] : 0u;
     }
-    if (lane == 63u) s_u32[tid >> 6] = inc;
-    if (lane == 0u) s_max[tid >> 6] = cmax;
+#pragma unroll
+    for (u32 i = 0; i < ROWS; i++) {
+        mine += (u32)__popcll(__ballot(cnt[i] != 0u));
+        cmax = cnt[i] > cmax ? cnt[i] : cmax;
+    }
+    cmax = (u32)__builtin_amdgcn_readlane((int)wave_incl_max(cmax), 63);
+    if (lane == 0u) {
+        s_n[wave] = mine;
+        s_max[wave] = cmax;
+    }
     __syncthreads();
     u32 base = 0u, m = 0u, maxc = 0u;
-    for (u32 wv = 0; wv < BLOCK / 64; wv++) {
-        const u32 y = s_u32[wv];
-        if (wv < (tid >> 6)) base += y;
+    for (u32 wv = 0; wv < WAVES; wv++) {
+        const u32 y = s_n[wv];
+        if (wv < wave) base += y;
         m += y;
         maxc = s_max[wv] > maxc ? s_max[wv] : maxc;
     }
     // the rest, for bucket lists in LDS or in device memory
-    auto cluster = [&](auto *xq, auto *w, auto *dist) {
-        u32 pos = base + inc - mine;
-        for (u32 i = 0; i < PER; i++) {
-            const u32 v = tid * PER + i;
-            const u32 slot = slot_in_value_order(v < (u32)SK_HIST ? v : 0u);
-            const u32 c = v < (u32)SK_HIST ? h[slot] : 0u;
-            if (c) {
-                xq[pos] = slot_value(slot, P);
-                w[pos] = (double)c; // the count, replaced by the weight below
-                pos++;
+    auto cluster = [&](auto *xq, auto *xw, auto in_lds) {
+        constexpr bool LDS = decltype(in_lds)::value;
+        u32 pos = base;
+#pragma unroll
+        for (u32 i = 0; i < ROWS; i++) {
+            const u64 some = __ballot(cnt[i] != 0u);
+            if (cnt[i]) {
+                const u32 at = pos + __builtin_amdgcn_mbcnt_hi((u32)(some >> 32), __builtin_amdgcn_mbcnt_lo((u32)some, 0u));
+                xq[at] = slot_value(slot_in_value_order((wave * ROWS + i) * 64u + lane), P);
+                xw[at].x = (double)cnt[i]; // the count, replaced by the weight below
             }
+            pos += (u32)__popcll(some);
         }
-        __syncthreads();
         if (m == 0u) { // (cannot happen: at least one value lies between the thresholds)
             if (tid == 0) {
                 P.info[t].n_buckets = 0u;
@@ -252,239 +546,95 @@ __global__ __launch_bounds__(BLOCK) void k_sketch_kmeans(const GridDesc *__restr
             }
             return;
         }
+        double *uni = cen; // the draws' random numbers (the sorted centres take this array afterwards)
+        if (tid < 256u) uni[tid] = P.uniforms[(size_t)t * 256 + tid];
+        __syncthreads();
         // ---- sample weights (Algorithm 2): sigma * C / max C + (1 - sigma) * |X| / max |X| ----
         const double x_first = fabs(xq[0]), x_last = fabs(xq[m - 1u]);
         const double mx = x_first > x_last ? x_first : x_last;
         const double one_minus = sub_rn(1.0, P.sigma);
-        __syncthreads();
-        for (u32 i = tid; i < m; i += BLOCK) {
-            const double c_hat = div_rn(w[i], (double)maxc);
+        for (u32 i = tid; i < m; i += KM_BLOCK) {
+            const double c_hat = div_rn(xw[i].x, (double)maxc);
             const double x_hat = mx > 0.0 ? div_rn(fabs(xq[i]), mx) : 0.0;
-            w[i] = add_rn(mul_rn(P.sigma, c_hat), mul_rn(one_minus, x_hat));
+            xw[i].x = add_rn(mul_rn(P.sigma, c_hat), mul_rn(one_minus, x_hat));
         }
         __syncthreads();
-
-        // ---- weighted K-Means++ draws (Algorithm 3) ----
-        const u32 per = (m + BLOCK - 1u) / BLOCK;
-        const u32 lo = tid * per < m ? tid * per : m, hi = lo + per < m ? lo + per : m;
-        double *uni = cen; // the draws' random numbers (the sorted centres take this array afterwards)
-        if (tid < 256u) uni[tid] = P.uniforms[(size_t)t * 256 + tid];
-        if (tid < 2u) {
-            s_pick[tid] = 0xFFFFFFFFu;
-            s_last[tid] = 0u;
+        // ---- weighted K-Means++ draws ----
+        if (!LDS || m > 24u * 64u)
+            draw_centres_long(xq, xw, m, K, uni, craw, s_red, s_pick, s_last, s_chosen);
+        else if (wave == 0u) {
+            if (m <= 4u * 64u)
+                draw_centres<4>(xq, xw, m, K, uni, craw);
+            else if (m <= 6u * 64u)
+                draw_centres<6>(xq, xw, m, K, uni, craw);
+            else if (m <= 8u * 64u)
+                draw_centres<8>(xq, xw, m, K, uni, craw);
+            else if (m <= 12u * 64u)
+                draw_centres<12>(xq, xw, m, K, uni, craw);
+            else if (m <= 16u * 64u)
+                draw_centres<16>(xq, xw, m, K, uni, craw);
+            else
+                draw_centres<24>(xq, xw, m, K, uni, craw);
         }
         __syncthreads();
-        // Per draw: (1) every thread sums the probabilities of its share, a wave scan gives the running
-        // sums inside the wave, the wave totals go to LDS; (2) every thread adds the totals of the
-        // waves before its own (in wave order) and the first thread whose running sum exceeds the
-        // target announces itself; (3) that thread walks its share.  With at most one bucket per
-        // thread (the rule) step 3 is empty.  The LDS cells alternate between two copies from draw to
-        // draw, so that a draw never waits for the cells of the one before to be read.
-        // Waves without buckets only take part in the barriers (their sums are zero, and whatever they would find,
-        // the last bucket's thread finds too).  With one bucket per thread its value, weight and distance
-        // are registers.
-        const bool one = per == 1u;
-        const u32 n_act = (m + per * 64u - 1u) / (per * 64u);
-        double x1 = 0.0, w1 = 0.0, d1 = 0.0;
-        if (one && tid < m) {
-            x1 = xq[tid];
-            w1 = w[tid];
-        }
-        for (u32 r = 0; r < K; r++) {
-            const u32 cp = r & 1u;
-            double inc = 0.0, before = 0.0;
-            u32 last_pos = 0u; // last bucket of the share that could be drawn, + 1
-            if (wave < n_act) {
-                if (one) {
-                    inc = r ? mul_rn(d1, w1) : w1;
-                    last_pos = inc > 0.0 ? tid + 1u : 0u;
-                } else {
-                    for (u32 i = lo; i < hi; i++) {
-                        const double p = r ? mul_rn(dist[i], w[i]) : w[i];
-                        inc = add_rn(inc, p);
-                        if (p > 0.0) last_pos = i + 1u;
-                    }
-                }
-#pragma unroll
-                for (int o = 1; o < 64; o <<= 1) {
-                    const double y = __shfl_up(inc, o);
-                    if ((int)lane >= o) inc = add_rn(inc, y);
-                }
-                before = __shfl_up(inc, 1); // inclusive value of the lane below
-                if (lane == 63u) s_red[cp * (BLOCK / 64) + wave] = inc;
+        // ---- every set's first centres, sorted, by a thread per centre (the random numbers in their place have been
+        // used); the products (the distances are done with) ----
+        auto each_centre = [&](auto &&f) { // f(set, number of its centres, centre)
+            for (u32 j = tid; j < (P.multi ? 508u : K); j += KM_BLOCK) {
+                const u32 set = P.multi ? 29u - (u32)__builtin_clz(j + 4u) : 0u; // (centres of narrower sets before: (4 << set) - 4)
+                f(set, P.multi ? 4u << set : K, P.multi ? j + 4u - (4u << set) : j);
             }
-            __syncthreads();
-            double wbase = 0.0, total = 0.0;
-            for (u32 wv = 0; wv < n_act; wv++) {
-                if (wv == wave) wbase = total;
-                total = add_rn(total, s_red[cp * (BLOCK / 64) + wv]);
-            }
-            if (r > 0u && !(total > 0.0)) { // every bucket is a centre already: repeat the last one
-                if (tid == 0) craw[r] = craw[r - 1u];
-                continue; // (nothing of this draw's cells is used again before two more barriers)
-            }
-            const double target = mul_rn(uni[r], total);
-            const double excl = lane ? add_rn(wbase, before) : wbase;
-            if (wave < n_act) { // one atomic per wave: its first lane above the target, its last lane with a drawable bucket
-                const double incl = add_rn(wbase, inc);
-                const u64 above = __ballot(incl > target && lo < hi), drawable = __ballot(last_pos != 0u);
-                if (above && lane == (u32)__builtin_ctzll(above)) atomicMin(&s_pick[cp], tid);
-                if (drawable && lane == 63u - (u32)__builtin_clzll(drawable)) atomicMax(&s_last[cp], last_pos);
-            }
-            __syncthreads();
-            const u32 pick = s_pick[cp];
-            u32 j;
-            if (one) {
-                // no running sum exceeds the target (rounding): the last bucket that could be drawn
-                j = pick != 0xFFFFFFFFu ? pick : (s_last[cp] ? s_last[cp] - 1u : 0u);
-                if (tid == 0) {
-                    craw[r] = xq[j];
-                    s_pick[cp ^ 1u] = 0xFFFFFFFFu;
-                    s_last[cp ^ 1u] = 0u;
-                }
-                const double df = sub_rn(x1, xq[j]);
-                const double d2 = mul_rn(df, df);
-                d1 = (r == 0u || d2 < d1) ? d2 : d1;
-            } else {
-                if (tid == (pick == 0xFFFFFFFFu ? 0u : pick)) {
-                    u32 jj = s_last[cp] ? s_last[cp] - 1u : 0u;
-                    if (pick != 0xFFFFFFFFu) {
-                        double run = excl; // the running sum at the start of this thread's share
-                        jj = last_pos ? last_pos - 1u : lo;
-                        for (u32 i = lo; i < hi; i++) {
-                            run = add_rn(run, r ? mul_rn(dist[i], w[i]) : w[i]);
-                            if (run > target) {
-                                jj = i;
-                                break;
-                            }
-                        }
-                    }
-                    s_chosen = jj;
-                    craw[r] = xq[jj];
-                    s_pick[cp ^ 1u] = 0xFFFFFFFFu;
-                    s_last[cp ^ 1u] = 0u;
-                }
-                __syncthreads();
-                j = s_chosen;
-                const double cj = xq[j];
-                for (u32 i = lo; i < hi; i++) {
-                    const double df = sub_rn(xq[i], cj);
-                    const double d2 = mul_rn(df, df);
-                    dist[i] = (r == 0u || d2 < dist[i]) ? d2 : dist[i];
-                }
-            }
-        }
-        __syncthreads();
-        // ---- the sets of centres, all at once: the widest takes the first waves, a cluster per thread --------------
-        // (one after the other, each with a few rounds of bisection and of sums by few threads, they took half of the
-        // kernel's 1.17 ms for 74 tensors; 0.59 ms so)
-        u32 set = n_sets - 1u, j0 = 0u; // this wave's set; its first thread
-        while (set > 0u && wave * 64u >= j0 + (4u << set)) j0 += ((4u << set) + 63u) & ~63u, set--;
-        const u32 bits = P.multi ? 2u + set : gd->cfg_bits[s.cfg], Kb = 1u << bits, k = tid - j0;
-        const bool mine_k = k < Kb; // (threads past the last set's: none)
-        double *c_set = cen + (P.multi ? (4u << set) - 4u : 0u);
-        u32 *seg_set = seg + (P.multi ? (4u << set) - 4u + set : 0u);
-        double c_raw = 0.0;
-        u32 rank = 0u;
-        if (mine_k) {
-            c_raw = craw[k];
+        };
+        each_centre([&](u32 set, u32 Kb, u32 k) {
+            const double c_raw = craw[k];
+            u32 rank = 0u;
             for (u32 i = 0; i < Kb; i++) {
                 const double y = craw[i];
                 rank += (y < c_raw || (y == c_raw && i < k)) ? 1u : 0u;
             }
-        }
-        if (tid < (u32)SK_SETS) s_changed[tid] = 0u;
-        if (tid == 0u) s_live = n_sets;
-        if (mine_k) { // (the draws' random numbers, which this array held, have been used)
-            c_set[rank] = c_raw;
-            if (k == 0u) seg_set[Kb] = m;
-        }
+            cen[(P.multi ? (4u << set) - 4u : 0u) + rank] = c_raw;
+        });
+        for (u32 i = tid; i < m; i += KM_BLOCK) xw[i].y = mul_rn(xw[i].x, xq[i]);
         __syncthreads();
-        // weighted Lloyd rounds: cluster k = buckets (mid[k-1], mid[k]]; a set whose clusters stay as they are is done
-        u32 rounds = 0u, first_prev = 0u;
-        bool busy = mine_k;
-        for (u32 it = 0; it < P.max_iter; it++) {
-            u32 first = 0u;
-            if (busy) {
-                if (k > 0u) {
-                    const double mid = mul_rn(add_rn(c_set[k - 1u], c_set[k]), 0.5);
-                    u32 a = 0u, b = m; // first bucket above the midpoint
-                    while (a < b) {
-                        const u32 c = (a + b) >> 1;
-                        if (xq[c] > mid)
-                            b = c;
-                        else
-                            a = c + 1u;
-                    }
-                    first = a;
-                }
-                seg_set[k] = first;
-                if (it == 0u || first_prev != first) s_changed[set] = it + 1u;
-                first_prev = first;
-            }
-            __syncthreads();
-            if (busy && s_changed[set] != it + 1u) {
-                busy = false;
-                if (k == 0u) atomicSub(&s_live, 1u);
-            }
-            if (busy) {
-                double sw = 0.0, swx = 0.0;
-                const u32 end = seg_set[k + 1u];
-                u32 i = first;
-                for (; i + 8u <= end; i += 8u) { // (eight reads in flight, added in order)
-                    double wi[8], xi[8];
-#pragma unroll
-                    for (u32 q = 0; q < 8u; q++) {
-                        wi[q] = w[i + q];
-                        xi[q] = xq[i + q];
-                    }
-#pragma unroll
-                    for (u32 q = 0; q < 8u; q++) {
-                        sw = add_rn(sw, wi[q]);
-                        swx = add_rn(swx, mul_rn(wi[q], xi[q]));
-                    }
-                }
-                for (; i < end; i++) {
-                    sw = add_rn(sw, w[i]);
-                    swx = add_rn(swx, mul_rn(w[i], xq[i]));
-                }
-                if (sw > 0.0) c_set[k] = div_rn(swx, sw);
-                rounds++;
-            }
-            __syncthreads();
-            if (!s_live) break; // (changes between the next two barriers only)
+        // ---- Lloyd rounds, a wave per set ----
+        static_assert(SK_SETS <= WAVES, "a wave per set");
+        if (wave < n_sets) {
+            const u32 Ks = P.multi ? 4u << wave : K;
+            double *c_set = cen + (P.multi ? Ks - 4u : 0u);
+            const u32 r = Ks <= 64u    ? lloyd_rounds<1, LDS>(xq, xw, m, Ks, c_set, P.max_iter)
+                          : Ks <= 128u ? lloyd_rounds<2, LDS>(xq, xw, m, Ks, c_set, P.max_iter)
+                                       : lloyd_rounds<4, LDS>(xq, xw, m, Ks, c_set, P.max_iter);
+            if (lane == 0u) s_rounds[wave] = r;
         }
         // ---- codebooks and boundaries ----
-        const u32 sh = 8u - bits;
         u32 *ak = P.alt_key + (size_t)t * n_sets * 256;
         float *acb = P.alt_cb + (size_t)t * n_sets * 256;
-        for (u32 i = tid; i < n_sets * 256u; i += BLOCK) {
+        for (u32 i = tid; i < n_sets * 256u; i += KM_BLOCK) {
             ak[i] = 0u;
             acb[i] = 0.0f;
         }
         __syncthreads();
-        if (mine_k) {
-            ak += set * 256u;
-            acb += set * 256u;
-            acb[k] = __double2float_rn(c_set[k]);
+        each_centre([&](u32 set, u32 Kb, u32 k) {
+            const double *c_set = cen + (P.multi ? Kb - 4u : 0u);
+            acb[set * 256u + k] = __double2float_rn(c_set[k]);
             if (k + 1u < Kb) {
-                const double a = (double)__double2float_rn(c_set[k]), b = (double)__double2float_rn(c_set[k + 1u]);
-                const double mid = mul_rn(add_rn(a, b), 0.5);
+                const double lo = (double)__double2float_rn(c_set[k]), hi = (double)__double2float_rn(c_set[k + 1u]);
+                const double mid = mul_rn(add_rn(lo, hi), 0.5);
                 // a value goes to the upper centre when it lies strictly above the midpoint: the
                 // boundary is the smallest fp32 number above it
-                ak[((k + 1u) << sh) - 1u] = key_of_float(__double2float_rd(mid)) + 1u;
+                ak[set * 256u + (k + 1u) * (256u / Kb) - 1u] = key_of_float(__double2float_rd(mid)) + 1u;
             }
-            if (k == 0u && P.multi) P.set_rounds[(size_t)t * SK_SETS + set] = rounds;
-        }
-        if (tid == 0) { // (the widest set's thread)
+        });
+        if (P.multi && tid < n_sets) P.set_rounds[(size_t)t * SK_SETS + tid] = s_rounds[tid];
+        if (tid == 0) { // (of the widest set)
             P.info[t].n_buckets = m;
-            P.info[t].rounds = rounds;
+            P.info[t].rounds = s_rounds[n_sets - 1u];
         }
     };
     if (m <= (u32)SK_LDS)
-        cluster(l_x, l_w, l_d);
+        cluster(l_x, l_w, std::true_type());
     else
-        cluster(gptr(P.xq) + (size_t)t * SK_HIST, gptr(P.w) + (size_t)t * SK_HIST, gptr(P.d) + (size_t)t * SK_HIST);
+        cluster(gptr(P.xq) + (size_t)t * SK_HIST, gptr((d2 *)P.wd) + (size_t)t * SK_HIST, std::false_type());
 }
 
 // ------------------------------------------------------------------------------------------
@@ -867,7 +1017,7 @@ hipError_t launch_sketch(const Batch &bt, const SketchDesc *sd, const SketchPara
     else
         PROF("k_sketch_hist", s, k_sketch_hist<false><<<bt.n_wg_all, BLOCK, 0, s>>>(bt.td, bt.nT, bt.wg_tile0_all, nullptr,
                                                                                bt.gd, sd, P, bt.bufs));
-    PROF("k_sketch_kmeans", s, k_sketch_kmeans<<<bt.nT, BLOCK, 0, s>>>(bt.gd, sd, P));
+    PROF("k_sketch_kmeans", s, k_sketch_kmeans<<<bt.nT, KM_BLOCK, 0, s>>>(bt.gd, sd, P));
     if (P.multi) {
         PROF("k_sketch_score", s,
              k_sketch_score<<<bt.n_wg_all, BLOCK, 0, s>>>(bt.td, bt.nT, bt.wg_tile0_all, bt.gd, sd, P, bt.bufs));

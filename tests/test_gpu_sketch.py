@@ -79,6 +79,17 @@ def test_parameters(ctx):
         check(ctx, [x, -np.abs(x)], [(5, 100000, 1000), (6, 0, 0)], alpha, sigma, max_iter, 7)
 
 
+@pytest.mark.parametrize("m", [1, 64, 255, 256, 257, 384, 385, 512, 513, 768, 769, 1024, 1025, 1536, 1537, 4096, 4097])
+def test_lists_of_every_length(ctx, m):
+    """m non-empty buckets of both signs: the edges of what a lane keeps of them while the centres are drawn, of
+    the lists in LDS and of those in device memory."""
+    rng = np.random.default_rng(m)
+    neg = m // 3
+    mags = np.exp(0.0203 * (np.arange(m) - m // 2))
+    x = np.repeat(np.concatenate([-mags[:neg], mags[neg:]]), rng.integers(1, 4, m)).astype(np.float32)
+    check(ctx, [rng.permutation(x)], [(8 if m % 2 else 5, 0, 0)], 0.01, 0.2, 60, 2000 + m)
+
+
 def test_sums_are_not_contracted(ctx):
     """Eleven symmetric buckets, four clusters, magnitude-only weights: after the first Lloyd round
     the two inner centres are exact mirror images only if every product is rounded before it is
