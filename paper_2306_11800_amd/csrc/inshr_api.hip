@@ -727,12 +727,12 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         rc = check_results(c, nT, any_pooled);
         if (rc == 1) return run_search(c, tensors, nT, grid, n_cfg, eps, mode, group);
         if (rc) return rc;
-        // tensors whose choice the bounds leave open are scored
+        // tensors whose choice the bounds leave open are scored: the configuration it hangs on, or all of them
         std::vector<u32> open(nB, VIEW_NONE);
         bool any_open = false;
         for (uint32_t t = 0; t < nB; t++)
-            if (res[t].best == VIEW_NONE) {
-                open[t] = c->resolved[t] = VIEW_ALL;
+            if (res[t].best >= CHOICE_IF) {
+                open[t] = c->resolved[t] = res[t].best == VIEW_NONE ? VIEW_ALL : res[t].best & ~CHOICE_IF;
                 any_open = true;
             }
         if (!any_open) break;

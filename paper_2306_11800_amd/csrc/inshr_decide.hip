@@ -7,7 +7,8 @@
 // pair of the grid: of 32768 bins 259 hold an edge instead of up to 3885, the gathered keys of which took sweep 3,
 // the split and the group sort two thirds of a search (6.7 G values, 105 configurations: 16.8 of 25.0 ms;
 // k_decide in their place: 0.07 ms.  Search and quantizing together 33.4 -> 20.0 ms).
-// A tensor whose bounds leave the choice open is scored exactly (launch_resolve), as before.
+// Where one configuration's bounds leave the choice open, its exact error is worked out (launch_resolve with that
+// configuration in view) and settles it; a tensor with more of them is scored exactly, the whole grid.
 //
 // The bounds.  Let x^ be the sorted values with every value replaced by the middle of its bin's key range
 // (the order stays), F_P(y) = sum over the clusters of partition P of (y - mean)^2 + sum of the pruned y^2.
@@ -375,10 +376,18 @@ __global__ __launch_bounds__(BLOCK) void k_decide(const TDesc *__restrict__ td, 
                 bg = g2;
             }
         }
-        bool undecided = !usable;
-        if (bg != 0xFFFFFFFFu) {
+        // One configuration whose bounds leave it open, and nothing else: the choice hangs on its error alone, and
+        // what it is if that configuration is out is known.  (Of the tensors that stay open none has been seen with
+        // more: the bounds are a few tenths of a percent apart, the errors of neighbouring configurations far more.)
+        const bool any_sure = bg != 0xFFFFFFFFu;
+        u32 n_open = usable ? 0u : 2u, og = 0u;
+        bool undecided = false;
+        if (any_sure) {
             for (u32 g = lane; g < n_cfg; g += 64u)
-                undecided |= !(sh.hi[g] <= lim) && !(sh.lo[g] > lim) && (sh.cost[g] < bc || (sh.cost[g] == bc && g < bg));
+                if (!(sh.hi[g] <= lim) && !(sh.lo[g] > lim) && (sh.cost[g] < bc || (sh.cost[g] == bc && g < bg))) {
+                    n_open++;
+                    og = g;
+                }
         } else { // none surely within: settled where all are surely beyond and one is surely the most accurate
             float bh = __uint_as_float(0x7f800000u);
             for (u32 g = lane; g < n_cfg; g += 64u)
@@ -395,12 +404,25 @@ __global__ __launch_bounds__(BLOCK) void k_decide(const TDesc *__restrict__ td, 
                     bg = g2;
                 }
             }
-            for (u32 g = lane; g < n_cfg; g += 64u) undecided |= !(sh.lo[g] > lim) || (g != bg && !(sh.lo[g] > bh));
+            for (u32 g = lane; g < n_cfg; g += 64u) {
+                if (!(sh.lo[g] > lim)) {
+                    n_open++;
+                    og = g;
+                }
+                undecided |= g != bg && !(sh.lo[g] > bh);
+            }
         }
-        const bool open = __ballot(undecided) != 0ull;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const u32 g2 = __shfl_xor(og, o);
+            og = og > g2 ? og : g2; // (the only one, or of no account)
+        }
+        const u32 opens = wave_sum(n_open);
+        const bool open = opens > 1u || __ballot(undecided) != 0ull;
         if (lane == 0u) {
-            st->best = open ? VIEW_NONE : bg;
-            st->feasible = sh.hi[bg] <= lim ? 1u : 0u;
+            st->best = open ? VIEW_NONE : opens ? CHOICE_IF | og : bg;
+            st->feasible = st->feasible_else = any_sure ? 1u : 0u;
+            st->best_else = bg;
             store_result(st, B.res + t);
         }
     }

@@ -270,6 +270,7 @@ struct TState {
     double sumsq;                      // sum of x^2
     double thr_sumsq[MAX_THR];         // prune: sum x^2 over mag < tau; protect: over mag > tau
     u32 best, feasible;
+    u32 best_else, feasible_else;      // the choice if best (CHOICE_IF) turns out not to be within eps
 };
 
 struct SearchResult {    // what the host reads of a tensor's state

@@ -20,6 +20,9 @@ struct Unit {       // the tiles of one tensor that one workgroup of a sweep wal
 // Which configurations of the grid the boundaries, centres and errors of a tensor are worked out for
 // (`View` below): none, all, or one of them (its index).
 constexpr u32 VIEW_NONE = 0xFFFFFFFFu, VIEW_ALL = 0xFFFFFFFEu;
+// TState::best where the choice hangs on one configuration: its index with this bit set
+constexpr u32 CHOICE_IF = 0x80000000u;
+static_assert(MAX_CFG < (1 << 16), "no index looks like VIEW_ALL");
 
 struct Bufs { // device pointers, indexed by the tensor's position on the device unless noted; nB rows
               // (tensors searched by the sweeps) except ts, table2, tgt_key, codebook, scores (all)

@@ -61,6 +61,26 @@ def test_choice_alone(monkeypatch, grid, ordered):
     bare.close()
 
 
+@pytest.mark.parametrize("n", [16_385, 300_001, 2_500_000])
+def test_choice_that_hangs_on_one_configuration(n):
+    """A bound just above and just below one configuration's error, where a cheaper one may or may not be within it, and
+    where the most accurate one of all may or may not be: the choice of the scored search, and what quantizing gives
+    with it and with another configuration."""
+    g = GRIDS["full"]
+    x = dev(family(np.random.default_rng(47), 0, n))
+    scored, bare = api.Context(torch.device("cuda:0")), api.Context(torch.device("cuda:0"))
+    _, _, sc = scored.search([x], g, synth.EPS_DEFAULT)
+    rel = np.sort([s.sse / s.sumsq for s in sc])
+    for at in (rel[0], rel[20], rel[55]):
+        for eps in (at * (1 - 2e-4), at * (1 + 2e-4)):  # (closer than the bounds are, farther than rounding)
+            want, got = scored.search([x], g, float(eps)), bare.search([x], g, float(eps), want_scores=False)
+            assert (got[0][0], got[1][0]) == (want[0][0], want[1][0]), eps
+            for k in (want[0][0], (want[0][0] + 52) % len(g)):
+                same(bare.quantize([x], [g[k]], reuse_search=True), scored.quantize([x], [g[k]], reuse_search=True))
+    scored.close()
+    bare.close()
+
+
 def test_shares_of_the_pool_grow_in_the_quantizer(monkeypatch):
     """One value makes up most of the tensor and holds boundaries: all its keys are gathered."""
     rng = np.random.default_rng(42)
