@@ -24,6 +24,7 @@ struct DevBuf { // grow-only device allocation
 struct HostBuf { // grow-only pinned host allocation
     void *p = nullptr;
     size_t cap = 0;
+    bool lent = false; // a part of the context's own pinned block
 };
 
 } // namespace
@@ -44,9 +45,11 @@ struct inshr_ctx {
     uint32_t pool_wcap = 136;
     std::string last_err;
 
-    u32 *delta_flags = nullptr; // flag word of the delta kernels (DF_*), allocated with the context
+    char *pinned = nullptr;     // host memory allocated with the context (an allocation takes 80 us and more):
+                                // the flags and what the host buffers begin with
+    u32 *flags = nullptr;       // flag words of the delta kernels (DF_*), then those of calls that wait for theirs
     bool delta_pending = false; // an asynchronous delta call has not had its flags read yet
-    bool static_pending = false; // the same for inshr_delta_static (its flag word is in its own scratch)
+    bool static_pending = false; // the same for inshr_delta_static (its flag words are in its own scratch)
     DevBuf search_mem; // everything a search leaves behind for inshr_quantize
     DevBuf aux_mem;    // quantize descriptors, delta scratch
     DevBuf totals_mem; // symbol populations of a delta or reconstruct call, when aux_mem has a limit
@@ -57,7 +60,8 @@ struct inshr_ctx {
     std::vector<u32> sketch_cell, sketch_tops;
     std::vector<double> sketch_rep;
     HostBuf h_up;      // staging for descriptor uploads
-    HostBuf h_down;    // staging for result downloads
+    HostBuf h_down;    // results of a call, stored there by the kernels or downloaded
+    HostBuf h_res;     // what a search and the calls that work from its state say of every tensor (SearchResult)
 
     // state of the last search
     bool have_search = false;
@@ -66,7 +70,7 @@ struct inshr_ctx {
     std::vector<inshr_config> grid_cfgs;
     std::vector<inshr_tensor> tensors;
     std::vector<u32> pos;       // device position of tensors[t]
-    size_t res_off = 0, scores_off = 0;
+    size_t scores_off = 0;
     // (what the state holds of boundaries and centres, and what it takes to work out more of them)
     std::vector<u32> resolved;  // per device position: VIEW_NONE, VIEW_ALL or the one configuration
     std::vector<TDesc> td;
@@ -166,12 +170,11 @@ int ensure_dev(inshr_ctx *c, DevBuf &b, size_t bytes)
 int take_delta_flags(inshr_ctx *c)
 {
     if (!c->delta_pending && !c->static_pending) return INSHR_OK;
-    u32 f = 0, g = 0;
-    if (c->delta_pending) HIPCHK(c, hipMemcpy(&f, c->delta_flags, sizeof(u32), hipMemcpyDeviceToHost));
-    if (c->static_pending)
-        HIPCHK(c, hipMemcpy(&g, delta_static_flags(c->device), sizeof(u32), hipMemcpyDeviceToHost));
+    u32 f = 0, g[FLAG_WORDS] = {};
+    if (c->delta_pending) f = raised_flags(c->flags);
+    if (c->static_pending) HIPCHK(c, hipMemcpy(g, delta_static_flags(c->device), sizeof(g), hipMemcpyDeviceToHost));
     c->delta_pending = c->static_pending = false;
-    f |= g;
+    f |= raised_flags(g);
     if (f & DF_ORDER) {
         c->last_err = "delta: ranks from returning LDS atomics disagree with ballot ranks (set INSHR_NO_LDS_ORDER=1)";
         return INSHR_E_INTERNAL;
@@ -183,12 +186,22 @@ int take_delta_flags(inshr_ctx *c)
 int ensure_host(inshr_ctx *c, HostBuf &b, size_t bytes)
 {
     if (bytes <= b.cap) return INSHR_OK;
-    if (b.p) HIPCHK(c, hipHostFree(b.p));
+    if (b.p && !b.lent) HIPCHK(c, hipHostFree(b.p));
     b.p = nullptr;
     b.cap = 0;
+    b.lent = false;
+    bytes = (bytes + 255) & ~(size_t)255; // (copies are made in whole pieces)
     HIPCHK(c, hipHostMalloc(&b.p, bytes, hipHostMallocDefault));
     b.cap = bytes;
     return INSHR_OK;
+}
+
+// The flag words of a call that waits for them, clear.  Nothing in flight raises any.
+u32 *call_flags(inshr_ctx *c)
+{
+    u32 *f = c->flags + FLAG_WORDS;
+    memset(f, 0, FLAG_WORDS * sizeof(u32));
+    return f;
 }
 
 struct Carver { // lays sub-buffers out in one allocation, 256-byte aligned
@@ -202,7 +215,7 @@ struct Carver { // lays sub-buffers out in one allocation, 256-byte aligned
 };
 
 struct QuantScratch { // of inshr_quantize; the first up_bytes are uploaded
-    size_t qd, wg, un, up_bytes, qi, bytes;
+    size_t qd, wg, un, up_bytes, bytes;
     QuantScratch(uint32_t nT, uint32_t nB, int n_wg)
     {
         Carver cv;
@@ -210,7 +223,6 @@ struct QuantScratch { // of inshr_quantize; the first up_bytes are uploaded
         wg = cv.take(sizeof(u32) * (n_wg + 1));
         un = cv.take(sizeof(Unit) * ((size_t)n_wg + nB));
         up_bytes = cv.off;
-        qi = cv.take(sizeof(QInfo) * nT);
         bytes = cv.off;
     }
 };
@@ -332,10 +344,10 @@ void deal_tiles(const std::vector<TDesc> &td, uint32_t nB, const std::vector<u32
     for (uint32_t t = 0; t < nB; t++) p.t_off[t + 1] += p.t_off[t];
 }
 
-// Gather units for the tensors ts (device positions, ascending), on the device and in p.  The copy is staged
+// Gather units for the tensors ts (device positions, ascending), in p and, with st, on the device.  The copy is staged
 // at offset at of h_up: nothing in flight reads that part of it, and where it is too small to
 // hold it, nothing in flight reads any of it.
-int upload_units(inshr_ctx *c, const std::vector<u32> &view, const std::vector<u32> &ts, Partition &p, size_t at)
+int upload_units(inshr_ctx *c, const std::vector<u32> &view, const std::vector<u32> &ts, Partition &p, size_t at, Stage &st)
 {
     Batch &bt = c->batch;
     const uint32_t nB = (uint32_t)bt.nB;
@@ -354,8 +366,7 @@ int upload_units(inshr_ctx *c, const std::vector<u32> &view, const std::vector<u
     memcpy(hb + (c->gw_off - c->view_off), p.wg0.data(), sizeof(u32) * p.wg0.size());
     memcpy(hb + (c->tgo_off - c->view_off), p.t_off.data(), sizeof(u32) * (nB + 1));
     memcpy(hb + (c->gun_off - c->view_off), p.units.data(), sizeof(Unit) * p.units.size());
-    HIPCHK(c, hipMemcpyAsync(db + c->view_off, hb, c->gun_off - c->view_off + sizeof(Unit) * p.units.size(),
-                             hipMemcpyHostToDevice, c->stream));
+    st.add(db + c->view_off, hb, c->gun_off - c->view_off + sizeof(Unit) * p.units.size());
     bt.n_gwg = (int)p.wg0.size() - 1;
     bt.n_gunits = (int)p.units.size();
     return INSHR_OK;
@@ -371,8 +382,10 @@ int resolve(inshr_ctx *c, const std::vector<u32> &view, size_t at)
         if (view[t] != VIEW_NONE) ts.push_back(t);
     if (ts.empty()) return INSHR_OK;
     Partition p;
-    const int rc = upload_units(c, view, ts, p, at);
+    Stage st;
+    const int rc = upload_units(c, view, ts, p, at, st);
     if (rc) return rc;
+    HIPCHK(c, launch_stage(st, c->n_cu, c->stream));
     HIPCHK(c, launch_resolve(c->batch, c->stream));
     return INSHR_OK;
 }
@@ -389,12 +402,12 @@ constexpr uint32_t FUSE_MAX_PPM = 10000, FUSE_MIN_WCAP = 32;
 // not offered to INSHR_REUSE_SEARCH.
 enum { CHOOSE, SCORES, GIVEN, LIGHT };
 
-// The results of a search or of resolve(), which are in h_down: 1 when a wave's share of a gather pool was
+// The results of a search or of resolve(), which are in h_res: 1 when a wave's share of a gather pool was
 // too small and the search has to be repeated (with the larger pools that pool_wcap stands for now).
 int check_results(inshr_ctx *c, uint32_t nT, bool any_pooled)
 {
     const std::vector<u32> &pos = c->pos;
-    const SearchResult *res = (const SearchResult *)c->h_down.p;
+    const SearchResult *res = (const SearchResult *)c->h_res.p;
     for (uint32_t t = 0; t < nT; t++) {
         if (res[t].nonfinite) return INSHR_E_NONFINITE;
     }
@@ -569,7 +582,6 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         const size_t o_gsx = cv.take(full((size_t)nB * 2 * MAX_EDGES * 8));
         const size_t o_ms = cv.take(full((size_t)nB * MAX_SUB * 8));
         const size_t o_psel = cv.take(any_pooled ? (size_t)nB * 2 * SEL_WORDS * 4 : 0);
-        const size_t o_rs = cv.take(sizeof(SearchResult) * nT);
         const size_t o_tab = cv.take((size_t)nT * COARSE * 4);
         const size_t o_ut = cv.take((size_t)units * 16 * 4);
         const size_t o_bi = cv.take(full((size_t)nB * L2_BINS * 4));
@@ -606,6 +618,8 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         view_at = std::max(up_bytes, QuantScratch(nT, nB, n_wg).up_bytes);
         rc = ensure_host(c, c->h_up, view_at + (c->view_end - c->view_off));
         if (rc) return rc;
+        rc = ensure_host(c, c->h_res, sizeof(SearchResult) * nT);
+        if (rc) return rc;
         char *hb = (char *)c->h_up.p;
         char *db = (char *)c->search_mem.p;
         memcpy(hb + o_td, td.data(), sizeof(TDesc) * nT);
@@ -618,8 +632,10 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
             u64 *wa = (u64 *)(hb + o_wa);
             for (int w = 0; w <= n_wg_all; w++) wa[w] = all_tiles * (u64)w / (u64)n_wg_all;
         }
-        HIPCHK(c, hipMemcpyAsync(db, hb, up_bytes, hipMemcpyHostToDevice, c->stream));
-        HIPCHK(c, hipMemsetAsync(db + o_ts, 0, zero_end - o_ts, c->stream));
+        Stage up;
+        up.add(db, hb, up_bytes);
+        up.zero(db + o_ts, zero_end - o_ts);
+        HIPCHK(c, launch_stage(up, c->n_cu, c->stream));
 
         Batch &bt = c->batch;
         bt.td = (const TDesc *)(db + o_td);
@@ -649,7 +665,7 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         bt.n_tiles = all_tiles;
         Bufs &B = bt.bufs;
         B.ts = (TState *)(db + o_ts);
-        B.res = (SearchResult *)(db + o_rs);
+        B.res = (SearchResult *)c->h_res.p;
         B.hist1 = (u32 *)(db + o_h1);
         B.pool_h1 = (u32 *)(db + o_ph1);
         B.pool_sel = (u32 *)(db + o_psel);
@@ -694,7 +710,6 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         B.sub_cnt = (u32 *)(db + o_sbn);
         B.codebook = (float *)(db + o_cb);
         B.scores = (Score *)(db + o_sc);
-        c->res_off = o_rs;
         c->scores_off = o_sc;
     }
     c->batch.light = light;
@@ -713,16 +728,14 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
     }
 
     // results, in device order
-    const size_t rs_bytes = sizeof(SearchResult) * nT, sc_bytes = want_scores ? sizeof(Score) * (size_t)nT * n_cfg : 0;
-    rc = ensure_host(c, c->h_down, rs_bytes + std::max(sc_bytes, sizeof(QInfo) * nT));
+    const size_t sc_bytes = want_scores ? sizeof(Score) * (size_t)nT * n_cfg : 0;
+    rc = ensure_host(c, c->h_down, std::max(sc_bytes, sizeof(QInfo) * nT));
     if (rc) return rc;
     char *db = (char *)c->search_mem.p;
-    const SearchResult *res = (const SearchResult *)c->h_down.p;
+    const SearchResult *res = (const SearchResult *)c->h_res.p;
     for (;;) {
-        HIPCHK(c, hipMemcpyAsync(c->h_down.p, db + c->res_off, rs_bytes, hipMemcpyDeviceToHost, c->stream));
         if (sc_bytes)
-            HIPCHK(c, hipMemcpyAsync((char *)c->h_down.p + rs_bytes, db + c->scores_off, sc_bytes,
-                                     hipMemcpyDeviceToHost, c->stream));
+            HIPCHK(c, hipMemcpyAsync(c->h_down.p, db + c->scores_off, sc_bytes, hipMemcpyDeviceToHost, c->stream));
         HIPCHK(c, hipStreamSynchronize(c->stream));
         rc = check_results(c, nT, any_pooled);
         if (rc == 1) return run_search(c, tensors, nT, grid, n_cfg, eps, mode, group);
@@ -789,10 +802,6 @@ int resolve_all(inshr_ctx *c)
         HIPCHK(c, hipStreamSynchronize(c->stream));
         int rc = resolve(c, view, 0);
         if (rc) return rc;
-        rc = ensure_host(c, c->h_down, sizeof(SearchResult) * nT);
-        if (rc) return rc;
-        HIPCHK(c, hipMemcpyAsync(c->h_down.p, (char *)c->search_mem.p + c->res_off, sizeof(SearchResult) * nT,
-                                 hipMemcpyDeviceToHost, c->stream));
         HIPCHK(c, hipStreamSynchronize(c->stream));
         rc = check_results(c, nT, c->any_pooled);
         if (rc == 1) {
@@ -846,9 +855,24 @@ int inshr_create(inshr_ctx **out, int device, void *hip_stream, uint64_t scratch
             if (const char *e = getenv(name))
                 if (atoi(e) != 0) c->lds_ordered = false;
     }
-    if (hipMalloc(&c->delta_flags, 256) != hipSuccess || delta_static_init(device) != hipSuccess) {
-        delete c;
-        return INSHR_E_DEVICE;
+    {
+        const size_t n_flags = 256;
+        const struct { HostBuf *b; size_t bytes; } first[3] = {{&c->h_res, 16 << 10}, {&c->h_down, 16 << 10}, {&c->h_up, 64 << 10}};
+        size_t bytes = n_flags;
+        for (auto &f : first) bytes += f.bytes;
+        if (hipHostMalloc((void **)&c->pinned, bytes, hipHostMallocDefault) != hipSuccess || delta_static_init(device) != hipSuccess) {
+            if (c->pinned) (void)hipHostFree(c->pinned);
+            delete c;
+            return INSHR_E_DEVICE;
+        }
+        c->flags = (u32 *)c->pinned;
+        size_t at = n_flags;
+        for (auto &f : first) {
+            f.b->p = c->pinned + at;
+            f.b->cap = f.bytes;
+            f.b->lent = true;
+            at += f.bytes;
+        }
     }
     if (const char *e = getenv("INSHR_SAMPLE_MIN_N")) c->sample_min_n = strtoull(e, nullptr, 10);
     if (const char *e = getenv("INSHR_SAMPLE_FORCE_MISS")) c->sample_force_miss = atoi(e) != 0;
@@ -870,9 +894,9 @@ void inshr_destroy(inshr_ctx *c)
     if (c->totals_mem.p) (void)hipFree(c->totals_mem.p);
     if (c->sketch_mem.p) (void)hipFree(c->sketch_mem.p);
     if (c->sens_mem.p) (void)hipFree(c->sens_mem.p);
-    if (c->delta_flags) (void)hipFree(c->delta_flags);
-    if (c->h_up.p) (void)hipHostFree(c->h_up.p);
-    if (c->h_down.p) (void)hipHostFree(c->h_down.p);
+    for (const HostBuf *h : {&c->h_up, &c->h_down, &c->h_res})
+        if (h->p && !h->lent) (void)hipHostFree(h->p);
+    if (c->pinned) (void)hipHostFree(c->pinned);
     delete c;
 }
 
@@ -939,8 +963,8 @@ static void take_results(const inshr_ctx *c, uint32_t nT, uint32_t n_cfg, uint32
                          inshr_score *scores)
 {
     static_assert(sizeof(Score) == sizeof(inshr_score), "score layout");
-    const SearchResult *res = (const SearchResult *)c->h_down.p;
-    const Score *hsc = (const Score *)((const char *)c->h_down.p + sizeof(SearchResult) * nT);
+    const SearchResult *res = (const SearchResult *)c->h_res.p;
+    const Score *hsc = (const Score *)c->h_down.p;
     for (uint32_t t = 0; t < nT; t++) {
         const u32 p = c->pos[t];
         best[t] = res[p].best;
@@ -1017,14 +1041,15 @@ static int quantize_with_state(inshr_ctx *c, const inshr_config *cfg, inshr_quan
     }
     const uint32_t nB = (uint32_t)c->batch.nB;
     const QuantScratch lay(nT, nB, c->batch.n_wg);
-    const size_t o_qd = lay.qd, o_wg = lay.wg, o_un = lay.un, o_qi = lay.qi, up_bytes = lay.up_bytes;
+    const size_t o_qd = lay.qd, o_wg = lay.wg, o_un = lay.un, up_bytes = lay.up_bytes;
     int rc = ensure_dev(c, c->aux_mem, lay.bytes);
     if (rc) return rc;
     rc = ensure_host(c, c->h_up, up_bytes);
     if (rc) return rc;
-    rc = ensure_host(c, c->h_down, (sizeof(QInfo) + sizeof(SearchResult)) * nT);
+    rc = ensure_host(c, c->h_down, sizeof(QInfo) * nT);
     if (rc) return rc;
     char *db = (char *)c->aux_mem.p;
+    QInfo *const qi = (QInfo *)c->h_down.p;
     HIPCHK(c, hipStreamSynchronize(c->stream)); // staging buffers may be in flight (inshr_delta)
     // Tensors whose boundaries and centres the state does not hold are quantized in one sweep that works them
     // out (launch_fused).  Where that does not do (a protect fraction whose lists are long, or what the
@@ -1044,8 +1069,9 @@ static int quantize_with_state(inshr_ctx *c, const inshr_config *cfg, inshr_quan
                 open = true;
         }
         Partition p;
+        Stage up;
         if (!fuse.empty()) {
-            if ((rc = upload_units(c, view, fuse, p, up_bytes))) return rc;
+            if ((rc = upload_units(c, view, fuse, p, up_bytes, up))) return rc;
             for (u32 t : fuse) c->resolved[t] = VIEW_NONE;
         } else if (open) {
             ready.clear();
@@ -1074,19 +1100,13 @@ static int quantize_with_state(inshr_ctx *c, const inshr_config *cfg, inshr_quan
         memcpy(hb + o_qd, qd.data(), sizeof(QDesc) * nT);
         memcpy(hb + o_wg, pq.wg0.data(), sizeof(u32) * pq.wg0.size());
         memcpy(hb + o_un, pq.units.data(), sizeof(Unit) * pq.units.size());
-        HIPCHK(c, hipMemcpyAsync(db, hb, o_un + sizeof(Unit) * pq.units.size(), hipMemcpyHostToDevice, c->stream));
+        up.add(db, hb, o_un + sizeof(Unit) * pq.units.size());
+        HIPCHK(c, launch_stage(up, c->n_cu, c->stream));
         const QDesc *dq = (const QDesc *)(db + o_qd);
-        QInfo *dqi = (QInfo *)(db + o_qi);
-        if (!fuse.empty()) HIPCHK(c, launch_fused(c->batch, dq, dqi, c->stream));
+        if (!fuse.empty()) HIPCHK(c, launch_fused(c->batch, dq, qi, c->stream));
         HIPCHK(c, launch_quantize(c->batch, dq, (const Unit *)(db + o_un), (const u32 *)(db + o_wg),
-                                  (int)pq.wg0.size() - 1, dqi, c->stream));
+                                  (int)pq.wg0.size() - 1, qi, c->stream));
         const bool any = !fuse.empty() || open;
-        // (search results first: check_results looks for them there)
-        if (any)
-            HIPCHK(c, hipMemcpyAsync(c->h_down.p, (char *)c->search_mem.p + c->res_off, sizeof(SearchResult) * nT,
-                                     hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(c, hipMemcpyAsync((char *)c->h_down.p + sizeof(SearchResult) * nT, db + o_qi, sizeof(QInfo) * nT,
-                                 hipMemcpyDeviceToHost, c->stream));
         HIPCHK(c, hipStreamSynchronize(c->stream));
         if (!any) break;
         rc = check_results(c, nT, c->any_pooled);
@@ -1096,7 +1116,7 @@ static int quantize_with_state(inshr_ctx *c, const inshr_config *cfg, inshr_quan
             std::fill(done.begin(), done.end(), 0);
             continue;
         }
-        const SearchResult *res = (const SearchResult *)c->h_down.p;
+        const SearchResult *res = (const SearchResult *)c->h_res.p;
         for (uint32_t t = 0; t < nT; t++) done[t] = asked[t].packed && (t >= nB || done[t]);
         for (u32 t : ready) done[t] = 1;
         for (u32 t : fuse) {
@@ -1109,7 +1129,6 @@ static int quantize_with_state(inshr_ctx *c, const inshr_config *cfg, inshr_quan
         for (uint32_t t = 0; t < nT; t++) all = all && (done[t] || !asked[t].packed);
         if (all) break;
     }
-    const QInfo *qi = (const QInfo *)((const char *)c->h_down.p + sizeof(SearchResult) * nT);
     int result = INSHR_OK;
     for (uint32_t k = 0; k < n_sel; k++) {
         const QInfo &r = qi[c->pos[which[k]]];
@@ -1287,7 +1306,6 @@ int sketch_with_state(inshr_ctx *c, const inshr_config *cfg, const uint32_t *whi
     const size_t o_uni = cv.take(sizeof(double) * 256 * nT);
     const size_t o_sd = cv.take(sizeof(SketchDesc) * nT);
     const size_t upload = cv.off; // everything up to here comes from the host
-    const size_t o_info = cv.take(sizeof(SketchInfo) * nT);
     const size_t o_hist = cv.take(sizeof(u32) * SK_HIST * nT);
     const size_t o_xq = cv.take(sizeof(double) * SK_HIST * nT);
     const size_t o_wd = cv.take(2 * sizeof(double) * SK_HIST * nT);
@@ -1295,7 +1313,6 @@ int sketch_with_state(inshr_ctx *c, const inshr_config *cfg, const uint32_t *whi
     const size_t o_key = cv.take(sizeof(u32) * 256 * n_sets * nT);
     const size_t o_cb = cv.take(sizeof(float) * 256 * n_sets * nT);
     const size_t o_sr = cv.take(sizeof(u32) * SK_SETS * nT);
-    const size_t o_ch = cv.take(sizeof(SketchChoice) * nT);
     const size_t o_fk = cv.take(sizeof(u32) * 256 * nT);
     const size_t o_fc = cv.take(sizeof(float) * 256 * nT);
     const size_t o_se = cv.take(sizeof(u32) * SK_SLOTS * nT);
@@ -1319,8 +1336,14 @@ int sketch_with_state(inshr_ctx *c, const inshr_config *cfg, const uint32_t *whi
         memcpy(hb + o_uni + sizeof(double) * 256 * c->pos[which[k]], params->uniforms + (size_t)src[k] * 256,
                sizeof(double) * 256);
     memcpy(hb + o_sd, sd.data(), sizeof(SketchDesc) * nT);
-    HIPCHK(c, hipMemcpyAsync(db, hb, upload, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipMemsetAsync(db + o_hist, 0, sizeof(u32) * SK_HIST * nT, c->stream));
+    Stage up;
+    up.add(db, hb, upload);
+    up.zero(db + o_hist, sizeof(u32) * SK_HIST * nT);
+    if (multi) up.zero(db + o_slot, slot_end - o_slot);
+    HIPCHK(c, launch_stage(up, c->n_cu, c->stream));
+    // (results of a few bytes per tensor: the kernels store them to the host)
+    SketchChoice *const hch = (SketchChoice *)c->h_down.p;
+    SketchInfo *const hinfo = (SketchInfo *)(hch + nT);
     SketchParams P;
     P.sigma = params->sigma;
     P.max_iter = params->max_iter;
@@ -1334,7 +1357,7 @@ int sketch_with_state(inshr_ctx *c, const inshr_config *cfg, const uint32_t *whi
     P.wd = (double *)(db + o_wd);
     P.alt_key = (u32 *)(db + o_key);
     P.alt_cb = (float *)(db + o_cb);
-    P.info = (SketchInfo *)(db + o_info);
+    P.info = hinfo;
     P.multi = multi ? 1u : 0u;
     P.light = c->batch.light ? 1u : 0u;
     P.eps = eps;
@@ -1342,28 +1365,20 @@ int sketch_with_state(inshr_ctx *c, const inshr_config *cfg, const uint32_t *whi
     P.slot_cnt = (u32 *)(db + o_sc);
     P.slot_sx = (double *)(db + o_sx);
     P.slot_edge = (u32 *)(db + o_se);
-    P.choice = (SketchChoice *)(db + o_ch);
+    P.choice = hch;
     P.final_key = (u32 *)(db + o_fk);
     P.final_cb = (float *)(db + o_fc);
-    if (multi) HIPCHK(c, hipMemsetAsync(db + o_slot, 0, slot_end - o_slot, c->stream));
     HIPCHK(c, launch_sketch(c->batch, (const SketchDesc *)(db + o_sd), P, c->stream));
-    if (multi)
-        HIPCHK(c, hipMemcpyAsync((char *)c->h_down.p + sizeof(SketchInfo) * nT, db + o_ch,
-                                 sizeof(SketchChoice) * nT, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipMemcpyAsync(c->h_down.p, db + o_info, sizeof(SketchInfo) * nT, hipMemcpyDeviceToHost,
-                             c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     if (info) {
-        const SketchInfo *si = (const SketchInfo *)c->h_down.p;
         for (uint32_t k = 0; k < n_sel; k++) {
-            info[src[k]].n_buckets = si[c->pos[which[k]]].n_buckets;
-            info[src[k]].rounds = si[c->pos[which[k]]].rounds;
+            info[src[k]].n_buckets = hinfo[c->pos[which[k]]].n_buckets;
+            info[src[k]].rounds = hinfo[c->pos[which[k]]].rounds;
         }
     }
     if (multi && choice) {
-        const SketchChoice *sc = (const SketchChoice *)((const char *)c->h_down.p + sizeof(SketchInfo) * nT);
         for (uint32_t k = 0; k < n_sel; k++) {
-            const SketchChoice &r = sc[c->pos[which[k]]];
+            const SketchChoice &r = hch[c->pos[which[k]]];
             inshr_sketch_choice &o = choice[src[k]];
             for (int b = 0; b < SK_SETS; b++) {
                 o.sse[b] = r.sse[b];
@@ -1748,8 +1763,7 @@ int inshr_quantize_sens(inshr_ctx *c, const inshr_tensor *tensors, const float *
     HIPCHK(c, hipSetDevice(c->device));
     Carver cv;
     const size_t o_sd = cv.take(sizeof(SDesc) * nT);
-    const size_t o_si = cv.take(sizeof(SInfo) * nT);
-    const size_t o_st = cv.take(n_runs * 8 + 256); // [flags, ticket, pad to 256 bytes; states of the runs]: cleared
+    const size_t o_st = cv.take(n_runs * 8 + 256); // [ticket, pad to 256 bytes; states of the runs]: cleared
     const size_t o_bp = cv.take(n_runs * 4);
     const size_t o_bq = cv.take(n_runs * 16);
     const size_t o_S = cv.take(n_total * 4 + 64ull * nT);
@@ -1773,12 +1787,18 @@ int inshr_quantize_sens(inshr_ctx *c, const inshr_tensor *tensors, const float *
             off += (tensors[t].n + 15) / 16 * 16; // every tensor's scratch starts 64-byte aligned
         }
     }
-    auto upload = [&]() -> int {
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-        HIPCHK(c, hipMemcpy(db + o_sd, sd.data(), sizeof(SDesc) * nT, hipMemcpyHostToDevice));
+    auto upload = [&](size_t clear) -> int { // the descriptors; bytes at o_st to clear
+        HIPCHK(c, hipStreamSynchronize(c->stream)); // the staging buffer may still be in flight
+        const int ru = ensure_host(c, c->h_up, sizeof(SDesc) * nT);
+        if (ru) return ru;
+        memcpy(c->h_up.p, sd.data(), sizeof(SDesc) * nT);
+        Stage up;
+        up.add(db + o_sd, c->h_up.p, sizeof(SDesc) * nT);
+        up.zero(db + o_st, clear);
+        HIPCHK(c, launch_stage(up, c->n_cu, c->stream));
         return INSHR_OK;
     };
-    if ((rc = upload())) return rc;
+    if ((rc = upload(0))) return rc;
     HIPCHK(c, launch_sens_score((const SDesc *)(db + o_sd), (int)nT, (u32)n_runs, c->stream));
 
     // thresholds: order statistics of the scores and of the weights (threshold searches only), in one
@@ -1793,7 +1813,7 @@ int inshr_quantize_sens(inshr_ctx *c, const inshr_tensor *tensors, const float *
         const int rs = run_search(c, sub.data() + from, to - from, frac_grid.data(), (uint32_t)frac_grid.size(), 0.0,
                                   LIGHT);
         if (rs) return rs;
-        const SearchResult *res = (const SearchResult *)c->h_down.p;
+        const SearchResult *res = (const SearchResult *)c->h_res.p;
         for (uint32_t k = from; k < to; k++) {
             const uint32_t t = k % nT;
             uint32_t qp = 0, qo = 0;
@@ -1814,15 +1834,14 @@ int inshr_quantize_sens(inshr_ctx *c, const inshr_tensor *tensors, const float *
     if (rc) return rc;
     sub.resize(nT);
     c->have_search = false;
-    if ((rc = upload())) return rc;
-    u32 *flags = (u32 *)(db + o_st);
-    HIPCHK(c, hipMemsetAsync(flags, 0, n_runs * 8 + 256, c->stream));
-    HIPCHK(c, launch_sens_partition((const SDesc *)(db + o_sd), (int)nT, (u32)n_runs, flags + 1,
+    if ((rc = upload(n_runs * 8 + 256))) return rc;
+    rc = ensure_host(c, c->h_down, sizeof(SInfo) * nT);
+    if (rc) return rc;
+    HIPCHK(c, launch_sens_partition((const SDesc *)(db + o_sd), (int)nT, (u32)n_runs, (u32 *)(db + o_st),
                                     (u64 *)(db + o_st + 256), (u32 *)(db + o_bp), (double *)(db + o_bq),
-                                    (SInfo *)(db + o_si), c->stream));
-    std::vector<SInfo> si(nT);
+                                    (SInfo *)c->h_down.p, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    HIPCHK(c, hipMemcpy(si.data(), db + o_si, sizeof(SInfo) * nT, hipMemcpyDeviceToHost));
+    const std::vector<SInfo> si((const SInfo *)c->h_down.p, (const SInfo *)c->h_down.p + nT);
     for (uint32_t t = 0; t < nT; t++) {
         if (si[t].n_kept == 0) {
             c->last_err = "the thresholds leave tensor " + std::to_string(t) + " without quantized values";
@@ -1836,7 +1855,7 @@ int inshr_quantize_sens(inshr_ctx *c, const inshr_tensor *tensors, const float *
     rc = run_search(c, sub.data(), nT, bin_grid.data(), (uint32_t)bin_grid.size(), 0.0, SCORES);
     if (rc) return rc;
     c->have_search = false; // (the state describes the compacted values, not the caller's tensors)
-    const Score *hsc = (const Score *)((const char *)c->h_down.p + sizeof(SearchResult) * nT);
+    const Score *hsc = (const Score *)c->h_down.p;
     const uint32_t n_bg = (uint32_t)bin_grid.size();
     std::vector<double> sse_q(nT), sq_q(nT);
     for (uint32_t t = 0; t < nT; t++) {
@@ -1855,13 +1874,12 @@ int inshr_quantize_sens(inshr_ctx *c, const inshr_tensor *tensors, const float *
         sd[t].K = bins_of(cfg[t]);
         sd[t].sym_bits = symbol_bits(sd[t].K);
     }
-    if ((rc = upload())) return rc;
+    if ((rc = upload(0))) return rc;
+    u32 *const flags = call_flags(c);
     HIPCHK(c, launch_sens_quant((const SDesc *)(db + o_sd), (int)nT, (u32)n_runs, (const u32 *)(db + o_bp), flags,
                                 c->stream));
-    u32 fl = 0;
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    HIPCHK(c, hipMemcpy(&fl, flags, 4, hipMemcpyDeviceToHost));
-    if (fl & 2u) return INSHR_E_CAPACITY;
+    if (raised_flags(flags) & 2u) return INSHR_E_CAPACITY;
     for (uint32_t t = 0; t < nT; t++) {
         out[t].n_pruned = si[t].n_pruned;
         out[t].n_outlier = si[t].n_outlier;
@@ -1915,9 +1933,9 @@ static size_t totals_bytes(const std::vector<DDesc> &dd)
         if (d.n_chunks > DELTA_FEW) return sizeof(u32) * DELTA_SS * dd.size();
     return 0;
 }
-// That room, cleared: at offset o of aux_mem, or an allocation of its own where the caller limits the size of
+// That room, to be cleared: at offset o of aux_mem, or an allocation of its own where the caller limits the size of
 // one (a call that fitted the limit without them still does).
-static int clear_totals(inshr_ctx *c, size_t bytes, size_t o, u32 **totals)
+static int clear_totals(inshr_ctx *c, size_t bytes, size_t o, u32 **totals, Stage &st)
 {
     *totals = nullptr;
     if (!bytes) return INSHR_OK;
@@ -1926,7 +1944,7 @@ static int clear_totals(inshr_ctx *c, size_t bytes, size_t o, u32 **totals)
         if (rc) return rc;
     }
     *totals = (u32 *)(c->scratch_limit ? c->totals_mem.p : (char *)c->aux_mem.p + o);
-    HIPCHK(c, hipMemsetAsync(*totals, 0, bytes, c->stream));
+    st.zero(*totals, bytes);
     return INSHR_OK;
 }
 
@@ -2001,13 +2019,15 @@ int inshr_delta(inshr_ctx *c, const inshr_codes *prev, const uint32_t *const *pr
     char *hb = (char *)c->h_up.p, *db = (char *)c->aux_mem.p;
     memcpy(hb + o_dd, dd.data(), sizeof(DDesc) * n_tensors);
     memcpy(hb + o_ct, chunk_tensor.data(), sizeof(u32) * chunk_tensor.size());
-    HIPCHK(c, hipMemcpyAsync(db, hb, up_bytes, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipMemsetAsync(c->delta_flags, 0, sizeof(u32), c->stream));
     u32 *totals;
-    if ((rc = clear_totals(c, tt_bytes, o_tt, &totals))) return rc;
+    Stage up;
+    if ((rc = clear_totals(c, tt_bytes, o_tt, &totals, up))) return rc;
+    up.add(db, hb, up_bytes);
+    HIPCHK(c, launch_stage(up, c->n_cu, c->stream));
+    memset(c->flags, 0, FLAG_WORDS * sizeof(u32));
     c->delta_pending = true;
     HIPCHK(c, launch_delta((const DDesc *)(db + o_dd), (int)n_tensors, dtile, chunk,
-                           (const u32 *)(db + o_ct), (u32 *)(db + o_ck), totals, c->delta_flags, any_scatter,
+                           (const u32 *)(db + o_ct), (u32 *)(db + o_ck), totals, c->flags, any_scatter,
                            any_perm, any_gather, c->lds_ordered, c->stream));
     return INSHR_OK;
 }
@@ -2118,25 +2138,23 @@ int inshr_dequantize(inshr_ctx *c, const inshr_dequant_in *in, float *const *out
     HIPCHK(c, hipSetDevice(c->device));
     Carver cv;
     const size_t o_rd = cv.take(sizeof(RDesc) * n_tensors);
-    const size_t o_fl = cv.take(sizeof(u32) * (n_tensors + 1)); // flags, then symbol-1 counts
-    const size_t up_bytes = cv.off;
+    const size_t o_one = cv.take(sizeof(u32) * n_tensors); // symbol-1 counts
     int rc = ensure_dev(c, c->aux_mem, cv.off);
     if (rc) return rc;
-    rc = ensure_host(c, c->h_up, up_bytes);
-    if (rc) return rc;
-    rc = ensure_host(c, c->h_down, sizeof(u32));
-    if (rc) return rc;
     HIPCHK(c, hipStreamSynchronize(c->stream)); // the staging buffer may still be in flight
+    rc = ensure_host(c, c->h_up, o_one);
+    if (rc) return rc;
     char *hb = (char *)c->h_up.p, *db = (char *)c->aux_mem.p;
-    memset(hb, 0, up_bytes);
     memcpy(hb + o_rd, rd.data(), sizeof(RDesc) * n_tensors);
-    HIPCHK(c, hipMemcpyAsync(db, hb, up_bytes, hipMemcpyHostToDevice, c->stream));
-    u32 *flags = (u32 *)(db + o_fl);
+    Stage up;
+    up.add(db, hb, o_one);
+    up.zero(db + o_one, sizeof(u32) * n_tensors);
+    HIPCHK(c, launch_stage(up, c->n_cu, c->stream));
+    u32 *const flags = call_flags(c);
     HIPCHK(c, launch_dequantize((const RDesc *)(db + o_rd), (int)n_tensors, tile, max_out, flags,
-                                flags + 1, c->n_cu, c->stream));
-    HIPCHK(c, hipMemcpyAsync(c->h_down.p, flags, sizeof(u32), hipMemcpyDeviceToHost, c->stream));
+                                (u32 *)(db + o_one), c->n_cu, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    const u32 f = *(const u32 *)c->h_down.p;
+    const u32 f = raised_flags(flags);
     if (f & RF_SYMBOL) return INSHR_E_ARG;
     if (f & RF_LIST) return INSHR_E_SHAPE;
     return INSHR_OK;
@@ -2195,7 +2213,6 @@ int inshr_reconstruct(inshr_ctx *c, const inshr_codes *prev, const inshr_delta_o
     const size_t o_dd = cv.take(sizeof(DDesc) * n_tensors);
     const size_t o_xd = cv.take(sizeof(XDesc) * n_tensors);
     const size_t o_ct = cv.take(sizeof(u32) * chunk_tensor.size());
-    const size_t o_fl = cv.take(sizeof(u32));
     const size_t up_bytes = cv.off;
     const size_t o_go = cv.take(sizeof(u64) * (DELTA_SS + 8) * n_tensors); // group offsets from prev
     const size_t tt_bytes = totals_bytes(dd), o_tt = cv.take(c->scratch_limit ? 0 : tt_bytes);
@@ -2204,25 +2221,23 @@ int inshr_reconstruct(inshr_ctx *c, const inshr_codes *prev, const inshr_delta_o
     if (rc) return rc;
     rc = ensure_host(c, c->h_up, up_bytes);
     if (rc) return rc;
-    rc = ensure_host(c, c->h_down, sizeof(u32));
-    if (rc) return rc;
     HIPCHK(c, hipStreamSynchronize(c->stream));
     char *hb = (char *)c->h_up.p, *db = (char *)c->aux_mem.p;
     u32 *totals;
-    if ((rc = clear_totals(c, tt_bytes, o_tt, &totals))) return rc;
+    Stage up;
+    if ((rc = clear_totals(c, tt_bytes, o_tt, &totals, up))) return rc;
     for (uint32_t t = 0; t < n_tensors; t++) dd[t].group_off = (u64 *)(db + o_go) + (size_t)t * (DELTA_SS + 8);
-    memset(hb, 0, up_bytes);
     memcpy(hb + o_dd, dd.data(), sizeof(DDesc) * n_tensors);
     memcpy(hb + o_xd, xd.data(), sizeof(XDesc) * n_tensors);
     memcpy(hb + o_ct, chunk_tensor.data(), sizeof(u32) * chunk_tensor.size());
-    HIPCHK(c, hipMemcpyAsync(db, hb, up_bytes, hipMemcpyHostToDevice, c->stream));
-    u32 *flags = (u32 *)(db + o_fl);
+    up.add(db, hb, up_bytes);
+    HIPCHK(c, launch_stage(up, c->n_cu, c->stream));
+    u32 *const flags = call_flags(c);
     HIPCHK(c, launch_reconstruct((const DDesc *)(db + o_dd), (const XDesc *)(db + o_xd),
                                  (int)n_tensors, chunk, (const u32 *)(db + o_ct),
                                  (u32 *)(db + o_ck), totals, flags, c->lds_ordered, c->stream));
-    HIPCHK(c, hipMemcpyAsync(c->h_down.p, flags, sizeof(u32), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    const u32 f = *(const u32 *)c->h_down.p;
+    const u32 f = raised_flags(flags);
     if (f & RF_ORDER) {
         c->last_err = "reconstruct: ranks from returning LDS atomics disagree with ballot ranks (set INSHR_NO_LDS_ORDER=1)";
         return INSHR_E_INTERNAL;

@@ -711,7 +711,7 @@ __global__ __launch_bounds__(DBLOCK, 6) void k_dscatter(const DDesc *__restrict_
         if (r.bits && part)
             __hip_atomic_fetch_or(out + r.word, part, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (ORDERED && order_bad) atomicOr(flags, DF_ORDER);
+    if (ORDERED && order_bad) raise_flag(flags, DF_ORDER);
 }
 
 // regrouping given: e[r] = d[perm[r]] by gathering
@@ -771,7 +771,7 @@ __global__ __launch_bounds__(BLOCK) void k_dgather(const DDesc *__restrict__ dd,
         GLOBAL_AS unsigned long long *dst = gptr(d.out) + r0 * wB / 64u;
         for (u32 k = tid; k < n_words; k += BLOCK) dst[k] = pk[k];
     }
-    if (bad_index) atomicOr(flags, DF_PERM);
+    if (bad_index) raise_flag(flags, DF_PERM);
 }
 
 // Restore side (Algorithm 6): s_cur[i] = (s_prev[i] - e[r]) mod B, where r is the position of element
@@ -964,8 +964,8 @@ __global__ __launch_bounds__(DBLOCK, 6) void k_drestore(const DDesc *__restrict_
             for (u32 k = tid; k < NWAVE * srow; k += DBLOCK) sh.wst[k] = 0u; // for the next tile's counts
         }
     }
-    if (__ballot(e_max >= Bm || s_max >= x.Sc) && lane == 0u) atomicOr(flags, RF_DELTA);
-    if (ORDERED && order_bad) atomicOr(flags, RF_ORDER);
+    if (__ballot(e_max >= Bm || s_max >= x.Sc) && lane == 0u) raise_flag(flags, RF_DELTA);
+    if (ORDERED && order_bad) raise_flag(flags, RF_ORDER);
 }
 
 // group offsets that came with the stream against those of the previous symbols
@@ -977,7 +977,7 @@ __global__ __launch_bounds__(SS) void k_dcheck_groups(const DDesc *__restrict__ 
     const XDesc x = xd[blockIdx.x];
     const u32 g = threadIdx.x;
     if (x.group_off_in && g <= d.Kp + 2u && gptr(x.group_off_in)[g] != gptr(d.group_off)[g])
-        atomicOr(flags, RF_GROUPS);
+        raise_flag(flags, RF_GROUPS);
 }
 
 // totals: NULL when no tensor has more than DELTA_FEW chunks
@@ -1047,16 +1047,17 @@ hipError_t launch_lds_order_check(u32 *violations, hipStream_t s)
 
 // ------------------------------------------------------------------------------------------
 // The delta without any allocation: descriptors, the chunk -> tensor table, the per-chunk symbol
-// populations and the flag word live in one file-scope device array.  Every GPU holds its own copy
+// populations and the flag words live in one file-scope device array.  Every GPU holds its own copy
 // at its own address; delta_static_init asks for it once per device, and host code uses that
 // pointer only (the array's name is not a device address on the host side).
 // ------------------------------------------------------------------------------------------
 constexpr size_t DST_DD = 0;                                                   // DDesc[MAX_TENSORS]
-constexpr size_t DST_FLAGS = DST_DD + sizeof(DDesc) * DELTA_STATIC_MAX_TENSORS; // u32 flag word
+constexpr size_t DST_FLAGS = DST_DD + sizeof(DDesc) * DELTA_STATIC_MAX_TENSORS; // u32 flag words
 constexpr size_t DST_CT = (DST_FLAGS + 256) & ~(size_t)255;                    // u32[MAX_CHUNKS]
 constexpr size_t DST_CK = DST_CT + sizeof(u32) * DELTA_STATIC_MAX_CHUNKS;      // u32[MAX_CHUNKS][SS]
 constexpr size_t DST_TOT = DST_CK + sizeof(u32) * (size_t)DELTA_STATIC_MAX_CHUNKS * DELTA_SS; // u32[MAX_TENSORS][SS]
 constexpr size_t DST_BYTES = DST_TOT + sizeof(u32) * DELTA_STATIC_MAX_TENSORS * DELTA_SS;
+static_assert(DST_CT - DST_FLAGS >= FLAG_WORDS * sizeof(u32), "room for the flag words");
 static __device__ __align__(256) unsigned char scratch[DST_BYTES];
 
 constexpr int MAX_DEVICES = 64;
@@ -1086,7 +1087,7 @@ __global__ __launch_bounds__(256) void k_dstatic_setup(DeltaStaticArgs a, DDesc 
 {
     const u32 tid = threadIdx.x;
     if (tid < a.n_tensors) dd[tid] = a.dd[tid];
-    if (tid == 0u) *flags = 0u;
+    if (tid < (u32)FLAG_WORDS) flags[tid] = 0u;
     for (u32 i = tid; i < a.n_tensors * (u32)SS; i += 256u) totals[i] = 0u;
     for (u32 t = 0; t < a.n_tensors; t++) {
         const u64 c0 = a.dd[t].chunk0, c1 = c0 + a.dd[t].n_chunks;

@@ -27,7 +27,7 @@ static_assert(MAX_CFG < (1 << 16), "no index looks like VIEW_ALL");
 struct Bufs { // device pointers, indexed by the tensor's position on the device unless noted; nB rows
               // (tensors searched by the sweeps) except ts, table2, tgt_key, codebook, scores (all)
     TState *ts;
-    SearchResult *res; // [nT]
+    SearchResult *res; // [nT], in host memory
     u32 *hist1;     // [nT][32768]
     u32 *pool_h1;   // [nT][32768] row of a group's leader: the first-level histograms of the group, added up
     u32 *pool_sel;  // [nT][2][SEL_WORDS] row of a group's leader: the group's selection histograms, per pass
@@ -178,13 +178,13 @@ struct XDesc { // one tensor of a reconstruct call: the delta descriptor plus wh
     const u64 *group_off_in;     // group offsets that came with the stream, or NULL
     u32 Sc, pad;                 // symbols of the current checkpoint
 };
-// bits of the flag word the restore kernels raise
+// flags the restore kernels raise
 constexpr u32 RF_SYMBOL = 1u;  // a symbol outside 0 .. K + 1
 constexpr u32 RF_LIST = 2u;    // protected list and symbol stream disagree
 constexpr u32 RF_GROUPS = 4u;  // group offsets do not match the previous symbols
 constexpr u32 RF_DELTA = 8u;   // a delta outside 0 .. B - 1, or a result outside 0 .. K_cur + 1
 constexpr u32 RF_ORDER = 16u;  // ranks from returning LDS adds disagree with ranks from ballots
-// bits of the flag word of a delta call
+// flags of a delta call
 constexpr u32 DF_PERM = 1u;    // a given permutation holds an index outside its tensor
 constexpr u32 DF_ORDER = 2u;   // ranks from returning LDS adds disagree with ranks from ballots
 constexpr int DELTA_TILE = 12288;
@@ -209,6 +209,39 @@ struct DeltaStaticArgs {
     DDesc dd[DELTA_STATIC_MAX_TENSORS];
     u32 n_tensors, pad;
 };
+
+// What a call uploads and clears before its kernels (inshr_stage.hip).  Sizes are rounded up to 16 bytes: sources
+// and destinations have that room (they come from allocations and offsets in multiples of 256).
+struct Stage {
+    static constexpr int PARTS = 4;
+    struct Copy {
+        const void *from; // pinned host memory
+        void *to;
+        u64 pieces;       // of 16 bytes
+    } copy[PARTS];
+    struct Clear {
+        void *at;
+        u64 pieces;
+    } clear[PARTS];
+    int n_copy = 0, n_clear = 0;
+    void add(void *to, const void *from, size_t bytes) { copy[n_copy++] = {from, to, (bytes + 15) / 16}; }
+    void zero(void *at, size_t bytes)
+    {
+        if (bytes) clear[n_clear++] = {at, (bytes + 15) / 16};
+    }
+};
+hipError_t launch_stage(const Stage &st, int n_cu, hipStream_t s);
+
+// Flags that kernels raise for the host: a word per bit, so that a plain store does (the words may lie in
+// host memory).
+constexpr int FLAG_WORDS = 8;
+__device__ __forceinline__ void raise_flag(u32 *flags, u32 bit) { gptr(flags)[__builtin_ctz(bit)] = 1u; }
+inline u32 raised_flags(const u32 *words)
+{
+    u32 f = 0;
+    for (int i = 0; i < FLAG_WORDS; i++) f |= words[i] ? 1u << i : 0u;
+    return f;
+}
 
 // Optional per-kernel timing with HIP events on the launch stream (off by default).
 void prof_begin(const char *name, hipStream_t s);
@@ -237,7 +270,7 @@ hipError_t launch_delta(const DDesc *dd, int nT, u64 n_dtiles, u64 n_chunks,
                         const u32 *chunk_tensor, u32 *chunk_tot, u32 *totals, u32 *flags, bool any_scatter,
                         bool any_perm, bool any_gather, bool lds_ordered, hipStream_t s);
 hipError_t delta_static_init(int device); // once per device, with that device current
-u32 *delta_static_flags(int device);      // the flag word of launch_delta_static on that device
+u32 *delta_static_flags(int device);      // the flag words of launch_delta_static on that device
 hipError_t launch_delta_static(int device, const DeltaStaticArgs &a, u64 n_dtiles, u64 n_chunks,
                                bool any_scatter, bool any_perm, bool lds_ordered, hipStream_t s);
 hipError_t launch_sens_score(const SDesc *sd, int nT, u32 n_runs, hipStream_t s);

@@ -138,7 +138,7 @@ __global__ __launch_bounds__(DQ_BLOCK, 7) void k_dequant(const RDesc *__restrict
         bad |= s_max >= K + 2u;
         if ((tid & 63u) == 0u && n_one) atomicAdd(&ones[t_now], n_one);
     }
-    if (__ballot(bad) && (tid & 63u) == 0u) atomicOr(flags, RF_SYMBOL);
+    if (__ballot(bad) && (tid & 63u) == 0u) raise_flag(flags, RF_SYMBOL);
 }
 
 __global__ __launch_bounds__(256) void k_dequant_protected(const RDesc *__restrict__ rd,
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(256) void k_dequant_protected(const RDesc *__restri
 {
     const RDesc d = rd[blockIdx.y];
     if (blockIdx.x == 0 && threadIdx.x == 0 && (u64)ones[blockIdx.y] != d.n_outlier)
-        atomicOr(flags, RF_LIST);
+        raise_flag(flags, RF_LIST);
     const u32 mask = (1u << d.w) - 1u;
     for (u64 j = (u64)blockIdx.x * 256u + threadIdx.x; j < d.n_outlier; j += (u64)gridDim.x * 256u) {
         const u64 i = gptr(d.out_idx)[j];
@@ -164,7 +164,7 @@ __global__ __launch_bounds__(256) void k_dequant_protected(const RDesc *__restri
                                  ? __uint_as_float((u32)((const GLOBAL_AS u16 *)gptr(d.out_val))[j] << 16)
                                  : gptr(d.out_val)[j];
         else
-            atomicOr(flags, RF_LIST);
+            raise_flag(flags, RF_LIST);
     }
 }
 

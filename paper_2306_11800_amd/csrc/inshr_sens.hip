@@ -327,7 +327,7 @@ __global__ __launch_bounds__(SWG) void k_sens_quant(const SDesc *__restrict__ sd
             ppos += (u64)__popcll(mp);
         }
     }
-    if (__ballot(overflow) && lane == 0u) atomicOr(flags, 2u);
+    if (__ballot(overflow) && lane == 0u) raise_flag(flags, 2u);
     __syncthreads();
     if (!left) return;
     // 1024 symbols of wb bits are 16 * wb whole words; the tensor's last block may end earlier
