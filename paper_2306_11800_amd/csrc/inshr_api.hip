@@ -1925,26 +1925,39 @@ static u32 call_chunk_tiles(const inshr_ctx *c, const inshr_codes *prev, uint32_
     return ct;
 }
 
-// Room for the symbol populations of the tensors of a call: none where no tensor has enough chunks for them to
-// be added up.
-static size_t totals_bytes(const std::vector<DDesc> &dd)
+// The parts of a call's tensors: where their symbol populations are added up and, behind those, the tensor of every
+// part.  None where no tensor has enough chunks for them to be added up; every tensor is one part then.
+struct Parts {
+    std::vector<u32> tensor;
+    bool many = false;
+    void enter(DDesc &d, u32 t)
+    {
+        d.part0 = (u32)tensor.size();
+        tensor.insert(tensor.end(), delta_parts(d.n_chunks), t);
+        many = many || d.n_chunks > DELTA_FEW;
+    }
+    size_t sums() const { return many ? sizeof(u32) * DELTA_SS * tensor.size() : 0; }
+    size_t bytes() const { return many ? sums() + sizeof(u32) * tensor.size() : 0; }
+};
+// They lie at offset o of aux_mem, or in an allocation of its own where the caller limits the size of one (a call that
+// fitted the limit without them still does: aux_mem holds as much for every chunk, and there are no more parts than
+// chunks).  The tensors' numbers are staged at offset at of h_up.
+static int place_parts(inshr_ctx *c, const Parts &parts, size_t o, size_t at, DeltaCall &call, Stage &st)
 {
-    for (const DDesc &d : dd)
-        if (d.n_chunks > DELTA_FEW) return sizeof(u32) * DELTA_SS * dd.size();
-    return 0;
-}
-// That room, to be cleared: at offset o of aux_mem, or an allocation of its own where the caller limits the size of
-// one (a call that fitted the limit without them still does).
-static int clear_totals(inshr_ctx *c, size_t bytes, size_t o, u32 **totals, Stage &st)
-{
-    *totals = nullptr;
-    if (!bytes) return INSHR_OK;
+    call.totals = nullptr;
+    call.part_tensor = nullptr;
+    call.n_parts = parts.tensor.size();
+    if (!parts.many) return INSHR_OK;
     if (c->scratch_limit) {
-        const int rc = ensure_dev(c, c->totals_mem, bytes);
+        const int rc = ensure_dev(c, c->totals_mem, (parts.bytes() + 255) & ~(size_t)255);
         if (rc) return rc;
     }
-    *totals = (u32 *)(c->scratch_limit ? c->totals_mem.p : (char *)c->aux_mem.p + o);
-    st.zero(*totals, bytes);
+    char *p = c->scratch_limit ? (char *)c->totals_mem.p : (char *)c->aux_mem.p + o;
+    call.totals = (u32 *)p;
+    st.zero(p, parts.sums());
+    memcpy((char *)c->h_up.p + at, parts.tensor.data(), sizeof(u32) * parts.tensor.size());
+    call.part_tensor = (const u32 *)(p + parts.sums());
+    st.add(p + parts.sums(), (char *)c->h_up.p + at, sizeof(u32) * parts.tensor.size());
     return INSHR_OK;
 }
 
@@ -1954,9 +1967,10 @@ int inshr_delta(inshr_ctx *c, const inshr_codes *prev, const uint32_t *const *pr
     if (!c || !prev || !cur || !out || n_tensors == 0) return INSHR_E_ARG;
     std::vector<DDesc> dd(n_tensors);
     std::vector<u32> chunk_tensor;
-    u64 dtile = 0, chunk = 0;
+    Parts parts;
+    u64 chunk = 0;
     const u32 ctiles = call_chunk_tiles(c, prev, n_tensors);
-    bool any_scatter = false, any_gather = false, any_perm = false;
+    bool any_scatter = false, any_gather = false, any_perm = false, any_long = false;
     for (uint32_t t = 0; t < n_tensors; t++) {
         uint64_t words = 0;
         int rc = inshr_delta_bound(&prev[t], &cur[t], &words);
@@ -1986,13 +2000,13 @@ int inshr_delta(inshr_ctx *c, const inshr_codes *prev, const uint32_t *const *pr
         d.B = std::max(Kp, Kc) + 2u;
         d.wB = symbol_bits(std::max(Kp, Kc));
         out[t].delta_bits = d.wB;
-        d.dtile0 = dtile;
         d.chunk0 = chunk;
         const u64 nt = (n + DELTA_TILE - 1) / DELTA_TILE;
         d.n_chunks = (nt + ctiles - 1) / ctiles;
         d.ctiles = ctiles;
         for (u64 k = 0; k < d.n_chunks; k++) chunk_tensor.push_back(t);
-        dtile += nt;
+        parts.enter(d, t);
+        any_long = any_long || !delta_single(d);
         chunk += d.n_chunks;
         if (d.prev_perm)
             any_gather = true;
@@ -2006,29 +2020,34 @@ int inshr_delta(inshr_ctx *c, const inshr_codes *prev, const uint32_t *const *pr
     const size_t o_dd = cv.take(sizeof(DDesc) * n_tensors);
     const size_t o_ct = cv.take(sizeof(u32) * chunk_tensor.size());
     const size_t up_bytes = cv.off;
-    const size_t tt_bytes = totals_bytes(dd), o_tt = cv.take(c->scratch_limit ? 0 : tt_bytes);
+    const size_t o_tt = cv.take(c->scratch_limit ? 0 : parts.bytes());
     const size_t o_ck = cv.take((size_t)chunk * DELTA_SS * 4);
     int rc = ensure_dev(c, c->aux_mem, cv.off);
     if (rc) return rc;
-    rc = ensure_host(c, c->h_up, up_bytes);
-    if (rc) return rc;
     // the staging buffer may still be in flight from an earlier asynchronous delta call
     HIPCHK(c, hipStreamSynchronize(c->stream));
+    rc = ensure_host(c, c->h_up, up_bytes + sizeof(u32) * parts.tensor.size());
+    if (rc) return rc;
     rc = take_delta_flags(c); // (of a call whose flags nobody has asked for yet)
     if (rc) return rc;
     char *hb = (char *)c->h_up.p, *db = (char *)c->aux_mem.p;
     memcpy(hb + o_dd, dd.data(), sizeof(DDesc) * n_tensors);
     memcpy(hb + o_ct, chunk_tensor.data(), sizeof(u32) * chunk_tensor.size());
-    u32 *totals;
+    DeltaCall call;
     Stage up;
-    if ((rc = clear_totals(c, tt_bytes, o_tt, &totals, up))) return rc;
+    if ((rc = place_parts(c, parts, o_tt, up_bytes, call, up))) return rc;
     up.add(db, hb, up_bytes);
     HIPCHK(c, launch_stage(up, c->n_cu, c->stream));
     memset(c->flags, 0, FLAG_WORDS * sizeof(u32));
     c->delta_pending = true;
-    HIPCHK(c, launch_delta((const DDesc *)(db + o_dd), (int)n_tensors, dtile, chunk,
-                           (const u32 *)(db + o_ct), (u32 *)(db + o_ck), totals, c->flags, any_scatter,
-                           any_perm, any_gather, c->lds_ordered, c->stream));
+    call.dd = (const DDesc *)(db + o_dd);
+    call.chunk_tensor = (const u32 *)(db + o_ct);
+    call.chunk_tot = (u32 *)(db + o_ck);
+    call.flags = c->flags;
+    call.n_chunks = chunk;
+    call.any_long = any_long;
+    call.lds_ordered = c->lds_ordered;
+    HIPCHK(c, launch_delta(call, any_scatter, any_perm, any_gather, c->stream));
     return INSHR_OK;
 }
 
@@ -2043,7 +2062,7 @@ int inshr_delta_static(inshr_ctx *c, const inshr_codes *prev, const inshr_codes 
     DeltaStaticArgs a;
     memset(&a, 0, sizeof(a));
     a.n_tensors = n_tensors;
-    u64 dtile = 0, chunk = 0;
+    u64 chunk = 0;
     u32 ctiles = call_chunk_tiles(c, prev, n_tensors);
     { // (the static scratch holds a fixed number of chunks: longer ones where they would not fit)
         auto chunks_with = [&](u32 ct) {
@@ -2053,7 +2072,8 @@ int inshr_delta_static(inshr_ctx *c, const inshr_codes *prev, const inshr_codes 
         };
         while (ctiles < (u32)DELTA_CHUNK && chunks_with(ctiles) > (u64)DELTA_STATIC_MAX_CHUNKS) ctiles++;
     }
-    bool any_scatter = false, any_perm = false;
+    bool any_scatter = false, any_perm = false, any_long = false;
+    u64 parts = 0;
     for (uint32_t t = 0; t < n_tensors; t++) {
         uint64_t words = 0;
         int rc = inshr_delta_bound(&prev[t], &cur[t], &words);
@@ -2080,12 +2100,13 @@ int inshr_delta_static(inshr_ctx *c, const inshr_codes *prev, const inshr_codes 
         d.B = std::max(Kp, Kc) + 2u;
         d.wB = symbol_bits(std::max(Kp, Kc));
         out[t].delta_bits = d.wB;
-        d.dtile0 = dtile;
         d.chunk0 = chunk;
         const u64 nt = (n + DELTA_TILE - 1) / DELTA_TILE;
         d.n_chunks = (nt + ctiles - 1) / ctiles;
         d.ctiles = ctiles;
-        dtile += nt;
+        d.part0 = (u32)parts;
+        parts += delta_parts(d.n_chunks);
+        any_long = any_long || !delta_single(d);
         chunk += d.n_chunks;
         if (d.perm)
             any_perm = true;
@@ -2100,7 +2121,7 @@ int inshr_delta_static(inshr_ctx *c, const inshr_codes *prev, const inshr_codes 
     }
     HIPCHK(c, hipSetDevice(c->device));
     c->static_pending = true;
-    HIPCHK(c, launch_delta_static(c->device, a, dtile, chunk, any_scatter, any_perm, c->lds_ordered, c->stream));
+    HIPCHK(c, launch_delta_static(c->device, a, chunk, parts, any_long, any_scatter, any_perm, c->lds_ordered, c->stream));
     return INSHR_OK;
 }
 
@@ -2167,7 +2188,9 @@ int inshr_reconstruct(inshr_ctx *c, const inshr_codes *prev, const inshr_delta_o
     std::vector<DDesc> dd(n_tensors);
     std::vector<XDesc> xd(n_tensors);
     std::vector<u32> chunk_tensor;
-    u64 dtile = 0, chunk = 0;
+    Parts parts;
+    u64 chunk = 0;
+    bool any_long = false;
     const u32 ctiles = call_chunk_tiles(c, prev, n_tensors);
     for (uint32_t t = 0; t < n_tensors; t++) {
         const uint64_t n = prev[t].n;
@@ -2194,13 +2217,13 @@ int inshr_reconstruct(inshr_ctx *c, const inshr_codes *prev, const inshr_delta_o
         d.Kp = Kp;
         d.B = std::max(Kp, Kc) + 2u;
         d.wB = wB;
-        d.dtile0 = dtile;
         d.chunk0 = chunk;
         const u64 nt = (n + DELTA_TILE - 1) / DELTA_TILE;
         d.n_chunks = (nt + ctiles - 1) / ctiles;
         d.ctiles = ctiles;
         for (u64 k = 0; k < d.n_chunks; k++) chunk_tensor.push_back(t);
-        dtile += nt;
+        parts.enter(d, t);
+        any_long = any_long || !delta_single(d);
         chunk += d.n_chunks;
         XDesc &x = xd[t];
         memset(&x, 0, sizeof(x));
@@ -2215,17 +2238,17 @@ int inshr_reconstruct(inshr_ctx *c, const inshr_codes *prev, const inshr_delta_o
     const size_t o_ct = cv.take(sizeof(u32) * chunk_tensor.size());
     const size_t up_bytes = cv.off;
     const size_t o_go = cv.take(sizeof(u64) * (DELTA_SS + 8) * n_tensors); // group offsets from prev
-    const size_t tt_bytes = totals_bytes(dd), o_tt = cv.take(c->scratch_limit ? 0 : tt_bytes);
+    const size_t o_tt = cv.take(c->scratch_limit ? 0 : parts.bytes());
     const size_t o_ck = cv.take((size_t)chunk * DELTA_SS * 4);
     int rc = ensure_dev(c, c->aux_mem, cv.off);
     if (rc) return rc;
-    rc = ensure_host(c, c->h_up, up_bytes);
+    HIPCHK(c, hipStreamSynchronize(c->stream)); // the staging buffer may still be in flight
+    rc = ensure_host(c, c->h_up, up_bytes + sizeof(u32) * parts.tensor.size());
     if (rc) return rc;
-    HIPCHK(c, hipStreamSynchronize(c->stream));
     char *hb = (char *)c->h_up.p, *db = (char *)c->aux_mem.p;
-    u32 *totals;
+    DeltaCall call;
     Stage up;
-    if ((rc = clear_totals(c, tt_bytes, o_tt, &totals, up))) return rc;
+    if ((rc = place_parts(c, parts, o_tt, up_bytes, call, up))) return rc;
     for (uint32_t t = 0; t < n_tensors; t++) dd[t].group_off = (u64 *)(db + o_go) + (size_t)t * (DELTA_SS + 8);
     memcpy(hb + o_dd, dd.data(), sizeof(DDesc) * n_tensors);
     memcpy(hb + o_xd, xd.data(), sizeof(XDesc) * n_tensors);
@@ -2233,9 +2256,14 @@ int inshr_reconstruct(inshr_ctx *c, const inshr_codes *prev, const inshr_delta_o
     up.add(db, hb, up_bytes);
     HIPCHK(c, launch_stage(up, c->n_cu, c->stream));
     u32 *const flags = call_flags(c);
-    HIPCHK(c, launch_reconstruct((const DDesc *)(db + o_dd), (const XDesc *)(db + o_xd),
-                                 (int)n_tensors, chunk, (const u32 *)(db + o_ct),
-                                 (u32 *)(db + o_ck), totals, flags, c->lds_ordered, c->stream));
+    call.dd = (const DDesc *)(db + o_dd);
+    call.chunk_tensor = (const u32 *)(db + o_ct);
+    call.chunk_tot = (u32 *)(db + o_ck);
+    call.flags = flags;
+    call.n_chunks = chunk;
+    call.any_long = any_long;
+    call.lds_ordered = c->lds_ordered;
+    HIPCHK(c, launch_reconstruct(call, (const XDesc *)(db + o_xd), c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     const u32 f = raised_flags(flags);
     if (f & RF_ORDER) {

@@ -4,13 +4,14 @@
 // The regrouping is a stable partition into at most 258 groups:
 //   k_dhist     per chunk (1 .. 64 tiles of 12288 elements): population of every previous symbol
 //   k_dgroups   per tensor: group offsets and the start of every chunk inside every group; clears
-//               the stream words that k_dscatter ORs into
+//               the stream words that k_dscatter ORs into; checks the offsets that came with a stream
 //   k_dscatter  one workgroup of 12 waves per chunk walks its tiles in order.  Per tile each wave
 //               owns 1024 consecutive elements, 64 consecutive elements per step; a returning LDS
 //               add per element (or lane bits OR-ed into the symbol's LDS slot) gives the stable
 //               rank.  The tile's deltas are written to an LDS array in regrouped order, one thread
 //               per output word packs the fields of its bits and stores it (first / last word of a
 //               chunk's run are OR-ed into words that k_dgroups cleared).
+// A tensor of one tile needs neither of the first two: its workgroup of k_dscatter (k_drestore) has all counts.
 #include "inshr_launch.h"
 
 namespace inshr {
@@ -92,6 +93,7 @@ __global__ __launch_bounds__(HBLOCK) void k_dhist(const DDesc *__restrict__ dd,
     const u64 chunk = blockIdx.x;
     const u32 t = __builtin_amdgcn_readfirstlane(chunk_tensor[chunk]);
     const DDesc d = dd[t];
+    if (delta_single(d)) return;
     const u32 tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const u32 S = d.Kp + 2u;
     const u64 c_elems = (u64)d.ctiles * DTILE;
@@ -127,76 +129,100 @@ __global__ __launch_bounds__(HBLOCK) void k_dhist(const DDesc *__restrict__ dd,
     for (u32 h = 0; h < 2u; h++) {
         const u32 sy = tid + h * HBLOCK;
         if (sy < (u32)SS) chunk_tot[chunk * SS + sy] = sy < S ? mine[h] : 0u;
-        if (d.n_chunks > DELTA_FEW && sy < S && mine[h]) atomicAdd(&totals[t * (u32)SS + sy], mine[h]); // (cleared beforehand)
+        if (d.n_chunks > DELTA_FEW && sy < S && mine[h]) // (cleared beforehand)
+            atomicAdd(&totals[(d.part0 + (u32)(chunk - d.chunk0) / DELTA_PART) * SS + sy], mine[h]);
     }
 }
 
 // Per tensor: group offsets; chunk_tot becomes the start of each chunk inside its group.  With CLEAR
 // also the stream words that k_dscatter ORs into are cleared: the first word of every (chunk, group)
-// run, which is also where the run before it ends, and the word where the stream ends.
-// A workgroup takes 64 symbols, a lane each, its waves equal shares of the chunks: their sums first, then
-// the starts from the sums of the shares before.  Bound by memory latency, sixteen chunks at a time (one
-// workgroup per tensor whose threads walked all chunks of a symbol, eight at a time: 28 us for the 86 chunks
-// of 1 Mi elements, 9 us so; up to 3072 chunks belong to one tensor).
+// run, which is also where the run before it ends, and the word where the stream ends.  Without, the offsets that
+// came with the stream are compared.
+// A workgroup takes 64 symbols, a lane each, of a part of up to 128 chunks, sixteen of them a wave: one round of loads,
+// asked for together with the sums of all parts (at most some forty), which give the offsets and what lies before the
+// part.  Bound by the latency of four dependent reads.  (One workgroup per 64 symbols walked all chunks of a
+// tensor: 3072 chunks 107 us, 887 of them 43 us; so 23 and 10.  k_dhist, whose additions to one row per tensor met
+// each other, 66 and 27; now 30 and 13.)
 // With at most DELTA_FEW chunks one workgroup does it all, a wave per 64 symbols, and adds the populations up itself.
 constexpr u32 DG_WAVES = 8, DG_AHEAD = 16, DG_BLOCKS = (SS + 63) / 64;
+static_assert(DELTA_PART == DG_WAVES * DG_AHEAD, "a part is one round of loads");
 static_assert(DELTA_FEW <= DG_AHEAD && DG_BLOCKS <= DG_WAVES, "one round of loads, a wave per 64 symbols");
 template <bool CLEAR>
-__global__ __launch_bounds__(64 * DG_WAVES) void k_dgroups(const DDesc *__restrict__ dd, u32 *__restrict__ chunk_tot,
-                                                           const u32 *__restrict__ totals)
+__global__ __launch_bounds__(64 * DG_WAVES) void k_dgroups(const DDesc *__restrict__ dd, const XDesc *__restrict__ xd,
+                                                           const u32 *__restrict__ part_tensor, u32 *__restrict__ chunk_tot,
+                                                           const u32 *__restrict__ totals, u32 *__restrict__ flags)
 {
-    __shared__ u32 share[DG_WAVES][64];
-    const u32 t = blockIdx.y, lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    __shared__ u32 share[DG_WAVES][64];                   // sums of the waves' chunks
+    __shared__ u32 all[DG_WAVES][DG_BLOCKS * 64], pre[DG_WAVES][64]; // the waves' parts added up: all; those before this one
+    const u32 p = blockIdx.x / DG_BLOCKS, block = blockIdx.x % DG_BLOCKS;
+    const u32 t = part_tensor ? __builtin_amdgcn_readfirstlane(part_tensor[p]) : p;
+    const u32 lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const DDesc d = dd[t];
-    const u32 S = d.Kp + 2u, nc = (u32)d.n_chunks;
+    if (delta_single(d)) return;
+    const u32 S = d.Kp + 2u, nc = (u32)d.n_chunks, part = p - d.part0;
     const bool few = nc <= DELTA_FEW, clear = CLEAR && !d.prev_perm;
-    if (few ? blockIdx.x != 0u : blockIdx.x * 64u > S) return;
-    const u32 part = few ? wave : blockIdx.x, g = part * 64u + lane; // this lane's symbol
-    const bool is = part < DG_BLOCKS && g < S;
+    if (few ? block != 0u : block * 64u > S) return;
+    const u32 sb = few ? wave : block, g = sb * 64u + lane; // this lane's symbol
+    const bool is = sb < DG_BLOCKS && g < S;
     GLOBAL_AS u32 *ct = gptr(chunk_tot) + d.chunk0 * SS + (is ? g : 0u);
     GLOBAL_AS unsigned long long *out = gptr(d.out);
-    const u32 per = few ? nc : (nc + DG_WAVES - 1u) / DG_WAVES; // chunks of a share
-    const u32 c0 = few ? 0u : wave * per < nc ? wave * per : nc, c1 = c0 + per < nc ? c0 + per : nc;
-    u32 v[DG_AHEAD];
-    auto load = [&](u32 c) {
+    const u32 c0 = few ? 0u : part * DELTA_PART + wave * DG_AHEAD, c1 = c0 + DG_AHEAD < nc ? c0 + DG_AHEAD : nc;
+    u32 v[DG_AHEAD], sum = 0u; // of the wave's chunks
 #pragma unroll
-        for (u32 j = 0; j < DG_AHEAD; j++) v[j] = is && c + j < c1 ? ct[(u64)(c + j) * SS] : 0u;
-    };
-    u32 sum = 0u; // of the share
-    for (u32 c = c0; c < c1; c += DG_AHEAD) {
-        load(c);
+    for (u32 j = 0; j < DG_AHEAD; j++) v[j] = is && c0 + j < c1 ? ct[(u64)(c0 + j) * SS] : 0u;
+    if (!few) {
+        const u32 n_parts = (nc + DELTA_PART - 1u) / DELTA_PART;
+        u32 a[DG_BLOCKS] = {}, before = 0u;
+        for (u32 r = wave; r < n_parts; r += DG_WAVES) {
+            const GLOBAL_AS u32 *row = gptr(totals) + (u64)(d.part0 + r) * SS;
 #pragma unroll
-        for (u32 j = 0; j < DG_AHEAD; j++) sum += v[j];
+            for (u32 b = 0; b < DG_BLOCKS; b++) {
+                const u32 x = b <= block && b * 64u + lane < S ? row[b * 64u + lane] : 0u;
+                a[b] += x;
+                before += b == block && r < part ? x : 0u;
+            }
+        }
+#pragma unroll
+        for (u32 b = 0; b < DG_BLOCKS; b++) all[wave][b * 64u + lane] = a[b];
+        pre[wave][lane] = before;
     }
+#pragma unroll
+    for (u32 j = 0; j < DG_AHEAD; j++) sum += v[j];
     share[wave][lane] = sum;
     __syncthreads();
-    u32 off = 0u, run = 0u; // symbols of lower groups (below 2^32, as n is); of this one before the share
+    u32 off = 0u, run = 0u; // symbols of lower groups (below 2^32, as n is); of this one before the wave's chunks
     if (few) {
         for (u32 w = 0; w < wave; w++) off += wave_sum(share[w][lane]);
         off += wave_incl_scan(sum) - sum;
     } else {
-        for (u32 r = 0; r <= part; r++) {
-            const u32 h = r * 64u + lane, x = h < S ? totals[t * (u32)SS + h] : 0u;
-            off += r < part ? wave_sum(x) : wave_incl_scan(x) - x;
+        for (u32 b = 0; b <= block; b++) {
+            u32 x = 0u;
+#pragma unroll
+            for (u32 w = 0; w < DG_WAVES; w++) x += all[w][b * 64u + lane];
+            off += b < block ? wave_sum(x) : wave_incl_scan(x) - x;
         }
-        for (u32 w = 0; w < wave; w++) run += share[w][lane];
+#pragma unroll
+        for (u32 w = 0; w < DG_WAVES; w++) run += pre[w][lane] + (w < wave ? share[w][lane] : 0u);
     }
-    if ((few || wave == 0u) && g <= S) gptr(d.group_off)[g] = off; // (entry S: everything)
-    if (clear && (few || wave == 0u) && g == S) {
-        const u64 word = (d.n * d.wB) >> 6; // where the stream ends
-        if (word < d.out_words) out[word] = 0ull;
+    if ((few || (wave == 0u && part == 0u)) && g <= S) { // (entry S: everything)
+        gptr(d.group_off)[g] = off;
+        if (!CLEAR) {
+            const u64 *given = xd[t].group_off_in;
+            if (given && gptr(given)[g] != (u64)off) raise_flag(flags, RF_GROUPS);
+        }
+        if (clear && g == S) {
+            const u64 word = (d.n * d.wB) >> 6; // where the stream ends
+            if (word < d.out_words) out[word] = 0ull;
+        }
     }
     if (!is) return;
-    for (u32 c = c0; c < c1; c += DG_AHEAD) {
-        if (!few) load(c); // (a single round's are still there)
 #pragma unroll
-        for (u32 j = 0; j < DG_AHEAD; j++) {
-            if (c + j >= c1) break;
-            ct[(u64)(c + j) * SS] = run; // (n < 2^32)
-            const u64 word = ((u64)(off + run) * d.wB) >> 6;
-            if (clear && word < d.out_words) out[word] = 0ull;
-            run += v[j];
-        }
+    for (u32 j = 0; j < DG_AHEAD; j++) {
+        if (c0 + j >= c1) break;
+        ct[(u64)(c0 + j) * SS] = run; // (n < 2^32)
+        const u64 word = ((u64)(off + run) * d.wB) >> 6;
+        if (clear && word < d.out_words) out[word] = 0ull;
+        run += v[j];
     }
 }
 
@@ -481,6 +507,55 @@ __device__ __forceinline__ void regroup_rows(const u32 *wst, u16 *to, const u32 
     }
 }
 
+// Words of W-bit fields that lie in LDS in the order of the stream, `cnt` of them: a thread per word.
+template <u32 W>
+__device__ __forceinline__ void store_packed(const u16 *fields, u32 cnt, GLOBAL_AS unsigned long long *dst)
+{
+    const u32 bits = cnt * W, n_words = (bits + 63u) >> 6;
+    u32 k0 = threadIdx.x;
+    asm volatile("" : "+v"(k0)); // (what depends on it is computed here, for the width at hand)
+    for (u32 k = k0; k < n_words; k += DBLOCK) {
+        const u32 bit0 = k * 64u, i = bit0 / W;
+        unsigned long long v = pack_fields<W>(fields, (int)i, (int)(i * W) - (int)bit0);
+        if (bits - bit0 < 64u) v &= (1ull << (bits - bit0)) - 1ull;
+        dst[k] = v;
+    }
+}
+
+// A tensor of one tile, after its ranking: the counts of every (wave, symbol) become the start of its elements,
+// start(elements of the tile before them); returns the group offset of this thread's symbol (thread S: everything).
+// wtot: LDS for five words.
+template <class F> __device__ __forceinline__ u32 single_starts(u32 *wst, u32 srow, u32 S, u32 *wtot, F &&start)
+{
+    const u32 tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    u32 c[NWAVE], tot = 0u, off = 0u;
+    if (tid < 320u) { // waves 0..4 hold the 258 symbols
+#pragma unroll
+        for (int w = 0; w < NWAVE; w++) {
+            c[w] = tid < S ? wst[w * srow + tid] : 0u;
+            tot += c[w];
+        }
+        off = wave_incl_scan(tot);
+        if (lane == 63u) wtot[wave] = off;
+        off -= tot;
+    }
+    __syncthreads();
+    if (tid < 320u) {
+#pragma unroll
+        for (u32 w = 0; w < 4u; w++) off += w < wave ? wtot[w] : 0u;
+        if (tid < S) {
+            u32 at = off;
+#pragma unroll
+            for (int w = 0; w < NWAVE; w++) {
+                wst[w * srow + tid] = start(at);
+                at += c[w];
+            }
+        }
+    }
+    __syncthreads();
+    return off;
+}
+
 // ORDERED: same-address LDS atomics with return are served in ascending lane order on this device
 // (checked by k_lds_order_check before the library relies on it); one returning add then ranks an
 // element.  Otherwise equal symbols of a step find each other through the slot array.
@@ -527,6 +602,37 @@ __global__ __launch_bounds__(DBLOCK, 6) void k_dscatter(const DDesc *__restrict_
     const u64 lt0 = (chunk - d.chunk0) * d.ctiles;
     const u64 lt1 = (lt0 + d.ctiles < n_tiles) ? lt0 + d.ctiles : n_tiles;
     GLOBAL_AS unsigned long long *out = gptr(d.out);
+    if (delta_single(d)) {
+        // One tile: its own counts give the group offsets, and the regrouped tile is the stream.  (4096 values by
+        // k_dhist, k_dgroups and the general walk: 28 us in three launches, 12 us so.)
+        const u32 cnt = (u32)d.n;
+        lds_fetch<NWAVE>(gptr(d.prev), 0u, cnt, wp, Pw, wave);
+        lds_fetch<NWAVE>(gptr(d.cur), 0u, cnt, wc, Cw, wave);
+        for (u32 k = tid; k < NWAVE * srow; k += DBLOCK) sh.wst[k] = 0u;
+        if (!ORDERED)
+            for (u32 k = tid; k < (u32)(NWAVE * SS); k += DBLOCK) slot[k] = 0ull;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // this wave's share of the words
+        __syncthreads();
+        u32 order_bad = 0u, reg[16], dv[8];
+        const u32 ebase = wave * 1024u + lane, row_bytes = wave * srow * 4u;
+        if (ORDERED) order_bad = ordered_rank_check(Pw, sh.wst + wave * srow, ebase, cnt, S, wp);
+        // (symbol 0, the pruned one, is taken for the most frequent)
+        rank_rows<false, ORDERED, true>(Pw, Cw, sh.wst, row_bytes, slot + wave * SS, ebase, cnt, S, Bm, wp, wc, 0u, reg, dv);
+        __syncthreads();
+        const u32 off = single_starts(sh.wst, srow, S, sh.wtot, [](u32 at) { return at * 2u; });
+        if (tid <= S) gptr(d.group_off)[tid] = off;
+        regroup_rows<false>(sh.wst, fields, reg, ebase, cnt, [&](u32 r) { return (u16)((r & 1u) ? dv[r >> 1] >> 16 : dv[r >> 1]); });
+        __syncthreads();
+        with_width(wB, [&](auto width) { store_packed<decltype(width)::value>(fields, cnt, out); });
+        if (PERM) {
+            __syncthreads();
+            regroup_rows<false>(sh.wst, fields, reg, ebase, cnt, [&](u32 r) { return (u16)(ebase + r * 64u); });
+            __syncthreads();
+            for (u32 i = tid; i < cnt; i += DBLOCK) gptr(d.perm)[i] = fields[i];
+        }
+        if (ORDERED && order_bad) raise_flag(flags, DF_ORDER);
+        return;
+    }
     if (tid < S) {
         const u32 g0 = (u32)gptr(d.group_off)[tid] + chunk_tot[chunk * SS + tid];
         sh.gb[tid] = g0;
@@ -791,6 +897,42 @@ struct RestoreShared {
     ItemSets items;
 };
 
+// The current symbols of a tile's elements from the image of its stream words: reg as rank_rows leaves it, wst the
+// bit position of every (wave, symbol) in the image.
+__device__ __forceinline__ void restore_rows(const u32 *img, const u32 *wst, u16 *fields, const u32 (&reg)[16], u32 ebase,
+                                             u32 cnt, u32 row_bytes, u32 wB, u32 Bm, u32 &e_max, u32 &s_max)
+{
+    const u32 mB = (1u << wB) - 1u;
+    // sweep 2 (lanes past the tile's end read some word of the image and write fields that are masked)
+#pragma unroll
+    for (u32 rb = 0; rb < 16u; rb += 4u) {
+        u32 bo[4], x2[4][2];
+#pragma unroll
+        for (u32 q = 0; q < 4u; q++) bo[q] = *(const u32 *)((const char *)wst + (reg[rb + q] & 0xFFFFu));
+#pragma unroll
+        for (u32 q = 0; q < 4u; q++) {
+            const u32 r = rb + q;
+            const bool valid = ebase + r * 64u < cnt;
+            bo[q] = valid ? bo[q] + (reg[r] >> 16) * wB : 0u;
+            x2[q][0] = img[bo[q] >> 5];
+            x2[q][1] = img[(bo[q] >> 5) + 1u];
+        }
+#pragma unroll
+        for (u32 q = 0; q < 4u; q++) {
+            const u32 r = rb + q;
+            const u32 sp = ((reg[r] & 0xFFFFu) - row_bytes) >> 2;
+            const u32 e = __builtin_amdgcn_alignbit(x2[q][1], x2[q][0], bo[q]) & mB;
+            const u32 a = sp - e, b = a + Bm; // the one that did not wrap below zero is the smaller
+            const u32 sc = a < b ? a : b;
+            if (ebase + r * 64u < cnt) {
+                e_max = e > e_max ? e : e_max;
+                s_max = sc > s_max ? sc : s_max;
+            }
+            fields[ebase + r * 64u] = (u16)sc;
+        }
+    }
+}
+
 template <bool ORDERED>
 __global__ __launch_bounds__(DBLOCK, 6) void k_drestore(const DDesc *__restrict__ dd,
                                                         const XDesc *__restrict__ xd,
@@ -814,6 +956,35 @@ __global__ __launch_bounds__(DBLOCK, 6) void k_drestore(const DDesc *__restrict_
     const u64 n_tiles = (d.n + DTILE - 1) / DTILE;
     const u64 lt0 = (chunk - d.chunk0) * d.ctiles;
     const u64 lt1 = (lt0 + d.ctiles < n_tiles) ? lt0 + d.ctiles : n_tiles;
+    if (delta_single(d)) { // one tile, as in k_dscatter: the image is the stream
+        const u32 cnt = (u32)d.n, n_words = (cnt * wB + 63u) >> 6, row_bytes = wave * srow * 4u;
+        const u32 ebase = wave * 1024u + lane;
+        lds_fetch<NWAVE>(gptr(d.prev), 0u, cnt, wp, Pw, wave);
+        for (u32 k = tid; k < NWAVE * srow; k += DBLOCK) sh.wst[k] = 0u;
+        if (!ORDERED)
+            for (u32 k = tid; k < (u32)(NWAVE * SS); k += DBLOCK) slot[k] = 0ull;
+        constexpr u32 PER = (TWORDS + DBLOCK - 1) / DBLOCK;
+        unsigned long long w[PER];
+#pragma unroll
+        for (u32 j = 0; j < PER; j++) w[j] = tid + j * DBLOCK < n_words ? gptr(d.out)[tid + j * DBLOCK] : 0ull;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // this wave's share of the words
+        __syncthreads();
+        u32 e_max = 0u, s_max = 0u, order_bad = 0u, reg[16], unused[8];
+        if (ORDERED) order_bad = ordered_rank_check(Pw, sh.wst + wave * srow, ebase, cnt, S, wp);
+        rank_rows<false, ORDERED, false>(Pw, Pw, sh.wst, row_bytes, slot + wave * SS, ebase, cnt, S, Bm, wp, wp, 0u, reg, unused);
+        __syncthreads();
+#pragma unroll
+        for (u32 j = 0; j < PER; j++)
+            if (tid + j * DBLOCK < n_words + 1u) slot[tid + j * DBLOCK] = w[j]; // (a word behind the last: zero)
+        const u32 off = single_starts(sh.wst, srow, S, sh.wtot, [&](u32 at) { return at * wB; });
+        if (tid <= S && x.group_off_in && gptr(x.group_off_in)[tid] != (u64)off) raise_flag(flags, RF_GROUPS);
+        restore_rows((const u32 *)slot, sh.wst, fields, reg, ebase, cnt, row_bytes, wB, Bm, e_max, s_max);
+        __syncthreads();
+        with_width(wc, [&](auto width) { store_packed<decltype(width)::value>(fields, cnt, gptr(x.cur_out)); });
+        if (__ballot(e_max >= Bm || s_max >= x.Sc) && lane == 0u) raise_flag(flags, RF_DELTA);
+        if (ORDERED && order_bad) raise_flag(flags, RF_ORDER);
+        return;
+    }
     if (tid < S) sh.gb[tid] = (u32)gptr(d.group_off)[tid] + chunk_tot[chunk * SS + tid];
     if (tid == 0u) sh.hotkey = 0ull;
     for (u32 k = tid; k < (u32)WST; k += DBLOCK) sh.wst[k] = 0u;
@@ -824,7 +995,6 @@ __global__ __launch_bounds__(DBLOCK, 6) void k_drestore(const DDesc *__restrict_
     const u32 hot = __builtin_amdgcn_readfirstlane((u32)sh.hotkey & 511u);
     const u32 row_bytes = wave * srow * 4u;
     const GLOBAL_AS unsigned long long *stream = gptr(d.out);
-    const u32 mB = (1u << wB) - 1u;
     u32 e_max = 0u, s_max = 0u, order_bad = 0u; // largest delta, largest symbol
     auto tile_cnt = [&](u64 lt) -> u32 {
         const u64 rem = d.n - lt * (u64)DTILE;
@@ -915,52 +1085,12 @@ __global__ __launch_bounds__(DBLOCK, 6) void k_drestore(const DDesc *__restrict_
             }
         }
         __syncthreads();
-        // sweep 2 (lanes past the tile's end read some word of the image and write fields that are masked)
-        const u32 *img = (const u32 *)slot;
-#pragma unroll
-        for (u32 rb = 0; rb < 16u; rb += 4u) {
-            u32 bo[4], x2[4][2];
-#pragma unroll
-            for (u32 q = 0; q < 4u; q++) bo[q] = *(const u32 *)((const char *)sh.wst + (reg[rb + q] & 0xFFFFu));
-#pragma unroll
-            for (u32 q = 0; q < 4u; q++) {
-                const u32 r = rb + q;
-                const bool valid = ebase + r * 64u < cnt;
-                bo[q] = valid ? bo[q] + (reg[r] >> 16) * wB : 0u;
-                x2[q][0] = img[bo[q] >> 5];
-                x2[q][1] = img[(bo[q] >> 5) + 1u];
-            }
-#pragma unroll
-            for (u32 q = 0; q < 4u; q++) {
-                const u32 r = rb + q;
-                const u32 sp = ((reg[r] & 0xFFFFu) - row_bytes) >> 2;
-                const u32 e = __builtin_amdgcn_alignbit(x2[q][1], x2[q][0], bo[q]) & mB;
-                const u32 a = sp - e, b = a + Bm; // the one that did not wrap below zero is the smaller
-                const u32 sc = a < b ? a : b;
-                if (ebase + r * 64u < cnt) {
-                    e_max = e > e_max ? e : e_max;
-                    s_max = sc > s_max ? sc : s_max;
-                }
-                fields[ebase + r * 64u] = (u16)sc;
-            }
-        }
+        restore_rows((const u32 *)slot, sh.wst, fields, reg, ebase, cnt, row_bytes, wB, Bm, e_max, s_max);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // this wave's share of the next tile's words
         __syncthreads();
         {
-            auto words = [&](auto width) {
-                constexpr u32 W = decltype(width)::value;
-                const u32 bits = cnt * W, n_words = (bits + 63u) >> 6;
-                GLOBAL_AS unsigned long long *dst = gptr(x.cur_out) + e0 * W / 64u;
-                u32 k0 = tid;
-                asm volatile("" : "+v"(k0)); // (what depends on it is computed here, for the width at hand)
-                for (u32 k = k0; k < n_words; k += DBLOCK) {
-                    const u32 bit0 = k * 64u, i = bit0 / W;
-                    unsigned long long v = pack_fields<W>(fields, (int)i, (int)(i * W) - (int)bit0);
-                    if (bits - bit0 < 64u) v &= (1ull << (bits - bit0)) - 1ull;
-                    dst[k] = v;
-                }
-            };
-            with_width(wc, words);
+            GLOBAL_AS unsigned long long *dst = gptr(x.cur_out) + e0 * wc / 64u;
+            with_width(wc, [&](auto width) { store_packed<decltype(width)::value>(fields, cnt, dst); });
             for (u32 k = tid; k < NWAVE * srow; k += DBLOCK) sh.wst[k] = 0u; // for the next tile's counts
         }
     }
@@ -968,40 +1098,22 @@ __global__ __launch_bounds__(DBLOCK, 6) void k_drestore(const DDesc *__restrict_
     if (ORDERED && order_bad) raise_flag(flags, RF_ORDER);
 }
 
-// group offsets that came with the stream against those of the previous symbols
-__global__ __launch_bounds__(SS) void k_dcheck_groups(const DDesc *__restrict__ dd,
-                                                      const XDesc *__restrict__ xd,
-                                                      u32 *__restrict__ flags)
+// populations and group starts of the tensors that have more than one tile
+template <bool CLEAR> static void launch_counts_and_groups(const DeltaCall &c, const XDesc *xd, hipStream_t s)
 {
-    const DDesc d = dd[blockIdx.x];
-    const XDesc x = xd[blockIdx.x];
-    const u32 g = threadIdx.x;
-    if (x.group_off_in && g <= d.Kp + 2u && gptr(x.group_off_in)[g] != gptr(d.group_off)[g])
-        raise_flag(flags, RF_GROUPS);
+    if (!c.any_long) return;
+    PROF("k_dhist", s, k_dhist<<<(unsigned)c.n_chunks, HBLOCK, 0, s>>>(c.dd, c.chunk_tensor, c.chunk_tot, c.totals));
+    PROF("k_dgroups", s, k_dgroups<CLEAR><<<(unsigned)(c.n_parts * DG_BLOCKS), 64 * DG_WAVES, 0, s>>>(
+                             c.dd, xd, c.part_tensor, c.chunk_tot, c.totals, c.flags));
 }
 
-// totals: NULL when no tensor has more than DELTA_FEW chunks
-template <bool CLEAR>
-static void launch_dgroups(const DDesc *dd, int nT, u32 *chunk_tot, const u32 *totals, hipStream_t s)
+hipError_t launch_reconstruct(const DeltaCall &c, const XDesc *xd, hipStream_t s)
 {
-    for (int t0 = 0; t0 < nT; t0 += 65535) { // (the grid's second dimension ends there)
-        const int k = nT - t0 < 65535 ? nT - t0 : 65535;
-        PROF("k_dgroups", s, k_dgroups<CLEAR><<<dim3(totals ? DG_BLOCKS : 1u, k), 64 * DG_WAVES, 0, s>>>(
-                              dd + t0, chunk_tot, totals ? totals + (size_t)t0 * SS : nullptr));
-    }
-}
-
-hipError_t launch_reconstruct(const DDesc *dd, const XDesc *xd, int nT, u64 n_chunks,
-                              const u32 *chunk_tensor, u32 *chunk_tot, u32 *totals, u32 *flags, bool lds_ordered,
-                              hipStream_t s)
-{
-    PROF("k_dhist", s, k_dhist<<<(unsigned)n_chunks, HBLOCK, 0, s>>>(dd, chunk_tensor, chunk_tot, totals));
-    launch_dgroups<false>(dd, nT, chunk_tot, totals, s);
-    PROF("k_dcheck_groups", s, k_dcheck_groups<<<nT, SS, 0, s>>>(dd, xd, flags));
-    if (lds_ordered)
-        PROF("k_drestore", s, k_drestore<true><<<(unsigned)n_chunks, DBLOCK, 0, s>>>(dd, xd, chunk_tensor, chunk_tot, flags));
+    launch_counts_and_groups<false>(c, xd, s);
+    if (c.lds_ordered)
+        PROF("k_drestore", s, k_drestore<true><<<(unsigned)c.n_chunks, DBLOCK, 0, s>>>(c.dd, xd, c.chunk_tensor, c.chunk_tot, c.flags));
     else
-        PROF("k_drestore_slots", s, k_drestore<false><<<(unsigned)n_chunks, DBLOCK, 0, s>>>(dd, xd, chunk_tensor, chunk_tot, flags));
+        PROF("k_drestore_slots", s, k_drestore<false><<<(unsigned)c.n_chunks, DBLOCK, 0, s>>>(c.dd, xd, c.chunk_tensor, c.chunk_tot, c.flags));
     return hipGetLastError();
 }
 
@@ -1055,8 +1167,10 @@ constexpr size_t DST_DD = 0;                                                   /
 constexpr size_t DST_FLAGS = DST_DD + sizeof(DDesc) * DELTA_STATIC_MAX_TENSORS; // u32 flag words
 constexpr size_t DST_CT = (DST_FLAGS + 256) & ~(size_t)255;                    // u32[MAX_CHUNKS]
 constexpr size_t DST_CK = DST_CT + sizeof(u32) * DELTA_STATIC_MAX_CHUNKS;      // u32[MAX_CHUNKS][SS]
-constexpr size_t DST_TOT = DST_CK + sizeof(u32) * (size_t)DELTA_STATIC_MAX_CHUNKS * DELTA_SS; // u32[MAX_TENSORS][SS]
-constexpr size_t DST_BYTES = DST_TOT + sizeof(u32) * DELTA_STATIC_MAX_TENSORS * DELTA_SS;
+constexpr size_t DST_MAX_PARTS = DELTA_STATIC_MAX_TENSORS + DELTA_STATIC_MAX_CHUNKS / DELTA_PART;
+constexpr size_t DST_TOT = DST_CK + sizeof(u32) * (size_t)DELTA_STATIC_MAX_CHUNKS * DELTA_SS; // u32[MAX_PARTS][SS]
+constexpr size_t DST_PT = DST_TOT + sizeof(u32) * DST_MAX_PARTS * DELTA_SS;    // u32[MAX_PARTS]
+constexpr size_t DST_BYTES = DST_PT + sizeof(u32) * DST_MAX_PARTS;
 static_assert(DST_CT - DST_FLAGS >= FLAG_WORDS * sizeof(u32), "room for the flag words");
 static __device__ __align__(256) unsigned char scratch[DST_BYTES];
 
@@ -1080,57 +1194,64 @@ u32 *delta_static_flags(int device)
     return (u32 *)(g_scratch_ptr[device] + DST_FLAGS);
 }
 
-// descriptors from the kernel arguments into the scratch array; tensor of every chunk; flags cleared
+// descriptors from the kernel arguments into the scratch array; tensor of every chunk and part; totals and flags cleared
 __global__ __launch_bounds__(256) void k_dstatic_setup(DeltaStaticArgs a, DDesc *__restrict__ dd,
-                                                       u32 *__restrict__ chunk_tensor, u32 *__restrict__ totals,
-                                                       u32 *__restrict__ flags)
+                                                       u32 *__restrict__ chunk_tensor, u32 *__restrict__ part_tensor,
+                                                       u32 *__restrict__ totals, u32 n_parts, u32 *__restrict__ flags)
 {
     const u32 tid = threadIdx.x;
     if (tid < a.n_tensors) dd[tid] = a.dd[tid];
     if (tid < (u32)FLAG_WORDS) flags[tid] = 0u;
-    for (u32 i = tid; i < a.n_tensors * (u32)SS; i += 256u) totals[i] = 0u;
+    for (u32 i = tid; i < n_parts * (u32)SS; i += 256u) totals[i] = 0u;
     for (u32 t = 0; t < a.n_tensors; t++) {
         const u64 c0 = a.dd[t].chunk0, c1 = c0 + a.dd[t].n_chunks;
         for (u64 c = c0 + tid; c < c1; c += 256u) chunk_tensor[c] = t;
+        const u32 k = (u32)((a.dd[t].n_chunks + DELTA_PART - 1u) / DELTA_PART);
+        for (u32 i = tid; i < k; i += 256u) part_tensor[a.dd[t].part0 + i] = t;
     }
 }
 
-hipError_t launch_delta_static(int device, const DeltaStaticArgs &a, u64 n_dtiles, u64 n_chunks,
+hipError_t launch_delta_static(int device, const DeltaStaticArgs &a, u64 n_chunks, u64 n_parts, bool any_long,
                                bool any_scatter, bool any_perm, bool lds_ordered, hipStream_t s)
 {
     if (device < 0 || device >= MAX_DEVICES || !g_scratch_ptr[device]) return hipErrorNotInitialized;
-    if (a.n_tensors > (u32)DELTA_STATIC_MAX_TENSORS || n_chunks > (u64)DELTA_STATIC_MAX_CHUNKS)
+    if (a.n_tensors > (u32)DELTA_STATIC_MAX_TENSORS || n_chunks > (u64)DELTA_STATIC_MAX_CHUNKS || n_parts > DST_MAX_PARTS)
         return hipErrorInvalidValue;
     unsigned char *base = g_scratch_ptr[device];
     DDesc *dd = (DDesc *)(base + DST_DD);
-    u32 *flags = (u32 *)(base + DST_FLAGS);
-    u32 *chunk_tensor = (u32 *)(base + DST_CT);
-    u32 *totals = (u32 *)(base + DST_TOT);
-    u32 *chunk_tot = (u32 *)(base + DST_CK); // every entry of the chunks in use is written by k_dhist
-    PROF("k_dstatic_setup", s, k_dstatic_setup<<<1, 256, 0, s>>>(a, dd, chunk_tensor, totals, flags));
-    return launch_delta(dd, (int)a.n_tensors, n_dtiles, n_chunks, chunk_tensor, chunk_tot, totals, flags,
-                        any_scatter, any_perm, false, lds_ordered, s);
+    u32 *chunk_tensor = (u32 *)(base + DST_CT), *part_tensor = (u32 *)(base + DST_PT);
+    DeltaCall c;
+    c.dd = dd;
+    c.chunk_tensor = chunk_tensor;
+    c.part_tensor = part_tensor;
+    c.chunk_tot = (u32 *)(base + DST_CK); // every entry of the chunks in use is written by k_dhist
+    c.totals = (u32 *)(base + DST_TOT);
+    c.flags = (u32 *)(base + DST_FLAGS);
+    c.n_chunks = n_chunks;
+    c.n_parts = n_parts;
+    c.any_long = any_long;
+    c.lds_ordered = lds_ordered;
+    PROF("k_dstatic_setup", s, k_dstatic_setup<<<1, 256, 0, s>>>(a, dd, chunk_tensor, part_tensor, c.totals, (u32)n_parts, c.flags));
+    return launch_delta(c, any_scatter, any_perm, false, s);
 }
 
-hipError_t launch_delta(const DDesc *dd, int nT, u64 n_dtiles, u64 n_chunks,
-                        const u32 *chunk_tensor, u32 *chunk_tot, u32 *totals, u32 *flags, bool any_scatter,
-                        bool any_perm, bool any_gather, bool lds_ordered, hipStream_t s)
+hipError_t launch_delta(const DeltaCall &c, bool any_scatter, bool any_perm, bool any_gather, hipStream_t s)
 {
-    PROF("k_dhist", s, k_dhist<<<(unsigned)n_chunks, HBLOCK, 0, s>>>(dd, chunk_tensor, chunk_tot, totals));
-    launch_dgroups<true>(dd, nT, chunk_tot, totals, s);
+    launch_counts_and_groups<true>(c, nullptr, s);
+    const unsigned n = (unsigned)c.n_chunks;
     if (any_scatter) {
-        if (lds_ordered)
-            PROF("k_dscatter", s, k_dscatter<false, true><<<(unsigned)n_chunks, DBLOCK, 0, s>>>(dd, chunk_tensor, chunk_tot, flags));
+        if (c.lds_ordered)
+            PROF("k_dscatter", s, k_dscatter<false, true><<<n, DBLOCK, 0, s>>>(c.dd, c.chunk_tensor, c.chunk_tot, c.flags));
         else
-            PROF("k_dscatter_slots", s, k_dscatter<false, false><<<(unsigned)n_chunks, DBLOCK, 0, s>>>(dd, chunk_tensor, chunk_tot, flags));
+            PROF("k_dscatter_slots", s, k_dscatter<false, false><<<n, DBLOCK, 0, s>>>(c.dd, c.chunk_tensor, c.chunk_tot, c.flags));
     }
     if (any_perm) {
-        if (lds_ordered)
-            PROF("k_dscatter_perm", s, k_dscatter<true, true><<<(unsigned)n_chunks, DBLOCK, 0, s>>>(dd, chunk_tensor, chunk_tot, flags));
+        if (c.lds_ordered)
+            PROF("k_dscatter_perm", s, k_dscatter<true, true><<<n, DBLOCK, 0, s>>>(c.dd, c.chunk_tensor, c.chunk_tot, c.flags));
         else
-            PROF("k_dscatter_perm_slots", s, k_dscatter<true, false><<<(unsigned)n_chunks, DBLOCK, 0, s>>>(dd, chunk_tensor, chunk_tot, flags));
+            PROF("k_dscatter_perm_slots", s, k_dscatter<true, false><<<n, DBLOCK, 0, s>>>(c.dd, c.chunk_tensor, c.chunk_tot, c.flags));
     }
-    if (any_gather) PROF("k_dgather", s, k_dgather<<<(unsigned)n_chunks, BLOCK, 0, s>>>(dd, chunk_tensor, flags));
+    if (any_gather) PROF("k_dgather", s, k_dgather<<<n, BLOCK, 0, s>>>(c.dd, c.chunk_tensor, c.flags));
     return hipGetLastError();
 }
 

@@ -158,9 +158,10 @@ struct DDesc { // one tensor of a delta call
     u32 *perm;
     const u32 *prev_perm;
     u64 n, out_words;
-    u64 dtile0, chunk0, n_chunks;
+    u64 chunk0, n_chunks;
     u32 wp, wc, Kp, B, wB;
     u32 ctiles;          // tiles of a chunk (delta_chunk_tiles)
+    u32 part0, pad;      // first of its parts (DELTA_PART) in the call-wide numbering
 };
 struct RDesc { // one tensor of a dequantize call
     const unsigned long long *packed;
@@ -190,6 +191,11 @@ constexpr u32 DF_ORDER = 2u;   // ranks from returning LDS adds disagree with ra
 constexpr int DELTA_TILE = 12288;
 constexpr int DELTA_CHUNK = 64; // most tiles of a chunk
 constexpr u32 DELTA_FEW = 16;   // chunks of a tensor up to which nobody adds its symbols' populations up in `totals`
+constexpr u32 DELTA_PART = 128; // chunks of a part: the unit in which they are added up, and that a workgroup of
+                                // k_dgroups takes
+inline u64 delta_parts(u64 n_chunks) { return (n_chunks + DELTA_PART - 1) / DELTA_PART; }
+// A tensor of one tile is regrouped by one workgroup from the tile's own counts (unless its regrouping is given).
+__host__ __device__ inline bool delta_single(const DDesc &d) { return d.n <= (u64)DELTA_TILE && !d.prev_perm; }
 // Tiles per chunk of a delta / reconstruct call over n_tiles tiles in all.  A chunk is walked by one
 // workgroup and costs about a tile's time on top of its tiles (its groups' runs are found, opened and
 // closed), so chunks are as long as possible; but two workgroups fit a CU, and with fewer than
@@ -266,12 +272,21 @@ hipError_t launch_quantize(const Batch &bt, const QDesc *qd, const Unit *units, 
                            hipStream_t s);
 // the tensors marked in their descriptors, which the batch's gather units cover
 hipError_t launch_fused(const Batch &bt, const QDesc *qd, QInfo *qi, hipStream_t s);
-hipError_t launch_delta(const DDesc *dd, int nT, u64 n_dtiles, u64 n_chunks,
-                        const u32 *chunk_tensor, u32 *chunk_tot, u32 *totals, u32 *flags, bool any_scatter,
-                        bool any_perm, bool any_gather, bool lds_ordered, hipStream_t s);
+struct DeltaCall { // what the kernels of a delta or reconstruct call share
+    const DDesc *dd;           // device
+    const u32 *chunk_tensor;   // device [n_chunks]
+    const u32 *part_tensor;    // device [n_parts], NULL: every tensor has one part
+    u32 *chunk_tot;            // device [n_chunks][DELTA_SS] populations of the previous symbols
+    u32 *totals;               // device [n_parts][DELTA_SS], cleared; NULL: no tensor has more than DELTA_FEW chunks
+    u32 *flags;
+    u64 n_chunks, n_parts;
+    bool any_long;             // some tensor is not delta_single
+    bool lds_ordered;
+};
+hipError_t launch_delta(const DeltaCall &c, bool any_scatter, bool any_perm, bool any_gather, hipStream_t s);
 hipError_t delta_static_init(int device); // once per device, with that device current
 u32 *delta_static_flags(int device);      // the flag words of launch_delta_static on that device
-hipError_t launch_delta_static(int device, const DeltaStaticArgs &a, u64 n_dtiles, u64 n_chunks,
+hipError_t launch_delta_static(int device, const DeltaStaticArgs &a, u64 n_chunks, u64 n_parts, bool any_long,
                                bool any_scatter, bool any_perm, bool lds_ordered, hipStream_t s);
 hipError_t launch_sens_score(const SDesc *sd, int nT, u32 n_runs, hipStream_t s);
 hipError_t launch_sens_partition(const SDesc *sd, int nT, u32 n_runs, u32 *ticket, u64 *state,
@@ -281,9 +296,7 @@ hipError_t launch_sens_quant(const SDesc *sd, int nT, u32 n_runs, const u32 *run
 hipError_t launch_lds_order_check(u32 *violations, hipStream_t s);
 hipError_t launch_dequantize(const RDesc *rd, int nT, u64 n_tiles, u64 max_outlier, u32 *flags,
                              u32 *ones, int n_cu, hipStream_t s);
-hipError_t launch_reconstruct(const DDesc *dd, const XDesc *xd, int nT, u64 n_chunks,
-                              const u32 *chunk_tensor, u32 *chunk_tot, u32 *totals, u32 *flags, bool lds_ordered,
-                              hipStream_t s);
+hipError_t launch_reconstruct(const DeltaCall &c, const XDesc *xd, hipStream_t s);
 
 // ------------------------------------------------------------------------------------------
 // the pairs and boundaries in view

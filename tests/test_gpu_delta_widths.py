@@ -172,3 +172,31 @@ def test_numbers_of_chunks(n):
     assert np.array_equal(u64(d.packed), ref.pack(e[order].astype(np.uint16), api.symbol_bits(K)))
     assert torch.equal(ctx.reconstruct([prev], [d], [5], [K])[0], cur.packed)
     ctx.close()
+
+
+@pytest.mark.parametrize("sizes", [[128 * 12288], [128 * 12288 + 1, 40], [256 * 12288 + 5, 17 * 12288], [5, 12288, 300],
+                                   [12289, 16 * 12288, 3, 391 * 12288 + 77, 17 * 12288 + 1]])
+def test_parts_of_chunks(sizes):
+    """Chunks of one tile around the numbers that make one part, several, none; tensors of one tile alone and beside
+    longer ones; offsets that do not match are reported by either way of counting."""
+    from paper_2306_11800_amd import api
+    ctx = api.Context(torch.device("cuda:0"))
+    rng = np.random.default_rng(len(sizes) * 1000 + sizes[0] % 997)
+    sp, sc = ([symbols(rng, n, 256, "even") for n in sizes] for _ in range(2))
+    qp, qc = [codes(s, 256) for s in sp], [codes(s, 256) for s in sc]
+    ds = ctx.delta(qp, qc, want_perm=True)
+    ctx.sync()
+    for d, a, b in zip(ds, sp, sc):
+        r = ref.delta(a, 0, b, 0, K_prev=256, K_cur=256)
+        assert np.array_equal(u64(d.group_off), r["group_off"])
+        assert np.array_equal(u64(d.packed), ref.pack(r["stream"], r["delta_bits"]))
+        assert np.array_equal(u32(d.perm), r["perm"])
+    for w, q in zip(ctx.reconstruct(qp, ds, [0] * len(qp), [256] * len(qp)), qc):
+        assert torch.equal(w, q.packed)
+    for t in range(len(sizes)):
+        ds[t].group_off[257] += 1
+        with pytest.raises(api.InshrError) as e:
+            ctx.reconstruct(qp, ds, [0] * len(qp), [256] * len(qp))
+        assert e.value.code == -5
+        ds[t].group_off[257] -= 1
+    ctx.close()
