@@ -649,6 +649,7 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         bt.n_grp_total = (u32 *)(db + o_ngt);
         bt.n_units = (int)units;
         bt.n_bucket_blocks = c->n_cu * 4;
+        bt.n_cu = c->n_cu;
         bt.lds_ordered = c->lds_ordered;
         bt.any_sampled = any_sampled;
         bt.any_pooled = any_pooled;
@@ -714,7 +715,7 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
     }
     c->batch.light = light;
     c->batch.spread = mode == CHOOSE || mode == LIGHT;
-    HIPCHK(c, launch_small(c->batch, c->stream));
+    if (mode != CHOOSE) HIPCHK(c, launch_small(c->batch, c->stream));
     HIPCHK(c, launch_select(c->batch, c->stream));
     c->resolved.assign(nT, VIEW_ALL); // (the small tensors are searched completely)
     std::fill(c->resolved.begin(), c->resolved.begin() + nB, VIEW_NONE);

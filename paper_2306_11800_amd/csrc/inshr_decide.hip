@@ -32,7 +32,7 @@
 //
 // One workgroup per tensor (its LDS leaves room for one on a CU), bound by the latency of its steps: 39 us for one tensor
 // (k_plan2, the first of those it takes the place of, 36 us), 128 us for 294 tensors and 105 configurations.
-#include "inshr_launch.h"
+#include "inshr_small.h"
 
 namespace inshr {
 
@@ -65,11 +65,9 @@ struct DecideShared {
     u32 tmp[BLOCK / 64], tmp2[BLOCK / 64];
 };
 
-__global__ __launch_bounds__(BLOCK) void k_decide(const TDesc *__restrict__ td, const GridDesc *__restrict__ gd,
-                                                  const u32 *__restrict__ t_fu_off, Bufs B)
+__device__ __forceinline__ void decide(DecideShared &sh, int t, const TDesc *__restrict__ td, const GridDesc *__restrict__ gd,
+                                       const u32 *__restrict__ t_fu_off, const Bufs &B)
 {
-    __shared__ DecideShared sh;
-    const int t = blockIdx.x;
     const u32 tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const u64 n = td[t].n;
     TState *st = B.ts + t;
@@ -428,9 +426,39 @@ __global__ __launch_bounds__(BLOCK) void k_decide(const TDesc *__restrict__ td, 
     }
 }
 
+// The small tensors' searches in the first n_small workgroups (n16 of the larger kind first), which take as long as a
+// decision: 70 us, 60 us here and two launches of small ones before them were 70 + 50 + 60 us for a checkpoint of all
+// three kinds.
+template <bool ORDERED>
+__global__ __launch_bounds__(BLOCK) void k_decide(const TDesc *__restrict__ td, const GridDesc *__restrict__ gd,
+                                                  const u32 *__restrict__ t_fu_off, Bufs B, int nB, int n16, int n_small)
+{
+    extern __shared__ double sm_decide[];
+    const int b = blockIdx.x;
+    if (b < n_small)
+        small_beside<ORDERED>(sm_decide, td, gd, B, nB + b, b < n16);
+    else
+        decide(*reinterpret_cast<DecideShared *>(sm_decide), b - n_small, td, gd, t_fu_off, B);
+}
+
 hipError_t launch_decide(const Batch &bt, hipStream_t s)
 {
-    if (bt.nB) PROF("k_decide", s, k_decide<<<bt.nB, BLOCK, 0, s>>>(bt.td, bt.gd, bt.t_fu_off, bt.bufs));
+    constexpr int lds = (int)sizeof(DecideShared) > SMALL_LDS ? (int)sizeof(DecideShared) : SMALL_LDS;
+    static bool attr = false;
+    hipError_t e;
+    if (!attr) {
+        if ((e = hipFuncSetAttribute((const void *)k_decide<true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds))) return e;
+        if ((e = hipFuncSetAttribute((const void *)k_decide<false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds))) return e;
+        attr = true;
+    }
+    if (bt.nB == 0) return launch_small(bt, s);
+    const bool crowd = small_crowd(bt, bt.nB);
+    if (crowd && bt.nS0 && (e = launch_small_many(bt, s))) return e;
+    const int n_small = bt.nS1 + (crowd ? 0 : bt.nS0);
+    if (bt.lds_ordered)
+        PROF("k_decide", s, k_decide<true><<<n_small + bt.nB, BLOCK, lds, s>>>(bt.td, bt.gd, bt.t_fu_off, bt.bufs, bt.nB, bt.nS1, n_small));
+    else
+        PROF("k_decide", s, k_decide<false><<<n_small + bt.nB, BLOCK, lds, s>>>(bt.td, bt.gd, bt.t_fu_off, bt.bufs, bt.nB, bt.nS1, n_small));
     return hipGetLastError();
 }
 

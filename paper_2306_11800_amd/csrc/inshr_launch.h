@@ -95,6 +95,7 @@ struct Batch {
     int n_units;
     int n_gwg, n_gunits; // workgroups and units of sweep 3
     int n_bucket_blocks;
+    int n_cu;
     bool lds_ordered;    // same-address LDS atomics return in lane order on this device
     bool spread;         // k_decide or the sketch kernels work with the second histogram's bins
     bool light;          // thresholds and class counts only: no boundaries, no scores (the sketch
@@ -261,12 +262,14 @@ void prof_end(hipStream_t s);
 
 hipError_t launch_select(const Batch &bt, hipStream_t s); // thresholds: sweeps 1 and 2 and what follows from them
 hipError_t launch_counts(const Batch &bt, hipStream_t s); // class counts of every pair: ends a search without a choice
-hipError_t launch_decide(const Batch &bt, hipStream_t s); // the choice, where bounds of the errors settle it
+// the choice of a search without scores: small tensors searched, the others where bounds of the errors settle it
+hipError_t launch_decide(const Batch &bt, hipStream_t s);
 // boundaries, centres and errors of the configurations in view (sweep 3 and what follows from it)
 hipError_t launch_resolve(const Batch &bt, hipStream_t s);
 hipError_t launch_edges(const Batch &bt, hipStream_t s); // edge order, bins without edges (inside launch_resolve)
 hipError_t launch_score(const Batch &bt, hipStream_t s); // centres, errors, choice (inside launch_resolve)
 hipError_t launch_small(const Batch &bt, hipStream_t s); // the whole search of the small tensors
+hipError_t launch_small_many(const Batch &bt, hipStream_t s); // of those of up to SMALL_TINY values (small_crowd)
 // the tensors of the units (and the small ones), whose boundaries and centres the state holds
 hipError_t launch_quantize(const Batch &bt, const QDesc *qd, const Unit *units, const u32 *wg_u0, int n_wg, QInfo *qi,
                            hipStream_t s);
