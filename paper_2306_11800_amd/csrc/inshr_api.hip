@@ -34,7 +34,7 @@ struct inshr_ctx {
     hipStream_t stream = nullptr;
     uint64_t scratch_limit = 0;
     int n_cu = 256;
-    int wg_per_cu = 2;
+    int wg_per_cu = 0; // workgroups that a sweep deals a CU, 0: by sweep_workgroups (INSHR_WG_PER_CU)
     bool lds_ordered = false; // same-address LDS atomics return in lane order (checked at creation)
     // tensors of at least this many elements get a sampled first sweep (INSHR_SAMPLE_MIN_N; 0 = never)
     uint64_t sample_min_n = 16ull << 20;
@@ -344,6 +344,17 @@ void deal_tiles(const std::vector<TDesc> &td, uint32_t nB, const std::vector<u32
     for (uint32_t t = 0; t < nB; t++) p.t_off[t + 1] += p.t_off[t];
 }
 
+// Workgroups of a sweep over so many tiles.  One is resident on a CU (its tables fill the LDS).  A second one in turn
+// evens out what tiles cost and makes more, shorter units for the kernels that take a workgroup per unit, but starts and
+// empties its tables once more, which tensors of a few hundred tiles take as long for as for their tiles.  One / two, ms of
+// kernels: 12 M values scored 0.47 / 0.55, 54 M step 0.80 / 0.94, 330 M step 2.44 / 2.56, 355 M scored 2.66 / 2.82,
+// 615 M step 3.26 / 3.25, 6.7 G step 33.7 / 33.2: two from 96 tiles per CU (400 M values) on.
+int sweep_workgroups(const inshr_ctx *c, u64 tiles)
+{
+    const u64 per = c->wg_per_cu ? (u64)c->wg_per_cu : tiles >= 96ull * (u64)c->n_cu ? 2ull : 1ull;
+    return (int)std::min<u64>(tiles, (u64)c->n_cu * per);
+}
+
 // Gather units for the tensors ts (device positions, ascending), in p and, with st, on the device.  The copy is staged
 // at offset at of h_up: nothing in flight reads that part of it, and where it is too small to
 // hold it, nothing in flight reads any of it.
@@ -510,8 +521,7 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
     HIPCHK(c, hipStreamSynchronize(c->stream)); // staging buffers may be in flight (inshr_delta)
 
     // work partition: tiles are dealt out evenly to workgroups in order
-    const int n_wg = (int)std::min<uint64_t>(total_tiles, (uint64_t)c->n_cu * c->wg_per_cu);
-    const int n_wg_all = (int)std::min<uint64_t>(all_tiles, (uint64_t)c->n_cu * c->wg_per_cu);
+    const int n_wg = sweep_workgroups(c, total_tiles), n_wg_all = sweep_workgroups(c, all_tiles);
     std::vector<TDesc> &td = c->td;
     td.assign(nT, TDesc());
     std::vector<u64> wg_tile0(n_wg + 1);
@@ -558,7 +568,7 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         const size_t o_gd = cv.take(sizeof(GridDesc));
         const size_t o_wt = cv.take(sizeof(u64) * (n_wg + 1));
         const size_t o_wa = cv.take(sizeof(u64) * (n_wg_all + 1));
-        const size_t o_wf = cv.take(sizeof(u32) * n_wg);
+        const size_t o_wf = cv.take(sizeof(u32) * (n_wg + 1));
         const size_t o_tfo = cv.take(sizeof(u32) * (nB + 1));
         const size_t o_un = cv.take(sizeof(Unit) * units);
         const size_t up_bytes = cv.off;
@@ -625,7 +635,7 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         memcpy(hb + o_td, td.data(), sizeof(TDesc) * nT);
         memcpy(hb + o_gd, &g, sizeof(GridDesc));
         memcpy(hb + o_wt, wg_tile0.data(), sizeof(u64) * (n_wg + 1));
-        memcpy(hb + o_wf, part.wg0.data(), sizeof(u32) * n_wg);
+        memcpy(hb + o_wf, part.wg0.data(), sizeof(u32) * part.wg0.size());
         memcpy(hb + o_tfo, part.t_off.data(), sizeof(u32) * (nB + 1));
         memcpy(hb + o_un, part.units.data(), sizeof(Unit) * units);
         {

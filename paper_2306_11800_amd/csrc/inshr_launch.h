@@ -81,7 +81,7 @@ struct Batch {
     const TDesc *td;     // device
     const GridDesc *gd;  // device
     const u64 *wg_tile0; // device [n_wg + 1]
-    const u32 *wg_fu0;   // device [n_wg] first (workgroup, tensor) unit of each workgroup
+    const u32 *wg_fu0;   // device [n_wg + 1] (workgroup, tensor) units of each workgroup
     const u32 *t_fu_off; // device [nT + 1] first unit of each tensor (in ascending workgroup order)
     const u32 *wg_gu0;   // device [n_gwg + 1] gather units of each workgroup of sweep 3
     const u32 *t_gu_off; // device [nB + 1] gather units of each tensor
