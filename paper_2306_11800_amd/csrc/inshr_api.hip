@@ -405,6 +405,53 @@ int resolve(inshr_ctx *c, const std::vector<u32> &view, size_t at)
 // a unit's share of a pool for each wave) are made for small fractions.
 constexpr uint32_t FUSE_MAX_PPM = 10000, FUSE_MIN_WCAP = 32;
 
+// a tensor's span of the gather pools, which its units' lists share
+void enter_span(QDesc &q, const Partition &p, u32 t)
+{
+    const u32 u0 = p.t_off[t], u1 = p.t_off[t + 1];
+    q.fused = 1u;
+    q.span = p.units[u0].off();
+    q.span_len = p.units[u1 - 1].off() + (u64)p.units[u1 - 1].capw * (BLOCK / 64) - q.span;
+}
+
+bool fusable(const inshr_ctx *c, u32 g)
+{
+    return c->wcap >= FUSE_MIN_WCAP && c->grid_cfgs[g].outlier_ppm <= FUSE_MAX_PPM;
+}
+
+// Room in h_up that score_one takes: what upload_units stages, and the descriptors.
+size_t score_one_bytes(const inshr_ctx *c) { return (c->view_end - c->view_off) + sizeof(QDesc) * (size_t)c->batch.nB + 256; }
+
+// Enqueues the work that gives boundaries, centres and the exact error of one configuration per tensor (cfg: per device
+// position, VIEW_NONE: none; all of them fusable) by the quantizer's sweep without its outputs.  A tensor that
+// its means do not hold says so in its results (fuse_bad) and is left as it was.  Staged at offset at of h_up.
+int score_one(inshr_ctx *c, const std::vector<u32> &cfg, size_t at)
+{
+    const uint32_t nB = (uint32_t)c->batch.nB;
+    std::vector<u32> ts;
+    for (uint32_t t = 0; t < nB; t++)
+        if (cfg[t] != VIEW_NONE) ts.push_back(t);
+    if (ts.empty()) return INSHR_OK;
+    int rc = ensure_dev(c, c->aux_mem, sizeof(QDesc) * nB); // (less than the search took)
+    if (rc) return rc;
+    rc = ensure_host(c, c->h_up, at + score_one_bytes(c));
+    if (rc) return rc;
+    Partition p;
+    Stage st;
+    if ((rc = upload_units(c, std::vector<u32>(nB, VIEW_NONE), ts, p, at, st))) return rc;
+    const size_t o_qd = (at + (c->view_end - c->view_off) + 255) & ~(size_t)255;
+    QDesc *qd = (QDesc *)((char *)c->h_up.p + o_qd);
+    memset(qd, 0, sizeof(QDesc) * nB);
+    for (u32 t : ts) {
+        qd[t].cfg = cfg[t];
+        enter_span(qd[t], p, t);
+    }
+    st.add(c->aux_mem.p, qd, sizeof(QDesc) * nB);
+    HIPCHK(c, launch_stage(st, c->n_cu, c->stream));
+    HIPCHK(c, launch_fused(c->batch, (const QDesc *)c->aux_mem.p, nullptr, c->stream));
+    return INSHR_OK;
+}
+
 // What a search is for.  CHOOSE: best and feasible alone; where bounds of the errors settle the choice of a
 // tensor, nothing else is worked out for it (resolve() does so for the configurations that
 // inshr_quantize asks for).  SCORES: every configuration's score.  GIVEN: thresholds and class counts for
@@ -723,6 +770,7 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         B.scores = (Score *)(db + o_sc);
         c->scores_off = o_sc;
     }
+    c->grid_cfgs.assign(grid, grid + n_cfg);
     c->batch.light = light;
     c->batch.spread = mode == CHOOSE || mode == LIGHT;
     if (mode != CHOOSE) HIPCHK(c, launch_small(c->batch, c->stream));
@@ -744,6 +792,7 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
     if (rc) return rc;
     char *db = (char *)c->search_mem.p;
     const SearchResult *res = (const SearchResult *)c->h_res.p;
+    std::vector<char> tried(nB, 0);
     for (;;) {
         if (sc_bytes)
             HIPCHK(c, hipMemcpyAsync(c->h_down.p, db + c->scores_off, sc_bytes, hipMemcpyDeviceToHost, c->stream));
@@ -751,16 +800,24 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         rc = check_results(c, nT, any_pooled);
         if (rc == 1) return run_search(c, tensors, nT, grid, n_cfg, eps, mode, group);
         if (rc) return rc;
-        // tensors whose choice the bounds leave open are scored: the configuration it hangs on, or all of them
+        // Tensors whose choice the bounds leave open are scored: the configuration it hangs on, by the quantizer's
+        // sweep where its means hold all of them (they go along where a tensor's whole grid is scored: the other
+        // chain of kernels takes longer than they do on top of it, BERT-base with Adam state 3.11 instead of 3.03 ms),
+        // or the whole grid.
         std::vector<u32> open(nB, VIEW_NONE);
-        bool any_open = false;
+        bool any_open = false, fuse = true;
         for (uint32_t t = 0; t < nB; t++)
             if (res[t].best >= CHOICE_IF) {
                 open[t] = c->resolved[t] = res[t].best == VIEW_NONE ? VIEW_ALL : res[t].best & ~CHOICE_IF;
-                any_open = true;
+                fuse = fuse && open[t] != VIEW_ALL && !tried[t] && fusable(c, open[t]);
+                tried[t] = any_open = true;
             }
         if (!any_open) break;
-        if ((rc = resolve(c, open, view_at))) return rc;
+        if (fuse) {
+            rc = ensure_host(c, c->h_up, view_at + score_one_bytes(c)); // (nothing is in flight)
+            if (rc) return rc;
+        }
+        if ((rc = fuse ? score_one(c, open, view_at) : resolve(c, open, view_at))) return rc;
     }
     if (getenv("INSHR_SAMPLE_DEBUG")) { // how many sampled first sweeps had to be repeated exactly
         uint32_t n_sampled = 0, n_redo = 0;
@@ -776,7 +833,6 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
                 nT, n_sampled, n_redo);
     }
     c->grid = g;
-    c->grid_cfgs.assign(grid, grid + n_cfg);
     c->tensors.assign(tensors, tensors + nT);
     c->groups.clear();
     if (group) c->groups.assign(group, group + nT);
@@ -795,6 +851,41 @@ int repeat_search(inshr_ctx *c)
     const std::vector<u32> groups = c->groups;
     return run_search(c, tensors.data(), (uint32_t)tensors.size(), grid.data(), (uint32_t)grid.size(), c->eps, c->mode,
                       groups.empty() ? nullptr : groups.data());
+}
+
+// Boundaries, centres and scores of one configuration per tensor (cfg: by the caller's order) after a search for given
+// configurations; the scores go to h_down, for every configuration of the grid and device position.  1: the search has to
+// be repeated for larger pools.
+int score_given(inshr_ctx *c, const std::vector<uint32_t> &cfg)
+{
+    const uint32_t nT = (uint32_t)c->batch.nT, nB = (uint32_t)c->batch.nB;
+    const size_t sc_bytes = sizeof(Score) * (size_t)nT * c->batch.n_cfg;
+    int rc = ensure_host(c, c->h_down, sc_bytes);
+    if (rc) return rc;
+    std::vector<u32> want(nB, VIEW_NONE), one(nB, VIEW_NONE), apart(nB, VIEW_NONE);
+    for (uint32_t t = 0; t < nT; t++)
+        if (c->pos[t] < nB) want[c->pos[t]] = cfg[t];
+    for (uint32_t t = 0; t < nB; t++) (fusable(c, want[t]) ? one : apart)[t] = want[t];
+    const SearchResult *res = (const SearchResult *)c->h_res.p;
+    for (;;) {
+        // (each of the two stages its units in a place of its own)
+        const size_t one_at = (c->view_end - c->view_off + 255) & ~(size_t)255;
+        rc = ensure_host(c, c->h_up, one_at + score_one_bytes(c)); // (nothing is in flight)
+        if (rc) return rc;
+        if ((rc = score_one(c, one, one_at))) return rc;
+        if ((rc = resolve(c, apart, 0))) return rc;
+        HIPCHK(c, hipMemcpyAsync(c->h_down.p, (char *)c->search_mem.p + c->scores_off, sc_bytes, hipMemcpyDeviceToHost, c->stream));
+        HIPCHK(c, hipStreamSynchronize(c->stream));
+        rc = check_results(c, nT, c->any_pooled);
+        if (rc) return rc;
+        bool again = false;
+        for (uint32_t t = 0; t < nB; t++) {
+            apart[t] = one[t] != VIEW_NONE && res[t].fuse_bad ? one[t] : VIEW_NONE;
+            again = again || apart[t] != VIEW_NONE;
+            one[t] = VIEW_NONE;
+        }
+        if (!again) return INSHR_OK;
+    }
 }
 
 // Everything a search with scores leaves behind, for all tensors.
@@ -1074,7 +1165,7 @@ static int quantize_with_state(inshr_ctx *c, const inshr_config *cfg, inshr_quan
             if (!asked[t].packed || done[t]) continue;
             if (alt_key || c->resolved[t] == VIEW_ALL || c->resolved[t] == asked[t].cfg)
                 ready.push_back(t);
-            else if (!apart[t] && c->wcap >= FUSE_MIN_WCAP && c->grid_cfgs[asked[t].cfg].outlier_ppm <= FUSE_MAX_PPM)
+            else if (!apart[t] && fusable(c, asked[t].cfg))
                 fuse.push_back(t);
             else
                 open = true;
@@ -1099,11 +1190,8 @@ static int quantize_with_state(inshr_ctx *c, const inshr_config *cfg, inshr_quan
         }
         for (u32 t : ready) qd[t].packed = asked[t].packed;
         for (u32 t : fuse) {
-            const u32 u0 = p.t_off[t], u1 = p.t_off[t + 1];
             qd[t].packed = asked[t].packed;
-            qd[t].fused = 1u;
-            qd[t].span = p.units[u0].off();
-            qd[t].span_len = p.units[u1 - 1].off() + (u64)p.units[u1 - 1].capw * (BLOCK / 64) - qd[t].span;
+            enter_span(qd[t], p, t);
         }
         Partition pq;
         deal_tiles(c->td, nB, ready, c->batch.n_wg, c->wcap, pq);
@@ -1863,9 +1951,14 @@ int inshr_quantize_sens(inshr_ctx *c, const inshr_tensor *tensors, const float *
         sub[t].n = si[t].n_kept;
     }
     // the bins: the quantized values as tensors of their own, nothing pruned, nothing protected
-    rc = run_search(c, sub.data(), nT, bin_grid.data(), (uint32_t)bin_grid.size(), 0.0, SCORES);
-    if (rc) return rc;
-    c->have_search = false; // (the state describes the compacted values, not the caller's tensors)
+    // (every tensor's own number of bins is all that is scored)
+    do {
+        rc = run_search(c, sub.data(), nT, bin_grid.data(), (uint32_t)bin_grid.size(), 0.0, GIVEN);
+        if (rc) return rc;
+        c->have_search = false; // (the state describes the compacted values, not the caller's tensors)
+        rc = score_given(c, bin_of_t);
+        if (rc < 0) return rc;
+    } while (rc == 1); // larger pools
     const Score *hsc = (const Score *)c->h_down.p;
     const uint32_t n_bg = (uint32_t)bin_grid.size();
     std::vector<double> sse_q(nT), sq_q(nT);

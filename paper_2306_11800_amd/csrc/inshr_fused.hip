@@ -23,6 +23,10 @@
 // k_quant for one configuration took 8.7 (k_gather) + 0.6 + 8.9 (k_quant).  100 M values in 48 tensors: 0.25 ms where
 // k_plan2 .. k_quant took 0.70.
 //
+// Without output buffers (QDesc::packed is NULL) the same kernels work out boundaries, centres and the exact error of the
+// configuration and settle a choice that hangs on it: 1 Mi values 67 us where k_plan2 .. k_final took 130, 162 M
+// compacted values 0.22 ms instead of 0.38.
+//
 // A tensor that these means do not hold (a bin with more values than one wave should read, lists that
 // overflow) is marked (TState::fuse_bad); the host sends it through launch_resolve and launch_quantize.
 #include "inshr_quant.h"
@@ -344,7 +348,8 @@ __device__ __forceinline__ void add_value(FuseShared &fs, u32 sym, u32 key, floa
               (unsigned long long)(__float_as_uint(x) & 0x7fffffu) | (1ull << F_CNT));
 }
 
-template <bool FULL>
+// DRY: nothing is written but the lists (no output buffers).
+template <bool FULL, bool DRY>
 __device__ __forceinline__ void fuse_tile(FuseShared &fs, const float (&v)[16], u32 mask, u32 e0, u32 n_bp, u32 w,
                                           u32 zero_sym, u32 tau_o, unsigned long long *pk, FuseOut &o, u32 (&pc)[4])
 {
@@ -413,7 +418,7 @@ __device__ __forceinline__ void fuse_tile(FuseShared &fs, const float (&v)[16], 
                         if (aside) {
                             const u32 at = __builtin_amdgcn_mbcnt_hi((u32)(am >> 32), __builtin_amdgcn_mbcnt_lo((u32)am, o.n));
                             o.key[at] = k;
-                            o.idx[at] = e0 + 4u * (tid + 1024u * j) + c;
+                            if (!DRY) o.idx[at] = e0 + 4u * (tid + 1024u * j) + c;
                         }
                         o.n += m;
                     }
@@ -437,19 +442,21 @@ __device__ __forceinline__ void fuse_tile(FuseShared &fs, const float (&v)[16], 
         }
         const u32 bitoff = 4u * (tid + 1024u * j) * w;
         const u32 word = bitoff >> 6, shf = bitoff & 63u;
-        if (piece) {
+        if (!DRY && piece) {
             atomicOr(&pk[word], piece << shf);
             if (shf + 4u * w > 64u) atomicOr(&pk[word + 1u], piece >> (64u - shf));
         }
     }
 }
 
+template <bool DRY>
 __global__ __launch_bounds__(BLOCK) void k_fuse(const TDesc *__restrict__ td, const u32 *__restrict__ wg_gu0,
                                                 const GridDesc *__restrict__ gd, const QDesc *__restrict__ qd, Bufs B)
 {
     __shared__ FuseShared fs; // (one static object: it starts at LDS address 0, offsets fold into the instructions)
     const u32 tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    for (u32 k = tid; k < 2u * PKW; k += BLOCK) fs.pk[k] = 0ull;
+    if (!DRY)
+        for (u32 k = tid; k < 2u * PKW; k += BLOCK) fs.pk[k] = 0ull;
     for (u32 k = tid; k < F_CELLS * F_COPIES; k += BLOCK) fs.cell[k] = 0ull;
     u32 buf = 0u;
     for (u32 gu = wg_gu0[blockIdx.x]; gu < wg_gu0[blockIdx.x + 1]; gu++) {
@@ -538,29 +545,33 @@ __global__ __launch_bounds__(BLOCK) void k_fuse(const TDesc *__restrict__ td, co
 #pragma unroll
             for (int i = 0; i < 16; i++)
                 asm volatile("" : "+v"(v[i])); // the values are taken here, before any store below
-            if (have_prev) write_out(tile - 1, buf ^ 1u);
+            if (!DRY && have_prev) write_out(tile - 1, buf ^ 1u);
             ahead = tile + 1 < un.tile1 && tile_cnt(tile + 1) == (u32)TILE;
             if (ahead) load_tile_ahead(d, e0 + TILE, vn);
             u32 pc[4];
             // (whole tile or not is the same for every lane: the tile code uses ballots)
             if (cnt == (u32)TILE)
-                fuse_tile<true>(fs, v, mask, (u32)e0, n_bp, w, zero_sym, tau_o, fs.pk + buf * PKW, o, pc);
+                fuse_tile<true, DRY>(fs, v, mask, (u32)e0, n_bp, w, zero_sym, tau_o, fs.pk + buf * PKW, o, pc);
             else
-                fuse_tile<false>(fs, v, mask, (u32)e0, n_bp, w, zero_sym, tau_o, fs.pk + buf * PKW, o, pc);
+                fuse_tile<false, DRY>(fs, v, mask, (u32)e0, n_bp, w, zero_sym, tau_o, fs.pk + buf * PKW, o, pc);
             if (lane == 0u) {
                 typedef u32 u2 __attribute__((ext_vector_type(2)));
                 const u2 x = {pc[0] | (pc[1] << 16), pc[2] | (pc[3] << 16)};
                 *(GLOBAL_AS u2 *)(gptr(B.pool) + pl.counts + (tile - un.tile0) * F_TILEW + 2u * wave) = x;
             }
-            __syncthreads();
-            if ((tile + 1 - un.tile0) % F_FLUSH == 0 && tile + 1 < un.tile1) {
+            const bool full = (tile + 1 - un.tile0) % F_FLUSH == 0 && tile + 1 < un.tile1;
+            if (!DRY || full) __syncthreads(); // (the bit buffers: without them the waves drift apart freely)
+            if (full) {
                 flush();
                 __syncthreads();
             }
             have_prev = true;
             buf ^= 1u;
         }
-        write_out(un.tile1 - 1, buf ^ 1u);
+        if (DRY)
+            __syncthreads();
+        else
+            write_out(un.tile1 - 1, buf ^ 1u);
         flush();
         if (tid < F_CELLS && sum_c) {
             unsigned long long *gm = (unsigned long long *)B.mom_sx + (size_t)t * MAX_SUB;
@@ -812,7 +823,7 @@ __global__ __launch_bounds__(BLOCK) void k_fpatch(const GridDesc *__restrict__ g
         for (u32 j = 0; j < 4u; j++) {
             const u32 i = b + lane + j * 64u;
             key[j] = i < c ? kp[i] : 0u;
-            idx[j] = i < c ? ip[i] : 0u;
+            idx[j] = q.packed && i < c ? ip[i] : 0u;
         }
 #pragma unroll
         for (u32 j = 0; j < 4u; j++) {
@@ -820,12 +831,14 @@ __global__ __launch_bounds__(BLOCK) void k_fpatch(const GridDesc *__restrict__ g
             const u32 old = listed_symbol(gsym[slot_of_key(gbp, n_bp, key[j])], key[j], tau_o);
             const u32 sym = qt.symtab[slot_of_key(qt.bp, n_bp, key[j])];
             if (old == sym) continue;
-            const u64 bit = (u64)idx[j] * w;
-            const u32 sh = (u32)(bit & 63u);
-            GLOBAL_AS unsigned long long *p = packed + (bit >> 6);
-            __hip_atomic_fetch_xor(p, (unsigned long long)(old ^ sym) << sh, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (sh + w > 64u)
-                __hip_atomic_fetch_xor(p + 1, (unsigned long long)(old ^ sym) >> (64u - sh), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (q.packed) {
+                const u64 bit = (u64)idx[j] * w;
+                const u32 sh = (u32)(bit & 63u);
+                GLOBAL_AS unsigned long long *p = packed + (bit >> 6);
+                __hip_atomic_fetch_xor(p, (unsigned long long)(old ^ sym) << sh, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (sh + w > 64u)
+                    __hip_atomic_fetch_xor(p + 1, (unsigned long long)(old ^ sym) >> (64u - sh), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
             const u32 x = key[j] >> 23, m = bits_of_key(key[j]) & 0x7fffffu;
             if (old >= 2u) { // (sums modulo 2^64 and 2^32: what leaves one cell enters another)
                 atomicAdd(&cc[old + x], 0xFFFFFFFFu);
@@ -850,7 +863,9 @@ __global__ __launch_bounds__(BLOCK) void k_fpatch(const GridDesc *__restrict__ g
 // ------------------------------------------------------------------------------------------
 // A unit's lists, one per wave, hold for every tile and quarter those of the wave's 256 consecutive values, in
 // index order.  The tensor's order is tile, quarter, wave.  The tiles' counts stay behind for k_quant, which takes a
-// further call for the same configuration (6.7 G values: 8.5 ms, this sweep again 12.4).
+// further call for the same configuration (6.7 G values: 8.5 ms, this sweep again 12.4).  Without output buffers the
+// unit's sum of their squares is all that is wanted, in a fixed order; it goes where the unit's numbers of listed values
+// were (unit_cand, read no more).
 __global__ __launch_bounds__(BLOCK) void k_fprot(const TDesc *__restrict__ td, const GridDesc *__restrict__ gd,
                                                  const u32 *__restrict__ t_gu_off,
                                                  const QDesc *__restrict__ qd, Bufs B)
@@ -858,6 +873,7 @@ __global__ __launch_bounds__(BLOCK) void k_fprot(const TDesc *__restrict__ td, c
     constexpr u32 NW = BLOCK / 64;
     __shared__ u32 seg[NW][16]; // entries per list in every wave's share of the tiles
     __shared__ u32 s_before[NW];
+    __shared__ double s_sq[NW];
     const u32 gu = blockIdx.x;
     const Unit un = B.gunits[gu];
     const int t = (int)un.tensor;
@@ -869,10 +885,13 @@ __global__ __launch_bounds__(BLOCK) void k_fprot(const TDesc *__restrict__ td, c
     const TDesc d = td[t];
     const u32 tiles = un.tile1 - un.tile0, per = (tiles + NW - 1u) / NW;
     GLOBAL_AS u32 *tile_out = gptr(B.tile_out) + (size_t)un.tile0 * MAX_FRAC + gd->pair_o[gd->cfg_pair[q.cfg]];
+    GLOBAL_AS double *squares = (GLOBAL_AS double *)gptr(B.unit_cand + (size_t)gu * 16);
     if (__ballot(own != 0u) == 0ull) {
         for (u32 k = tid; k < tiles; k += BLOCK) tile_out[(size_t)k * MAX_FRAC] = 0u;
+        if (!q.packed && tid == 0u) *squares = 0.0;
         return;
     }
+    double sq = 0.0;
     // protected values of the tensor's units before this one
     u32 before = 0u;
     for (u32 k = t_gu_off[t] * 16u + tid; k < gu * 16u; k += BLOCK) before += B.unit_prot[k];
@@ -907,19 +926,34 @@ __global__ __launch_bounds__(BLOCK) void k_fprot(const TDesc *__restrict__ td, c
         const GLOBAL_AS u32 *p = list + (u64)l * pl.cap + from;
         for (u32 i = 0; i < c; i++) { // (rarely more than one or two)
             const u32 x = p[i];
-            store_protected(q, dst + (inc - c) + i, x, gptr(d.data)[x]);
+            const float value = gptr(d.data)[x];
+            if (q.packed)
+                store_protected(q, dst + (inc - c) + i, x, value);
+            else
+                sq = fma((double)value, (double)value, sq);
         }
         src += c0 + c1 + c2 + c3;
         dst += (u32)__builtin_amdgcn_readlane((int)inc, 63);
+    }
+    if (q.packed) return;
+    sq = wave_sum_f64(sq);
+    if (lane == 0u) s_sq[wave] = sq;
+    __syncthreads();
+    if (tid == 0u) {
+        double all = 0.0;
+        for (u32 w = 0; w < NW; w++) all += s_sq[w];
+        *squares = all;
     }
 }
 
 // ------------------------------------------------------------------------------------------
 // centres
 // ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(BLOCK) void k_fhead(const GridDesc *__restrict__ gd, const u32 *__restrict__ t_gu_off,
+__global__ __launch_bounds__(BLOCK) void k_fhead(const TDesc *__restrict__ td, const GridDesc *__restrict__ gd,
+                                                 const u32 *__restrict__ t_fu_off, const u32 *__restrict__ t_gu_off,
                                                  const QDesc *__restrict__ qd, QInfo *__restrict__ qi, Bufs B)
 {
+    __shared__ double part[256], s_sq[2]; // of the bins: 2 c S - n c^2; sums of squares: all, protected
     __shared__ unsigned long long cm[F_CELLS], cc[F_CELLS];
     __shared__ float cb[256];
     __shared__ unsigned long long s_n;
@@ -977,25 +1011,64 @@ __global__ __launch_bounds__(BLOCK) void k_fhead(const GridDesc *__restrict__ gd
             s += __shfl_xor(s, (int)o);
             n += __shfl_xor(n, (int)o);
         }
-        if (tid % per == 0u)
-            codebook[k] = cb[k] = n ? (float)(s / (double)n) : __uint_as_float(bits_of_key(tk[bnd_index(K, k == 0u ? 1u : k)]));
+        if (tid % per == 0u) {
+            const float c = n ? (float)(s / (double)n) : __uint_as_float(bits_of_key(tk[bnd_index(K, k == 0u ? 1u : k)]));
+            codebook[k] = cb[k] = c;
+            part[k] = 2.0 * (double)c * s - (double)n * (double)c * (double)c;
+        }
     }
     if (tid == 0u && s_n != st->pair_M[pair]) atomicOr(&st->internal_err, 2048u); // every quantized value is in a cell
     __syncthreads();
-    store_head(q, st, gd, tk, cb, s_prot, qi + t);
-    if (tid == 0u) store_result(st, B.res + t);
+    if (q.packed) {
+        store_head(q, st, gd, tk, cb, s_prot, qi + t);
+        if (tid == 0u) store_result(st, B.res + t);
+        return;
+    }
+    // the configuration's score, as k_final works it out; sums of squares of the units in a fixed order
+    if (wave < 2u) {
+        const u32 *off = wave ? t_gu_off : t_fu_off;
+        double x = 0.0;
+        for (u32 u = off[t] + lane; u < off[t + 1]; u += 64u)
+            x += wave ? *(const double *)(B.unit_cand + (size_t)u * 16) : B.sq_part[(size_t)u * SQ_STRIDE];
+        x = wave_sum_f64(x);
+        if (lane == 0u) s_sq[wave] = x;
+    }
+    __syncthreads();
+    if (wave == 0u) {
+        double acc = 0.0;
+        for (u32 k = lane; k < K; k += 64u) acc += part[k];
+        acc = wave_sum_f64(acc);
+        if (lane == 0u) {
+            const double sse = s_sq[0] - s_sq[1] - acc;
+            Score r;
+            r.sse = sse < 0.0 ? 0.0 : sse;
+            r.sumsq = s_sq[0];
+            r.n_pruned = st->pair_Pn[pair] + st->pair_Pp[pair];
+            r.n_outlier = st->pair_An[pair] + st->pair_Ap[pair];
+            r.n_kept = st->pair_M[pair];
+            r.cost_bits = payload_bits(r.n_kept, r.n_outlier, K, gd->cfg_l16[q.cfg]);
+            B.scores[(size_t)t * gd->n_cfg + q.cfg] = r;
+            st->sumsq = r.sumsq;
+            if (r.n_pruned + r.n_outlier + r.n_kept != td[t].n || (u64)s_prot != r.n_outlier) atomicOr(&st->internal_err, 256u);
+            settle_choice(st, q.cfg, r.sse, r.sumsq, gd->eps);
+            store_result(st, B.res + t);
+        }
+    }
 }
 
 hipError_t launch_fused(const Batch &bt, const QDesc *qd, QInfo *qi, hipStream_t s)
 {
     const Bufs &B = bt.bufs;
     PROF("k_fplan", s, k_fplan<<<bt.nB, BLOCK, 0, s>>>(bt.td, bt.gd, qd, B));
-    PROF("k_fuse", s, k_fuse<<<bt.n_gwg, BLOCK, 0, s>>>(bt.td, bt.wg_gu0, bt.gd, qd, B));
+    if (qi)
+        PROF("k_fuse", s, k_fuse<false><<<bt.n_gwg, BLOCK, 0, s>>>(bt.td, bt.wg_gu0, bt.gd, qd, B));
+    else
+        PROF("k_fuse_dry", s, k_fuse<true><<<bt.n_gwg, BLOCK, 0, s>>>(bt.td, bt.wg_gu0, bt.gd, qd, B));
     PROF("k_fsplit", s, k_fsplit<<<dim3(bt.n_gunits, FS_PARTS), BLOCK, 0, s>>>(qd, B));
     PROF("k_fsel", s, k_fsel<<<dim3(bt.nB, 256 / SEL_WAVES), 64 * SEL_WAVES, 0, s>>>(bt.gd, qd, B));
     PROF("k_fpatch", s, k_fpatch<<<dim3(bt.n_gunits, FP_PARTS), BLOCK, 0, s>>>(bt.gd, qd, B));
     PROF("k_fprot", s, k_fprot<<<bt.n_gunits, BLOCK, 0, s>>>(bt.td, bt.gd, bt.t_gu_off, qd, B));
-    PROF("k_fhead", s, k_fhead<<<bt.nB, BLOCK, 0, s>>>(bt.gd, bt.t_gu_off, qd, qi, B));
+    PROF("k_fhead", s, k_fhead<<<bt.nB, BLOCK, 0, s>>>(bt.td, bt.gd, bt.t_fu_off, bt.t_gu_off, qd, qi, B));
     return hipGetLastError();
 }
 

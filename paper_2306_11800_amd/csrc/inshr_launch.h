@@ -109,7 +109,7 @@ struct Batch {
 };
 
 struct QDesc { // one tensor of a quantize call (indexed like the batch)
-    unsigned long long *packed; // NULL: tensor not part of the call
+    unsigned long long *packed; // NULL: tensor not part of the call (or, where fused is set, no outputs)
     float *codebook;
     float *boundaries;
     u32 *out_idx;
@@ -273,7 +273,9 @@ hipError_t launch_small_many(const Batch &bt, hipStream_t s); // of those of up 
 // the tensors of the units (and the small ones), whose boundaries and centres the state holds
 hipError_t launch_quantize(const Batch &bt, const QDesc *qd, const Unit *units, const u32 *wg_u0, int n_wg, QInfo *qi,
                            hipStream_t s);
-// the tensors marked in their descriptors, which the batch's gather units cover
+// The tensors marked in their descriptors, which the batch's gather units cover.  Without qi no descriptor has output
+// buffers: boundaries, centres and the error of the configuration stay in the state, and a choice that hangs on it is
+// settled.
 hipError_t launch_fused(const Batch &bt, const QDesc *qd, QInfo *qi, hipStream_t s);
 struct DeltaCall { // what the kernels of a delta or reconstruct call share
     const DDesc *dd;           // device
@@ -332,6 +334,15 @@ __device__ __forceinline__ View view_of(const GridDesc *gd, u32 view)
 __device__ __forceinline__ u32 view_bnd(const GridDesc *gd, const View &v, u32 i)
 {
     return v.K ? bnd_index(v.K, i + 1u) : (u32)gd->bnd[i];
+}
+
+// A choice that hangs on configuration g (CHOICE_IF), whose error is known now; compared as choose_config does.
+__device__ __forceinline__ void settle_choice(TState *st, u32 g, double sse, double sumsq, double eps)
+{
+    if (st->best != (CHOICE_IF | g)) return;
+    const bool in = (sumsq > 0.0 ? sse / sumsq : 0.0) <= eps;
+    st->best = in ? g : st->best_else;
+    st->feasible = in ? 1u : st->feasible_else;
 }
 
 // Class counts of every (prune, protect) pair from the exact thresholds, by the first n_pairs threads.

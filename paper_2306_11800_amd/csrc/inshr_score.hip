@@ -568,11 +568,7 @@ __global__ __launch_bounds__(BLOCK) void k_final(const TDesc *__restrict__ td,
     __syncthreads();
     if (wave == 0u) {
         if (vw.K) {
-            if (lane == 0u && st->best == (CHOICE_IF | vw.cfg)) { // (as choose_config compares)
-                const bool in = (s_sumsq > 0.0 ? s_sse[vw.cfg] / s_sumsq : 0.0) <= gd->eps;
-                st->best = in ? vw.cfg : st->best_else;
-                st->feasible = in ? 1u : st->feasible_else;
-            }
+            if (lane == 0u) settle_choice(st, vw.cfg, s_sse[vw.cfg], s_sumsq, gd->eps);
         } else {
             const Choice c = choose_config(s_sse, s_cost, n_cfg, gd->eps, s_sumsq);
             if (lane == 0u) {
