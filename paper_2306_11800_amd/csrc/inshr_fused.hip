@@ -323,7 +323,7 @@ __global__ __launch_bounds__(BLOCK) void k_fplan(const TDesc *__restrict__ td, c
 struct FuseShared {
     u32 T[COARSE];                   // key prefix -> bins
     u16 symt[L2_BINS];               // table of the bins
-    unsigned long long pk[2 * PKW];  // two bit buffers of packed symbols
+    unsigned long long piece[BLOCK]; // four symbols of every lane: a wave's 64 are 4 w words of the stream
     unsigned long long cell[F_CELLS * F_COPIES];
     u32 bp[QBP + 8];
     u16 symtab[QBP + 8];
@@ -351,9 +351,12 @@ __device__ __forceinline__ void add_value(FuseShared &fs, u32 sym, u32 key, floa
 // DRY: nothing is written but the lists (no output buffers).
 template <bool FULL, bool DRY>
 __device__ __forceinline__ void fuse_tile(FuseShared &fs, const float (&v)[16], u32 mask, u32 e0, u32 n_bp, u32 w,
-                                          u32 zero_sym, u32 tau_o, unsigned long long *pk, FuseOut &o, u32 (&pc)[4])
+                                          u32 zero_sym, u32 tau_o, GLOBAL_AS unsigned long long *dst, u32 n_words, FuseOut &o,
+                                          u32 (&pc)[4])
 {
-    const u32 tid = threadIdx.x, copy = tid & (F_COPIES - 1u);
+    const u32 tid = threadIdx.x, copy = tid & (F_COPIES - 1u), lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // word `lane` of the wave's 4 w begins in piece p0, `skip` bits from its start
+    const u32 p0 = (16u * lane) / w, skip = 64u * lane - 4u * w * p0;
 #pragma unroll
     for (int j = 0; j < 4; j++) {
         u32 e[4], key[4];
@@ -440,11 +443,17 @@ __device__ __forceinline__ void fuse_tile(FuseShared &fs, const float (&v)[16], 
                 pc[j] = k;
             }
         }
-        const u32 bitoff = 4u * (tid + 1024u * j) * w;
-        const u32 word = bitoff >> 6, shf = bitoff & 63u;
-        if (!DRY && piece) {
-            atomicOr(&pk[word], piece << shf);
-            if (shf + 4u * w > 64u) atomicOr(&pk[word + 1u], piece >> (64u - shf));
+        if (!DRY) { // (a wave's LDS operations complete in order: no other wave is asked)
+            unsigned long long *mine = fs.piece + wave * 64u;
+            asm volatile("" ::: "memory");
+            mine[lane] = piece;
+            asm volatile("" ::: "memory");
+            if (lane < 4u * w) {
+                unsigned long long x = mine[p0] >> skip;
+                for (u32 i = 1u; 4u * w * i < 64u + skip; i++) x |= mine[p0 + i] << (4u * w * i - skip);
+                const u32 at = ((u32)j * (BLOCK / 64) + wave) * 4u * w + lane;
+                if (FULL || at < n_words) dst[at] = x;
+            }
         }
     }
 }
@@ -455,10 +464,7 @@ __global__ __launch_bounds__(BLOCK) void k_fuse(const TDesc *__restrict__ td, co
 {
     __shared__ FuseShared fs; // (one static object: it starts at LDS address 0, offsets fold into the instructions)
     const u32 tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if (!DRY)
-        for (u32 k = tid; k < 2u * PKW; k += BLOCK) fs.pk[k] = 0ull;
     for (u32 k = tid; k < F_CELLS * F_COPIES; k += BLOCK) fs.cell[k] = 0ull;
-    u32 buf = 0u;
     for (u32 gu = wg_gu0[blockIdx.x]; gu < wg_gu0[blockIdx.x + 1]; gu++) {
         const Unit un = B.gunits[gu];
         const int t = (int)un.tensor;
@@ -498,23 +504,6 @@ __global__ __launch_bounds__(BLOCK) void k_fuse(const TDesc *__restrict__ td, co
             const u64 rem = d.n - (tl - d.tile0) * (u64)TILE;
             return tile_len(rem, (u32)TILE);
         };
-        auto write_out = [&](u64 tl, u32 bf) { // the words of tile tl leave buffer bf, which is clean afterwards
-            unsigned long long *pk = fs.pk + bf * PKW;
-            const u32 n_words = (tile_cnt(tl) * w + 63u) >> 6;
-            GLOBAL_AS unsigned long long *dst = packed + (tl - d.tile0) * (u64)(256u * w);
-            unsigned long long xw[3];
-#pragma unroll
-            for (u32 j = 0; j < 3u; j++) {
-                const u32 k = tid + j * BLOCK;
-                xw[j] = k < 256u * w ? pk[k] : 0ull;
-            }
-#pragma unroll
-            for (u32 j = 0; j < 3u; j++) {
-                const u32 k = tid + j * BLOCK;
-                if (k < n_words) dst[k] = xw[j];
-                if (k < 256u * w) pk[k] = 0ull;
-            }
-        };
         auto flush = [&] { // the cells are emptied, by all threads together
             if (tid < F_CELLS) {
 #pragma unroll
@@ -526,11 +515,10 @@ __global__ __launch_bounds__(BLOCK) void k_fuse(const TDesc *__restrict__ td, co
                 }
             }
         };
-        // Software pipeline of one tile, as in k_quant: the tile's values, asked for during the tile before,
-        // arrive; the words of the tile before leave; the next tile is asked for; this tile is classified
-        // into the other buffer; barrier.
+        // The waves drift apart freely: a wave's symbols are whole words of their own, which it packs and stores.  A tile's
+        // values are asked for during the tile before.
         float vn[16];
-        bool ahead = false, have_prev = false;
+        bool ahead = false;
         for (u64 tile = un.tile0; tile < un.tile1; tile++) {
             const u64 e0 = (tile - d.tile0) * (u64)TILE;
             const u32 cnt = tile_cnt(tile);
@@ -545,33 +533,28 @@ __global__ __launch_bounds__(BLOCK) void k_fuse(const TDesc *__restrict__ td, co
 #pragma unroll
             for (int i = 0; i < 16; i++)
                 asm volatile("" : "+v"(v[i])); // the values are taken here, before any store below
-            if (!DRY && have_prev) write_out(tile - 1, buf ^ 1u);
             ahead = tile + 1 < un.tile1 && tile_cnt(tile + 1) == (u32)TILE;
             if (ahead) load_tile_ahead(d, e0 + TILE, vn);
             u32 pc[4];
+            GLOBAL_AS unsigned long long *dst = packed + (tile - d.tile0) * (u64)(256u * w);
+            const u32 n_words = (cnt * w + 63u) >> 6;
             // (whole tile or not is the same for every lane: the tile code uses ballots)
             if (cnt == (u32)TILE)
-                fuse_tile<true, DRY>(fs, v, mask, (u32)e0, n_bp, w, zero_sym, tau_o, fs.pk + buf * PKW, o, pc);
+                fuse_tile<true, DRY>(fs, v, mask, (u32)e0, n_bp, w, zero_sym, tau_o, dst, n_words, o, pc);
             else
-                fuse_tile<false, DRY>(fs, v, mask, (u32)e0, n_bp, w, zero_sym, tau_o, fs.pk + buf * PKW, o, pc);
+                fuse_tile<false, DRY>(fs, v, mask, (u32)e0, n_bp, w, zero_sym, tau_o, dst, n_words, o, pc);
             if (lane == 0u) {
                 typedef u32 u2 __attribute__((ext_vector_type(2)));
                 const u2 x = {pc[0] | (pc[1] << 16), pc[2] | (pc[3] << 16)};
                 *(GLOBAL_AS u2 *)(gptr(B.pool) + pl.counts + (tile - un.tile0) * F_TILEW + 2u * wave) = x;
             }
-            const bool full = (tile + 1 - un.tile0) % F_FLUSH == 0 && tile + 1 < un.tile1;
-            if (!DRY || full) __syncthreads(); // (the bit buffers: without them the waves drift apart freely)
-            if (full) {
+            if ((tile + 1 - un.tile0) % F_FLUSH == 0 && tile + 1 < un.tile1) {
+                __syncthreads();
                 flush();
                 __syncthreads();
             }
-            have_prev = true;
-            buf ^= 1u;
         }
-        if (DRY)
-            __syncthreads();
-        else
-            write_out(un.tile1 - 1, buf ^ 1u);
+        __syncthreads();
         flush();
         if (tid < F_CELLS && sum_c) {
             unsigned long long *gm = (unsigned long long *)B.mom_sx + (size_t)t * MAX_SUB;
@@ -583,7 +566,7 @@ __global__ __launch_bounds__(BLOCK) void k_fuse(const TDesc *__restrict__ td, co
             B.unit_prot[(size_t)gu * 16 + wave] = o.np;
             if (o.overflow) atomicOr(&st->fuse_bad, 2u);
         }
-        // (a unit's cells and buffers are clean before the next one's first barrier)
+        // (a unit's cells are clean before the next one's first barrier)
     }
 }
 
