@@ -645,7 +645,6 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         const size_t o_tb = cv.take(full((size_t)nB * TGT_STRIDE * 4));
         const size_t o_tr = cv.take(full((size_t)nB * TGT_STRIDE * 4));
         const size_t o_tk = cv.take(full((size_t)nT * TGT_STRIDE * 4));
-        const size_t o_tf = cv.take((size_t)total_tiles * 4);
         const size_t o_sq = cv.take((size_t)units * SQ_STRIDE * 8);
         const size_t o_ed = cv.take(full((size_t)nB * MAX_EDGES * 4));
         const size_t o_sl = cv.take(full((size_t)nB * (L2_BINS + 64) * 2));
@@ -749,7 +748,6 @@ int run_search(inshr_ctx *c, const inshr_tensor *tensors, uint32_t nT, const ins
         B.tgt_klo = (u32 *)(db + o_tkl);
         B.tgt_khi = (u32 *)(db + o_tkh);
         B.tile_out = (u32 *)(db + o_to);
-        B.tile_off = (u32 *)(db + o_tf);
         B.sq_part = (double *)(db + o_sq);
         B.sq_prot = (double *)(db + o_h1);
         static_assert(MAX_FRAC * sizeof(double) == 16 * sizeof(u32), "sq_prot and unit_prot take the same room");

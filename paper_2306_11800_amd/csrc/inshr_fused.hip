@@ -17,9 +17,9 @@
 //   k_fprot    protected values: the sweep's lists, one per wave -> the tensor's list in index order
 //   k_fhead    per tensor: centres, boundaries, class counts
 //
-// 6.7 G values, symbols of 9 bits: k_fuse 11.0 ms (27.0 GB read, 8.7 GB written: 3.2 TB/s; vector issue takes 0.71 of
-// the CU-cycles, the LDS pipe 0.46, half of it bank conflicts of the table reads; one workgroup of 16 waves fits a CU, and
-// its waves wait half of the time), k_fsplit 0.34, k_fsel 0.22, k_fpatch 0.41, k_fprot 0.37; boundaries, centres and
+// 6.7 G values, symbols of 9 bits: k_fuse 10.3 ms (27.0 GB read, 8.7 GB written: 3.5 TB/s; bound by vector issue and the
+// LDS pipe, half of whose time are bank conflicts of the table reads; one workgroup of 16 waves fits a CU.  11.0 when
+// a tile's words were OR-ed together in LDS behind a barrier), k_fsplit 0.34, k_fsel 0.22, k_fpatch 0.41, k_fprot 0.37; boundaries, centres and
 // k_quant for one configuration took 8.7 (k_gather) + 0.6 + 8.9 (k_quant).  100 M values in 48 tensors: 0.25 ms where
 // k_plan2 .. k_quant took 0.70.
 //
@@ -355,8 +355,7 @@ __device__ __forceinline__ void fuse_tile(FuseShared &fs, const float (&v)[16], 
                                           u32 (&pc)[4])
 {
     const u32 tid = threadIdx.x, copy = tid & (F_COPIES - 1u), lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // word `lane` of the wave's 4 w begins in piece p0, `skip` bits from its start
-    const u32 p0 = (16u * lane) / w, skip = 64u * lane - 4u * w * p0;
+    const WavePack wp(w, lane);
 #pragma unroll
     for (int j = 0; j < 4; j++) {
         u32 e[4], key[4];
@@ -443,17 +442,10 @@ __device__ __forceinline__ void fuse_tile(FuseShared &fs, const float (&v)[16], 
                 pc[j] = k;
             }
         }
-        if (!DRY) { // (a wave's LDS operations complete in order: no other wave is asked)
-            unsigned long long *mine = fs.piece + wave * 64u;
-            asm volatile("" ::: "memory");
-            mine[lane] = piece;
-            asm volatile("" ::: "memory");
-            if (lane < 4u * w) {
-                unsigned long long x = mine[p0] >> skip;
-                for (u32 i = 1u; 4u * w * i < 64u + skip; i++) x |= mine[p0 + i] << (4u * w * i - skip);
-                const u32 at = ((u32)j * (BLOCK / 64) + wave) * 4u * w + lane;
-                if (FULL || at < n_words) dst[at] = x;
-            }
+        if (!DRY) {
+            const unsigned long long x = wp.word(piece, fs.piece + wave * 64u, lane);
+            const u32 at = ((u32)j * (BLOCK / 64) + wave) * 4u * w + lane;
+            if (lane < 4u * w && (FULL || at < n_words)) dst[at] = x;
         }
     }
 }

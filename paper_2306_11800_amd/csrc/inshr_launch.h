@@ -74,7 +74,6 @@ struct Bufs { // device pointers, indexed by the tensor's position on the device
                     // without an edge
     float *codebook; // [nT][n_cfg][CB_STRIDE]
     Score *scores;  // [nT][n_cfg]
-    u32 *tile_off;  // [tiles of the nB] exclusive prefix of protected values per tensor (quantize)
 };
 
 struct Batch {

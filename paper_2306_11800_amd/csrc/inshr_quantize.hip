@@ -12,30 +12,37 @@
 
 namespace inshr {
 
-struct QuantShared {
-    u32 T[COARSE];                     // key prefix -> bins
-    u16 symt[L2_BINS];                 // symbol, or 0x8000 | first breakpoint of the bin
-    unsigned long long pk[2 * PKW];    // two bit buffers of packed symbols
-    QuantTables qt;
-};
-
 // How the symbol of a key is found.  BINS: the search's equal-population bins; building the table
 // of 32768 bins takes a walk over 32 bins per thread (with a search per bin a workgroup needed about 40 us; 355 M values in
 // 292 tensors 0.73 -> 0.65 ms), so it is for long runs of tiles.  CELLS: cells of the
 // key's upper 14 bits, each with its first breakpoint and their number (a dozen of them in the
-// densest cells: a few bisection steps); the table takes 4 us.
+// densest cells: a few bisection steps); a thread per breakpoint finds the cells that hold some.
 constexpr int Q_BINS = 0, Q_CELLS = 1;
+template <int M> struct Mode {
+    static constexpr int value = M;
+};
 constexpr int QUANT_CELL_TILES = 16; // most tiles of a run classified by cells (4 .. 40 are alike; 100 costs 20 %)
 constexpr int CELL_SHIFT = 18, CELLS = 1 << (32 - CELL_SHIFT);
 constexpr u32 CELL_MANY = 63u; // number field of a cell: this many or more
 
+struct QuantShared {
+    u32 T[COARSE];                   // key prefix -> bins
+    u16 symt[L2_BINS];               // symbol, or 0x8000 | first breakpoint of the bin
+    unsigned long long piece[BLOCK]; // four symbols of every lane: a wave's 64 are 4 w words of the stream
+    u32 held[CELLS / 32];            // cells that hold breakpoints
+    u32 sum[BLOCK / 64];
+    QuantTables qt;
+};
+
 template <bool FULL, int MODE>
-__device__ __forceinline__ void classify_tile(const float (&v)[16], u32 mask, const u32 *T,
-                                              const u16 *symt, const QuantTables &qt, u32 n_bp, u32 zero_slot, u32 w,
-                                              unsigned long long *pk, u32 *wcnt, u32 &omask,
-                                              u32 (&pre)[4])
+__device__ __forceinline__ void classify_tile(QuantShared &qs, u32 tid, const float (&v)[16], u32 mask, u32 n_bp, u32 zero_slot, u32 w,
+                                              GLOBAL_AS unsigned long long *dst, u32 n_words, bool any_prot, u32 *wcnt,
+                                              u32 &omask, u32 (&pre)[4])
 {
-    const u32 tid = threadIdx.x, lane = tid & 63u;
+    const u32 lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const WavePack wp(w, lane);
+    const u16 *symt = qs.symt;
+    const QuantTables &qt = qs.qt;
     omask = 0u;
 #pragma unroll
     for (int j = 0; j < 4; j++) {
@@ -43,7 +50,7 @@ __device__ __forceinline__ void classify_tile(const float (&v)[16], u32 mask, co
 #pragma unroll
         for (int c = 0; c < 4; c++) {
             key[c] = key_of_float(v[4 * j + c]);
-            e[c] = MODE == Q_BINS ? T[key[c] >> COARSE_SHIFT] : (u32)symt[key[c] >> CELL_SHIFT];
+            e[c] = MODE == Q_BINS ? qs.T[key[c] >> COARSE_SHIFT] : (u32)symt[key[c] >> CELL_SHIFT];
         }
         if (MODE == Q_BINS) {
 #pragma unroll
@@ -83,54 +90,17 @@ __device__ __forceinline__ void classify_tile(const float (&v)[16], u32 mask, co
                 s3 = sym;
             omask |= (sym == 1u ? 1u : 0u) << (4 * j + c);
         }
-        const unsigned long long piece = (unsigned long long)lo32 | ((unsigned long long)s3 << (3u * w));
-        const u32 bitoff = 4u * (tid + 1024u * j) * w;
-        const u32 word = bitoff >> 6, shf = bitoff & 63u;
-        if (piece) {
-            atomicOr(&pk[word], piece << shf);
-            if (shf + 4u * w > 64u) atomicOr(&pk[word + 1u], piece >> (64u - shf));
+        const unsigned long long x = wp.word((unsigned long long)lo32 | ((unsigned long long)s3 << (3u * w)), qs.piece + wave * 64u, lane);
+        const u32 at = ((u32)j * (BLOCK / 64) + wave) * 4u * w + lane;
+        if (lane < 4u * w && (FULL || at < n_words)) dst[at] = x;
+        if (any_prot) { // protected values of this wave's 256 elements: total, and those of lower lanes
+            const u32 cj = __popc((omask >> (4 * j)) & 0xFu);
+            u32 tot = 0u;
+            pre[j] = 0u;
+            if (__ballot(cj != 0u)) tot = rank_counts(cj, pre[j]);
+            if (lane == 0u) wcnt[j * 16 + wave] = tot;
         }
-        // protected values of this wave's 256 elements: total, and those of lower lanes
-        const u32 cj = __popc((omask >> (4 * j)) & 0xFu);
-        u32 tot = 0u;
-        pre[j] = 0u;
-        if (__ballot(cj != 0u)) tot = rank_counts(cj, pre[j]);
-        if (lane == 0u) wcnt[j * 16 + (tid >> 6)] = tot;
     }
-}
-
-// per tensor: prefix of protected counts over its tiles, meta data, codebook / boundary copy
-__global__ __launch_bounds__(BLOCK) void k_qprep(const TDesc *__restrict__ td,
-                                                 const GridDesc *__restrict__ gd,
-                                                 const QDesc *__restrict__ qd,
-                                                 QInfo *__restrict__ qi, Bufs B)
-{
-    extern __shared__ u32 smem[]; // [32768 + 4]
-    __shared__ u32 tmp[BLOCK / 64 + 1];
-    const int i = blockIdx.x;
-    const QDesc q = qd[i];
-    if (q.packed == nullptr || q.fused) return;
-    const int t = i;
-    const u32 tid = threadIdx.x;
-    const TDesc d = td[t];
-    const TState *st = B.ts + t;
-    const u32 g = q.cfg, pair = gd->cfg_pair[g], o = gd->pair_o[pair];
-    const u64 n_tiles = (d.n + TILE - 1) / TILE;
-    u32 carry = 0;
-    for (u64 base = 0; base < n_tiles; base += L2_BINS) {
-        const u64 left = n_tiles - base;
-        const int m = left < (u64)L2_BINS ? (int)left : L2_BINS;
-        for (int k = tid; k < m; k += BLOCK) smem[k] = B.tile_out[(d.tile0 + base + k) * MAX_FRAC + o];
-        __syncthreads();
-        u32 tot = block_excl_scan(smem, smem, m, tmp);
-        for (int k = tid; k < m; k += BLOCK) B.tile_off[d.tile0 + base + k] = carry + smem[k];
-        carry += tot;
-        __syncthreads();
-    }
-    // (boundary keys given from outside come as 256 entries, boundary j of K = 2^b at j * 256 / K - 1)
-    const u32 *tk = q.alt_key ? q.alt_key : B.tgt_key + (size_t)t * TGT_STRIDE + pair * NBT;
-    const float *cb = q.alt_cb ? q.alt_cb : B.codebook + ((size_t)t * gd->n_cfg + g) * CB_STRIDE;
-    store_head(q, st, gd, tk, cb, carry, qi + i);
 }
 
 // Small tensors (one tile at most): a workgroup each, no table, every symbol by bisection.
@@ -218,23 +188,30 @@ __global__ __launch_bounds__(QS_NT) void k_qsmall(const TDesc *__restrict__ td, 
     store_head(q, st, gd, tk, cb, found, qi + t);
 }
 
+// Long runs: bound by vector issue and the table's dependent LDS reads (355 M values in 292 tensors 0.55 ms, 2.6 TB/s of
+// values; 1.6 G of 3 to 9 bits 2.2).  Runs of one tile: by the latency of what comes before the tile (64 of them 21 us).
+// A wave packs its own words without waiting for the others (0.60 ms, 64 runs 30 us with lane pieces OR-ed into a
+// buffer of the tile behind a barrier, every held cell of the table bisected and the tile read after it; that needed a
+// kernel before, of 8 us, for the places of the protected values, which a unit now adds up itself: at most a few loads per thread).
 __global__ __launch_bounds__(BLOCK) void k_quant(const TDesc *__restrict__ td, const Unit *__restrict__ units,
                                                  const u32 *__restrict__ wg_u0,
                                                  const GridDesc *__restrict__ gd,
-                                                 const QDesc *__restrict__ qd_by_tensor, Bufs B)
+                                                 const QDesc *__restrict__ qd_by_tensor, QInfo *__restrict__ qi,
+                                                 Bufs B)
 {
     // one static LDS object (it starts at LDS address 0): table offsets then fold into the LDS
     // instructions, which the base of a dynamic array does not allow
     __shared__ QuantShared qs;
     u32 *T = qs.T;
     u16 *symt = qs.symt;
-    unsigned long long *pk0 = qs.pk;
     QuantTables &qt = qs.qt;
 
-    const u32 tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    for (u32 k = tid; k < 2u * PKW; k += BLOCK) pk0[k] = 0ull;
+    const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     u32 buf = 0u;
     for (u32 u = wg_u0[blockIdx.x]; u < wg_u0[blockIdx.x + 1]; u++) {
+        u32 tid = threadIdx.x;
+        asm volatile("" : "+v"(tid)); // (what is derived from it is cheap: worked out per unit it is not kept in scratch)
+        const u32 lane = tid & 63u;
         const Unit un = units[u];
         const int t = (int)un.tensor;
         u64 tile = un.tile0;
@@ -249,21 +226,50 @@ __global__ __launch_bounds__(BLOCK) void k_quant(const TDesc *__restrict__ td, c
         const u32 nb2 = st->nb2;
         const u32 *tk = q.alt_key ? q.alt_key : B.tgt_key + (size_t)t * TGT_STRIDE + pair * NBT;
         const u32 n_bp = K + 3u;
-        __syncthreads();
+        auto tile_cnt = [&](u64 tl) -> u32 {
+            const u64 rem = d.n - (tl - d.tile0) * (u64)TILE;
+            return tile_len(rem, (u32)TILE);
+        };
+        // the first tile is asked for, and the protected values of the tiles before are added up, beside the tables
+        float vn[16];
+        bool ahead = tile_cnt(tile) == (u32)TILE; // vn holds the tile about to be worked on (uniform)
+        if (ahead) load_tile_ahead(d, (tile - d.tile0) * (u64)TILE, vn);
+        const GLOBAL_AS u32 *n_prot = gptr(B.tile_out) + o; // (u64 index below: tiles of a call x MAX_FRAC)
+        u32 obase = 0u;
+        for (u64 k = d.tile0 + tid; k < tile; k += BLOCK) obase += n_prot[k * MAX_FRAC];
+        obase = wave_sum(obase);
+        __syncthreads(); // (nothing of the unit before is read any more)
+        if (lane == 0u) qs.sum[wave] = obase;
+        if (tid < (u32)(CELLS / 32)) qs.held[tid] = 0u;
         const bool cells = stop - tile <= (u64)QUANT_CELL_TILES; // (the same for the whole workgroup)
         if (!cells)
             for (u32 i = tid; i < (u32)COARSE; i += BLOCK) T[i] = entry_for_u16(B.table2[(size_t)t * COARSE + i]);
         make_breakpoints(qt, tk, K, tau_p, tau_o);
-        if (cells) { // first breakpoint of every cell and how many it holds, or its symbol
+        if (cells) {
+            // The cells that hold breakpoints, by the first one of each; then sixteen cells a thread: the breakpoints
+            // below them by one bisection, and from there on what the held ones say.  (Held cells lie side by side, up to
+            // sixteen for one thread, which took a bisection for each.)
+            if (tid < n_bp) {
+                const u32 c = qt.bp[tid] >> CELL_SHIFT;
+                if (tid == 0u || qt.bp[tid - 1u] >> CELL_SHIFT != c) {
+                    const u32 m = slot_of_key(qt.bp, n_bp, (c << CELL_SHIFT) | ((1u << CELL_SHIFT) - 1u)) - tid;
+                    symt[c] = (u16)(0x8000u | ((m < CELL_MANY ? m : CELL_MANY) << 9) | tid);
+                    atomicOr(&qs.held[c >> 5], 1u << (c & 31u));
+                }
+            }
+            __syncthreads();
             constexpr u32 PER = CELLS / BLOCK;
+            static_assert(PER == 16, "half a word of held cells per thread");
+            const u32 held = qs.held[tid >> 1] >> ((tid & 1u) * PER);
             u32 s = slot_of_key(qt.bp, n_bp, tid * PER ? (tid * PER << CELL_SHIFT) - 1u : 0u); // (no breakpoint is key 0)
             for (u32 i = 0; i < PER; i++) {
-                const u32 c = tid * PER + i, last = (c << CELL_SHIFT) | ((1u << CELL_SHIFT) - 1u);
-                u32 e = s;
-                if (s < n_bp && qt.bp[s] <= last) e = slot_of_key(qt.bp, n_bp, last);
-                const u32 m = e - s < CELL_MANY ? e - s : CELL_MANY;
-                symt[c] = m ? (u16)(0x8000u | (m << 9) | s) : qt.symtab[s];
-                s = e;
+                const u32 c = tid * PER + i;
+                if ((held >> i) & 1u) {
+                    const u32 m = (symt[c] >> 9) & CELL_MANY;
+                    s = m == CELL_MANY ? slot_of_key(qt.bp, n_bp, (c << CELL_SHIFT) | ((1u << CELL_SHIFT) - 1u)) : s + m;
+                } else {
+                    symt[c] = qt.symtab[s];
+                }
             }
         }
         constexpr u32 PER_BINS = L2_BINS / BLOCK;
@@ -305,128 +311,78 @@ __global__ __launch_bounds__(BLOCK) void k_quant(const TDesc *__restrict__ td, c
         const u32 zero_slot = __builtin_amdgcn_readfirstlane(slot_of_key(qt.bp, n_bp, ZERO_KEY));
         __syncthreads();
         GLOBAL_AS unsigned long long *packed = gptr(q.packed);
-        auto tile_cnt = [&](u64 tl) -> u32 {
-            const u64 rem = d.n - (tl - d.tile0) * (u64)TILE;
-            return tile_len(rem, (u32)TILE);
-        };
-        // Software pipeline of one tile: (1) the tile's values, asked for during the tile before,
-        // arrive; (2) the words and protected values of the tile before leave (their stores drain
-        // while this tile is classified, and no load ever waits behind a store); (3) the next tile
-        // is asked for; (4) this tile is classified into the other LDS buffer; barrier.
-        float vn[16];
-        bool ahead = false; // vn holds the tile about to be worked on (uniform)
-        float vp[16];           // values of the tile before (its protected ones are still to be written)
-        u32 omask_p = 0u, pre_p[4] = {0u, 0u, 0u, 0u}, obase_p = 0u;
-        bool have_prev = false; // uniform
-        auto write_out = [&](u64 tl, u32 bf) { // phase 2 of tile tl, classified into buffer bf
-            const u64 e0 = (tl - d.tile0) * (u64)TILE;
-            const u32 cnt = tile_cnt(tl);
-            const u32 w_ = w;
-            unsigned long long *pk = pk0 + bf * PKW;
-            const u32 *wcnt = qt.wcnt[bf];
-            // the tile's words leave, and the buffer is clean for the tile after the next
-            const u32 n_words = (cnt * w_ + 63u) >> 6;
-            GLOBAL_AS unsigned long long *dst = packed + (tl - d.tile0) * (u64)(256u * w_);
-            // (at most 9 * 256 words: three per thread, read together, so the LDS latency is paid once)
-            unsigned long long xw[3];
+        obase = 0u;
 #pragma unroll
-            for (u32 j = 0; j < 3u; j++) {
-                const u32 k = tid + j * BLOCK;
-                xw[j] = k < 256u * w_ ? pk[k] : 0ull;
-            }
+        for (u32 i = 0; i < BLOCK / 64; i++) obase += qs.sum[i]; // (wave-uniform)
+        obase = __builtin_amdgcn_readfirstlane(obase);
+        // A wave's symbols are whole words of their own, which it packs and stores; the waves meet only where a tile has
+        // protected values, whose places depend on the other waves' counts.  The next tile is asked for before a tile is
+        // worked on.
+        auto walk = [&](auto mode) {
+            constexpr int MODE = decltype(mode)::value;
+            u32 next = n_prot[tile * MAX_FRAC]; // (asked for with the tile's values)
+            for (; tile < stop; tile++) {
+                const u64 e0 = (tile - d.tile0) * (u64)TILE;
+                const u32 cnt = tile_cnt(tile);
+                float v[16];
+                u32 mask = 0xFFFFu;
+                if (ahead) {
 #pragma unroll
-            for (u32 j = 0; j < 3u; j++) {
-                const u32 k = tid + j * BLOCK;
-                if (k < n_words) dst[k] = xw[j];
-                if (k < 256u * w_) pk[k] = 0ull;
-            }
-            // protected values in ascending index: quarter j, wave, lane, c
-            const u32 wc = wcnt[lane];
-            u32 inc = wc;
+                    for (int i = 0; i < 16; i++) v[i] = vn[i];
+                } else {
+                    mask = load_tile(d, e0, cnt, v);
+                }
+                const u32 found = __builtin_amdgcn_readfirstlane(next);
 #pragma unroll
-            for (int ofs = 1; ofs < 64; ofs <<= 1) {
-                const u32 y = __shfl_up(inc, ofs);
-                if ((int)lane >= ofs) inc += y;
-            }
-            if (__builtin_amdgcn_readlane(inc, 63) != 0u) {
-                const u32 excl = inc - wc;
-                const u64 obase = obase_p;
+                for (int i = 0; i < 16; i++)
+                    asm volatile("" : "+v"(v[i])); // the values are taken here, before any store below
+                ahead = tile + 1 < stop && tile_cnt(tile + 1) == (u32)TILE;
+                if (ahead) load_tile_ahead(d, e0 + TILE, vn);
+                next = tile + 1 < stop ? n_prot[(tile + 1) * MAX_FRAC] : 0u;
+                u32 omask, pre[4];
+                GLOBAL_AS unsigned long long *dst = packed + (tile - d.tile0) * (u64)(256u * w);
+                const u32 n_words = (cnt * w + 63u) >> 6;
+                u32 *wcnt = qt.wcnt[buf];
+                // (whole tile or not is the same for every lane: the tile code uses ballots)
+                if (cnt == (u32)TILE)
+                    classify_tile<true, MODE>(qs, tid, v, mask, n_bp, zero_slot, w, dst, n_words, found != 0u, wcnt, omask, pre);
+                else
+                    classify_tile<false, MODE>(qs, tid, v, mask, n_bp, zero_slot, w, dst, n_words, found != 0u, wcnt, omask, pre);
+                if (!found) continue;
+                __syncthreads();
+                buf ^= 1u; // (a wave that writes these counts again has passed the next such barrier)
+                // protected values in ascending index: quarter j, wave, lane, c
+                const u32 wc = wcnt[lane], excl = wave_incl_scan(wc) - wc;
 #pragma unroll
                 for (int j = 0; j < 4; j++) {
-                    u32 r = __builtin_amdgcn_readlane(excl, j * 16 + wave) + pre_p[j];
+                    u32 r = __builtin_amdgcn_readlane(excl, j * 16 + wave) + pre[j];
 #pragma unroll
                     for (int c = 0; c < 4; c++) {
                         const int i = 4 * j + c;
-                        if ((omask_p >> i) & 1u) {
-                            store_protected(q, obase + r, (u32)(e0 + 4u * (tid + 1024u * j) + c), vp[i]);
+                        if ((omask >> i) & 1u) {
+                            store_protected(q, (u64)obase + r, (u32)(e0 + 4u * (tid + 1024u * j) + c), v[i]);
                             r++;
                         }
                     }
                 }
+                obase += found;
             }
         };
-        for (; tile < stop; tile++) {
-            const u64 e0 = (tile - d.tile0) * (u64)TILE;
-            const u32 cnt = tile_cnt(tile);
-            float v[16];
-            u32 mask = 0xFFFFu;
-            if (ahead) {
-#pragma unroll
-                for (int i = 0; i < 16; i++) v[i] = vn[i];
-            } else {
-                mask = load_tile(d, e0, cnt, v);
-            }
-#pragma unroll
-            for (int i = 0; i < 16; i++)
-                asm volatile("" : "+v"(v[i])); // the values are taken here, before any store below
-            // offset of this tile's protected values in the list (needed one tile later)
-            const u32 obase = __builtin_amdgcn_readfirstlane(B.tile_off[tile]);
-            if (have_prev) write_out(tile - 1, buf ^ 1u);
-            // a whole next tile is asked for now and used one iteration later
-            ahead = tile + 1 < stop && tile_cnt(tile + 1) == (u32)TILE;
-            if (ahead) load_tile_ahead(d, e0 + TILE, vn);
-            u32 omask, pre[4];
-            unsigned long long *pkb = pk0 + buf * PKW;
-            // (whole tile or not is the same for every lane: the tile code uses ballots)
-            if (cells) {
-                if (cnt == (u32)TILE)
-                    classify_tile<true, Q_CELLS>(v, mask, T, symt, qt, n_bp, zero_slot, w, pkb, qt.wcnt[buf], omask, pre);
-                else
-                    classify_tile<false, Q_CELLS>(v, mask, T, symt, qt, n_bp, zero_slot, w, pkb, qt.wcnt[buf], omask, pre);
-            } else {
-                if (cnt == (u32)TILE)
-                    classify_tile<true, Q_BINS>(v, mask, T, symt, qt, n_bp, zero_slot, w, pkb, qt.wcnt[buf], omask, pre);
-                else
-                    classify_tile<false, Q_BINS>(v, mask, T, symt, qt, n_bp, zero_slot, w, pkb, qt.wcnt[buf], omask, pre);
-            }
-            __syncthreads();
-#pragma unroll
-            for (int i = 0; i < 16; i++) vp[i] = v[i];
-            omask_p = omask;
-            obase_p = obase;
-#pragma unroll
-            for (int j = 0; j < 4; j++) pre_p[j] = pre[j];
-            have_prev = true;
-            buf ^= 1u;
+        if (cells)
+            walk(Mode<Q_CELLS>());
+        else
+            walk(Mode<Q_BINS>());
+        if (stop == d.tile0 + (d.n + TILE - 1) / TILE) { // the tensor's last unit
+            const float *cb = q.alt_cb ? q.alt_cb : B.codebook + ((size_t)t * gd->n_cfg + g) * CB_STRIDE;
+            store_head(q, st, gd, tk, cb, obase, qi + t);
         }
-        if (have_prev) write_out(stop - 1, buf ^ 1u);
     }
 }
 
 hipError_t launch_quantize(const Batch &bt, const QDesc *qd, const Unit *units, const u32 *wg_u0, int n_wg, QInfo *qi,
                            hipStream_t s)
 {
-    static bool attr = false;
-    if (!attr) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_qprep,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (L2_BINS + 4) * 4);
-        if (e) return e;
-        attr = true;
-    }
-    if (n_wg) {
-        PROF("k_qprep", s, k_qprep<<<bt.nB, BLOCK, (L2_BINS + 4) * 4, s>>>(bt.td, bt.gd, qd, qi, bt.bufs));
-        PROF("k_quant", s, k_quant<<<n_wg, BLOCK, 0, s>>>(bt.td, units, wg_u0, bt.gd, qd, bt.bufs));
-    }
+    if (n_wg) PROF("k_quant", s, k_quant<<<n_wg, BLOCK, 0, s>>>(bt.td, units, wg_u0, bt.gd, qd, qi, bt.bufs));
     if (bt.nT > bt.nB)
         PROF("k_qsmall", s, k_qsmall<<<bt.nT - bt.nB, QS_NT, 0, s>>>(bt.td, bt.gd, qd, qi, bt.bufs, bt.nB));
     return hipGetLastError();

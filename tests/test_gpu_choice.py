@@ -8,7 +8,9 @@ import torch
 
 from oracle import ref
 from paper_2306_11800_amd import api, synth
+from test_gpu_full_size import unpack
 from test_gpu_fuzz import family
+from test_gpu_parity import check_quantized
 from test_gpu_small import KINDS, repeated
 
 pytestmark = pytest.mark.gpu
@@ -199,6 +201,42 @@ def test_quantizing_again_from_a_choice():
     same(ctx.quantize(ts, first, reuse_search=True), want.quantize(ts, first, reuse_search=True))
     ctx.close()
     want.close()
+
+
+@pytest.mark.parametrize("bits", range(1, 9))
+def test_symbols_of_every_width(bits):
+    """Both sweeps pack 2 to 9 bits a symbol, wave by wave: ends inside a wave's words, units of one tile and (70 M values
+    on 256 workgroups) of more than the 16 whose symbols are found by cells, with protected values in every tile, in one
+    and in none.  Every whole number as the oracle's, or as the thresholds and boundaries say."""
+    rng = np.random.default_rng(49)
+    ctx = api.Context(torch.device("cuda:0"))
+    for n in (16_385, 49_229, 330_001):
+        x = (0.02 * rng.standard_t(4, n)).astype(np.float32)
+        x[20_000:20_900] *= np.float32(40 if n > 330_000 else 1)
+        for cfg in ((bits, 200_000, 1000), (bits, 200_000, 0)):
+            t = [dev(x)]
+            ctx.search(t, [cfg], synth.EPS_DEFAULT, want_scores=False)
+            q = ctx.quantize(t, [cfg], reuse_search=True)
+            check_quantized(q[0], x, cfg)
+            ctx.profile(True)
+            again = ctx.quantize(t, [cfg], reuse_search=True)
+            assert "k_quant" in ctx.profile_read()
+            ctx.profile(False)
+            same(again, q)
+    n, cfg = 70_000_037, (bits, 200_000, 1000)
+    x = torch.empty(n, device="cuda:0")
+    x.normal_(generator=torch.Generator(device="cuda:0").manual_seed(50))
+    first = ctx.quantize([x], [cfg])
+    again = ctx.quantize([x], [cfg], reuse_search=True)
+    same(again, first)
+    q = again[0]
+    sym = torch.bucketize(x, q.boundaries[:q.K - 1].contiguous(), right=True) + 2
+    sym[x.abs() < q.tau_prune] = 0
+    sym[x.abs() > q.tau_outlier] = 1
+    assert torch.equal(unpack(q.packed, n, bits + 1).long(), sym)
+    assert torch.equal(q.outlier_idx[:q.n_outlier].long(), (sym == 1).nonzero()[:, 0])
+    assert torch.equal(q.outlier_val[:q.n_outlier], x[sym == 1])
+    ctx.close()
 
 
 def test_tensors_of_every_kind_in_one_call():
