@@ -17,7 +17,7 @@
 //   k_fprot    protected values: the sweep's lists, one per wave -> the tensor's list in index order
 //   k_fhead    per tensor: centres, boundaries, class counts
 //
-// 6.7 G values, symbols of 9 bits: k_fuse 10.3 ms (27.0 GB read, 8.7 GB written: 3.5 TB/s; bound by vector issue and the
+// 6.7 G values, symbols of 9 bits: k_fuse 9.5 ms (27.0 GB read, 8.7 GB written: 3.8 TB/s; bound by vector issue and the
 // LDS pipe, half of whose time are bank conflicts of the table reads; one workgroup of 16 waves fits a CU.  11.0 when
 // a tile's words were OR-ed together in LDS behind a barrier), k_fsplit 0.34, k_fsel 0.22, k_fpatch 0.41, k_fprot 0.37; boundaries, centres and
 // k_quant for one configuration took 8.7 (k_gather) + 0.6 + 8.9 (k_quant).  100 M values in 48 tensors: 0.25 ms where
@@ -323,7 +323,8 @@ __global__ __launch_bounds__(BLOCK) void k_fplan(const TDesc *__restrict__ td, c
 struct FuseShared {
     u32 T[COARSE];                   // key prefix -> bins
     u16 symt[L2_BINS];               // table of the bins
-    unsigned long long piece[BLOCK]; // four symbols of every lane: a wave's 64 are 4 w words of the stream
+    unsigned long long piece[4 * BLOCK]; // a tile's symbols, joined as WavePack does: 64 words for every wave and quarter
+    unsigned long long queue[BLOCK];     // per wave: values whose symbol the table of the bins does not say
     unsigned long long cell[F_CELLS * F_COPIES];
     u32 bp[QBP + 8];
     u16 symtab[QBP + 8];
@@ -332,6 +333,7 @@ struct FuseOut { // where a wave's lists go
     GLOBAL_AS u32 *key, *idx, *prot;
     u32 cap, pcap;       // entries of the lists
     u32 n, np;           // ... in use (wave-uniform)
+    u32 nq;              // values in the wave's queue, at most 64
     bool overflow;
 };
 
@@ -348,18 +350,90 @@ __device__ __forceinline__ void add_value(FuseShared &fs, u32 sym, u32 key, floa
               (unsigned long long)(__float_as_uint(x) & 0x7fffffu) | (1ull << F_CNT));
 }
 
+// Of 1024 values that a wave takes of a tile some twenty lie in bins that hold a breakpoint or are protected: few enough
+// for one pass over all of them, and in every quarter of them there are some.  So they queue up, and the wave works
+// on them together, a lane each, when the tile is through or the queue is full.  (A pass per quarter, or several if two
+// of a lane's four were among them: 6.7 G values 10.3 ms, 9.5 so; GPT-2 medium with Adam state 1.46 and 1.41.)
+// An entry: the key, and above it the table's entry and the value's place in the tile: quarter << 8 | lane << 2 | which of four.
+__device__ __forceinline__ unsigned long long queue_entry(u32 key, u32 e, u32 place) { return (u64)(place << 16 | e) << 32 | key; }
+
+struct FuseTile { // what the wave knows of the tile
+    u32 e0, n_bp, tau_o;
+    u32 zero_sym; // symbol of the zeros, if their bin holds breakpoints; F_PROT or above if the table says it
+};
+
 // DRY: nothing is written but the lists (no output buffers).
-template <bool FULL, bool DRY>
-__device__ __forceinline__ void fuse_tile(FuseShared &fs, const float (&v)[16], u32 mask, u32 e0, u32 n_bp, u32 w,
-                                          u32 zero_sym, u32 tau_o, GLOBAL_AS unsigned long long *dst, u32 n_words, FuseOut &o,
-                                          u32 (&pc)[4])
+// pc[j]: protected values of the wave's quarter j so far.
+template <bool DRY>
+__device__ __forceinline__ void fuse_queue(FuseShared &fs, u32 lane, const FuseTile &ft, const WavePack &wp, FuseOut &o, u32 (&pc)[4])
 {
-    const u32 tid = threadIdx.x, copy = tid & (F_COPIES - 1u), lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    bool aside = false, prot = false;
+    u32 k = 0u, place = 0u, index = 0u;
+    asm volatile("" ::: "memory"); // (a wave's LDS operations complete in order)
+    if (lane < o.nq) {
+        const unsigned long long entry = fs.queue[wave * 64u + lane];
+        k = (u32)entry;
+        const u32 x = (u32)(entry >> 32) & 0xFFFFu;
+        place = (u32)(entry >> 48);
+        index = ft.e0 + 4096u * (place >> 8) + 256u * wave + (place & 255u);
+        u32 sym = 1u;
+        if (x != F_PROT) {
+            u32 s = x & 511u; // breakpoints at or below the key, from the bin's first one on
+            if (fs.bp[s] <= k) {
+                s++;
+                if (fs.bp[s] <= k) s = slot_of_key(fs.bp, ft.n_bp, k);
+            }
+            sym = fs.symtab[s];
+            if (x & F_OPEN) {
+                aside = true;
+                sym = listed_symbol(sym, k, ft.tau_o);
+            }
+        }
+        prot = sym == 1u;
+        if (!DRY) wp.add(fs.piece + (place >> 8) * BLOCK + wave * 64u, (place >> 2) & 63u, place & 3u, sym);
+        if (sym >= 2u) add_value(fs, sym, k, __uint_as_float(bits_of_key(k)), lane & (F_COPIES - 1u));
+    }
+    o.nq = 0u;
+    const u64 am = __ballot(aside);
+    if (am) {
+        const u32 m = (u32)__popcll(am);
+        if (o.n + m > o.cap) {
+            o.overflow = true;
+        } else {
+            if (aside) {
+                const u32 at = __builtin_amdgcn_mbcnt_hi((u32)(am >> 32), __builtin_amdgcn_mbcnt_lo((u32)am, o.n));
+                o.key[at] = k;
+                if (!DRY) o.idx[at] = index;
+            }
+            o.n += m;
+        }
+    }
+    const u64 pm = __ballot(prot);
+    if (pm) { // listed in index order, as they queued up
+        const u32 m = (u32)__popcll(pm);
+        if (o.np + m > o.pcap) {
+            o.overflow = true;
+        } else {
+            if (prot) o.prot[__builtin_amdgcn_mbcnt_hi((u32)(pm >> 32), __builtin_amdgcn_mbcnt_lo((u32)pm, o.np))] = index;
+            o.np += m;
+#pragma unroll
+            for (u32 j = 0; j < 4u; j++) pc[j] += (u32)__popcll(__ballot(prot && place >> 8 == j));
+        }
+    }
+    asm volatile("" ::: "memory");
+}
+
+template <bool FULL, bool DRY>
+__device__ __forceinline__ void fuse_tile(FuseShared &fs, u32 lane, const float (&v)[16], u32 mask, const FuseTile &ft, u32 w,
+                                          GLOBAL_AS unsigned long long *dst, u32 n_words, FuseOut &o, u32 (&pc)[4])
+{
+    const u32 copy = lane & (F_COPIES - 1u), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const WavePack wp(w, lane);
+    pc[0] = pc[1] = pc[2] = pc[3] = 0u;
 #pragma unroll
     for (int j = 0; j < 4; j++) {
         u32 e[4], key[4];
-        pc[j] = 0u;
 #pragma unroll
         for (int c = 0; c < 4; c++) {
             key[c] = key_of_float(v[4 * j + c]);
@@ -370,6 +444,9 @@ __device__ __forceinline__ void fuse_tile(FuseShared &fs, const float (&v)[16], 
             e[c] = lookup_u16(fs.symt, key[c], e[c]);
             if (!FULL && !((mask >> (4 * j + c)) & 1u)) e[c] = 0u;
         }
+        if (ft.zero_sym < F_PROT) // (they may be most of a tensor)
+#pragma unroll
+            for (int c = 0; c < 4; c++) e[c] = key[c] == ZERO_KEY && e[c] >= F_PROT ? ft.zero_sym : e[c];
         u32 lo32 = 0u, s3 = 0u;
 #pragma unroll
         for (int c = 0; c < 4; c++) {
@@ -380,73 +457,35 @@ __device__ __forceinline__ void fuse_tile(FuseShared &fs, const float (&v)[16], 
                 s3 = sym;
             if (sym >= 2u) add_value(fs, sym, key[c], v[4 * j + c], copy);
         }
-        unsigned long long piece = (unsigned long long)lo32 | ((unsigned long long)s3 << (3u * w));
-        u32 protected4 = 0u;
+        if (!DRY) wp.put((unsigned long long)lo32 | ((unsigned long long)s3 << (3u * w)), fs.piece + j * BLOCK + wave * 64u, lane);
         if (__ballot((e[0] | e[1] | e[2] | e[3]) >= F_PROT)) { // (the same for the whole wave)
-            u32 rest = 0u; // which of the lane's four lie in such a bin; one at a time, rarely two
+            u32 n = 0u, below;
 #pragma unroll
-            for (u32 c = 0; c < 4u; c++) rest |= e[c] >= F_PROT ? 1u << c : 0u;
-            do {
-                const u32 c = (u32)__ffs((int)rest) - 1u;
-                const u32 x = c == 0u ? e[0] : c == 1u ? e[1] : c == 2u ? e[2] : e[3];
-                const u32 k = c == 0u ? key[0] : c == 1u ? key[1] : c == 2u ? key[2] : key[3];
-                bool aside = false;
-                if (rest) {
-                    u32 sym = 1u;
-                    if (x != F_PROT) {
-                        u32 s = x & 511u; // breakpoints at or below the key, from the bin's first one on
-                        if (fs.bp[s] <= k) {
-                            s++;
-                            if (k != ZERO_KEY && fs.bp[s] <= k) s = slot_of_key(fs.bp, n_bp, k);
-                        }
-                        sym = fs.symtab[s];
-                        if (k == ZERO_KEY) {
-                            sym = zero_sym;
-                        } else if (x & F_OPEN) {
-                            aside = true;
-                            sym = listed_symbol(sym, k, tau_o);
-                        }
-                    }
-                    protected4 |= sym == 1u ? 1u << c : 0u;
-                    piece |= (unsigned long long)sym << (c * w);
-                    if (sym >= 2u) add_value(fs, sym, k, __uint_as_float(bits_of_key(k)), copy);
-                }
-                const u64 am = __ballot(aside);
-                if (am) {
-                    const u32 m = (u32)__popcll(am);
-                    if (o.n + m > o.cap) {
-                        o.overflow = true;
-                    } else {
-                        if (aside) {
-                            const u32 at = __builtin_amdgcn_mbcnt_hi((u32)(am >> 32), __builtin_amdgcn_mbcnt_lo((u32)am, o.n));
-                            o.key[at] = k;
-                            if (!DRY) o.idx[at] = e0 + 4u * (tid + 1024u * j) + c;
-                        }
-                        o.n += m;
-                    }
-                }
-                rest &= rest - 1u;
-            } while (__ballot(rest != 0u));
-        }
-        if (__ballot(protected4 != 0u)) { // listed in index order
-            u32 at;
-            const u32 k = rank_counts((u32)__popc(protected4), at);
-            if (o.np + k > o.pcap) {
-                o.overflow = true;
-            } else {
-                at += o.np;
+            for (int c = 0; c < 4; c++) n += e[c] >= F_PROT ? 1u : 0u;
+            const u32 all = rank_counts(n, below);
+            // (more than 64 of a quarter: 16 lanes at a time)
+            for (u32 part = 0u; part < 4u; part += all > 64u ? 1u : 4u) {
+                const bool now = all <= 64u || lane >> 4 == part;
+                u32 m = all;
+                if (all > 64u) m = rank_counts(now ? n : 0u, below);
+                if (o.nq + m > 64u) fuse_queue<DRY>(fs, lane, ft, wp, o, pc);
+                u32 at = wave * 64u + o.nq + below;
 #pragma unroll
-                for (u32 c = 0; c < 4u; c++)
-                    if ((protected4 >> c) & 1u) o.prot[at++] = e0 + 4u * (tid + 1024u * j) + c;
-                o.np += k;
-                pc[j] = k;
+                for (int c = 0; c < 4; c++)
+                    if (now && e[c] >= F_PROT) fs.queue[at++] = queue_entry(key[c], e[c], (u32)j << 8 | lane << 2 | (u32)c);
+                o.nq += m;
             }
         }
-        if (!DRY) {
-            const unsigned long long x = wp.word(piece, fs.piece + wave * 64u, lane);
+    }
+    if (o.nq) fuse_queue<DRY>(fs, lane, ft, wp, o, pc);
+    if (!DRY) {
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            const unsigned long long x = wp.word(fs.piece + j * BLOCK + wave * 64u, lane);
             const u32 at = ((u32)j * (BLOCK / 64) + wave) * 4u * w + lane;
             if (lane < 4u * w && (FULL || at < n_words)) dst[at] = x;
         }
+        asm volatile("" ::: "memory");
     }
 }
 
@@ -455,9 +494,12 @@ __global__ __launch_bounds__(BLOCK) void k_fuse(const TDesc *__restrict__ td, co
                                                 const GridDesc *__restrict__ gd, const QDesc *__restrict__ qd, Bufs B)
 {
     __shared__ FuseShared fs; // (one static object: it starts at LDS address 0, offsets fold into the instructions)
-    const u32 tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    for (u32 k = tid; k < F_CELLS * F_COPIES; k += BLOCK) fs.cell[k] = 0ull;
+    const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (u32 k = threadIdx.x; k < F_CELLS * F_COPIES; k += BLOCK) fs.cell[k] = 0ull;
     for (u32 gu = wg_gu0[blockIdx.x]; gu < wg_gu0[blockIdx.x + 1]; gu++) {
+        u32 tid = threadIdx.x;
+        asm volatile("" : "+v"(tid)); // (what is derived from it is cheap: worked out per unit it is not kept in scratch)
+        const u32 lane = tid & 63u;
         const Unit un = B.gunits[gu];
         const int t = (int)un.tensor;
         TState *st = B.ts + t;
@@ -478,7 +520,8 @@ __global__ __launch_bounds__(BLOCK) void k_fuse(const TDesc *__restrict__ td, co
             fs.symtab[tid] = B.edge_item[(size_t)t * MAX_EDGES + tid];
         }
         __syncthreads();
-        const u32 zero_sym = __builtin_amdgcn_readfirstlane((u32)fs.symtab[QBP]);
+        const u32 zero_e = lookup_u16(fs.symt, ZERO_KEY, fs.T[ZERO_KEY >> COARSE_SHIFT]);
+        const u32 zero_sym = __builtin_amdgcn_readfirstlane(zero_e >= F_PROT ? (u32)fs.symtab[QBP] : F_PROT);
         const u32 tau_o = __builtin_amdgcn_readfirstlane(st->thr_mag[gd->n_p + gd->pair_o[gd->cfg_pair[q.cfg]]]);
         GLOBAL_AS unsigned long long *packed = gptr(q.packed);
         const ProtLists pl = prot_lists(un, q.span);
@@ -488,7 +531,7 @@ __global__ __launch_bounds__(BLOCK) void k_fuse(const TDesc *__restrict__ td, co
         o.idx = o.key + o.cap;
         o.prot = gptr(B.pool) + pl.list + (u64)wave * pl.cap;
         o.pcap = pl.cap;
-        o.n = o.np = 0u;
+        o.n = o.np = o.nq = 0u;
         o.overflow = false;
         u64 sum_m = 0ull; // cell tid of the unit so far
         u32 sum_c = 0u;
@@ -531,10 +574,11 @@ __global__ __launch_bounds__(BLOCK) void k_fuse(const TDesc *__restrict__ td, co
             GLOBAL_AS unsigned long long *dst = packed + (tile - d.tile0) * (u64)(256u * w);
             const u32 n_words = (cnt * w + 63u) >> 6;
             // (whole tile or not is the same for every lane: the tile code uses ballots)
+            const FuseTile ft = {(u32)e0, n_bp, tau_o, zero_sym};
             if (cnt == (u32)TILE)
-                fuse_tile<true, DRY>(fs, v, mask, (u32)e0, n_bp, w, zero_sym, tau_o, dst, n_words, o, pc);
+                fuse_tile<true, DRY>(fs, lane, v, mask, ft, w, dst, n_words, o, pc);
             else
-                fuse_tile<false, DRY>(fs, v, mask, (u32)e0, n_bp, w, zero_sym, tau_o, dst, n_words, o, pc);
+                fuse_tile<false, DRY>(fs, lane, v, mask, ft, w, dst, n_words, o, pc);
             if (lane == 0u) {
                 typedef u32 u2 __attribute__((ext_vector_type(2)));
                 const u2 x = {pc[0] | (pc[1] << 16), pc[2] | (pc[3] << 16)};

@@ -34,7 +34,7 @@ __device__ __forceinline__ u32 rank_counts(u32 cj, u32 &below)
 // the symbols of 4, 2 or 1 lanes (as many as fit a word) are joined in registers, these pieces exchanged through the
 // wave's own 64 words of LDS, and lane k < 4 w takes word k from the two or three pieces that it lies in.
 // (A wave's LDS operations complete in order: no other wave is asked.  Pieces of one lane each, up to nine of them a word:
-// k_quant on 1.6 G values of 3 to 9 bits 2.37 ms, 2.29 so; k_fuse on 6.7 G of 9 bits 10.54 and 10.29.)
+// k_quant on 1.6 G values of 3 to 9 bits 2.37 ms, 2.29 so; k_fuse on 6.7 G of 9 bits, with the same means otherwise, 10.54 and 10.29.)
 struct WavePack {
     u32 w, join, bits, p0, skip; // lanes per piece; bits of a piece; the word's first piece, bits of it before the word
     __device__ __forceinline__ WavePack(u32 w_, u32 lane) : w(w_)
@@ -57,14 +57,24 @@ struct WavePack {
         }
         return (unsigned long long)b << 32 | a;
     }
-    // all lanes of the wave; word `lane` of the 4 w in lanes below 4 w
-    __device__ __forceinline__ unsigned long long word(unsigned long long piece, unsigned long long *mine, u32 lane) const
+    // the pieces of a wave's lanes
+    __device__ __forceinline__ void put(unsigned long long piece, unsigned long long *mine, u32 lane) const
     {
         if (join > 1u) piece |= swapped(piece, true) << (4u * w); // (right in the first lane of two)
         if (join > 2u) piece |= swapped(piece, false) << (8u * w); // (... of four)
         asm volatile("" ::: "memory");
-        if ((lane & (join - 1u)) == 0u) mine[join == 4u ? lane >> 2 : join == 2u ? lane >> 1 : lane] = piece;
+        if ((lane & (join - 1u)) == 0u) mine[place(lane)] = piece;
         asm volatile("" ::: "memory");
+    }
+    __device__ __forceinline__ u32 place(u32 lane) const { return join == 4u ? lane >> 2 : join == 2u ? lane >> 1 : lane; }
+    // a symbol that put() found zero: value c of a lane
+    __device__ __forceinline__ void add(unsigned long long *mine, u32 lane, u32 c, u32 sym) const
+    {
+        atomicOr(&mine[place(lane)], (unsigned long long)sym << ((4u * (lane & (join - 1u)) + c) * w));
+    }
+    // word `lane` of the 4 w, in lanes below 4 w
+    __device__ __forceinline__ unsigned long long word(const unsigned long long *mine, u32 lane) const
+    {
         unsigned long long x = 0ull;
         if (lane < 4u * w) {
             x = mine[p0] >> skip;

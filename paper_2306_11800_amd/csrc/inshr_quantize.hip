@@ -90,7 +90,9 @@ __device__ __forceinline__ void classify_tile(QuantShared &qs, u32 tid, const fl
                 s3 = sym;
             omask |= (sym == 1u ? 1u : 0u) << (4 * j + c);
         }
-        const unsigned long long x = wp.word((unsigned long long)lo32 | ((unsigned long long)s3 << (3u * w)), qs.piece + wave * 64u, lane);
+        unsigned long long *mine = qs.piece + wave * 64u;
+        wp.put((unsigned long long)lo32 | ((unsigned long long)s3 << (3u * w)), mine, lane);
+        const unsigned long long x = wp.word(mine, lane);
         const u32 at = ((u32)j * (BLOCK / 64) + wave) * 4u * w + lane;
         if (lane < 4u * w && (FULL || at < n_words)) dst[at] = x;
         if (any_prot) { // protected values of this wave's 256 elements: total, and those of lower lanes

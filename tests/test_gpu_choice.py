@@ -239,6 +239,31 @@ def test_symbols_of_every_width(bits):
     ctx.close()
 
 
+@pytest.mark.parametrize("levels", [0, 4000, 300, 40])
+@pytest.mark.parametrize("n", [16_385, 120_001])
+def test_values_in_bins_with_breakpoints(levels, n):
+    """Values whose symbol the sweep works out one by one, from a few of a wave's 256 to all of them: the fewer distinct values
+    there are, the more share a bin with a boundary (40 levels: nearly every bin that holds any).  Also with half of the
+    values zero and boundaries there.  Against the oracle."""
+    rng = np.random.default_rng(51)
+    ctx = api.Context(torch.device("cuda:0"))
+    x = rng.standard_normal(n).astype(np.float32)
+    if levels:
+        x = np.round(x * np.float32(levels / 8)) / np.float32(levels / 8)
+    half = x.copy()
+    half[rng.random(n) < 0.5] = 0.0
+    half[::7] *= np.float32(-1)  # (zeros of both signs)
+    for y in (x, half):
+        for cfg in ((8, 200_000, 1000), (5, 0, 5000), (2, 0, 0)):
+            ctx.profile(True)
+            q = ctx.quantize([dev(y)], [cfg])
+            kernels = ctx.profile_read()
+            ctx.profile(False)
+            assert "k_fuse" in kernels, kernels
+            check_quantized(q[0], y, cfg)
+    ctx.close()
+
+
 def test_tensors_of_every_kind_in_one_call():
     """One call with tensors that the state holds, that the sweep takes, that it gives up (one bin holds more values
     than a wave should read), that protect too much for its lists, and a small one: several passes, each on its own
