@@ -88,7 +88,10 @@ public:
             guard([&] { f(i); });
         }
         const uint32_t turn = turn_.load(std::memory_order_relaxed);
-        if (arrived_.fetch_add(1, std::memory_order_acq_rel) + 1 == size_.load(std::memory_order_relaxed)) {
+        // (first the arrival, then the size: the team may have become smaller until this thread arrived, and the last one to
+        // arrive has to find that; the operands of one == come in no order)
+        const uint32_t there = arrived_.fetch_add(1, std::memory_order_acq_rel) + 1;
+        if (there == size_.load(std::memory_order_relaxed)) {
             guard(once);
             arrived_.store(0, std::memory_order_relaxed);
             next_.store(0, std::memory_order_relaxed);

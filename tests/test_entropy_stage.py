@@ -3,6 +3,8 @@ against the oracle: run-length tokens and the payload size of every group are un
 exactly (the total cost of a Huffman code does not depend on tie-breaking); the codes themselves are
 checked for validity: the container decodes back to the same stream, bit for bit."""
 import ctypes as C
+import os
+import resource
 import struct
 import subprocess
 import sys
@@ -251,6 +253,52 @@ data = np.concatenate([head.view(np.uint8), table.view(np.uint8).ravel()])
 dec = lambda: lib.inshr_entropy_decode(data.ctypes.data, data.size, 0, 1, 1, packed.ctypes.data, None, None)
 print(limited(dec), dec())
 """
+
+
+FEWER_THREADS = """
+import resource, threading
+import numpy as np
+from paper_2306_11800_amd import api
+rng = np.random.default_rng(9)
+n, G = (1 << 20) + 5, 66
+goff = np.concatenate([[0], np.sort(rng.integers(0, n, G - 1)), [n]]).astype(np.uint64)
+v = np.minimum(rng.geometric(0.4, n) - 1, 65).astype(np.uint16)
+want, stats = api.entropy_encode(goff, 7, values=v)
+vm = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+stack, old = resource.getrlimit(resource.RLIMIT_STACK)[0], resource.getrlimit(resource.RLIMIT_AS)
+for more in (0, 1, 2):             # threads that there is room for
+    resource.setrlimit(resource.RLIMIT_AS, (vm + more * stack + stack // 2, old[1]))
+    go, started = threading.Event(), []
+    try:
+        for _ in range(4):
+            t = threading.Thread(target=go.wait)
+            t.start()
+            started.append(t)
+    except RuntimeError:
+        pass
+    go.set()
+    for t in started:
+        t.join()
+    assert len(started) == more, (len(started), more)
+    for _ in range(20):
+        data, st = api.entropy_encode(goff, 7, values=v)
+        assert np.array_equal(data, want) and st == stats
+        back, goff2 = api.entropy_decode(data, n, 7, G, as_values=True)
+        assert np.array_equal(back, v) and np.array_equal(goff2, goff)
+    resource.setrlimit(resource.RLIMIT_AS, old)
+print("ok")
+"""
+
+
+def test_fewer_threads_than_asked_for():
+    """Threads that cannot be started (stacks of 4 GB, address space for 0, 1 or 2 of them): the others do their work, and
+    every pass of a call ends, while some of them work before the call knows how many there are."""
+    if len(os.sched_getaffinity(0)) < 4:
+        pytest.skip("as many threads as there is room for")
+    r = subprocess.run([sys.executable, "-c", FEWER_THREADS], capture_output=True, text=True, timeout=120,
+                       env=dict(os.environ, OMP_NUM_THREADS="1", OPENBLAS_NUM_THREADS="1"),
+                       preexec_fn=lambda: resource.setrlimit(resource.RLIMIT_STACK, (4 << 30, resource.getrlimit(resource.RLIMIT_STACK)[1])))
+    assert r.returncode == 0 and r.stdout.split() == ["ok"], r.stderr
 
 
 def test_host_memory_that_runs_out_is_an_error():
