@@ -243,11 +243,14 @@ __device__ __forceinline__ void draw_centres(const T *xq, const D *xw, u32 m, u3
         const double inc = wave_incl_sum(upto[PER - 1u]), before = lane_below(inc), total = lane_value(inc, 63u);
         if (r == 0u || total > 0.0) { // (else every bucket is a centre already: the last one again)
             const double target = mul_rn(uni[r], total);
-            const u64 above = __ballot(lo < m && inc > target);
+            // (a lane that has something to draw from: the tree's sums need not ascend, one that adds nothing may end an ulp
+            // above the lane below it)
+            const double whole = upto[PER - 1u];
+            const u64 above = __ballot(whole > 0.0 && inc > target);
             if (above) {
                 // (where rounding leaves no sum of the lane above: its last bucket that can be drawn)
                 double rest = sub_rn(target, before);
-                const double whole = upto[PER - 1u];
+                rest = rest > 0.0 ? rest : 0.0;
                 rest = whole > rest ? rest : __longlong_as_double(__double_as_longlong(whole) - 1ll);
                 double pick = x[PER - 1u];
 #pragma unroll
@@ -289,8 +292,8 @@ __device__ __forceinline__ void draw_centres_long(const T *xq, D *xw, u32 m, u32
     __syncthreads();
     // Per draw: (1) every thread sums the probabilities of its share, a scan gives the running
     // sums inside the wave, the wave totals go to LDS; (2) every thread adds the totals of the
-    // waves before its own (in wave order) and the first thread whose running sum exceeds the
-    // target announces itself; (3) that thread walks its share.  The LDS cells alternate between two copies
+    // waves before its own (in wave order) and the first thread that has something to draw from and whose
+    // running sum exceeds the target announces itself; (3) that thread walks its share.  The LDS cells alternate between two copies
     // from draw to draw, so that a draw never waits for the cells of the one before to be read.
     for (u32 r = 0; r < K; r++) {
         const u32 cp = r & 1u;
@@ -318,7 +321,7 @@ __device__ __forceinline__ void draw_centres_long(const T *xq, D *xw, u32 m, u32
         const double target = mul_rn(uni[r], total);
         const double excl = add_rn(wbase, before), incl = add_rn(wbase, inc);
         // one atomic per wave: its first lane above the target, its last lane with a drawable bucket
-        const u64 above = __ballot(incl > target && lo < hi), drawable = __ballot(last_pos != 0u);
+        const u64 above = __ballot(incl > target && last_pos != 0u), drawable = __ballot(last_pos != 0u);
         if (above && lane == (u32)__builtin_ctzll(above)) atomicMin(&s_pick[cp], tid);
         if (drawable && lane == 63u - (u32)__builtin_clzll(drawable)) atomicMax(&s_last[cp], last_pos);
         __syncthreads();
@@ -328,11 +331,12 @@ __device__ __forceinline__ void draw_centres_long(const T *xq, D *xw, u32 m, u32
             u32 jj = s_last[cp] ? s_last[cp] - 1u : 0u;
             if (pick != 0xFFFFFFFFu) {
                 double run = excl; // the running sum at the start of this thread's share
-                jj = last_pos ? last_pos - 1u : lo;
+                jj = last_pos - 1u;
                 for (u32 i = lo; i < hi; i++) {
                     const d2 b = xw[i];
-                    run = add_rn(run, r ? mul_rn(b.y, b.x) : b.x);
-                    if (run > target) {
+                    const double p = r ? mul_rn(b.y, b.x) : b.x;
+                    run = add_rn(run, p);
+                    if (p > 0.0 && run > target) {
                         jj = i;
                         break;
                     }

@@ -90,6 +90,70 @@ def test_lists_of_every_length(ctx, m):
     check(ctx, [rng.permutation(x)], [(8 if m % 2 else 5, 0, 0)], 0.01, 0.2, 60, 2000 + m)
 
 
+def running_sums(probs, m, per, waves):
+    """The running sums that the draws compare with their target: `per` buckets to a lane, added in index order, the lanes'
+    sums by a tree (in rows of 16, then rows, then halves), the waves' one after the other."""
+    share = np.zeros(64 * waves * per)
+    share[:m] = probs
+    share = share.reshape(-1, per)
+    upto = share[:, 0].copy()
+    for q in range(1, per):
+        upto = upto + share[:, q]
+    out, base = np.zeros(64 * waves), 0.0
+    for wv in range(waves):
+        a = upto[64 * wv:64 * wv + 64].reshape(4, 16).copy()
+        for step in (1, 2, 4, 8):
+            a[:, step:] = a[:, step:] + a[:, :-step].copy()
+        a[1] += a[0, 15]
+        a[3] += a[2, 15]
+        a[2:] += a[1, 15]
+        out[64 * wv:64 * wv + 64] = base + a.ravel()
+        base += a[3, 15]
+    return out, upto, base
+
+
+@pytest.mark.parametrize("m,per,waves", [(64, 4, 1), (300, 6, 1), (384, 6, 1), (700, 12, 1), (1000, 16, 1), (1500, 24, 1),
+                                         (2000, 4, 8), (4000, 8, 8)])
+def test_a_lane_whose_buckets_are_all_centres_is_not_drawn_from(ctx, m, per, waves):
+    """The lanes' sums come from a tree, so a lane that adds nothing can still end an ulp above the lane before it.  The
+    uniforms make every bucket of such a lane a centre and then aim at that ulp: the next centre is another one."""
+    found = 0
+    for seed in range(40):
+        rng = np.random.default_rng(seed)
+        mags = np.exp((0.0203 if m < 2000 else 0.0201) * (np.arange(m) - m // 2))
+        x = np.repeat(np.concatenate([-mags[:m // 3], mags[m // 3:]]), rng.integers(1, 4, m)).astype(np.float32)
+        sign, index, count = sk.sketch_histogram(x, 0.01)
+        assert count.size == m
+        xq = sk.bucket_value(sign, index, 0.01)
+        w = sk.sample_weights(xq, count, 0.2)
+        for lane in range(1, min(63, m // per - 1)):
+            dist, uni = np.ones(m), []
+            for b in range(lane * per, lane * per + per):
+                sums, _, total = running_sums(dist * w, m, per, waves)
+                p = dist * w
+                uni.append((sums[lane - 1] + p[lane * per:b].sum() + 0.5 * p[b]) / total)
+                d = (xq - xq[b]) ** 2
+                dist = d if len(uni) == 1 else np.minimum(dist, d)
+            sums, upto, total = running_sums(dist * w, m, per, waves)
+            assert upto[lane] == 0.0
+            top = sums[:lane].max()
+            us = [top / total]
+            us += [np.nextafter(us[0], 0.0), np.nextafter(us[0], 1.0)]
+            us = [u for u in us if top <= u * total < sums[lane]]
+            if us:
+                found += 1
+                uniforms = np.full((1, 256), 0.5)
+                uniforms[0, :per + 1] = uni + us[:1]
+                q, _ = ctx.quantize_sketch([dev(x)], [(5, 0, 0)], uniforms, alpha=0.01, sigma=0.2, max_iter=0)
+                centres = q[0].codebook.cpu().numpy()[:32]
+                assert np.isin(xq[lane * per:lane * per + per].astype(np.float32), centres).all()  # (as they were meant to be)
+                assert np.unique(centres).size == 32, (seed, lane)
+                break
+        if found >= 3:
+            break
+    assert found
+
+
 def test_sums_are_not_contracted(ctx):
     """Eleven symmetric buckets, four clusters, magnitude-only weights: after the first Lloyd round
     the two inner centres are exact mirror images only if every product is rounded before it is
