@@ -1405,7 +1405,7 @@ int sketch_with_state(inshr_ctx *c, const inshr_config *cfg, const uint32_t *whi
     const size_t upload = cv.off; // everything up to here comes from the host
     const size_t o_hist = cv.take(sizeof(u32) * SK_HIST * nT);
     const size_t o_xq = cv.take(sizeof(double) * SK_HIST * nT);
-    const size_t o_wd = cv.take(2 * sizeof(double) * SK_HIST * nT);
+    const size_t o_wd = cv.take(2 * sizeof(double) * SK_HIST * nT); // (read up to 240 bytes past a row: more follows)
     const size_t n_sets = multi ? SK_SETS : 1;
     const size_t o_key = cv.take(sizeof(u32) * 256 * n_sets * nT);
     const size_t o_cb = cv.take(sizeof(float) * 256 * n_sets * nT);

@@ -356,20 +356,14 @@ __device__ __forceinline__ void draw_centres_long(const T *xq, D *xw, u32 m, u32
     }
 }
 
-// Weights and products of the run [i, e) of a list, each added up in index order.  PADDED: 15 entries may be read past
-// the list's end; eight entries are then asked for before the eight before them are added: about 14 ns a bucket,
-// 25 with eight reads and the sums of what they bring in turn.
-template <bool PADDED, class D> __device__ __forceinline__ d2 run_sum(const D *xw, u32 i, u32 e)
+// Weights and products of the run [i, e) of a list, each added up in index order.  15 entries may be read past the list's
+// end (LDS has room for them; behind a scratch row lies more of the same allocation): eight entries are asked for before the
+// eight before them are added: about 14 ns a bucket in LDS, 25 with eight reads and the sums of what they bring in turn.
+// (Lists in device memory, 16 of 6000 buckets, all widths / 256 / 16 centres: one entry at a time 16.3 / 8.8 / 5.8 ms, so 8.0 /
+// 4.7 / 1.6.)
+template <class D> __device__ __forceinline__ d2 run_sum(const D *xw, u32 i, u32 e)
 {
     double sw = 0.0, sx = 0.0;
-    if (!PADDED) {
-        for (; i < e; i++) {
-            const d2 b = xw[i];
-            sw = add_rn(sw, b.x);
-            sx = add_rn(sx, b.y);
-        }
-        return d2{sw, sx};
-    }
     constexpr u32 N = 8;
     d2 a[N], b[N];
     auto ask = [&](d2 (&to)[N]) {
@@ -416,7 +410,7 @@ template <bool PADDED, class D> __device__ __forceinline__ d2 run_sum(const D *x
 // sorted list, belongs to lane k % 64.  No wave waits for another set's rounds, and a cluster whose run is the one of
 // the round before keeps its centre.  Bound by the longest run that changed: a cluster around zero can hold
 // half of the buckets.
-template <u32 Q, bool PADDED, class T, class D>
+template <u32 Q, class T, class D>
 __device__ __forceinline__ u32 lloyd_rounds(const T *xq, const D *xw, u32 m, u32 Kb, double *c_set, u32 max_iter)
 {
     const u32 lane = threadIdx.x & 63u;
@@ -467,7 +461,7 @@ __device__ __forceinline__ u32 lloyd_rounds(const T *xq, const D *xw, u32 m, u32
 #pragma unroll
         for (u32 q = 0; q < Q; q++) {
             if (!again[q]) continue;
-            const d2 s = run_sum<PADDED>(xw, first[q], end[q]);
+            const d2 s = run_sum(xw, first[q], end[q]);
             if (s.x > 0.0) c[q] = div_rn(s.y, s.x);
         }
         rounds++;
@@ -605,9 +599,9 @@ __global__ __launch_bounds__(KM_BLOCK) void k_sketch_kmeans(const GridDesc *__re
         if (wave < n_sets) {
             const u32 Ks = P.multi ? 4u << wave : K;
             double *c_set = cen + (P.multi ? Ks - 4u : 0u);
-            const u32 r = Ks <= 64u    ? lloyd_rounds<1, LDS>(xq, xw, m, Ks, c_set, P.max_iter)
-                          : Ks <= 128u ? lloyd_rounds<2, LDS>(xq, xw, m, Ks, c_set, P.max_iter)
-                                       : lloyd_rounds<4, LDS>(xq, xw, m, Ks, c_set, P.max_iter);
+            const u32 r = Ks <= 64u    ? lloyd_rounds<1>(xq, xw, m, Ks, c_set, P.max_iter)
+                          : Ks <= 128u ? lloyd_rounds<2>(xq, xw, m, Ks, c_set, P.max_iter)
+                                       : lloyd_rounds<4>(xq, xw, m, Ks, c_set, P.max_iter);
             if (lane == 0u) s_rounds[wave] = r;
         }
         // ---- codebooks and boundaries ----

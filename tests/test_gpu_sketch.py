@@ -79,7 +79,7 @@ def test_parameters(ctx):
         check(ctx, [x, -np.abs(x)], [(5, 100000, 1000), (6, 0, 0)], alpha, sigma, max_iter, 7)
 
 
-@pytest.mark.parametrize("m", [1, 64, 255, 256, 257, 384, 385, 512, 513, 768, 769, 1024, 1025, 1536, 1537, 4096, 4097])
+@pytest.mark.parametrize("m", [1, 64, 255, 256, 257, 384, 385, 512, 513, 768, 769, 1024, 1025, 1536, 1537, 4096, 4097, 8600])
 def test_lists_of_every_length(ctx, m):
     """m non-empty buckets of both signs: the edges of what a lane keeps of them while the centres are drawn, of
     the lists in LDS and of those in device memory."""
