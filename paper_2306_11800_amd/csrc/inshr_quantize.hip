@@ -40,7 +40,10 @@ __device__ __forceinline__ void classify_tile(QuantShared &qs, u32 tid, const fl
                                               u32 &omask, u32 (&pre)[4])
 {
     const u32 lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const WavePack wp(w, lane);
+    // (Of a whole tile every lane stores a word, those past the wave's 4 w its first one again: the number of stores since a
+    // load is the same on every way, and waiting for the next tile's values does not wait for these stores, too.)
+    const u32 word = FULL && lane >= 4u * w ? 0u : lane;
+    const WavePack wp(w, word);
     const u16 *symt = qs.symt;
     const QuantTables &qt = qs.qt;
     omask = 0u;
@@ -92,9 +95,9 @@ __device__ __forceinline__ void classify_tile(QuantShared &qs, u32 tid, const fl
         }
         unsigned long long *mine = qs.piece + wave * 64u;
         wp.put((unsigned long long)lo32 | ((unsigned long long)s3 << (3u * w)), mine, lane);
-        const unsigned long long x = wp.word(mine, lane);
-        const u32 at = ((u32)j * (BLOCK / 64) + wave) * 4u * w + lane;
-        if (lane < 4u * w && (FULL || at < n_words)) dst[at] = x;
+        const unsigned long long x = wp.word(mine, word);
+        const u32 at = ((u32)j * (BLOCK / 64) + wave) * 4u * w + word;
+        if (FULL || (lane < 4u * w && at < n_words)) dst[at] = x;
         if (any_prot) { // protected values of this wave's 256 elements: total, and those of lower lanes
             const u32 cj = __popc((omask >> (4 * j)) & 0xFu);
             u32 tot = 0u;
@@ -190,8 +193,12 @@ __global__ __launch_bounds__(QS_NT) void k_qsmall(const TDesc *__restrict__ td, 
     store_head(q, st, gd, tk, cb, found, qi + t);
 }
 
-// Long runs: bound by vector issue and the table's dependent LDS reads (355 M values in 292 tensors 0.55 ms, 2.6 TB/s of
-// values; 1.6 G of 3 to 9 bits 2.2).  Runs of one tile: by the latency of what comes before the tile (64 of them 21 us).
+// Long runs: bound by vector issue and the table's dependent LDS reads (355 M values in 292 tensors, 9 bits, 0.53 ms: 2.7 TB/s of
+// values; 6.7 G in 291 7.9).  Runs of one tile: by the latency of what comes before the tile (64 of them 21 us).
+// Whole tiles have a loop of their own in which nothing waits for the stores of the tile before (with the last tile's code in it
+// the compiler waited for all of them: 8.5 ms), and their waves meet once a tile, also where nothing is protected: waves
+// that drift apart read from too many places (8 bits, nothing protected: 7.9 ms, 7.05 so; protected values kept in
+// a list per wave and the waves meeting every few tiles: 9.0).
 // A wave packs its own words without waiting for the others (0.60 ms, 64 runs 30 us with lane pieces OR-ed into a
 // buffer of the tile behind a barrier, every held cell of the table bisected and the tile read after it; that needed a
 // kernel before, of 8 us, for the places of the protected values.  A unit now adds the counts of the tiles before it up itself,
@@ -330,40 +337,14 @@ __global__ __launch_bounds__(BLOCK) void k_quant(const TDesc *__restrict__ td, c
 #pragma unroll
         for (u32 i = 0; i < BLOCK / 64; i++) obase += qs.sum[i]; // (wave-uniform)
         obase = __builtin_amdgcn_readfirstlane(obase);
-        // A wave's symbols are whole words of their own, which it packs and stores; the waves meet only where a tile has
-        // protected values, whose places depend on the other waves' counts.  The next tile is asked for before a tile is
-        // worked on.
+        // A wave's symbols are whole words of their own, which it packs and stores; the places of a tile's protected values
+        // depend on the other waves' counts.  The next tile is asked for before a tile is worked on.
         auto walk = [&](auto mode) {
             constexpr int MODE = decltype(mode)::value;
-            u32 next = n_prot[tile * MAX_FRAC]; // (asked for with the tile's values)
-            for (; tile < stop; tile++) {
-                const u64 e0 = (tile - d.tile0) * (u64)TILE;
-                const u32 cnt = tile_cnt(tile);
-                float v[16];
-                u32 mask = 0xFFFFu;
-                if (ahead) {
-#pragma unroll
-                    for (int i = 0; i < 16; i++) v[i] = vn[i];
-                } else {
-                    mask = load_tile(d, e0, cnt, v);
-                }
-                const u32 found = __builtin_amdgcn_readfirstlane(next);
-#pragma unroll
-                for (int i = 0; i < 16; i++)
-                    asm volatile("" : "+v"(v[i])); // the values are taken here, before any store below
-                ahead = tile + 1 < stop && tile_cnt(tile + 1) == (u32)TILE;
-                if (ahead) load_tile_ahead(d, e0 + TILE, vn);
-                next = tile + 1 < stop ? n_prot[(tile + 1) * MAX_FRAC] : 0u;
-                u32 omask, pre[4];
-                GLOBAL_AS unsigned long long *dst = packed + (tile - d.tile0) * (u64)(256u * w);
-                const u32 n_words = (cnt * w + 63u) >> 6;
-                u32 *wcnt = qt.wcnt[buf];
-                // (whole tile or not is the same for every lane: the tile code uses ballots)
-                if (cnt == (u32)TILE)
-                    classify_tile<true, MODE>(qs, tid, v, mask, n_bp, zero_slot, w, dst, n_words, found != 0u, wcnt, omask, pre);
-                else
-                    classify_tile<false, MODE>(qs, tid, v, mask, n_bp, zero_slot, w, dst, n_words, found != 0u, wcnt, omask, pre);
-                if (!found) continue;
+            u32 found = __builtin_amdgcn_readfirstlane(n_prot[tile * MAX_FRAC]);
+            u32 omask, pre[4];
+            float v[16];
+            auto place_protected = [&](u64 e0, const u32 *wcnt) {
                 __syncthreads();
                 buf ^= 1u; // (a wave that writes these counts again has passed the next such barrier)
                 // protected values in ascending index: quarter j, wave, lane, c
@@ -381,6 +362,33 @@ __global__ __launch_bounds__(BLOCK) void k_quant(const TDesc *__restrict__ td, c
                     }
                 }
                 obase += found;
+            };
+            for (; ahead; tile++) { // whole tiles
+                const u64 e0 = (tile - d.tile0) * (u64)TILE;
+#pragma unroll
+                for (int i = 0; i < 16; i++) v[i] = vn[i];
+#pragma unroll
+                for (int i = 0; i < 16; i++)
+                    asm volatile("" : "+v"(v[i])); // the values are taken here, before any store below
+                const u32 next = n_prot[(tile + 1 < stop ? tile + 1 : tile) * MAX_FRAC]; // (asked for before the values)
+                ahead = tile + 1 < stop && tile_cnt(tile + 1) == (u32)TILE;
+                if (ahead) load_tile_ahead(d, e0 + TILE, vn);
+                GLOBAL_AS unsigned long long *dst = packed + (tile - d.tile0) * (u64)(256u * w);
+                u32 *wcnt = qt.wcnt[buf];
+                classify_tile<true, MODE>(qs, tid, v, 0xFFFFu, n_bp, zero_slot, w, dst, 0u, found != 0u, wcnt, omask, pre);
+                if (found)
+                    place_protected(e0, wcnt);
+                else
+                    __syncthreads(); // (only to keep the waves together)
+                found = __builtin_amdgcn_readfirstlane(next);
+            }
+            if (tile < stop) { // the tensor's last, not a whole one
+                const u64 e0 = (tile - d.tile0) * (u64)TILE;
+                const u32 cnt = tile_cnt(tile), mask = load_tile(d, e0, cnt, v);
+                GLOBAL_AS unsigned long long *dst = packed + (tile - d.tile0) * (u64)(256u * w);
+                u32 *wcnt = qt.wcnt[buf];
+                classify_tile<false, MODE>(qs, tid, v, mask, n_bp, zero_slot, w, dst, (cnt * w + 63u) >> 6, found != 0u, wcnt, omask, pre);
+                if (found) place_protected(e0, wcnt);
             }
         };
         if (cells)
