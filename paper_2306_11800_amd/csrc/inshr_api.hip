@@ -1142,6 +1142,7 @@ static int quantize_with_state(inshr_ctx *c, const inshr_config *cfg, inshr_quan
     const uint32_t nB = (uint32_t)c->batch.nB;
     const QuantScratch lay(nT, nB, c->batch.n_wg);
     const size_t o_qd = lay.qd, o_wg = lay.wg, o_un = lay.un, up_bytes = lay.up_bytes;
+    HIPCHK(c, hipStreamSynchronize(c->stream)); // staging buffers and scratch may be in use (inshr_delta)
     int rc = ensure_dev(c, c->aux_mem, lay.bytes);
     if (rc) return rc;
     rc = ensure_host(c, c->h_up, up_bytes);
@@ -1150,7 +1151,6 @@ static int quantize_with_state(inshr_ctx *c, const inshr_config *cfg, inshr_quan
     if (rc) return rc;
     char *db = (char *)c->aux_mem.p;
     QInfo *const qi = (QInfo *)c->h_down.p;
-    HIPCHK(c, hipStreamSynchronize(c->stream)); // staging buffers may be in flight (inshr_delta)
     // Tensors whose boundaries and centres the state does not hold are quantized in one sweep that works them
     // out (launch_fused).  Where that does not do (a protect fraction whose lists are long, or what the
     // kernels find too much for them), and for those the state holds, the ordinary way.
@@ -1417,6 +1417,7 @@ int sketch_with_state(inshr_ctx *c, const inshr_config *cfg, const uint32_t *whi
     const size_t o_sc = cv.take(sizeof(u32) * SK_SLOTS * nT);
     const size_t o_sx = cv.take(sizeof(double) * SK_SLOTS * nT);
     const size_t slot_end = cv.off;
+    HIPCHK(c, hipStreamSynchronize(c->stream)); // the staging buffer may still be in use (inshr_delta)
     int rc = ensure_dev(c, c->sketch_mem, cv.off);
     if (rc) return rc;
     rc = ensure_host(c, c->h_up, upload);
@@ -1424,7 +1425,6 @@ int sketch_with_state(inshr_ctx *c, const inshr_config *cfg, const uint32_t *whi
     rc = ensure_host(c, c->h_down, (sizeof(SketchInfo) + sizeof(SketchChoice)) * nT);
     if (rc) return rc;
     char *hb = (char *)c->h_up.p, *db = (char *)c->sketch_mem.p;
-    HIPCHK(c, hipStreamSynchronize(c->stream)); // the staging buffer may still be in flight
     memcpy(hb + o_cell, T.cell.data(), sizeof(u32) * SK_CELLS);
     memcpy(hb + o_tops, T.tops.data(), sizeof(u32) * n_idx);
     memcpy(hb + o_rep, T.rep.data(), sizeof(double) * n_idx);
@@ -1777,6 +1777,7 @@ int inshr_sketch_quantiles(inshr_ctx *c, const inshr_tensor *tensors, uint32_t n
     const size_t o_nf = cv.take(256);
     const size_t zero_end = cv.off;
     const size_t o_est = cv.take(sizeof(double) * ranks.size());
+    HIPCHK(c, hipStreamSynchronize(c->stream)); // the staging buffer may still be in use (inshr_delta)
     rc = ensure_dev(c, c->sketch_mem, cv.off);
     if (rc) return rc;
     rc = ensure_host(c, c->h_up, upload);
@@ -1784,7 +1785,6 @@ int inshr_sketch_quantiles(inshr_ctx *c, const inshr_tensor *tensors, uint32_t n
     rc = ensure_host(c, c->h_down, sizeof(double) * ranks.size() + 256);
     if (rc) return rc;
     char *hb = (char *)c->h_up.p, *db = (char *)c->sketch_mem.p;
-    HIPCHK(c, hipStreamSynchronize(c->stream)); // the staging buffer may still be in flight
     memcpy(hb + o_cell, T.cell.data(), sizeof(u32) * SK_CELLS);
     memcpy(hb + o_tops, T.tops.data(), sizeof(u32) * n_idx);
     memcpy(hb + o_rep, T.rep.data(), sizeof(double) * n_idx);
@@ -2124,10 +2124,10 @@ int inshr_delta(inshr_ctx *c, const inshr_codes *prev, const uint32_t *const *pr
     const size_t up_bytes = cv.off;
     const size_t o_tt = cv.take(c->scratch_limit ? 0 : parts.bytes());
     const size_t o_ck = cv.take((size_t)chunk * DELTA_SS * 4);
+    // the staging buffer and the scratch may still be in use by an earlier asynchronous delta call
+    HIPCHK(c, hipStreamSynchronize(c->stream));
     int rc = ensure_dev(c, c->aux_mem, cv.off);
     if (rc) return rc;
-    // the staging buffer may still be in flight from an earlier asynchronous delta call
-    HIPCHK(c, hipStreamSynchronize(c->stream));
     rc = ensure_host(c, c->h_up, up_bytes + sizeof(u32) * parts.tensor.size());
     if (rc) return rc;
     rc = take_delta_flags(c); // (of a call whose flags nobody has asked for yet)
@@ -2262,9 +2262,9 @@ int inshr_dequantize(inshr_ctx *c, const inshr_dequant_in *in, float *const *out
     Carver cv;
     const size_t o_rd = cv.take(sizeof(RDesc) * n_tensors);
     const size_t o_one = cv.take(sizeof(u32) * n_tensors); // symbol-1 counts
+    HIPCHK(c, hipStreamSynchronize(c->stream)); // staging buffer and scratch may still be in use (inshr_delta)
     int rc = ensure_dev(c, c->aux_mem, cv.off);
     if (rc) return rc;
-    HIPCHK(c, hipStreamSynchronize(c->stream)); // the staging buffer may still be in flight
     rc = ensure_host(c, c->h_up, o_one);
     if (rc) return rc;
     char *hb = (char *)c->h_up.p, *db = (char *)c->aux_mem.p;
@@ -2342,9 +2342,9 @@ int inshr_reconstruct(inshr_ctx *c, const inshr_codes *prev, const inshr_delta_o
     const size_t o_go = cv.take(sizeof(u64) * (DELTA_SS + 8) * n_tensors); // group offsets from prev
     const size_t o_tt = cv.take(c->scratch_limit ? 0 : parts.bytes());
     const size_t o_ck = cv.take((size_t)chunk * DELTA_SS * 4);
+    HIPCHK(c, hipStreamSynchronize(c->stream)); // staging buffer and scratch may still be in use (inshr_delta)
     int rc = ensure_dev(c, c->aux_mem, cv.off);
     if (rc) return rc;
-    HIPCHK(c, hipStreamSynchronize(c->stream)); // the staging buffer may still be in flight
     rc = ensure_host(c, c->h_up, up_bytes + sizeof(u32) * parts.tensor.size());
     if (rc) return rc;
     char *hb = (char *)c->h_up.p, *db = (char *)c->aux_mem.p;
