@@ -63,24 +63,116 @@ def test_choice_alone(monkeypatch, grid, ordered):
     bare.close()
 
 
+def choose(ctx, ts, g, eps):
+    """A search for its choice alone, and which means it took for what the bounds leave open: one configuration's error by
+    the quantizer's sweep ("one"), one configuration or all of them by the scored search's kernels ("grid")."""
+    ctx.profile(True)
+    best, feasible, _ = ctx.search(ts, g, float(eps), want_scores=False)
+    kernels = ctx.profile_read()
+    ctx.profile(False)
+    return (list(best), list(feasible)), {m for m, k in (("one", "k_fuse_dry"), ("grid", "k_final")) if k in kernels}
+
+
+def check_choice(scored, bare, ts, g, eps, means):
+    best, feasible, _ = scored.search(ts, g, float(eps))
+    got, took = choose(bare, ts, g, eps)
+    assert got == (list(best), list(feasible)) and took == means, (eps, got, took)
+    n = len(g)
+    for cfgs in ([g[b] for b in best], [g[(b + n // 2) % n] for b in best]):
+        same(bare.quantize(ts, cfgs, reuse_search=True), scored.quantize(ts, cfgs, reuse_search=True))
+
+
+@pytest.fixture
+def two_contexts():
+    pair = [api.Context(torch.device("cuda:0")) for _ in range(2)]
+    yield pair
+    for c in pair:
+        c.close()
+
+
+AROUND = (1 - 2e-4, 1 + 2e-4)  # of an error: closer than the bounds are, farther than rounding
+
+
 @pytest.mark.parametrize("n", [16_385, 300_001, 2_500_000])
-def test_choice_that_hangs_on_one_configuration(n):
-    """A bound just above and just below one configuration's error, where a cheaper one may or may not be within it, and
-    where the most accurate one of all may or may not be: the choice of the scored search, and what quantizing gives
-    with it and with another configuration."""
+def test_choice_that_hangs_on_one_configuration(two_contexts, n):
+    """A bound just above and just below the error of a configuration that costs less than all more accurate ones: its
+    error alone is worked out, by the quantizer's sweep.  Among them the most accurate of all, with none to fall back on."""
     g = GRIDS["full"]
     x = dev(family(np.random.default_rng(47), 0, n))
-    scored, bare = api.Context(torch.device("cuda:0")), api.Context(torch.device("cuda:0"))
+    scored, bare = two_contexts
     _, _, sc = scored.search([x], g, synth.EPS_DEFAULT)
-    rel = np.sort([s.sse / s.sumsq for s in sc])
-    for at in (rel[0], rel[20], rel[55]):
-        for eps in (at * (1 - 2e-4), at * (1 + 2e-4)):  # (closer than the bounds are, farther than rounding)
-            want, got = scored.search([x], g, float(eps)), bare.search([x], g, float(eps), want_scores=False)
-            assert (got[0][0], got[1][0]) == (want[0][0], want[1][0]), eps
-            for k in (want[0][0], (want[0][0] + 52) % len(g)):
-                same(bare.quantize([x], [g[k]], reuse_search=True), scored.quantize([x], [g[k]], reuse_search=True))
-    scored.close()
-    bare.close()
+    order = sorted(range(len(g)), key=lambda k: sc[k].sse)
+    hang = [k for i, k in enumerate(order) if all(sc[k].cost_bits < sc[j].cost_bits for j in order[:i])]
+    assert hang[0] == order[0] and len(hang) >= 8
+    for k in hang[::3]:
+        for f in AROUND:
+            check_choice(scored, bare, [x], g, sc[k].sse / sc[k].sumsq * f, {"one"})
+
+
+def crowded(rng, n):
+    """A quarter of the values is one number: a bin that a boundary lies in holds more than one wave of the sweep reads."""
+    y = family(rng, 0, n)
+    y[rng.random(n) < 0.25] = np.float32(0.01)
+    return y
+
+
+@pytest.mark.parametrize("kind,cheap,means", [("long lists", (4, 0, 20_000), {"grid"}), ("crowded bin", (4, 0, 1000), {"one", "grid"}),
+                                              ("crowded bin", (4, 0, 0), {"one", "grid"})])
+def test_choice_that_hangs_on_what_the_sweep_does_not_hold(two_contexts, kind, cheap, means):
+    """More protected values than its lists are made for: not tried.  A bin too full for it: tried, and left to the others."""
+    rng = np.random.default_rng(48)
+    g = [cheap, (8, 0, cheap[2])]
+    x = dev(family(rng, 0, 300_001) if kind == "long lists" else crowded(rng, 400_001))
+    scored, bare = two_contexts
+    _, _, sc = scored.search([x], g, synth.EPS_DEFAULT)
+    for ts in ([x], [x, dev(family(rng, 0, 90_000)), 2 * x]):
+        for f in AROUND:
+            check_choice(scored, bare, ts, g, sc[0].sse / sc[0].sumsq * f, means)
+
+
+def with_tail(ctx, rng, n, g, k, rel):
+    """Values whose relative error with configuration k is rel: a twentieth of them as much larger as it takes."""
+    x = dev(rng.standard_normal(n).astype(np.float32))
+    some = torch.from_numpy(rng.random(n) < 0.05).to("cuda:0")
+    lo, hi = 0.1, 100.0
+    for _ in range(40):
+        s = (lo * hi) ** 0.5
+        y = torch.where(some, x * s, x)
+        _, _, sc = ctx.search([y], g, synth.EPS_DEFAULT)
+        r = sc[k].sse / sc[k].sumsq
+        if abs(r / rel - 1) < 5e-5:
+            return y
+        lo, hi = (s, hi) if r < rel else (lo, s)
+    raise AssertionError((r, rel, s))
+
+
+def test_choices_of_one_call_that_hang_on_different_means(two_contexts):
+    """At one bound: a tensor that the sweep holds, one with a bin too full for it, one that is settled by its bounds, a small
+    one; and a tensor with one configuration open beside one with two (equal errors: a protect fraction that protects none
+    of its values), whose whole grid is scored, which the first one's configuration then joins."""
+    rng = np.random.default_rng(49)
+    scored, bare = two_contexts
+    g = [(4, 0, 1000), (8, 0, 1000)]
+    bad = dev(crowded(rng, 400_001))
+    _, _, sc = scored.search([bad], g, synth.EPS_DEFAULT)
+    rel = sc[0].sse / sc[0].sumsq
+    held = with_tail(scored, rng, 300_001, g, 0, rel)
+    ts = [dev(family(rng, 0, 50_000)), held, dev(family(rng, 0, 700)), bad, 4 * held, 4 * bad]
+    for f in (1 - 4e-4, 1 + 4e-4):
+        check_choice(scored, bare, [held], g, rel * f, {"one"})
+        check_choice(scored, bare, ts, g, rel * f, {"one", "grid"})
+    g = [(4, 0, 0), (4, 0, 2), (8, 0, 0)]
+    one = (rng.standard_normal(2_500_000) * np.where(rng.random(2_500_000) < 0.01, 3.0, 1.0)).astype(np.float32)
+    one[1_000_003] = one[77] = 300.0
+    one = dev(one)
+    _, _, sc = scored.search([one], g, synth.EPS_DEFAULT)
+    rel = sc[1].sse / sc[1].sumsq
+    assert sc[0].sse > 1.1 * sc[1].sse
+    two = with_tail(scored, rng, 300_001, g, 1, rel)
+    for f in (1 - 4e-4, 1 + 4e-4):
+        check_choice(scored, bare, [one], g, rel * f, {"one"})
+        check_choice(scored, bare, [two], g, rel * f, {"grid"})
+        check_choice(scored, bare, [one, two], g, rel * f, {"grid"})
 
 
 def test_shares_of_the_pool_grow_in_the_quantizer(monkeypatch):

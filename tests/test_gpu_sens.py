@@ -206,3 +206,20 @@ def test_scratch_limit(ctx):
     for q, inf, (x, g), b in zip(qs[1:], infos[1:], data, by[1:]):
         check(q, inf, x, g, cfgs[0], b)
     c.close()
+
+
+def test_bins_that_the_sweep_does_not_hold(ctx):
+    """The bins of the values left over are scored by the quantizer's sweep, but for tensors with a bin too full for it
+    (a quarter of one's values is one number), which take the scored search's kernels after it has been tried."""
+    rng = np.random.default_rng(98)
+    data = [make(rng, n) for n in (400_003, 70_001, 5000)]
+    data[0][0][rng.random(400_003) < 0.25] = np.float32(0.01)
+    cfgs = [(4, 0, 1000), (4, 200000, 1000), (8, 0, 1000)]
+    for order in ([0, 1, 2], [1, 2], [0]):
+        ctx.profile(True)
+        qs, info = ctx.quantize_sens([dev(data[k][0]) for k in order], [dev(data[k][1]) for k in order], [cfgs[k] for k in order], [k != 1 for k in order])
+        kernels = ctx.profile_read()
+        ctx.profile(False)
+        assert "k_fuse_dry" in kernels and ("k_final" in kernels) == (0 in order)
+        for k, q, inf in zip(order, qs, info):
+            check(q, inf, *data[k], cfgs[k], k != 1)
