@@ -1203,12 +1203,14 @@ __global__ __launch_bounds__(256) void k_dstatic_setup(DeltaStaticArgs a, DDesc 
     if (tid < a.n_tensors) dd[tid] = a.dd[tid];
     if (tid < (u32)FLAG_WORDS) flags[tid] = 0u;
     for (u32 i = tid; i < n_parts * (u32)SS; i += 256u) totals[i] = 0u;
+    u32 part_of = 0u; // the tensor of part tid
     for (u32 t = 0; t < a.n_tensors; t++) {
         const u64 c0 = a.dd[t].chunk0, c1 = c0 + a.dd[t].n_chunks;
         for (u64 c = c0 + tid; c < c1; c += 256u) chunk_tensor[c] = t;
-        const u32 k = (u32)((a.dd[t].n_chunks + DELTA_PART - 1u) / DELTA_PART);
-        for (u32 i = tid; i < k; i += 256u) part_tensor[a.dd[t].part0 + i] = t;
+        part_of = tid >= a.dd[t].part0 ? t : part_of;
     }
+    static_assert(DST_MAX_PARTS <= 256, "a thread per part");
+    if (tid < n_parts) part_tensor[tid] = part_of;
 }
 
 hipError_t launch_delta_static(int device, const DeltaStaticArgs &a, u64 n_chunks, u64 n_parts, bool any_long,
