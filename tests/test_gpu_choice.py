@@ -63,11 +63,11 @@ def test_choice_alone(monkeypatch, grid, ordered):
     bare.close()
 
 
-def choose(ctx, ts, g, eps):
+def choose(ctx, ts, g, eps, groups=None):
     """A search for its choice alone, and which means it took for what the bounds leave open: one configuration's error by
     the quantizer's sweep ("one"), one configuration or all of them by the scored search's kernels ("grid")."""
     ctx.profile(True)
-    best, feasible, _ = ctx.search(ts, g, float(eps), want_scores=False)
+    best, feasible, _ = ctx.search(ts, g, float(eps), want_scores=False, groups=groups)
     kernels = ctx.profile_read()
     ctx.profile(False)
     return (list(best), list(feasible)), {m for m, k in (("one", "k_fuse_dry"), ("grid", "k_final")) if k in kernels}
@@ -107,6 +107,21 @@ def test_choice_that_hangs_on_one_configuration(two_contexts, n):
     for k in hang[::3]:
         for f in AROUND:
             check_choice(scored, bare, [x], g, sc[k].sse / sc[k].sumsq * f, {"one"})
+
+
+def test_choice_that_hangs_with_shared_thresholds(two_contexts):
+    """The same for tensors whose thresholds are their group's."""
+    rng = np.random.default_rng(52)
+    ts, groups = [dev(family(rng, 0, n)) for n in (300_001, 90_000, 120_001)], [0, 1, 0]
+    g = [(4, 100_000, 0), (8, 100_000, 0)]
+    scored, bare = two_contexts
+    _, _, sc = scored.search(ts, g, synth.EPS_DEFAULT, groups=groups)
+    for t in range(3):
+        for f in AROUND:
+            eps = sc[t * len(g)].sse / sc[t * len(g)].sumsq * f
+            best, feasible, _ = scored.search(ts, g, float(eps), groups=groups)
+            got, took = choose(bare, ts, g, eps, groups)
+            assert got == (list(best), list(feasible)) and "one" in took, (t, eps, took)
 
 
 def crowded(rng, n):
