@@ -17,7 +17,7 @@
 //   k_fprot    protected values: the sweep's lists, one per wave -> the tensor's list in index order
 //   k_fhead    per tensor: centres, boundaries, class counts
 //
-// 6.7 G values, symbols of 9 bits: k_fuse 9.5 ms (27.0 GB read, 8.7 GB written: 3.8 TB/s; bound by vector issue and the
+// 6.7 G values, symbols of 9 bits: k_fuse 9.5 ms (27.0 GB read, 9.3 GB written: 3.8 TB/s; bound by vector issue and the
 // LDS pipe, half of whose time are bank conflicts of the table reads; one workgroup of 16 waves fits a CU.  11.0 when
 // a tile's words were OR-ed together in LDS behind a barrier), k_fsplit 0.34, k_fsel 0.22, k_fpatch 0.41, k_fprot 0.37; boundaries, centres and
 // k_quant for one configuration took 8.7 (k_gather) + 0.6 + 8.9 (k_quant).  100 M values in 48 tensors: 0.25 ms where
